@@ -178,8 +178,8 @@ int adaqp_unpack_dequant_add(const uint8_t *packed_dev, int64_t packed_bytes, co
 int adaqp_spmm_workspace_bytes(int64_t n_rows, int64_t nnz, int32_t dim, int64_t *bytes_out);
 
 /* out[v, 0:dim] = sum_{k = rowptr[v]}^{rowptr[v+1]-1} val[k] * H[col[k], 0:dim]   for v in [row_begin, row_end).
- * fp32 fused multiply-adds; the summation order is fixed by (row range, nnz_range, dim), so repeated calls
- * give bit-identical results.  Rows without entries give zeros.
+ * fp32 fused multiply-adds; the summation order is fixed by (row range, nnz_range, n_cols, dim) and the layout, so
+ * repeated calls give bit-identical results.  Rows without entries give zeros.
  *
  *   rowptr_dev [>= row_end + 1] int64 (non-decreasing), col_dev / val_dev [nnz] int32 / fp32
  *   nnz        length of col_dev and val_dev; no entry index >= nnz is ever read

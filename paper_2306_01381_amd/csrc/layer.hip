@@ -211,13 +211,11 @@ int aggregate_rows(const adaqp_layer_desc *d, bool overlap_part, hipStream_t st)
         return adaqp_spmm_csr_tiled(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, d->feat_dev,
                                     d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo, tile_off,
                                     overlap_part ? d->tile_chunk_overlap : d->tile_chunk_dependent, ws, wsb, st);
-    if (!overlap_part && fused_receive(d))
-        return adaqp_spmm_csr_packed(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, nz, d->feat_dev,
-                                     d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo, d->slot_of_row_dev,
-                                     d->recv_packed_dev, d->packed_bytes, d->recv_params_dev, d->bits_dev,
-                                     d->row_offset_dev, d->n_send, ws, wsb, st);
-    return adaqp_spmm_csr(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, nz, d->feat_dev,
-                          d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo, ws, wsb, st);
+    const bool fused = !overlap_part && fused_receive(d);
+    return spmm_rows(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, nz, d->feat_dev, d->n_feat_rows, d->ld, d->dim,
+                     d->out_dev, d->ldo, fused ? d->slot_of_row_dev : nullptr, d->recv_packed_dev, d->packed_bytes,
+                     d->recv_params_dev, d->bits_dev, d->row_offset_dev, d->n_send, ws, wsb, st,
+                     d->direction == ADAQP_BACKWARD);
 }
 
 bool has_panels(const adaqp_layer_desc *d, bool overlap_part)

@@ -14,40 +14,17 @@
 // A second, tiny kernel adds the carries of each split row in piece order.  The summation order therefore
 // depends only on the launch geometry: results are bit-identical from run to run and across schedules.
 //
+// Line-padded operands take the kernel of spmm_sliced.hip instead (same path, feature columns sliced over the XCDs); this
+// one serves every other layout, and matrices too large for that kernel's 32-bit offsets.
+//
 // The kernel is a gather: per entry it reads 8 bytes of (col, alpha) and 4*dim bytes of H.  It is bound by
 // how fast H rows come out of L2 / Infinity Cache / HBM, not by arithmetic, so there is no MFMA use.
 #include <mutex>
 
-#include "common.hpp"
+#include "spmm_common.hpp"
 
 namespace adaqp {
 namespace {
-
-struct SpmmArgs {
-    const int64_t *rowptr;      // already offset: rowptr[0] is the start of the first row of the range
-    const int32_t *col;
-    const float *val;
-    int64_t nnz;                // capacity of col / val
-    int32_t n_rows;             // rows in the range
-    const float *H;
-    int64_t n_cols, ldh;
-    int32_t dim, wdim;          // wdim >= dim: columns [dim, wdim) of a written row receive zeros (whole lines)
-    float *out;                 // already offset to the first row of the range
-    int64_t ldo;
-    int32_t *carry_row;         // [n_items]
-    float *carry;               // [n_items, carry_ld]
-    int64_t carry_ld;
-    int32_t n_items;
-    // optional: rows of H that are still packed (received halo rows, de-quantised on the fly)
-    const int32_t *slot_of_row; // [n_cols], -1 = read the row from H
-    const uint8_t *packed;
-    int64_t packed_bytes;
-    const float *params;
-    const uint8_t *bits;
-    const int64_t *row_offset;
-    int64_t n_slots;
-    int32_t col0, full_dim;     // first column of this launch's chunk and the row length of the packed layout
-};
 
 template <int VW> struct VecOf;
 template <> struct VecOf<1> { using type = float; };
@@ -82,8 +59,6 @@ __device__ __forceinline__ void store_vec_streaming(float *p, const float *src)
     for (int k = 0; k < VW; ++k) v[k] = src[k];
     __builtin_nontemporal_store(v, reinterpret_cast<vec_t *>(p));
 }
-
-__device__ __forceinline__ int64_t clamp64(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 __device__ __forceinline__ int32_t uniform_i32(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -392,8 +367,9 @@ bool geometry(int64_t n_rows, int64_t nnz, int32_t dim, Geometry *g)
     // and the carry are amortised
     int64_t per = 32;
     while (per < 512 && total / per > 65536) per *= 2;
-    const int64_t items = (total + per - 1) / per;
+    int64_t items = (total + per - 1) / per;
     if (items > (int64_t)1 << 30) return false;
+    if (items < kWavesPerBlock) items = kWavesPerBlock;     // the sliced kernel cuts a workgroup's share into four
     g->n_items = (int32_t)items;
     g->carry_ld = ((int64_t)dim + 31) / 32 * 32;
     g->carry_off = (items * 4 + 255) / 256 * 256;
@@ -429,6 +405,19 @@ hipError_t launch_merge_nv(const SpmmArgs &a, int nv, dim3 grid, hipStream_t st)
     }
 }
 
+hipError_t launch_carry_nv(const SpmmArgs &a, int nv, hipStream_t st)
+{
+    const dim3 grid((unsigned)((a.n_items + kWavesPerBlock - 1) / kWavesPerBlock));
+    switch (nv) {
+#define ADAQP_CASE(N) case N: hipLaunchKernelGGL((spmm_carry_kernel<4, N>), grid, dim3(kBlock), 0, st, a); break;
+        ADAQP_CASE(1) ADAQP_CASE(2) ADAQP_CASE(3) ADAQP_CASE(4)
+        ADAQP_CASE(5) ADAQP_CASE(6) ADAQP_CASE(7) ADAQP_CASE(8)
+#undef ADAQP_CASE
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
 }  // namespace adaqp
 
@@ -462,6 +451,20 @@ extern "C" int adaqp_spmm_csr_packed(const int64_t *rowptr_dev, const int32_t *c
                                      const float *params_dev, const uint8_t *bits_dev, const int64_t *row_offset_dev,
                                      int64_t n_slots,
                                      void *workspace_dev, int64_t workspace_bytes, void *stream)
+{
+    return spmm_rows(rowptr_dev, col_dev, val_dev, nnz, row_begin, row_end, nnz_range, H_dev, n_cols, ldh, dim, out_dev, ldo,
+                     slot_of_row_dev, packed_dev, packed_bytes, params_dev, bits_dev, row_offset_dev, n_slots,
+                     workspace_dev, workspace_bytes, stream, false);
+}
+
+int adaqp::spmm_rows(const int64_t *rowptr_dev, const int32_t *col_dev, const float *val_dev,
+                     int64_t nnz, int64_t row_begin, int64_t row_end, int64_t nnz_range,
+                     const float *H_dev, int64_t n_cols, int64_t ldh, int32_t dim,
+                     float *out_dev, int64_t ldo,
+                     const int32_t *slot_of_row_dev, const uint8_t *packed_dev, int64_t packed_bytes,
+                     const float *params_dev, const uint8_t *bits_dev, const int64_t *row_offset_dev,
+                     int64_t n_slots,
+                     void *workspace_dev, int64_t workspace_bytes, void *stream, bool skewed_columns)
 {
     if (slot_of_row_dev) {
         if (!packed_dev || !params_dev || !bits_dev || !row_offset_dev || packed_bytes < 4 || n_slots <= 0)
@@ -529,7 +532,10 @@ extern "C" int adaqp_spmm_csr_packed(const int64_t *rowptr_dev, const int32_t *c
         const int nv = (a.wdim + kWave * vw - 1) / (kWave * vw);
         const dim3 grid((unsigned)((g.n_items + kWavesPerBlock - 1) / kWavesPerBlock));
         hipError_t err;
-        if (vw == 4) err = launch_merge_nv<4>(a, nv, grid, st);
+        if (whole_lines && sliced_fits(a)) {
+            err = launch_sliced(a, nnz_range, skewed_columns, st, &a.n_items);
+            if (err == hipSuccess) err = launch_carry_nv(a, nv, st);
+        } else if (vw == 4) err = launch_merge_nv<4>(a, nv, grid, st);
         else if (vw == 2) err = launch_merge_nv<2>(a, nv, grid, st);
         else err = launch_merge_nv<1>(a, nv, grid, st);
         ADAQP_HIP_TRY(err);

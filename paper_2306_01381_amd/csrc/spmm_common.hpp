@@ -1,0 +1,43 @@
+// Shared by the aggregation kernels of spmm.hip and spmm_sliced.hip: the launch arguments and small device helpers.
+#pragma once
+
+#include <type_traits>
+
+#include "common.hpp"
+
+namespace adaqp {
+
+struct SpmmArgs {
+    const int64_t *rowptr;      // already offset: rowptr[0] is the start of the first row of the range
+    const int32_t *col;
+    const float *val;
+    int64_t nnz;                // capacity of col / val
+    int32_t n_rows;             // rows in the range
+    const float *H;
+    int64_t n_cols, ldh;
+    int32_t dim, wdim;          // wdim >= dim: columns [dim, wdim) of a written row receive zeros (whole lines)
+    float *out;                 // already offset to the first row of the range
+    int64_t ldo;
+    int32_t *carry_row;         // [n_items]
+    float *carry;               // [n_items, carry_ld]
+    int64_t carry_ld;
+    int32_t n_items;
+    // optional: rows of H that are still packed (received halo rows, de-quantised on the fly)
+    const int32_t *slot_of_row; // [n_cols], -1 = read the row from H
+    const uint8_t *packed;
+    int64_t packed_bytes;
+    const float *params;
+    const uint8_t *bits;
+    const int64_t *row_offset;
+    int64_t n_slots;
+    int32_t col0, full_dim;     // first column of this launch's chunk and the row length of the packed layout
+};
+
+__device__ __forceinline__ int64_t clamp64(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
+
+// The rows of a range with the feature columns sliced over the XCDs (spmm_sliced.hip): whole-line layout, operands
+// that sliced_fits.  nnz_hint sizes the launch.  Uses a.n_items carry slots at most; writes how many are in use.
+bool sliced_fits(const SpmmArgs &a);
+hipError_t launch_sliced(const SpmmArgs &a, int64_t nnz_hint, bool skewed_columns, hipStream_t st, int32_t *n_carries_out);
+
+}  // namespace adaqp

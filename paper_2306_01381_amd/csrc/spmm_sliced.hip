@@ -1,0 +1,482 @@
+// Neighbour aggregation (Sec. 2.1 Eq. 3) on the line-padded layout, with the feature columns sliced over the XCDs.
+//
+// The gather is bound by what comes from behind the L2s: rows of H are drawn from a power law with no locality, every
+// XCD has a private 4 MB L2, and when all eight walk whole rows (1 KB and more) each holds the same few thousand
+// popular rows.  Here an XCD walks the graph for ITS share of the feature columns only, a slice of VPL 128-byte lines
+// of every row at a time: its L2 then holds one line of 32 768 rows (two of 16 384) instead of eight or more lines of
+// 4 000, the L2s hold different data, and no line of H is fetched behind two of them.  The price is that the entries
+// (8 bytes each) are read once per slice.
+//
+// Work split: a wave walks a contiguous share of the merge path of row ends and entries (as in spmm.hip).  Its entries
+// go through LDS 8 at a time: one load instruction per line fetches the lines of 8 consecutive entries, a lane holding
+// four columns of one of them, and kAhead such steps are in flight at any time, across row ends and across the chunks
+// in which entries are staged.  A step in which no row ends costs one LDS read, one add and 4 multiply-adds per line;
+// where a row ends, the products of the groups before the end are added to the row's sums, these are added across the
+// eight groups (halving the registers at each level) and stored, and the products after it start the next row.  The row
+// a share begins in is finished by the carry kernel, from the part that the share before it left.  The summation
+// order depends on the launch geometry only.
+//
+// Bound: what a slice misses in its L2 (7-8 TB/s behind the L2s), and where it fits, the rate at which a CU takes 16-byte
+// gathers (32 TB/s over the chip for bare loads out of L2; this loop 25-28).  Measured against the merge-path kernel
+// walking whole rows (aggregation of all rows, before -> after): 50 000 x 30 000, 4 M entries, 128 columns 0.239 ->
+// 0.096 ms; 34 000 columns, 0.42 M entries, 66 columns 0.050 -> 0.027; 376 000 x 196 000, 16.2 M entries, 256 columns
+// (transposed graph) 0.96 -> 0.80; 306 000 x 456 000, 7.7 M entries, 256 columns 1.13 -> 1.07; 179 000 x 269 000, 2 M
+// entries, 300 columns 0.386 -> 0.361.  Tried on the way: a piece of the path per group of eight lanes (every row end
+// then stops seven other rows), steps padded to row ends (a third of the gather slots fetch nothing), and repeating an
+// entry in idle slots instead of an offset outside the buffer (the L1 stalls on a line that is already on its way).
+#include <algorithm>
+
+#include "spmm_common.hpp"
+
+namespace adaqp {
+namespace {
+
+constexpr int kXcds = 8;
+constexpr int64_t kColumnsForFour = 49152, kRowsForFour = 8;   // see launch_sliced
+constexpr int64_t kWorkgroups = 512, kMinPath = 1024;
+constexpr int kStep = 8;                            // entries of a step = groups of a wave
+constexpr int kGroup = kWave / kStep;               // lanes per entry: 8 x 16 bytes = one line
+constexpr int kLine = 32;                           // columns per line
+constexpr int kPer = 6;                             // entries a lane stages per chunk
+constexpr int kChunk = kPer * kWave;                // entries of a chunk: a whole number of rings for every VPL
+constexpr int kEnds = kWave - 1;                    // row ends of a chunk at most
+constexpr int32_t kNoEnd = 0x10000;                 // lies after every step of a chunk
+constexpr int kRowSteps = 8;                        // entries a row end counts for where shares are cut
+constexpr uint32_t kOutside = 0xFFFFFF00u;          // past the end of any buffer the kernel is launched with
+constexpr int kNonTemporal = 2;                     // cache policy bits of a buffer load: nt
+constexpr int kRawBuffer = 0x00020000;              // buffer resource, last word: raw 32-bit data, no swizzle
+
+struct SlicedArgs {
+    SpmmArgs s;
+    int32_t n_blocks;           // workgroups per slice, kWavesPerBlock shares each
+    int32_t lines;              // lines of a row
+};
+
+typedef float float4_t __attribute__((ext_vector_type(4)));
+
+// An entry in LDS: byte offset of its row of H and its coefficient.  PACKED: bits 0-1 of the offset name the width of
+// a row that is still packed (1, 2, 3: 2, 4, 8 bits; the offset is then one into the receive buffer) and (Z, S) follow.
+template <bool PACKED> struct Entry;
+template <> struct alignas(8) Entry<false> { uint32_t off; float val; };
+template <> struct alignas(16) Entry<true> { uint32_t off; float val; float z, s; };
+
+__device__ __forceinline__ int64_t readlane_i64(int64_t v, int lane_id)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)v, lane_id);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)((uint64_t)v >> 32), lane_id);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+template <int U, int N, typename F>
+__device__ __forceinline__ void unroll(F &&f)
+{
+    if constexpr (U < N) {
+        f(std::integral_constant<int, U>());
+        unroll<U + 1, N>(f);
+    }
+}
+
+// Row ends before two diagonals of the merge path: row end p precedes d iff end_p + kRowSteps * (p + 1) <= d.  256-ary
+// search by a whole wave; wave-uniform results.
+__device__ void split_rows2(const SpmmArgs &a, const int64_t (&d)[2], int64_t base, int64_t nnz_r, int lane, int32_t (&at)[2])
+{
+    constexpr int K = 4;
+    int32_t lo[2], hi[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int64_t least = d[q] - nnz_r > 0 ? (d[q] - nnz_r) / kRowSteps : 0, most = d[q] / kRowSteps;
+        hi[q] = (int32_t)(most < a.n_rows ? most : a.n_rows);
+        lo[q] = (int32_t)(least < hi[q] ? least : hi[q]);
+    }
+    while (lo[0] < hi[0] || lo[1] < hi[1]) {
+        bool before[2][K];
+        int32_t step[2], probes[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int32_t n = hi[q] - lo[q];
+            step[q] = (n + K * kWave - 1) / (K * kWave);
+            probes[q] = n > 0 ? (n + step[q] - 1) / step[q] : 0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int32_t i = k * kWave + lane;
+                before[q][k] = false;
+                if (i < probes[q]) {
+                    const int64_t p = (int64_t)lo[q] + (int64_t)i * step[q];
+                    before[q][k] = clamp64(a.rowptr[p + 1], base, base + nnz_r) - base + kRowSteps * (p + 1) <= d[q];
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            int32_t cnt = 0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) cnt += __popcll(__ballot(before[q][k]));
+            const int32_t new_lo = cnt > 0 ? lo[q] + (cnt - 1) * step[q] + 1 : lo[q];
+            const int32_t new_hi = cnt < probes[q] ? lo[q] + cnt * step[q] : hi[q];
+            lo[q] = new_lo;
+            hi[q] = new_hi;
+        }
+    }
+    at[0] = __builtin_amdgcn_readfirstlane(lo[0]);
+    at[1] = __builtin_amdgcn_readfirstlane(lo[1]);
+}
+
+// x and y hold two values per lane for two halves of the wave (HALF = 32) or of each half (16): afterwards a lane of the
+// lower half holds the sum of both halves' x, a lane of the upper half that of both halves' y.
+template <int HALF>
+__device__ __forceinline__ float fold(float x, float y)
+{
+    typedef unsigned pair_t __attribute__((ext_vector_type(2)));
+    const uint32_t ux = __builtin_bit_cast(uint32_t, x), uy = __builtin_bit_cast(uint32_t, y);
+    pair_t r;
+    if constexpr (HALF == 32) r = __builtin_bit_cast(pair_t, __builtin_amdgcn_permlane32_swap(ux, uy, false, false));
+    else                      r = __builtin_bit_cast(pair_t, __builtin_amdgcn_permlane16_swap(ux, uy, false, false));
+    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+
+__device__ __forceinline__ float ror8(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int32_t, v), 0x128, 0xF, 0xF, false));
+}
+
+// One wave's share of the path for one slice of VPL lines.
+template <int VPL, bool PACKED>
+__device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const int32_t item, Entry<PACKED> (*stages)[kChunk])
+{
+    constexpr int kAhead = VPL >= 3 ? 2 : 8 / VPL;          // steps in flight: 6 to 8 KB per wave
+    constexpr int kRing = kAhead * kStep;                   // entries of a turn of the ring
+    static_assert(kChunk % kRing == 0, "a chunk is a whole number of turns");
+    const SpmmArgs &a = sa.s;
+    const int lane = threadIdx.x & (kWave - 1), gl = lane & (kGroup - 1), grp = lane / kGroup;
+
+    // extent of the range on the device: the host only sized the launch
+    const int64_t base = clamp64(a.rowptr[0], 0, a.nnz);
+    const int64_t nnz_r = clamp64(a.rowptr[a.n_rows], base, a.nnz) - base;
+    const int64_t total = (int64_t)a.n_rows * kRowSteps + nnz_r;
+    const int64_t n_items = (int64_t)sa.n_blocks * kWavesPerBlock;
+    const int64_t per = (total + n_items - 1) / n_items;
+    int64_t d[2];
+    d[0] = item * per < total ? item * per : total;
+    d[1] = d[0] + per < total ? d[0] + per : total;
+    int32_t i[2];
+    split_rows2(a, d, base, nnz_r, lane, i);
+    int64_t j[2];                                           // entries before a diagonal: those of the open row up to it,
+#pragma unroll                                              // none of the weight of its end
+    for (int q = 0; q < 2; ++q) {
+        const int64_t end = i[q] < a.n_rows ? clamp64(a.rowptr[(int64_t)i[q] + 1], base, base + nnz_r) - base : nnz_r;
+        j[q] = clamp64(d[q] - (int64_t)kRowSteps * i[q], 0, end);
+    }
+    if (j[1] < j[0]) j[1] = j[0];
+
+    const int32_t c0 = first_line * kLine + gl * 4;         // first column of the lane's line 0
+    // one buffer per line of the slice
+    __amdgpu_buffer_rsrc_t rows[VPL];
+#pragma unroll
+    for (int v = 0; v < VPL; ++v)
+        rows[v] = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float *>(a.H + (first_line + v) * kLine), 0,
+            (int)(uint32_t)(a.n_cols * a.ldh * 4 - (first_line + v) * kLine * 4), kRawBuffer);
+    const auto packed_rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.packed), 0,
+                                                               (int)(uint32_t)a.packed_bytes, kRawBuffer);
+    const uint32_t lane_off = gl * 16;
+    const uint32_t pitch = (uint32_t)a.ldh * 4u;
+
+    // After `sum_groups` lane l (and lane l + 32) holds column l of each line.
+    const int line_col = lane & (kLine - 1);
+    const int from_lane = ((line_col & 3) * 16 + line_col / 4) << 2;
+    auto sum_groups = [&](const float4_t (&acc)[VPL], float (&out)[VPL]) {
+#pragma unroll
+        for (int v = 0; v < VPL; ++v) {
+            const float lo = fold<32>(acc[v][0], acc[v][2]), hi = fold<32>(acc[v][1], acc[v][3]);
+            float x = fold<16>(lo, hi);                     // row q of 16 lanes: column 4 * gl + q, twice
+            x = x + ror8(x);
+            out[v] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(from_lane, __builtin_bit_cast(int32_t, x)));
+        }
+    };
+
+    // The share is walked in chunks of up to kChunk entries and kEnds row ends.  What a chunk needs from memory is
+    // requested one chunk ahead and waits in registers: bounds of rows, one per lane, and entries.
+    struct Chunk {
+        int32_t row0, n_end, n_ent;                         // first row, row ends, entries
+        int64_t ent0;                                       // first entry
+        int32_t ends;                                       // lane l: where row row0 + l ends in the chunk, else kNoEnd
+    };
+    int64_t r_hi;
+    auto request_rows = [&](int32_t row) {
+        const int64_t r = (int64_t)row + lane + 1;
+        r_hi = a.rowptr[r < a.n_rows ? r : a.n_rows];
+    };
+    auto take = [&](int32_t row0, int64_t ent0) {           // from r_hi, requested for row0
+        Chunk c;
+        c.row0 = row0;
+        c.ent0 = ent0;
+        const int64_t end = clamp64(clamp64(r_hi, base, base + nnz_r) - base - ent0, 0, kNoEnd);
+        c.ends = (int32_t)end;
+        const int64_t left = j[1] - ent0;
+        c.n_ent = (int32_t)(left < kChunk ? left : kChunk);
+        c.n_end = __popcll(__ballot(lane < kEnds && row0 + lane < i[1] && c.ends <= c.n_ent));
+        if (c.n_end == kEnds) c.n_ent = min(c.n_ent, __builtin_amdgcn_readlane(c.ends, kEnds - 1));
+        if (lane >= c.n_end) c.ends = kNoEnd;
+        return c;
+    };
+    int32_t st_col[kPer];
+    float st_val[kPer];
+    auto request_entries = [&](const Chunk &c) {            // past the chunk's entries: zeros
+        const auto cols = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.col + base + c.ent0), 0, c.n_ent * 4, kRawBuffer);
+        const auto vals = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.val + base + c.ent0), 0, c.n_ent * 4, kRawBuffer);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {                    // streamed: keep the caches for H
+            st_col[k] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(cols, lane * 4, k * kWave * 4, kNonTemporal);
+            st_val[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vals, lane * 4, k * kWave * 4, kNonTemporal));
+        }
+    };
+    auto stage = [&](const Chunk &c, Entry<PACKED> *ent) {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int32_t col = st_col[k];
+            const bool ok = k * kWave + lane < c.n_ent && col >= 0 && col < a.n_cols;       // else: fetches nothing
+            Entry<PACKED> en = {};
+            en.off = ok ? (uint32_t)col * pitch : kOutside;
+            en.val = ok ? st_val[k] : 0.0f;
+            if constexpr (PACKED) {
+                if (ok) {
+                    const int32_t slot = a.slot_of_row[col];
+                    if (slot >= 0 && slot < a.n_slots) {
+                        const int32_t b = a.bits[slot];
+                        const int64_t off = a.row_offset[slot];
+                        const int64_t stride = 4 * (((int64_t)a.full_dim * b + 31) >> 5);
+                        if ((b == 2 || b == 4 || b == 8) && off >= 0 && (off & 3) == 0 && off + stride <= a.packed_bytes) {
+                            const float2 zs = *reinterpret_cast<const float2 *>(a.params + 2 * (int64_t)slot);
+                            en.off = (uint32_t)off | (b == 2 ? 1u : (b == 4 ? 2u : 3u));
+                            en.z = zs.x;
+                            en.s = zs.y;
+                        }                                   // else: fall back to the row in H
+                    }
+                }
+            }
+            ent[k * kWave + lane] = en;
+        }
+    };
+
+    // the ring: kAhead steps whose lines are on their way
+    float4_t h[kAhead][VPL];
+    uint32_t words[kAhead][VPL];
+    Entry<PACKED> in_flight[kAhead];
+    auto fetch = [&](auto tag, const Entry<PACKED> &en) {
+        constexpr int U = decltype(tag)::value;
+        in_flight[U] = en;
+        uint32_t off = en.off + lane_off;
+        const uint32_t w = PACKED ? en.off & 3u : 0u;
+        if (PACKED && w != 0) off = kOutside;
+#pragma unroll
+        for (int v = 0; v < VPL; ++v) {
+            h[U][v] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(rows[v], (int)off, 0, 0));
+            if constexpr (PACKED) {
+                // one 32-bit word holds the four codes of a lane (4 * b <= 32 and divides 32)
+                const uint32_t last_word = (((uint32_t)a.full_dim << w) - 1) >> 5;
+                const uint32_t word = ((uint32_t)(a.col0 + c0 + v * kLine) << w) >> 5;
+                words[U][v] = __builtin_amdgcn_raw_buffer_load_b32(
+                    packed_rows, w != 0 ? (int)((en.off & ~3u) + 4 * min(word, last_word)) : (int)kOutside, 0, 0);
+            }
+        }
+    };
+    auto neighbour = [&](auto tag, int v) {                 // the four columns a lane fetched
+        constexpr int U = decltype(tag)::value;
+        float4_t x = h[U][v];
+        if constexpr (PACKED) {
+            const uint32_t w = in_flight[U].off & 3u;
+            if (w != 0) {
+                const uint32_t b = 1u << w, mask = (1u << b) - 1u;
+                const uint32_t word = words[U][v] >> (((uint32_t)(a.col0 + c0 + v * kLine) << w) & 31u);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float scaled = (float)((word >> (k * b)) & mask) * in_flight[U].s;    // Eq. 5: product rounded,
+                    x[k] = scaled + in_flight[U].z;                                             // then sum rounded
+                }
+            }
+        }
+        return x;
+    };
+
+    float4_t acc[VPL];
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    float *out_row = a.out + (int64_t)i[0] * a.ldo;         // the rows of a share end one after the other
+    auto finish_row = [&]() {
+        float sum[VPL];
+        sum_groups(acc, sum);
+#pragma unroll
+        for (int v = 0; v < VPL; ++v) {
+            const int32_t c = (first_line + v) * kLine + line_col;
+            if (lane < kLine) __builtin_nontemporal_store(c < a.dim ? sum[v] : 0.0f, out_row + (uint32_t)c);
+            acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        out_row += a.ldo;
+    };
+
+    request_rows(i[0]);
+    Chunk cur = take(i[0], j[0]);
+    request_entries(cur);
+    request_rows(cur.row0 + cur.n_end);
+    int buf = 0;
+    stage(cur, stages[0]);
+    unroll<0, kAhead>([&](auto tag) {
+        fetch(tag, stages[0][decltype(tag)::value * kStep + grp]);
+        __builtin_amdgcn_sched_barrier(0);                  // the order of issue is the order of use
+    });
+    for (;;) {
+        const int32_t next_row = cur.row0 + cur.n_end;
+        const int64_t next_ent = cur.ent0 + cur.n_ent;
+        Chunk next = take(next_row, next_ent);
+        const bool more = next.n_end > 0 || next.n_ent > 0;
+        if (more) {
+            request_entries(next);
+            request_rows(next.row0 + next.n_end);
+        }
+        int32_t e = 0, end = __builtin_amdgcn_readlane(cur.ends, 0);       // next row end
+        while (end == 0) {                                  // ends that belong to what the chunks before have added up
+            finish_row();
+            end = __builtin_amdgcn_readlane(cur.ends, ++e);
+        }
+        const int32_t turns = cur.n_ent > 0 ? (cur.n_ent + kRing - 1) / kRing : 1;
+        for (int32_t t = 0; t < turns; ++t) {
+            const Entry<PACKED> *src = stages[buf] + (t + 1) * kRing + grp;
+            if (t + 1 == turns) {                           // the ring goes on in the next chunk
+                if (more) stage(next, stages[buf ^ 1]);
+                else if (lane < kRing) stages[buf ^ 1][lane] = Entry<PACKED>{kOutside, 0.0f};
+                src = stages[buf ^ 1] + grp;
+            }
+            Entry<PACKED> en = src[0];
+            unroll<0, kAhead>([&](auto tag) {
+                constexpr int U = decltype(tag)::value;
+                const Entry<PACKED> now = en;
+                if (U + 1 < kAhead) en = src[(U + 1) * kStep];
+                __builtin_amdgcn_sched_barrier(0);
+                const int32_t rel = end - t * kRing - U * kStep;        // where in this step a row ends
+                if (rel > kStep) {
+#pragma unroll
+                    for (int v = 0; v < VPL; ++v) {
+                        const float4_t x = neighbour(tag, v);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) acc[v][k] = fmaf(in_flight[U].val, x[k], acc[v][k]);
+                    }
+                } else {
+                    // the groups from the last end to this one belong to the row that ends here
+                    int32_t from = 0, to = rel;
+                    do {
+                        const bool mine = grp >= from && grp < to;
+#pragma unroll
+                        for (int v = 0; v < VPL; ++v) {
+                            const float4_t x = neighbour(tag, v);
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const float sum = fmaf(in_flight[U].val, x[k], acc[v][k]);
+                                acc[v][k] = mine ? sum : acc[v][k];
+                            }
+                        }
+                        finish_row();
+                        end = __builtin_amdgcn_readlane(cur.ends, ++e);
+                        from = to;
+                        to = end - t * kRing - U * kStep;
+                    } while (to <= kStep);
+#pragma unroll
+                    for (int v = 0; v < VPL; ++v) {
+                        const float4_t x = neighbour(tag, v);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) acc[v][k] = grp >= from ? in_flight[U].val * x[k] : 0.0f;
+                    }
+                }
+                fetch(tag, now);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+        if (!more) break;
+        cur = next;
+        buf ^= 1;
+    }
+    // what is left belongs to a row that goes on in the next wave's share
+    const int64_t began = i[1] < a.n_rows ? clamp64(a.rowptr[i[1]], base, base + nnz_r) - base : nnz_r;
+    const bool held = i[1] < a.n_rows && j[1] > (began > j[0] ? began : j[0]);
+    if (held) {
+        float sum[VPL];
+        sum_groups(acc, sum);
+#pragma unroll
+        for (int v = 0; v < VPL; ++v)
+            if (lane < kLine) a.carry[(int64_t)item * a.carry_ld + (first_line + v) * kLine + line_col] = sum[v];
+    }
+    if (first_line == 0 && lane == 0) a.carry_row[item] = held ? i[1] : -1;
+}
+
+template <int VPL, bool PACKED>
+__global__ __launch_bounds__(kBlock, 2) void spmm_sliced_kernel(const SlicedArgs sa)
+{
+    __shared__ Entry<PACKED> stages[kWavesPerBlock][2][kChunk];
+    // Tasks in slice-major order; consecutive workgroups land on consecutive XCDs, an XCD takes a run of tasks that adds up
+    // to an eighth of all lines (the last slice may be narrower than the others).
+    const int64_t full = sa.lines / VPL * (int64_t)sa.n_blocks, rest = sa.lines % VPL;       // tasks of whole slices
+    auto task_at = [&](int64_t line) -> int64_t {           // first task that begins at or after this many lines
+        if (line <= full * VPL || rest == 0) return (line + VPL - 1) / VPL;
+        return full + (line - full * VPL + rest - 1) / rest;
+    };
+    const int64_t all = (int64_t)sa.lines * sa.n_blocks;
+    const uint32_t xcd = blockIdx.x % kXcds;
+    const int64_t task = task_at(all * xcd / kXcds) + blockIdx.x / kXcds;
+    if (task >= task_at(all * (xcd + 1) / kXcds)) return;
+    const int32_t slice = (int32_t)(task / sa.n_blocks), blk = (int32_t)(task % sa.n_blocks);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int32_t item = blk * kWavesPerBlock + wave;
+    const int live = min(VPL, sa.lines - slice * VPL);
+    if (live == VPL) walk_share<VPL, PACKED>(sa, slice * VPL, item, stages[wave]);
+    else if (VPL > 3 && live == 3) walk_share<3, PACKED>(sa, slice * VPL, item, stages[wave]);
+    else if (VPL > 2 && live == 2) walk_share<2, PACKED>(sa, slice * VPL, item, stages[wave]);
+    else walk_share<1, PACKED>(sa, slice * VPL, item, stages[wave]);
+}
+
+}  // namespace
+
+bool sliced_fits(const SpmmArgs &a)
+{
+    // offsets of rows of H and of packed rows are kept in 32 bits
+    const int64_t limit = (int64_t)kOutside;
+    return a.n_cols <= INT32_MAX && a.ldh < limit / 4 && a.n_cols * a.ldh < limit / 4 && (!a.slot_of_row || a.packed_bytes < limit) &&
+           a.full_dim < (1 << 28);
+}
+
+hipError_t launch_sliced(const SpmmArgs &a, int64_t nnz_hint, bool skewed_columns, hipStream_t st, int32_t *n_carries_out)
+{
+    SlicedArgs sa;
+    sa.s = a;
+    sa.lines = a.wdim / kLine;
+    // Lines per slice.  Four cost the least per line: one LDS read, one address and one row end serve four loads.  Two keep
+    // twice as many rows in an L2, which pays where the columns neither fit nor are few of them used most of the time.
+    // Rows of a few entries spend their time on row ends: four again.
+    int vpl = a.n_cols <= kColumnsForFour || skewed_columns || nnz_hint < kRowsForFour * (int64_t)a.n_rows ? 4 : 2;
+    if (sa.lines < vpl) vpl = sa.lines >= 3 ? 4 : sa.lines;
+    const int64_t slices = (sa.lines + vpl - 1) / vpl;
+    const int64_t path = nnz_hint + (int64_t)a.n_rows * kRowSteps;
+    // two workgroups per CU, each with one share per wave: fewer and longer shares measured faster than more of them
+    // (16 M entries, 256 columns, 4 lines per slice: 0.85 ms with 512 workgroups, 0.91 with 4096), but a wave's share is
+    // at least 256 steps of the path
+    int64_t n_blocks = kWorkgroups / slices;
+    n_blocks = std::min(n_blocks, (path + kMinPath - 1) / kMinPath);
+    if (n_blocks > a.n_items / kWavesPerBlock) n_blocks = a.n_items / kWavesPerBlock;      // one carry slot per share
+    if (n_blocks < 1) n_blocks = 1;
+    sa.n_blocks = (int32_t)n_blocks;
+    // workgroups per XCD: the narrowest slice decides how many tasks an eighth of the lines can be
+    const int64_t narrow = sa.lines % vpl ? sa.lines % vpl : vpl;
+    const int64_t per_xcd = std::min(n_blocks * slices, (n_blocks * sa.lines / kXcds + 1) / narrow + 2);
+    const dim3 grid((unsigned)(per_xcd * kXcds));
+#define ADAQP_SLICED(V)                                                                                          \
+    do {                                                                                                         \
+        if (a.slot_of_row) hipLaunchKernelGGL((spmm_sliced_kernel<V, true>), grid, dim3(kBlock), 0, st, sa);     \
+        else hipLaunchKernelGGL((spmm_sliced_kernel<V, false>), grid, dim3(kBlock), 0, st, sa);                  \
+    } while (0)
+    if (vpl == 1) ADAQP_SLICED(1);
+    else if (vpl == 2) ADAQP_SLICED(2);
+    else ADAQP_SLICED(4);
+#undef ADAQP_SLICED
+    *n_carries_out = sa.n_blocks * kWavesPerBlock;
+    return hipGetLastError();
+}
+
+}  // namespace adaqp

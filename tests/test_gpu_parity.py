@@ -347,6 +347,30 @@ def test_spmm_shapes(oracle, dim, ldh):
     _check_spmm(oracle, rowptr, col, val, 0, n_rows, H, dim, ldo=dim + 3)            # unpadded output
 
 
+@pytest.mark.parametrize("n_cols", [700, 50_000])                      # four and two lines per slice
+@pytest.mark.parametrize("dim", [32, 60, 96, 128, 160, 250, 288])      # 1 to 9 lines: every width of a last slice
+def test_spmm_sliced_edges(oracle, dim, n_cols):
+    """Line-padded layout: row ends at every place of a step, more row ends than a chunk takes, rows of a chunk's length
+    and of many shares', empty rows at both ends; the launch sized for far fewer and far more entries than there are."""
+    _say(f"spmm sliced dim={dim} n_cols={n_cols}")
+    rng = np.random.default_rng(dim + n_cols)
+    degs = np.concatenate([np.zeros(70), np.ones(130), np.arange(40), [383, 384, 385, 8, 16, 0, 0], np.full(60, 23),
+                           [20_000, 5, 3_000], rng.integers(0, 90, size=400), np.zeros(3)]).astype(int)
+    rowptr, col, val = _random_graph(rng, degs.shape[0], n_cols, degs)
+    ld = _padded_cols(dim, 64 * dim)
+    H = np.full((n_cols, ld), np.nan, dtype=np.float32)
+    H[:, :dim] = rng.standard_normal((n_cols, dim), dtype=np.float32)
+    n_rows = degs.shape[0]
+    _check_spmm(oracle, rowptr, col, val, 0, n_rows, H, dim, ldo=ld)
+    _check_spmm(oracle, rowptr, col, val, 65, n_rows - 1, H, dim, nnz_range="exact", ldo=ld)
+    out = torch.full((n_rows, ld), 7.0, device=DEV)
+    ws = torch.empty(max(B.adaqp_spmm_workspace_bytes(n_rows, len(col), dim), 256), dtype=torch.uint8, device=DEV)
+    B.adaqp_spmm_csr(torch.from_numpy(rowptr).to(DEV), torch.from_numpy(col).to(DEV), torch.from_numpy(val).to(DEV), 0,
+                     n_rows, torch.from_numpy(H).to(DEV), dim, out, ws, nnz_range=1)
+    want, mag = oracle.spmm_csr(rowptr, col, val, 0, n_rows, np.ascontiguousarray(H[:, :dim]), dim)
+    assert np.all(np.abs(out.cpu().numpy()[:, :dim].astype(np.float64) - want) <= SPMM_RTOL * mag + 1e-30)
+
+
 def test_spmm_degenerate(oracle):
     _say("spmm degenerate")
     rng = np.random.default_rng(1)
