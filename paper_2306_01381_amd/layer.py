@@ -77,9 +77,14 @@ class SendPlan:
 
 def line_padded(a: np.ndarray, device, pad: bool = True) -> torch.Tensor:
     """Uploads a [n, dim] fp32 matrix into rows whose pitch is a whole number of 128-byte lines (the layout
-    the kernels are built for) and returns the [n, dim] view; the padding columns are zero."""
+    the kernels are built for) and returns the [n, dim] view; the padding columns are zero.  The number of lines is
+    never a multiple of four: an aggregation that takes the same lines of every row would find them in a quarter of the
+    L1's sets or fewer (256 columns, transposed graph: 0.84 ms at a pitch of 8 lines, 0.80 at 9)."""
     n, dim = a.shape
-    ld = (dim + 31) // 32 * 32 if pad else dim
+    ld = dim
+    if pad:
+        lines = (dim + 31) // 32
+        ld = 32 * (lines + 1 if lines % 4 == 0 else lines)
     buf = torch.zeros((n, ld), dtype=torch.float32, device=device)
     view = buf[:, :dim]
     view.copy_(torch.from_numpy(a))
