@@ -466,7 +466,9 @@ typedef struct adaqp_layer_desc {
 
 /* Enqueues one layer step.  On return all work has been enqueued and stream_msg has been made to wait for
  * stream_agg, so synchronising stream_msg completes the step.  The three schedules give bit-identical
- * results.
+ * results.  A step whose transfer is too short to hide anything behind (packed_bytes up to 64 MB, no tile tables) runs on
+ * stream_msg alone in every schedule; if the overlap range ends where the dependent one begins and one of the two
+ * workspaces holds adaqp_spmm_workspace_bytes of both ranges together, they are then aggregated in one launch.
  * ISOLATED and FREE only overlap anything if stream_msg and stream_agg sit on different hardware queues.  HIP maps
  * the streams of a process onto a few hardware queues (four by default): in a process that has created more
  * streams than that, the two may share a queue, and the step then takes the SERIAL time (same results).  A caller

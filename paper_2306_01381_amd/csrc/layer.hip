@@ -198,6 +198,16 @@ int64_t tiled_part_bytes(const adaqp_layer_desc *d, bool overlap_part)
     return bytes;
 }
 
+// Rows [rb, re) along the merge path; fused: received rows are read from the receive buffer.
+int aggregate_range(const adaqp_layer_desc *d, int64_t rb, int64_t re, int64_t nz, bool fused, void *ws, int64_t wsb,
+                    hipStream_t st)
+{
+    return spmm_rows(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, nz, d->feat_dev, d->n_feat_rows, d->ld, d->dim,
+                     d->out_dev, d->ldo, fused ? d->slot_of_row_dev : nullptr, d->recv_packed_dev, d->packed_bytes,
+                     d->recv_params_dev, d->bits_dev, d->row_offset_dev, d->n_send, ws, wsb, st,
+                     d->direction == ADAQP_BACKWARD);
+}
+
 // The rows of a range that are aggregated entry by entry: all of them, or those outside the panels.
 int aggregate_rows(const adaqp_layer_desc *d, bool overlap_part, hipStream_t st)
 {
@@ -211,11 +221,7 @@ int aggregate_rows(const adaqp_layer_desc *d, bool overlap_part, hipStream_t st)
         return adaqp_spmm_csr_tiled(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, d->feat_dev,
                                     d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo, tile_off,
                                     overlap_part ? d->tile_chunk_overlap : d->tile_chunk_dependent, ws, wsb, st);
-    const bool fused = !overlap_part && fused_receive(d);
-    return spmm_rows(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, nz, d->feat_dev, d->n_feat_rows, d->ld, d->dim,
-                     d->out_dev, d->ldo, fused ? d->slot_of_row_dev : nullptr, d->recv_packed_dev, d->packed_bytes,
-                     d->recv_params_dev, d->bits_dev, d->row_offset_dev, d->n_send, ws, wsb, st,
-                     d->direction == ADAQP_BACKWARD);
+    return aggregate_range(d, rb, re, nz, !overlap_part && fused_receive(d), ws, wsb, st);
 }
 
 bool has_panels(const adaqp_layer_desc *d, bool overlap_part)
@@ -245,15 +251,132 @@ int aggregate(const adaqp_layer_desc *d, bool overlap_part, hipStream_t st)
     return rc != ADAQP_OK ? rc : aggregate_panels(d, overlap_part, st);
 }
 
+// The loop-back copy, both buffers in one launch (the runtime's copies cost the host more than a launch each, and the
+// second one waits for the first).
+struct CopyArgs {
+    const uint8_t *from;
+    uint8_t *to;
+    int64_t bytes, units;       // whole units of 16, 4 or 1 bytes, as the addresses allow
+    int32_t unit;
+};
+
+CopyArgs copy_args(const void *from, void *to, int64_t bytes)
+{
+    CopyArgs c;
+    c.from = static_cast<const uint8_t *>(from);
+    c.to = static_cast<uint8_t *>(to);
+    c.bytes = bytes;
+    c.unit = aligned_to(from, 16) && aligned_to(to, 16) ? 16 : (aligned_to(from, 4) && aligned_to(to, 4) ? 4 : 1);
+    c.units = bytes / c.unit;
+    return c;
+}
+
+// Thread i copies unit i, or one byte of what the whole units leave over.
+__device__ __forceinline__ void copy_one(const CopyArgs &c, int64_t i)
+{
+    if (i >= c.units) {
+        const int64_t at = c.units * c.unit + (i - c.units);
+        if (at < c.bytes) c.to[at] = c.from[at];
+    } else if (c.unit == 16) {
+        reinterpret_cast<uint4 *>(c.to)[i] = reinterpret_cast<const uint4 *>(c.from)[i];
+    } else if (c.unit == 4) {
+        reinterpret_cast<uint32_t *>(c.to)[i] = reinterpret_cast<const uint32_t *>(c.from)[i];
+    } else {
+        c.to[i] = c.from[i];
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void loop_back_kernel(const CopyArgs a, const CopyArgs b, uint32_t blocks_a)
+{
+    if (blockIdx.x < blocks_a) copy_one(a, (int64_t)blockIdx.x * kBlock + threadIdx.x);
+    else copy_one(b, (int64_t)(blockIdx.x - blocks_a) * kBlock + threadIdx.x);
+}
+
 int loop_back(const adaqp_layer_desc *d, hipStream_t st)
 {
     if (d->n_send == 0) return ADAQP_OK;
-    if (d->packed_bytes > 0)
-        ADAQP_HIP_TRY(hipMemcpyAsync(d->recv_packed_dev, d->packed_dev, (size_t)d->packed_bytes,
-                                     hipMemcpyDeviceToDevice, st));
-    ADAQP_HIP_TRY(hipMemcpyAsync(d->recv_params_dev, d->params_dev, (size_t)d->n_send * 2 * sizeof(float),
-                                 hipMemcpyDeviceToDevice, st));
+    const CopyArgs a = copy_args(d->packed_dev, d->recv_packed_dev, d->packed_bytes);
+    const CopyArgs b = copy_args(d->params_dev, d->recv_params_dev, d->n_send * 2 * (int64_t)sizeof(float));
+    const int64_t blocks_a = (a.units + a.bytes % a.unit + kBlock - 1) / kBlock;
+    const int64_t blocks_b = (b.units + b.bytes % b.unit + kBlock - 1) / kBlock;
+    if (blocks_a + blocks_b > INT32_MAX) return ADAQP_ESIZE;
+    hipLaunchKernelGGL(loop_back_kernel, dim3((unsigned)(blocks_a + blocks_b)), dim3(kBlock), 0, st, a, b, (uint32_t)blocks_a);
+    ADAQP_HIP_TRY(hipGetLastError());
     return ADAQP_OK;
+}
+
+// Where the second stream has nothing to give, the step runs on stream_msg alone, and row ranges that touch are aggregated
+// in one launch.  What a second stream can hide is the transfer, here a copy of packed_bytes: 64 MB take about 25 us.  Its
+// price is a fork and a join (20-30 us of the host, several of the GPU) and two gathers that compete for the L2s and
+// what is behind them.  Two streams against one, measured: 2 000 nodes 61 us, 28; 50 000-node backward step 141, 111;
+// 179 000 nodes, 12 MB sent, 438, 409; 306 000 nodes, 8 MB sent, 1151, 1079; 196 000-node backward step, 18 MB sent,
+// 895, 875.  Ranges with tile tables keep two streams: their panel and tiled kernels run side by side.  The rule looks at
+// sizes only, so that every schedule gives the same bits.
+constexpr int64_t kOneStreamBytes = (int64_t)64 << 20;
+
+bool one_stream(const adaqp_layer_desc *d)
+{
+    return !d->tile_off_overlap_dev && !d->tile_off_dependent_dev && d->packed_bytes <= kOneStreamBytes;
+}
+
+int64_t range_nnz(const adaqp_layer_desc *d, bool overlap_part)
+{
+    const int64_t nz = overlap_part ? d->overlap_nnz : d->dependent_nnz;
+    return nz < 0 || nz > d->nnz ? d->nnz : nz;
+}
+
+// Both ranges: in one launch if they are neighbours and one of the workspaces can take them.  With the received rows still
+// packed that launch looks a slot up for every column, also those of rows that cannot have one: a step that
+// de-quantises first must give the same bits, so it has to be cut the same way.
+int aggregate_both(const adaqp_layer_desc *d, hipStream_t st)
+{
+    if (d->overlap_end == d->dependent_begin && d->overlap_end > d->overlap_begin && d->dependent_end > d->dependent_begin) {
+        const int64_t nz = std::min(range_nnz(d, true) + range_nnz(d, false), d->nnz);
+        int64_t need = 0;
+        const int rc = adaqp_spmm_workspace_bytes(d->dependent_end - d->overlap_begin, nz, d->dim, &need);
+        if (rc != ADAQP_OK) return rc;
+        const bool first = d->workspace_overlap_bytes >= d->workspace_dependent_bytes;
+        void *ws = first ? d->workspace_overlap_dev : d->workspace_dependent_dev;
+        const int64_t wsb = first ? d->workspace_overlap_bytes : d->workspace_dependent_bytes;
+        if (ws && wsb >= need) return aggregate_range(d, d->overlap_begin, d->dependent_end, nz, fused_receive(d), ws, wsb, st);
+    }
+    const int rc = aggregate_rows(d, true, st);
+    return rc != ADAQP_OK ? rc : aggregate_rows(d, false, st);
+}
+
+int quantise(const adaqp_layer_desc *d, hipStream_t st)
+{
+    const bool forward = d->direction == ADAQP_FORWARD;
+    return adaqp_quantize_pack_trace(forward ? d->feat_dev : d->out_dev,
+                                     forward ? d->n_feat_rows : std::max(d->dependent_end, d->overlap_end),
+                                     forward ? d->ld : d->ldo, d->dim, d->send_idx_dev, d->bits_dev, d->row_offset_dev,
+                                     d->n_send, d->seed, d->packed_dev, d->packed_bytes, d->params_dev, d->alpha_sq_dev,
+                                     d->beta_dev, st);
+}
+
+// What the received messages become: halo rows of feat (forward, unless the aggregation reads them packed), or additions
+// to rows of out (backward, if segments are given).
+int receive(const adaqp_layer_desc *d, hipStream_t st)
+{
+    if (d->direction == ADAQP_FORWARD) {
+        if (fused_receive(d)) return ADAQP_OK;
+        return adaqp_unpack_dequant(d->recv_packed_dev, d->packed_bytes, d->recv_params_dev, d->bits_dev, d->row_offset_dev,
+                                    d->halo_idx_dev, d->recv_order_dev, d->n_send, d->dim, d->feat_dev, d->n_feat_rows,
+                                    d->ld, st);
+    }
+    if (!(d->n_recv_seg > 0 && d->recv_seg_order_dev && d->recv_seg_ptr_dev && d->halo_idx_dev)) return ADAQP_OK;
+    return adaqp_unpack_dequant_add(d->recv_packed_dev, d->packed_bytes, d->recv_params_dev, d->bits_dev, d->row_offset_dev,
+                                    d->halo_idx_dev, d->n_send, d->recv_seg_order_dev, d->recv_seg_ptr_dev, d->n_recv_seg,
+                                    d->dim, d->out_dev, std::max(d->dependent_end, d->overlap_end), d->ldo, st);
+}
+
+int one_stream_step(const adaqp_layer_desc *d, hipStream_t st)
+{
+    int rc = ADAQP_OK;
+    if (d->direction == ADAQP_BACKWARD && (rc = aggregate_both(d, st)) != ADAQP_OK) return rc;
+    if ((rc = quantise(d, st)) != ADAQP_OK || (rc = loop_back(d, st)) != ADAQP_OK) return rc;
+    if ((rc = receive(d, st)) != ADAQP_OK) return rc;
+    return d->direction == ADAQP_FORWARD ? aggregate_both(d, st) : ADAQP_OK;
 }
 
 }  // namespace
@@ -289,6 +412,7 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
     }
 
     hipStream_t msg = (hipStream_t)d->stream_msg;
+    if (one_stream(d)) return one_stream_step(d, msg);
     hipStream_t agg = d->schedule == ADAQP_SERIAL ? msg : (hipStream_t)d->stream_agg;
     hipEvent_t fork = (hipEvent_t)d->event_fork, join = (hipEvent_t)d->event_join;
     const bool forward = d->direction == ADAQP_FORWARD;
@@ -328,18 +452,13 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
             ADAQP_STEP(fork_now());
             ADAQP_STEP(paired ? aggregate_rows(d, true, agg) : aggregate(d, true, agg));
         }
-        ADAQP_STEP(adaqp_quantize_pack_trace(d->feat_dev, d->n_feat_rows, d->ld, d->dim, d->send_idx_dev,
-                                             d->bits_dev, d->row_offset_dev, d->n_send, d->seed, d->packed_dev,
-                                             d->packed_bytes, d->params_dev, d->alpha_sq_dev, d->beta_dev, msg));
+        ADAQP_STEP(quantise(d, msg));
         if (d->schedule == ADAQP_ISOLATED) {
             ADAQP_STEP(fork_now());
             ADAQP_STEP(paired ? aggregate_rows(d, true, agg) : aggregate(d, true, agg));
         }
         ADAQP_STEP(loop_back(d, msg));
-        if (!fused_receive(d))
-            ADAQP_STEP(adaqp_unpack_dequant(d->recv_packed_dev, d->packed_bytes, d->recv_params_dev, d->bits_dev,
-                                            d->row_offset_dev, d->halo_idx_dev, d->recv_order_dev, d->n_send, d->dim,
-                                            d->feat_dev, d->n_feat_rows, d->ld, msg));
+        ADAQP_STEP(receive(d, msg));
         if (d->schedule == ADAQP_SERIAL) ADAQP_STEP(aggregate(d, true, msg));
         if (paired) {
             // a panel kernel (matrix cores) and a tiled kernel (vector-memory pipeline) fill each other's gaps:
@@ -363,27 +482,16 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
             if (both_tiled) ADAQP_STEP(join_now());         // as in the forward step: one tiled launch at a time
         }
         ADAQP_STEP(aggregate(d, false, msg));
-        ADAQP_STEP(adaqp_quantize_pack_trace(d->out_dev,
-                                             d->dependent_end > d->overlap_end ? d->dependent_end : d->overlap_end,
-                                             d->ldo, d->dim, d->send_idx_dev, d->bits_dev, d->row_offset_dev,
-                                             d->n_send, d->seed, d->packed_dev, d->packed_bytes, d->params_dev,
-                                             d->alpha_sq_dev, d->beta_dev, msg));
+        ADAQP_STEP(quantise(d, msg));
         if (d->schedule == ADAQP_ISOLATED) {
             ADAQP_STEP(fork_now());
             ADAQP_STEP(aggregate(d, true, agg));
         }
         ADAQP_STEP(loop_back(d, msg));
         if (d->schedule == ADAQP_SERIAL) ADAQP_STEP(aggregate(d, true, msg));
-        if (d->n_recv_seg > 0 && d->recv_seg_order_dev && d->recv_seg_ptr_dev && d->halo_idx_dev) {
-            // the received gradients are added to rows that the local aggregation also writes: join first
-            ADAQP_STEP(join_now());
-            ADAQP_STEP(adaqp_unpack_dequant_add(d->recv_packed_dev, d->packed_bytes, d->recv_params_dev, d->bits_dev,
-                                                d->row_offset_dev, d->halo_idx_dev, d->n_send,
-                                                d->recv_seg_order_dev, d->recv_seg_ptr_dev, d->n_recv_seg, d->dim,
-                                                d->out_dev,
-                                                d->dependent_end > d->overlap_end ? d->dependent_end : d->overlap_end,
-                                                d->ldo, msg));
-        }
+        // the received gradients are added to rows that the local aggregation also writes: join first
+        ADAQP_STEP(join_now());
+        ADAQP_STEP(receive(d, msg));
     }
     ADAQP_STEP(join_now());
 #undef ADAQP_STEP

@@ -144,6 +144,8 @@ class LayerStep:
         min_row_o, min_row_d = panel_min_row if isinstance(panel_min_row, tuple) else (panel_min_row, panel_min_row)
         ws_o = B.adaqp_spmm_workspace_bytes(oe - ob, self.overlap_nnz, cfg.dim)
         ws_d = B.adaqp_spmm_workspace_bytes(de - db, self.dependent_nnz, cfg.dim)
+        if oe == db:        # a step without tiles aggregates both ranges in one launch, if this workspace can take them
+            ws_o = max(ws_o, B.adaqp_spmm_workspace_bytes(de - ob, self.overlap_nnz + self.dependent_nnz, cfg.dim))
         if pad and tiled is not False:
             if oe > ob and (tiled or B.adaqp_spmm_tiled_pays(oe - ob, self.overlap_nnz)):
                 bounds, off = B.adaqp_plan_spmm_tiles(p.rowptr, p.col, ob, oe, p.feat.shape[0])
