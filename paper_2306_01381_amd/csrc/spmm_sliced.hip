@@ -3,7 +3,7 @@
 // The gather is bound by what comes from behind the L2s: rows of H are drawn from a power law with no locality, every
 // XCD has a private 4 MB L2, and when all eight walk whole rows (1 KB and more) each holds the same few thousand
 // popular rows.  Here an XCD walks the graph for ITS share of the feature columns only, a slice of VPL 128-byte lines
-// of every row at a time: its L2 then holds one line of 32 768 rows (two of 16 384) instead of eight or more lines of
+// of every row at a time: its L2 then holds one line of 32 768 rows (four of 8 192) instead of eight or more lines of
 // 4 000, the L2s hold different data, and no line of H is fetched behind two of them.  The price is that the entries
 // (8 bytes each) are read once per slice.
 //
@@ -32,7 +32,7 @@ namespace adaqp {
 namespace {
 
 constexpr int kXcds = 8;
-constexpr int64_t kColumnsForFour = 49152, kRowsForFour = 8;   // see launch_sliced
+constexpr int64_t kColumnsThatFit = 10240, kOneLineProduct = 700000, kColumnsForTwo = 200000;      // see launch_sliced
 constexpr int64_t kWorkgroups = 512, kMinPath = 1024;
 constexpr int kStep = 8;                            // entries of a step = groups of a wave
 constexpr int kGroup = kWave / kStep;               // lanes per entry: 8 x 16 bytes = one line
@@ -447,17 +447,22 @@ hipError_t launch_sliced(const SpmmArgs &a, int64_t nnz_hint, bool skewed_column
     SlicedArgs sa;
     sa.s = a;
     sa.lines = a.wdim / kLine;
-    // Lines per slice.  Four cost the least per line: one LDS read, one address and one row end serve four loads.  Two keep
-    // twice as many rows in an L2, which pays where the columns neither fit nor are few of them used most of the time.
-    // Rows of a few entries spend their time on row ends: four again.
-    int vpl = a.n_cols <= kColumnsForFour || skewed_columns || nnz_hint < kRowsForFour * (int64_t)a.n_rows ? 4 : 2;
-    if (sa.lines < vpl) vpl = sa.lines >= 3 ? 4 : sa.lines;
+    // Lines per slice: one or four.  With four, one LDS read, one address and one row end serve four loads (bare loop out of
+    // L2: 28 TB/s against 21); with one, an L2 holds four times as many rows.  One pays where the rows are long enough
+    // for their ends not to matter and the columns too many for an L2 to hold four lines of each: measured at 224
+    // columns of power-law popularity, the two break even at 12 entries per row x 50 000 columns, 20 x 34 000, 40 x
+    // 20 000 (150 entries x 50 000 columns 0.29 ms against 0.42; 5 entries x 100 000 columns 0.064 against 0.058).
+    // Where a few columns hold most of the entries four lines of those fit anyway (196 000 columns used as often as
+    // Zipf(1.5) degrees say: 0.80 ms against 0.99).  Two per slice: only where even one line of each column is ten times what an L2 holds, and
+    // the lines come in pairs (269 000 columns of 10 lines: 0.360 ms against 0.375).
+    const bool many = a.n_cols > kColumnsThatFit && nnz_hint / a.n_rows * a.n_cols > kOneLineProduct;
+    const int vpl = !many || skewed_columns ? 4 : (a.n_cols > kColumnsForTwo && sa.lines % 2 == 0 ? 2 : 1);
     const int64_t slices = (sa.lines + vpl - 1) / vpl;
     const int64_t path = nnz_hint + (int64_t)a.n_rows * kRowSteps;
-    // two workgroups per CU, each with one share per wave: fewer and longer shares measured faster than more of them
-    // (16 M entries, 256 columns, 4 lines per slice: 0.85 ms with 512 workgroups, 0.91 with 4096), but a wave's share is
-    // at least 256 steps of the path
-    int64_t n_blocks = kWorkgroups / slices;
+    // Two workgroups per CU with two or four lines, up to eight with one; each wave takes one share, of at least 256 steps of the
+    // path.  More and shorter shares cost a search and an empty ring each (16 M entries at four lines: 0.85 ms with 512
+    // workgroups, 0.91 with 4096; at one line 1.11 with 512, 0.99 with 2048).
+    int64_t n_blocks = (vpl == 1 ? 4 : 1) * kWorkgroups / slices;
     n_blocks = std::min(n_blocks, (path + kMinPath - 1) / kMinPath);
     if (n_blocks > a.n_items / kWavesPerBlock) n_blocks = a.n_items / kWavesPerBlock;      // one carry slot per share
     if (n_blocks < 1) n_blocks = 1;

@@ -347,8 +347,8 @@ def test_spmm_shapes(oracle, dim, ldh):
     _check_spmm(oracle, rowptr, col, val, 0, n_rows, H, dim, ldo=dim + 3)            # unpadded output
 
 
-@pytest.mark.parametrize("n_cols", [700, 50_000])                      # four and two lines per slice
-@pytest.mark.parametrize("dim", [32, 60, 96, 128, 160, 250, 288])      # 1 to 9 lines: every width of a last slice
+@pytest.mark.parametrize("dim,n_cols", [(d, 700) for d in (32, 60, 96, 128, 160, 250, 288)] +  # four lines per slice: every
+                         [(d, 50_000) for d in (32, 60, 96, 250)] + [(60, 201_000), (100, 201_000)])   # last width; one; two
 def test_spmm_sliced_edges(oracle, dim, n_cols):
     """Line-padded layout: row ends at every place of a step, more row ends than a chunk takes, rows of a chunk's length
     and of many shares', empty rows at both ends; the launch sized for far fewer and far more entries than there are."""
