@@ -9,12 +9,15 @@
 // pair takes the longest prefix that fits under it, and the time with the smallest Eq. 9 value wins.  With one
 // pair this is the exact optimum; with several, a pair misses its best packing by less than one upgrade.
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 #include <numeric>
 #include <vector>
 
 #include "adaqp.h"
+#include "host_sort.hpp"
 
 namespace {
 
@@ -27,7 +30,7 @@ struct Upgrade {
 };
 
 struct PairPath {
-    std::vector<std::vector<int64_t>> groups;   // slot numbers, descending beta
+    size_t begin, end;                          // the pair's messages in the list sorted by (pair, descending beta)
     std::vector<Upgrade> upgrades;              // in the order they are taken
     std::vector<double> time;                   // [m]: pair time with the first m upgrades applied
     std::vector<double> variance;               // [m]: Eq. 8 share of this pair
@@ -39,49 +42,74 @@ double inv_levels_sq(int b)
     return 1.0 / (levels * levels);
 }
 
-}  // namespace
-
-extern "C" int adaqp_assign_bits(int64_t n, const float *beta_host, const int32_t *peer_of_slot_host,
-                                 int32_t n_peers, int32_t dim, int32_t group_size, double lambda,
-                                 const double *theta_host, const double *gamma_host, uint8_t *bits_out,
-                                 double *objective_out)
+float beta_of(uint32_t key)
 {
-    if (n < 0 || n_peers <= 0 || dim <= 0 || group_size <= 0 || !(lambda >= 0.0 && lambda <= 1.0))
-        return ADAQP_EINVAL;
-    if (!theta_host || !gamma_host) return ADAQP_EINVAL;
-    if (n > 0 && (!beta_host || !peer_of_slot_host || !bits_out)) return ADAQP_EINVAL;
-    if (n > ((int64_t)1 << 40) / dim) return ADAQP_ESIZE;           // bit counts stay far inside int64
-    for (int32_t i = 0; i < n_peers; ++i)
-        if (!(theta_host[i] >= 0.0) || !std::isfinite(theta_host[i]) || !std::isfinite(gamma_host[i]))
-            return ADAQP_EINVAL;
-    for (int64_t k = 0; k < n; ++k) {
-        if (peer_of_slot_host[k] < 0 || peer_of_slot_host[k] >= n_peers) return ADAQP_EINVAL;
-        if (!(beta_host[k] >= 0.0f) || !std::isfinite(beta_host[k])) return ADAQP_EINVAL;
-    }
+    const uint32_t bits = ~key;
+    float f;
+    memcpy(&f, &bits, sizeof(f));
+    return f;
+}
 
+template <typename Index>
+void assign(int64_t n, const float *beta_host, const int32_t *peer_of_slot_host, int32_t n_peers, int32_t dim,
+            int32_t group_size, double lambda, const double *theta_host, const double *gamma_host, uint8_t *bits_out,
+            double *objective_out)
+{
     const double w2 = inv_levels_sq(2), w4 = inv_levels_sq(4), w8 = inv_levels_sq(8);
     const double step_weight[2] = {w2 - w4, w4 - w8};
     const int64_t step_bits[2] = {2, 4};
 
+    // ---- the messages of each pair by descending beta (non-negative floats order as their bits do), ties by slot ----
+    // slots mostly come peer by peer: counted and placed in runs of one peer
+    std::vector<size_t> first((size_t)n_peers + 1, 0);
+    auto for_runs = [&](auto &&f) {
+        for (int64_t k = 0; k < n;) {
+            const int32_t peer = peer_of_slot_host[k];
+            int64_t e = k + 1;
+            while (e < n && peer_of_slot_host[e] == peer) ++e;
+            f((size_t)peer, k, e);
+            k = e;
+        }
+    };
+    for_runs([&](size_t peer, int64_t k, int64_t e) { first[peer + 1] += (size_t)(e - k); });
+    size_t most = 0;
+    for (int32_t i = 0; i < n_peers; ++i) {
+        most = std::max(most, first[(size_t)i + 1]);
+        first[(size_t)i + 1] += first[(size_t)i];
+    }
+    std::vector<adaqp::KeyedIndex<Index>> sorted((size_t)n), other(most);
+    {
+        std::vector<size_t> next(first.begin(), first.end() - 1);
+        for_runs([&](size_t peer, int64_t k, int64_t e) {
+            adaqp::KeyedIndex<Index> *to = sorted.data() + next[peer];
+            next[peer] += (size_t)(e - k);
+            for (; k < e; ++k) {
+                const float beta = beta_host[k] + 0.0f;             // -0 counts as 0
+                uint32_t bits;
+                memcpy(&bits, &beta, sizeof(bits));
+                *to++ = {~bits, (Index)k};
+            }
+        });
+    }
+    for (int32_t i = 0; i < n_peers; ++i)
+        adaqp::sort_by_key(sorted.data() + first[(size_t)i], other.data(), first[(size_t)i + 1] - first[(size_t)i]);
+
     // ---- per pair: groups, upgrade order, reachable (time, variance) points ----
-    std::vector<std::vector<int64_t>> members((size_t)n_peers);
-    for (int64_t k = 0; k < n; ++k) members[(size_t)peer_of_slot_host[k]].push_back(k);
     std::vector<PairPath> pairs;
     std::vector<int32_t> pair_id;
     for (int32_t i = 0; i < n_peers; ++i) {
-        std::vector<int64_t> &slots = members[(size_t)i];
-        if (slots.empty()) continue;                                // a pair that exchanges nothing takes no time
-        std::stable_sort(slots.begin(), slots.end(),
-                         [&](int64_t a, int64_t b) { return beta_host[a] > beta_host[b]; });
         PairPath path;
+        path.begin = first[(size_t)i];
+        path.end = first[(size_t)i + 1];
+        const size_t n_slots = path.end - path.begin;
+        if (n_slots == 0) continue;                                 // a pair that exchanges nothing takes no time
         double variance_at_2 = 0.0;
-        for (size_t s = 0; s < slots.size(); s += (size_t)group_size) {
-            const size_t e = std::min(slots.size(), s + (size_t)group_size);
-            path.groups.emplace_back(slots.begin() + (std::ptrdiff_t)s, slots.begin() + (std::ptrdiff_t)e);
+        for (size_t s = 0; s < n_slots; s += (size_t)group_size) {
+            const size_t e = std::min(n_slots, s + (size_t)group_size);
             double group_beta = 0.0;
-            for (size_t q = s; q < e; ++q) group_beta += (double)beta_host[slots[q]];
+            for (size_t q = s; q < e; ++q) group_beta += (double)beta_of(sorted[path.begin + q].key);
             variance_at_2 += group_beta * w2;
-            const int32_t g = (int32_t)path.groups.size() - 1;
+            const int32_t g = (int32_t)(s / (size_t)group_size);
             for (int32_t step = 0; step < 2; ++step) {
                 Upgrade u;
                 u.group = g;
@@ -97,7 +125,7 @@ extern "C" int adaqp_assign_bits(int64_t n, const float *beta_host, const int32_
             if (a.group != b.group) return a.group < b.group;
             return a.step < b.step;
         });
-        const int64_t base_bits = 2 * (int64_t)dim * (int64_t)slots.size();
+        const int64_t base_bits = 2 * (int64_t)dim * (int64_t)n_slots;
         path.time.push_back(theta_host[i] * (double)base_bits + gamma_host[i]);
         path.variance.push_back(variance_at_2);
         int64_t cost = 0;
@@ -125,12 +153,12 @@ extern "C" int adaqp_assign_bits(int64_t n, const float *beta_host, const int32_
         candidates.erase(std::unique(candidates.begin(), candidates.end()), candidates.end());
         bool have = false;
         double best = 0.0;
-        std::vector<size_t> m(pairs.size());
-        for (double z : candidates) {
+        std::vector<size_t> m(pairs.size(), 0);
+        for (double z : candidates) {                               // ascending: the prefixes only grow
             double variance = 0.0, worst = 0.0;
             for (size_t q = 0; q < pairs.size(); ++q) {
                 const std::vector<double> &t = pairs[q].time;           // non-decreasing (theta >= 0)
-                m[q] = (size_t)(std::upper_bound(t.begin(), t.end(), z) - t.begin()) - 1;
+                while (m[q] + 1 < t.size() && t[m[q] + 1] <= z) ++m[q];
                 variance += pairs[q].variance[m[q]];
                 worst = q == 0 ? t[m[q]] : std::max(worst, t[m[q]]);
             }
@@ -147,22 +175,52 @@ extern "C" int adaqp_assign_bits(int64_t n, const float *beta_host, const int32_
     double variance = 0.0, worst = 0.0;
     for (size_t q = 0; q < pairs.size(); ++q) {
         const PairPath &p = pairs[q];
-        std::vector<int> width(p.groups.size(), 2);
+        const size_t n_slots = p.end - p.begin, n_groups = (n_slots + (size_t)group_size - 1) / (size_t)group_size;
+        std::vector<int> width(n_groups, 2);
         for (size_t j = 0; j < taken[q]; ++j) width[(size_t)p.upgrades[j].group] += p.upgrades[j].step == 0 ? 2 : 4;
         int64_t payload = 0;
-        for (size_t g = 0; g < p.groups.size(); ++g)
-            for (int64_t k : p.groups[g]) {
-                bits_out[k] = (uint8_t)width[g];
-                payload += (int64_t)dim * width[g];
-            }
+        for (size_t g = 0; g < n_groups; ++g) {
+            const size_t s = g * (size_t)group_size, e = std::min(n_slots, s + (size_t)group_size);
+            for (size_t k = s; k < e; ++k) bits_out[sorted[p.begin + k].index] = (uint8_t)width[g];
+            payload += (int64_t)(e - s) * dim * width[g];
+        }
         const double t = theta_host[pair_id[q]] * (double)payload + gamma_host[pair_id[q]];
         worst = q == 0 ? t : std::max(worst, t);
     }
     if (objective_out) {
-        for (int64_t k = 0; k < n; ++k) variance += (double)beta_host[k] * inv_levels_sq(bits_out[k]);
+        const double weight[9] = {0, 0, w2, 0, w4, 0, 0, 0, w8};
+        for (int64_t k = 0; k < n; ++k) variance += (double)beta_host[k] * weight[bits_out[k]];
         objective_out[0] = lambda * variance + (1.0 - lambda) * worst;
         objective_out[1] = variance;
         objective_out[2] = worst;
     }
+}
+
+}  // namespace
+
+extern "C" int adaqp_assign_bits(int64_t n, const float *beta_host, const int32_t *peer_of_slot_host,
+                                 int32_t n_peers, int32_t dim, int32_t group_size, double lambda,
+                                 const double *theta_host, const double *gamma_host, uint8_t *bits_out,
+                                 double *objective_out)
+{
+    if (n < 0 || n_peers <= 0 || dim <= 0 || group_size <= 0 || !(lambda >= 0.0 && lambda <= 1.0))
+        return ADAQP_EINVAL;
+    if (!theta_host || !gamma_host) return ADAQP_EINVAL;
+    if (n > 0 && (!beta_host || !peer_of_slot_host || !bits_out)) return ADAQP_EINVAL;
+    if (n > ((int64_t)1 << 40) / dim) return ADAQP_ESIZE;           // bit counts stay far inside int64
+    for (int32_t i = 0; i < n_peers; ++i)
+        if (!(theta_host[i] >= 0.0) || !std::isfinite(theta_host[i]) || !std::isfinite(gamma_host[i]))
+            return ADAQP_EINVAL;
+    bool ok = true;
+    for (int64_t k = 0; k < n; ++k)
+        ok &= (uint32_t)peer_of_slot_host[k] < (uint32_t)n_peers & beta_host[k] >= 0.0f & beta_host[k] <= FLT_MAX;
+    if (!ok) return ADAQP_EINVAL;
+
+    if (n <= INT32_MAX)
+        assign<int32_t>(n, beta_host, peer_of_slot_host, n_peers, dim, group_size, lambda, theta_host, gamma_host, bits_out,
+                        objective_out);
+    else
+        assign<int64_t>(n, beta_host, peer_of_slot_host, n_peers, dim, group_size, lambda, theta_host, gamma_host, bits_out,
+                        objective_out);
     return ADAQP_OK;
 }

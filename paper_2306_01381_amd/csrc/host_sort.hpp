@@ -1,0 +1,84 @@
+// Stable sorts of index lists by 32-bit keys for the host planners.
+#pragma once
+
+#include <stdint.h>
+#include <string.h>
+
+#include <algorithm>
+#include <utility>
+#include <vector>
+
+namespace adaqp {
+
+template <typename Index> struct KeyedIndex { uint32_t key; Index index; };
+
+// Sorts by ascending key, equal keys in their present order: least significant digit first, eleven bits at a time, digits
+// in which all keys agree left out.  A comparison sort through an index spends its time on mispredicted branches and
+// scattered reads.  `other`: scratch of n items.
+template <typename Index>
+void sort_by_key(KeyedIndex<Index> *items, KeyedIndex<Index> *other, size_t n)
+{
+    constexpr int kDigits = 3, kBits = 11, kSize = 1 << kBits;
+    if (n < 256) {
+        std::stable_sort(items, items + n,
+                         [](const KeyedIndex<Index> &x, const KeyedIndex<Index> &y) { return x.key < y.key; });
+        return;
+    }
+    std::vector<uint32_t> count(n <= UINT32_MAX ? (size_t)kDigits * kSize : 0);
+    std::vector<uint64_t> count64(n <= UINT32_MAX ? 0 : (size_t)kDigits * kSize);
+    auto passes = [&](auto *counts) {
+        for (size_t i = 0; i < n; ++i)
+            for (int d = 0; d < kDigits; ++d) ++counts[(size_t)d * kSize + ((items[i].key >> (d * kBits)) & (kSize - 1))];
+        KeyedIndex<Index> *from = items, *to = other;
+        for (int d = 0; d < kDigits; ++d) {
+            auto *at = counts + (size_t)d * kSize;
+            if (at[(from[0].key >> (d * kBits)) & (kSize - 1)] == n) continue;
+            size_t sum = 0;
+            for (int b = 0; b < kSize; ++b) {
+                const size_t c = at[b];
+                at[b] = sum;
+                sum += c;
+            }
+            for (size_t i = 0; i < n; ++i) to[at[(from[i].key >> (d * kBits)) & (kSize - 1)]++] = from[i];
+            std::swap(from, to);
+        }
+        if (from != items) memcpy(items, from, n * sizeof(*items));
+    };
+    if (n <= UINT32_MAX) passes(count.data());
+    else passes(count64.data());
+}
+
+// order_out[k] = position of the k-th smallest value, ties by position (n up to 2^31 - 1).
+inline void order_by_value(int64_t n, const int32_t *values, int32_t *order_out)
+{
+    int32_t lo = values[0], hi = values[0];
+    bool sorted = true;
+    for (int64_t i = 1; i < n; ++i) {
+        sorted = sorted && values[i - 1] <= values[i];
+        lo = std::min(lo, values[i]);
+        hi = std::max(hi, values[i]);
+    }
+    if (sorted) {
+        for (int64_t i = 0; i < n; ++i) order_out[i] = (int32_t)i;
+        return;
+    }
+    const int64_t range = (int64_t)hi - lo + 1;
+    if (range <= 4 * n) {                                   // rows of one partition: one counter each
+        std::vector<int32_t> at((size_t)range, 0);
+        for (int64_t i = 0; i < n; ++i) ++at[(size_t)((int64_t)values[i] - lo)];
+        int32_t sum = 0;
+        for (int32_t &c : at) {
+            const int32_t here = c;
+            c = sum;
+            sum += here;
+        }
+        for (int64_t i = 0; i < n; ++i) order_out[at[(size_t)((int64_t)values[i] - lo)]++] = (int32_t)i;
+        return;
+    }
+    std::vector<KeyedIndex<int32_t>> items((size_t)n), other((size_t)n);
+    for (int64_t i = 0; i < n; ++i) items[(size_t)i] = {(uint32_t)values[i] ^ 0x80000000u, (int32_t)i};
+    sort_by_key(items.data(), other.data(), (size_t)n);
+    for (int64_t k = 0; k < n; ++k) order_out[k] = items[(size_t)k].index;
+}
+
+}  // namespace adaqp

@@ -7,6 +7,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "host_sort.hpp"
 
 namespace adaqp {
 
@@ -51,7 +52,11 @@ extern "C" int adaqp_plan_layout(int64_t n, int32_t dim, const uint8_t *bits_hos
     if (n < 0 || dim <= 0 || n_peers < 0 || !peer_byte_ptr_out) return ADAQP_EINVAL;
     if (n > 0 && (!bits_host || !peer_of_slot_host || !perm_out || !row_offset_out)) return ADAQP_EINVAL;
     if (n > 0 && n_peers == 0) return ADAQP_EINVAL;
-    for (int64_t i = 0; i < n; ++i) {
+    // checked without a branch per slot; only where something is wrong a second look says what comes first
+    bool ok = n == 0 || (peer_of_slot_host[0] >= 0 && peer_of_slot_host[n - 1] < n_peers);
+    for (int64_t i = 0; i < n; ++i) ok &= (bits_host[i] == 2) | (bits_host[i] == 4) | (bits_host[i] == 8);
+    for (int64_t i = 1; i < n; ++i) ok &= peer_of_slot_host[i - 1] <= peer_of_slot_host[i];
+    for (int64_t i = 0; !ok && i < n; ++i) {
         if (!valid_bits(bits_host[i])) return ADAQP_EBITS;
         const int32_t p = peer_of_slot_host[i];
         if (p < 0 || p >= n_peers) return ADAQP_EINVAL;
@@ -63,11 +68,7 @@ extern "C" int adaqp_plan_layout(int64_t n, int32_t dim, const uint8_t *bits_hos
     for (int32_t p = 0; p < n_peers; ++p) {
         int64_t seg_end = seg_begin;
         int64_t count[3] = {0, 0, 0};
-        while (seg_end < n && peer_of_slot_host[seg_end] == p) {
-            const int w = bits_host[seg_end] == 2 ? 0 : (bits_host[seg_end] == 4 ? 1 : 2);
-            ++count[w];
-            ++seg_end;
-        }
+        while (seg_end < n && peer_of_slot_host[seg_end] == p) ++count[bits_host[seg_end++] >> 2];     // 2, 4, 8 -> 0, 1, 2
         peer_byte_ptr_out[p] = bytes;
         int64_t next_slot[3], next_byte[3];
         next_slot[0] = seg_begin;
@@ -78,7 +79,7 @@ extern "C" int adaqp_plan_layout(int64_t n, int32_t dim, const uint8_t *bits_hos
         next_byte[2] = next_byte[1] + count[1] * stride_of[1];
         bytes = next_byte[2] + count[2] * stride_of[2];
         for (int64_t i = seg_begin; i < seg_end; ++i) {
-            const int w = bits_host[i] == 2 ? 0 : (bits_host[i] == 4 ? 1 : 2);
+            const int w = bits_host[i] >> 2;
             const int64_t k = next_slot[w]++;
             perm_out[k] = i;
             row_offset_out[k] = next_byte[w];
@@ -96,9 +97,7 @@ extern "C" int adaqp_plan_recv_order(int64_t n, const int32_t *halo_idx_host, in
     if (n == 0) return ADAQP_OK;
     if (!halo_idx_host || !order_out) return ADAQP_EINVAL;
     if (n > INT32_MAX) return ADAQP_ESIZE;
-    for (int64_t i = 0; i < n; ++i) order_out[i] = (int32_t)i;
-    std::stable_sort(order_out, order_out + n,
-                     [halo_idx_host](int32_t x, int32_t y) { return halo_idx_host[x] < halo_idx_host[y]; });
+    order_by_value(n, halo_idx_host, order_out);
     return ADAQP_OK;
 }
 
@@ -127,12 +126,13 @@ extern "C" int adaqp_plan_recv_segments(int64_t n, const int32_t *dst_idx_host, 
     if (n == 0) return ADAQP_OK;
     if (!dst_idx_host || !order_out) return ADAQP_EINVAL;
     if (n > INT32_MAX) return ADAQP_ESIZE;
-    for (int64_t i = 0; i < n; ++i) order_out[i] = (int32_t)i;
-    std::stable_sort(order_out, order_out + n,
-                     [dst_idx_host](int32_t x, int32_t y) { return dst_idx_host[x] < dst_idx_host[y]; });
+    order_by_value(n, dst_idx_host, order_out);
     int64_t n_seg = 0;
+    int32_t before = 0;
     for (int64_t k = 0; k < n; ++k) {
-        if (k == 0 || dst_idx_host[order_out[k]] != dst_idx_host[order_out[k - 1]]) seg_ptr_out[n_seg++] = k;
+        const int32_t dst = dst_idx_host[order_out[k]];
+        if (k == 0 || dst != before) seg_ptr_out[n_seg++] = k;
+        before = dst;
     }
     seg_ptr_out[n_seg] = n;
     *n_seg_out = n_seg;
