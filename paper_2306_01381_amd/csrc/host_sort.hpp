@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <new>
 #include <utility>
 #include <vector>
 
@@ -63,22 +64,28 @@ inline void order_by_value(int64_t n, const int32_t *values, int32_t *order_out)
         return;
     }
     const int64_t range = (int64_t)hi - lo + 1;
-    if (range <= 4 * n) {                                   // rows of one partition: one counter each
-        std::vector<int32_t> at((size_t)range, 0);
-        for (int64_t i = 0; i < n; ++i) ++at[(size_t)((int64_t)values[i] - lo)];
-        int32_t sum = 0;
-        for (int32_t &c : at) {
-            const int32_t here = c;
-            c = sum;
-            sum += here;
+    try {
+        if (range <= 4 * n) {                               // rows of one partition: one counter each
+            std::vector<int32_t> at((size_t)range, 0);
+            for (int64_t i = 0; i < n; ++i) ++at[(size_t)((int64_t)values[i] - lo)];
+            int32_t sum = 0;
+            for (int32_t &c : at) {
+                const int32_t here = c;
+                c = sum;
+                sum += here;
+            }
+            for (int64_t i = 0; i < n; ++i) order_out[at[(size_t)((int64_t)values[i] - lo)]++] = (int32_t)i;
+            return;
         }
-        for (int64_t i = 0; i < n; ++i) order_out[at[(size_t)((int64_t)values[i] - lo)]++] = (int32_t)i;
-        return;
+        std::vector<KeyedIndex<int32_t>> items((size_t)n), other((size_t)n);
+        for (int64_t i = 0; i < n; ++i) items[(size_t)i] = {(uint32_t)values[i] ^ 0x80000000u, (int32_t)i};
+        sort_by_key(items.data(), other.data(), (size_t)n);
+        for (int64_t k = 0; k < n; ++k) order_out[k] = items[(size_t)k].index;
+    } catch (const std::bad_alloc &) {
+        // no room for the scratch, and nothing may be thrown through a C entry: a comparison sort does without
+        for (int64_t i = 0; i < n; ++i) order_out[i] = (int32_t)i;
+        std::stable_sort(order_out, order_out + n, [values](int32_t x, int32_t y) { return values[x] < values[y]; });
     }
-    std::vector<KeyedIndex<int32_t>> items((size_t)n), other((size_t)n);
-    for (int64_t i = 0; i < n; ++i) items[(size_t)i] = {(uint32_t)values[i] ^ 0x80000000u, (int32_t)i};
-    sort_by_key(items.data(), other.data(), (size_t)n);
-    for (int64_t k = 0; k < n; ++k) order_out[k] = items[(size_t)k].index;
 }
 
 }  // namespace adaqp

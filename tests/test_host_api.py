@@ -3,6 +3,8 @@
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -123,6 +125,40 @@ def test_plan_recv_order():
     assert B.adaqp_plan_recv_order(np.zeros(0, np.int32)).size == 0
     # ties keep slot order
     assert B.adaqp_plan_recv_order(np.array([5, 1, 5, 1], np.int32)).tolist() == [1, 3, 0, 2]
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 5000])
+@pytest.mark.parametrize("span", [1, 5, 2_000, 3_000_000, 2**32])
+def test_plan_recv_order_ranges(n, span):
+    """Few values, a partition's rows, values all over the range of the type, negative ones among them; every way the
+    planner sorts them against a stable comparison sort."""
+    rng = np.random.default_rng(n + span)
+    dst = (rng.integers(0, span, size=n) - span // 2).astype(np.int32)
+    want = np.argsort(dst, kind="stable")
+    assert np.array_equal(B.adaqp_plan_recv_order(dst), want)
+    assert np.array_equal(B.adaqp_plan_recv_order(dst[want]), np.arange(n))
+    order, seg_ptr = B.adaqp_plan_recv_segments(dst)
+    assert np.array_equal(order, want)
+    assert np.array_equal(seg_ptr, np.append(np.flatnonzero(np.diff(dst[want], prepend=dst[want[0]].astype(np.int64) - 1)), n))
+
+
+@pytest.mark.parametrize("span", [12_000_000, 2**31])
+def test_plan_recv_order_without_room(span):
+    """Scratch that cannot be had is no error, and no exception leaves the library."""
+    code = f"""
+import resource, numpy as np
+from paper_2306_01381_amd import binding as B
+dst = np.random.default_rng(1).integers(0, {span}, size=4_000_000).astype(np.int32)
+want = np.argsort(dst, kind="stable")
+B.adaqp_plan_recv_order(dst[:1000])
+pages = int(open("/proc/self/statm").read().split()[0])
+limit = pages * resource.getpagesize() + (28 << 20)     # the result fits, counters or keys do not
+resource.setrlimit(resource.RLIMIT_AS, (limit, limit))
+assert np.array_equal(B.adaqp_plan_recv_order(dst), want)
+print("same order")
+"""
+    done = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert done.returncode == 0 and "same order" in done.stdout, done.stderr[-2000:]
 
 
 def test_plan_recv_segments():
