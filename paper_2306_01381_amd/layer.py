@@ -75,16 +75,16 @@ class SendPlan:
             self.seg_ptr = torch.from_numpy(seg_ptr).to(device)
 
 
-def line_padded(a: np.ndarray, device, pad: bool = True) -> torch.Tensor:
+def line_padded(a: np.ndarray, device, pad: bool = True, spread: bool = False) -> torch.Tensor:
     """Uploads a [n, dim] fp32 matrix into rows whose pitch is a whole number of 128-byte lines (the layout
-    the kernels are built for) and returns the [n, dim] view; the padding columns are zero.  The number of lines is
-    never a multiple of four: an aggregation that takes the same lines of every row would find them in a quarter of the
-    L1's sets or fewer (256 columns, transposed graph: 0.84 ms at a pitch of 8 lines, 0.80 at 9)."""
+    the kernels are built for) and returns the [n, dim] view; the padding columns are zero.  With `spread` the number of
+    lines is never a multiple of four: an aggregation that takes the same lines of every row would find them in a quarter of
+    the L1's sets or fewer (256 columns, transposed graph: 0.84 ms at a pitch of 8 lines, 0.80 at 9)."""
     n, dim = a.shape
     ld = dim
     if pad:
         lines = (dim + 31) // 32
-        ld = 32 * (lines + 1 if lines % 4 == 0 else lines)
+        ld = 32 * (lines + 1 if spread and lines % 4 == 0 else lines)
     buf = torch.zeros((n, ld), dtype=torch.float32, device=device)
     view = buf[:, :dim]
     view.copy_(torch.from_numpy(a))
@@ -109,8 +109,13 @@ class LayerStep:
         self.rowptr = torch.from_numpy(p.rowptr).to(dev)
         self.col = torch.from_numpy(p.col).to(dev)
         self.val = torch.from_numpy(p.val).to(dev)
-        self.feat = line_padded(p.feat, dev, pad)
-        self.out = line_padded(np.zeros((p.n_rows, cfg.dim), dtype=np.float32), dev, pad)
+        # the tiled and panel kernels take whole rows of a column range and gain nothing from a spread pitch (58 000 rows,
+        # 28 M entries, 256 columns: step 1.60 ms at 8 lines, 1.63 at 9)
+        spread = not (pad and tiled is not False and any(
+            e > b and (tiled or B.adaqp_spmm_tiled_pays(e - b, int(p.rowptr[e] - p.rowptr[b])))
+            for b, e in (p.overlap_rows, p.dependent_rows)))
+        self.feat = line_padded(p.feat, dev, pad, spread)
+        self.out = line_padded(np.zeros((p.n_rows, cfg.dim), dtype=np.float32), dev, pad, spread)
         self.plan = SendPlan(cfg.dim, p.send_idx, p.bits, p.peer_of_slot, cfg.n_peers, p.halo_idx, dev,
                              add_segments=self.backward)
         n = self.plan.n
