@@ -1,4 +1,5 @@
-// Neighbour aggregation (Sec. 2.1 Eq. 3) on the line-padded layout, with the feature columns sliced over the XCDs.
+// Neighbour aggregation (Sec. 2.1 Eq. 3) with the feature columns sliced over the XCDs.  Made for the line-padded layout;
+// takes rows that start anywhere too.
 //
 // The gather is bound by what comes from behind the L2s: rows of H are drawn from a power law with no locality, every
 // XCD has a private 4 MB L2, and when all eight walk whole rows (1 KB and more) each holds the same few thousand
@@ -42,7 +43,8 @@ constexpr int kChunk = kPer * kWave;                // entries of a chunk: a who
 constexpr int kEnds = kWave - 1;                    // row ends of a chunk at most
 constexpr int32_t kNoEnd = 0x10000;                 // lies after every step of a chunk
 constexpr int kRowSteps = 8;                        // entries a row end counts for where shares are cut
-constexpr uint32_t kOutside = 0xFFFFFF00u;          // past the end of any buffer the kernel is launched with
+constexpr uint32_t kOutside = 0xFFFF0000u;          // past the end of any buffer the kernel is launched with, also with a
+                                                    // column offset (at most 8 KB) added
 constexpr int kNonTemporal = 2;                     // cache policy bits of a buffer load: nt
 constexpr int kRawBuffer = 0x00020000;              // buffer resource, last word: raw 32-bit data, no swizzle
 
@@ -139,8 +141,10 @@ __device__ __forceinline__ float ror8(float v)
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int32_t, v), 0x128, 0xF, 0xF, false));
 }
 
-// One wave's share of the path for one slice of VPL lines.
-template <int VPL, bool PACKED>
+// One wave's share of the path for one slice of VPL lines.  WHOLE: rows of H and out start on lines and have whole lines
+// of room.  Otherwise rows start anywhere (4-byte aligned) and end after a.dim columns: a lane whose four columns would
+// not end in the row takes the row's last four, and columns that two lanes hold are stored twice with the same bits.
+template <int VPL, bool PACKED, bool WHOLE>
 __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const int32_t item, Entry<PACKED> (*stages)[kChunk])
 {
     constexpr int kAhead = VPL >= 3 ? 2 : 8 / VPL;          // steps in flight: 6 to 8 KB per wave
@@ -169,21 +173,29 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
     if (j[1] < j[0]) j[1] = j[0];
 
     const int32_t c0 = first_line * kLine + gl * 4;         // first column of the lane's line 0
-    // one buffer per line of the slice
+    // one buffer per line of the slice; rows of any length: one buffer, and the lane's column in each line
     __amdgpu_buffer_rsrc_t rows[VPL];
+    uint32_t lane_off[VPL];
 #pragma unroll
-    for (int v = 0; v < VPL; ++v)
-        rows[v] = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(a.H + (first_line + v) * kLine), 0,
-            (int)(uint32_t)(a.n_cols * a.ldh * 4 - (first_line + v) * kLine * 4), kRawBuffer);
+    for (int v = 0; v < VPL; ++v) {
+        const int32_t begin = WHOLE ? (first_line + v) * kLine : 0;
+        rows[v] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.H + begin), 0,
+                                                    (int)(uint32_t)(a.n_cols * a.ldh * 4 - begin * 4), kRawBuffer);
+        lane_off[v] = WHOLE ? gl * 16 : (uint32_t)min(c0 + v * kLine, a.dim - 4) * 4;
+    }
     const auto packed_rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.packed), 0,
                                                                (int)(uint32_t)a.packed_bytes, kRawBuffer);
-    const uint32_t lane_off = gl * 16;
     const uint32_t pitch = (uint32_t)a.ldh * 4u;
 
     // After `sum_groups` lane l (and lane l + 32) holds column l of each line.
     const int line_col = lane & (kLine - 1);
     const int from_lane = ((line_col & 3) * 16 + line_col / 4) << 2;
+    auto column_of = [&](int v) {                           // the column lane l holds a sum of; negative: none of its own
+        const int32_t line = (first_line + v) * kLine;
+        if constexpr (WHOLE) return line + line_col;
+        const int32_t four = line + (line_col & ~3);
+        return four < a.dim ? min(four, a.dim - 4) + (line_col & 3) : -1;
+    };
     auto sum_groups = [&](const float4_t (&acc)[VPL], float (&out)[VPL]) {
 #pragma unroll
         for (int v = 0; v < VPL; ++v) {
@@ -260,23 +272,27 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
 
     // the ring: kAhead steps whose lines are on their way
     float4_t h[kAhead][VPL];
-    uint32_t words[kAhead][VPL];
+    uint32_t words[kAhead][VPL], words_up[kAhead][VPL];     // four codes, where rows end anywhere across two words
     Entry<PACKED> in_flight[kAhead];
+    auto packed_col = [&](int v) { return (uint32_t)a.col0 + (WHOLE ? (uint32_t)(c0 + v * kLine) : lane_off[v] / 4); };
     auto fetch = [&](auto tag, const Entry<PACKED> &en) {
         constexpr int U = decltype(tag)::value;
         in_flight[U] = en;
-        uint32_t off = en.off + lane_off;
         const uint32_t w = PACKED ? en.off & 3u : 0u;
-        if (PACKED && w != 0) off = kOutside;
 #pragma unroll
         for (int v = 0; v < VPL; ++v) {
+            const uint32_t off = PACKED && w != 0 ? kOutside : en.off + lane_off[v];
             h[U][v] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(rows[v], (int)off, 0, 0));
             if constexpr (PACKED) {
-                // one 32-bit word holds the four codes of a lane (4 * b <= 32 and divides 32)
+                // one 32-bit word holds the four codes of a lane whose first column is a multiple of four (4 * b <= 32 and
+                // divides 32)
                 const uint32_t last_word = (((uint32_t)a.full_dim << w) - 1) >> 5;
-                const uint32_t word = ((uint32_t)(a.col0 + c0 + v * kLine) << w) >> 5;
+                const uint32_t word = (packed_col(v) << w) >> 5;
                 words[U][v] = __builtin_amdgcn_raw_buffer_load_b32(
                     packed_rows, w != 0 ? (int)((en.off & ~3u) + 4 * min(word, last_word)) : (int)kOutside, 0, 0);
+                if constexpr (!WHOLE)
+                    words_up[U][v] = __builtin_amdgcn_raw_buffer_load_b32(
+                        packed_rows, w != 0 ? (int)((en.off & ~3u) + 4 * min(word + 1, last_word)) : (int)kOutside, 0, 0);
             }
         }
     };
@@ -287,7 +303,9 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
             const uint32_t w = in_flight[U].off & 3u;
             if (w != 0) {
                 const uint32_t b = 1u << w, mask = (1u << b) - 1u;
-                const uint32_t word = words[U][v] >> (((uint32_t)(a.col0 + c0 + v * kLine) << w) & 31u);
+                const uint32_t shift = (packed_col(v) << w) & 31u;
+                uint32_t word = words[U][v] >> shift;
+                if constexpr (!WHOLE) word = (uint32_t)(((uint64_t)words_up[U][v] << 32 | words[U][v]) >> shift);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const float scaled = (float)((word >> (k * b)) & mask) * in_flight[U].s;    // Eq. 5: product rounded,
@@ -307,8 +325,12 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
         sum_groups(acc, sum);
 #pragma unroll
         for (int v = 0; v < VPL; ++v) {
-            const int32_t c = (first_line + v) * kLine + line_col;
-            if (lane < kLine) __builtin_nontemporal_store(c < a.dim ? sum[v] : 0.0f, out_row + (uint32_t)c);
+            const int32_t c = column_of(v);
+            if constexpr (WHOLE) {
+                if (lane < kLine) __builtin_nontemporal_store(c < a.dim ? sum[v] : 0.0f, out_row + (uint32_t)c);
+            } else {                                        // lines are shared with other rows: left for the L2 to merge
+                if (lane < kLine && c >= 0) out_row[c] = sum[v];
+            }
             acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
         }
         out_row += a.ldo;
@@ -402,12 +424,12 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
         sum_groups(acc, sum);
 #pragma unroll
         for (int v = 0; v < VPL; ++v)
-            if (lane < kLine) a.carry[(int64_t)item * a.carry_ld + (first_line + v) * kLine + line_col] = sum[v];
+            if (lane < kLine && column_of(v) >= 0) a.carry[(int64_t)item * a.carry_ld + column_of(v)] = sum[v];
     }
     if (first_line == 0 && lane == 0) a.carry_row[item] = held ? i[1] : -1;
 }
 
-template <int VPL, bool PACKED>
+template <int VPL, bool PACKED, bool WHOLE>
 __global__ __launch_bounds__(kBlock, 2) void spmm_sliced_kernel(const SlicedArgs sa)
 {
     __shared__ Entry<PACKED> stages[kWavesPerBlock][2][kChunk];
@@ -426,10 +448,10 @@ __global__ __launch_bounds__(kBlock, 2) void spmm_sliced_kernel(const SlicedArgs
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int32_t item = blk * kWavesPerBlock + wave;
     const int live = min(VPL, sa.lines - slice * VPL);
-    if (live == VPL) walk_share<VPL, PACKED>(sa, slice * VPL, item, stages[wave]);
-    else if (VPL > 3 && live == 3) walk_share<3, PACKED>(sa, slice * VPL, item, stages[wave]);
-    else if (VPL > 2 && live == 2) walk_share<2, PACKED>(sa, slice * VPL, item, stages[wave]);
-    else walk_share<1, PACKED>(sa, slice * VPL, item, stages[wave]);
+    if (live == VPL) walk_share<VPL, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
+    else if (VPL > 3 && live == 3) walk_share<3, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
+    else if (VPL > 2 && live == 2) walk_share<2, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
+    else walk_share<1, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
 }
 
 }  // namespace
@@ -442,21 +464,23 @@ bool sliced_fits(const SpmmArgs &a)
            a.full_dim < (1 << 28);
 }
 
-hipError_t launch_sliced(const SpmmArgs &a, int64_t nnz_hint, bool skewed_columns, hipStream_t st, int32_t *n_carries_out)
+hipError_t launch_sliced(const SpmmArgs &a, int64_t nnz_hint, bool whole_lines, bool skewed_columns, hipStream_t st,
+                         int32_t *n_carries_out)
 {
     SlicedArgs sa;
     sa.s = a;
-    sa.lines = a.wdim / kLine;
+    sa.lines = (a.wdim + kLine - 1) / kLine;
     // Lines per slice: one or four.  With four, one LDS read, one address and one row end serve four loads (bare loop out of
     // L2: 28 TB/s against 21); with one, an L2 holds four times as many rows.  One pays where the rows are long enough
     // for their ends not to matter and the columns too many for an L2 to hold four lines of each: measured at 224
     // columns of power-law popularity, the two break even at 12 entries per row x 50 000 columns, 20 x 34 000, 40 x
     // 20 000 (150 entries x 50 000 columns 0.29 ms against 0.42; 5 entries x 100 000 columns 0.064 against 0.058).
     // Where a few columns hold most of the entries four lines of those fit anyway (196 000 columns used as often as
-    // Zipf(1.5) degrees say: 0.80 ms against 0.99).  Two per slice: only where even one line of each column is ten times what an L2 holds, and
+    // Zipf(1.5) degrees say: 0.80 ms against 0.99), and a line of a row that starts anywhere is two lines to fetch, four are
+    // five (16 entries x 90 000 columns, 301 wide: 197 us with four, 264 with one).  Two per slice: only where even one line of each column is ten times what an L2 holds, and
     // the lines come in pairs (269 000 columns of 10 lines: 0.360 ms against 0.375).
     const bool many = a.n_cols > kColumnsThatFit && nnz_hint / a.n_rows * a.n_cols > kOneLineProduct;
-    const int vpl = !many || skewed_columns ? 4 : (a.n_cols > kColumnsForTwo && sa.lines % 2 == 0 ? 2 : 1);
+    const int vpl = !many || skewed_columns || !whole_lines ? 4 : (a.n_cols > kColumnsForTwo && sa.lines % 2 == 0 ? 2 : 1);
     const int64_t slices = (sa.lines + vpl - 1) / vpl;
     const int64_t path = nnz_hint + (int64_t)a.n_rows * kRowSteps;
     // Two workgroups per CU with two or four lines, up to eight with one; each wave takes one share, of at least 256 steps of the
@@ -471,14 +495,15 @@ hipError_t launch_sliced(const SpmmArgs &a, int64_t nnz_hint, bool skewed_column
     const int64_t narrow = sa.lines % vpl ? sa.lines % vpl : vpl;
     const int64_t per_xcd = std::min(n_blocks * slices, (n_blocks * sa.lines / kXcds + 1) / narrow + 2);
     const dim3 grid((unsigned)(per_xcd * kXcds));
-#define ADAQP_SLICED(V)                                                                                          \
+#define ADAQP_SLICED(V, WHOLE)                                                                                   \
     do {                                                                                                         \
-        if (a.slot_of_row) hipLaunchKernelGGL((spmm_sliced_kernel<V, true>), grid, dim3(kBlock), 0, st, sa);     \
-        else hipLaunchKernelGGL((spmm_sliced_kernel<V, false>), grid, dim3(kBlock), 0, st, sa);                  \
+        if (a.slot_of_row) hipLaunchKernelGGL((spmm_sliced_kernel<V, true, WHOLE>), grid, dim3(kBlock), 0, st, sa); \
+        else hipLaunchKernelGGL((spmm_sliced_kernel<V, false, WHOLE>), grid, dim3(kBlock), 0, st, sa);           \
     } while (0)
-    if (vpl == 1) ADAQP_SLICED(1);
-    else if (vpl == 2) ADAQP_SLICED(2);
-    else ADAQP_SLICED(4);
+    if (!whole_lines) ADAQP_SLICED(4, false);
+    else if (vpl == 1) ADAQP_SLICED(1, true);
+    else if (vpl == 2) ADAQP_SLICED(2, true);
+    else ADAQP_SLICED(4, true);
 #undef ADAQP_SLICED
     *n_carries_out = sa.n_blocks * kWavesPerBlock;
     return hipGetLastError();

@@ -371,6 +371,23 @@ def test_spmm_sliced_edges(oracle, dim, n_cols):
     assert np.all(np.abs(out.cpu().numpy()[:, :dim].astype(np.float64) - want) <= SPMM_RTOL * mag + 1e-30)
 
 
+@pytest.mark.parametrize("dim,ldh,ldo", [(4, 4, 4), (5, 7, 5), (31, 31, 33), (33, 33, 33), (97, 97, 98), (100, 100, 100),
+                                         (128, 129, 128), (130, 160, 130), (131, 131, 160), (301, 301, 301),
+                                         (515, 515, 515), (516, 517, 516), (517, 517, 517)])   # chunks end in 3, 4, 5 columns
+def test_spmm_sliced_unpadded(oracle, dim, ldh, ldo):
+    """Rows that start anywhere and share lines: the last columns of a row, nothing read or written beside it."""
+    _say(f"spmm sliced unpadded dim={dim} ldh={ldh} ldo={ldo}")
+    rng = np.random.default_rng(dim)
+    degs = np.concatenate([np.zeros(70), np.arange(40), [383, 384, 385, 8, 16, 0, 0], np.full(60, 23), [700, 5, 600],
+                           rng.integers(40, 160, size=700), np.zeros(3)]).astype(int)      # long rows: the sliced kernel
+    n_rows, n_cols = degs.shape[0], 700
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, degs)
+    H = np.full((n_cols, ldh), np.nan, dtype=np.float32)    # what lies between the rows must never reach a sum
+    H[:, :dim] = rng.standard_normal((n_cols, dim), dtype=np.float32)
+    _check_spmm(oracle, rowptr, col, val, 0, n_rows, H, dim, ldo=ldo)
+    _check_spmm(oracle, rowptr, col, val, 65, n_rows - 1, H, dim, nnz_range="exact", ldo=ldo)
+
+
 def test_spmm_degenerate(oracle):
     _say("spmm degenerate")
     rng = np.random.default_rng(1)
