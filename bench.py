@@ -53,7 +53,7 @@ def parse_args():
     ap.add_argument("--no-panels", action="store_true",
                     help="keep the longest rows in the L2-tiled kernel instead of dense panels on the matrix cores")
     ap.add_argument("--no-tiled", action="store_true",
-                    help="aggregate with the merge-path kernel even where the L2-tiled kernel would be chosen")
+                    help="aggregate along the merge path (sliced kernel) even where the L2-tiled kernel would be chosen")
     ap.add_argument("--calibrate", action="store_true",
                     help="also launch a plain elementwise kernel of known size (reads and writes 256 MiB): the "
                          "reference dispatch that scales the FETCH_SIZE / WRITE_SIZE counters of a --pmc run")
@@ -390,7 +390,7 @@ def measure_config(name, args, headline, B, torch, np):
 
     (ob, oe), (db_, de) = p.overlap_rows, p.dependent_rows
 
-    # the same launches the step makes: tiled over the L2 caches where LayerStep planned tiles, else merge-path
+    # the same launches the step makes: tiled over the L2 caches where LayerStep planned tiles, else along the merge path
     def spmm_overlap(i):
         if L.tile_off_overlap is not None:
             B.adaqp_spmm_csr_tiled(L.rowptr, L.col, L.val, ob, oe, L.feat, dim, L.out, L.tile_off_overlap,
@@ -480,7 +480,7 @@ def measure_config(name, args, headline, B, torch, np):
         t_all = event_time_ms(st, spmm_all, sreps)
         kernels["spmm_all_rows_one_launch"] = {"ms": t_all, "edges": p.nnz, "edges_per_s": p.nnz / t_all * 1e3,
                                                "kernel": ("tiled + panels" if panel_parts else "tiled") if tiled_both
-                                               else "merge-path"}
+                                               else "sliced"}
         del ws_all
         if tiled:
             t_m = event_time_ms(st, spmm_merge_both, max(3, sreps // 2))
@@ -533,7 +533,7 @@ def measure_config(name, args, headline, B, torch, np):
         avg_ms = t_both / 2
         frac_hbm = primary_gbps / HBM_PEAK_GBPS
         roofline = {
-            "kernel": "spmm_tiled_kernel" if tiled else "spmm_merge_kernel",
+            "kernel": "spmm_tiled_kernel" if tiled else "spmm_sliced_kernel",
             "bound": "hbm" if frac_hbm <= 1.0 else "l2",
             "achieved": primary_gbps, "peak": HBM_PEAK_GBPS if frac_hbm <= 1.0 else GATHER_RATE_GBPS, "unit": "GB/s",
             "frac": frac_hbm if frac_hbm <= 1.0 else primary_gbps / GATHER_RATE_GBPS, "traffic": None,
