@@ -28,6 +28,7 @@
 #include <algorithm>
 
 #include "spmm_common.hpp"
+#include "spmm_rules.hpp"
 
 namespace adaqp {
 namespace {
@@ -43,8 +44,6 @@ constexpr int kChunk = kPer * kWave;                // entries of a chunk: a who
 constexpr int kEnds = kWave - 1;                    // row ends of a chunk at most
 constexpr int32_t kNoEnd = 0x10000;                 // lies after every step of a chunk
 constexpr int kRowSteps = 8;                        // entries a row end counts for where shares are cut
-constexpr uint32_t kOutside = 0xFFFF0000u;          // past the end of any buffer the kernel is launched with, also with a
-                                                    // column offset (at most 8 KB) added
 constexpr int kNonTemporal = 2;                     // cache policy bits of a buffer load: nt
 constexpr int kRawBuffer = 0x00020000;              // buffer resource, last word: raw 32-bit data, no swizzle
 
@@ -458,10 +457,7 @@ __global__ __launch_bounds__(kBlock, 2) void spmm_sliced_kernel(const SlicedArgs
 
 bool sliced_fits(const SpmmArgs &a)
 {
-    // offsets of rows of H and of packed rows are kept in 32 bits
-    const int64_t limit = (int64_t)kOutside;
-    return a.n_cols <= INT32_MAX && a.ldh < limit / 4 && a.n_cols * a.ldh < limit / 4 && (!a.slot_of_row || a.packed_bytes < limit) &&
-           a.full_dim < (1 << 28);
+    return sliced_takes(a.nnz, a.n_cols, a.ldh, a.slot_of_row != nullptr, a.packed_bytes, a.full_dim);
 }
 
 hipError_t launch_sliced(const SpmmArgs &a, int64_t nnz_hint, bool whole_lines, bool skewed_columns, hipStream_t st,

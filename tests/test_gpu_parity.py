@@ -416,6 +416,20 @@ def test_spmm_degenerate(oracle):
     assert np.all(got == 7.0)
 
 
+@pytest.mark.parametrize("dim", [16, 33, 64, 300, 2080])
+def test_spmm_no_columns(dim):
+    """A matrix without rows, of every pitch: nothing is read of it, every row of out is zero."""
+    _say(f"spmm no columns dim={dim}")
+    for ld in (dim, (dim + 31) // 32 * 32, (dim + 31) // 32 * 32 + 32):
+        out = torch.full((50, ld), 7.0, device=DEV)
+        ws = torch.empty(max(B.adaqp_spmm_workspace_bytes(50, 0, dim), 256), dtype=torch.uint8, device=DEV)
+        B.adaqp_spmm_csr(torch.zeros(51, dtype=torch.int64, device=DEV), torch.zeros(0, dtype=torch.int32, device=DEV),
+                         torch.zeros(0, device=DEV), 0, 50, torch.zeros((0, ld), device=DEV), dim, out, ws)
+        torch.cuda.synchronize()
+        zero_to = _padded_cols(dim, ld)
+        assert bool((out[:, :zero_to] == 0.0).all()) and bool((out[:, zero_to:] == 7.0).all())
+
+
 def test_spmm_is_deterministic(oracle):
     _say("spmm determinism")
     p = make_partition(CONFIGS["c0"])

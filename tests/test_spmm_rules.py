@@ -1,0 +1,53 @@
+"""Arithmetic of the sliced aggregation, compiled by the host compiler from the header that the kernel uses."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2306_01381_amd", "csrc")
+
+
+def _run(tmp_path, body):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text('#include <stdio.h>\n#include "spmm_rules.hpp"\nusing namespace adaqp;\n'
+                   '#define CHECK(x) do { if (!(x)) { printf("line %d: %s\\n", __LINE__, #x); return 1; } } while (0)\n'
+                   "int main() {\n" + body + "\nreturn 0; }\n")
+    subprocess.run([cxx, "-std=c++17", "-Wall", "-Werror", "-I", CSRC, "-o", str(exe), str(src)], check=True)
+    done = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert done.returncode == 0, done.stdout
+
+
+def test_buffer_extent(tmp_path):
+    """No extent holds the offset that stands for "nothing to fetch", whatever column is added to it; every row's columns
+    lie inside."""
+    _run(tmp_path, """
+    const int64_t cols[] = {0, 1, 2, 5, 1000, 1 << 20};
+    const int64_t pitches[] = {32, 64, 608, 2048, 2080, 1000};
+    for (int64_t n : cols) for (int64_t ld : pitches) {
+        if (n * ld * 4 >= (int64_t)kOutside) continue;
+        for (int32_t begin = 0; begin < 2048; begin += 32) {
+            const uint32_t e = buffer_extent(n, ld, begin);
+            CHECK(e <= kOutside);
+            CHECK(n > 0 || e == 0);
+            if (n > 0 && begin + 32 <= ld) CHECK((int64_t)e >= ((n - 1) * ld + 32) * 4 && (int64_t)e <= n * ld * 4);
+        }
+    }
+    """)
+
+
+def test_what_the_sliced_kernel_takes(tmp_path):
+    """Never a call whose arrays may be NULL (no entries, no columns), nor one whose offsets do not fit 32 bits."""
+    _run(tmp_path, """
+    CHECK(sliced_takes(1, 1, 32, false, 0, 32));
+    CHECK(!sliced_takes(0, 0, 64, false, 0, 64) && !sliced_takes(0, 0, 64, true, 4, 64));
+    CHECK(!sliced_takes(0, 5, 64, false, 0, 64) && !sliced_takes(5, 0, 64, false, 0, 64));
+    const int64_t floats = (int64_t)kOutside / 4;
+    CHECK(sliced_takes(9, floats / 32 - 1, 32, false, 0, 32) && !sliced_takes(9, floats / 32 + 1, 32, false, 0, 32));
+    CHECK(!sliced_takes(9, (int64_t)1 << 33, 32, false, 0, 32) && !sliced_takes(9, 2, (int64_t)1 << 62, false, 0, 32));
+    CHECK(sliced_takes(9, 10, 32, true, 4096, 32) && !sliced_takes(9, 10, 32, true, (int64_t)1 << 32, 32));
+    """)
