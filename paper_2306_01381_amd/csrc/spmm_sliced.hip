@@ -237,8 +237,9 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
         const auto vals = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.val + base + c.ent0), 0, c.n_ent * 4, kRawBuffer);
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {                    // streamed: keep the caches for H
-            st_col[k] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(cols, lane * 4, k * kWave * 4, kNonTemporal);
-            st_val[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vals, lane * 4, k * kWave * 4, kNonTemporal));
+            const int at = lane * 4 + k * kWave * 4;        // all of it here: the scalar offset is outside the range check
+            st_col[k] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(cols, at, 0, kNonTemporal);
+            st_val[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vals, at, 0, kNonTemporal));
         }
     };
     auto stage = [&](const Chunk &c, Entry<PACKED> *ent) {

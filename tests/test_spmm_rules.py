@@ -1,5 +1,6 @@
 """Arithmetic of the sliced aggregation, compiled by the host compiler from the header that the kernel uses."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -51,3 +52,27 @@ def test_what_the_sliced_kernel_takes(tmp_path):
     CHECK(!sliced_takes(9, (int64_t)1 << 33, 32, false, 0, 32) && !sliced_takes(9, 2, (int64_t)1 << 62, false, 0, 32));
     CHECK(sliced_takes(9, 10, 32, true, 4096, 32) && !sliced_takes(9, 10, 32, true, (int64_t)1 << 32, 32));
     """)
+
+
+def test_buffer_loads_carry_no_scalar_offset():
+    """The scalar offset of a raw buffer load is not part of what is compared with the buffer's extent: a load that relies
+    on that comparison must not use it."""
+    calls = 0
+    for name in sorted(os.listdir(CSRC)):
+        if not name.endswith((".hip", ".hpp")):
+            continue
+        with open(os.path.join(CSRC, name)) as f:
+            text = f.read()
+        for found in re.finditer(r"__builtin_amdgcn_raw_buffer_load_\w+\(", text):
+            args, depth, at = [""], 0, found.end()
+            while depth >= 0:
+                c = text[at]
+                depth += (c in "([{") - (c in ")]}")
+                if depth == 0 and c == ",":
+                    args.append("")
+                elif depth >= 0:
+                    args[-1] += c
+                at += 1
+            calls += 1
+            assert len(args) == 4 and args[2].strip() == "0", f"{name}: scalar offset {args[2].strip()}"
+    assert calls > 0
