@@ -316,13 +316,31 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
         return x;
     };
 
+    // Sums of the open row: acc what the present chunk has given so far, per group; before what earlier chunks of the share
+    // gave, as `sum_groups` leaves it.  No addition chain is longer than a chunk's 48 steps, the chunks of a share, or the
+    // shares of a row (one running sum over a share would be thousands of terms long and rounds accordingly).
     float4_t acc[VPL];
+    float before[VPL];
+    bool has_before = false;
 #pragma unroll
-    for (int v = 0; v < VPL; ++v) acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int v = 0; v < VPL; ++v) {
+        acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        before[v] = 0.0f;
+    }
+    auto take_sums = [&](float (&sum)[VPL]) {               // and start anew
+        sum_groups(acc, sum);
+        if (has_before) {
+#pragma unroll
+            for (int v = 0; v < VPL; ++v) sum[v] = before[v] + sum[v];
+            has_before = false;
+        }
+#pragma unroll
+        for (int v = 0; v < VPL; ++v) acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    };
     float *out_row = a.out + (int64_t)i[0] * a.ldo;         // the rows of a share end one after the other
     auto finish_row = [&]() {
         float sum[VPL];
-        sum_groups(acc, sum);
+        take_sums(sum);
 #pragma unroll
         for (int v = 0; v < VPL; ++v) {
             const int32_t c = column_of(v);
@@ -331,7 +349,6 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
             } else {                                        // lines are shared with other rows: left for the L2 to merge
                 if (lane < kLine && c >= 0) out_row[c] = sum[v];
             }
-            acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
         }
         out_row += a.ldo;
     };
@@ -413,6 +430,11 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
             });
         }
         if (!more) break;
+        float sum[VPL];                                     // the open row goes on in the next chunk
+        take_sums(sum);
+#pragma unroll
+        for (int v = 0; v < VPL; ++v) before[v] = sum[v];
+        has_before = true;
         cur = next;
         buf ^= 1;
     }
@@ -421,7 +443,7 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
     const bool held = i[1] < a.n_rows && j[1] > (began > j[0] ? began : j[0]);
     if (held) {
         float sum[VPL];
-        sum_groups(acc, sum);
+        take_sums(sum);
 #pragma unroll
         for (int v = 0; v < VPL; ++v)
             if (lane < kLine && column_of(v) >= 0) a.carry[(int64_t)item * a.carry_ld + column_of(v)] = sum[v];

@@ -416,6 +416,26 @@ def test_spmm_degenerate(oracle):
     assert np.all(got == 7.0)
 
 
+@pytest.mark.parametrize("dim,n_cols", [(608, 64), (608, 12_000), (601, 64)])       # four lines per slice; one; rows that share lines
+def test_spmm_sliced_long_sums(dim, n_cols):
+    """Rows far longer than a wave's share of a launch with few shares (16 000 entries each): no addition chain is longer than
+    a chunk's 48 steps per group, the chunks of a share (43) or the shares of a row (8), plus the three additions across
+    the groups and one between chain and chain.  The term is one whose running sum always rounds the same way (2 000
+    additions: 3e-5 off), so that the bound is what is measured."""
+    _say(f"spmm sliced long sums dim={dim} n_cols={n_cols}")
+    n_rows, degree, term = 66, 100_000, np.float32(1.9876709)
+    rowptr = torch.arange(n_rows + 1, dtype=torch.int64, device=DEV) * degree
+    col = torch.arange(n_rows * degree, dtype=torch.int32, device=DEV) % n_cols
+    val = torch.ones(n_rows * degree, device=DEV)
+    H = torch.full((n_cols, dim), float(term), device=DEV)
+    out = torch.full((n_rows, dim), 7.0, device=DEV)
+    ws = torch.empty(B.adaqp_spmm_workspace_bytes(n_rows, n_rows * degree, dim), dtype=torch.uint8, device=DEV)
+    B.adaqp_spmm_csr(rowptr, col, val, 0, n_rows, H, dim, out, ws)
+    torch.cuda.synchronize()
+    error = float((out.double() / (degree * float(term)) - 1).abs().max())
+    assert error <= (48 + 43 + 8 + 3 + 3) * 2.0 ** -24, error
+
+
 @pytest.mark.parametrize("dim", [16, 33, 64, 300, 2080])
 def test_spmm_no_columns(dim):
     """A matrix without rows, of every pitch: nothing is read of it, every row of out is zero."""
