@@ -388,7 +388,12 @@ typedef enum adaqp_schedule {
     ADAQP_SERIAL   = 0, /* everything on stream_msg in program order */
     ADAQP_ISOLATED = 1, /* Fig. 7: the overlapped SpMM starts only once quantisation has finished, so it
                            overlaps the transfer (here: the loop-back copy) and nothing else by design */
-    ADAQP_FREE     = 2  /* the overlapped SpMM starts at once on stream_agg and may overlap quantisation */
+    ADAQP_FREE     = 2, /* the overlapped SpMM starts at once on stream_agg and may overlap quantisation */
+    ADAQP_CHAIN    = 3  /* for a caller with nothing to overlap: as SERIAL, but where neither row range has a tile
+                           table, the overlap range ends where the dependent one begins and one of the two
+                           workspaces holds adaqp_spmm_workspace_bytes of both ranges together, they are
+                           aggregated in one launch.  Its sums may be cut differently (other rounding).
+                           SERIAL and CHAIN use neither stream_agg nor the events */
 } adaqp_schedule;
 
 typedef enum adaqp_direction {
@@ -459,16 +464,14 @@ typedef struct adaqp_layer_desc {
     void *workspace_overlap_dev;   int64_t workspace_overlap_bytes;
     void *workspace_dependent_dev; int64_t workspace_dependent_bytes;
     void *stream_msg;           /* message path and dependent aggregation */
-    void *stream_agg;           /* overlapped aggregation; joined back into stream_msg before returning */
-    void *event_fork;           /* two hipEvent_t created by the caller (timing may be disabled) */
+    void *stream_agg;           /* ISOLATED, FREE: overlapped aggregation; joined back into stream_msg before returning */
+    void *event_fork;           /* ISOLATED, FREE: two hipEvent_t created by the caller (timing may be disabled) */
     void *event_join;
 } adaqp_layer_desc;
 
 /* Enqueues one layer step.  On return all work has been enqueued and stream_msg has been made to wait for
- * stream_agg, so synchronising stream_msg completes the step.  The three schedules give bit-identical
- * results.  A step whose transfer is too short to hide anything behind (packed_bytes up to 64 MB, no tile tables) runs on
- * stream_msg alone in every schedule; if the overlap range ends where the dependent one begins and one of the two
- * workspaces holds adaqp_spmm_workspace_bytes of both ranges together, they are then aggregated in one launch.
+ * stream_agg (ISOLATED, FREE), so synchronising stream_msg completes the step.  Three schedules give bit-identical
+ * results (SERIAL, ISOLATED, FREE).
  * ISOLATED and FREE only overlap anything if stream_msg and stream_agg sit on different hardware queues.  HIP maps
  * the streams of a process onto a few hardware queues (four by default): in a process that has created more
  * streams than that, the two may share a queue, and the step then takes the SERIAL time (same results).  A caller

@@ -18,7 +18,7 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libadaqp.so")
 
 OK, EINVAL, EBITS, ESIZE, EHIP = 0, -1, -2, -3, -4
-SERIAL, ISOLATED, FREE = 0, 1, 2
+SERIAL, ISOLATED, FREE, CHAIN = 0, 1, 2, 3
 FORWARD, BACKWARD = 0, 1
 
 _i64, _i32, _u64, _vp = ctypes.c_int64, ctypes.c_int32, ctypes.c_uint64, ctypes.c_void_p

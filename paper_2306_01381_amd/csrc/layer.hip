@@ -141,12 +141,13 @@ extern "C" int adaqp_plan_recv_segments(int64_t n, const int32_t *dst_idx_host, 
 
 namespace {
 
+bool two_streams(const adaqp_layer_desc *d) { return d->schedule == ADAQP_ISOLATED || d->schedule == ADAQP_FREE; }
+
 int check_desc(const adaqp_layer_desc *d)
 {
     if (!d) return ADAQP_EINVAL;
     if (d->direction != ADAQP_FORWARD && d->direction != ADAQP_BACKWARD) return ADAQP_EINVAL;
-    if (d->schedule != ADAQP_SERIAL && d->schedule != ADAQP_ISOLATED && d->schedule != ADAQP_FREE)
-        return ADAQP_EINVAL;
+    if (d->schedule < ADAQP_SERIAL || d->schedule > ADAQP_CHAIN) return ADAQP_EINVAL;
     if (d->dim <= 0 || d->ld < d->dim || d->ldo < d->dim || d->n_send < 0 || d->packed_bytes < 0 || d->nnz < 0)
         return ADAQP_EINVAL;
     if (d->overlap_begin < 0 || d->overlap_end < d->overlap_begin || d->dependent_begin < 0 ||
@@ -173,7 +174,7 @@ int check_desc(const adaqp_layer_desc *d)
             !p->panel_piece_dev)
             return ADAQP_EINVAL;
     }
-    if (d->schedule != ADAQP_SERIAL) {
+    if (two_streams(d)) {
         if (!d->event_fork || !d->event_join) return ADAQP_EINVAL;
         if (d->stream_msg == d->stream_agg) return ADAQP_EINVAL;
         // the two aggregations run at the same time: they need separate scratch
@@ -305,43 +306,39 @@ int loop_back(const adaqp_layer_desc *d, hipStream_t st)
     return ADAQP_OK;
 }
 
-// Where the second stream has nothing to give, the step runs on stream_msg alone, and row ranges that touch are aggregated
-// in one launch.  What a second stream can hide is the transfer, here a copy of packed_bytes: 64 MB take about 25 us.  Its
-// price is a fork and a join (20-30 us of the host, several of the GPU) and two gathers that compete for the L2s and
-// what is behind them.  Two streams against one, measured: 2 000 nodes 61 us, 28; 50 000-node backward step 141, 111;
-// 179 000 nodes, 12 MB sent, 438, 409; 306 000 nodes, 8 MB sent, 1151, 1079; 196 000-node backward step, 18 MB sent,
-// 895, 875.  Ranges with tile tables keep two streams: their panel and tiled kernels run side by side.  The rule looks at
-// sizes only, so that every schedule gives the same bits.
-constexpr int64_t kOneStreamBytes = (int64_t)64 << 20;
-
-bool one_stream(const adaqp_layer_desc *d)
-{
-    return !d->tile_off_overlap_dev && !d->tile_off_dependent_dev && d->packed_bytes <= kOneStreamBytes;
-}
-
 int64_t range_nnz(const adaqp_layer_desc *d, bool overlap_part)
 {
     const int64_t nz = overlap_part ? d->overlap_nnz : d->dependent_nnz;
     return nz < 0 || nz > d->nnz ? d->nnz : nz;
 }
 
-// Both ranges: in one launch if they are neighbours and one of the workspaces can take them.  With the received rows still
-// packed that launch looks a slot up for every column, also those of rows that cannot have one: a step that
-// de-quantises first must give the same bits, so it has to be cut the same way.
+int64_t both_nnz(const adaqp_layer_desc *d) { return std::min(range_nnz(d, true) + range_nnz(d, false), d->nnz); }
+
+bool larger_is_overlap(const adaqp_layer_desc *d) { return d->workspace_overlap_bytes >= d->workspace_dependent_bytes; }
+
+// CHAIN: both row ranges in one launch, if neither has tiles, they are neighbours and one of the workspaces can take them.  A
+// second aggregation is two launches and another start and end on a part empty GPU (SERIAL against CHAIN: 2 000 rows 45 us,
+// 27; 24 000 rows 58, 42; 50 000-row backward step 120, 108; 179 000 rows 425, 419).
+bool one_launch(const adaqp_layer_desc *d)
+{
+    if (d->schedule != ADAQP_CHAIN || d->tile_off_overlap_dev || d->tile_off_dependent_dev) return false;
+    if (d->overlap_end != d->dependent_begin || d->overlap_end == d->overlap_begin || d->dependent_end == d->dependent_begin)
+        return false;
+    const int64_t rows = d->dependent_end - d->overlap_begin;
+    int64_t need = 0;
+    if (rows > INT32_MAX - 1 || adaqp_spmm_workspace_bytes(rows, both_nnz(d), d->dim, &need) != ADAQP_OK) return false;
+    return larger_is_overlap(d) ? d->workspace_overlap_dev && d->workspace_overlap_bytes >= need
+                                : d->workspace_dependent_dev && d->workspace_dependent_bytes >= need;
+}
+
+// With the received rows still packed the launch looks a slot up for every column, also those of rows that cannot have one: a
+// step that de-quantises first must give the same bits, so it has to be cut the same way.
 int aggregate_both(const adaqp_layer_desc *d, hipStream_t st)
 {
-    if (d->overlap_end == d->dependent_begin && d->overlap_end > d->overlap_begin && d->dependent_end > d->dependent_begin) {
-        const int64_t nz = std::min(range_nnz(d, true) + range_nnz(d, false), d->nnz);
-        int64_t need = 0;
-        const int rc = adaqp_spmm_workspace_bytes(d->dependent_end - d->overlap_begin, nz, d->dim, &need);
-        if (rc != ADAQP_OK) return rc;
-        const bool first = d->workspace_overlap_bytes >= d->workspace_dependent_bytes;
-        void *ws = first ? d->workspace_overlap_dev : d->workspace_dependent_dev;
-        const int64_t wsb = first ? d->workspace_overlap_bytes : d->workspace_dependent_bytes;
-        if (ws && wsb >= need) return aggregate_range(d, d->overlap_begin, d->dependent_end, nz, fused_receive(d), ws, wsb, st);
-    }
-    const int rc = aggregate_rows(d, true, st);
-    return rc != ADAQP_OK ? rc : aggregate_rows(d, false, st);
+    const bool first = larger_is_overlap(d);
+    return aggregate_range(d, d->overlap_begin, d->dependent_end, both_nnz(d), fused_receive(d),
+                           first ? d->workspace_overlap_dev : d->workspace_dependent_dev,
+                           first ? d->workspace_overlap_bytes : d->workspace_dependent_bytes, st);
 }
 
 int quantise(const adaqp_layer_desc *d, hipStream_t st)
@@ -368,15 +365,6 @@ int receive(const adaqp_layer_desc *d, hipStream_t st)
     return adaqp_unpack_dequant_add(d->recv_packed_dev, d->packed_bytes, d->recv_params_dev, d->bits_dev, d->row_offset_dev,
                                     d->halo_idx_dev, d->n_send, d->recv_seg_order_dev, d->recv_seg_ptr_dev, d->n_recv_seg,
                                     d->dim, d->out_dev, std::max(d->dependent_end, d->overlap_end), d->ldo, st);
-}
-
-int one_stream_step(const adaqp_layer_desc *d, hipStream_t st)
-{
-    int rc = ADAQP_OK;
-    if (d->direction == ADAQP_BACKWARD && (rc = aggregate_both(d, st)) != ADAQP_OK) return rc;
-    if ((rc = quantise(d, st)) != ADAQP_OK || (rc = loop_back(d, st)) != ADAQP_OK) return rc;
-    if ((rc = receive(d, st)) != ADAQP_OK) return rc;
-    return d->direction == ADAQP_FORWARD ? aggregate_both(d, st) : ADAQP_OK;
 }
 
 }  // namespace
@@ -412,16 +400,16 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
     }
 
     hipStream_t msg = (hipStream_t)d->stream_msg;
-    if (one_stream(d)) return one_stream_step(d, msg);
-    hipStream_t agg = d->schedule == ADAQP_SERIAL ? msg : (hipStream_t)d->stream_agg;
+    hipStream_t agg = two_streams(d) ? (hipStream_t)d->stream_agg : msg;
     hipEvent_t fork = (hipEvent_t)d->event_fork, join = (hipEvent_t)d->event_join;
     const bool forward = d->direction == ADAQP_FORWARD;
     const bool both_tiled = d->tile_off_overlap_dev && d->tile_off_dependent_dev;
-    const bool paired = forward && both_tiled && d->schedule != ADAQP_SERIAL &&
+    const bool joint = one_launch(d);
+    const bool paired = forward && both_tiled && two_streams(d) &&
                         (has_panels(d, true) || has_panels(d, false));
     bool forked = false;
     auto fork_now = [&]() -> int {
-        if (d->schedule == ADAQP_SERIAL) return ADAQP_OK;
+        if (!two_streams(d)) return ADAQP_OK;
         ADAQP_HIP_TRY(hipEventRecord(fork, msg));
         ADAQP_HIP_TRY(hipStreamWaitEvent(agg, fork, 0));
         forked = true;
@@ -459,8 +447,10 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
         }
         ADAQP_STEP(loop_back(d, msg));
         ADAQP_STEP(receive(d, msg));
-        if (d->schedule == ADAQP_SERIAL) ADAQP_STEP(aggregate(d, true, msg));
-        if (paired) {
+        if (!two_streams(d) && !joint) ADAQP_STEP(aggregate(d, true, msg));
+        if (joint) {
+            ADAQP_STEP(aggregate_both(d, msg));
+        } else if (paired) {
             // a panel kernel (matrix cores) and a tiled kernel (vector-memory pipeline) fill each other's gaps:
             // both tiled launches on the second stream, one after the other, both panel launches here
             ADAQP_STEP(agg_waits_for_msg());                            // the halo rows are in place
@@ -481,14 +471,14 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
             ADAQP_STEP(aggregate(d, true, agg));
             if (both_tiled) ADAQP_STEP(join_now());         // as in the forward step: one tiled launch at a time
         }
-        ADAQP_STEP(aggregate(d, false, msg));
+        ADAQP_STEP(joint ? aggregate_both(d, msg) : aggregate(d, false, msg));
         ADAQP_STEP(quantise(d, msg));
         if (d->schedule == ADAQP_ISOLATED) {
             ADAQP_STEP(fork_now());
             ADAQP_STEP(aggregate(d, true, agg));
         }
         ADAQP_STEP(loop_back(d, msg));
-        if (d->schedule == ADAQP_SERIAL) ADAQP_STEP(aggregate(d, true, msg));
+        if (!two_streams(d) && !joint) ADAQP_STEP(aggregate(d, true, msg));
         // the received gradients are added to rows that the local aggregation also writes: join first
         ADAQP_STEP(join_now());
         ADAQP_STEP(receive(d, msg));

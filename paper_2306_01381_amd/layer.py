@@ -14,6 +14,11 @@ import torch
 from . import binding as B
 from .synth import Partition, alpha_sq_stand_in
 
+# What a second stream can hide is the transfer: the loop-back copy of this many bytes takes about 25 us.  Its price is a fork and
+# a join (about 25 us), a second aggregation, and two gathers that compete for the L2s and what is behind them (ISOLATED
+# against CHAIN: 2 000 rows 42 us, 27; 24 000 rows 64, 42; 50 000-row backward step 141, 108; 179 000 rows 435, 419).
+CHAIN_BYTES = 64 << 20
+
 _hip: Optional[ctypes.CDLL] = None
 
 
@@ -149,7 +154,7 @@ class LayerStep:
         min_row_o, min_row_d = panel_min_row if isinstance(panel_min_row, tuple) else (panel_min_row, panel_min_row)
         ws_o = B.adaqp_spmm_workspace_bytes(oe - ob, self.overlap_nnz, cfg.dim)
         ws_d = B.adaqp_spmm_workspace_bytes(de - db, self.dependent_nnz, cfg.dim)
-        if oe == db:        # a step without tiles aggregates both ranges in one launch, if this workspace can take them
+        if oe == db:        # CHAIN aggregates both ranges in one launch, if this workspace can take them
             ws_o = max(ws_o, B.adaqp_spmm_workspace_bytes(de - ob, self.overlap_nnz + self.dependent_nnz, cfg.dim))
         if pad and tiled is not False:
             if oe > ob and (tiled or B.adaqp_spmm_tiled_pays(oe - ob, self.overlap_nnz)):
@@ -232,9 +237,16 @@ class LayerStep:
         d.event_fork, d.event_join = self.event_fork.handle, self.event_join.handle
         return d
 
-    def run(self, schedule: int = B.ISOLATED) -> None:
-        """Enqueues one layer step; synchronise stream_msg to wait for it."""
-        B.adaqp_layer_step(self.desc(schedule))
+    def default_schedule(self) -> int:
+        """CHAIN where a second stream has nothing to hide or to pair, else ISOLATED."""
+        tiled = self.tile_off_overlap is not None or (self.tile_off_dependent is not None and not self.fused_receive)
+        return B.ISOLATED if tiled or self.plan.packed_bytes > CHAIN_BYTES else B.CHAIN
+
+    def run(self, schedule: Optional[int] = None) -> None:
+        """Enqueues one layer step; synchronise stream_msg to wait for it.  Without a schedule the step takes the one of
+        default_schedule(): work that a caller queues on stream_agg itself is ordered with such a step through stream_msg
+        only.  A schedule that is given is kept."""
+        B.adaqp_layer_step(self.desc(self.default_schedule() if schedule is None else schedule))
 
     def synchronize(self) -> None:
         self.stream_msg.synchronize()

@@ -979,6 +979,106 @@ def test_layer_step_fused_receive(oracle):
         assert np.array_equal(L.recv_packed.cpu().numpy(), plain.recv_packed.cpu().numpy())
 
 
+def _c0_partition(name):
+    if name == "c0":
+        return make_partition(CONFIGS["c0"])
+    return make_partition(replace(CONFIGS["c4"], n_local=2000, n_halo=1800, n_send=1500, mean_degree=9.0, dim=128))
+
+
+@pytest.mark.parametrize("name", ["c0", "c0_backward"])
+@pytest.mark.parametrize("schedule", [B.ISOLATED, B.FREE])
+def test_layer_step_is_ordered_with_both_streams(name, schedule):
+    """A step of any size: what the caller has queued on stream_agg comes before the overlapped aggregation, what it queues
+    there afterwards comes after it, and synchronising stream_msg covers both."""
+    p = _c0_partition(name)
+    L = LayerStep(p, DEV, seed=5)
+    L.run(B.SERIAL)
+    L.synchronize()
+    want = L.out.clone()
+    (ob, oe), (db, de) = p.overlap_rows, p.dependent_rows
+    x = torch.full((4096, 4096), 2.0 ** -12, device=DEV)
+    y = torch.empty_like(x)
+
+    def slow():
+        for _ in range(10):
+            torch.mm(x, x, out=y)
+
+    slow()
+    L.out.fill_(float("nan"))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(L.stream_agg):
+        slow()
+        L.out[ob:oe].fill_(5.0)
+    L.run(schedule)
+    L.stream_msg.synchronize()
+    assert L.stream_agg.query()
+    torch.cuda.synchronize()
+    assert torch.equal(L.out.view(torch.int32), want.view(torch.int32))
+    L.out.fill_(float("nan"))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(L.stream_msg):
+        slow()
+    L.run(schedule)
+    with torch.cuda.stream(L.stream_agg):
+        seen = L.out[ob:oe].clone()
+    torch.cuda.synchronize()
+    if not p.cfg.backward:                                  # backward: received gradients are added on stream_msg
+        assert torch.equal(seen.view(torch.int32), want[ob:oe].view(torch.int32))
+    else:
+        assert not bool(torch.isnan(seen).any())
+    assert torch.equal(L.out.view(torch.int32), want.view(torch.int32))
+
+
+@pytest.mark.parametrize("name", ["c0", "c0_backward"])
+@pytest.mark.parametrize("fused", [False, True])
+def test_layer_step_chain(oracle, name, fused):
+    """CHAIN, which a step without a schedule takes here: one aggregation launch for both ranges against the oracle; with the
+    received rows still packed the same bits; the bits of SERIAL where the ranges do not touch or no workspace holds both."""
+    p = _c0_partition(name)
+    cfg, seed = p.cfg, 1234
+    _, _, _, out64, mag = _oracle_layer(oracle, p, seed)
+
+    def step(schedule, **kw):
+        L = LayerStep(p, DEV, seed=seed, fused_receive=fused, **kw)
+        if not cfg.backward:
+            L.feat[cfg.n_local: cfg.n_local + cfg.n_send] = float("nan")
+        L.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        return L, L.desc(schedule)
+
+    L, d = step(B.CHAIN, backward_receive=False)
+    assert L.default_schedule() == B.CHAIN
+    B.adaqp_layer_step(d)
+    L.synchronize()
+    out = L.out.cpu().numpy()
+    assert np.all(np.abs(out.astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
+    again, _ = step(B.CHAIN, backward_receive=False)
+    again.set_fused_receive(False)
+    again.run()
+    again.synchronize()
+    assert np.array_equal(again.out.cpu().numpy().view(np.uint32), out.view(np.uint32))
+    assert torch.equal(again.recv_packed, L.recv_packed)
+    # what keeps the ranges apart: no room for both, a row between them; received gradients are added in either case
+    bits = {}
+    for cut in ("small", "gap"):
+        for schedule in (B.SERIAL, B.CHAIN, B.ISOLATED):
+            L, d = step(schedule)
+            if cut == "small":
+                d.workspace_overlap_bytes = B.adaqp_spmm_workspace_bytes(d.overlap_end - d.overlap_begin, d.overlap_nnz, cfg.dim)
+                d.workspace_dependent_bytes = B.adaqp_spmm_workspace_bytes(d.dependent_end - d.dependent_begin,
+                                                                           d.dependent_nnz, cfg.dim)
+            else:
+                d.overlap_end -= 1
+                d.overlap_nnz = int(p.rowptr[d.overlap_end] - p.rowptr[d.overlap_begin])
+                L.out[d.overlap_end].fill_(3.0)
+                torch.cuda.synchronize()
+            B.adaqp_layer_step(d)
+            L.synchronize()
+            bits.setdefault(cut, []).append(L.out.view(torch.int32).clone())
+        assert torch.equal(bits[cut][0], bits[cut][1]) and torch.equal(bits[cut][0], bits[cut][2]), cut
+        assert not bool(torch.isnan(bits[cut][0].view(torch.float32)).any())
+
+
 def test_mean_aggregator_layer_step(oracle):
     """GraphSAGE-style mean coefficients (1 / row degree) through the same step."""
     p = make_partition(replace(CONFIGS["c0"], aggregator="mean"))
@@ -1107,13 +1207,13 @@ def test_layer_step_with_panels(oracle, name):
     assert np.all(np.abs(L.out.cpu().numpy().astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
 
 
-@pytest.mark.parametrize("schedule_name", ["serial", "isolated", "isolated_tiled_panels", "free_tiled_panels"])
+@pytest.mark.parametrize("schedule_name", ["serial", "isolated", "free", "chain", "isolated_tiled_panels", "free_tiled_panels"])
 def test_layer_step_captured_in_a_graph(schedule_name):
     """The step allocates nothing and clears nothing with memset, so it can be captured into a HIP graph; every
     replay (with eager work and synchronisations in between) must give the bits of the eager step.  With tiles
     and panels in both row ranges the two streams wait for each other twice more (the panel kernels run beside
     the tiled ones)."""
-    schedule = {"serial": B.SERIAL, "isolated": B.ISOLATED, "free": B.FREE}[schedule_name.split("_")[0]]
+    schedule = {"serial": B.SERIAL, "isolated": B.ISOLATED, "free": B.FREE, "chain": B.CHAIN}[schedule_name.split("_")[0]]
     p = make_partition(CONFIGS["c0"])
     cfg = p.cfg
     if schedule_name.endswith("tiled_panels"):
