@@ -14,8 +14,9 @@
 // A second, tiny kernel adds the carries of each split row in piece order.  The summation order therefore
 // depends only on the launch geometry: results are bit-identical from run to run and across schedules.
 //
-// Line-padded operands, and others where rows are long or narrow, take the kernel of spmm_sliced.hip instead (same path,
-// feature columns sliced over the XCDs); this one serves the rest, and matrices too large for that kernel's 32-bit offsets.
+// Where sliced_cut (spmm_rules.hpp) says so the kernel of spmm_sliced.hip takes the call instead (same path, feature columns
+// sliced over the XCDs); this one serves launches of few entries, short rows that slices fit badly, most rows that share
+// lines, and matrices too large for that kernel's 32-bit offsets.
 //
 // The kernel is a gather: per entry it reads 8 bytes of (col, alpha) and 4*dim bytes of H.  It is bound by
 // how fast H rows come out of L2 / Infinity Cache / HBM, not by arithmetic, so there is no MFMA use.
@@ -356,10 +357,6 @@ __global__ __launch_bounds__(kBlock) void spmm_carry_kernel(const SpmmArgs a)
 // code the array's name is only a handle for hipGetSymbolAddress, never an address to pass to a kernel.
 static __device__ __align__(256) unsigned char scratch[ADAQP_SPMM_NOALLOC_SCRATCH_BYTES];
 
-constexpr int32_t kNarrowRow = 64;                  // columns
-constexpr int64_t kNarrowEntries = 65536;
-constexpr int64_t kLongRow = 64;                    // entries per row, on average
-
 // Geometry shared by the workspace query and the launch.
 struct Geometry { int32_t n_items; int64_t carry_ld; int64_t bytes; int64_t carry_off; };
 
@@ -506,13 +503,6 @@ int adaqp::spmm_rows(const int64_t *rowptr_dev, const int32_t *col_dev, const fl
 
     hipStream_t st = (hipStream_t)stream;
     const int32_t chunk_cap = kWave * vw * 8;               // columns one launch covers (NV <= 8)
-    // Rows that share lines: a slice of four lines touches five, and a row end costs the sliced kernel more than this one, so
-    // rows have to be long (100 entries of 101 columns 147 us here, 83 sliced; of 601 columns 1000, 900; but 33 entries of
-    // 301 columns 626, 659; 16 of 301 columns 220, 233; 5 of 602 columns 224, 269) or narrower than a wave and
-    // enough of them (0.09 M entries of 20 columns 17.6, 15.4; 1.9 M of 17 columns 118, 56; 0.02 M of 50 columns 14.2, 16.5).
-    // A lane takes four columns: a row, and what the last launch has of it, cannot be less.
-    const bool pays = nnz_range / n_rows >= kLongRow || (dim <= kNarrowRow && nnz_range >= kNarrowEntries);
-    const bool sliced = whole_lines || (pays && dim >= 4 && (dim % chunk_cap == 0 || dim % chunk_cap >= 4));
     for (int32_t c0 = 0; c0 < dim; c0 += chunk_cap) {
         const int32_t cdim = dim - c0 < chunk_cap ? dim - c0 : chunk_cap;
         SpmmArgs a;
@@ -544,8 +534,9 @@ int adaqp::spmm_rows(const int64_t *rowptr_dev, const int32_t *col_dev, const fl
         const int nv = (a.wdim + kWave * vw - 1) / (kWave * vw);
         const dim3 grid((unsigned)((g.n_items + kWavesPerBlock - 1) / kWavesPerBlock));
         hipError_t err;
-        if (sliced && sliced_fits(a)) {
-            err = launch_sliced(a, nnz_range, whole_lines, skewed_columns, st, &a.n_items);
+        const SlicedCut cut = plan_sliced(a, nnz_range, whole_lines, skewed_columns);
+        if (cut.lines > 0) {
+            err = launch_sliced(a, cut, nnz_range, whole_lines, st, &a.n_items);
             if (err == hipSuccess)
                 err = vw == 4 ? launch_carry_nv<4>(a, nv, st)
                               : (vw == 2 ? launch_carry_nv<2>(a, nv, st) : launch_carry_nv<1>(a, nv, st));

@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "spmm_rules.hpp"
 
 namespace adaqp {
 
@@ -35,10 +36,11 @@ struct SpmmArgs {
 
 __device__ __forceinline__ int64_t clamp64(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// The rows of a range with the feature columns sliced over the XCDs (spmm_sliced.hip): operands that sliced_fits; without
-// whole_lines at least four columns.  nnz_hint sizes the launch.  Uses a.n_items carry slots at most; writes how many are in use.
-bool sliced_fits(const SpmmArgs &a);
-hipError_t launch_sliced(const SpmmArgs &a, int64_t nnz_hint, bool whole_lines, bool skewed_columns, hipStream_t st,
+// The rows of a range with the feature columns sliced over the XCDs (spmm_sliced.hip).  plan_sliced: how, or lines = 0 where
+// spmm_merge_kernel has to take the launch or is faster; nnz_hint is what the caller says of the entries.  launch_sliced uses
+// a.n_items carry slots at most and writes how many are in use.
+SlicedCut plan_sliced(const SpmmArgs &a, int64_t nnz_hint, bool whole_lines, bool skewed_columns);
+hipError_t launch_sliced(const SpmmArgs &a, const SlicedCut &cut, int64_t nnz_hint, bool whole_lines, hipStream_t st,
                          int32_t *n_carries_out);
 
 }  // namespace adaqp

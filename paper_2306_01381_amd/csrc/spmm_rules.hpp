@@ -27,4 +27,94 @@ constexpr bool sliced_takes(int64_t nnz, int64_t n_cols, int64_t ldh, bool packe
            (!packed || packed_bytes < limit) && full_dim < (1 << 28);
 }
 
+constexpr int kXcds = 8;
+
+// How the sliced kernel cuts a launch: lines per slice for plain rows and where rows may still be packed, workgroups (of four
+// shares) per slice.  lines 0: the merge-path kernel is the faster one.  n_blocks alone decides the order of additions and is
+// the same for both: packed rows give the bits of the same rows de-quantised beforehand.
+struct SlicedCut { int32_t lines, packed_lines; int64_t n_blocks; };
+
+// Times below: merge-path kernel / sliced kernel, power-law columns, plain (packed) rows, measured over 3 750 to 450 000
+// columns, 4 to 300 entries per row, 16 to 602 columns of H.
+constexpr SlicedCut sliced_cut(int64_t n_rows, int64_t nnz, int64_t n_cols, int32_t lines, bool whole_lines, bool skewed_columns)
+{
+    constexpr int64_t kBlocks = 512;        // two workgroups on each CU
+    constexpr SlicedCut kMergePath = {0, 0, 0};
+    const int64_t degree = nnz / n_rows, fours = (lines + 3) / 4;
+    // few entries: a share's search and the empty ring cost more than its entries (45 000 entries 0.8-1.0, 112 000 1.05-1.25;
+    // whole slices of wide rows 80 000 1.1-1.2; a line left over 112 000 0.9, 180 000 1.1)
+    const bool whole_fours = whole_lines && lines >= 12 && lines % 4 == 0, one_over = lines >= 9 && lines % 4 == 1;
+    if (nnz < (whole_fours ? 60000 : (one_over ? 150000 : 100000))) return kMergePath;
+    if (!whole_lines) {
+        // rows that share lines: a slice of four lines touches five, and a row end costs more.  Rows up to two lines wide: 1.1-4.
+        // Wider ones have to be long (18 entries x 300 columns 0.9-1.0), and past four lines what the slices keep in the L2s
+        // has to be most of the columns (130 to 515 columns wide: 15 000 columns 1.1-1.5, 60 000 0.77-1.04)
+        const bool pays = lines <= 2 ||
+                          (degree >= 64 && (lines <= 4 || n_cols <= 30000 || (lines >= 16 && n_cols <= 100000)));
+        return pays ? SlicedCut{4, 4, kBlocks / fours} : kMergePath;
+    }
+    // Lines per slice.  With four, one LDS read, one address and one row end serve four loads; with one, an L2 holds four times
+    // as many rows: one pays where rows are long and the columns too many for an L2 to hold four lines of each (measured break-even
+    // at 224 columns of H: 12 entries x 50 000 columns, 20 x 34 000, 40 x 20 000).  Where a few columns hold most of the
+    // entries four lines of those fit anyway.
+    const bool many = !skewed_columns && n_cols > 10240 && degree * n_cols > 700000;
+    if (!many) {
+        // rows of four or five entries: only where no slice is a line or three wide (160 columns 0.8-0.9, 352 columns packed 0.8)
+        if (degree < 6 && lines >= 5 && lines % 2 == 1) return kMergePath;
+        // two lines per slice where four would leave two over (300 columns: 1.3 against 1.1), or five lines as 4 + 1 (1.25, 1.0)
+        const int32_t v = lines % 4 == 2 || lines == 5 ? 2 : 4;
+        int64_t n_blocks = kBlocks / ((lines + v - 1) / v);
+        // three lines over: the XCDs that take them have more tasks than room for workgroups, and twice as many of half the
+        // size spread that (60 000 columns, 352 wide packed 1.03, 1.16; 602 wide 0.96, 1.15) where shares stay long enough
+        // and the columns do not fit the L2s anyway (15 000 columns, 352 wide 1.7, 1.5)
+        if (lines % 4 == 3 && lines >= 7 && (lines >= 15 || n_cols > 40000) && nnz >= 500 * 4 * 2 * n_blocks) n_blocks *= 2;
+        return {v, v, n_blocks};
+    }
+    // Two per slice: past 200 000 columns, six times what an L2 holds of one line each, if lines come in pairs (plain rows
+    // 1.02-1.2; one line 0.95-1.15).  Packed rows prefer four lines, whose codes share a line; a cut that serves both needs
+    // shares of 1 900 entries.
+    if (n_cols > 200000 && lines % 2 == 0) {
+        if (lines >= 8 && nnz >= 1900 * 4 * (2 * kBlocks / fours)) return {2, 4, 2 * kBlocks / fours};
+        return {2, 2, kBlocks / (lines / 2)};
+    }
+    if (degree < 6 && lines >= 5) return kMergePath;        // (150 000 rows of four entries: 0.90-0.97)
+    // one per slice, up to eight workgroups per CU in all; packed rows four (352 columns 1.2 against 0.8 with one)
+    const bool halves = lines >= 5 && n_cols > 40000 && nnz >= 600 * 4 * (2 * kBlocks / fours);
+    return {1, 4, (halves ? 2 : 1) * kBlocks / fours};
+}
+
+// Which workgroup takes which slice and share.  Tasks in slice-major order, n_blocks of each slice; consecutive workgroups land
+// on consecutive XCDs, and an XCD takes a run of tasks of an eighth of the whole weight.  The last slice may be narrower than
+// the others; walking the entries costs it as much as them, so a task weighs its lines and that walk.
+struct SliceTasks {
+    int64_t full, all;                  // tasks of whole slices; weight of all tasks
+    int32_t whole_weight, rest_weight;  // of a task of a whole slice, of the narrower one (0: there is none)
+
+    constexpr SliceTasks(int32_t lines, int32_t lines_per_slice, int32_t n_blocks, bool packed)
+        : full((int64_t)(lines / lines_per_slice) * n_blocks), all(0), whole_weight(0), rest_weight(0)
+    {
+        // The walk is worth half a line of plain rows (160 columns in slices of four: 1.3 times as fast as with none, five
+        // lines' worth 1.26; but seven lines 0.96), three lines where slots are looked up as well (288 to 519 columns 1.25-1.3)
+        const int32_t rest = lines % lines_per_slice, walk = packed ? 6 : (rest == 3 ? 0 : 1);
+        whole_weight = 2 * lines_per_slice + walk;
+        rest_weight = rest ? 2 * rest + walk : 0;
+        all = full * whole_weight + (int64_t)n_blocks * rest_weight;
+    }
+
+    // first task that begins at or after this much weight
+    constexpr int64_t task_at(int64_t at) const
+    {
+        return at <= full * whole_weight || rest_weight == 0 ? (at + whole_weight - 1) / whole_weight
+                                                             : full + (at - full * whole_weight + rest_weight - 1) / rest_weight;
+    }
+    constexpr int64_t first_task(int32_t xcd) const { return task_at(all * xcd / kXcds); }
+    constexpr int64_t most_per_xcd() const          // what the grid has to provide for
+    {
+        int64_t most = 0;
+        for (int32_t x = 0; x < kXcds; ++x)
+            if (first_task(x + 1) - first_task(x) > most) most = first_task(x + 1) - first_task(x);
+        return most;
+    }
+};
+
 }  // namespace adaqp

@@ -22,20 +22,18 @@
 // walking whole rows (aggregation of all rows, before -> after): 50 000 x 30 000, 4 M entries, 128 columns 0.239 ->
 // 0.096 ms; 34 000 columns, 0.42 M entries, 66 columns 0.050 -> 0.027; 376 000 x 196 000, 16.2 M entries, 256 columns
 // (transposed graph) 0.96 -> 0.80; 306 000 x 456 000, 7.7 M entries, 256 columns 1.13 -> 1.07; 179 000 x 269 000, 2 M
-// entries, 300 columns 0.386 -> 0.361.  Tried on the way: a piece of the path per group of eight lanes (every row end
+// entries, 300 columns 0.386 -> 0.361.  Packed rows cost a slot lookup per entry and slice and fetch whole lines of codes for a
+// part of them: 66 columns 1.6-2.7 times as fast as the merge path, 256 columns 1.1-1.5, 400 to 602 columns 0.83-1.2.  Tried on the way: a piece of the path per group of eight lanes (every row end
 // then stops seven other rows), steps padded to row ends (a third of the gather slots fetch nothing), and repeating an
 // entry in idle slots instead of an offset outside the buffer (the L1 stalls on a line that is already on its way).
 #include <algorithm>
 
 #include "spmm_common.hpp"
-#include "spmm_rules.hpp"
 
 namespace adaqp {
 namespace {
 
-constexpr int kXcds = 8;
-constexpr int64_t kColumnsThatFit = 10240, kOneLineProduct = 700000, kColumnsForTwo = 200000;      // see launch_sliced
-constexpr int64_t kWorkgroups = 512, kMinPath = 1024;
+constexpr int64_t kMinPath = 1024;                  // of a workgroup's four shares
 constexpr int kStep = 8;                            // entries of a step = groups of a wave
 constexpr int kGroup = kWave / kStep;               // lanes per entry: 8 x 16 bytes = one line
 constexpr int kLine = 32;                           // columns per line
@@ -60,13 +58,6 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 template <bool PACKED> struct Entry;
 template <> struct alignas(8) Entry<false> { uint32_t off; float val; };
 template <> struct alignas(16) Entry<true> { uint32_t off; float val; float z, s; };
-
-__device__ __forceinline__ int64_t readlane_i64(int64_t v, int lane_id)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)v, lane_id);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)((uint64_t)v >> 32), lane_id);
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
 
 template <int U, int N, typename F>
 __device__ __forceinline__ void unroll(F &&f)
@@ -243,31 +234,45 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
         }
     };
     auto stage = [&](const Chunk &c, Entry<PACKED> *ent) {
+        Entry<PACKED> en[kPer];
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
             const int32_t col = st_col[k];
             const bool ok = k * kWave + lane < c.n_ent && col >= 0 && col < a.n_cols;       // else: fetches nothing
-            Entry<PACKED> en = {};
-            en.off = ok ? (uint32_t)col * pitch : kOutside;
-            en.val = ok ? st_val[k] : 0.0f;
-            if constexpr (PACKED) {
-                if (ok) {
-                    const int32_t slot = a.slot_of_row[col];
-                    if (slot >= 0 && slot < a.n_slots) {
-                        const int32_t b = a.bits[slot];
-                        const int64_t off = a.row_offset[slot];
-                        const int64_t stride = 4 * (((int64_t)a.full_dim * b + 31) >> 5);
-                        if ((b == 2 || b == 4 || b == 8) && off >= 0 && (off & 3) == 0 && off + stride <= a.packed_bytes) {
-                            const float2 zs = *reinterpret_cast<const float2 *>(a.params + 2 * (int64_t)slot);
-                            en.off = (uint32_t)off | (b == 2 ? 1u : (b == 4 ? 2u : 3u));
-                            en.z = zs.x;
-                            en.s = zs.y;
-                        }                                   // else: fall back to the row in H
-                    }
-                }
-            }
-            ent[k * kWave + lane] = en;
+            en[k] = {};
+            en[k].off = ok ? (uint32_t)col * pitch : kOutside;
+            en[k].val = ok ? st_val[k] : 0.0f;
         }
+        if constexpr (PACKED) {
+            // all lookups of a chunk are on their way together, those of entries without a slot at index 0: behind a branch
+            // each they would wait for one another, six times two latencies per chunk
+            int32_t slot[kPer], b[kPer];
+            int64_t off[kPer];
+            float2 zs[kPer];
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) slot[k] = a.slot_of_row[en[k].off != kOutside ? st_col[k] : 0];
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const bool has = en[k].off != kOutside && slot[k] >= 0 && slot[k] < a.n_slots;
+                slot[k] = has ? slot[k] : -1;
+                const int64_t at = has ? slot[k] : 0;
+                b[k] = a.bits[at];
+                off[k] = a.row_offset[at];
+                zs[k] = *reinterpret_cast<const float2 *>(a.params + 2 * at);
+            }
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const int64_t stride = 4 * (((int64_t)a.full_dim * b[k] + 31) >> 5);
+                if (slot[k] >= 0 && (b[k] == 2 || b[k] == 4 || b[k] == 8) && off[k] >= 0 && (off[k] & 3) == 0 &&
+                    off[k] + stride <= a.packed_bytes) {
+                    en[k].off = (uint32_t)off[k] | (b[k] == 2 ? 1u : (b[k] == 4 ? 2u : 3u));
+                    en[k].z = zs[k].x;
+                    en[k].s = zs[k].y;
+                }                                           // else: the row in H
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) ent[k * kWave + lane] = en[k];
     };
 
     // the ring: kAhead steps whose lines are on their way
@@ -302,14 +307,13 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
         if constexpr (PACKED) {
             const uint32_t w = in_flight[U].off & 3u;
             if (w != 0) {
-                const uint32_t b = 1u << w, mask = (1u << b) - 1u;
-                const uint32_t shift = (packed_col(v) << w) & 31u;
+                const uint32_t b = 1u << w, shift = (packed_col(v) << w) & 31u;
                 uint32_t word = words[U][v] >> shift;
                 if constexpr (!WHOLE) word = (uint32_t)(((uint64_t)words_up[U][v] << 32 | words[U][v]) >> shift);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const float scaled = (float)((word >> (k * b)) & mask) * in_flight[U].s;    // Eq. 5: product rounded,
-                    x[k] = scaled + in_flight[U].z;                                             // then sum rounded
+                    const float scaled = (float)__builtin_amdgcn_ubfe(word, k * b, b) * in_flight[U].s; // Eq. 5: product
+                    x[k] = scaled + in_flight[U].z;                                             // rounded, then sum rounded
                 }
             }
         }
@@ -392,38 +396,38 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
                 if (U + 1 < kAhead) en = src[(U + 1) * kStep];
                 __builtin_amdgcn_sched_barrier(0);
                 const int32_t rel = end - t * kRing - U * kStep;        // where in this step a row ends
+                float4_t unpacked[VPL];                         // once per step; plain rows as they came
+                if constexpr (PACKED) {
+#pragma unroll
+                    for (int v = 0; v < VPL; ++v) unpacked[v] = neighbour(tag, v);
+                }
+                auto &x = *(PACKED ? &unpacked : &h[U]);
                 if (rel > kStep) {
 #pragma unroll
-                    for (int v = 0; v < VPL; ++v) {
-                        const float4_t x = neighbour(tag, v);
+                    for (int v = 0; v < VPL; ++v)
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) acc[v][k] = fmaf(in_flight[U].val, x[k], acc[v][k]);
-                    }
+                        for (int k = 0; k < 4; ++k) acc[v][k] = fmaf(in_flight[U].val, x[v][k], acc[v][k]);
                 } else {
                     // the groups from the last end to this one belong to the row that ends here
                     int32_t from = 0, to = rel;
                     do {
                         const bool mine = grp >= from && grp < to;
 #pragma unroll
-                        for (int v = 0; v < VPL; ++v) {
-                            const float4_t x = neighbour(tag, v);
+                        for (int v = 0; v < VPL; ++v)
 #pragma unroll
                             for (int k = 0; k < 4; ++k) {
-                                const float sum = fmaf(in_flight[U].val, x[k], acc[v][k]);
+                                const float sum = fmaf(in_flight[U].val, x[v][k], acc[v][k]);
                                 acc[v][k] = mine ? sum : acc[v][k];
                             }
-                        }
                         finish_row();
                         end = __builtin_amdgcn_readlane(cur.ends, ++e);
                         from = to;
                         to = end - t * kRing - U * kStep;
                     } while (to <= kStep);
 #pragma unroll
-                    for (int v = 0; v < VPL; ++v) {
-                        const float4_t x = neighbour(tag, v);
+                    for (int v = 0; v < VPL; ++v)
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) acc[v][k] = grp >= from ? in_flight[U].val * x[k] : 0.0f;
-                    }
+                        for (int k = 0; k < 4; ++k) acc[v][k] = grp >= from ? in_flight[U].val * x[v][k] : 0.0f;
                 }
                 fetch(tag, now);
                 __builtin_amdgcn_sched_barrier(0);
@@ -455,17 +459,10 @@ template <int VPL, bool PACKED, bool WHOLE>
 __global__ __launch_bounds__(kBlock, 2) void spmm_sliced_kernel(const SlicedArgs sa)
 {
     __shared__ Entry<PACKED> stages[kWavesPerBlock][2][kChunk];
-    // Tasks in slice-major order; consecutive workgroups land on consecutive XCDs, an XCD takes a run of tasks that adds up
-    // to an eighth of all lines (the last slice may be narrower than the others).
-    const int64_t full = sa.lines / VPL * (int64_t)sa.n_blocks, rest = sa.lines % VPL;       // tasks of whole slices
-    auto task_at = [&](int64_t line) -> int64_t {           // first task that begins at or after this many lines
-        if (line <= full * VPL || rest == 0) return (line + VPL - 1) / VPL;
-        return full + (line - full * VPL + rest - 1) / rest;
-    };
-    const int64_t all = (int64_t)sa.lines * sa.n_blocks;
-    const uint32_t xcd = blockIdx.x % kXcds;
-    const int64_t task = task_at(all * xcd / kXcds) + blockIdx.x / kXcds;
-    if (task >= task_at(all * (xcd + 1) / kXcds)) return;
+    const SliceTasks tasks(sa.lines, VPL, sa.n_blocks, PACKED);
+    const int32_t xcd = blockIdx.x % kXcds;
+    const int64_t task = tasks.first_task(xcd) + blockIdx.x / kXcds;
+    if (task >= tasks.first_task(xcd + 1)) return;
     const int32_t slice = (int32_t)(task / sa.n_blocks), blk = (int32_t)(task % sa.n_blocks);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int32_t item = blk * kWavesPerBlock + wave;
@@ -478,42 +475,27 @@ __global__ __launch_bounds__(kBlock, 2) void spmm_sliced_kernel(const SlicedArgs
 
 }  // namespace
 
-bool sliced_fits(const SpmmArgs &a)
+SlicedCut plan_sliced(const SpmmArgs &a, int64_t nnz_hint, bool whole_lines, bool skewed_columns)
 {
-    return sliced_takes(a.nnz, a.n_cols, a.ldh, a.slot_of_row != nullptr, a.packed_bytes, a.full_dim);
+    if (!sliced_takes(a.nnz, a.n_cols, a.ldh, a.slot_of_row != nullptr, a.packed_bytes, a.full_dim)) return {0, 0, 0};
+    if (!whole_lines && a.dim < 4) return {0, 0, 0};        // a lane takes four columns
+    return sliced_cut(a.n_rows, nnz_hint, a.n_cols, (a.wdim + kLine - 1) / kLine, whole_lines, skewed_columns);
 }
 
-hipError_t launch_sliced(const SpmmArgs &a, int64_t nnz_hint, bool whole_lines, bool skewed_columns, hipStream_t st,
+hipError_t launch_sliced(const SpmmArgs &a, const SlicedCut &cut, int64_t nnz_hint, bool whole_lines, hipStream_t st,
                          int32_t *n_carries_out)
 {
     SlicedArgs sa;
     sa.s = a;
     sa.lines = (a.wdim + kLine - 1) / kLine;
-    // Lines per slice: one or four.  With four, one LDS read, one address and one row end serve four loads (bare loop out of
-    // L2: 28 TB/s against 21); with one, an L2 holds four times as many rows.  One pays where the rows are long enough
-    // for their ends not to matter and the columns too many for an L2 to hold four lines of each: measured at 224
-    // columns of power-law popularity, the two break even at 12 entries per row x 50 000 columns, 20 x 34 000, 40 x
-    // 20 000 (150 entries x 50 000 columns 0.29 ms against 0.42; 5 entries x 100 000 columns 0.064 against 0.058).
-    // Where a few columns hold most of the entries four lines of those fit anyway (196 000 columns used as often as
-    // Zipf(1.5) degrees say: 0.80 ms against 0.99), and a line of a row that starts anywhere is two lines to fetch, four are
-    // five (16 entries x 90 000 columns, 301 wide: 197 us with four, 264 with one).  Two per slice: only where even one line of each column is ten times what an L2 holds, and
-    // the lines come in pairs (269 000 columns of 10 lines: 0.360 ms against 0.375).
-    const bool many = a.n_cols > kColumnsThatFit && nnz_hint / a.n_rows * a.n_cols > kOneLineProduct;
-    const int vpl = !many || skewed_columns || !whole_lines ? 4 : (a.n_cols > kColumnsForTwo && sa.lines % 2 == 0 ? 2 : 1);
-    const int64_t slices = (sa.lines + vpl - 1) / vpl;
+    const int vpl = a.slot_of_row ? cut.packed_lines : cut.lines;
+    // each wave takes one share, of at least 256 steps of the path: a search and an empty ring each
     const int64_t path = nnz_hint + (int64_t)a.n_rows * kRowSteps;
-    // Two workgroups per CU with two or four lines, up to eight with one; each wave takes one share, of at least 256 steps of the
-    // path.  More and shorter shares cost a search and an empty ring each (16 M entries at four lines: 0.85 ms with 512
-    // workgroups, 0.91 with 4096; at one line 1.11 with 512, 0.99 with 2048).
-    int64_t n_blocks = (vpl == 1 ? 4 : 1) * kWorkgroups / slices;
-    n_blocks = std::min(n_blocks, (path + kMinPath - 1) / kMinPath);
+    int64_t n_blocks = std::min(cut.n_blocks, (path + kMinPath - 1) / kMinPath);
     if (n_blocks > a.n_items / kWavesPerBlock) n_blocks = a.n_items / kWavesPerBlock;      // one carry slot per share
     if (n_blocks < 1) n_blocks = 1;
     sa.n_blocks = (int32_t)n_blocks;
-    // workgroups per XCD: the narrowest slice decides how many tasks an eighth of the lines can be
-    const int64_t narrow = sa.lines % vpl ? sa.lines % vpl : vpl;
-    const int64_t per_xcd = std::min(n_blocks * slices, (n_blocks * sa.lines / kXcds + 1) / narrow + 2);
-    const dim3 grid((unsigned)(per_xcd * kXcds));
+    const dim3 grid((unsigned)(SliceTasks(sa.lines, vpl, sa.n_blocks, a.slot_of_row != nullptr).most_per_xcd() * kXcds));
 #define ADAQP_SLICED(V, WHOLE)                                                                                   \
     do {                                                                                                         \
         if (a.slot_of_row) hipLaunchKernelGGL((spmm_sliced_kernel<V, true, WHOLE>), grid, dim3(kBlock), 0, st, sa); \

@@ -548,6 +548,38 @@ def test_spmm_packed_rows(oracle, dim, ldh):
     assert np.array_equal(again.view(np.uint32), got.view(np.uint32))
 
 
+@pytest.mark.parametrize("dim,ldh,n_cols,rows,mean", [
+    # whole lines, all of the matrix in the L2s: slices of four lines and what may be left over, of two lines
+    (32, 32, 700, 1500, 80), (96, 96, 700, 1500, 80), (128, 160, 700, 1500, 80), (150, 160, 700, 1500, 80),
+    (192, 192, 700, 1500, 80), (224, 224, 700, 1500, 80), (288, 288, 700, 1500, 120), (300, 320, 700, 1500, 80),
+    (410, 416, 700, 1500, 120), (512, 544, 700, 1500, 50), (480, 480, 700, 1500, 400),
+    # slices of one line (packed: four) and half shares, of two lines, of two lines (packed: four)
+    (60, 64, 50_000, 1500, 80), (100, 128, 50_000, 1500, 80), (224, 224, 50_000, 1500, 80), (640, 640, 41_000, 3000, 180),
+    (64, 64, 201_000, 1500, 80), (250, 256, 201_000, 1500, 80), (620, 640, 201_000, 4000, 420),
+    # rows that share lines: narrow ones, long ones
+    (5, 7, 700, 1500, 80), (33, 33, 700, 1500, 80), (64, 65, 700, 1500, 80), (66, 66, 700, 1500, 100),
+    (97, 98, 700, 1500, 100), (131, 131, 700, 1500, 100), (301, 302, 700, 1500, 100), (515, 517, 700, 1500, 100)])
+def test_spmm_cuts(oracle, dim, ldh, n_cols, rows, mean):
+    """Entries enough for the sliced kernel in each of its cuts, plain and from packed rows: row ends at every place of a step,
+    more row ends than a chunk takes, rows of many shares' length, empty rows at both ends; the same bits packed."""
+    _say(f"spmm cut dim={dim} ldh={ldh} n_cols={n_cols} mean={mean}")
+    rng = np.random.default_rng(dim + n_cols)
+    degs = np.concatenate([np.zeros(70), np.ones(130), np.arange(40), [383, 384, 385, 8, 16, 0, 0], np.full(60, 23),
+                           [20_000, 5, 3_000], rng.integers(mean // 2, mean * 3 // 2 + 1, size=rows), np.zeros(3)]).astype(int)
+    n_rows = degs.shape[0]
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, degs)
+    assert len(col) >= (60_000 if dim == 512 else (150_000 if dim in (288, 410) else 100_000))
+    halo, bits, off, packed, params, H_plain, H_ref = _packed_case(oracle, rng, n_cols, min(n_cols // 2, 3000), dim, ldh, seed=7)
+    slot_of_row = B.adaqp_plan_slot_of_row(n_cols, halo)
+    H_filled = np.full((n_cols, ldh), np.nan, dtype=np.float32)     # what lies between the rows must never reach a sum
+    H_filled[:, :dim] = H_ref
+    ldo = ldh if ldh % 32 == 0 else dim
+    got = _check_spmm(oracle, rowptr, col, val, 0, n_rows, H_filled, dim, ldo=ldo)
+    _check_spmm(oracle, rowptr, col, val, 65, n_rows - 1, H_filled, dim, nnz_range="exact", ldo=ldo)
+    fused = _gpu_spmm_packed(rowptr, col, val, 0, n_rows, H_plain, dim, slot_of_row, packed, params, bits, off, ldo)
+    assert np.array_equal(fused.view(np.uint32), got.view(np.uint32))
+
+
 def test_spmm_packed_argument_checks():
     z = torch.zeros(64, dtype=torch.uint8, device=DEV)
     rowptr = torch.zeros(2, dtype=torch.int64, device=DEV)

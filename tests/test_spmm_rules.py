@@ -15,7 +15,7 @@ def _run(tmp_path, body):
     if cxx is None:
         pytest.skip("no host compiler")
     src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
-    src.write_text('#include <stdio.h>\n#include "spmm_rules.hpp"\nusing namespace adaqp;\n'
+    src.write_text('#include <stdio.h>\n#include <initializer_list>\n#include "spmm_rules.hpp"\nusing namespace adaqp;\n'
                    '#define CHECK(x) do { if (!(x)) { printf("line %d: %s\\n", __LINE__, #x); return 1; } } while (0)\n'
                    "int main() {\n" + body + "\nreturn 0; }\n")
     subprocess.run([cxx, "-std=c++17", "-Wall", "-Werror", "-I", CSRC, "-o", str(exe), str(src)], check=True)
@@ -76,3 +76,50 @@ def test_buffer_loads_carry_no_scalar_offset():
             calls += 1
             assert len(args) == 4 and args[2].strip() == "0", f"{name}: scalar offset {args[2].strip()}"
     assert calls > 0
+
+
+def test_cuts_of_the_sliced_kernel(tmp_path):
+    """A cut is always one that the kernel has; and where launches were measured slower than along the merge path (few entries,
+    short rows with a narrower slice, packed rows one line at a time, rows that share lines and too many columns), that
+    path or another cut is taken."""
+    _run(tmp_path, """
+    for (int64_t rows : {1, 40, 2000, 60000, 300000, 2000000000}) for (int64_t degree : {0, 1, 5, 18, 64, 300, 30000})
+        for (int64_t cols : {1, 700, 10241, 40001, 100000, 200001, 3000000}) for (int32_t lines = 1; lines <= 64; ++lines)
+            for (int whole = 0; whole < 2; ++whole) for (int skewed = 0; skewed < 2; ++skewed) {
+                const SlicedCut c = sliced_cut(rows, rows * degree, cols, lines, whole != 0, skewed != 0);
+                CHECK((c.lines == 0) == (c.packed_lines == 0) && (c.lines == 0 || (c.n_blocks >= 1 && c.n_blocks <= 1024)));
+                CHECK(c.lines == 0 || c.lines == 1 || c.lines == 2 || c.lines == 4);
+                CHECK(c.packed_lines == 0 || c.packed_lines == 2 || c.packed_lines == 4);
+                CHECK(whole || c.lines == 0 || c.lines == 4);
+            }
+    CHECK(sliced_cut(2000, 20656, 2600, 4, true, false).lines == 0);
+    CHECK(sliced_cut(10000, 80000, 15000, 4, true, true).lines == 0);
+    CHECK(sliced_cut(40000, 160000, 60000, 13, true, false).lines == 0);
+    CHECK(sliced_cut(150000, 600000, 225000, 17, true, false).lines == 0);
+    CHECK(sliced_cut(46921, 841725, 65616, 17, true, false).packed_lines == 4);
+    CHECK(sliced_cut(40000, 2800000, 60000, 5, false, false).lines == 0);
+    CHECK(sliced_cut(2500, 45000, 3750, 1, false, false).lines == 0);
+    """)
+
+
+def test_every_slice_task_is_taken_once(tmp_path):
+    """Every share of every slice by exactly one workgroup, whatever the last slice's width, and no XCD with much more weight
+    than another."""
+    _run(tmp_path, """
+    for (int packed = 0; packed < 2; ++packed)
+        for (int32_t vpl : {1, 2, 4}) for (int32_t lines = 1; lines <= 64; ++lines)
+            for (int32_t n_blocks : {1, 2, 3, 7, 8, 31, 64, 127, 170, 512, 2048}) {
+                const SliceTasks t(lines, vpl, n_blocks, packed != 0);
+                const int64_t n_tasks = (int64_t)((lines + vpl - 1) / vpl) * n_blocks;
+                CHECK(t.first_task(0) == 0 && t.first_task(kXcds) == n_tasks);
+                int64_t next = 0;
+                for (int32_t x = 0; x < kXcds; ++x) {
+                    CHECK(t.first_task(x) == next);
+                    next = t.first_task(x + 1);
+                    CHECK(next >= t.first_task(x) && next - t.first_task(x) <= t.most_per_xcd());
+                    int64_t weight = 0;
+                    for (int64_t k = t.first_task(x); k < next; ++k) weight += k < t.full ? t.whole_weight : t.rest_weight;
+                    CHECK(weight <= t.all / kXcds + 1 + t.whole_weight);
+                }
+            }
+    """)
