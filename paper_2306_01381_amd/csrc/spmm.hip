@@ -370,7 +370,6 @@ bool geometry(int64_t n_rows, int64_t nnz, int32_t dim, Geometry *g)
     while (per < 512 && total / per > 65536) per *= 2;
     int64_t items = (total + per - 1) / per;
     if (items > (int64_t)1 << 30) return false;
-    if (items < kWavesPerBlock) items = kWavesPerBlock;     // the sliced kernel cuts a workgroup's share into four
     g->n_items = (int32_t)items;
     g->carry_ld = ((int64_t)dim + 31) / 32 * 32;
     g->carry_off = (items * 4 + 255) / 256 * 256;

@@ -161,6 +161,17 @@ print("same order")
     assert done.returncode == 0 and "same order" in done.stdout, done.stderr[-2000:]
 
 
+def test_spmm_workspace_of_few_rows():
+    """One carry slot per 32 path steps and no more: the widest rows that fit the built-in scratch of the call without a
+    workspace."""
+    for n_rows, nnz, items in ((1, 5, 1), (1, 31, 1), (2, 31, 2), (40, 60, 4), (40, 100, 5)):
+        for dim in (1, 33, 4096):
+            ld = (dim + 31) // 32 * 32
+            assert B.adaqp_spmm_workspace_bytes(n_rows, nnz, dim) == \
+                (items * 4 + 255) // 256 * 256 + (items * ld * 4 + 255) // 256 * 256
+    assert B.adaqp_spmm_workspace_bytes(1, 5, 16_000_000) <= B.SPMM_NOALLOC_SCRATCH_BYTES
+
+
 def test_plan_recv_segments():
     dst = np.array([7, 3, 7, 9, 3, 3], dtype=np.int32)
     order, seg_ptr = B.adaqp_plan_recv_segments(dst)
