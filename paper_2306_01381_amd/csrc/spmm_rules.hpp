@@ -17,13 +17,17 @@ constexpr uint32_t buffer_extent(int64_t n_cols, int64_t ldh, int32_t begin)
     return floats > 0 ? (uint32_t)(floats * 4) : 0u;
 }
 
+// Row ends that one step of the search for a share's first row looks at (a wave, four each).  The search counts rows in 32
+// bits, up to a step past the range.
+constexpr int32_t kProbes = 256;
+
 // Whether the sliced kernel takes a launch.  Offsets of rows of H and of packed rows are kept in 32 bits.  Without columns or
 // without entries there is nothing to gather and H, col and val may be NULL: the merge-path kernel then reads none of them,
 // while the sliced one has loads in flight from the start.
-constexpr bool sliced_takes(int64_t nnz, int64_t n_cols, int64_t ldh, bool packed, int64_t packed_bytes, int32_t full_dim)
+constexpr bool sliced_takes(int64_t n_rows, int64_t nnz, int64_t n_cols, int64_t ldh, bool packed, int64_t packed_bytes, int32_t full_dim)
 {
     constexpr int64_t limit = (int64_t)kOutside;
-    return nnz > 0 && n_cols > 0 && n_cols <= INT32_MAX && ldh < limit / 4 && n_cols * ldh < limit / 4 &&
+    return n_rows + n_rows / kProbes + kProbes <= INT32_MAX && nnz > 0 && n_cols > 0 && n_cols <= INT32_MAX && ldh < limit / 4 && n_cols * ldh < limit / 4 &&
            (!packed || packed_bytes < limit) && full_dim < (1 << 28);
 }
 

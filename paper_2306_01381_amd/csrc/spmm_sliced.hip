@@ -72,7 +72,7 @@ __device__ __forceinline__ void unroll(F &&f)
 // search by a whole wave; wave-uniform results.
 __device__ void split_rows2(const SpmmArgs &a, const int64_t (&d)[2], int64_t base, int64_t nnz_r, int lane, int32_t (&at)[2])
 {
-    constexpr int K = 4;
+    constexpr int K = kProbes / kWave;
     int32_t lo[2], hi[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(kBlock, 2) void spmm_sliced_kernel(const SlicedArgs
 
 SlicedCut plan_sliced(const SpmmArgs &a, int64_t nnz_hint, bool whole_lines, bool skewed_columns)
 {
-    if (!sliced_takes(a.nnz, a.n_cols, a.ldh, a.slot_of_row != nullptr, a.packed_bytes, a.full_dim)) return {0, 0, 0};
+    if (!sliced_takes(a.n_rows, a.nnz, a.n_cols, a.ldh, a.slot_of_row != nullptr, a.packed_bytes, a.full_dim)) return {0, 0, 0};
     if (!whole_lines && a.dim < 4) return {0, 0, 0};        // a lane takes four columns
     return sliced_cut(a.n_rows, nnz_hint, a.n_cols, (a.wdim + kLine - 1) / kLine, whole_lines, skewed_columns);
 }

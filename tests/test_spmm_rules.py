@@ -44,13 +44,19 @@ def test_buffer_extent(tmp_path):
 def test_what_the_sliced_kernel_takes(tmp_path):
     """Never a call whose arrays may be NULL (no entries, no columns), nor one whose offsets do not fit 32 bits."""
     _run(tmp_path, """
-    CHECK(sliced_takes(1, 1, 32, false, 0, 32));
-    CHECK(!sliced_takes(0, 0, 64, false, 0, 64) && !sliced_takes(0, 0, 64, true, 4, 64));
-    CHECK(!sliced_takes(0, 5, 64, false, 0, 64) && !sliced_takes(5, 0, 64, false, 0, 64));
+    CHECK(sliced_takes(5, 1, 1, 32, false, 0, 32));
+    CHECK(!sliced_takes(5, 0, 0, 64, false, 0, 64) && !sliced_takes(5, 0, 0, 64, true, 4, 64));
+    CHECK(!sliced_takes(5, 0, 5, 64, false, 0, 64) && !sliced_takes(5, 5, 0, 64, false, 0, 64));
     const int64_t floats = (int64_t)kOutside / 4;
-    CHECK(sliced_takes(9, floats / 32 - 1, 32, false, 0, 32) && !sliced_takes(9, floats / 32 + 1, 32, false, 0, 32));
-    CHECK(!sliced_takes(9, (int64_t)1 << 33, 32, false, 0, 32) && !sliced_takes(9, 2, (int64_t)1 << 62, false, 0, 32));
-    CHECK(sliced_takes(9, 10, 32, true, 4096, 32) && !sliced_takes(9, 10, 32, true, (int64_t)1 << 32, 32));
+    CHECK(sliced_takes(5, 9, floats / 32 - 1, 32, false, 0, 32) && !sliced_takes(5, 9, floats / 32 + 1, 32, false, 0, 32));
+    CHECK(!sliced_takes(5, 9, (int64_t)1 << 33, 32, false, 0, 32) && !sliced_takes(5, 9, 2, (int64_t)1 << 62, false, 0, 32));
+    for (int64_t n = 1; n < ((int64_t)1 << 32); n = n * 5 / 4 + 1)        // what the search adds to a number of rows stays in 32 bits
+        if (sliced_takes(n, 9, 10, 32, false, 0, 32)) {
+            const int64_t step = (n + kProbes - 1) / kProbes;
+            CHECK(n + kProbes - 1 <= INT32_MAX && n + step - 1 <= INT32_MAX && n + 64 <= INT32_MAX);
+        }
+    CHECK(sliced_takes(2000000000, 9, 10, 32, false, 0, 32) && !sliced_takes(INT32_MAX - 1, 9, 10, 32, false, 0, 32));
+    CHECK(sliced_takes(5, 9, 10, 32, true, 4096, 32) && !sliced_takes(5, 9, 10, 32, true, (int64_t)1 << 32, 32));
     """)
 
 
