@@ -287,10 +287,16 @@ __device__ __forceinline__ void copy_one(const CopyArgs &c, int64_t i)
     }
 }
 
+// A launch has fewer than 2^32 threads: what 2^20 workgroups per buffer do not copy at one unit each they copy in turns.
+constexpr int64_t kCopyBlocks = (int64_t)1 << 20;
+
 __global__ __launch_bounds__(kBlock) void loop_back_kernel(const CopyArgs a, const CopyArgs b, uint32_t blocks_a)
 {
-    if (blockIdx.x < blocks_a) copy_one(a, (int64_t)blockIdx.x * kBlock + threadIdx.x);
-    else copy_one(b, (int64_t)(blockIdx.x - blocks_a) * kBlock + threadIdx.x);
+    const bool first = blockIdx.x < blocks_a;
+    const CopyArgs &c = first ? a : b;
+    const int64_t block = first ? blockIdx.x : blockIdx.x - blocks_a, blocks = first ? blocks_a : gridDim.x - blocks_a;
+    const int64_t n = c.units + (c.bytes - c.units * c.unit);
+    for (int64_t i = block * kBlock + threadIdx.x; i < n; i += blocks * kBlock) copy_one(c, i);
 }
 
 int loop_back(const adaqp_layer_desc *d, hipStream_t st)
@@ -298,9 +304,8 @@ int loop_back(const adaqp_layer_desc *d, hipStream_t st)
     if (d->n_send == 0) return ADAQP_OK;
     const CopyArgs a = copy_args(d->packed_dev, d->recv_packed_dev, d->packed_bytes);
     const CopyArgs b = copy_args(d->params_dev, d->recv_params_dev, d->n_send * 2 * (int64_t)sizeof(float));
-    const int64_t blocks_a = (a.units + a.bytes % a.unit + kBlock - 1) / kBlock;
-    const int64_t blocks_b = (b.units + b.bytes % b.unit + kBlock - 1) / kBlock;
-    if (blocks_a + blocks_b > INT32_MAX) return ADAQP_ESIZE;
+    const int64_t blocks_a = std::min((a.units + a.bytes % a.unit + kBlock - 1) / kBlock, kCopyBlocks);
+    const int64_t blocks_b = std::min((b.units + b.bytes % b.unit + kBlock - 1) / kBlock, kCopyBlocks);
     hipLaunchKernelGGL(loop_back_kernel, dim3((unsigned)(blocks_a + blocks_b)), dim3(kBlock), 0, st, a, b, (uint32_t)blocks_a);
     ADAQP_HIP_TRY(hipGetLastError());
     return ADAQP_OK;

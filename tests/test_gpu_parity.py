@@ -1111,6 +1111,26 @@ def test_layer_step_chain(oracle, name, fused):
         assert not bool(torch.isnan(bits[cut][0].view(torch.float32)).any())
 
 
+@pytest.mark.parametrize("extra,offset", [(0, 0), (5, 4), (7, 1), ((1 << 28) + 3, 1), ((1 << 32) + 77, 1)])
+def test_layer_step_copies_the_whole_buffer(extra, offset):
+    """The loop-back of a send buffer of any size and alignment: units of 16, 4 and 1 bytes, what they leave over, and more of
+    them than a launch has threads (a backward step without receive reads nothing of the copy)."""
+    p = _c0_partition("c0_backward")
+    L = LayerStep(p, DEV, seed=5, backward_receive=False)
+    n = L.plan.packed_bytes + extra
+    _say(f"loop-back {n} bytes at offset {offset}")
+    sent = torch.randint(0, 256, (n,), dtype=torch.uint8, device=DEV)
+    received = torch.full((n + 32,), 7, dtype=torch.uint8, device=DEV)
+    torch.cuda.synchronize()
+    d = L.desc(B.SERIAL)
+    d.packed_dev, d.packed_bytes, d.recv_packed_dev = sent.data_ptr(), n, received.data_ptr() + offset
+    B.adaqp_layer_step(d)
+    L.synchronize()
+    assert torch.equal(received[offset:offset + n], sent)
+    assert bool((received[:offset] == 7).all()) and bool((received[offset + n:] == 7).all())
+    assert torch.equal(L.recv_params, L.params)
+
+
 def test_mean_aggregator_layer_step(oracle):
     """GraphSAGE-style mean coefficients (1 / row degree) through the same step."""
     p = make_partition(replace(CONFIGS["c0"], aggregator="mean"))
