@@ -42,18 +42,18 @@ def parse_args():
     ap.add_argument("--config", default="c1", help="headline workload, c0..c4 (c1 is the one the metric is quoted on)")
     ap.add_argument("--only-headline", action="store_true",
                     help="skip the `configs` block (c2, c3, c4 after the headline): for profiling one workload")
-    ap.add_argument("--schedule", default=None, choices=["serial", "isolated", "free"],
-                    help="schedule of the timed steps.  Default: isolated (Fig. 7: the central rows start on the second "
-                         "stream once quantisation is done).  On workload c1 that pairs a panel kernel with a tiled "
-                         "kernel on the two streams; elsewhere (one aggregation kernel per row range, no transfer to "
-                         "hide on one GPU) it is worth 0-4 %.  The figures under `kernels` are always timed one "
+    ap.add_argument("--schedule", default=None, choices=["serial", "isolated", "free", "chain"],
+                    help="schedule of the timed steps.  Default: what LayerStep.run() takes.  On workload c1 that is "
+                         "isolated (Fig. 7: the central rows start on the second stream once quantisation is done), "
+                         "which pairs a panel kernel with a tiled kernel on the two streams; elsewhere (no tiles, no "
+                         "transfer to hide on one GPU) chain: one stream, one aggregation launch.  The figures under `kernels` are always timed one "
                          "launch at a time")
     ap.add_argument("--kernel-reps", type=int, default=20, help="launches per kernel in the breakdown")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-panels", action="store_true",
                     help="keep the longest rows in the L2-tiled kernel instead of dense panels on the matrix cores")
     ap.add_argument("--no-tiled", action="store_true",
-                    help="aggregate along the merge path (sliced kernel) even where the L2-tiled kernel would be chosen")
+                    help="aggregate with adaqp_spmm_csr (sliced or merge-path kernel) even where the L2-tiled kernel would be chosen")
     ap.add_argument("--calibrate", action="store_true",
                     help="also launch a plain elementwise kernel of known size (reads and writes 256 MiB): the "
                          "reference dispatch that scales the FETCH_SIZE / WRITE_SIZE counters of a --pmc run")
@@ -206,9 +206,11 @@ def measure_config(name, args, headline, B, torch, np):
     schedule = args.schedule if headline else None
     pairs = (not cfg.backward and L.tile_off_overlap is not None and L.tile_off_dependent is not None
              and bool(L.panels_overlap or L.panels_dependent))
+    sched = {"serial": B.SERIAL, "isolated": B.ISOLATED, "free": B.FREE, "chain": B.CHAIN}
     if schedule is None:
-        schedule = "isolated"
-    sched = {"serial": B.SERIAL, "isolated": B.ISOLATED, "free": B.FREE}
+        schedule = {v: k for k, v in sched.items()}[L.default_schedule()]
+    if schedule != "chain" and (L.tile_off_overlap is not None or L.tile_off_dependent is not None):
+        del sched["chain"]                              # with tiles it is the serial step
 
     def timed_steps(sch, steps, warmup):
         desc = L.desc(sch)
@@ -227,9 +229,8 @@ def measure_config(name, args, headline, B, torch, np):
         by_schedule[s_name] = ms_per_step if s_name == schedule else timed_steps(s, max(3, args.steps // 4), 1)
     # a two-stream schedule that does not beat the serial one has lost its overlap (the two streams share a hardware
     # queue): say so instead of printing the serial time under its name.  Only where the step pairs the panel and
-    # the tiled kernel (14 % to win); with one aggregation kernel per row range there is no transfer to hide on one
-    # GPU and the two-stream schedules stay within +-3 % of the serial one
-    overlap_lost = pairs and schedule != "serial" and ms_per_step > 0.97 * by_schedule["serial"]
+    # the tiled kernel (14 % to win); elsewhere there is no transfer to hide on one GPU
+    overlap_lost = pairs and schedule in ("isolated", "free") and ms_per_step > 0.97 * by_schedule["serial"]
 
     fused = None
     ms_graph = None
@@ -411,7 +412,7 @@ def measure_config(name, args, headline, B, torch, np):
             B.adaqp_spmm_csr(L.rowptr, L.col, L.val, db_, de, L.feat, dim, L.out, L.ws_dependent,
                              nnz_range=L.dependent_nnz, stream=st)
 
-    def spmm_merge_both(i):
+    def spmm_untiled_both(i):
         B.adaqp_spmm_csr(L.rowptr, L.col, L.val, ob, oe, L.feat, dim, L.out, L.ws_overlap,
                          nnz_range=L.overlap_nnz, stream=st)
         B.adaqp_spmm_csr(L.rowptr, L.col, L.val, db_, de, L.feat, dim, L.out, L.ws_dependent,
@@ -480,12 +481,12 @@ def measure_config(name, args, headline, B, torch, np):
         t_all = event_time_ms(st, spmm_all, sreps)
         kernels["spmm_all_rows_one_launch"] = {"ms": t_all, "edges": p.nnz, "edges_per_s": p.nnz / t_all * 1e3,
                                                "kernel": ("tiled + panels" if panel_parts else "tiled") if tiled_both
-                                               else "sliced"}
+                                               else "untiled"}
         del ws_all
         if tiled:
-            t_m = event_time_ms(st, spmm_merge_both, max(3, sreps // 2))
-            kernels["spmm_merge_path_both_launches"] = {"ms": t_m, "edges_per_s": p.nnz / t_m * 1e3,
-                                                        "note": "the untiled kernel on the same rows, for comparison"}
+            t_m = event_time_ms(st, spmm_untiled_both, max(3, sreps // 2))
+            kernels["spmm_untiled_both_launches"] = {"ms": t_m, "edges_per_s": p.nnz / t_m * 1e3,
+                                                        "note": "adaqp_spmm_csr on the same rows, for comparison"}
 
     # ---- roofline of the dominant kernel, against the limit that binds it ----
     # Floors of the whole aggregation: what has to cross the HBM interface at least (every entry, every row of H that
@@ -494,7 +495,14 @@ def measure_config(name, args, headline, B, torch, np):
     # fits its L2), the fp32 FMA rate.
     touched_cols = int(np.count_nonzero(np.bincount(p.col, minlength=p.feat.shape[0])))
     compulsory = p.nnz * 8 + touched_cols * 4 * dim + p.n_rows * 4 * dim
-    t_both = t_o + t_d
+    t_both, launches = t_o + t_d, 2
+    if schedule == "chain":
+        # the step's one launch, by a step that sends nothing
+        desc_agg = L.desc(B.CHAIN)
+        desc_agg.n_send, desc_agg.n_recv_seg, desc_agg.stream_msg = 0, 0, st.cuda_stream
+        t_both, launches = event_time_ms(st, lambda i: B.adaqp_layer_step(desc_agg), sreps), 1
+        kernels["spmm_of_the_step"] = {"ms": t_both, "edges": p.nnz, "edges_per_s": p.nnz / t_both * 1e3,
+                                       "pct_hbm_primary": 100 * (b_o + b_d) / t_both / 1e6 / HBM_PEAK_GBPS}
     t_ceiling = max(compulsory / HBM_PEAK_GBPS / 1e6, p.nnz * 4 * dim / GATHER_RATE_GBPS / 1e6,
                     p.nnz * dim / FMA_RATE_PER_S * 1e3)
     ceilings = {"compulsory_bytes_both_launches": compulsory,
@@ -529,15 +537,16 @@ def measure_config(name, args, headline, B, torch, np):
                              "per 32-row panel (out of the XCD's L2) and multiplied with the panel's dense "
                              "coefficient table; `frac` counts the method's own multiply-adds (2 * entries * dim)"}
     else:
-        alg = (b_o + b_d) / 2
-        avg_ms = t_both / 2
+        alg = (b_o + b_d) / launches
+        avg_ms = t_both / launches
         frac_hbm = primary_gbps / HBM_PEAK_GBPS
         roofline = {
-            "kernel": "spmm_tiled_kernel" if tiled else "spmm_sliced_kernel",
+            "kernel": "spmm_tiled_kernel" if tiled else                                 # few entries: along the merge path
+            "spmm_sliced_kernel" if p.nnz >= 100_000 else "spmm_merge_kernel",
             "bound": "hbm" if frac_hbm <= 1.0 else "l2",
             "achieved": primary_gbps, "peak": HBM_PEAK_GBPS if frac_hbm <= 1.0 else GATHER_RATE_GBPS, "unit": "GB/s",
             "frac": frac_hbm if frac_hbm <= 1.0 else primary_gbps / GATHER_RATE_GBPS, "traffic": None,
-            "launches_per_step": 2, "avg_launch_ms": avg_ms, "algorithmic_bytes_per_launch": alg,
+            "launches_per_step": launches, "avg_launch_ms": avg_ms, "algorithmic_bytes_per_launch": alg,
             "binding_limit": ("the path behind L2 (fabric / Infinity Cache / HBM) for the neighbour rows that miss L2"
                               if frac_hbm <= 1.0 else
                               "the CUs' gather rate out of L2 (25 TB/s measured on this part with a gather kernel, not "
@@ -554,7 +563,7 @@ def measure_config(name, args, headline, B, torch, np):
         entry = tf.get(cfg.name, {}).get(roofline["kernel"])
         if entry:
             roofline["traffic"] = entry["fetch"] + entry["write"]
-            roofline["traffic_detail"] = dict(entry, measured_at=tf.get("measured_at", "unknown"),
+            roofline["traffic_detail"] = dict(entry, measured_at=entry.get("measured_at", tf.get("measured_at", "unknown")),
                                               file="profiles/hbm_traffic.json")
 
     rec = {
@@ -593,12 +602,13 @@ def degree_law_check(args, B, torch, np):
            "rows_at_or_above_panel_threshold": int(np.count_nonzero(deg >= B.SPMM_PANEL_MIN_ROW)), "ms_per_step": {}}
     steps = max(3, args.steps // 2)
     for tag, kw in (("library_rules", {}), ("panels_forced", {"panels": True}), ("tiled_without_panels", {"panels": False}),
-                    ("merge_path", {"tiled": False})):
+                    ("untiled", {"tiled": False})):
         L = LayerStep(p, "cuda:0", seed=2306, streams=_STREAMS.get("pair"), **kw)
         _STREAMS["pair"] = (L.stream_msg, L.stream_agg)
         paired = L.tile_off_overlap is not None and L.tile_off_dependent is not None and \
             bool(L.panels_overlap or L.panels_dependent)
-        desc = L.desc(B.ISOLATED if paired else B.SERIAL)
+        untiled = L.tile_off_overlap is None and L.tile_off_dependent is None
+        desc = L.desc(B.ISOLATED if paired else (L.default_schedule() if untiled else B.SERIAL))
         for _ in range(2):
             B.adaqp_layer_step(desc)
         torch.cuda.synchronize()

@@ -355,18 +355,20 @@ def test_spmm_sliced_edges(oracle, dim, n_cols):
     _say(f"spmm sliced dim={dim} n_cols={n_cols}")
     rng = np.random.default_rng(dim + n_cols)
     degs = np.concatenate([np.zeros(70), np.ones(130), np.arange(40), [383, 384, 385, 8, 16, 0, 0], np.full(60, 23),
-                           [20_000, 5, 3_000], rng.integers(0, 90, size=400), np.zeros(3)]).astype(int)
+                           [20_000, 5, 3_000], rng.integers(0, 90, size=3000), np.zeros(3)]).astype(int)
     rowptr, col, val = _random_graph(rng, degs.shape[0], n_cols, degs)
+    assert len(col) > 110_000                               # fewer go along the merge path
     ld = _padded_cols(dim, 64 * dim)
     H = np.full((n_cols, ld), np.nan, dtype=np.float32)
     H[:, :dim] = rng.standard_normal((n_cols, dim), dtype=np.float32)
     n_rows = degs.shape[0]
     _check_spmm(oracle, rowptr, col, val, 0, n_rows, H, dim, ldo=ld)
     _check_spmm(oracle, rowptr, col, val, 65, n_rows - 1, H, dim, nnz_range="exact", ldo=ld)
+    _check_spmm(oracle, rowptr, col, val, 190, 300, H, dim, ldo=ld)
     out = torch.full((n_rows, ld), 7.0, device=DEV)
     ws = torch.empty(max(B.adaqp_spmm_workspace_bytes(n_rows, len(col), dim), 256), dtype=torch.uint8, device=DEV)
     B.adaqp_spmm_csr(torch.from_numpy(rowptr).to(DEV), torch.from_numpy(col).to(DEV), torch.from_numpy(val).to(DEV), 0,
-                     n_rows, torch.from_numpy(H).to(DEV), dim, out, ws, nnz_range=1)
+                     n_rows, torch.from_numpy(H).to(DEV), dim, out, ws, nnz_range=100_000)
     want, mag = oracle.spmm_csr(rowptr, col, val, 0, n_rows, np.ascontiguousarray(H[:, :dim]), dim)
     assert np.all(np.abs(out.cpu().numpy()[:, :dim].astype(np.float64) - want) <= SPMM_RTOL * mag + 1e-30)
 
@@ -379,9 +381,10 @@ def test_spmm_sliced_unpadded(oracle, dim, ldh, ldo):
     _say(f"spmm sliced unpadded dim={dim} ldh={ldh} ldo={ldo}")
     rng = np.random.default_rng(dim)
     degs = np.concatenate([np.zeros(70), np.arange(40), [383, 384, 385, 8, 16, 0, 0], np.full(60, 23), [700, 5, 600],
-                           rng.integers(40, 160, size=700), np.zeros(3)]).astype(int)      # long rows: the sliced kernel
+                           rng.integers(40, 160, size=1200), np.zeros(3)]).astype(int)
     n_rows, n_cols = degs.shape[0], 700
     rowptr, col, val = _random_graph(rng, n_rows, n_cols, degs)
+    assert len(col) > 100_000 and len(col) // n_rows >= 64  # long rows and enough of them: the sliced kernel
     H = np.full((n_cols, ldh), np.nan, dtype=np.float32)    # what lies between the rows must never reach a sum
     H[:, :dim] = rng.standard_normal((n_cols, dim), dtype=np.float32)
     _check_spmm(oracle, rowptr, col, val, 0, n_rows, H, dim, ldo=ldo)
@@ -1009,6 +1012,30 @@ def test_layer_step_fused_receive(oracle):
         assert np.array_equal(out.view(np.uint32), want.view(np.uint32)), f"schedule {schedule}"
         assert bool(torch.isnan(L.feat[cfg.n_local: cfg.n_local + cfg.n_send]).all())
         assert np.array_equal(L.recv_packed.cpu().numpy(), plain.recv_packed.cpu().numpy())
+
+
+def test_layer_step_fused_receive_with_a_tiled_range(oracle):
+    """The central rows tiled, the marginal ones read from the receive buffer: two streams, the same bits in every schedule,
+    the halo rows of the feature matrix untouched."""
+    p = make_partition(CONFIGS["c0"])
+    cfg, seed = p.cfg, 1234
+    _, _, _, out64, mag = _oracle_layer(oracle, p, seed)
+    want = None
+    for schedule in (B.SERIAL, B.ISOLATED, B.FREE, B.CHAIN, None):
+        L = LayerStep(p, DEV, seed=seed, fused_receive=True, tiled=True)
+        assert L.tile_off_overlap is not None and L.default_schedule() == B.ISOLATED
+        d = L.desc(B.ISOLATED)
+        assert d.tile_off_overlap_dev and not d.tile_off_dependent_dev and d.slot_of_row_dev
+        L.feat[cfg.n_local: cfg.n_local + cfg.n_send] = float("nan")
+        L.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        L.run(schedule)
+        L.synchronize()
+        out = L.out.cpu().numpy()
+        assert np.all(np.abs(out.astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
+        assert bool(torch.isnan(L.feat[cfg.n_local: cfg.n_local + cfg.n_send]).all())
+        want = out if want is None else want
+        assert np.array_equal(out.view(np.uint32), want.view(np.uint32)), f"schedule {schedule}"
 
 
 def _c0_partition(name):
