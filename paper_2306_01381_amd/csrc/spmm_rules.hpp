@@ -75,10 +75,10 @@ constexpr SlicedCut sliced_cut(int64_t n_rows, int64_t nnz, int64_t n_cols, int3
         return {v, v, n_blocks};
     }
     // Two per slice: past 200 000 columns, six times what an L2 holds of one line each, if lines come in pairs (plain rows
-    // 1.02-1.2; one line 0.95-1.15).  Packed rows prefer four lines, whose codes share a line; a cut that serves both needs
-    // shares of 1 900 entries.
+    // 1.02-1.2; one line 0.95-1.15).  Wide packed rows prefer four lines, whose codes share a line (512 columns 0.92-1.0 against
+    // 0.80-0.93); a cut that serves both needs shares of 1 900 entries (256 columns: 1.08 ms, 1.11; 1.06, 1.05 as fast as the path).
     if (n_cols > 200000 && lines % 2 == 0) {
-        if (lines >= 8 && nnz >= 1900 * 4 * (2 * kBlocks / fours)) return {2, 4, 2 * kBlocks / fours};
+        if (lines >= 10 && nnz >= 1900 * 4 * (2 * kBlocks / fours)) return {2, 4, 2 * kBlocks / fours};
         return {2, 2, kBlocks / (lines / 2)};
     }
     if (degree < 6 && lines >= 5) return kMergePath;        // (150 000 rows of four entries: 0.90-0.97)
