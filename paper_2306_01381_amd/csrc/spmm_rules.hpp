@@ -75,11 +75,12 @@ constexpr SlicedCut sliced_cut(int64_t n_rows, int64_t nnz, int64_t n_cols, int3
         return {v, v, n_blocks};
     }
     // Two per slice: past 200 000 columns, six times what an L2 holds of one line each, if lines come in pairs (plain rows
-    // 1.02-1.2; one line 0.95-1.15).  Wide packed rows prefer four lines, whose codes share a line (512 columns 0.92-1.0 against
-    // 0.80-0.93); a cut that serves both needs shares of 1 900 entries (256 columns: 1.08 ms, 1.11; 1.06, 1.05 as fast as the path).
+    // 1.02-1.2; one line 0.95-1.15).  Packed rows prefer four lines, whose codes share a line: with the same shares where the
+    // lines come in fours (256 columns 0.95, 1.02; but 192 columns 1.05, 0.9), and wide ones with more shares (512 columns 0.92-1.0
+    // against 0.80-0.93), which plain rows take without loss if they are 1 900 entries long and more than eight lines wide.
     if (n_cols > 200000 && lines % 2 == 0) {
         if (lines >= 10 && nnz >= 1900 * 4 * (2 * kBlocks / fours)) return {2, 4, 2 * kBlocks / fours};
-        return {2, 2, kBlocks / (lines / 2)};
+        return {2, lines % 4 == 0 ? 4 : 2, kBlocks / (lines / 2)};
     }
     if (degree < 6 && lines >= 5) return kMergePath;        // (150 000 rows of four entries: 0.90-0.97)
     // one per slice, up to eight workgroups per CU in all; packed rows four (352 columns 1.2 against 0.8 with one)
