@@ -33,7 +33,8 @@
  *   - Feature matrices are fp32 row-major with a leading dimension (pitch) ld >= dim, counted in elements.
  *   - Preferred layout ("line-padded"): base pointer 128-byte aligned and ld a multiple of 32, so that every
  *     row starts on a 128-byte line and covers whole lines.  Any other layout is accepted and gives the same
- *     values, but partial-line writes are slower.  For a line-padded OUTPUT matrix the calls below write the
+ *     values (the aggregation: the same sums, whose additions may come in another order), but partial-line writes
+ *     are slower.  For a line-padded OUTPUT matrix the calls below write the
  *     rows they produce in whole lines: columns [dim, 32*ceil(dim/32)) of a written row are set to +0.0f
  *     (columns beyond that, and rows that are not written, stay untouched).  For any other output layout
  *     only columns [0, dim) are written.  Padding columns of INPUT matrices may hold anything.
@@ -242,8 +243,8 @@ int adaqp_plan_slot_of_row(int64_t n_rows, int64_t n, const int32_t *halo_idx_ho
 /* adaqp_spmm_csr with some rows of H still packed: an entry whose column c has slot_of_row[c] = t >= 0 takes
  * the neighbour row from the receive buffer (packed + row_offset[t], bits[t], params[t]) and de-quantises it
  * in registers, (float)code * S + Z with the two roundings of Eq. 5, instead of reading H[c].  The result is
- * bit-identical to adaqp_unpack_dequant into H followed by adaqp_spmm_csr; the rows of H are neither written
- * nor read.  A slot that is out of range falls back to H[c].  slot_of_row_dev NULL: plain adaqp_spmm_csr.
+ * bit-identical to adaqp_unpack_dequant into H followed by adaqp_spmm_csr (packed_bytes below 2^32 - 2^16; beyond,
+ * the additions may come in another order); the rows of H are neither written nor read.  A slot that is out of range falls back to H[c].  slot_of_row_dev NULL: plain adaqp_spmm_csr.
  *   slot_of_row_dev [n_cols] int32;  per-slot arrays [n_slots] as for adaqp_unpack_dequant.
  * Errors: as adaqp_spmm_csr; EINVAL if slot_of_row_dev is given without the per-slot arrays. */
 int adaqp_spmm_csr_packed(const int64_t *rowptr_dev, const int32_t *col_dev, const float *val_dev, int64_t nnz,

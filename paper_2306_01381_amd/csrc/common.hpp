@@ -18,8 +18,8 @@ int note_hip_error(hipError_t err, const char *what);
     } while (0)
 
 // adaqp_spmm_csr_packed (slot_of_row_dev NULL: adaqp_spmm_csr) with what the caller knows about the columns: skewed_columns
-// = a few columns hold most of the entries, as in a transposed graph, whose columns are used as often as their nodes'
-// degrees say.  It only picks how the work is cut.
+// = a few columns hold most of the entries, as in a transposed graph of power-law degrees, whose columns are used as often as
+// their nodes' degrees say.  It only picks how the work is cut.
 int spmm_rows(const int64_t *rowptr_dev, const int32_t *col_dev, const float *val_dev, int64_t nnz, int64_t row_begin,
               int64_t row_end, int64_t nnz_range, const float *H_dev, int64_t n_cols, int64_t ldh, int32_t dim,
               float *out_dev, int64_t ldo, const int32_t *slot_of_row_dev, const uint8_t *packed_dev,

@@ -60,7 +60,8 @@ constexpr SlicedCut sliced_cut(int64_t n_rows, int64_t nnz, int64_t n_cols, int3
     // Lines per slice.  With four, one LDS read, one address and one row end serve four loads; with one, an L2 holds four times
     // as many rows: one pays where rows are long and the columns too many for an L2 to hold four lines of each (measured break-even
     // at 224 columns of H: 12 entries x 50 000 columns, 20 x 34 000, 40 x 20 000).  Where a few columns hold most of the
-    // entries four lines of those fit anyway.
+    // entries four lines of those fit anyway: transposed graph, power-law degrees, 150 000 columns, 30 entries per row, 256 columns of
+    // H four lines 1.27, one 0.98.  (The caller says so by the direction; log-normal degrees there 1.11, 1.43.)
     const bool many = !skewed_columns && n_cols > 10240 && degree * n_cols > 700000;
     if (!many) {
         // rows of four or five entries: only where no slice is a line or three wide (160 columns 0.8-0.9, 352 columns packed 0.8)

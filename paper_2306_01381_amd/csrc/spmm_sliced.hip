@@ -17,8 +17,9 @@
 // a share begins in is finished by the carry kernel, from the part that the share before it left.  The summation
 // order depends on the launch geometry only.
 //
-// Bound: what a slice misses in its L2 (7-8 TB/s behind the L2s), and where it fits, the rate at which a CU takes 16-byte
-// gathers (32 TB/s over the chip for bare loads out of L2; this loop 25-28).  Measured against the merge-path kernel
+// Bound: what a slice misses in its L2 (306 000 x 456 000, 256 columns: 17 % hits, 7.3 TB/s behind the L2s), and where it fits,
+// the rate at which a CU takes 16-byte gathers (32 TB/s over the chip for bare loads out of L2; this loop 25-28, and 19.8 with
+// 81 % hits on the transposed graph below).  Measured against the merge-path kernel
 // walking whole rows (aggregation of all rows, before -> after): 50 000 x 30 000, 4 M entries, 128 columns 0.239 ->
 // 0.096 ms; 34 000 columns, 0.42 M entries, 66 columns 0.050 -> 0.027; 376 000 x 196 000, 16.2 M entries, 256 columns
 // (transposed graph) 0.96 -> 0.80; 306 000 x 456 000, 7.7 M entries, 256 columns 1.13 -> 1.07; 179 000 x 269 000, 2 M
