@@ -9,17 +9,25 @@
 // (8 bytes each) are read once per slice.
 //
 // Work split: a wave walks a contiguous share of the merge path of row ends and entries (as in spmm.hip).  Its entries
-// go through LDS 8 at a time: one load instruction per line fetches the lines of 8 consecutive entries, a lane holding
-// four columns of one of them, and kAhead such steps are in flight at any time, across row ends and across the chunks
-// in which entries are staged.  A step in which no row ends costs one LDS read, one add and 4 multiply-adds per line;
-// where a row ends, the products of the groups before the end are added to the row's sums, these are added across the
+// go through LDS in chunks: one load instruction per line fetches the lines of 8 consecutive entries, a lane holding
+// four columns of one of them, and kAhead such steps are in flight at any time, across row ends and across chunks.
+// A step in which no row ends (a bit per step says so) costs half an LDS read, one add, one jump and 4 multiply-adds per
+// line; where a row ends, the products of the groups before the end are added to the row's sums, these are added across the
 // eight groups (halving the registers at each level) and stored, and the products after it start the next row.  The row
 // a share begins in is finished by the carry kernel, from the part that the share before it left.  The summation
 // order depends on the launch geometry only.
 //
+// The L1 answers loads in order: a load of entries, which always comes from behind the L2, holds up every gather of the CU
+// that would hit (bare gathers with 3 KB of entries per 48 of them: 21 TB/s where the entries come from memory, 28 where they
+// are in the L2; 24-25 if four times as many are asked for four times as rarely).  So chunks are large, a lane loads four
+// entries at a time and no line of col or val is asked for twice: chunks begin at multiples of a line once the first is over.
+// 8 M entries in rows of 2 048, 20 000 columns, 256 columns of H, one line per slice: 384 entries per chunk and four
+// per lane and load apart 18.0 TB/s, so 21.0; 30 000 x 20 000 backward step of 4 M entries 109 -> 106 us.
+//
 // Bound: what a slice misses in its L2 (306 000 x 456 000, 256 columns: 17 % hits, 7.3 TB/s behind the L2s), and where it fits,
 // the rate at which a CU takes 16-byte gathers (32 TB/s over the chip for bare loads out of L2; this loop 25-28, and 19.8 with
-// 81 % hits on the transposed graph below).  Measured against the merge-path kernel
+// 81 % hits on the transposed graph below).  Columns of H must not all fall on the same channels of an L2: a pitch of 8 lines
+// costs a slice of one line a quarter of its rate (28 M entries, 98 000 columns: 2.48 ms, 1.93 at a pitch of 9).  Measured against the merge-path kernel
 // walking whole rows (aggregation of all rows, before -> after): 50 000 x 30 000, 4 M entries, 128 columns 0.239 ->
 // 0.096 ms; 34 000 columns, 0.42 M entries, 66 columns 0.050 -> 0.027; 376 000 x 196 000, 16.2 M entries, 256 columns
 // (transposed graph) 0.96 -> 0.80; 306 000 x 456 000, 7.7 M entries, 256 columns 1.13 -> 1.07; 179 000 x 269 000, 2 M
@@ -34,12 +42,16 @@
 namespace adaqp {
 namespace {
 
+// A lambda that is not inlined keeps what it captures in scratch memory.
+#define ADAQP_INLINE __attribute__((always_inline))
+
 constexpr int64_t kMinPath = 1024;                  // of a workgroup's four shares
 constexpr int kStep = 8;                            // entries of a step = groups of a wave
 constexpr int kGroup = kWave / kStep;               // lanes per entry: 8 x 16 bytes = one line
 constexpr int kLine = 32;                           // columns per line
-constexpr int kPer = 6;                             // entries a lane stages per chunk
-constexpr int kChunk = kPer * kWave;                // entries of a chunk: a whole number of rings for every VPL
+constexpr int kLoads = 3;                           // of four entries per lane: what a chunk takes of col, and of val
+constexpr int kChunk = kLoads * 4 * kWave;          // entries of a chunk
+constexpr int kPart = kChunk / 2;                   // no sum runs longer: a whole number of rings for every VPL
 constexpr int kEnds = kWave - 1;                    // row ends of a chunk at most
 constexpr int32_t kNoEnd = 0x10000;                 // lies after every step of a chunk
 constexpr int kRowSteps = 8;                        // entries a row end counts for where shares are cut
@@ -53,6 +65,7 @@ struct SlicedArgs {
 };
 
 typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef int int4_t __attribute__((ext_vector_type(4)));
 
 // An entry in LDS: byte offset of its row of H and its coefficient.  PACKED: bits 0-1 of the offset name the width of
 // a row that is still packed (1, 2, 3: 2, 4, 8 bits; the offset is then one into the receive buffer) and (Z, S) follow.
@@ -71,7 +84,7 @@ __device__ __forceinline__ void unroll(F &&f)
 
 // Row ends before two diagonals of the merge path: row end p precedes d iff end_p + kRowSteps * (p + 1) <= d.  256-ary
 // search by a whole wave; wave-uniform results.
-__device__ void split_rows2(const SpmmArgs &a, const int64_t (&d)[2], int64_t base, int64_t nnz_r, int lane, int32_t (&at)[2])
+__device__ __forceinline__ void split_rows2(const SpmmArgs &a, const int64_t (&d)[2], int64_t base, int64_t nnz_r, int lane, int32_t (&at)[2])
 {
     constexpr int K = kProbes / kWave;
     int32_t lo[2], hi[2];
@@ -132,15 +145,27 @@ __device__ __forceinline__ float ror8(float v)
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int32_t, v), 0x128, 0xF, 0xF, false));
 }
 
+// x of all lanes or-ed together.
+__device__ __forceinline__ uint32_t or_lanes(uint32_t x)
+{
+    int32_t v = (int32_t)x;
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, false);     // row_ror:1, 2, 4, 8: the row of 16 lanes
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, false);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);
+    return (uint32_t)(__builtin_amdgcn_readlane(v, 0) | __builtin_amdgcn_readlane(v, 16) | __builtin_amdgcn_readlane(v, 32) |
+                      __builtin_amdgcn_readlane(v, 48));
+}
+
 // One wave's share of the path for one slice of VPL lines.  WHOLE: rows of H and out start on lines and have whole lines
 // of room.  Otherwise rows start anywhere (4-byte aligned) and end after a.dim columns: a lane whose four columns would
 // not end in the row takes the row's last four, and columns that two lanes hold are stored twice with the same bits.
 template <int VPL, bool PACKED, bool WHOLE>
-__device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const int32_t item, Entry<PACKED> (*stages)[kChunk])
+__device__ __forceinline__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const int32_t item, Entry<PACKED> *stage_of_wave)
 {
     constexpr int kAhead = VPL >= 3 ? 2 : 8 / VPL;          // steps in flight: 6 to 8 KB per wave
     constexpr int kRing = kAhead * kStep;                   // entries of a turn of the ring
-    static_assert(kChunk % kRing == 0, "a chunk is a whole number of turns");
+    static_assert(kPart % kRing == 0 && kPart / kStep <= 64, "a part is a whole number of turns, a bit per step");
     const SpmmArgs &a = sa.s;
     const int lane = threadIdx.x & (kWave - 1), gl = lane & (kGroup - 1), grp = lane / kGroup;
 
@@ -164,16 +189,15 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
     if (j[1] < j[0]) j[1] = j[0];
 
     const int32_t c0 = first_line * kLine + gl * 4;         // first column of the lane's line 0
-    // one buffer per line of the slice; rows of any length: one buffer, and the lane's column in each line
-    __amdgpu_buffer_rsrc_t rows[VPL];
+    // whole lines: from the slice's first line on, line v of a row in the instruction's offset; rows of any length: from the
+    // first column on, and the lane's column in each line
+    const int32_t begin = WHOLE ? first_line * kLine : 0;
+    const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.H + begin), 0,
+                                                        (int)buffer_extent(a.n_cols, a.ldh, begin), kRawBuffer);
     uint32_t lane_off[VPL];
 #pragma unroll
-    for (int v = 0; v < VPL; ++v) {
-        const int32_t begin = WHOLE ? (first_line + v) * kLine : 0;
-        rows[v] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.H + begin), 0,
-                                                    (int)(uint32_t)(a.n_cols * a.ldh * 4 - begin * 4), kRawBuffer);
-        lane_off[v] = WHOLE ? gl * 16 : (uint32_t)min(c0 + v * kLine, a.dim - 4) * 4;
-    }
+    for (int v = 0; v < VPL; ++v)
+        lane_off[v] = WHOLE ? gl * 16 + v * kLine * 4 : (uint32_t)min(c0 + v * kLine, a.dim - 4) * 4;
     const auto packed_rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.packed), 0,
                                                                (int)(uint32_t)a.packed_bytes, kRawBuffer);
     const uint32_t pitch = (uint32_t)a.ldh * 4u;
@@ -181,7 +205,7 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
     // After `sum_groups` lane l (and lane l + 32) holds column l of each line.
     const int line_col = lane & (kLine - 1);
     const int from_lane = ((line_col & 3) * 16 + line_col / 4) << 2;
-    auto column_of = [&](int v) {                           // the column lane l holds a sum of; negative: none of its own
+    auto column_of = [&](int v) ADAQP_INLINE {                           // the column lane l holds a sum of; negative: none of its own
         const int32_t line = (first_line + v) * kLine;
         if constexpr (WHOLE) return line + line_col;
         const int32_t four = line + (line_col & ~3);
@@ -203,92 +227,124 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
         int32_t row0, n_end, n_ent;                         // first row, row ends, entries
         int64_t ent0;                                       // first entry
         int32_t ends;                                       // lane l: where row row0 + l ends in the chunk, else kNoEnd
+        uint64_t marks[2];                                  // bit s: a row ends in step s of the part, after one of its entries
     };
     int64_t r_hi;
-    auto request_rows = [&](int32_t row) {
+    auto request_rows = [&](int32_t row) ADAQP_INLINE {
         const int64_t r = (int64_t)row + lane + 1;
         r_hi = a.rowptr[r < a.n_rows ? r : a.n_rows];
     };
-    auto take = [&](int32_t row0, int64_t ent0) {           // from r_hi, requested for row0
+    auto take = [&](int32_t row0, int64_t ent0) ADAQP_INLINE {           // from r_hi, requested for row0
         Chunk c;
         c.row0 = row0;
         c.ent0 = ent0;
         const int64_t end = clamp64(clamp64(r_hi, base, base + nnz_r) - base - ent0, 0, kNoEnd);
         c.ends = (int32_t)end;
         const int64_t left = j[1] - ent0;
-        c.n_ent = (int32_t)(left < kChunk ? left : kChunk);
+        const int64_t most = kChunk - ((base + ent0) & (kLine - 1));       // up to a line of col and val
+        c.n_ent = (int32_t)(left < most ? left : most);
         c.n_end = __popcll(__ballot(lane < kEnds && row0 + lane < i[1] && c.ends <= c.n_ent));
         if (c.n_end == kEnds) c.n_ent = min(c.n_ent, __builtin_amdgcn_readlane(c.ends, kEnds - 1));
         if (lane >= c.n_end) c.ends = kNoEnd;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int32_t last = c.ends - 1 - p * kPart;    // entry of the part that is its row's last
+            const uint64_t mark = last >= 0 && last < kPart ? (uint64_t)1 << (last / kStep) : 0;
+            c.marks[p] = (uint64_t)or_lanes((uint32_t)(mark >> 32)) << 32 | or_lanes((uint32_t)mark);
+        }
         return c;
     };
-    int32_t st_col[kPer];
-    float st_val[kPer];
-    auto request_entries = [&](const Chunk &c) {            // past the chunk's entries: zeros
+    int4_t st_col[kLoads];
+    float4_t st_val[kLoads];
+    auto request_entries = [&](const Chunk &c) ADAQP_INLINE {            // past the chunk's entries: zeros
         const auto cols = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.col + base + c.ent0), 0, c.n_ent * 4, kRawBuffer);
         const auto vals = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.val + base + c.ent0), 0, c.n_ent * 4, kRawBuffer);
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {                    // streamed: keep the caches for H
-            const int at = lane * 4 + k * kWave * 4;        // all of it here: the scalar offset is outside the range check
-            st_col[k] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(cols, at, 0, kNonTemporal);
-            st_val[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vals, at, 0, kNonTemporal));
+        for (int k = 0; k < kLoads; ++k) {                  // streamed: keep the caches for H
+            const int at = (k * kWave + lane) * 16;         // all of it here: the scalar offset is outside the range check
+            st_col[k] = __builtin_bit_cast(int4_t, __builtin_amdgcn_raw_buffer_load_b128(cols, at, 0, kNonTemporal));
+            st_val[k] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(vals, at, 0, kNonTemporal));
         }
     };
-    auto stage = [&](const Chunk &c, Entry<PACKED> *ent) {
-        Entry<PACKED> en[kPer];
+    auto stage = [&](const Chunk &c) ADAQP_INLINE {
+        auto valid = [&](int k, int q) ADAQP_INLINE {                    // else: fetches nothing
+            return (k * kWave + lane) * 4 + q < c.n_ent && (uint32_t)st_col[k][q] < (uint32_t)a.n_cols;
+        };
+        int4_t slots[kLoads];
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int32_t col = st_col[k];
-            const bool ok = k * kWave + lane < c.n_ent && col >= 0 && col < a.n_cols;       // else: fetches nothing
-            en[k] = {};
-            en[k].off = ok ? (uint32_t)col * pitch : kOutside;
-            en[k].val = ok ? st_val[k] : 0.0f;
-        }
-        if constexpr (PACKED) {
-            // all lookups of a chunk are on their way together, those of entries without a slot at index 0: behind a branch
-            // each they would wait for one another, six times two latencies per chunk
-            int32_t slot[kPer], b[kPer];
-            int64_t off[kPer];
-            float2 zs[kPer];
+        for (int k = 0; k < kLoads; ++k) {
+            // here and not earlier: the compiler would take the entries of a chunk apart when they arrive, for twice the registers
+            asm volatile("" : "+v"(st_col[k]));
+            if constexpr (PACKED) {                         // all slots of a chunk on their way together, none: index 0
+                if (k == 0 || k * 4 * kWave < c.n_ent) {
 #pragma unroll
-            for (int k = 0; k < kPer; ++k) slot[k] = a.slot_of_row[en[k].off != kOutside ? st_col[k] : 0];
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) {
-                const bool has = en[k].off != kOutside && slot[k] >= 0 && slot[k] < a.n_slots;
-                slot[k] = has ? slot[k] : -1;
-                const int64_t at = has ? slot[k] : 0;
-                b[k] = a.bits[at];
-                off[k] = a.row_offset[at];
-                zs[k] = *reinterpret_cast<const float2 *>(a.params + 2 * at);
-            }
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) {
-                const int64_t stride = 4 * (((int64_t)a.full_dim * b[k] + 31) >> 5);
-                if (slot[k] >= 0 && (b[k] == 2 || b[k] == 4 || b[k] == 8) && off[k] >= 0 && (off[k] & 3) == 0 &&
-                    off[k] + stride <= a.packed_bytes) {
-                    en[k].off = (uint32_t)off[k] | (b[k] == 2 ? 1u : (b[k] == 4 ? 2u : 3u));
-                    en[k].z = zs[k].x;
-                    en[k].s = zs[k].y;
-                }                                           // else: the row in H
+                    for (int q = 0; q < 4; ++q) slots[k][q] = a.slot_of_row[valid(k, q) ? st_col[k][q] : 0];
+                }
             }
         }
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) ent[k * kWave + lane] = en[k];
+        for (int k = 0; k < kLoads; ++k) {
+            if (k > 0 && k * 4 * kWave >= c.n_ent) break;   // a whole number of turns past every entry: never read
+            Entry<PACKED> en[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const bool ok = valid(k, q);
+                en[q] = {};
+                en[q].off = ok ? (uint32_t)st_col[k][q] * pitch : kOutside;
+                en[q].val = ok ? st_val[k][q] : 0.0f;
+            }
+            if constexpr (PACKED) {
+                // the lookups of four entries are on their way together, those of entries without a slot at index 0: behind a
+                // branch each they would wait for one another
+                int32_t slot[4], b[4];
+                int64_t off[4];
+                float2 zs[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const bool has = en[q].off != kOutside && slots[k][q] >= 0 && slots[k][q] < a.n_slots;
+                    slot[q] = has ? slots[k][q] : -1;
+                    const int64_t at = has ? slot[q] : 0;
+                    b[q] = a.bits[at];
+                    off[q] = a.row_offset[at];
+                    zs[q] = *reinterpret_cast<const float2 *>(a.params + 2 * at);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t stride = 4 * (((int64_t)a.full_dim * b[q] + 31) >> 5);
+                    if (slot[q] >= 0 && (b[q] == 2 || b[q] == 4 || b[q] == 8) && off[q] >= 0 && (off[q] & 3) == 0 &&
+                        off[q] + stride <= a.packed_bytes) {
+                        en[q].off = (uint32_t)off[q] | (b[q] == 2 ? 1u : (b[q] == 4 ? 2u : 3u));
+                        en[q].z = zs[q].x;
+                        en[q].s = zs[q].y;
+                    }                                       // else: the row in H
+                }
+            }
+            Entry<PACKED> *to = stage_of_wave + (k * kWave + lane) * 4;
+            if constexpr (PACKED) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) to[q] = en[q];
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; q += 2)
+                    *reinterpret_cast<float4_t *>(to + q) = float4_t{__builtin_bit_cast(float, en[q].off), en[q].val,
+                                                                     __builtin_bit_cast(float, en[q + 1].off), en[q + 1].val};
+            }
+        }
     };
 
     // the ring: kAhead steps whose lines are on their way
     float4_t h[kAhead][VPL];
     uint32_t words[kAhead][VPL], words_up[kAhead][VPL];     // four codes, where rows end anywhere across two words
     Entry<PACKED> in_flight[kAhead];
-    auto packed_col = [&](int v) { return (uint32_t)a.col0 + (WHOLE ? (uint32_t)(c0 + v * kLine) : lane_off[v] / 4); };
-    auto fetch = [&](auto tag, const Entry<PACKED> &en) {
+    auto packed_col = [&](int v) ADAQP_INLINE { return (uint32_t)a.col0 + (WHOLE ? (uint32_t)(c0 + v * kLine) : lane_off[v] / 4); };
+    auto fetch = [&](auto tag, const Entry<PACKED> &en) ADAQP_INLINE {
         constexpr int U = decltype(tag)::value;
         in_flight[U] = en;
         const uint32_t w = PACKED ? en.off & 3u : 0u;
 #pragma unroll
         for (int v = 0; v < VPL; ++v) {
             const uint32_t off = PACKED && w != 0 ? kOutside : en.off + lane_off[v];
-            h[U][v] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(rows[v], (int)off, 0, 0));
+            h[U][v] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, 0));
             if constexpr (PACKED) {
                 // one 32-bit word holds the four codes of a lane whose first column is a multiple of four (4 * b <= 32 and
                 // divides 32)
@@ -302,7 +358,7 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
             }
         }
     };
-    auto neighbour = [&](auto tag, int v) {                 // the four columns a lane fetched
+    auto neighbour = [&](auto tag, int v) ADAQP_INLINE {                 // the four columns a lane fetched
         constexpr int U = decltype(tag)::value;
         float4_t x = h[U][v];
         if constexpr (PACKED) {
@@ -326,7 +382,6 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
     // shares of a row (one running sum over a share would be thousands of terms long and rounds accordingly).
     float4_t acc[VPL];
     float before[VPL];
-    bool has_before = false;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
@@ -334,40 +389,58 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
     }
     auto take_sums = [&](float (&sum)[VPL]) {               // and start anew
         sum_groups(acc, sum);
-        if (has_before) {
 #pragma unroll
-            for (int v = 0; v < VPL; ++v) sum[v] = before[v] + sum[v];
-            has_before = false;
+        for (int v = 0; v < VPL; ++v) {
+            sum[v] = before[v] + sum[v];
+            before[v] = 0.0f;
+            acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
         }
-#pragma unroll
-        for (int v = 0; v < VPL; ++v) acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
     };
-    float *out_row = a.out + (int64_t)i[0] * a.ldo;         // the rows of a share end one after the other
-    auto finish_row = [&]() {
+    auto keep_sums = [&]() ADAQP_INLINE {
         float sum[VPL];
         take_sums(sum);
 #pragma unroll
-        for (int v = 0; v < VPL; ++v) {
-            const int32_t c = column_of(v);
-            if constexpr (WHOLE) {
-                if (lane < kLine) __builtin_nontemporal_store(c < a.dim ? sum[v] : 0.0f, out_row + (uint32_t)c);
-            } else {                                        // lines are shared with other rows: left for the L2 to merge
-                if (lane < kLine && c >= 0) out_row[c] = sum[v];
-            }
+        for (int v = 0; v < VPL; ++v) before[v] = sum[v];
+    };
+    float *out_row = a.out + (int64_t)i[0] * a.ldo;         // the rows of a share end one after the other
+    // Lanes without a column of their own store outside the row's buffer: a branch around the store would be one the compiler
+    // cannot take for uniform, and cost every step of the ring copies of the sums and a second jump.
+    uint32_t store_at[VPL];
+#pragma unroll
+    for (int v = 0; v < VPL; ++v)
+        store_at[v] = lane < kLine && column_of(v) >= 0 ? (uint32_t)column_of(v) * 4u : kOutside;
+    auto store_row = [&](float *row, const float (&sum)[VPL], auto policy) {
+        const auto to = __builtin_amdgcn_make_buffer_rsrc(row, 0, a.wdim * 4, kRawBuffer);
+#pragma unroll
+        for (int v = 0; v < VPL; ++v)
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sum[v]), to, (int)store_at[v], 0, decltype(policy)::value);
+    };
+    auto finish_row = [&]() ADAQP_INLINE {
+        float sum[VPL];
+        take_sums(sum);
+        if constexpr (WHOLE) {
+#pragma unroll
+            for (int v = 0; v < VPL; ++v) sum[v] = column_of(v) < a.dim ? sum[v] : 0.0f;
+            store_row(out_row, sum, std::integral_constant<int, kNonTemporal>());
+        } else {                                            // lines are shared with other rows: left for the L2 to merge
+            store_row(out_row, sum, std::integral_constant<int, 0>());
         }
         out_row += a.ldo;
     };
 
+    // The walk starts behind a chunk of nothing, whose one turn finds an empty ring and fills it: staging and the first fetches
+    // would be a second copy of that code, which a short launch pays for in instruction fetches.
     request_rows(i[0]);
-    Chunk cur = take(i[0], j[0]);
-    request_entries(cur);
-    request_rows(cur.row0 + cur.n_end);
-    int buf = 0;
-    stage(cur, stages[0]);
-    unroll<0, kAhead>([&](auto tag) {
-        fetch(tag, stages[0][decltype(tag)::value * kStep + grp]);
-        __builtin_amdgcn_sched_barrier(0);                  // the order of issue is the order of use
-    });
+    Chunk cur = {i[0], 0, 0, j[0], kNoEnd, {0, 0}};
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+        in_flight[u] = {};
+#pragma unroll
+        for (int v = 0; v < VPL; ++v) {
+            h[u][v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            words[u][v] = words_up[u][v] = 0;
+        }
+    }
     for (;;) {
         const int32_t next_row = cur.row0 + cur.n_end;
         const int64_t next_ent = cur.ent0 + cur.n_ent;
@@ -377,71 +450,71 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
             request_entries(next);
             request_rows(next.row0 + next.n_end);
         }
-        int32_t e = 0, end = __builtin_amdgcn_readlane(cur.ends, 0);       // next row end
-        while (end == 0) {                                  // ends that belong to what the chunks before have added up
+        int32_t e = 0;                                      // row ends behind us
+        while (__builtin_amdgcn_readlane(cur.ends, e) == 0) {   // that belong to what the chunks before have added up
             finish_row();
-            end = __builtin_amdgcn_readlane(cur.ends, ++e);
+            ++e;
         }
         const int32_t turns = cur.n_ent > 0 ? (cur.n_ent + kRing - 1) / kRing : 1;
+        uint64_t marks = cur.marks[0];
         for (int32_t t = 0; t < turns; ++t) {
-            const Entry<PACKED> *src = stages[buf] + (t + 1) * kRing + grp;
-            if (t + 1 == turns) {                           // the ring goes on in the next chunk
-                if (more) stage(next, stages[buf ^ 1]);
-                else if (lane < kRing) stages[buf ^ 1][lane] = Entry<PACKED>{kOutside, 0.0f};
-                src = stages[buf ^ 1] + grp;
+            if (t == kPart / kRing) {                       // the chunk's second part
+                keep_sums();
+                marks = cur.marks[1];
             }
-            Entry<PACKED> en = src[0];
+            const Entry<PACKED> *src = stage_of_wave + (t + 1) * kRing + grp;
+            if (t + 1 == turns) {                           // the ring goes on in the next chunk: all of this one has been read
+                if (more) stage(next);
+                else if (lane < kRing) stage_of_wave[lane] = Entry<PACKED>{kOutside, 0.0f};
+                src = stage_of_wave + grp;
+            }
+            Entry<PACKED> en[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) en[u] = src[u * kStep];
+            __builtin_amdgcn_sched_barrier(0);
             unroll<0, kAhead>([&](auto tag) {
                 constexpr int U = decltype(tag)::value;
-                const Entry<PACKED> now = en;
-                if (U + 1 < kAhead) en = src[(U + 1) * kStep];
-                __builtin_amdgcn_sched_barrier(0);
-                const int32_t rel = end - t * kRing - U * kStep;        // where in this step a row ends
-                float4_t unpacked[VPL];                         // once per step; plain rows as they came
-                if constexpr (PACKED) {
+                float4_t x[VPL];
+                float val = in_flight[U].val;
 #pragma unroll
-                    for (int v = 0; v < VPL; ++v) unpacked[v] = neighbour(tag, v);
-                }
-                auto &x = *(PACKED ? &unpacked : &h[U]);
-                if (rel > kStep) {
-#pragma unroll
-                    for (int v = 0; v < VPL; ++v)
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) acc[v][k] = fmaf(in_flight[U].val, x[v][k], acc[v][k]);
-                } else {
+                for (int v = 0; v < VPL; ++v) x[v] = neighbour(tag, v);
+                if ((uint32_t)marks & (1u << U)) {
                     // the groups from the last end to this one belong to the row that ends here
-                    int32_t from = 0, to = rel;
+                    const int32_t at = (t * kAhead + U) * kStep;
+                    int32_t from = 0, to = __builtin_amdgcn_readlane(cur.ends, e) - at;
                     do {
                         const bool mine = grp >= from && grp < to;
 #pragma unroll
                         for (int v = 0; v < VPL; ++v)
 #pragma unroll
                             for (int k = 0; k < 4; ++k) {
-                                const float sum = fmaf(in_flight[U].val, x[v][k], acc[v][k]);
+                                const float sum = fmaf(val, x[v][k], acc[v][k]);
                                 acc[v][k] = mine ? sum : acc[v][k];
                             }
                         finish_row();
-                        end = __builtin_amdgcn_readlane(cur.ends, ++e);
+                        ++e;
                         from = to;
-                        to = end - t * kRing - U * kStep;
+                        to = __builtin_amdgcn_readlane(cur.ends, e) - at;
                     } while (to <= kStep);
+                    // what is left is the next row's; no else: the sums would be copied where two branches meet
+                    val = grp >= from ? val : 0.0f;
 #pragma unroll
                     for (int v = 0; v < VPL; ++v)
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) acc[v][k] = grp >= from ? in_flight[U].val * x[v][k] : 0.0f;
+                        for (int k = 0; k < 4; ++k) x[v][k] = grp >= from ? x[v][k] : 0.0f;
                 }
-                fetch(tag, now);
+#pragma unroll
+                for (int v = 0; v < VPL; ++v)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) acc[v][k] = fmaf(val, x[v][k], acc[v][k]);
+                fetch(tag, en[U]);
                 __builtin_amdgcn_sched_barrier(0);
             });
+            marks >>= kAhead;
         }
         if (!more) break;
-        float sum[VPL];                                     // the open row goes on in the next chunk
-        take_sums(sum);
-#pragma unroll
-        for (int v = 0; v < VPL; ++v) before[v] = sum[v];
-        has_before = true;
+        keep_sums();                                        // the open row goes on in the next chunk
         cur = next;
-        buf ^= 1;
     }
     // what is left belongs to a row that goes on in the next wave's share
     const int64_t began = i[1] < a.n_rows ? clamp64(a.rowptr[i[1]], base, base + nnz_r) - base : nnz_r;
@@ -449,9 +522,7 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
     if (held) {
         float sum[VPL];
         take_sums(sum);
-#pragma unroll
-        for (int v = 0; v < VPL; ++v)
-            if (lane < kLine && column_of(v) >= 0) a.carry[(int64_t)item * a.carry_ld + column_of(v)] = sum[v];
+        store_row(a.carry + (int64_t)item * a.carry_ld, sum, std::integral_constant<int, 0>());
     }
     if (first_line == 0 && lane == 0) a.carry_row[item] = held ? i[1] : -1;
 }
@@ -459,7 +530,7 @@ __device__ void walk_share(const SlicedArgs &sa, const int32_t first_line, const
 template <int VPL, bool PACKED, bool WHOLE>
 __global__ __launch_bounds__(kBlock, 2) void spmm_sliced_kernel(const SlicedArgs sa)
 {
-    __shared__ Entry<PACKED> stages[kWavesPerBlock][2][kChunk];
+    __shared__ alignas(16) Entry<PACKED> stages[kWavesPerBlock][kChunk];
     const SliceTasks tasks(sa.lines, VPL, sa.n_blocks, PACKED);
     const int32_t xcd = blockIdx.x % kXcds;
     const int64_t task = tasks.first_task(xcd) + blockIdx.x / kXcds;
@@ -469,9 +540,9 @@ __global__ __launch_bounds__(kBlock, 2) void spmm_sliced_kernel(const SlicedArgs
     const int32_t item = blk * kWavesPerBlock + wave;
     const int live = min(VPL, sa.lines - slice * VPL);
     if (live == VPL) walk_share<VPL, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
-    else if (VPL > 3 && live == 3) walk_share<3, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
-    else if (VPL > 2 && live == 2) walk_share<2, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
-    else walk_share<1, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
+    if constexpr (VPL > 3) if (live == 3) walk_share<3, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
+    if constexpr (VPL > 2) if (live == 2) walk_share<2, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
+    if constexpr (VPL > 1) if (live == 1) walk_share<1, PACKED, WHOLE>(sa, slice * VPL, item, stages[wave]);
 }
 
 }  // namespace

@@ -419,6 +419,22 @@ def test_spmm_degenerate(oracle):
     assert np.all(got == 7.0)
 
 
+@pytest.mark.parametrize("dim,ldh", [(256, 288), (96, 96), (60, 61)])       # one line per slice, three, rows that share lines
+@pytest.mark.parametrize("base", [0, 1, 31])                                # first entry of the range: chunks end at multiples of 32
+def test_spmm_sliced_chunks(oracle, dim, ldh, base):
+    """Rows that end next to the bounds of a chunk (768 entries) and of its parts (384): one to two entries off them, empty rows
+    there, rows of several chunks, and runs of more than 63 row ends, which cut a chunk short."""
+    _say(f"spmm sliced chunks dim={dim} ldh={ldh} base={base}")
+    rng = np.random.default_rng(77)
+    near = [384 + d for d in (-2, -1, 0, 0, 1, 2)] + [768 + d for d in (-1, 0, 1)] + [2304, 353, 31, 0, 0, 1, 736, 32, 383]
+    degs = np.array([base] + (near + [0] * 70 + near[::-1] + [8] * 70 + [1] * 130) * 16)
+    rowptr, col, val = _random_graph(rng, degs.size, 20_000, degs)
+    H = np.zeros((20_000, ldh), dtype=np.float32)
+    H[:, :dim] = rng.standard_normal((20_000, dim))
+    assert rowptr[1] == base and rowptr[-1] >= 150_000
+    _check_spmm(oracle, rowptr, col, val, 1, degs.size, H, dim)
+
+
 @pytest.mark.parametrize("dim,n_cols", [(608, 64), (608, 12_000), (601, 64)])       # four lines per slice; one; rows that share lines
 def test_spmm_sliced_long_sums(dim, n_cols):
     """Rows far longer than a wave's share of a launch with few shares (16 000 entries each): no addition chain is longer than
