@@ -382,6 +382,61 @@ int adaqp_spmm_csr_panels(const adaqp_spmm_panels *panels_host, int64_t row_begi
                           void *workspace_dev, int64_t workspace_bytes, void *stream);
 
 /* ---------------------------------------------------------------------------------------------------- */
+/* Dense blocks: as the panels above for rows that list a good part of all columns, ADAQP_SPMM_BLOCK_ROWS of them at a
+ * time, on the bf16 matrix cores with fp32 operands split exactly into three bf16 (six of the nine partial products,
+ * none of those left out above 2^-24 of the product; fp32 sums).  The rows taken are struck from the tile table as for panels,
+ * and the call may run beside adaqp_spmm_csr_tiled in the same way.  H must be finite: a non-finite row reaches all rows of
+ * the blocks that list its column. */
+#define ADAQP_SPMM_BLOCK_ROWS 128
+#define ADAQP_SPMM_BLOCK_STEP 32        /* columns of a block are listed in multiples of this */
+
+/* Device side of a block plan for one row range.  The struct lives in host memory and is read during the call only. */
+typedef struct adaqp_spmm_blocks {
+    int32_t n_blocks;                   /* 0: no blocks, the struct is ignored */
+    int32_t n_pieces;                   /* column intervals, the same for all blocks */
+    int64_t n_steps;                    /* of ADAQP_SPMM_BLOCK_STEP columns, of all blocks together */
+    int32_t col_begin, piece_width;     /* interval p: columns col_begin + p * piece_width and the next piece_width - 1 */
+    const int32_t *rows_dev;            /* [n_blocks * 128] rows of out, -1 = unused */
+    const int32_t *step_ptr_dev;        /* [n_blocks * n_pieces + 1] first step of each (block, interval) */
+    const int32_t *cols_dev;            /* [n_steps][32] columns of H, ascending within (block, interval), the last repeated */
+    float *table_dev;                   /* [n_steps][4][2][64][8] coefficients: column 16 k + 8 h + j of a step, row 32 g + m
+                                           at [step][g][k][32 h + m][j]; adaqp_fill_spmm_blocks writes it */
+} adaqp_spmm_blocks;
+
+/* Host only.  Plans the blocks of rows [row_begin, row_end) of a host CSR (ascending, distinct, in-range columns per row) with
+ * at least min_row_len entries, longest first (ties: ascending row).  Two calls: with the three output arrays NULL to learn
+ * sizes_inout[6] = { rows taken, n_blocks, n_pieces, n_steps, col_begin, piece_width }, then with those sizes and arrays of
+ * n_blocks * 128, n_blocks * n_pieces + 1 and n_steps * 32.  tile_off_inout: NULL or adaqp_plan_spmm_tiles' table of the
+ * range, from which the rows taken are struck (entries -1; second call only).  dim only picks the number of intervals.
+ * Errors: EINVAL (bad rowptr or columns, sizes of another plan), ESIZE. */
+int adaqp_plan_spmm_blocks(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end,
+                           int64_t n_cols, int32_t dim, int32_t min_row_len, int64_t *sizes_inout,
+                           int32_t *tile_off_inout, int32_t *rows_out, int32_t *step_ptr_out, int32_t *cols_out);
+
+/* Host only: the row length from which a row is worth a place in a block, where the rows of the range reference columns below
+ * n_cols (column bound ADAQP_SPMM_TILES of adaqp_plan_spmm_tiles), and whether a plan that takes n_rows_taken rows is worth
+ * launching on a matrix of n_cols rows with a pitch of ldh floats (1) or not, or not possible (0). */
+int32_t adaqp_spmm_blocks_min_row(int64_t n_cols);
+int32_t adaqp_spmm_blocks_pay(int64_t n_rows_taken, int64_t n_cols, int64_t ldh);
+
+/* Floats of table_dev for that many steps. */
+int64_t adaqp_spmm_blocks_table_floats(int64_t n_steps);
+
+/* Writes blocks_host->table_dev from the CSR the plan was made for, once per graph (or whenever val changes). */
+int adaqp_fill_spmm_blocks(const adaqp_spmm_blocks *blocks_host, int64_t row_begin, int64_t row_end, const int64_t *rowptr_dev,
+                           const int32_t *col_dev, const float *val_dev, int64_t nnz, void *stream);
+
+/* Bytes of workspace adaqp_spmm_csr_blocks needs. */
+int adaqp_spmm_blocks_workspace_bytes(int32_t n_blocks, int32_t n_pieces, int32_t dim, int64_t *bytes_out);
+
+/* out[r, 0:dim] = sum_j val[j] * H[col[j], 0:dim] for the rows the plan took; others are not written.  Layout, alignment and
+ * padding as adaqp_spmm_csr_panels; workspace_dev: 256-byte aligned.  The order of additions is fixed by the plan.
+ * Errors: EINVAL, ESIZE (workspace, or H of 2^32 - 2^16 bytes and more), EHIP. */
+int adaqp_spmm_csr_blocks(const adaqp_spmm_blocks *blocks_host, int64_t row_begin, int64_t row_end, const float *H_dev,
+                          int64_t n_cols, int64_t ldh, int32_t dim, float *out_dev, int64_t ldo,
+                          void *workspace_dev, int64_t workspace_bytes, void *stream);
+
+/* ---------------------------------------------------------------------------------------------------- */
 /* One layer's aggregation step with the message path overlapped (Sec. 3.1, Sec. 3.4 Fig. 7).             */
 /* ---------------------------------------------------------------------------------------------------- */
 
@@ -452,6 +507,9 @@ typedef struct adaqp_layer_desc {
                                                de-quantisation) and both tiled launches to stream_agg, so that a
                                                panel kernel and a tiled kernel run side by side; otherwise a
                                                range's panels follow its tiled launch on the same stream */
+    adaqp_spmm_blocks blocks_overlap;       /* optional (n_blocks = 0: none): adaqp_plan_spmm_blocks of the two row ranges, */
+    adaqp_spmm_blocks blocks_dependent;     /* like panels and in their place (a range has panels or blocks, not both); the */
+                                            /* workspace's second part holds adaqp_spmm_blocks_workspace_bytes */
     const int32_t *recv_seg_order_dev;  /* backward only, optional: adaqp_plan_recv_segments of halo_idx */
     const int64_t *recv_seg_ptr_dev;
     int64_t n_recv_seg;

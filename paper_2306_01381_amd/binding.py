@@ -43,6 +43,14 @@ class SpmmPanels(ctypes.Structure):
     ]
 
 
+class SpmmBlocks(ctypes.Structure):
+    """Mirror of struct adaqp_spmm_blocks."""
+    _fields_ = [
+        ("n_blocks", _i32), ("n_pieces", _i32), ("n_steps", _i64), ("col_begin", _i32), ("piece_width", _i32),
+        ("rows_dev", _vp), ("step_ptr_dev", _vp), ("cols_dev", _vp), ("table_dev", _vp),
+    ]
+
+
 class LayerDesc(ctypes.Structure):
     """Mirror of struct adaqp_layer_desc."""
     _fields_ = [
@@ -58,6 +66,7 @@ class LayerDesc(ctypes.Structure):
         ("tile_off_overlap_dev", _vp), ("tile_off_dependent_dev", _vp),
         ("tile_chunk_overlap", _i32), ("tile_chunk_dependent", _i32),
         ("panels_overlap", SpmmPanels), ("panels_dependent", SpmmPanels),
+        ("blocks_overlap", SpmmBlocks), ("blocks_dependent", SpmmBlocks),
         ("recv_seg_order_dev", _vp), ("recv_seg_ptr_dev", _vp), ("n_recv_seg", _i64),
         ("n_send", _i64), ("seed", _u64),
         ("packed_dev", _vp), ("params_dev", _vp), ("alpha_sq_dev", _vp), ("beta_dev", _vp),
@@ -100,6 +109,14 @@ _SIGNATURES = {
                                               _vp, _vp, _vp, _vp]),
     "adaqp_spmm_panels_workspace_bytes": (ctypes.c_int, [_i32, _i32, _vp]),
     "adaqp_spmm_panels_pay": (_i32, [_i64, _i32]),
+    "adaqp_plan_spmm_blocks": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp]),
+    "adaqp_spmm_blocks_min_row": (_i32, [_i64]),
+    "adaqp_spmm_blocks_pay": (_i32, [_i64, _i64, _i64]),
+    "adaqp_spmm_blocks_table_floats": (_i64, [_i64]),
+    "adaqp_fill_spmm_blocks": (ctypes.c_int, [ctypes.POINTER(SpmmBlocks), _i64, _i64, _vp, _vp, _vp, _i64, _vp]),
+    "adaqp_spmm_blocks_workspace_bytes": (ctypes.c_int, [_i32, _i32, _i32, _vp]),
+    "adaqp_spmm_csr_blocks": (ctypes.c_int, [ctypes.POINTER(SpmmBlocks), _i64, _i64, _vp, _i64, _i64, _i32, _vp, _i64, _vp, _i64,
+                                             _vp]),
     "adaqp_spmm_csr_panels": (ctypes.c_int, [ctypes.POINTER(SpmmPanels), _i64, _i64, _vp, _i64, _i64, _i32, _vp,
                                              _i64, _vp, _i64, _vp]),
     "adaqp_assign_bits": (ctypes.c_int, [_i64, _vp, _vp, _i32, _i32, _i32, ctypes.c_double, _vp, _vp, _vp, _vp]),
@@ -425,6 +442,87 @@ def adaqp_spmm_csr_panels(panels: DevicePanels, row_begin: int, row_end: int, H:
     _check(lib().adaqp_spmm_csr_panels(ctypes.byref(panels.c), row_begin, row_end, hp, n_cols, ldh, dim, op, ldo,
                                        _dev(workspace, torch.uint8, "workspace"), workspace.numel(),
                                        _stream(stream)), "adaqp_spmm_csr_panels")
+
+
+SPMM_BLOCK_ROWS = 128
+SPMM_BLOCK_STEP = 32
+
+
+def adaqp_plan_spmm_blocks(rowptr_host: np.ndarray, col_host: np.ndarray, row_begin: int, row_end: int, n_cols: int, dim: int,
+                           min_row_len: int, tile_off: Optional[np.ndarray] = None,
+                           only_if_pays_for_ld: int = 0) -> Optional[dict]:
+    """Host-only.  None when no row of the range has min_row_len entries (or, with only_if_pays_for_ld = the pitch of H, when
+    adaqp_spmm_blocks_pay turns the sized plan down), else a dict of host arrays (rows, step_ptr, cols) and sizes.  tile_off
+    (the table of adaqp_plan_spmm_tiles for the same range) is changed in place: the rows taken are struck."""
+    rowptr = np.ascontiguousarray(rowptr_host, dtype=np.int64)
+    col = np.ascontiguousarray(col_host, dtype=np.int32)
+    if tile_off is not None:
+        if tile_off.dtype != np.int32 or not tile_off.flags.c_contiguous or \
+                tile_off.shape != (max(row_end - row_begin, 0), SPMM_TILES + 1):
+            raise ValueError("tile_off must be the C-contiguous int32 table of adaqp_plan_spmm_tiles for this range")
+    sizes = np.zeros(6, dtype=np.int64)
+    args = (rowptr.ctypes.data, col.ctypes.data, row_begin, row_end, n_cols, dim, min_row_len, sizes.ctypes.data)
+    _check(lib().adaqp_plan_spmm_blocks(*args, None, None, None, None), "adaqp_plan_spmm_blocks")
+    names = ("n_rows_taken", "n_blocks", "n_pieces", "n_steps", "col_begin", "piece_width")
+    plan = {k: int(v) for k, v in zip(names, sizes)}
+    if plan["n_rows_taken"] == 0:
+        return None
+    if only_if_pays_for_ld > 0 and not lib().adaqp_spmm_blocks_pay(plan["n_rows_taken"], n_cols, only_if_pays_for_ld):
+        return None
+    plan.update(rows=np.empty(plan["n_blocks"] * SPMM_BLOCK_ROWS, dtype=np.int32),
+                step_ptr=np.empty(plan["n_blocks"] * plan["n_pieces"] + 1, dtype=np.int32),
+                cols=np.empty((plan["n_steps"], SPMM_BLOCK_STEP), dtype=np.int32))
+    _check(lib().adaqp_plan_spmm_blocks(*args, None if tile_off is None else tile_off.ctypes.data, plan["rows"].ctypes.data,
+                                        plan["step_ptr"].ctypes.data, plan["cols"].ctypes.data), "adaqp_plan_spmm_blocks")
+    return plan
+
+
+def adaqp_spmm_blocks_min_row(n_cols: int) -> int:
+    """Host-only.  The row length from which a row is worth a place in a block."""
+    return int(lib().adaqp_spmm_blocks_min_row(n_cols))
+
+
+class DeviceBlocks:
+    """Device copies of a block plan, its table of coefficients and the struct the C calls take.  Keeps the tensors alive."""
+
+    def __init__(self, plan: Optional[dict], device="cuda"):
+        self.c = SpmmBlocks()
+        self.tensors = {}
+        if plan is None:
+            return
+        for k in ("rows", "step_ptr", "cols"):
+            self.tensors[k] = torch.from_numpy(plan[k]).to(device)
+        self.tensors["table"] = torch.empty(int(lib().adaqp_spmm_blocks_table_floats(plan["n_steps"])), dtype=torch.float32,
+                                            device=device)
+        t = self.tensors
+        self.c = SpmmBlocks(plan["n_blocks"], plan["n_pieces"], plan["n_steps"], plan["col_begin"], plan["piece_width"],
+                            t["rows"].data_ptr(), t["step_ptr"].data_ptr(), t["cols"].data_ptr(), t["table"].data_ptr())
+
+    def __bool__(self) -> bool:
+        return self.c.n_blocks > 0
+
+
+def adaqp_fill_spmm_blocks(blocks: DeviceBlocks, row_begin: int, row_end: int, rowptr: torch.Tensor, col: torch.Tensor,
+                           val: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
+    _check(lib().adaqp_fill_spmm_blocks(ctypes.byref(blocks.c), row_begin, row_end, _dev(rowptr, torch.int64, "rowptr"),
+                                        _dev(col, torch.int32, "col"), _dev(val, torch.float32, "val"), col.numel(),
+                                        _stream(stream)), "adaqp_fill_spmm_blocks")
+
+
+def adaqp_spmm_blocks_workspace_bytes(blocks: DeviceBlocks, dim: int) -> int:
+    out = ctypes.c_int64(0)
+    _check(lib().adaqp_spmm_blocks_workspace_bytes(blocks.c.n_blocks, blocks.c.n_pieces, dim, ctypes.byref(out)),
+           "adaqp_spmm_blocks_workspace_bytes")
+    return int(out.value)
+
+
+def adaqp_spmm_csr_blocks(blocks: DeviceBlocks, row_begin: int, row_end: int, H: torch.Tensor, dim: int, out: torch.Tensor,
+                          workspace: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
+    hp, n_cols, ldh = _matrix(H, "H")
+    op, _, ldo = _matrix(out, "out")
+    _check(lib().adaqp_spmm_csr_blocks(ctypes.byref(blocks.c), row_begin, row_end, hp, n_cols, ldh, dim, op, ldo,
+                                       _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(stream)),
+           "adaqp_spmm_csr_blocks")
 
 
 def adaqp_spmm_csr_tiled(rowptr: torch.Tensor, col: torch.Tensor, val: torch.Tensor, row_begin: int, row_end: int,

@@ -168,6 +168,10 @@ int check_desc(const adaqp_layer_desc *d)
         const adaqp_spmm_panels *p = part ? &d->panels_overlap : &d->panels_dependent;
         const int32_t *tile_off = part ? d->tile_off_overlap_dev : d->tile_off_dependent_dev;
         if (p->n_panels < 0 || p->n_per_tile < 0 || p->n_groups < 0 || p->n_panel_pieces < 0) return ADAQP_EINVAL;
+        const adaqp_spmm_blocks *b = part ? &d->blocks_overlap : &d->blocks_dependent;
+        if (b->n_blocks < 0 || b->n_pieces < 0 || b->n_steps < 0) return ADAQP_EINVAL;
+        if (b->n_blocks > 0 && (!tile_off || p->n_panels > 0 || !b->rows_dev || !b->step_ptr_dev || !b->cols_dev || !b->table_dev))
+            return ADAQP_EINVAL;
         if (p->n_panels == 0) continue;
         if (!tile_off) return ADAQP_EINVAL;                 // panels complement a tile table, never the merge path
         if (!p->panel_rows_dev || !p->pcol_dev || !p->palpha_dev || !p->piece_dev || !p->panel_piece_ptr_dev ||
@@ -225,10 +229,17 @@ int aggregate_rows(const adaqp_layer_desc *d, bool overlap_part, hipStream_t st)
     return aggregate_range(d, rb, re, nz, !overlap_part && fused_receive(d), ws, wsb, st);
 }
 
+bool has_blocks(const adaqp_layer_desc *d, bool overlap_part)
+{
+    const int32_t *tile_off = overlap_part ? d->tile_off_overlap_dev : d->tile_off_dependent_dev;
+    return tile_off && (overlap_part ? d->blocks_overlap.n_blocks : d->blocks_dependent.n_blocks) > 0;
+}
+
+// Panels or blocks: rows that a matrix-core kernel takes.
 bool has_panels(const adaqp_layer_desc *d, bool overlap_part)
 {
     const int32_t *tile_off = overlap_part ? d->tile_off_overlap_dev : d->tile_off_dependent_dev;
-    return tile_off && (overlap_part ? d->panels_overlap.n_panels : d->panels_dependent.n_panels) > 0;
+    return tile_off && ((overlap_part ? d->panels_overlap.n_panels : d->panels_dependent.n_panels) > 0 || has_blocks(d, overlap_part));
 }
 
 // The rows of a range that were struck from its tile table.  Own part of the workspace, disjoint output rows:
@@ -242,6 +253,9 @@ int aggregate_panels(const adaqp_layer_desc *d, bool overlap_part, hipStream_t s
     const int64_t wsb = overlap_part ? d->workspace_overlap_bytes : d->workspace_dependent_bytes;
     const int64_t skip = tiled_part_bytes(d, overlap_part);
     if (skip < 0 || !ws || wsb < skip) return ADAQP_ESIZE;
+    if (has_blocks(d, overlap_part))
+        return adaqp_spmm_csr_blocks(overlap_part ? &d->blocks_overlap : &d->blocks_dependent, rb, re, d->feat_dev,
+                                     d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo, ws + skip, wsb - skip, st);
     return adaqp_spmm_csr_panels(overlap_part ? &d->panels_overlap : &d->panels_dependent, rb, re, d->feat_dev,
                                  d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo, ws + skip, wsb - skip, st);
 }
@@ -397,6 +411,13 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
                 rc = adaqp_spmm_panels_workspace_bytes(panels->n_per_tile, d->dim, &need_panels);
                 if (rc != ADAQP_OK) return rc;
                 need += need_panels;                        // side by side: the two kernels may run together
+            }
+            const adaqp_spmm_blocks *blocks = part ? &d->blocks_overlap : &d->blocks_dependent;
+            if (blocks->n_blocks > 0) {
+                int64_t need_blocks = 0;
+                rc = adaqp_spmm_blocks_workspace_bytes(blocks->n_blocks, blocks->n_pieces, d->dim, &need_blocks);
+                if (rc != ADAQP_OK) return rc;
+                need += need_blocks;
             }
         }
         const int64_t have = part ? d->workspace_overlap_bytes : d->workspace_dependent_bytes;

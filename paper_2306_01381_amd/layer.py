@@ -147,9 +147,10 @@ class LayerStep:
         # tiled=None lets the library decide per row range (adaqp_spmm_tiled_pays: mean row length).
         self.tile_off_overlap = self.tile_off_dependent = None
         self.tile_chunk_overlap = self.tile_chunk_dependent = 0
-        # within a tiled range, rows with thousands of entries go into dense panels for the matrix cores.
-        # panels=None: where the library says the plan fills enough of the GPU (adaqp_spmm_panels_pay); True: always
+        # within a tiled range, rows that list a good part of the columns go to the matrix cores: panels=None in dense blocks,
+        # where the library says that pays; True: rows of panel_min_row entries in panels, always
         self.panels_overlap = self.panels_dependent = B.DevicePanels(None)
+        self.blocks_overlap = self.blocks_dependent = B.DeviceBlocks(None)
         # panel_min_row: one threshold, or one per row range (overlap, dependent)
         min_row_o, min_row_d = panel_min_row if isinstance(panel_min_row, tuple) else (panel_min_row, panel_min_row)
         ws_o = B.adaqp_spmm_workspace_bytes(oe - ob, self.overlap_nnz, cfg.dim)
@@ -158,34 +159,44 @@ class LayerStep:
             ws_o = max(ws_o, B.adaqp_spmm_workspace_bytes(de - ob, self.overlap_nnz + self.dependent_nnz, cfg.dim))
         if pad and tiled is not False:
             if oe > ob and (tiled or B.adaqp_spmm_tiled_pays(oe - ob, self.overlap_nnz)):
-                bounds, off = B.adaqp_plan_spmm_tiles(p.rowptr, p.col, ob, oe, p.feat.shape[0])
-                if panels is not False:
-                    self.panels_overlap = B.DevicePanels(B.adaqp_plan_spmm_panels(
-                        p.rowptr, p.col, p.val, ob, oe, p.feat.shape[0], bounds, off, min_row_o, panel_piece_cols,
-                        only_if_pays_for_dim=0 if panels else cfg.dim), dev)
-                self.tile_off_overlap = torch.from_numpy(off).to(dev)
-                self.tile_chunk_overlap = B.adaqp_spmm_tiled_chunk_cols(bounds, cfg.dim)
-                # partial sums of the tiled kernel, then the piece sums of the panel kernel (they may run together)
-                ws_o = max(ws_o, B.adaqp_spmm_tiled_workspace_bytes(oe - ob, cfg.dim)
-                           + B.adaqp_spmm_panels_workspace_bytes(self.panels_overlap.n_per_tile, cfg.dim))
+                self.tile_off_overlap, self.tile_chunk_overlap, self.panels_overlap, self.blocks_overlap, need = \
+                    self._plan_long_rows(ob, oe, panels, min_row_o, panel_piece_cols)
+                ws_o = max(ws_o, need)
             if de > db and (tiled or B.adaqp_spmm_tiled_pays(de - db, self.dependent_nnz)):
-                bounds, off = B.adaqp_plan_spmm_tiles(p.rowptr, p.col, db, de, p.feat.shape[0])
-                if panels is not False:
-                    self.panels_dependent = B.DevicePanels(B.adaqp_plan_spmm_panels(
-                        p.rowptr, p.col, p.val, db, de, p.feat.shape[0], bounds, off, min_row_d, panel_piece_cols,
-                        only_if_pays_for_dim=0 if panels else cfg.dim), dev)
-                self.tile_off_dependent = torch.from_numpy(off).to(dev)
-                self.tile_chunk_dependent = B.adaqp_spmm_tiled_chunk_cols(bounds, cfg.dim)
-                ws_d = max(ws_d, B.adaqp_spmm_tiled_workspace_bytes(de - db, cfg.dim)
-                           + B.adaqp_spmm_panels_workspace_bytes(self.panels_dependent.n_per_tile, cfg.dim))
+                self.tile_off_dependent, self.tile_chunk_dependent, self.panels_dependent, self.blocks_dependent, need = \
+                    self._plan_long_rows(db, de, panels, min_row_d, panel_piece_cols)
+                ws_d = max(ws_d, need)
         self.ws_overlap = torch.empty(max(ws_o, 256), dtype=torch.uint8, device=dev)
         self.ws_dependent = torch.empty(max(ws_d, 256), dtype=torch.uint8, device=dev)
         # streams=(msg, agg): take over an existing pair.  HIP deals streams to a few hardware queues in turn, so a
         # process that keeps creating streams can end up with a step's two streams on one queue (no overlap)
         self.stream_msg, self.stream_agg = streams if streams is not None else (torch.cuda.Stream(device=dev),
                                                                                   torch.cuda.Stream(device=dev))
+        for st in (self.stream_msg, self.stream_agg):       # the tables of the blocks are written by a kernel
+            if self.blocks_overlap or self.blocks_dependent:
+                st.wait_stream(torch.cuda.current_stream(dev))
         self.event_fork = HipEvent()
         self.event_join = HipEvent()
+
+    def _plan_long_rows(self, begin, end, panels, min_row, piece_cols):
+        """Tile table, chunk width, panels or blocks of a row range, and the bytes of workspace these take: partial sums of the
+        tiled kernel, then the piece sums of the matrix-core kernel (they may run together)."""
+        p, dim, n_cols = self.p, self.dim, self.p.feat.shape[0]
+        bounds, off = B.adaqp_plan_spmm_tiles(p.rowptr, p.col, begin, end, n_cols)
+        with_panels, with_blocks = B.DevicePanels(None), B.DeviceBlocks(None)
+        if panels:
+            with_panels = B.DevicePanels(B.adaqp_plan_spmm_panels(p.rowptr, p.col, p.val, begin, end, n_cols, bounds, off, min_row,
+                                                                  piece_cols), self.device)
+        elif panels is None:
+            with_blocks = B.DeviceBlocks(B.adaqp_plan_spmm_blocks(
+                p.rowptr, p.col, begin, end, n_cols, dim, B.adaqp_spmm_blocks_min_row(int(bounds[-1])), off,
+                only_if_pays_for_ld=self.feat.stride(0)), self.device)
+            if with_blocks:
+                B.adaqp_fill_spmm_blocks(with_blocks, begin, end, self.rowptr, self.col, self.val)
+        need = B.adaqp_spmm_tiled_workspace_bytes(end - begin, dim) \
+            + B.adaqp_spmm_panels_workspace_bytes(with_panels.n_per_tile, dim) \
+            + B.adaqp_spmm_blocks_workspace_bytes(with_blocks, dim)
+        return torch.from_numpy(off).to(self.device), B.adaqp_spmm_tiled_chunk_cols(bounds, dim), with_panels, with_blocks, need
 
     def set_fused_receive(self, on: bool) -> None:
         """Forward only.  On: received rows are not de-quantised into feat; the dependent aggregation reads
@@ -218,9 +229,9 @@ class LayerStep:
         d.tile_off_dependent_dev = None if (self.tile_off_dependent is None or self.fused_receive) \
             else self.tile_off_dependent.data_ptr()
         if d.tile_off_overlap_dev:
-            d.panels_overlap = self.panels_overlap.c
+            d.panels_overlap, d.blocks_overlap = self.panels_overlap.c, self.blocks_overlap.c
         if d.tile_off_dependent_dev:
-            d.panels_dependent = self.panels_dependent.c
+            d.panels_dependent, d.blocks_dependent = self.panels_dependent.c, self.blocks_dependent.c
         if self.backward and self.backward_receive and pl.seg_order is not None:
             d.recv_seg_order_dev, d.recv_seg_ptr_dev = pl.seg_order.data_ptr(), pl.seg_ptr.data_ptr()
             d.n_recv_seg = pl.seg_ptr.shape[0] - 1

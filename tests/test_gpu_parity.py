@@ -925,6 +925,77 @@ def test_spmm_panels_rejects_what_it_cannot_do():
 # the layer step
 # ------------------------------------------------------------------------------------------------------
 
+@pytest.mark.parametrize("dim,ld", [(128, 128), (602, 608), (64, 64), (7, 32), (96, 96), (130, 160), (256, 288), (1025, 1056)])
+@pytest.mark.parametrize("n_rows,n_heavy,n_cols", [(300, 140, 900), (40, 3, 33), (150, 128, 5_000)])
+def test_spmm_blocks(oracle, dim, ld, n_rows, n_heavy, n_cols):
+    """Blocks of 128 rows, full and partly filled, one to 4 column tiles in the last chunk, steps that the columns do not fill,
+    with the tiled kernel for the other rows; then the blocks alone, which write the rows they list and nothing else."""
+    _say(f"blocks spmm dim={dim} ld={ld} rows={n_rows} heavy={n_heavy} cols={n_cols}")
+    rng = np.random.default_rng(4000 + dim)
+    degs = rng.integers(0, 20, size=n_rows)
+    heavy = rng.choice(n_rows, size=n_heavy, replace=False)
+    degs[heavy] = rng.integers(25, n_cols, size=n_heavy)
+    degs[heavy[0]], degs[heavy[1]] = n_cols, 25                        # every column; exactly the threshold
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, degs)
+    H = np.full((n_cols, ld), np.nan, dtype=np.float32)                # NaN in the row padding
+    H[:, :dim] = rng.standard_normal((n_cols, dim), dtype=np.float32)
+    want, mag = oracle.spmm_csr(rowptr, col, val, 0, n_rows, np.ascontiguousarray(H[:, :dim]), dim)
+    rp, cl, vl, Hd = (torch.from_numpy(x).to(DEV) for x in (rowptr, col, val, H))
+    for rb, re in ((0, n_rows), (n_rows // 3, n_rows - 1)):
+        _, off = B.adaqp_plan_spmm_tiles(rowptr, col, rb, re, n_cols)
+        blocks = B.DeviceBlocks(B.adaqp_plan_spmm_blocks(rowptr, col, rb, re, n_cols, dim, 25, off), DEV)
+        taken = np.nonzero(degs[rb:re] >= 25)[0] + rb
+        assert sorted(r for r in blocks.tensors["rows"].tolist() if r >= 0) == taken.tolist()
+        B.adaqp_fill_spmm_blocks(blocks, rb, re, rp, cl, vl)
+        ws = torch.empty(B.adaqp_spmm_blocks_workspace_bytes(blocks, dim), dtype=torch.uint8, device=DEV)
+        out = torch.full((n_rows, ld), 7.0, dtype=torch.float32, device=DEV)
+        B.adaqp_spmm_csr_blocks(blocks, rb, re, Hd, dim, out, ws)
+        torch.cuda.synchronize()
+        rest = np.setdiff1d(np.arange(n_rows), taken)
+        assert np.all(out.cpu().numpy()[rest] == 7.0)
+        first = out.clone()
+        ws_t = torch.empty(B.adaqp_spmm_tiled_workspace_bytes(re - rb, dim), dtype=torch.uint8, device=DEV)
+        B.adaqp_spmm_csr_tiled(rp, cl, vl, rb, re, Hd, dim, out, torch.from_numpy(off).to(DEV), ws_t)
+        B.adaqp_spmm_csr_blocks(blocks, rb, re, Hd, dim, out, ws)      # the same bits again
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert np.array_equal(got[taken].view(np.uint32), first.cpu().numpy()[taken].view(np.uint32))
+        err = np.abs(got[rb:re, :dim].astype(np.float64) - want[rb:re])
+        worst = float((err / (SPMM_RTOL * mag[rb:re] + 1e-30)).max())
+        assert worst <= 1.0, f"worst error {worst:.3f} x tolerance"
+        assert np.all(got[rb:re, dim:_padded_cols(dim, ld)] == 0.0) and np.all(got[:rb] == 7.0) and np.all(got[re:] == 7.0)
+
+
+def test_spmm_blocks_precision():
+    """fp32 operands as three bf16: against 64 bits no worse than a running fp32 sum of as many terms as one set of sums takes
+    (a piece's columns), also where the products differ by many orders of magnitude."""
+    _say("blocks precision")
+    rng = np.random.default_rng(8)
+    n_rows, n_cols, dim = 130, 4_000, 64
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, np.full(n_rows, 3_000))
+    for scale in (np.ones(n_cols), 10.0 ** rng.uniform(-6, 6, n_cols)):
+        for H in (np.abs(rng.standard_normal((n_cols, dim))), rng.standard_normal((n_cols, dim))):
+            H = (H * scale[:, None]).astype(np.float32)
+            plan = B.adaqp_plan_spmm_blocks(rowptr, col, 0, n_rows, n_cols, dim, 1)
+            blocks = B.DeviceBlocks(plan, DEV)
+            rp, cl, vl, Hd = (torch.from_numpy(x).to(DEV) for x in (rowptr, col, np.abs(val), H))
+            B.adaqp_fill_spmm_blocks(blocks, 0, n_rows, rp, cl, vl)
+            ws = torch.empty(B.adaqp_spmm_blocks_workspace_bytes(blocks, dim), dtype=torch.uint8, device=DEV)
+            out = torch.zeros((n_rows, dim), device=DEV)
+            B.adaqp_spmm_csr_blocks(blocks, 0, n_rows, Hd, dim, out, ws)
+            A = torch.zeros((n_rows, n_cols), dtype=torch.float64, device=DEV)
+            A[torch.repeat_interleave(torch.arange(n_rows, device=DEV), rp.diff()), cl.long()] = vl.double()
+            want, mag = A @ Hd.double(), A @ Hd.double().abs()
+            # chains: the instructions of a piece (two per step) and the pieces, of 16 columns each at most; the parts left out
+            # are 3 * 2^-24 of a product
+            steps = plan["n_steps"] // (plan["n_blocks"] * plan["n_pieces"]) + 1
+            bound = (2 * steps + plan["n_pieces"] + 8 + 3) * 2.0 ** -24
+            error = float(((out.double() - want).abs() / mag).max())
+            assert error <= bound, (error, bound)
+            rel = float((out.double() - want).norm() / want.norm())
+            assert rel <= 1.5e-7, rel                                   # a rounding per term would be sqrt(3000) of them
+
+
 def _oracle_layer(oracle, p, seed):
     """Composes the oracle's pieces in the order of Sec. 3.1: quantise, exchange (identity), de-quantise,
     aggregate.  Returns (packed, params, feat_after, out64, mag64)."""

@@ -380,6 +380,48 @@ def test_plan_spmm_panels_random_graphs():
             assert np.array_equal(dense[k], want), (case, k, r)
 
 
+@pytest.mark.parametrize("n_rows,n_cols,min_len", [(1, 1, 1), (40, 33, 5), (130, 900, 60), (300, 2_000, 40)])
+def test_plan_spmm_blocks(n_rows, n_cols, min_len):
+    """A block lists exactly the distinct columns of its rows, each in its interval, ascending, steps filled with the last one."""
+    rng = np.random.default_rng(n_rows)
+    degs = np.minimum(rng.integers(0, n_cols + 1, size=n_rows) // rng.integers(1, 20, size=n_rows), n_cols)
+    degs[0] = n_cols
+    rowptr = np.concatenate([[0], np.cumsum(degs)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n_cols, size=d, replace=False)) for d in degs]).astype(np.int32)
+    for rb, re in ((0, n_rows), (n_rows // 2, n_rows)):
+        _, off = B.adaqp_plan_spmm_tiles(rowptr, col, rb, re, n_cols)
+        before = off.copy()
+        plan = B.adaqp_plan_spmm_blocks(rowptr, col, rb, re, n_cols, 300, min_len, off)
+        rows = [r for r in range(rb, re) if degs[r] >= min_len]
+        if not rows:
+            assert plan is None and np.array_equal(off, before)
+            continue
+        rows.sort(key=lambda r: (-degs[r], r))
+        assert plan["rows"][:len(rows)].tolist() == rows and np.all(plan["rows"][len(rows):] == -1)
+        assert plan["rows"].size == plan["n_blocks"] * B.SPMM_BLOCK_ROWS == -(-len(rows) // 128) * 128
+        assert plan["n_pieces"] % 8 == 0 and plan["step_ptr"][-1] == plan["n_steps"] and np.all(np.diff(plan["step_ptr"]) >= 0)
+        for b in range(plan["n_blocks"]):
+            mine = [r for r in plan["rows"][b * 128: b * 128 + 128] if r >= 0]
+            want = np.unique(np.concatenate([col[rowptr[r]: rowptr[r + 1]] for r in mine]))
+            got = []
+            for p in range(plan["n_pieces"]):
+                s0, s1 = plan["step_ptr"][b * plan["n_pieces"] + p], plan["step_ptr"][b * plan["n_pieces"] + p + 1]
+                c = plan["cols"][s0:s1].reshape(-1)
+                lo = plan["col_begin"] + p * plan["piece_width"]
+                assert np.all((c >= lo) & (c < lo + plan["piece_width"])) and np.all(np.diff(c) >= 0)
+                distinct = np.unique(c)
+                assert s1 - s0 == -(-distinct.size // 32) and np.array_equal(c[:distinct.size], distinct)
+                got.append(distinct)
+            assert np.array_equal(np.concatenate(got), want)
+        taken = np.zeros(re - rb, dtype=bool)
+        taken[np.array(rows) - rb] = True
+        assert np.all(off[taken] == -1) and np.array_equal(off[~taken], before[~taken])
+    with pytest.raises(B.AdaqpError):
+        B.adaqp_plan_spmm_blocks(rowptr, col, 0, n_rows, n_cols, 300, 0)                                     # min_row_len < 1
+    with pytest.raises(B.AdaqpError):
+        B.adaqp_plan_spmm_blocks(np.array([0, 2], np.int64), np.array([5, 5], np.int32), 0, 1, 8, 300, 1)    # repeated column
+
+
 def test_rule_that_decides_whether_a_panel_plan_pays():
     # one wave per (piece, 128-column chunk); fewer than ADAQP_SPMM_PANEL_MIN_WAVES of them do not fill the GPU
     assert not B.adaqp_spmm_panels_pay(0, 602) and not B.adaqp_spmm_panels_pay(100, 0)
