@@ -304,6 +304,49 @@ int adaqp_spmm_csr_tiled(const int64_t *rowptr_dev, const int32_t *col_dev, cons
                          void *workspace_dev, int64_t workspace_bytes, void *stream);
 
 /* ---------------------------------------------------------------------------------------------------- */
+/* The same aggregation from a copy of the entries in the order of the tiles: all entries of the first group of tiles row by
+ * row, then those of the next.  A run of one row's entries in one group is a segment.  The kernel of adaqp_spmm_csr's
+ * sliced aggregation walks the segments like rows (every XCD a share of the feature columns, one group of tiles after the other,
+ * whose lines stay in its L2), and the segments of a row are added up in group order.  The copy costs 8 bytes per entry. */
+#define ADAQP_SPMM_SEGMENTS 8           /* of a row, at most */
+
+/* Device side of a segment plan for one row range.  The struct lives in host memory and is read during the call only. */
+typedef struct adaqp_spmm_segments {
+    int64_t n_seg;                      /* 0: no segments, the struct is ignored */
+    int64_t n_entries;                  /* in all segments */
+    int64_t n_rows;                     /* of the range */
+    const int64_t *ptr_dev;             /* [n_seg + 1] first entry of each segment in col_dev and val_dev */
+    const int64_t *src_dev;             /* [n_seg] its first entry in the CSR's col and val; adaqp_fill_spmm_segments reads it */
+    const int32_t *of_row_dev;          /* [n_rows][ADAQP_SPMM_SEGMENTS] segments of a row in group order, -1 = none; a row that
+                                           is not of this plan (struck from the tile table): -2 first */
+    int32_t *col_dev;                   /* [n_entries] adaqp_fill_spmm_segments writes both */
+    float   *val_dev;
+} adaqp_spmm_segments;
+
+/* Host only.  Segments of rows [row_begin, row_end) from adaqp_plan_spmm_tiles' outputs for the range (rows struck from the
+ * table are left out): neighbouring tiles are joined while a group's columns stay within what an L2 holds of one line each.
+ * Two calls: with the output arrays NULL to learn sizes_inout[2] = { n_seg, n_entries }, then with those and arrays of n_seg +
+ * 1, n_seg and (row_end - row_begin) * ADAQP_SPMM_SEGMENTS.  Errors: EINVAL (table that disagrees with rowptr, sizes of another
+ * plan), ESIZE. */
+int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_begin, int64_t row_end, const int32_t *col_bounds_host,
+                             const int32_t *tile_off_host, int64_t *sizes_inout, int64_t *ptr_out, int64_t *src_out,
+                             int32_t *of_row_out);
+
+/* Writes segments_host->col_dev and val_dev from the CSR the plan was made for, once per graph (or whenever val changes). */
+int adaqp_fill_spmm_segments(const adaqp_spmm_segments *segments_host, const int32_t *col_dev, const float *val_dev, int64_t nnz,
+                             void *stream);
+
+/* Bytes of workspace adaqp_spmm_csr_segments needs. */
+int adaqp_spmm_segments_workspace_bytes(int64_t n_seg, int64_t n_entries, int32_t dim, int64_t *bytes_out);
+
+/* out[r, 0:dim] = sum_j val[j] * H[col[j], 0:dim] for the rows of the plan, out_dev being the row of the range's first row;
+ * rows struck from the table are not written.  Layout, alignment and padding as adaqp_spmm_csr_tiled; out-of-range columns are
+ * skipped.  The order of additions is fixed by the plan and the launch geometry.  Errors: EINVAL, ESIZE (workspace; H of 2^32 -
+ * 2^16 bytes and more), EHIP. */
+int adaqp_spmm_csr_segments(const adaqp_spmm_segments *segments_host, const float *H_dev, int64_t n_cols, int64_t ldh, int32_t dim,
+                            float *out_dev, int64_t ldo, void *workspace_dev, int64_t workspace_bytes, void *stream);
+
+/* ---------------------------------------------------------------------------------------------------- */
 /* Dense panels for the longest rows of such a graph.  In a power-law graph (the degree shape of the paper's
  * densest dataset, Sec. 5) a few thousand rows hold most of the entries, and any 32 of them share most of their
  * columns.  The host gathers such rows into panels of ADAQP_SPMM_PANEL_ROWS rows: per panel the sorted list of
@@ -510,6 +553,9 @@ typedef struct adaqp_layer_desc {
     adaqp_spmm_blocks blocks_overlap;       /* optional (n_blocks = 0: none): adaqp_plan_spmm_blocks of the two row ranges, */
     adaqp_spmm_blocks blocks_dependent;     /* like panels and in their place (a range has panels or blocks, not both); the */
                                             /* workspace's second part holds adaqp_spmm_blocks_workspace_bytes */
+    adaqp_spmm_segments segments_overlap;   /* optional (n_seg = 0: none), only with that range's tile table: the range's */
+    adaqp_spmm_segments segments_dependent; /* entries in tile order.  It is then aggregated by adaqp_spmm_csr_segments instead of */
+                                            /* _tiled, and the workspace's first part holds that call's bytes */
     const int32_t *recv_seg_order_dev;  /* backward only, optional: adaqp_plan_recv_segments of halo_idx */
     const int64_t *recv_seg_ptr_dev;
     int64_t n_recv_seg;

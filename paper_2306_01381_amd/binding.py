@@ -51,6 +51,14 @@ class SpmmBlocks(ctypes.Structure):
     ]
 
 
+class SpmmSegments(ctypes.Structure):
+    """Mirror of struct adaqp_spmm_segments."""
+    _fields_ = [
+        ("n_seg", _i64), ("n_entries", _i64), ("n_rows", _i64), ("ptr_dev", _vp), ("src_dev", _vp), ("of_row_dev", _vp),
+        ("col_dev", _vp), ("val_dev", _vp),
+    ]
+
+
 class LayerDesc(ctypes.Structure):
     """Mirror of struct adaqp_layer_desc."""
     _fields_ = [
@@ -67,6 +75,7 @@ class LayerDesc(ctypes.Structure):
         ("tile_chunk_overlap", _i32), ("tile_chunk_dependent", _i32),
         ("panels_overlap", SpmmPanels), ("panels_dependent", SpmmPanels),
         ("blocks_overlap", SpmmBlocks), ("blocks_dependent", SpmmBlocks),
+        ("segments_overlap", SpmmSegments), ("segments_dependent", SpmmSegments),
         ("recv_seg_order_dev", _vp), ("recv_seg_ptr_dev", _vp), ("n_recv_seg", _i64),
         ("n_send", _i64), ("seed", _u64),
         ("packed_dev", _vp), ("params_dev", _vp), ("alpha_sq_dev", _vp), ("beta_dev", _vp),
@@ -109,6 +118,10 @@ _SIGNATURES = {
                                               _vp, _vp, _vp, _vp]),
     "adaqp_spmm_panels_workspace_bytes": (ctypes.c_int, [_i32, _i32, _vp]),
     "adaqp_spmm_panels_pay": (_i32, [_i64, _i32]),
+    "adaqp_plan_spmm_segments": (ctypes.c_int, [_vp, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp]),
+    "adaqp_fill_spmm_segments": (ctypes.c_int, [ctypes.POINTER(SpmmSegments), _vp, _vp, _i64, _vp]),
+    "adaqp_spmm_segments_workspace_bytes": (ctypes.c_int, [_i64, _i64, _i32, _vp]),
+    "adaqp_spmm_csr_segments": (ctypes.c_int, [ctypes.POINTER(SpmmSegments), _vp, _i64, _i64, _i32, _vp, _i64, _vp, _i64, _vp]),
     "adaqp_plan_spmm_blocks": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp]),
     "adaqp_spmm_blocks_min_row": (_i32, [_i64]),
     "adaqp_spmm_blocks_pay": (_i32, [_i64, _i64, _i64]),
@@ -442,6 +455,77 @@ def adaqp_spmm_csr_panels(panels: DevicePanels, row_begin: int, row_end: int, H:
     _check(lib().adaqp_spmm_csr_panels(ctypes.byref(panels.c), row_begin, row_end, hp, n_cols, ldh, dim, op, ldo,
                                        _dev(workspace, torch.uint8, "workspace"), workspace.numel(),
                                        _stream(stream)), "adaqp_spmm_csr_panels")
+
+
+SPMM_SEGMENTS = 8
+SPMM_SEGMENTS_MOST_BYTES = 0xFFFF0000       # of H
+
+
+def adaqp_plan_spmm_segments(rowptr_host: np.ndarray, row_begin: int, row_end: int, col_bounds_host: np.ndarray,
+                             tile_off: np.ndarray) -> Optional[dict]:
+    """Host-only.  None when the table leaves no entries, else a dict of host arrays (ptr, src, of_row) and sizes."""
+    rowptr = np.ascontiguousarray(rowptr_host, dtype=np.int64)
+    bounds = np.ascontiguousarray(col_bounds_host, dtype=np.int32)
+    off = np.ascontiguousarray(tile_off, dtype=np.int32)
+    n_rows = max(row_end - row_begin, 0)
+    if bounds.shape[0] != SPMM_TILES + 1 or off.shape != (n_rows, SPMM_TILES + 1):
+        raise ValueError("col_bounds and tile_off must be adaqp_plan_spmm_tiles' outputs for this range")
+    sizes = np.zeros(2, dtype=np.int64)
+    args = (rowptr.ctypes.data, row_begin, row_end, bounds.ctypes.data, off.ctypes.data, sizes.ctypes.data)
+    _check(lib().adaqp_plan_spmm_segments(*args, None, None, None), "adaqp_plan_spmm_segments")
+    n_seg = int(sizes[0])
+    if n_seg == 0:
+        return None
+    plan = {"n_seg": n_seg, "n_entries": int(sizes[1]), "n_rows": n_rows, "ptr": np.empty(n_seg + 1, dtype=np.int64),
+            "src": np.empty(n_seg, dtype=np.int64), "of_row": np.empty((n_rows, SPMM_SEGMENTS), dtype=np.int32)}
+    _check(lib().adaqp_plan_spmm_segments(*args, plan["ptr"].ctypes.data, plan["src"].ctypes.data, plan["of_row"].ctypes.data),
+           "adaqp_plan_spmm_segments")
+    return plan
+
+
+class DeviceSegments:
+    """Device copies of a segment plan, its copy of the entries and the struct the C calls take.  Keeps the tensors alive."""
+
+    def __init__(self, plan: Optional[dict], device="cuda"):
+        self.c = SpmmSegments()
+        self.tensors = {}
+        if plan is None:
+            return
+        for k in ("ptr", "src", "of_row"):
+            self.tensors[k] = torch.from_numpy(plan[k]).to(device)
+        self.tensors["col"] = torch.empty(plan["n_entries"], dtype=torch.int32, device=device)
+        self.tensors["val"] = torch.empty(plan["n_entries"], dtype=torch.float32, device=device)
+        t = self.tensors
+        self.c = SpmmSegments(plan["n_seg"], plan["n_entries"], plan["n_rows"], t["ptr"].data_ptr(), t["src"].data_ptr(),
+                              t["of_row"].data_ptr(), t["col"].data_ptr(), t["val"].data_ptr())
+
+    def __bool__(self) -> bool:
+        return self.c.n_seg > 0
+
+
+def adaqp_fill_spmm_segments(segments: DeviceSegments, col: torch.Tensor, val: torch.Tensor,
+                             stream: Optional[torch.cuda.Stream] = None) -> None:
+    _check(lib().adaqp_fill_spmm_segments(ctypes.byref(segments.c), _dev(col, torch.int32, "col"),
+                                          _dev(val, torch.float32, "val"), col.numel(), _stream(stream)),
+           "adaqp_fill_spmm_segments")
+
+
+def adaqp_spmm_segments_workspace_bytes(segments: DeviceSegments, dim: int) -> int:
+    out = ctypes.c_int64(0)
+    _check(lib().adaqp_spmm_segments_workspace_bytes(segments.c.n_seg, segments.c.n_entries, dim, ctypes.byref(out)),
+           "adaqp_spmm_segments_workspace_bytes")
+    return int(out.value)
+
+
+def adaqp_spmm_csr_segments(segments: DeviceSegments, row_begin: int, H: torch.Tensor, dim: int, out: torch.Tensor,
+                            workspace: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
+    """out: the whole matrix; row_begin: the first row of the range the plan was made for."""
+    hp, n_cols, ldh = _matrix(H, "H")
+    _, _, ldo = _matrix(out, "out")
+    op, _, _ = _matrix(out[row_begin:], "out")
+    _check(lib().adaqp_spmm_csr_segments(ctypes.byref(segments.c), hp, n_cols, ldh, dim, op, ldo,
+                                         _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(stream)),
+           "adaqp_spmm_csr_segments")
 
 
 SPMM_BLOCK_ROWS = 128

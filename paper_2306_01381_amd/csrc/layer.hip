@@ -168,6 +168,9 @@ int check_desc(const adaqp_layer_desc *d)
         const adaqp_spmm_panels *p = part ? &d->panels_overlap : &d->panels_dependent;
         const int32_t *tile_off = part ? d->tile_off_overlap_dev : d->tile_off_dependent_dev;
         if (p->n_panels < 0 || p->n_per_tile < 0 || p->n_groups < 0 || p->n_panel_pieces < 0) return ADAQP_EINVAL;
+        const adaqp_spmm_segments *s = part ? &d->segments_overlap : &d->segments_dependent;
+        if (s->n_seg < 0 || s->n_entries < 0 || s->n_rows < 0) return ADAQP_EINVAL;
+        if (s->n_seg > 0 && (!tile_off || !s->ptr_dev || !s->of_row_dev || !s->col_dev || !s->val_dev)) return ADAQP_EINVAL;
         const adaqp_spmm_blocks *b = part ? &d->blocks_overlap : &d->blocks_dependent;
         if (b->n_blocks < 0 || b->n_pieces < 0 || b->n_steps < 0) return ADAQP_EINVAL;
         if (b->n_blocks > 0 && (!tile_off || p->n_panels > 0 || !b->rows_dev || !b->step_ptr_dev || !b->cols_dev || !b->table_dev))
@@ -193,14 +196,16 @@ bool fused_receive(const adaqp_layer_desc *d)
            d->packed_bytes >= 4;
 }
 
-// Workspace of a row range: the tiled kernel's partial sums first, then (if the range has panels) the panel
-// kernel's piece sums, so that the two kernels can run at the same time.
+// Workspace of a row range: the partial sums of the tiled kernel or of the segments first, then (if the range has panels or blocks)
+// the matrix-core kernel's piece sums, so that the two kernels can run at the same time.
 int64_t tiled_part_bytes(const adaqp_layer_desc *d, bool overlap_part)
 {
     const int64_t rows = overlap_part ? d->overlap_end - d->overlap_begin : d->dependent_end - d->dependent_begin;
+    const adaqp_spmm_segments *seg = overlap_part ? &d->segments_overlap : &d->segments_dependent;
     int64_t bytes = 0;
-    if (adaqp_spmm_tiled_workspace_bytes(rows, d->dim, &bytes) != ADAQP_OK) return -1;
-    return bytes;
+    const int rc = seg->n_seg > 0 ? adaqp_spmm_segments_workspace_bytes(seg->n_seg, seg->n_entries, d->dim, &bytes)
+                                  : adaqp_spmm_tiled_workspace_bytes(rows, d->dim, &bytes);
+    return rc == ADAQP_OK ? bytes : -1;
 }
 
 // Rows [rb, re) along the merge path; fused: received rows are read from the receive buffer.
@@ -222,6 +227,11 @@ int aggregate_rows(const adaqp_layer_desc *d, bool overlap_part, hipStream_t st)
     void *ws = overlap_part ? d->workspace_overlap_dev : d->workspace_dependent_dev;
     const int64_t wsb = overlap_part ? d->workspace_overlap_bytes : d->workspace_dependent_bytes;
     const int32_t *tile_off = overlap_part ? d->tile_off_overlap_dev : d->tile_off_dependent_dev;
+    const adaqp_spmm_segments *seg = overlap_part ? &d->segments_overlap : &d->segments_dependent;
+    if (tile_off && seg->n_seg > 0)
+        return re - rb == seg->n_rows ? adaqp_spmm_csr_segments(seg, d->feat_dev, d->n_feat_rows, d->ld, d->dim,
+                                                                d->out_dev + rb * d->ldo, d->ldo, ws, wsb, st)
+                                      : ADAQP_EINVAL;
     if (tile_off)
         return adaqp_spmm_csr_tiled(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, d->feat_dev,
                                     d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo, tile_off,
@@ -403,8 +413,8 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
         rc = adaqp_spmm_workspace_bytes(rows, nz, d->dim, &need);
         if (rc != ADAQP_OK) return rc;
         if (part ? d->tile_off_overlap_dev != nullptr : d->tile_off_dependent_dev != nullptr) {
-            rc = adaqp_spmm_tiled_workspace_bytes(rows, d->dim, &need);         // that range takes the tiled kernel
-            if (rc != ADAQP_OK) return rc;
+            need = tiled_part_bytes(d, part != 0);          // that range takes the tiled kernel, or its segments
+            if (need < 0) return ADAQP_ESIZE;
             const adaqp_spmm_panels *panels = part ? &d->panels_overlap : &d->panels_dependent;
             if (panels->n_panels > 0) {
                 int64_t need_panels = 0;

@@ -20,6 +20,7 @@
 //
 // The kernel is a gather: per entry it reads 8 bytes of (col, alpha) and 4*dim bytes of H.  It is bound by
 // how fast H rows come out of L2 / Infinity Cache / HBM, not by arithmetic, so there is no MFMA use.
+#include <algorithm>
 #include <mutex>
 
 #include "spmm_common.hpp"
@@ -544,6 +545,207 @@ int adaqp::spmm_rows(const int64_t *rowptr_dev, const int32_t *col_dev, const fl
         else err = launch_merge_nv<1>(a, nv, grid, st);
         ADAQP_HIP_TRY(err);
     }
+    return ADAQP_OK;
+}
+
+// ---- segments: the sliced kernel over the entries in tile order ----------------------------------------------------------
+
+namespace {
+
+constexpr int kSegments = ADAQP_SPMM_SEGMENTS;
+static_assert(kSegments == ADAQP_SPMM_TILES, "a row has a segment per tile at most");
+
+// Workgroups per slice.  The fewer entries are under way at a time, the fewer groups of tiles an L2 has to hold, but a share is a
+// search and an empty ring: shares of about 1 100 entries (2.5 M entries, 602 columns: 256 workgroups 0.44 ms, 512 0.41, 1 024 0.42, 2 048
+// 0.54; 3.5 M: 0.70, 0.57, 0.58, 0.66), no more than 1 024 workgroups (15 M entries, 256 columns: 512 0.78, 1 024 0.75, 2 048 0.79).
+int64_t segment_blocks(int64_t n_seg, int64_t n_entries)
+{
+    const int64_t wanted = std::min<int64_t>(std::max<int64_t>(n_entries / 4500, 256), 1024);
+    return std::max<int64_t>(std::min(wanted, (n_entries + 8 * n_seg) / 1024), 1);
+}
+
+struct SegmentGeometry { int64_t n_items, wdim, carry_row_off, carry_off, bytes; };
+
+SegmentGeometry segment_geometry(int64_t n_seg, int64_t n_entries, int32_t dim)
+{
+    SegmentGeometry g;
+    g.wdim = ((int64_t)dim + 31) / 32 * 32;
+    g.n_items = segment_blocks(n_seg, n_entries) * kWavesPerBlock;
+    g.carry_row_off = (n_seg * g.wdim * 4 + 255) / 256 * 256;
+    g.carry_off = g.carry_row_off + (g.n_items * 4 + 255) / 256 * 256;
+    g.bytes = g.carry_off + (g.n_items * g.wdim * 4 + 255) / 256 * 256;
+    return g;
+}
+
+// A wave per segment.
+__global__ __launch_bounds__(kBlock) void segments_fill_kernel(const int64_t *ptr, const int64_t *src, int64_t n_seg, int64_t n_entries,
+                                                               const int32_t *col, const float *val, int64_t nnz, int32_t *col_out,
+                                                               float *val_out)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
+    for (int64_t s = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave; s < n_seg; s += waves) {
+        const int64_t to = clamp64(ptr[s], 0, n_entries), n = clamp64(ptr[s + 1], to, n_entries) - to;
+        const int64_t from = src[s];
+        for (int64_t i = lane; i < n; i += kWave) {
+            const bool in = from >= 0 && from + i < nnz;
+            col_out[to + i] = in ? col[from + i] : -1;
+            val_out[to + i] = in ? val[from + i] : 0.0f;
+        }
+    }
+}
+
+// out[r] = sum of the row's segments in group order; whole lines, row padding zero.  A wave per row: all segments of a strip of 256
+// columns in flight together.
+__global__ __launch_bounds__(kBlock) void segments_sum_kernel(const int32_t *of_row, int64_t n_rows, int64_t n_seg, const float *partial,
+                                                              int32_t dim, int32_t wdim, float *out, int64_t ldo)
+{
+    typedef float float4_t __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t r = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
+    if (r >= n_rows) return;
+    int32_t seg[kSegments];
+#pragma unroll
+    for (int q = 0; q < kSegments; ++q) seg[q] = uniform_i32(of_row[r * kSegments + q]);
+    if (seg[0] < -1) return;                                // a row struck from the table: someone else's to write
+    for (int32_t c = lane * 4; c < wdim; c += kWave * 4) {
+        float4_t x[kSegments];
+#pragma unroll
+        for (int q = 0; q < kSegments; ++q) {
+            x[q] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            if (seg[q] >= 0 && seg[q] < n_seg)
+                x[q] = __builtin_nontemporal_load(reinterpret_cast<const float4_t *>(partial + (int64_t)seg[q] * wdim + c));
+        }
+        float4_t sum = x[0];
+#pragma unroll
+        for (int q = 1; q < kSegments; ++q) sum += x[q];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (c + k >= dim) sum[k] = 0.0f;
+        __builtin_nontemporal_store(sum, reinterpret_cast<float4_t *>(out + r * ldo + c));
+    }
+}
+
+}  // namespace
+
+extern "C" int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_begin, int64_t row_end, const int32_t *col_bounds_host,
+                                        const int32_t *tile_off_host, int64_t *sizes_inout, int64_t *ptr_out, int64_t *src_out,
+                                        int32_t *of_row_out)
+{
+    constexpr int T = ADAQP_SPMM_TILES;
+    if (row_begin < 0 || row_end < row_begin || !rowptr_host || !col_bounds_host || !sizes_inout) return ADAQP_EINVAL;
+    const int64_t n_rows = row_end - row_begin;
+    if (n_rows > 0 && !tile_off_host) return ADAQP_EINVAL;
+    const bool fill = ptr_out != nullptr;
+    if (fill && (!src_out || (n_rows > 0 && !of_row_out))) return ADAQP_EINVAL;
+    // Groups of tiles: an L2 of 4 MB holds two lines of 16 384 columns.  Sums included, 12.7 M entries in 58 000 columns, 256 columns of
+    // H: groups of 7 000 columns 0.64 ms, 14 000 0.65, 21 000 0.70, 29 000 0.72; 15 M in 98 000 columns: 13 000 0.75, 24 000 0.77, 32 000
+    // 0.81.  Smaller graphs with short segments: 2.5 M entries in 58 000 columns, 602 columns of H 0.41, 0.42, 0.43, 0.47.
+    constexpr int32_t kGroupCols = 12288;
+    int first_tile[T + 1], n_groups = 0;
+    for (int t = 0; t < T; ++t) {
+        if (col_bounds_host[t + 1] < col_bounds_host[t]) return ADAQP_EINVAL;
+        if (n_groups == 0 || col_bounds_host[t + 1] - col_bounds_host[first_tile[n_groups - 1]] > kGroupCols) first_tile[n_groups++] = t;
+    }
+    first_tile[n_groups] = T;
+    int64_t n_seg = 0, n_entries = 0;
+    for (int g = 0; g < n_groups; ++g)
+        for (int64_t r = 0; r < n_rows; ++r) {
+            const int32_t *off = tile_off_host + r * (T + 1);
+            const int64_t first = rowptr_host[row_begin + r], degree = rowptr_host[row_begin + r + 1] - first;
+            if (off[0] < 0) {
+                if (fill) of_row_out[r * kSegments + g] = g == 0 ? -2 : -1;
+                continue;
+            }
+            const int32_t a = off[first_tile[g]], b = off[first_tile[g + 1]];
+            if (a < 0 || b < a || b > degree || (g == 0 && off[0] != 0) || (g + 1 == n_groups && off[T] != degree)) return ADAQP_EINVAL;
+            if (fill) of_row_out[r * kSegments + g] = b > a ? (int32_t)n_seg : -1;
+            if (b == a) continue;
+            if (fill) {
+                if (n_seg >= sizes_inout[0]) return ADAQP_EINVAL;
+                ptr_out[n_seg] = n_entries;
+                src_out[n_seg] = first + a;
+            }
+            ++n_seg;
+            n_entries += b - a;
+        }
+    if (n_seg > INT32_MAX - 1024) return ADAQP_ESIZE;
+    if (!fill) {
+        sizes_inout[0] = n_seg;
+        sizes_inout[1] = n_entries;
+        return ADAQP_OK;
+    }
+    if (n_seg != sizes_inout[0] || n_entries != sizes_inout[1]) return ADAQP_EINVAL;
+    ptr_out[n_seg] = n_entries;
+    for (int g = n_groups; g < kSegments; ++g)
+        for (int64_t r = 0; r < n_rows; ++r) of_row_out[r * kSegments + g] = -1;
+    return ADAQP_OK;
+}
+
+extern "C" int adaqp_fill_spmm_segments(const adaqp_spmm_segments *p, const int32_t *col_dev, const float *val_dev, int64_t nnz, void *stream)
+{
+    if (!p || p->n_seg < 0 || p->n_entries < 0 || nnz < 0) return ADAQP_EINVAL;
+    if (p->n_seg == 0 || p->n_entries == 0) return ADAQP_OK;
+    if (!p->ptr_dev || !p->src_dev || !p->col_dev || !p->val_dev || (nnz > 0 && (!col_dev || !val_dev))) return ADAQP_EINVAL;
+    hipLaunchKernelGGL(segments_fill_kernel, dim3((unsigned)std::min<int64_t>((p->n_seg + kWavesPerBlock - 1) / kWavesPerBlock, 65536)), dim3(kBlock),
+                       0, (hipStream_t)stream, p->ptr_dev, p->src_dev, p->n_seg, p->n_entries, col_dev, val_dev, nnz, p->col_dev, p->val_dev);
+    ADAQP_HIP_TRY(hipGetLastError());
+    return ADAQP_OK;
+}
+
+extern "C" int adaqp_spmm_segments_workspace_bytes(int64_t n_seg, int64_t n_entries, int32_t dim, int64_t *bytes_out)
+{
+    if (!bytes_out || n_seg < 0 || n_entries < 0 || dim <= 0) return ADAQP_EINVAL;
+    if (n_seg > INT32_MAX - 1024) return ADAQP_ESIZE;
+    *bytes_out = n_seg == 0 ? 0 : segment_geometry(n_seg, n_entries, dim).bytes;
+    return ADAQP_OK;
+}
+
+extern "C" int adaqp_spmm_csr_segments(const adaqp_spmm_segments *p, const float *H_dev, int64_t n_cols, int64_t ldh, int32_t dim,
+                                       float *out_dev, int64_t ldo, void *workspace_dev, int64_t workspace_bytes, void *stream)
+{
+    if (!p || p->n_seg < 0 || p->n_entries < 0 || p->n_rows < 0 || n_cols < 0 || dim <= 0 || ldh < dim || ldo < dim) return ADAQP_EINVAL;
+    if (p->n_seg == 0 || p->n_rows == 0) return ADAQP_OK;
+    if (!p->ptr_dev || !p->of_row_dev || !p->col_dev || !p->val_dev || !H_dev || !out_dev || n_cols == 0 || p->n_entries == 0) return ADAQP_EINVAL;
+    if (!aligned_to(p->ptr_dev, 8) || !aligned_to(p->of_row_dev, 4) || !aligned_to(p->col_dev, 4) || !aligned_to(p->val_dev, 4)) return ADAQP_EINVAL;
+    if (ldh % 32 != 0 || ldo % 32 != 0 || !aligned_to(H_dev, 128) || !aligned_to(out_dev, 128)) return ADAQP_EINVAL;
+    if (p->n_seg > INT32_MAX - 1024 || p->n_rows > INT32_MAX - 1 || !sliced_takes(p->n_seg, p->n_entries, n_cols, ldh, false, 0, dim)) return ADAQP_ESIZE;
+    const SegmentGeometry g = segment_geometry(p->n_seg, p->n_entries, dim);
+    if (!workspace_dev || !aligned_to(workspace_dev, 256)) return ADAQP_EINVAL;
+    if (workspace_bytes < g.bytes) return ADAQP_ESIZE;
+
+    char *ws = static_cast<char *>(workspace_dev);
+    float *partial = reinterpret_cast<float *>(ws);
+    hipStream_t st = (hipStream_t)stream;
+    constexpr int32_t kCap = kWave * 4 * 8;                 // columns one launch covers
+    for (int32_t c0 = 0; c0 < dim; c0 += kCap) {
+        SpmmArgs a = {};
+        a.rowptr = p->ptr_dev;
+        a.col = p->col_dev;
+        a.val = p->val_dev;
+        a.nnz = p->n_entries;
+        a.n_rows = (int32_t)p->n_seg;
+        a.H = H_dev + c0;
+        a.n_cols = n_cols;
+        a.ldh = ldh;
+        a.dim = std::min(dim - c0, kCap);
+        a.wdim = (a.dim + 31) / 32 * 32;
+        a.out = partial + c0;
+        a.ldo = g.wdim;
+        a.carry_row = reinterpret_cast<int32_t *>(ws + g.carry_row_off);
+        a.carry = reinterpret_cast<float *>(ws + g.carry_off);
+        a.carry_ld = g.wdim;
+        a.n_items = (int32_t)g.n_items;
+        a.full_dim = dim;
+        // two lines per slice (15 M entries, 98 000 columns: one line 0.80 ms, two 0.75, four 0.81)
+        const SlicedCut cut = {a.wdim > 32 ? 2 : 1, 0, segment_blocks(p->n_seg, p->n_entries)};
+        ADAQP_HIP_TRY(launch_sliced(a, cut, p->n_entries, true, st, &a.n_items));
+        ADAQP_HIP_TRY(launch_carry_nv<4>(a, (a.wdim + kWave * 4 - 1) / (kWave * 4), st));
+    }
+    const int64_t blocks = (p->n_rows + kWavesPerBlock - 1) / kWavesPerBlock;
+    hipLaunchKernelGGL(segments_sum_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, st, p->of_row_dev, p->n_rows, p->n_seg, partial, dim,
+                       (int32_t)g.wdim, out_dev, ldo);
+    ADAQP_HIP_TRY(hipGetLastError());
     return ADAQP_OK;
 }
 

@@ -114,13 +114,8 @@ class LayerStep:
         self.rowptr = torch.from_numpy(p.rowptr).to(dev)
         self.col = torch.from_numpy(p.col).to(dev)
         self.val = torch.from_numpy(p.val).to(dev)
-        # the tiled and panel kernels take whole rows of a column range and gain nothing from a spread pitch (58 000 rows,
-        # 28 M entries, 256 columns: step 1.60 ms at 8 lines, 1.63 at 9)
-        spread = not (pad and tiled is not False and any(
-            e > b and (tiled or B.adaqp_spmm_tiled_pays(e - b, int(p.rowptr[e] - p.rowptr[b])))
-            for b, e in (p.overlap_rows, p.dependent_rows)))
-        self.feat = line_padded(p.feat, dev, pad, spread)
-        self.out = line_padded(np.zeros((p.n_rows, cfg.dim), dtype=np.float32), dev, pad, spread)
+        self.feat = line_padded(p.feat, dev, pad, spread=True)
+        self.out = line_padded(np.zeros((p.n_rows, cfg.dim), dtype=np.float32), dev, pad, spread=True)
         self.plan = SendPlan(cfg.dim, p.send_idx, p.bits, p.peer_of_slot, cfg.n_peers, p.halo_idx, dev,
                              add_segments=self.backward)
         n = self.plan.n
@@ -151,6 +146,8 @@ class LayerStep:
         # where the library says that pays; True: rows of panel_min_row entries in panels, always
         self.panels_overlap = self.panels_dependent = B.DevicePanels(None)
         self.blocks_overlap = self.blocks_dependent = B.DeviceBlocks(None)
+        # and the others' entries are kept a second time, in the order of the tiles
+        self.segments_overlap = self.segments_dependent = B.DeviceSegments(None)
         # panel_min_row: one threshold, or one per row range (overlap, dependent)
         min_row_o, min_row_d = panel_min_row if isinstance(panel_min_row, tuple) else (panel_min_row, panel_min_row)
         ws_o = B.adaqp_spmm_workspace_bytes(oe - ob, self.overlap_nnz, cfg.dim)
@@ -159,12 +156,12 @@ class LayerStep:
             ws_o = max(ws_o, B.adaqp_spmm_workspace_bytes(de - ob, self.overlap_nnz + self.dependent_nnz, cfg.dim))
         if pad and tiled is not False:
             if oe > ob and (tiled or B.adaqp_spmm_tiled_pays(oe - ob, self.overlap_nnz)):
-                self.tile_off_overlap, self.tile_chunk_overlap, self.panels_overlap, self.blocks_overlap, need = \
-                    self._plan_long_rows(ob, oe, panels, min_row_o, panel_piece_cols)
+                (self.tile_off_overlap, self.tile_chunk_overlap, self.panels_overlap, self.blocks_overlap, self.segments_overlap,
+                 need) = self._plan_long_rows(ob, oe, panels, min_row_o, panel_piece_cols)
                 ws_o = max(ws_o, need)
             if de > db and (tiled or B.adaqp_spmm_tiled_pays(de - db, self.dependent_nnz)):
-                self.tile_off_dependent, self.tile_chunk_dependent, self.panels_dependent, self.blocks_dependent, need = \
-                    self._plan_long_rows(db, de, panels, min_row_d, panel_piece_cols)
+                (self.tile_off_dependent, self.tile_chunk_dependent, self.panels_dependent, self.blocks_dependent,
+                 self.segments_dependent, need) = self._plan_long_rows(db, de, panels, min_row_d, panel_piece_cols)
                 ws_d = max(ws_d, need)
         self.ws_overlap = torch.empty(max(ws_o, 256), dtype=torch.uint8, device=dev)
         self.ws_dependent = torch.empty(max(ws_d, 256), dtype=torch.uint8, device=dev)
@@ -172,15 +169,15 @@ class LayerStep:
         # process that keeps creating streams can end up with a step's two streams on one queue (no overlap)
         self.stream_msg, self.stream_agg = streams if streams is not None else (torch.cuda.Stream(device=dev),
                                                                                   torch.cuda.Stream(device=dev))
-        for st in (self.stream_msg, self.stream_agg):       # the tables of the blocks are written by a kernel
-            if self.blocks_overlap or self.blocks_dependent:
+        for st in (self.stream_msg, self.stream_agg):       # the tables of blocks and segments are written by kernels
+            if self.tile_off_overlap is not None or self.tile_off_dependent is not None:
                 st.wait_stream(torch.cuda.current_stream(dev))
         self.event_fork = HipEvent()
         self.event_join = HipEvent()
 
     def _plan_long_rows(self, begin, end, panels, min_row, piece_cols):
-        """Tile table, chunk width, panels or blocks of a row range, and the bytes of workspace these take: partial sums of the
-        tiled kernel, then the piece sums of the matrix-core kernel (they may run together)."""
+        """Tile table, chunk width, panels or blocks and segments of a row range, and the bytes of workspace these take: partial
+        sums of the segments (or of the tiled kernel), then the piece sums of the matrix-core kernel (they may run together)."""
         p, dim, n_cols = self.p, self.dim, self.p.feat.shape[0]
         bounds, off = B.adaqp_plan_spmm_tiles(p.rowptr, p.col, begin, end, n_cols)
         with_panels, with_blocks = B.DevicePanels(None), B.DeviceBlocks(None)
@@ -193,10 +190,16 @@ class LayerStep:
                 only_if_pays_for_ld=self.feat.stride(0)), self.device)
             if with_blocks:
                 B.adaqp_fill_spmm_blocks(with_blocks, begin, end, self.rowptr, self.col, self.val)
-        need = B.adaqp_spmm_tiled_workspace_bytes(end - begin, dim) \
+        segments = B.DeviceSegments(None)
+        if n_cols * self.feat.stride(0) * 4 < B.SPMM_SEGMENTS_MOST_BYTES:
+            segments = B.DeviceSegments(B.adaqp_plan_spmm_segments(p.rowptr, begin, end, bounds, off), self.device)
+        if segments:
+            B.adaqp_fill_spmm_segments(segments, self.col, self.val)
+        need = max(B.adaqp_spmm_tiled_workspace_bytes(end - begin, dim), B.adaqp_spmm_segments_workspace_bytes(segments, dim)) \
             + B.adaqp_spmm_panels_workspace_bytes(with_panels.n_per_tile, dim) \
             + B.adaqp_spmm_blocks_workspace_bytes(with_blocks, dim)
-        return torch.from_numpy(off).to(self.device), B.adaqp_spmm_tiled_chunk_cols(bounds, dim), with_panels, with_blocks, need
+        return (torch.from_numpy(off).to(self.device), B.adaqp_spmm_tiled_chunk_cols(bounds, dim), with_panels, with_blocks,
+                segments, need)
 
     def set_fused_receive(self, on: bool) -> None:
         """Forward only.  On: received rows are not de-quantised into feat; the dependent aggregation reads
@@ -230,8 +233,10 @@ class LayerStep:
             else self.tile_off_dependent.data_ptr()
         if d.tile_off_overlap_dev:
             d.panels_overlap, d.blocks_overlap = self.panels_overlap.c, self.blocks_overlap.c
+            d.segments_overlap = self.segments_overlap.c
         if d.tile_off_dependent_dev:
             d.panels_dependent, d.blocks_dependent = self.panels_dependent.c, self.blocks_dependent.c
+            d.segments_dependent = self.segments_dependent.c
         if self.backward and self.backward_receive and pl.seg_order is not None:
             d.recv_seg_order_dev, d.recv_seg_ptr_dev = pl.seg_order.data_ptr(), pl.seg_ptr.data_ptr()
             d.n_recv_seg = pl.seg_ptr.shape[0] - 1
@@ -250,8 +255,13 @@ class LayerStep:
 
     def default_schedule(self) -> int:
         """CHAIN where a second stream has nothing to hide or to pair, else ISOLATED."""
-        tiled = self.tile_off_overlap is not None or (self.tile_off_dependent is not None and not self.fused_receive)
-        return B.ISOLATED if tiled or self.plan.packed_bytes > CHAIN_BYTES else B.CHAIN
+        dependent = self.tile_off_dependent is not None and not self.fused_receive
+        tiled, both = self.tile_off_overlap is not None or dependent, self.tile_off_overlap is not None and dependent
+        # two tiled aggregations wait for each other, so that a second stream only hides the messages (58 000 rows, 28 M entries,
+        # 256 columns: 1.59 ms in a row, 1.64 on two streams), but pairs with what matrix-core kernels leave of the GPU
+        matrix = self.panels_overlap or self.panels_dependent or self.blocks_overlap or self.blocks_dependent
+        alone = not tiled or (both and not matrix)
+        return B.CHAIN if alone and self.plan.packed_bytes <= CHAIN_BYTES else B.ISOLATED
 
     def run(self, schedule: Optional[int] = None) -> None:
         """Enqueues one layer step; synchronise stream_msg to wait for it.  Without a schedule the step takes the one of

@@ -925,6 +925,46 @@ def test_spmm_panels_rejects_what_it_cannot_do():
 # the layer step
 # ------------------------------------------------------------------------------------------------------
 
+@pytest.mark.parametrize("dim,ld", [(128, 128), (602, 608), (64, 96), (7, 32), (96, 96), (256, 288), (2049, 2080)])
+@pytest.mark.parametrize("n_rows,n_cols", [(300, 900), (700, 40_000), (1, 9)])          # one group of tiles; several; one row
+def test_spmm_segments(oracle, dim, ld, n_rows, n_cols):
+    """Rows of none to eight segments, short ones whole in one, some struck from the table, which stay as they are."""
+    _say(f"segments spmm dim={dim} ld={ld} rows={n_rows} cols={n_cols}")
+    rng = np.random.default_rng(5000 + dim)
+    degs = np.minimum(rng.integers(0, 130, size=n_rows), n_cols)
+    degs[0] = min(n_cols, 3_000)
+    if n_rows > 9:
+        degs[5:9], degs[n_rows // 2] = 0, 800
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, degs)
+    H = np.full((n_cols, ld), np.nan, dtype=np.float32)                # NaN in the row padding
+    H[:, :dim] = rng.standard_normal((n_cols, dim), dtype=np.float32)
+    want, mag = oracle.spmm_csr(rowptr, col, val, 0, n_rows, np.ascontiguousarray(H[:, :dim]), dim)
+    cl, vl, Hd = (torch.from_numpy(x).to(DEV) for x in (col, val, H))
+    for rb, re in ((0, n_rows), (n_rows // 3, n_rows)):
+        bounds, off = B.adaqp_plan_spmm_tiles(rowptr, col, rb, re, n_cols)
+        struck = np.arange(re - rb) % 7 == 3
+        off[struck] = -1
+        plan = B.adaqp_plan_spmm_segments(rowptr, rb, re, bounds, off)
+        segments = B.DeviceSegments(plan, DEV)
+        B.adaqp_fill_spmm_segments(segments, cl, vl)
+        ws = torch.empty(B.adaqp_spmm_segments_workspace_bytes(segments, dim), dtype=torch.uint8, device=DEV)
+        ws.fill_(0xFF)                                                 # NaN patterns: unread unless written first
+        out = torch.full((n_rows, ld), 7.0, dtype=torch.float32, device=DEV)
+        B.adaqp_spmm_csr_segments(segments, rb, Hd, dim, out, ws)
+        again = torch.full((n_rows, ld), 7.0, dtype=torch.float32, device=DEV)
+        B.adaqp_spmm_csr_segments(segments, rb, Hd, dim, again, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int32), again.view(torch.int32))
+        got = out.cpu().numpy()
+        mine = np.zeros(n_rows, dtype=bool)
+        mine[rb:re] = ~struck
+        err = np.abs(got[mine][:, :dim].astype(np.float64) - want[mine])
+        worst = float((err / (SPMM_RTOL * mag[mine] + 1e-30)).max())
+        assert worst <= 1.0, f"worst error {worst:.3f} x tolerance"
+        zero_to = _padded_cols(dim, ld)
+        assert np.all(got[mine][:, dim:zero_to] == 0.0) and np.all(got[mine][:, zero_to:] == 7.0) and np.all(got[~mine] == 7.0)
+
+
 @pytest.mark.parametrize("dim,ld", [(128, 128), (602, 608), (64, 64), (7, 32), (96, 96), (130, 160), (256, 288), (1025, 1056)])
 @pytest.mark.parametrize("n_rows,n_heavy,n_cols", [(300, 140, 900), (40, 3, 33), (150, 128, 5_000)])
 def test_spmm_blocks(oracle, dim, ld, n_rows, n_heavy, n_cols):

@@ -380,6 +380,41 @@ def test_plan_spmm_panels_random_graphs():
             assert np.array_equal(dense[k], want), (case, k, r)
 
 
+@pytest.mark.parametrize("n_rows,n_cols", [(1, 1), (60, 500), (90, 90_000)])
+def test_plan_spmm_segments(n_rows, n_cols):
+    """The segments of a row, in group order, are its entries in order; nothing of rows struck from the table."""
+    rng = np.random.default_rng(n_cols)
+    degs = np.minimum(rng.integers(0, 400, size=n_rows), n_cols)
+    rowptr = np.concatenate([[0], np.cumsum(degs)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n_cols, size=d, replace=False)) for d in degs] or [[]]).astype(np.int32)
+    for rb, re in ((0, n_rows), (n_rows // 2, n_rows)):
+        bounds, off = B.adaqp_plan_spmm_tiles(rowptr, col, rb, re, n_cols)
+        struck = np.arange(re - rb) % 5 == 2
+        off[struck] = -1
+        plan = B.adaqp_plan_spmm_segments(rowptr, rb, re, bounds, off)
+        if plan is None:
+            assert degs[rb:re][~struck].sum() == 0
+            continue
+        assert plan["ptr"][0] == 0 and plan["ptr"][-1] == plan["n_entries"] == degs[rb:re][~struck].sum()
+        lengths = np.diff(plan["ptr"])
+        assert np.all(lengths > 0) and plan["n_seg"] == (plan["of_row"] >= 0).sum()
+        assert np.array_equal(np.sort(plan["of_row"][plan["of_row"] >= 0]), np.arange(plan["n_seg"]))
+        for r in range(re - rb):
+            mine = plan["of_row"][r][plan["of_row"][r] >= 0]
+            if struck[r]:
+                assert plan["of_row"][r][0] == -2 and mine.size == 0
+                continue
+            at = np.concatenate([np.arange(plan["src"][s], plan["src"][s] + lengths[s]) for s in mine] or [[]])
+            assert np.array_equal(at, np.arange(rowptr[rb + r], rowptr[rb + r + 1])) and np.all(np.diff(mine) > 0)
+        # a group's columns: what tiles that can be joined span
+        if n_cols > 50_000:
+            assert np.unique(np.nonzero(plan["of_row"] >= 0)[1]).size > 1
+    with pytest.raises(B.AdaqpError):
+        bounds, off = B.adaqp_plan_spmm_tiles(rowptr, col, 0, n_rows, n_cols)
+        off[0, -1] += 1                                                # a table that disagrees with rowptr
+        B.adaqp_plan_spmm_segments(rowptr, 0, n_rows, bounds, off)
+
+
 @pytest.mark.parametrize("n_rows,n_cols,min_len", [(1, 1, 1), (40, 33, 5), (130, 900, 60), (300, 2_000, 40)])
 def test_plan_spmm_blocks(n_rows, n_cols, min_len):
     """A block lists exactly the distinct columns of its rows, each in its interval, ascending, steps filled with the last one."""
