@@ -177,8 +177,6 @@ __device__ __forceinline__ void block_piece(const BlockArgs &a, Stage &stage, in
 #pragma unroll
         for (int v = 0; v < 16; ++v) high[t][v] = low[t][v] = 0.0f;
 
-    // Nothing in the loop is behind a condition, steps past the last are the last one again: the compiler counts the loads in
-    // flight over all paths, and waits for the youngest where one path has fewer.
     // Nothing in a step is behind a condition, steps past the last are the last one again: the compiler counts the loads in
     // flight over all paths, and waits for the youngest where one path has fewer.
     constexpr std::integral_constant<int, 0> even;
@@ -261,12 +259,41 @@ __global__ __launch_bounds__(kBlock, 2) void spmm_block_kernel(const BlockArgs a
     else block_piece<1>(a, stage, piece, s0, s1, c_begin);
 }
 
+// One wave's share of a row's sum in plain fp32, from the pieces wave, wave + 4, ...: only the columns that the row lists.
+__device__ float4_t listed_columns(const BlockArgs &a, int32_t first, int32_t m, int32_t wave, int32_t lane, int32_t c, bool live)
+{
+    float4_t sum = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int32_t p = wave; p < a.n_pieces; p += kWavesPerBlock) {
+        const int32_t s0 = max(0, min(a.step_ptr[first + p], a.n_steps)), s1 = max(s0, min(min(a.step_ptr[first + p + 1], a.n_steps), s0 + kMostSteps));
+        for (int32_t s = s0; s < s1; ++s) {
+            const int32_t k = lane % kStepCols;                     // lane k: the step's column k
+            const float alpha = a.table[((((int64_t)s * kRowGroups + m / 32) * 2 + k / 16) * kWave + (k / 8 % 2) * 32 + m % 32) * 8 + k % 8];
+            const int32_t col = (int32_t)min((uint32_t)a.cols[(int64_t)s * kStepCols + k], (uint32_t)a.n_cols - 1u);
+            for (uint32_t lists = (uint32_t)__ballot(alpha != 0.0f); lists; lists &= lists - 1) {
+                const int32_t q = __builtin_ctz(lists);
+                const float w = __shfl(alpha, q);
+                const int64_t from = __shfl(col, q);
+                if (live) {
+                    const float4_t x = *reinterpret_cast<const float4_t *>(a.H + from * a.ldh + c);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) sum[t] += w * x[t];
+                }
+            }
+        }
+    }
+    return sum;
+}
+
 // out[row of a block] = sum of the block's pieces, in a fixed order; whole lines, row padding zero.  A workgroup per row and
 // strip of 256 columns; its four waves take every fourth piece each and their sums are added in wave order.
+//
+// An infinity or NaN in H makes every row of the piece NaN there (0 x inf, and inf has no remainder to split off), so sums that
+// are not finite are taken again from the columns that the row itself lists: rows without such a column keep their sums, the
+// others get what fp32 gives.
 __global__ __launch_bounds__(kBlock) void spmm_block_sum_kernel(const BlockArgs a, int32_t n_strips)
 {
-    __shared__ float4_t part[kWavesPerBlock][kWave];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    __shared__ float4_t part[2][kWavesPerBlock][kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int64_t r = blockIdx.x / (uint32_t)n_strips;              // block * 128 + m
     const int32_t strip = (int32_t)(blockIdx.x % (uint32_t)n_strips);
     const int64_t row = a.rows[r];
@@ -289,17 +316,31 @@ __global__ __launch_bounds__(kBlock) void spmm_block_sum_kernel(const BlockArgs 
 #pragma unroll
         for (int q = 0; q < kAhead; ++q) sum += x[q];
     }
-    part[wave][lane] = sum;
-    __syncthreads();
-    if (wave == 0 && live) {
-        float4_t total = part[0][lane];
+    auto add_waves = [&](const float4_t (&of)[kWavesPerBlock][kWave]) {
+        float4_t total = of[0][lane];
 #pragma unroll
-        for (int w = 1; w < kWavesPerBlock; ++w) total += part[w][lane];
+        for (int w = 1; w < kWavesPerBlock; ++w) total += of[w][lane];
+        return total;
+    };
+    part[0][wave][lane] = sum;
+    __syncthreads();
+    float4_t total = add_waves(part[0]);                            // in every wave: all of them take the branch below, or none
+    bool again[4], any = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (c + k >= a.dim) total[k] = 0.0f;                        // row padding
+        again[k] = !(__builtin_fabsf(total[k]) < __builtin_inff());
+        any |= again[k];
+    }
+    if (__ballot(any) != 0) {
+        part[1][wave][lane] = listed_columns(a, first, m, wave, lane, c, live);
+        __syncthreads();
+        const float4_t exact = add_waves(part[1]);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (c + k >= a.dim) total[k] = 0.0f;                    // row padding
-        __builtin_nontemporal_store(total, reinterpret_cast<float4_t *>(a.out + row * a.ldo + c));
+            if (again[k]) total[k] = exact[k];
     }
+    if (wave == 0 && live) __builtin_nontemporal_store(total, reinterpret_cast<float4_t *>(a.out + row * a.ldo + c));
 }
 
 // The table: zeros, then the coefficient of every entry of the blocks' rows at its column's place.

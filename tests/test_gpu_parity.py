@@ -1036,6 +1036,61 @@ def test_spmm_blocks_precision():
             assert rel <= 1.5e-7, rel                                   # a rounding per term would be sqrt(3000) of them
 
 
+def test_spmm_blocks_non_finite():
+    """An infinity or NaN in H reaches the rows that list its column, and no others; next to values near the ends of fp32."""
+    _say("blocks non-finite")
+    rng = np.random.default_rng(9)
+    n_rows, n_cols, dim = 200, 700, 330                                # two strips of 256 columns, the second partly filled
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, rng.integers(150, 600, size=n_rows))
+    H = rng.standard_normal((n_cols, 352)).astype(np.float32)
+    for v, c, k in ((np.inf, 3, 0), (-np.inf, 90, 17), (np.nan, 400, 256), (np.inf, 401, 329), (-np.inf, 402, 329), (5e37, 500, 40)):
+        H[c, k] = v                                                    # (5e37: coefficients are up to 5, products within fp32)
+    H[:, dim:] = np.nan
+    plan = B.adaqp_plan_spmm_blocks(rowptr, col, 0, n_rows, n_cols, dim, 1)
+    blocks = B.DeviceBlocks(plan, DEV)
+    rp, cl, vl, Hd = (torch.from_numpy(x).to(DEV) for x in (rowptr, col, val, H))
+    B.adaqp_fill_spmm_blocks(blocks, 0, n_rows, rp, cl, vl)
+    out = torch.full((n_rows, 352), 7.0, device=DEV)
+    B.adaqp_spmm_csr_blocks(blocks, 0, n_rows, Hd, dim, out,
+                            torch.empty(B.adaqp_spmm_blocks_workspace_bytes(blocks, dim), dtype=torch.uint8, device=DEV))
+    got = out.cpu().numpy().astype(np.float64)
+    want, mag = np.zeros((n_rows, dim)), np.zeros((n_rows, dim))
+    with np.errstate(invalid="ignore"):
+        for r in range(n_rows):
+            c, a = col[rowptr[r]:rowptr[r + 1]], val[rowptr[r]:rowptr[r + 1]].astype(np.float64)[:, None]
+            x = H[c, :dim].astype(np.float64)
+            want[r], mag[r] = (a * x).sum(0), np.abs(a * x).sum(0)
+    fine = np.isfinite(want)
+    assert 0 < fine.sum() < fine.size and np.array_equal(np.isnan(got[:, :dim]), np.isnan(want))
+    assert np.array_equal(got[:, :dim][np.isinf(want)], want[np.isinf(want)])
+    assert np.all(np.abs(got[:, :dim][fine] - want[fine]) <= SPMM_RTOL * mag[fine])
+    assert np.all(got[:, dim:] == 0.0)
+
+
+@pytest.mark.parametrize("exponent", [-60, -100, -118])
+def test_spmm_blocks_small_values(exponent):
+    """Values whose lower parts are denormal in bf16 (2^-110 and below), and products that are denormal themselves: next to the
+    relative error, no more than a rounding of the smallest fp32 number per product."""
+    _say(f"blocks small values 2^{exponent}")
+    rng = np.random.default_rng(10)
+    n_rows, n_cols, dim = 140, 500, 64
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, rng.integers(100, 500, size=n_rows))
+    H = np.ldexp(rng.standard_normal((n_cols, dim)), exponent).astype(np.float32)
+    want, mag = np.zeros((n_rows, dim)), np.zeros((n_rows, dim))
+    for r in range(n_rows):
+        c, a = col[rowptr[r]:rowptr[r + 1]], val[rowptr[r]:rowptr[r + 1]].astype(np.float64)[:, None]
+        want[r], mag[r] = (a * H[c]).sum(0), np.abs(a * H[c]).sum(0)
+    blocks = B.DeviceBlocks(B.adaqp_plan_spmm_blocks(rowptr, col, 0, n_rows, n_cols, dim, 1), DEV)
+    rp, cl, vl, Hd = (torch.from_numpy(x).to(DEV) for x in (rowptr, col, val, H))
+    B.adaqp_fill_spmm_blocks(blocks, 0, n_rows, rp, cl, vl)
+    out = torch.zeros((n_rows, dim), device=DEV)
+    B.adaqp_spmm_csr_blocks(blocks, 0, n_rows, Hd, dim, out,
+                            torch.empty(B.adaqp_spmm_blocks_workspace_bytes(blocks, dim), dtype=torch.uint8, device=DEV))
+    error = np.abs(out.cpu().numpy().astype(np.float64) - want)
+    worst = float((error / (SPMM_RTOL * mag + n_cols * 2.0 ** -149)).max())
+    assert worst <= 1.0, worst
+
+
 def _oracle_layer(oracle, p, seed):
     """Composes the oracle's pieces in the order of Sec. 3.1: quantise, exchange (identity), de-quantise,
     aggregate.  Returns (packed, params, feat_after, out64, mag64)."""
