@@ -169,8 +169,10 @@ class LayerStep:
         # process that keeps creating streams can end up with a step's two streams on one queue (no overlap)
         self.stream_msg, self.stream_agg = streams if streams is not None else (torch.cuda.Stream(device=dev),
                                                                                   torch.cuda.Stream(device=dev))
-        for st in (self.stream_msg, self.stream_agg):       # the tables of blocks and segments are written by kernels
-            if self.tile_off_overlap is not None or self.tile_off_dependent is not None:
+        # the tables of blocks and segments hold the coefficients a second time; kernels write them
+        self._copied = (self.val, self.val._version)
+        for st in (self.stream_msg, self.stream_agg):
+            if self._copies():
                 st.wait_stream(torch.cuda.current_stream(dev))
         self.event_fork = HipEvent()
         self.event_join = HipEvent()
@@ -200,6 +202,22 @@ class LayerStep:
             + B.adaqp_spmm_blocks_workspace_bytes(with_blocks, dim)
         return (torch.from_numpy(off).to(self.device), B.adaqp_spmm_tiled_chunk_cols(bounds, dim), with_panels, with_blocks,
                 segments, need)
+
+    def _copies(self):
+        """(blocks, segments, row range) of the ranges that have them."""
+        return [c for c in ((self.blocks_overlap, self.segments_overlap, self.p.overlap_rows),
+                            (self.blocks_dependent, self.segments_dependent, self.p.dependent_rows)) if c[0] or c[1]]
+
+    def _refresh_copies(self) -> None:
+        """A caller may write new coefficients into val between steps: the copies follow, in the order of stream_msg, as the
+        step itself.  A captured step follows what was in val when it was captured."""
+        for blocks, segments, (begin, end) in self._copies():
+            if blocks:
+                B.adaqp_fill_spmm_blocks(blocks, begin, end, self.rowptr, self.col, self.val, self.stream_msg)
+            if segments:
+                B.adaqp_fill_spmm_segments(segments, self.col, self.val, self.stream_msg)
+            self.stream_agg.wait_stream(self.stream_msg)
+        self._copied = (self.val, self.val._version)
 
     def set_fused_receive(self, on: bool) -> None:
         """Forward only.  On: received rows are not de-quantised into feat; the dependent aggregation reads
@@ -267,6 +285,8 @@ class LayerStep:
         """Enqueues one layer step; synchronise stream_msg to wait for it.  Without a schedule the step takes the one of
         default_schedule(): work that a caller queues on stream_agg itself is ordered with such a step through stream_msg
         only.  A schedule that is given is kept."""
+        if self._copied[0] is not self.val or self._copied[1] != self.val._version:
+            self._refresh_copies()
         B.adaqp_layer_step(self.desc(self.default_schedule() if schedule is None else schedule))
 
     def synchronize(self) -> None:

@@ -1109,6 +1109,28 @@ def _oracle_layer(oracle, p, seed):
     return None, None, None, out64, mag
 
 
+def test_layer_step_follows_new_coefficients():
+    """Blocks and segments keep the coefficients a second time: a caller who writes others into val gets the step of those."""
+    _say("layer step, new coefficients")
+    p = make_partition(replace(CONFIGS["c0"], mean_degree=1500.0))
+    L = LayerStep(p, DEV, seed=5, tiled=True)
+    assert L.blocks_overlap and L.segments_overlap
+    L.run()
+    L.synchronize()
+    before = L.out.clone()
+    L.val.mul_(2.0)                                                    # every product and sum is exactly twice as large
+    torch.cuda.synchronize()
+    for _ in range(2):
+        L.run()
+        L.synchronize()
+        assert torch.equal(L.out, before * 2.0)
+    L.val = L.val * 0.5                                                # another tensor in its place
+    torch.cuda.synchronize()
+    L.run()
+    L.synchronize()
+    assert torch.equal(L.out, before)
+
+
 @pytest.mark.parametrize("name", ["c0", "c0_backward"])
 def test_layer_step_matches_oracle_in_every_schedule(oracle, name):
     _say(f"layer step {name}")
