@@ -170,7 +170,7 @@ class LayerStep:
         self.stream_msg, self.stream_agg = streams if streams is not None else (torch.cuda.Stream(device=dev),
                                                                                   torch.cuda.Stream(device=dev))
         # the tables of blocks and segments hold the coefficients a second time; kernels write them
-        self._copied = (self.val, self.val._version)
+        self._copied = self._coefficients()
         for st in (self.stream_msg, self.stream_agg):
             if self._copies():
                 st.wait_stream(torch.cuda.current_stream(dev))
@@ -208,6 +208,10 @@ class LayerStep:
         return [c for c in ((self.blocks_overlap, self.segments_overlap, self.p.overlap_rows),
                             (self.blocks_dependent, self.segments_dependent, self.p.dependent_rows)) if c[0] or c[1]]
 
+    def _coefficients(self):
+        """val and how often it was written to (-1: a tensor made in inference mode, which does not count that)."""
+        return self.val, -1 if self.val.is_inference() else self.val._version
+
     def _refresh_copies(self) -> None:
         """A caller may write new coefficients into val between steps: the copies follow, in the order of stream_msg, as the
         step itself.  A captured step follows what was in val when it was captured."""
@@ -217,7 +221,7 @@ class LayerStep:
             if segments:
                 B.adaqp_fill_spmm_segments(segments, self.col, self.val, self.stream_msg)
             self.stream_agg.wait_stream(self.stream_msg)
-        self._copied = (self.val, self.val._version)
+        self._copied = self._coefficients()
 
     def set_fused_receive(self, on: bool) -> None:
         """Forward only.  On: received rows are not de-quantised into feat; the dependent aggregation reads
@@ -285,7 +289,8 @@ class LayerStep:
         """Enqueues one layer step; synchronise stream_msg to wait for it.  Without a schedule the step takes the one of
         default_schedule(): work that a caller queues on stream_agg itself is ordered with such a step through stream_msg
         only.  A schedule that is given is kept."""
-        if self._copied[0] is not self.val or self._copied[1] != self.val._version:
+        tensor, version = self._coefficients()
+        if tensor is not self._copied[0] or version != self._copied[1]:
             self._refresh_copies()
         B.adaqp_layer_step(self.desc(self.default_schedule() if schedule is None else schedule))
 

@@ -1129,6 +1129,11 @@ def test_layer_step_follows_new_coefficients():
     L.run()
     L.synchronize()
     assert torch.equal(L.out, before)
+    with torch.inference_mode():                                       # such a tensor does not count its changes
+        L = LayerStep(p, DEV, seed=5, tiled=True)
+        L.run()
+        L.synchronize()
+        assert torch.equal(L.out, before)
 
 
 @pytest.mark.parametrize("name", ["c0", "c0_backward"])
