@@ -332,6 +332,15 @@ int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_begin, int6
                              const int32_t *tile_off_host, int64_t *sizes_inout, int64_t *ptr_out, int64_t *src_out,
                              int32_t *of_row_out);
 
+/* Host only.  What segments save over adaqp_spmm_csr on whole lines for rows [row_begin, row_end): *gain_out in entries times 128-byte lines
+ * of H, negative where they cost more.  A step that aggregates several ranges adds them up and takes segments in all of them from
+ * ADAQP_SPMM_SEGMENTS_MIN_GAIN on (what the further launches cost).  transposed: the range belongs to a backward step.  Rows
+ * that do not list ascending, distinct, in-range columns have no segments: -infinity, or EINVAL where adaqp_spmm_tiled_pays asks for
+ * them. */
+#define ADAQP_SPMM_SEGMENTS_MIN_GAIN 2e6
+int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end, int64_t n_cols,
+                             int32_t dim, int32_t transposed, double *gain_out);
+
 /* Writes segments_host->col_dev and val_dev from the CSR the plan was made for, once per graph (or whenever val changes). */
 int adaqp_fill_spmm_segments(const adaqp_spmm_segments *segments_host, const int32_t *col_dev, const float *val_dev, int64_t nnz,
                              void *stream);

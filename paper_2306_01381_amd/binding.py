@@ -118,6 +118,7 @@ _SIGNATURES = {
                                               _vp, _vp, _vp, _vp]),
     "adaqp_spmm_panels_workspace_bytes": (ctypes.c_int, [_i32, _i32, _vp]),
     "adaqp_spmm_panels_pay": (_i32, [_i64, _i32]),
+    "adaqp_spmm_segments_gain": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp]),
     "adaqp_plan_spmm_segments": (ctypes.c_int, [_vp, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp]),
     "adaqp_fill_spmm_segments": (ctypes.c_int, [ctypes.POINTER(SpmmSegments), _vp, _vp, _i64, _vp]),
     "adaqp_spmm_segments_workspace_bytes": (ctypes.c_int, [_i64, _i64, _i32, _vp]),
@@ -481,6 +482,20 @@ def adaqp_plan_spmm_segments(rowptr_host: np.ndarray, row_begin: int, row_end: i
     _check(lib().adaqp_plan_spmm_segments(*args, plan["ptr"].ctypes.data, plan["src"].ctypes.data, plan["of_row"].ctypes.data),
            "adaqp_plan_spmm_segments")
     return plan
+
+
+SPMM_SEGMENTS_MIN_GAIN = 2e6
+
+
+def adaqp_spmm_segments_gain(rowptr_host: np.ndarray, col_host: np.ndarray, row_begin: int, row_end: int, n_cols: int, dim: int,
+                             transposed: bool = False) -> float:
+    """Host-only.  What segments save for these rows; the ranges of a step add up to SPMM_SEGMENTS_MIN_GAIN where they pay."""
+    rowptr = np.ascontiguousarray(rowptr_host, dtype=np.int64)
+    col = np.ascontiguousarray(col_host, dtype=np.int32)
+    out = ctypes.c_double(0.0)
+    _check(lib().adaqp_spmm_segments_gain(rowptr.ctypes.data, col.ctypes.data, row_begin, row_end, n_cols, dim, int(transposed),
+                                          ctypes.byref(out)), "adaqp_spmm_segments_gain")
+    return out.value
 
 
 class DeviceSegments:

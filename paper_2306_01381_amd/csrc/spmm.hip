@@ -21,7 +21,11 @@
 // The kernel is a gather: per entry it reads 8 bytes of (col, alpha) and 4*dim bytes of H.  It is bound by
 // how fast H rows come out of L2 / Infinity Cache / HBM, not by arithmetic, so there is no MFMA use.
 #include <algorithm>
+#include <cmath>
+#include <functional>
 #include <mutex>
+#include <numeric>
+#include <vector>
 
 #include "spmm_common.hpp"
 
@@ -679,6 +683,62 @@ extern "C" int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_
     ptr_out[n_seg] = n_entries;
     for (int g = n_groups; g < kSegments; ++g)
         for (int64_t r = 0; r < n_rows; ++r) of_row_out[r * kSegments + g] = -1;
+    return ADAQP_OK;
+}
+
+// What segments save is what the sliced kernel misses in its L2s: entries of rows that are cut up (shorter ones lie whole in one group and
+// find no more there than before), but for those whose columns are the most popular ones.  What they cost is the walk over all
+// entries, and a partial row and its sum per row.  1 370 steps of 5 000 to 300 000 rows, 20 to 500 entries per row, 64 to
+// 602 columns of H, Zipf and log-normal rows, both directions, timed with and without; the weights below put 1 300 on the faster side and
+// lose 16 % at most, 8 % on all but one.  Against segments from a mean of 128 entries per row on: geometric mean 1.055 forward,
+// 1.093 backward (power-law degrees there 0.34-0.75 with segments: a few columns hold most of the entries); against none:
+// 1.116, 1.043 (150 000 rows, 256 columns: 48 entries per row 898 -> 675 us, 100 entries 1 808 -> 1 109 us).
+extern "C" int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end, int64_t n_cols,
+                                        int32_t dim, int32_t transposed, double *gain_out)
+{
+    if (!rowptr_host || !gain_out || row_begin < 0 || row_end < row_begin || n_cols < 0 || n_cols > INT32_MAX || dim <= 0) return ADAQP_EINVAL;
+    constexpr int64_t kPopular = 4096;          // columns that stay in an L2 beside everything else
+    constexpr int64_t kSample = 1 << 22;        // entries looked at for that
+    const int64_t first = rowptr_host[row_begin], last = rowptr_host[row_end], block_row = adaqp_spmm_blocks_min_row(n_cols);
+    const double lines = (double)(((int64_t)dim + 31) / 32);
+    double cut = 0.0, dense = 0.0;              // entries of rows that are cut up, of rows for the matrix cores
+    int64_t n_dense = 0;
+    for (int64_t r = row_begin; r < row_end; ++r) {
+        const int64_t degree = rowptr_host[r + 1] - rowptr_host[r];
+        if (degree < 0) return ADAQP_EINVAL;
+        if (degree >= ADAQP_SPMM_TILED_SHORT_ROW) cut += (double)degree;
+        if (degree >= block_row) {
+            dense += (double)degree;
+            ++n_dense;
+        }
+    }
+    if (!adaqp_spmm_blocks_pay(n_dense, n_cols, 32)) dense = 0.0;
+    const double entries = (double)(last - first), rows = (double)(row_end - row_begin);
+    // forward slices are one line, backward ones four: the misses that are left, and their weight, differ
+    const double cost = transposed ? (0.26 * lines + 0.41) * entries : (0.5 * lines + 0.25) * entries + 2.7 * lines * rows;
+    const double saved = transposed ? 0.0 : 0.56 * lines * dense;
+    *gain_out = saved - cost;
+    const bool asked_for = adaqp_spmm_tiled_pays(row_end - row_begin, last - first) != 0;
+    if (!asked_for && cut * lines + *gain_out <= 0.0) return ADAQP_OK;         // whatever the columns are
+    if (!col_host) return ADAQP_EINVAL;
+    for (int64_t r = row_begin; r < row_end; ++r) {
+        int32_t before = -1;
+        for (int64_t j = rowptr_host[r]; j < rowptr_host[r + 1]; ++j) {
+            const int32_t c = col_host[j];
+            if (c <= before || c >= n_cols) {
+                *gain_out = -INFINITY;
+                return asked_for ? ADAQP_EINVAL : ADAQP_OK;
+            }
+            before = c;
+        }
+    }
+    std::vector<int32_t> uses((size_t)n_cols, 0);
+    const int64_t stride = std::max<int64_t>((last - first) / kSample, 1);
+    int64_t seen = 0;
+    for (int64_t j = first; j < last; j += stride, ++seen) ++uses[(size_t)col_host[j]];
+    if (n_cols > kPopular) std::nth_element(uses.begin(), uses.begin() + kPopular, uses.end(), std::greater<int32_t>());
+    const int64_t popular = std::accumulate(uses.begin(), uses.begin() + std::min(kPopular, n_cols), (int64_t)0);
+    if (seen > 0) *gain_out += cut * lines * (1.0 - (double)popular / (double)seen);
     return ADAQP_OK;
 }
 

@@ -139,7 +139,8 @@ class LayerStep:
         self.overlap_nnz = int(p.rowptr[oe] - p.rowptr[ob])
         self.dependent_nnz = int(p.rowptr[de] - p.rowptr[db])
         # aggregation tiled over the L2 caches: pays when rows are long (every row of feat re-used many times).
-        # tiled=None lets the library decide per row range (adaqp_spmm_tiled_pays: mean row length).
+        # tiled=None lets the library decide: by what segments of both ranges save, or where they cannot be used per
+        # row range (adaqp_spmm_tiled_pays: mean row length).
         self.tile_off_overlap = self.tile_off_dependent = None
         self.tile_chunk_overlap = self.tile_chunk_dependent = 0
         # within a tiled range, rows that list a good part of the columns go to the matrix cores: panels=None in dense blocks,
@@ -155,11 +156,12 @@ class LayerStep:
         if oe == db:        # CHAIN aggregates both ranges in one launch, if this workspace can take them
             ws_o = max(ws_o, B.adaqp_spmm_workspace_bytes(de - ob, self.overlap_nnz + self.dependent_nnz, cfg.dim))
         if pad and tiled is not False:
-            if oe > ob and (tiled or B.adaqp_spmm_tiled_pays(oe - ob, self.overlap_nnz)):
+            tile_overlap, tile_dependent = self._ranges_to_tile(tiled)
+            if tile_overlap:
                 (self.tile_off_overlap, self.tile_chunk_overlap, self.panels_overlap, self.blocks_overlap, self.segments_overlap,
                  need) = self._plan_long_rows(ob, oe, panels, min_row_o, panel_piece_cols)
                 ws_o = max(ws_o, need)
-            if de > db and (tiled or B.adaqp_spmm_tiled_pays(de - db, self.dependent_nnz)):
+            if tile_dependent:
                 (self.tile_off_dependent, self.tile_chunk_dependent, self.panels_dependent, self.blocks_dependent,
                  self.segments_dependent, need) = self._plan_long_rows(db, de, panels, min_row_d, panel_piece_cols)
                 ws_d = max(ws_d, need)
@@ -176,6 +178,18 @@ class LayerStep:
                 st.wait_stream(torch.cuda.current_stream(dev))
         self.event_fork = HipEvent()
         self.event_join = HipEvent()
+
+    def _ranges_to_tile(self, tiled: Optional[bool]):
+        """(overlap, dependent): the ranges that are tiled."""
+        p, n_cols = self.p, self.p.feat.shape[0]
+        ranges = (p.overlap_rows, p.dependent_rows)
+        if not tiled and n_cols * self.feat.stride(0) * 4 < B.SPMM_SEGMENTS_MOST_BYTES:
+            # a range whose received rows stay packed is not tiled
+            counted = ranges[:1] if self.fused_receive else ranges
+            tiled = sum(B.adaqp_spmm_segments_gain(p.rowptr, p.col, b, e, n_cols, self.dim, self.backward)
+                        for b, e in counted) >= B.SPMM_SEGMENTS_MIN_GAIN
+            return tuple(tiled and e > b for b, e in ranges)
+        return tuple(e > b and (tiled or B.adaqp_spmm_tiled_pays(e - b, int(p.rowptr[e] - p.rowptr[b]))) for b, e in ranges)
 
     def _plan_long_rows(self, begin, end, panels, min_row, piece_cols):
         """Tile table, chunk width, panels or blocks and segments of a row range, and the bytes of workspace these take: partial
@@ -197,7 +211,7 @@ class LayerStep:
             segments = B.DeviceSegments(B.adaqp_plan_spmm_segments(p.rowptr, begin, end, bounds, off), self.device)
         if segments:
             B.adaqp_fill_spmm_segments(segments, self.col, self.val)
-        need = max(B.adaqp_spmm_tiled_workspace_bytes(end - begin, dim), B.adaqp_spmm_segments_workspace_bytes(segments, dim)) \
+        need = (B.adaqp_spmm_segments_workspace_bytes(segments, dim) if segments else B.adaqp_spmm_tiled_workspace_bytes(end - begin, dim)) \
             + B.adaqp_spmm_panels_workspace_bytes(with_panels.n_per_tile, dim) \
             + B.adaqp_spmm_blocks_workspace_bytes(with_blocks, dim)
         return (torch.from_numpy(off).to(self.device), B.adaqp_spmm_tiled_chunk_cols(bounds, dim), with_panels, with_blocks,

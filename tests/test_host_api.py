@@ -415,6 +415,39 @@ def test_plan_spmm_segments(n_rows, n_cols):
         B.adaqp_plan_spmm_segments(rowptr, 0, n_rows, bounds, off)
 
 
+@pytest.mark.parametrize("n_rows,n_cols,mean,transposed", [(0, 8, 0, False), (300, 50, 30, False), (3_000, 9_000, 90, False),
+                                                           (3_000, 9_000, 90, True), (400, 5_000, 700, False)])
+def test_spmm_segments_gain(n_rows, n_cols, mean, transposed):
+    """The stated sum of savings and costs; rows that the plan would refuse have no segments and are refused where they were."""
+    rng = np.random.default_rng(mean)
+    degs = np.minimum((rng.pareto(1.2, size=n_rows) * mean / 3).astype(np.int64), n_cols)
+    rowptr = np.concatenate([[0], np.cumsum(degs)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n_cols, size=d, replace=False)) for d in degs] or [[]]).astype(np.int32)
+    for rb, re in ((0, n_rows), (n_rows // 3, n_rows)):
+        got = B.adaqp_spmm_segments_gain(rowptr, col, rb, re, n_cols, 250, transposed)
+        d, lines = degs[rb:re], 8
+        dense = d[d >= max(n_cols // 20, 64)]
+        want = -(0.26 * lines + 0.41) * d.sum() if transposed else \
+            0.56 * lines * (dense.sum() if dense.size >= 256 else 0) - (0.5 * lines + 0.25) * d.sum() - 2.7 * lines * d.size
+        uses = np.sort(np.bincount(col[rowptr[rb]:rowptr[re]], minlength=n_cols))[::-1]
+        best = want + d[d >= 64].sum() * lines
+        if best > 0 or B.adaqp_spmm_tiled_pays(re - rb, int(d.sum())):
+            want += d[d >= 64].sum() * lines * (1 - uses[:4096].sum() / max(uses.sum(), 1))
+        assert got == pytest.approx(want, rel=1e-9, abs=1e-6)
+
+
+def test_spmm_segments_gain_of_unsorted_rows():
+    rowptr = np.array([0, 100, 200], np.int64)
+    col = np.tile(np.arange(100, dtype=np.int32) * 100, 2)
+    col[150] = col[149]                                                # a column twice
+    assert B.adaqp_spmm_segments_gain(rowptr, col, 0, 1, 10_000, 64, True) > -np.inf
+    assert B.adaqp_spmm_segments_gain(rowptr, col, 0, 2, 10_000, 64, True) == -np.inf
+    col = np.tile(np.arange(200, dtype=np.int32), 2)
+    col[250] = 10_000                                                  # outside; 200 entries per row: refused as ever
+    with pytest.raises(B.AdaqpError):
+        B.adaqp_spmm_segments_gain(np.array([0, 200, 400], np.int64), col, 0, 2, 10_000, 64, True)
+
+
 @pytest.mark.parametrize("n_rows,n_cols,min_len", [(1, 1, 1), (40, 33, 5), (130, 900, 60), (300, 2_000, 40)])
 def test_plan_spmm_blocks(n_rows, n_cols, min_len):
     """A block lists exactly the distinct columns of its rows, each in its interval, ascending, steps filled with the last one."""
