@@ -689,10 +689,10 @@ extern "C" int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_
 // What segments save is what the sliced kernel misses in its L2s: entries of rows that are cut up (shorter ones lie whole in one group and
 // find no more there than before), but for those whose columns are the most popular ones.  What they cost is the walk over all
 // entries, and a partial row and its sum per row.  1 370 steps of 5 000 to 300 000 rows, 20 to 500 entries per row, 64 to
-// 602 columns of H, Zipf and log-normal rows, both directions, timed with and without; the weights below put 1 300 on the faster side and
-// lose 16 % at most, 8 % on all but one.  Against segments from a mean of 128 entries per row on: geometric mean 1.055 forward,
-// 1.093 backward (power-law degrees there 0.34-0.75 with segments: a few columns hold most of the entries); against none:
-// 1.116, 1.043 (150 000 rows, 256 columns: 48 entries per row 898 -> 675 us, 100 entries 1 808 -> 1 109 us).
+// 602 columns of H, Zipf and log-normal rows, both directions, timed with and without; with the weights below none loses more than 8 %.
+// Geometric mean against no segments forward 1.117 (the better of both each time 1.120), backward 1.043 (1.049); segments from
+// a mean of 128 entries per row on 1.055 and 0.954 (power-law degrees there 0.34-0.75: a few columns hold most of the
+// entries).  150 000 rows, 256 columns: 48 entries per row 898 -> 675 us, 100 entries 1 808 -> 1 109 us.
 extern "C" int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end, int64_t n_cols,
                                         int32_t dim, int32_t transposed, double *gain_out)
 {
@@ -716,7 +716,9 @@ extern "C" int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_
     const double entries = (double)(last - first), rows = (double)(row_end - row_begin);
     // forward slices are one line, backward ones four: the misses that are left, and their weight, differ
     const double cost = transposed ? (0.26 * lines + 0.41) * entries : (0.5 * lines + 0.25) * entries + 2.7 * lines * rows;
-    const double saved = transposed ? 0.0 : 0.56 * lines * dense;
+    // (the matrix cores' rows cost their coefficients once, however few lines there are: 50 000 rows, 97 entries per row, 64 columns 121 ->
+    // 151 us with segments and blocks; 60 000 rows, 110, 256 columns 525 -> 402)
+    const double saved = transposed ? 0.0 : 0.56 * std::max(lines - 1.5, 0.0) * dense;
     *gain_out = saved - cost;
     const bool asked_for = adaqp_spmm_tiled_pays(row_end - row_begin, last - first) != 0;
     if (!asked_for && cut * lines + *gain_out <= 0.0) return ADAQP_OK;         // whatever the columns are

@@ -428,7 +428,7 @@ def test_spmm_segments_gain(n_rows, n_cols, mean, transposed):
         d, lines = degs[rb:re], 8
         dense = d[d >= max(n_cols // 20, 64)]
         want = -(0.26 * lines + 0.41) * d.sum() if transposed else \
-            0.56 * lines * (dense.sum() if dense.size >= 256 else 0) - (0.5 * lines + 0.25) * d.sum() - 2.7 * lines * d.size
+            0.56 * (lines - 1.5) * (dense.sum() if dense.size >= 256 else 0) - (0.5 * lines + 0.25) * d.sum() - 2.7 * lines * d.size
         uses = np.sort(np.bincount(col[rowptr[rb]:rowptr[re]], minlength=n_cols))[::-1]
         best = want + d[d >= 64].sum() * lines
         if best > 0 or B.adaqp_spmm_tiled_pays(re - rb, int(d.sum())):
