@@ -28,7 +28,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0
 GATHER_RATE_GBPS = 25000.0      # 16-byte-per-lane gather out of L2, every XCD on its own 4 MB: measured on MI355X
-MFMA_FP32_PEAK_TFLOPS = 157.3   # dense fp32 on the matrix cores
+MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16 on the matrix cores
 FMA_RATE_PER_S = 78.65e12       # fp32 vector FMAs per second (157.3 TFLOP/s)
 METRIC = "quantize+pack / unpack+dequant GB/s, halo SpMM edges/s, % HBM peak, 1xMI355X"
 OTHER_CONFIGS = ("c2", "c3", "c4")
@@ -45,13 +45,13 @@ def parse_args():
     ap.add_argument("--schedule", default=None, choices=["serial", "isolated", "free", "chain"],
                     help="schedule of the timed steps.  Default: what LayerStep.run() takes.  On workload c1 that is "
                          "isolated (Fig. 7: the central rows start on the second stream once quantisation is done), "
-                         "which pairs a panel kernel with a tiled kernel on the two streams; elsewhere (no tiles, no "
+                         "which pairs the kernel of the dense blocks with the other rows' on the two streams; elsewhere (no tiles, no "
                          "transfer to hide on one GPU) chain: one stream, one aggregation launch.  The figures under `kernels` are always timed one "
                          "launch at a time")
     ap.add_argument("--kernel-reps", type=int, default=20, help="launches per kernel in the breakdown")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-panels", action="store_true",
-                    help="keep the longest rows in the L2-tiled kernel instead of dense panels on the matrix cores")
+                    help="keep the longest rows with the others instead of dense blocks on the matrix cores")
     ap.add_argument("--no-tiled", action="store_true",
                     help="aggregate with adaqp_spmm_csr (sliced or merge-path kernel) even where the L2-tiled kernel would be chosen")
     ap.add_argument("--calibrate", action="store_true",
@@ -205,7 +205,7 @@ def measure_config(name, args, headline, B, torch, np):
     t_plan = time.perf_counter() - t0
     schedule = args.schedule if headline else None
     pairs = (not cfg.backward and L.tile_off_overlap is not None and L.tile_off_dependent is not None
-             and bool(L.panels_overlap or L.panels_dependent))
+             and bool(L.blocks_overlap or L.blocks_dependent))
     sched = {"serial": B.SERIAL, "isolated": B.ISOLATED, "free": B.FREE, "chain": B.CHAIN}
     if schedule is None:
         schedule = {v: k for k, v in sched.items()}[L.default_schedule()]
@@ -228,8 +228,8 @@ def measure_config(name, args, headline, B, torch, np):
     for s_name, s in sched.items():
         by_schedule[s_name] = ms_per_step if s_name == schedule else timed_steps(s, max(3, args.steps // 4), 1)
     # a two-stream schedule that does not beat the serial one has lost its overlap (the two streams share a hardware
-    # queue): say so instead of printing the serial time under its name.  Only where the step pairs the panel and
-    # the tiled kernel (14 % to win); elsewhere there is no transfer to hide on one GPU
+    # queue): say so instead of printing the serial time under its name.  Only where the step pairs the blocks with
+    # the other rows; elsewhere there is no transfer to hide on one GPU
     overlap_lost = pairs and schedule in ("isolated", "free") and ms_per_step > 0.97 * by_schedule["serial"]
 
     fused = None
@@ -391,23 +391,29 @@ def measure_config(name, args, headline, B, torch, np):
 
     (ob, oe), (db_, de) = p.overlap_rows, p.dependent_rows
 
-    # the same launches the step makes: tiled over the L2 caches where LayerStep planned tiles, else along the merge path
+    # the same launches the step makes: segments (or tiles) and dense blocks where LayerStep planned them, else the untiled kernels
+    def other_rows(segments, tile_off, chunk, rb, re, ws):
+        if segments:
+            B.adaqp_spmm_csr_segments(segments, rb, L.feat, dim, L.out, ws, stream=st)
+        else:
+            B.adaqp_spmm_csr_tiled(L.rowptr, L.col, L.val, rb, re, L.feat, dim, L.out, tile_off, ws, chunk_cols=chunk, stream=st)
+
+    def tiled_range(blocks, segments, tile_off, chunk, rb, re, ws):
+        other_rows(segments, tile_off, chunk, rb, re, ws)
+        if blocks:
+            B.adaqp_spmm_csr_blocks(blocks, rb, re, L.feat, dim, L.out, ws, stream=st)
+
     def spmm_overlap(i):
         if L.tile_off_overlap is not None:
-            B.adaqp_spmm_csr_tiled(L.rowptr, L.col, L.val, ob, oe, L.feat, dim, L.out, L.tile_off_overlap,
-                                   L.ws_overlap, chunk_cols=L.tile_chunk_overlap, stream=st)
-            if L.panels_overlap:
-                B.adaqp_spmm_csr_panels(L.panels_overlap, ob, oe, L.feat, dim, L.out, L.ws_overlap, stream=st)
+            tiled_range(L.blocks_overlap, L.segments_overlap, L.tile_off_overlap, L.tile_chunk_overlap, ob, oe, L.ws_overlap)
         else:
             B.adaqp_spmm_csr(L.rowptr, L.col, L.val, ob, oe, L.feat, dim, L.out, L.ws_overlap,
                              nnz_range=L.overlap_nnz, stream=st)
 
     def spmm_dependent(i):
         if L.tile_off_dependent is not None:
-            B.adaqp_spmm_csr_tiled(L.rowptr, L.col, L.val, db_, de, L.feat, dim, L.out, L.tile_off_dependent,
-                                   L.ws_dependent, chunk_cols=L.tile_chunk_dependent, stream=st)
-            if L.panels_dependent:
-                B.adaqp_spmm_csr_panels(L.panels_dependent, db_, de, L.feat, dim, L.out, L.ws_dependent, stream=st)
+            tiled_range(L.blocks_dependent, L.segments_dependent, L.tile_off_dependent, L.tile_chunk_dependent, db_, de,
+                        L.ws_dependent)
         else:
             B.adaqp_spmm_csr(L.rowptr, L.col, L.val, db_, de, L.feat, dim, L.out, L.ws_dependent,
                              nnz_range=L.dependent_nnz, stream=st)
@@ -429,48 +435,40 @@ def measure_config(name, args, headline, B, torch, np):
                          "GBps_primary": b_o / t_o / 1e6, "pct_hbm_primary": 100 * b_o / t_o / 1e6 / HBM_PEAK_GBPS}
     kernels[names[1]] = {"ms": t_d, "edges": L.dependent_nnz, "edges_per_s": L.dependent_nnz / t_d * 1e3,
                          "GBps_primary": b_d / t_d / 1e6, "pct_hbm_primary": 100 * b_d / t_d / 1e6 / HBM_PEAK_GBPS}
-    # where panels take the longest rows: the two kernels of each range on their own
+    # where dense blocks take the longest rows: the two kernels of each range on their own
     deg = np.diff(p.rowptr)
-    panel_parts = {}
-    panel_table_bytes = 0
-    for tag, pan, rb, re, ws, off_dev, chunk in (
-            (names[0], L.panels_overlap, ob, oe, L.ws_overlap, L.tile_off_overlap, L.tile_chunk_overlap),
-            (names[1], L.panels_dependent, db_, de, L.ws_dependent, L.tile_off_dependent, L.tile_chunk_dependent)):
-        if not pan:
+    block_parts = {}
+    block_table_bytes = 0
+    for tag, blk, seg, rb, re, ws, off_dev, chunk in (
+            (names[0], L.blocks_overlap, L.segments_overlap, ob, oe, L.ws_overlap, L.tile_off_overlap, L.tile_chunk_overlap),
+            (names[1], L.blocks_dependent, L.segments_dependent, db_, de, L.ws_dependent, L.tile_off_dependent,
+             L.tile_chunk_dependent)):
+        if not blk:
             continue
-        panel_table_bytes += sum(int(t_.numel() * t_.element_size()) for t_ in pan.tensors.values())
-        rows_p = pan.tensors["panel_rows"].cpu().numpy()
+        block_table_bytes += sum(int(t_.numel() * t_.element_size()) for t_ in blk.tensors.values())
+        rows_p = blk.tensors["rows"].cpu().numpy()
         rows_p = rows_p[rows_p >= 0]
-        t_p = event_time_ms(st, lambda i: B.adaqp_spmm_csr_panels(pan, rb, re, L.feat, dim, L.out, ws, stream=st), sreps)
-        t_t = event_time_ms(st, lambda i: B.adaqp_spmm_csr_tiled(L.rowptr, L.col, L.val, rb, re, L.feat, dim, L.out,
-                                                                 off_dev, ws, chunk_cols=chunk, stream=st), sreps)
+        t_p = event_time_ms(st, lambda i: B.adaqp_spmm_csr_blocks(blk, rb, re, L.feat, dim, L.out, ws, stream=st), sreps)
+        t_t = event_time_ms(st, lambda i: other_rows(seg, off_dev, chunk, rb, re, ws), sreps)
         wdim = (dim + 31) // 32 * 32            # the kernel multiplies whole tiles of 32 feature columns
-        panel_parts[tag] = {"panel_rows": int(rows_p.size), "panel_edges": int(deg[rows_p].sum()),
-                            "panels": int(pan.c.n_panels), "panel_columns_padded": int(pan.c.n_groups) * 8,
-                            "ms_panels": t_p, "ms_tiled_other_rows": t_t,
-                            "mfma_flops_executed": 2.0 * 32 * int(pan.c.n_groups) * 8 * wdim}
-        kernels[tag]["panels"] = panel_parts[tag]
+        columns = int(blk.c.n_steps) * B.SPMM_BLOCK_STEP
+        block_parts[tag] = {"block_rows": int(rows_p.size), "block_edges": int(deg[rows_p].sum()),
+                            "blocks": int(blk.c.n_blocks), "block_columns_padded": columns,
+                            "ms_blocks": t_p, "ms_other_rows": t_t,
+                            "mfma_flops_executed": 6 * 2.0 * B.SPMM_BLOCK_ROWS * columns * wdim}
+        kernels[tag]["blocks"] = block_parts[tag]
     tiled = L.tile_off_overlap is not None or L.tile_off_dependent is not None
     if headline:
         # the whole row range in one launch (what a step without the central / marginal split would run)
         all_rows = p.n_rows
         if tiled_both:
-            bounds_all, off_all = B.adaqp_plan_spmm_tiles(p.rowptr, p.col, 0, all_rows, p.feat.shape[0])
-            panels_all = B.DevicePanels(None)
-            if not args.no_panels:
-                panels_all = B.DevicePanels(B.adaqp_plan_spmm_panels(p.rowptr, p.col, p.val, 0, all_rows,
-                                                                     p.feat.shape[0], bounds_all, off_all), dev)
-            off_all_dev = torch.from_numpy(off_all).to(dev)
-            chunk_all = B.adaqp_spmm_tiled_chunk_cols(bounds_all, dim)
-            ws_all = torch.empty(max(B.adaqp_spmm_tiled_workspace_bytes(all_rows, dim),
-                                     B.adaqp_spmm_panels_workspace_bytes(panels_all.n_per_tile, dim)),
-                                 dtype=torch.uint8, device=dev)
+            off_all, chunk_all, _, blocks_all, segments_all, need_all = L._plan_long_rows(
+                0, all_rows, False if args.no_panels else None, B.SPMM_PANEL_MIN_ROW, B.SPMM_PANEL_PIECE_COLS)
+            ws_all = torch.empty(max(need_all, 256), dtype=torch.uint8, device=dev)
+            torch.cuda.synchronize()
 
             def spmm_all(i):
-                B.adaqp_spmm_csr_tiled(L.rowptr, L.col, L.val, 0, all_rows, L.feat, dim, L.out, off_all_dev, ws_all,
-                                       chunk_cols=chunk_all, stream=st)
-                if panels_all:
-                    B.adaqp_spmm_csr_panels(panels_all, 0, all_rows, L.feat, dim, L.out, ws_all, stream=st)
+                tiled_range(blocks_all, segments_all, off_all, chunk_all, 0, all_rows, ws_all)
         else:
             ws_all = torch.empty(max(B.adaqp_spmm_workspace_bytes(all_rows, p.nnz, dim), 256), dtype=torch.uint8,
                                  device=dev)
@@ -480,7 +478,7 @@ def measure_config(name, args, headline, B, torch, np):
                                  stream=st)
         t_all = event_time_ms(st, spmm_all, sreps)
         kernels["spmm_all_rows_one_launch"] = {"ms": t_all, "edges": p.nnz, "edges_per_s": p.nnz / t_all * 1e3,
-                                               "kernel": ("tiled + panels" if panel_parts else "tiled") if tiled_both
+                                               "kernel": ("segments + blocks" if block_parts else "segments") if tiled_both
                                                else "untiled"}
         del ws_all
         if tiled:
@@ -510,39 +508,37 @@ def measure_config(name, args, headline, B, torch, np):
                 "gather_rate_GBps": GATHER_RATE_GBPS, "fma_rate_per_s": FMA_RATE_PER_S,
                 "t_ceiling_ms": t_ceiling, "t_ceiling_over_t": t_ceiling / t_both}
     primary_gbps = (b_o + b_d) / t_both / 1e6
-    if panel_parts:
-        # most of the step's time is in the panel kernel: a dense product on the fp32 matrix cores
-        t_p = sum(v["ms_panels"] for v in panel_parts.values())
-        launches = len(panel_parts)
-        executed = sum(v["mfma_flops_executed"] for v in panel_parts.values())
-        useful = sum(2.0 * v["panel_edges"] * dim for v in panel_parts.values())
-        fetched = sum(v["panel_columns_padded"] for v in panel_parts.values()) + \
-            p.nnz - sum(v["panel_edges"] for v in panel_parts.values())
-        ceilings["with_panels"] = {
+    if block_parts:
+        # the largest kernel of the step is the one of the dense blocks: a product on the bf16 matrix cores, fp32 operands in three
+        t_p = sum(v["ms_blocks"] for v in block_parts.values())
+        launches = len(block_parts)
+        executed = sum(v["mfma_flops_executed"] for v in block_parts.values())
+        useful = sum(2.0 * v["block_edges"] * dim for v in block_parts.values())
+        fetched = sum(v["block_columns_padded"] for v in block_parts.values()) + \
+            p.nnz - sum(v["block_edges"] for v in block_parts.values())
+        ceilings["with_blocks"] = {
             "neighbour_rows_fetched": fetched, "t_gather_ms": fetched * 4 * dim / GATHER_RATE_GBPS / 1e6,
-            "t_mfma_executed_ms": executed / MFMA_FP32_PEAK_TFLOPS / 1e9,
-            "note": "floors of the panel + tiled pair: its gather at the L2 rate, its matrix-core work at the "
-                    "fp32 MFMA peak; the two overlap at best"}
+            "t_mfma_executed_ms": executed / MFMA_BF16_PEAK_TFLOPS / 1e9,
+            "note": "floors of the two kernels: the gather at the L2 rate, the matrix-core work at the bf16 MFMA peak"}
         roofline = {
-            "kernel": "spmm_panel_kernel", "bound": "mfma", "dtype": "f32",
-            "achieved": useful / t_p / 1e9, "peak": MFMA_FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-            "frac": useful / t_p / 1e9 / MFMA_FP32_PEAK_TFLOPS, "traffic": None,
+            "kernel": "spmm_block_kernel", "bound": "mfma", "dtype": "bf16",
+            "achieved": executed / t_p / 1e9, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
+            "frac": executed / t_p / 1e9 / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
             "launches_per_step": launches, "avg_launch_ms": t_p / launches,
             "algorithmic_flops_per_launch": useful / launches,
-            "executed": {"TFLOPs": executed / t_p / 1e9, "frac": executed / t_p / 1e9 / MFMA_FP32_PEAK_TFLOPS,
-                         "panel_density": sum(v["panel_edges"] for v in panel_parts.values())
-                         / (32.0 * sum(v["panel_columns_padded"] for v in panel_parts.values())),
-                         "note": "counts the zeros of the dense panels and the padding of dim to whole tiles of 32 columns"},
-            "binding_limit": "the fp32 matrix cores and the gather that feeds them: each neighbour row is fetched once "
-                             "per 32-row panel (out of the XCD's L2) and multiplied with the panel's dense "
-                             "coefficient table; `frac` counts the method's own multiply-adds (2 * entries * dim)"}
+            "useful": {"TFLOPs": useful / t_p / 1e9,
+                       "block_density": sum(v["block_edges"] for v in block_parts.values())
+                       / (float(B.SPMM_BLOCK_ROWS) * sum(v["block_columns_padded"] for v in block_parts.values())),
+                       "note": "2 * entries * dim"},
+            "binding_limit": "the bf16 matrix cores beside the vector instructions that split fp32 operands in three; "
+                             "`achieved` counts the six bf16 products of every fp32 one, the zeros of the dense blocks and the "
+                             "padding of dim to whole tiles of 32 columns"}
     else:
         alg = (b_o + b_d) / launches
         avg_ms = t_both / launches
         frac_hbm = primary_gbps / HBM_PEAK_GBPS
         roofline = {
-            "kernel": "spmm_tiled_kernel" if tiled else                                 # few entries: along the merge path
-            "spmm_sliced_kernel" if p.nnz >= 100_000 else "spmm_merge_kernel",
+            "kernel": "spmm_sliced_kernel" if tiled or p.nnz >= 100_000 else "spmm_merge_kernel",
             "bound": "hbm" if frac_hbm <= 1.0 else "l2",
             "achieved": primary_gbps, "peak": HBM_PEAK_GBPS if frac_hbm <= 1.0 else GATHER_RATE_GBPS, "unit": "GB/s",
             "frac": frac_hbm if frac_hbm <= 1.0 else primary_gbps / GATHER_RATE_GBPS, "traffic": None,
@@ -575,9 +571,9 @@ def measure_config(name, args, headline, B, torch, np):
                    "schedule": schedule, "seed": cfg.seed},
         "ms_per_step_by_schedule": by_schedule, "overlap_lost": bool(overlap_lost),
         "kernels": kernels, "roofline": roofline,
-        "setup_s": {"generate": t_gen, "upload_and_plan": t_plan, "panel_table_bytes": panel_table_bytes,
+        "setup_s": {"generate": t_gen, "upload_and_plan": t_plan, "block_table_bytes": block_table_bytes,
                     "note": "upload_and_plan: device copies, buffer layout, and (long-row graphs) the tile table and "
-                            "the dense panels, once per graph"},
+                            "the dense blocks, once per graph"},
     }
     if ms_graph is not None:
         rec["ms_per_step_graph_replay"] = ms_graph
@@ -592,7 +588,7 @@ def measure_config(name, args, headline, B, torch, np):
 
 def degree_law_check(args, B, torch, np):
     """c1's sizes with a milder degree law (log-normal instead of Zipf(1.5)): what the library's rules choose there
-    (tiles, panels) and what the other choices would cost.  Not one of the metric's workloads."""
+    (tiles, blocks) and what the other choices would cost.  Not one of the metric's workloads."""
     from paper_2306_01381_amd.layer import LayerStep
     from paper_2306_01381_amd.synth import config_by_name, make_partition
     cfg = config_by_name("c1m")
@@ -601,12 +597,12 @@ def degree_law_check(args, B, torch, np):
     out = {"workload": f"{cfg.name}: {cfg.stands_in_for}", "nnz": p.nnz, "max_row": int(deg.max()),
            "rows_at_or_above_panel_threshold": int(np.count_nonzero(deg >= B.SPMM_PANEL_MIN_ROW)), "ms_per_step": {}}
     steps = max(3, args.steps // 2)
-    for tag, kw in (("library_rules", {}), ("panels_forced", {"panels": True}), ("tiled_without_panels", {"panels": False}),
+    for tag, kw in (("library_rules", {}), ("panels_forced", {"panels": True}), ("tiled_without_blocks", {"panels": False}),
                     ("untiled", {"tiled": False})):
         L = LayerStep(p, "cuda:0", seed=2306, streams=_STREAMS.get("pair"), **kw)
         _STREAMS["pair"] = (L.stream_msg, L.stream_agg)
         paired = L.tile_off_overlap is not None and L.tile_off_dependent is not None and \
-            bool(L.panels_overlap or L.panels_dependent)
+            bool(L.blocks_overlap or L.blocks_dependent or L.panels_overlap or L.panels_dependent)
         untiled = L.tile_off_overlap is None and L.tile_off_dependent is None
         desc = L.desc(B.ISOLATED if paired else (L.default_schedule() if untiled else B.SERIAL))
         for _ in range(2):
@@ -619,7 +615,7 @@ def degree_law_check(args, B, torch, np):
         out["ms_per_step"][tag] = (time.perf_counter() - t) * 1e3 / steps
         if tag == "library_rules":
             out["library_rules_chose"] = {"tiled": L.tile_off_overlap is not None,
-                                          "panels": int(L.panels_overlap.c.n_panels + L.panels_dependent.c.n_panels)}
+                                          "blocks": int(L.blocks_overlap.c.n_blocks + L.blocks_dependent.c.n_blocks)}
         del L
         torch.cuda.empty_cache()
     best = min(out["ms_per_step"].values())
