@@ -223,19 +223,32 @@ class LayerStep:
                             (self.blocks_dependent, self.segments_dependent, self.p.dependent_rows)) if c[0] or c[1]]
 
     def _coefficients(self):
-        """val and how often it was written to (-1: a tensor made in inference mode, which does not count that)."""
-        return self.val, -1 if self.val.is_inference() else self.val._version
+        """val and how often it was written to (None: a tensor made in inference mode, which does not count that)."""
+        return self.val, None if self.val.is_inference() else self.val._version
 
-    def _refresh_copies(self) -> None:
-        """A caller may write new coefficients into val between steps: the copies follow, in the order of stream_msg, as the
-        step itself.  A captured step follows what was in val when it was captured."""
+    def refresh_coefficients(self) -> None:
+        """Blocks and segments keep val a second time.  Queues a copy of what is in val on stream_msg, which every step starts
+        from.  run() and desc() call it when val was written to or replaced; a caller does after writes that torch does
+        not count (through val.data or from a kernel of its own), with a descriptor kept across writes, and inside a
+        capture whose replays are to follow val."""
         for blocks, segments, (begin, end) in self._copies():
             if blocks:
                 B.adaqp_fill_spmm_blocks(blocks, begin, end, self.rowptr, self.col, self.val, self.stream_msg)
             if segments:
                 B.adaqp_fill_spmm_segments(segments, self.col, self.val, self.stream_msg)
-            self.stream_agg.wait_stream(self.stream_msg)
-        self._copied = self._coefficients()
+
+    def _follow_coefficients(self) -> None:
+        tensor, version = self._coefficients()
+        if tensor is self._copied[0] and version is not None and version == self._copied[1]:
+            return
+        if not self._copies():
+            return
+        self.refresh_coefficients()
+        # in a capture they have not been made yet
+        with torch.cuda.stream(self.stream_msg):
+            captured = torch.cuda.is_current_stream_capturing()
+        if not captured:
+            self._copied = tensor, version
 
     def set_fused_receive(self, on: bool) -> None:
         """Forward only.  On: received rows are not de-quantised into feat; the dependent aggregation reads
@@ -246,6 +259,7 @@ class LayerStep:
                 B.adaqp_plan_slot_of_row(self.p.feat.shape[0], self.plan.halo_idx_host)).to(self.device)
 
     def desc(self, schedule: int) -> B.LayerDesc:
+        self._follow_coefficients()
         p, pl = self.p, self.plan
         d = B.LayerDesc()
         d.direction = B.BACKWARD if self.backward else B.FORWARD
@@ -303,9 +317,6 @@ class LayerStep:
         """Enqueues one layer step; synchronise stream_msg to wait for it.  Without a schedule the step takes the one of
         default_schedule(): work that a caller queues on stream_agg itself is ordered with such a step through stream_msg
         only.  A schedule that is given is kept."""
-        tensor, version = self._coefficients()
-        if tensor is not self._copied[0] or version != self._copied[1]:
-            self._refresh_copies()
         B.adaqp_layer_step(self.desc(self.default_schedule() if schedule is None else schedule))
 
     def synchronize(self) -> None:

@@ -1129,11 +1129,52 @@ def test_layer_step_follows_new_coefficients():
     L.run()
     L.synchronize()
     assert torch.equal(L.out, before)
+    L.val.data.mul_(2.0)                                               # not counted
+    torch.cuda.synchronize()
+    L.refresh_coefficients()
+    L.run()
+    L.synchronize()
+    assert torch.equal(L.out, before * 2.0)
+    L.val.mul_(0.5)
+    torch.cuda.synchronize()
+    B.adaqp_layer_step(L.desc(B.ISOLATED))                             # a descriptor
+    L.synchronize()
+    assert torch.equal(L.out, before)
     with torch.inference_mode():                                       # such a tensor does not count its changes
         L = LayerStep(p, DEV, seed=5, tiled=True)
-        L.run()
-        L.synchronize()
-        assert torch.equal(L.out, before)
+        for factor in (1.0, 2.0):
+            L.val.mul_(factor)
+            torch.cuda.synchronize()
+            L.run()
+            L.synchronize()
+            assert torch.equal(L.out, before * factor)
+
+
+@pytest.mark.parametrize("schedule", [B.CHAIN, B.ISOLATED])
+def test_captured_step_and_new_coefficients(schedule):
+    """Copies made inside a capture are made by its replays: an eager step does not count on them."""
+    _say(f"captured step, new coefficients, schedule {schedule}")
+    p = make_partition(replace(CONFIGS["c0"], mean_degree=1500.0))
+    L = LayerStep(p, DEV, seed=5, tiled=True)
+    assert L.blocks_overlap and L.segments_overlap
+    L.run(schedule)
+    L.synchronize()
+    before = L.out.clone()
+    L.val.mul_(2.0)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=L.stream_msg):
+        L.run(schedule)
+    L.run(schedule)                                                    # before any replay
+    L.synchronize()
+    assert torch.equal(L.out, before * 2.0)
+    for factor in (4.0, 2.0, 1.0):
+        L.val.copy_(torch.from_numpy(p.val).to(DEV) * factor)
+        L.out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(L.out, before * factor)
 
 
 @pytest.mark.parametrize("name", ["c0", "c0_backward"])
