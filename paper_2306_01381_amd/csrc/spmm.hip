@@ -700,6 +700,7 @@ extern "C" int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_
     constexpr int64_t kPopular = 4096;          // columns that stay in an L2 beside everything else
     constexpr int64_t kSample = 1 << 22;        // entries looked at for that
     const int64_t first = rowptr_host[row_begin], last = rowptr_host[row_end], block_row = adaqp_spmm_blocks_min_row(n_cols);
+    if (first < 0 || last < first) return ADAQP_EINVAL;
     const double lines = (double)(((int64_t)dim + 31) / 32);
     double cut = 0.0, dense = 0.0;              // entries of rows that are cut up, of rows for the matrix cores
     int64_t n_dense = 0;
@@ -721,8 +722,8 @@ extern "C" int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_
     const double saved = transposed ? 0.0 : 0.56 * std::max(lines - 1.5, 0.0) * dense;
     *gain_out = saved - cost;
     const bool asked_for = adaqp_spmm_tiled_pays(row_end - row_begin, last - first) != 0;
-    if (!asked_for && cut * lines + *gain_out <= 0.0) return ADAQP_OK;         // whatever the columns are
-    if (!col_host) return ADAQP_EINVAL;
+    if (last > first && !col_host) return ADAQP_EINVAL;
+    // every range, also one that cannot gain: it would be tiled with the other ranges of its step
     for (int64_t r = row_begin; r < row_end; ++r) {
         int32_t before = -1;
         for (int64_t j = rowptr_host[r]; j < rowptr_host[r + 1]; ++j) {
@@ -734,6 +735,7 @@ extern "C" int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_
             before = c;
         }
     }
+    if (!asked_for && cut * lines + *gain_out <= 0.0) return ADAQP_OK;         // whatever the columns are
     std::vector<int32_t> uses((size_t)n_cols, 0);
     const int64_t stride = std::max<int64_t>((last - first) / kSample, 1);
     int64_t seen = 0;

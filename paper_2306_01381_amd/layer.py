@@ -121,6 +121,7 @@ class LayerStep:
         n = self.plan.n
         # forward, fused receive: the dependent aggregation reads received rows straight from the receive buffer
         self.slot_of_row = None
+        self._unplanned_dependent = None
         self.set_fused_receive(self.fused_receive)
         nbytes = max(self.plan.packed_bytes, 4)
         self.packed = torch.zeros(nbytes, dtype=torch.uint8, device=dev)
@@ -156,15 +157,19 @@ class LayerStep:
         if oe == db:        # CHAIN aggregates both ranges in one launch, if this workspace can take them
             ws_o = max(ws_o, B.adaqp_spmm_workspace_bytes(de - ob, self.overlap_nnz + self.dependent_nnz, cfg.dim))
         if pad and tiled is not False:
-            tile_overlap, tile_dependent = self._ranges_to_tile(tiled)
+            plan_dependent = (panels, min_row_d, panel_piece_cols)
+            if self.fused_receive:
+                # tiles do not read received rows that stay packed: planned when they are to be de-quantised first
+                tile_overlap, tile_dependent = self._ranges_to_tile(tiled, p.overlap_rows)[0], False
+                self._unplanned_dependent = (tiled, *plan_dependent)
+            else:
+                tile_overlap, tile_dependent = self._ranges_to_tile(tiled, p.overlap_rows, p.dependent_rows)
             if tile_overlap:
                 (self.tile_off_overlap, self.tile_chunk_overlap, self.panels_overlap, self.blocks_overlap, self.segments_overlap,
                  need) = self._plan_long_rows(ob, oe, panels, min_row_o, panel_piece_cols)
                 ws_o = max(ws_o, need)
             if tile_dependent:
-                (self.tile_off_dependent, self.tile_chunk_dependent, self.panels_dependent, self.blocks_dependent,
-                 self.segments_dependent, need) = self._plan_long_rows(db, de, panels, min_row_d, panel_piece_cols)
-                ws_d = max(ws_d, need)
+                ws_d = max(ws_d, self._plan_dependent(*plan_dependent))
         self.ws_overlap = torch.empty(max(ws_o, 256), dtype=torch.uint8, device=dev)
         self.ws_dependent = torch.empty(max(ws_d, 256), dtype=torch.uint8, device=dev)
         # streams=(msg, agg): take over an existing pair.  HIP deals streams to a few hardware queues in turn, so a
@@ -173,22 +178,25 @@ class LayerStep:
                                                                                   torch.cuda.Stream(device=dev))
         # the tables of blocks and segments hold the coefficients a second time; kernels write them
         self._copied = self._coefficients()
-        for st in (self.stream_msg, self.stream_agg):
-            if self._copies():
-                st.wait_stream(torch.cuda.current_stream(dev))
+        self._order_copies()
         self.event_fork = HipEvent()
         self.event_join = HipEvent()
 
-    def _ranges_to_tile(self, tiled: Optional[bool]):
-        """(overlap, dependent): the ranges that are tiled."""
+    def _order_copies(self) -> None:
+        """What was just planned is used on the step's streams."""
+        for st in (self.stream_msg, self.stream_agg):
+            if self._copies():
+                st.wait_stream(torch.cuda.current_stream(self.device))
+
+    def _ranges_to_tile(self, tiled: Optional[bool], *ranges):
+        """Which of the row ranges of a step are tiled."""
         p, n_cols = self.p, self.p.feat.shape[0]
-        ranges = (p.overlap_rows, p.dependent_rows)
         if not tiled and n_cols * self.feat.stride(0) * 4 < B.SPMM_SEGMENTS_MOST_BYTES:
-            # a range whose received rows stay packed is not tiled
-            counted = ranges[:1] if self.fused_receive else ranges
-            tiled = sum(B.adaqp_spmm_segments_gain(p.rowptr, p.col, b, e, n_cols, self.dim, self.backward)
-                        for b, e in counted) >= B.SPMM_SEGMENTS_MIN_GAIN
-            return tuple(tiled and e > b for b, e in ranges)
+            # (a range whose rows do not list ascending, distinct columns has a gain of -infinity and stays as it is)
+            gains = [B.adaqp_spmm_segments_gain(p.rowptr, p.col, b, e, n_cols, self.dim, self.backward) if e > b else -np.inf
+                     for b, e in ranges]
+            pays = sum(g for g in gains if g > -np.inf) >= B.SPMM_SEGMENTS_MIN_GAIN
+            return tuple(pays and g > -np.inf for g in gains)
         return tuple(e > b and (tiled or B.adaqp_spmm_tiled_pays(e - b, int(p.rowptr[e] - p.rowptr[b]))) for b, e in ranges)
 
     def _plan_long_rows(self, begin, end, panels, min_row, piece_cols):
@@ -216,6 +224,12 @@ class LayerStep:
             + B.adaqp_spmm_blocks_workspace_bytes(with_blocks, dim)
         return (torch.from_numpy(off).to(self.device), B.adaqp_spmm_tiled_chunk_cols(bounds, dim), with_panels, with_blocks,
                 segments, need)
+
+    def _plan_dependent(self, panels, min_row, piece_cols) -> int:
+        """Tiles the dependent rows; the bytes of workspace that takes."""
+        (self.tile_off_dependent, self.tile_chunk_dependent, self.panels_dependent, self.blocks_dependent,
+         self.segments_dependent, need) = self._plan_long_rows(*self.p.dependent_rows, panels, min_row, piece_cols)
+        return need
 
     def _copies(self):
         """(blocks, segments, row range) of the ranges that have them."""
@@ -252,11 +266,20 @@ class LayerStep:
 
     def set_fused_receive(self, on: bool) -> None:
         """Forward only.  On: received rows are not de-quantised into feat; the dependent aggregation reads
-        them from the receive buffer."""
+        them from the receive buffer.  Off, in a step that was made with it on: plans the tiles of the dependent rows."""
         self.fused_receive = bool(on) and not self.backward and self.plan.halo_idx_host is not None
         if self.fused_receive and self.slot_of_row is None:
             self.slot_of_row = torch.from_numpy(
                 B.adaqp_plan_slot_of_row(self.p.feat.shape[0], self.plan.halo_idx_host)).to(self.device)
+        if not self.fused_receive and self._unplanned_dependent is not None:
+            tiled, *how = self._unplanned_dependent
+            self._unplanned_dependent = None
+            if self._ranges_to_tile(tiled, self.p.dependent_rows)[0]:
+                need = self._plan_dependent(*how)
+                if need > self.ws_dependent.numel():                # descriptors that were taken before name the former one
+                    self._former_workspace = self.ws_dependent
+                    self.ws_dependent = torch.empty(need, dtype=torch.uint8, device=self.device)
+                self._order_copies()
 
     def desc(self, schedule: int) -> B.LayerDesc:
         self._follow_coefficients()

@@ -1288,6 +1288,51 @@ def test_layer_step_fused_receive_with_a_tiled_range(oracle):
         assert np.array_equal(out.view(np.uint32), want.view(np.uint32)), f"schedule {schedule}"
 
 
+@pytest.mark.parametrize("fused", [False, True])
+def test_layer_step_with_a_range_of_unsorted_rows(oracle, fused):
+    """Long rows whose range is tiled beside short ones that list their columns in no order, which tiles cannot take: the step of
+    all rows, also after the receive that it was made for is switched."""
+    _say(f"layer step, unsorted rows, fused {fused}")
+    p = make_partition(replace(CONFIGS["c0"], n_local=24_000, n_halo=5_000, n_send=4_000, dim=256))
+    b, e = p.dependent_rows
+    rng = np.random.default_rng(11)
+    long_rows = np.sort((np.arange(110) * 218 + rng.integers(0, 24_000, size=(b, 1))) % 24_000, axis=1)
+    short_rows = np.stack([np.full(e - b, 28_000), np.arange(e - b), 24_000 + np.arange(e - b)], axis=1)
+    col = np.concatenate([long_rows.reshape(-1), short_rows.reshape(-1)]).astype(np.int32)
+    p = replace(p, rowptr=np.concatenate([[0], np.cumsum(np.repeat([110, 3], [b, e - b]))]).astype(np.int64), col=col,
+                val=rng.standard_normal(col.size).astype(np.float32))
+    _, _, _, out64, mag = _oracle_layer(oracle, p, 9)
+    L = LayerStep(p, DEV, seed=9, fused_receive=fused)
+    assert L.segments_overlap and L.tile_off_dependent is None
+    for fused_now in (fused, not fused, fused):
+        L.set_fused_receive(fused_now)
+        L.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        L.run()
+        L.synchronize()
+        assert np.all(np.abs(L.out.cpu().numpy().astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
+    with pytest.raises(B.AdaqpError):                                  # tiles that are asked for are refused as ever
+        LayerStep(p, DEV, seed=9, tiled=True)
+
+
+def test_layer_step_made_with_fused_receive_plans_tiles_when_it_is_switched_off(oracle):
+    """Nothing reads tiles of received rows that stay packed: they are planned when these rows are to be de-quantised first."""
+    _say("layer step, tiles after fused receive")
+    p = make_partition(CONFIGS["c0"])
+    _, _, _, out64, mag = _oracle_layer(oracle, p, 9)
+    L = LayerStep(p, DEV, seed=9, fused_receive=True, tiled=True)
+    assert L.segments_overlap and L.tile_off_dependent is None and not L.segments_dependent
+    fused = L.desc(B.ISOLATED)
+    L.set_fused_receive(False)
+    assert L.tile_off_dependent is not None and L.segments_dependent
+    for d in (L.desc(B.ISOLATED), fused, L.desc(B.CHAIN)):
+        L.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        B.adaqp_layer_step(d)
+        L.synchronize()
+        assert np.all(np.abs(L.out.cpu().numpy().astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
+
+
 def _c0_partition(name):
     if name == "c0":
         return make_partition(CONFIGS["c0"])

@@ -448,6 +448,26 @@ def test_spmm_segments_gain_of_unsorted_rows():
         B.adaqp_spmm_segments_gain(np.array([0, 200, 400], np.int64), col, 0, 2, 10_000, 64, True)
 
 
+def test_ranges_of_unsorted_rows_are_not_tiled():
+    """A range that cannot gain is looked at too: it would be tiled with the range beside it, and the plan refuses such rows."""
+    from types import SimpleNamespace
+    import torch
+    from paper_2306_01381_amd.layer import LayerStep
+    rng = np.random.default_rng(5)
+    n, short, n_cols = 12_000, 500, 60_000
+    long_rows = np.sort(np.stack([rng.choice(n_cols, 110, replace=False) for _ in range(n)]), axis=1)
+    col = np.concatenate([long_rows.reshape(-1), np.tile([9, 3, 5], short)]).astype(np.int32)
+    rowptr = np.concatenate([np.arange(n) * 110, n * 110 + np.arange(short + 1) * 3]).astype(np.int64)
+    assert B.adaqp_spmm_segments_gain(rowptr, col, 0, n, n_cols, 256) > B.SPMM_SEGMENTS_MIN_GAIN
+    assert B.adaqp_spmm_segments_gain(rowptr, col, n, n + short, n_cols, 256) == -np.inf
+    step = SimpleNamespace(p=SimpleNamespace(rowptr=rowptr, col=col, feat=np.empty((n_cols, 1))), feat=torch.zeros(1, 288), dim=256,
+                           backward=False)
+    assert LayerStep._ranges_to_tile(step, None, (0, n), (n, n + short)) == (True, False)
+    assert LayerStep._ranges_to_tile(step, None, (n, n + short), (0, n), (n, n)) == (False, True, False)
+    with pytest.raises(B.AdaqpError):                                  # an offset below zero
+        B.adaqp_spmm_segments_gain(np.array([-5, 2], np.int64), col, 0, 1, n_cols, 256)
+
+
 @pytest.mark.parametrize("n_rows,n_cols,min_len", [(1, 1, 1), (40, 33, 5), (130, 900, 60), (300, 2_000, 40)])
 def test_plan_spmm_blocks(n_rows, n_cols, min_len):
     """A block lists exactly the distinct columns of its rows, each in its interval, ascending, steps filled with the last one."""
