@@ -452,7 +452,8 @@ typedef struct adaqp_spmm_blocks {
     const int32_t *step_ptr_dev;        /* [n_blocks * n_pieces + 1] first step of each (block, interval) */
     const int32_t *cols_dev;            /* [n_steps][32] columns of H, ascending within (block, interval), the last repeated */
     float *table_dev;                   /* [n_steps][4][2][64][8] coefficients: column 16 k + 8 h + j of a step, row 32 g + m
-                                           at [step][g][k][32 h + m][j]; adaqp_fill_spmm_blocks writes it */
+                                           at [step][g][k][32 h + m][j], +0 where the row has no entry, -0 for an entry of
+                                           coefficient 0; adaqp_fill_spmm_blocks writes it */
 } adaqp_spmm_blocks;
 
 /* Host only.  Plans the blocks of rows [row_begin, row_end) of a host CSR (ascending, distinct, in-range columns per row) with

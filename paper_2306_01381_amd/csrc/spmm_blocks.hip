@@ -259,7 +259,8 @@ __global__ __launch_bounds__(kBlock, 2) void spmm_block_kernel(const BlockArgs a
     else block_piece<1>(a, stage, piece, s0, s1, c_begin);
 }
 
-// One wave's share of a row's sum in plain fp32, from the pieces wave, wave + 4, ...: only the columns that the row lists.
+// One wave's share of a row's sum in plain fp32, from the pieces wave, wave + 4, ...: only the columns that the row lists, all of
+// whose places in the table hold something other than +0 (0 x inf is NaN where an entry has the coefficient 0, too).
 __device__ float4_t listed_columns(const BlockArgs &a, int32_t first, int32_t m, int32_t wave, int32_t lane, int32_t c, bool live)
 {
     float4_t sum = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -269,7 +270,7 @@ __device__ float4_t listed_columns(const BlockArgs &a, int32_t first, int32_t m,
             const int32_t k = lane % kStepCols;                     // lane k: the step's column k
             const float alpha = a.table[((((int64_t)s * kRowGroups + m / 32) * 2 + k / 16) * kWave + (k / 8 % 2) * 32 + m % 32) * 8 + k % 8];
             const int32_t col = (int32_t)min((uint32_t)a.cols[(int64_t)s * kStepCols + k], (uint32_t)a.n_cols - 1u);
-            for (uint32_t lists = (uint32_t)__ballot(alpha != 0.0f); lists; lists &= lists - 1) {
+            for (uint32_t lists = (uint32_t)__ballot(__builtin_bit_cast(uint32_t, alpha) != 0); lists; lists &= lists - 1) {
                 const int32_t q = __builtin_ctz(lists);
                 const float w = __shfl(alpha, q);
                 const int64_t from = __shfl(col, q);
@@ -343,7 +344,8 @@ __global__ __launch_bounds__(kBlock) void spmm_block_sum_kernel(const BlockArgs 
     if (wave == 0 && live) __builtin_nontemporal_store(total, reinterpret_cast<float4_t *>(a.out + row * a.ldo + c));
 }
 
-// The table: zeros, then the coefficient of every entry of the blocks' rows at its column's place.
+// The table: zeros, then the coefficient of every entry of the blocks' rows at its column's place, -0 for a coefficient of 0: a
+// product of it adds nothing, as the plain zeros do, and the column stays one that the row lists.
 __global__ __launch_bounds__(kBlock) void block_table_clear_kernel(float4_t *table, int64_t n)
 {
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
@@ -376,7 +378,7 @@ __global__ __launch_bounds__(kBlock) void block_table_fill_kernel(const BlockArg
         if (from >= end || a.cols[from] != c) continue;             // not of this plan
         const int64_t s = from / kStepCols;
         const int32_t k = (int32_t)(from % kStepCols), lane = (k / 8 % 2) * 32 + m % 32;
-        table[((((s * kRowGroups + m / 32) * 2 + k / 16) * kWave) + lane) * 8 + k % 8] = val[j];
+        table[((((s * kRowGroups + m / 32) * 2 + k / 16) * kWave) + lane) * 8 + k % 8] = val[j] == 0.0f ? -0.0f : val[j];
     }
 }
 

@@ -1036,12 +1036,15 @@ def test_spmm_blocks_precision():
             assert rel <= 1.5e-7, rel                                   # a rounding per term would be sqrt(3000) of them
 
 
-def test_spmm_blocks_non_finite():
+@pytest.mark.parametrize("zeros", [0.0, 0.3])                        # share of entries with a coefficient of 0, of either sign
+def test_spmm_blocks_non_finite(zeros):
     """An infinity or NaN in H reaches the rows that list its column, and no others; next to values near the ends of fp32."""
     _say("blocks non-finite")
     rng = np.random.default_rng(9)
     n_rows, n_cols, dim = 200, 700, 330                                # two strips of 256 columns, the second partly filled
     rowptr, col, val = _random_graph(rng, n_rows, n_cols, rng.integers(150, 600, size=n_rows))
+    dropped = np.random.default_rng(90).random(val.size) < zeros
+    val[dropped] = np.copysign(0.0, val[dropped])
     H = rng.standard_normal((n_cols, 352)).astype(np.float32)
     for v, c, k in ((np.inf, 3, 0), (-np.inf, 90, 17), (np.nan, 400, 256), (np.inf, 401, 329), (-np.inf, 402, 329), (5e37, 500, 40)):
         H[c, k] = v                                                    # (5e37: coefficients are up to 5, products within fp32)
