@@ -435,8 +435,8 @@ int adaqp_spmm_csr_panels(const adaqp_spmm_panels *panels_host, int64_t row_begi
 
 /* ---------------------------------------------------------------------------------------------------- */
 /* Dense blocks: as the panels above for rows that list a good part of all columns, ADAQP_SPMM_BLOCK_ROWS of them at a
- * time, on the bf16 matrix cores with fp32 operands split exactly into three bf16 (six of the nine partial products,
- * none of those left out above 2^-24 of the product; fp32 sums).  The rows taken are struck from the tile table as for panels,
+ * time, on the bf16 matrix cores with fp32 operands split exactly into three bf16, six of the nine partial products (what the
+ * other three would add is less than 2^-24 of a product in all) and fp32 sums.  The rows taken are struck from the tile table as for panels,
  * and the call may run beside adaqp_spmm_csr_tiled in the same way.  Sums that an infinity or NaN in H spoils are taken again
  * in fp32 from the columns that the row lists, so that it reaches those rows only. */
 #define ADAQP_SPMM_BLOCK_ROWS 128

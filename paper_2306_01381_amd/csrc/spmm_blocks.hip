@@ -6,7 +6,9 @@
 // the block and a dense [columns][128] table of fp32 coefficients.  out[block rows] = table^T x H[columns].
 //
 // fp32 to the matrix cores: the bf16 instructions run at 16 times the rate of the fp32 ones.  A value is hi + mid + lo, three
-// bf16, exactly (8 significant bits each); a product takes the six of the nine partial products that are not below 2^-24 of it.
+// bf16, exactly, each rounded to nearest, so that mid is at most 2^-8 of it and lo 2^-17.  A product takes six of the nine partial
+// products; mid x lo, lo x mid and lo x lo are left out, at most 2^-25, 2^-25 and 2^-34 of the product and together less than
+// 2^-24, half a unit in the last place (over all pairs of mantissas; with hi cut off instead of rounded 3.96 * 2^-24).
 // hi x hi goes into sums of its own: the instruction drops the bits of a product that lie far below the accumulator, and next
 // to a long sum the small products would lose theirs (one set of sums: relative error 4.6e-7 on rows of 6 000 entries and more
 // of normal features, 1.7e-7 on non-negative ones; two sets 1.3e-7 and 5.0e-8; fp32 instructions 2.9e-7 and 5.3e-8).
@@ -80,7 +82,8 @@ struct Operand {
     bf16x8_t hi, mid, lo;
 };
 
-// hi is the upper half of the bits, mid the remainder rounded to bf16, lo what is left of that.  Two values at a time; a
+// hi is the value rounded to bf16, mid the remainder rounded, lo what is left of that, 7 bits or fewer.  (A value that rounds to
+// infinity, 3.39e38 and above, has a NaN for remainder: spmm_block_sum_kernel takes such sums again.)  Two values at a time; a
 // subtraction is a dot product of a pair with (-1, 0) or (0, -1), which takes the bf16 as it is.
 __device__ __forceinline__ Operand split8(const float (&x)[8])
 {
@@ -92,9 +95,8 @@ __device__ __forceinline__ Operand split8(const float (&x)[8])
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const float x0 = x[2 * j], x1 = x[2 * j + 1];
-        hi[j] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, x1), __builtin_bit_cast(uint32_t, x0), 0x07060302u);
-        const uint32_t hj = hi[j];
-        const bf16x2_t h = __builtin_bit_cast(bf16x2_t, hj);
+        const bf16x2_t h = __builtin_convertvector((float2_t{x0, x1}), bf16x2_t);
+        hi[j] = __builtin_bit_cast(uint32_t, h);
         const float r0 = __builtin_amdgcn_fdot2_f32_bf16(h, first, x0, false);
         const float r1 = __builtin_amdgcn_fdot2_f32_bf16(h, second, x1, false);
         const bf16x2_t m = __builtin_convertvector((float2_t{r0, r1}), bf16x2_t);

@@ -1027,13 +1027,41 @@ def test_spmm_blocks_precision():
             A[torch.repeat_interleave(torch.arange(n_rows, device=DEV), rp.diff()), cl.long()] = vl.double()
             want, mag = A @ Hd.double(), A @ Hd.double().abs()
             # chains: the instructions of a piece (two per step) and the pieces, of 16 columns each at most; the parts left out
-            # are 3 * 2^-24 of a product
+            # are less than 2^-24 of a product
             steps = plan["n_steps"] // (plan["n_blocks"] * plan["n_pieces"]) + 1
-            bound = (2 * steps + plan["n_pieces"] + 8 + 3) * 2.0 ** -24
+            bound = (2 * steps + plan["n_pieces"] + 8 + 1) * 2.0 ** -24
             error = float(((out.double() - want).abs() / mag).max())
             assert error <= bound, (error, bound)
             rel = float((out.double() - want).norm() / want.norm())
             assert rel <= 1.5e-7, rel                                   # a rounding per term would be sqrt(3000) of them
+
+
+def test_spmm_blocks_products():
+    """Single products of the operands whose parts that are left out are largest (hi rounded to nearest; hi cut off), of values that
+    round to infinity in bf16, and of any others: less than 2^-24 of a product left out, the sum of the others rounded once to fp32,
+    and before that where the five smaller ones are added up (2^-7 of the product, five cuts of up to 2^-23)."""
+    _say("blocks products")
+    rng = np.random.default_rng(12)
+    x = np.concatenate([np.array([0x3F807FC0, 0x3F80FF80, 0x3F80817F, 0x3F800000, 0x3F7FFFFF], np.uint32).view(np.float32),
+                        rng.standard_normal(155).astype(np.float32)])
+    y = np.concatenate([x[:32], np.ldexp(x[:4], 126), [3.4e38, -3.39e38], rng.standard_normal(10)]).astype(np.float32)
+    x[-20:] *= 2.0 ** -60
+    y = y[None, :]
+    n, dim = x.size, y.size
+    H = np.repeat(y, n, axis=0)
+    H[:, 32:38][np.abs(x) > 2.0 ** -50] = 1.0                          # the largest values meet small ones only
+    rowptr, col = np.arange(n + 1, dtype=np.int64), np.arange(n, dtype=np.int32)
+    blocks = B.DeviceBlocks(B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n, dim, 1), DEV)
+    rp, cl, vl = (torch.from_numpy(a).to(DEV) for a in (rowptr, col, x))
+    Hd = torch.zeros((n, 64), device=DEV)
+    Hd[:, :dim] = torch.from_numpy(H).to(DEV)
+    B.adaqp_fill_spmm_blocks(blocks, 0, n, rp, cl, vl)
+    out = torch.zeros((n, 64), device=DEV)
+    B.adaqp_spmm_csr_blocks(blocks, 0, n, Hd, dim, out,
+                            torch.empty(B.adaqp_spmm_blocks_workspace_bytes(blocks, dim), dtype=torch.uint8, device=DEV))
+    want = x.astype(np.float64)[:, None] * H
+    error = np.abs(out[:, :dim].cpu().numpy() - want) / np.abs(want)
+    assert error.max() <= (2 + 10 * 2.0 ** -7) * 2.0 ** -24, error.max() * 2 ** 24
 
 
 @pytest.mark.parametrize("zeros", [0.0, 0.3])                        # share of entries with a coefficient of 0, of either sign
