@@ -466,11 +466,13 @@ int adaqp_plan_spmm_blocks(const int64_t *rowptr_host, const int32_t *col_host, 
                            int64_t n_cols, int32_t dim, int32_t min_row_len, int64_t *sizes_inout,
                            int32_t *tile_off_inout, int32_t *rows_out, int32_t *step_ptr_out, int32_t *cols_out);
 
-/* Host only: the row length from which a row is worth a place in a block, where the rows of the range reference columns below
- * n_cols (column bound ADAQP_SPMM_TILES of adaqp_plan_spmm_tiles), and whether a plan that takes n_rows_taken rows is worth
- * launching on a matrix of n_cols rows with a pitch of ldh floats (1) or not, or not possible (0). */
+/* Host only: the row length from which a row can be worth a place in a block, where the rows of the range reference columns below
+ * n_cols (column bound ADAQP_SPMM_TILES of adaqp_plan_spmm_tiles); whether a plan that takes n_rows_taken rows can be worth
+ * launching on a matrix of n_cols rows with a pitch of ldh floats (1) or not, or is not possible (0); and whether blocks of
+ * n_entries entries in n_steps steps take less time than the entries in tile order (1) or not (0). */
 int32_t adaqp_spmm_blocks_min_row(int64_t n_cols);
 int32_t adaqp_spmm_blocks_pay(int64_t n_rows_taken, int64_t n_cols, int64_t ldh);
+int32_t adaqp_spmm_blocks_save(int64_t n_entries, int64_t n_steps, int32_t dim);
 
 /* Floats of table_dev for that many steps. */
 int64_t adaqp_spmm_blocks_table_floats(int64_t n_steps);

@@ -126,6 +126,7 @@ _SIGNATURES = {
     "adaqp_plan_spmm_blocks": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp]),
     "adaqp_spmm_blocks_min_row": (_i32, [_i64]),
     "adaqp_spmm_blocks_pay": (_i32, [_i64, _i64, _i64]),
+    "adaqp_spmm_blocks_save": (_i32, [_i64, _i64, _i32]),
     "adaqp_spmm_blocks_table_floats": (_i64, [_i64]),
     "adaqp_fill_spmm_blocks": (ctypes.c_int, [ctypes.POINTER(SpmmBlocks), _i64, _i64, _vp, _vp, _vp, _i64, _vp]),
     "adaqp_spmm_blocks_workspace_bytes": (ctypes.c_int, [_i32, _i32, _i32, _vp]),
@@ -549,25 +550,33 @@ SPMM_BLOCK_STEP = 32
 
 def adaqp_plan_spmm_blocks(rowptr_host: np.ndarray, col_host: np.ndarray, row_begin: int, row_end: int, n_cols: int, dim: int,
                            min_row_len: int, tile_off: Optional[np.ndarray] = None,
-                           only_if_pays_for_ld: int = 0) -> Optional[dict]:
-    """Host-only.  None when no row of the range has min_row_len entries (or, with only_if_pays_for_ld = the pitch of H, when
-    adaqp_spmm_blocks_pay turns the sized plan down), else a dict of host arrays (rows, step_ptr, cols) and sizes.  tile_off
-    (the table of adaqp_plan_spmm_tiles for the same range) is changed in place: the rows taken are struck."""
+                           only_if_pays_for_ld: int = 0, if_slower: bool = False) -> Optional[dict]:
+    """Host-only.  None when no row of the range has min_row_len entries, else a dict of host arrays (rows, step_ptr, cols) and
+    sizes.  With only_if_pays_for_ld = the pitch of H: the longest of these rows whose blocks adaqp_spmm_blocks_pay and
+    (unless if_slower) adaqp_spmm_blocks_save speak for, None if there are none.  tile_off (the table of adaqp_plan_spmm_tiles for the same range) is
+    changed in place: the rows taken are struck."""
     rowptr = np.ascontiguousarray(rowptr_host, dtype=np.int64)
     col = np.ascontiguousarray(col_host, dtype=np.int32)
     if tile_off is not None:
         if tile_off.dtype != np.int32 or not tile_off.flags.c_contiguous or \
                 tile_off.shape != (max(row_end - row_begin, 0), SPMM_TILES + 1):
             raise ValueError("tile_off must be the C-contiguous int32 table of adaqp_plan_spmm_tiles for this range")
-    sizes = np.zeros(6, dtype=np.int64)
-    args = (rowptr.ctypes.data, col.ctypes.data, row_begin, row_end, n_cols, dim, min_row_len, sizes.ctypes.data)
-    _check(lib().adaqp_plan_spmm_blocks(*args, None, None, None, None), "adaqp_plan_spmm_blocks")
     names = ("n_rows_taken", "n_blocks", "n_pieces", "n_steps", "col_begin", "piece_width")
-    plan = {k: int(v) for k, v in zip(names, sizes)}
-    if plan["n_rows_taken"] == 0:
-        return None
-    if only_if_pays_for_ld > 0 and not lib().adaqp_spmm_blocks_pay(plan["n_rows_taken"], n_cols, only_if_pays_for_ld):
-        return None
+    degs = np.diff(rowptr[row_begin:row_end + 1]) if only_if_pays_for_ld > 0 else None
+    while True:
+        sizes = np.zeros(6, dtype=np.int64)
+        args = (rowptr.ctypes.data, col.ctypes.data, row_begin, row_end, n_cols, dim, min_row_len, sizes.ctypes.data)
+        _check(lib().adaqp_plan_spmm_blocks(*args, None, None, None, None), "adaqp_plan_spmm_blocks")
+        plan = {k: int(v) for k, v in zip(names, sizes)}
+        if plan["n_rows_taken"] == 0:
+            return None
+        if only_if_pays_for_ld <= 0:
+            break
+        if not lib().adaqp_spmm_blocks_pay(plan["n_rows_taken"], n_cols, only_if_pays_for_ld):
+            return None
+        if if_slower or lib().adaqp_spmm_blocks_save(int(degs[degs >= min_row_len].sum()), plan["n_steps"], dim):
+            break
+        min_row_len += min_row_len // 2 + 1                 # the longer ones fill their blocks better
     plan.update(rows=np.empty(plan["n_blocks"] * SPMM_BLOCK_ROWS, dtype=np.int32),
                 step_ptr=np.empty(plan["n_blocks"] * plan["n_pieces"] + 1, dtype=np.int32),
                 cols=np.empty((plan["n_steps"], SPMM_BLOCK_STEP), dtype=np.int32))

@@ -713,7 +713,8 @@ extern "C" int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_
             ++n_dense;
         }
     }
-    if (!adaqp_spmm_blocks_pay(n_dense, n_cols, 32)) dense = 0.0;
+    const int64_t block_steps = (n_dense + ADAQP_SPMM_BLOCK_ROWS - 1) / ADAQP_SPMM_BLOCK_ROWS * ((n_cols + ADAQP_SPMM_BLOCK_STEP - 1) / ADAQP_SPMM_BLOCK_STEP);
+    if (!adaqp_spmm_blocks_pay(n_dense, n_cols, 32) || !adaqp_spmm_blocks_save((int64_t)dense, block_steps, dim)) dense = 0.0;
     const double entries = (double)(last - first), rows = (double)(row_end - row_begin);
     // forward slices are one line, backward ones four: the misses that are left, and their weight, differ
     const double cost = transposed ? (0.26 * lines + 0.41) * entries : (0.5 * lines + 0.25) * entries + 2.7 * lines * rows;

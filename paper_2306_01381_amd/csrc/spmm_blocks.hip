@@ -532,10 +532,8 @@ extern "C" int adaqp_plan_spmm_blocks(const int64_t *rowptr_host, const int32_t 
     return ADAQP_OK;
 }
 
-// A row of a block costs every column of the block: 128 rows x 32 columns x a line of H 1.4 ns at 1.08 PFLOP/s, an entry 7.5 ps a
-// line where the columns are tiled over the L2s, so that 4.5 % of the columns break even.  Few rows leave most of the GPU to pieces
-// that are all start and sums (256 columns of H, 5 % dense: 95 rows 75 us against 31, 272 rows 96 against 65, 685 rows
-// about even).
+// A row of a block costs every column of the block: at 1.08 PFLOP/s and 7.5 ps per entry and line in tile order 4.5 % of the columns break
+// even, where there are many lines.  Which rows can be worth it; whether they are, adaqp_spmm_blocks_save says.
 constexpr int64_t kColumnsPerEntry = 20, kFewestRows = 256;
 
 extern "C" int32_t adaqp_spmm_blocks_min_row(int64_t n_cols)
@@ -546,6 +544,19 @@ extern "C" int32_t adaqp_spmm_blocks_min_row(int64_t n_cols)
 extern "C" int32_t adaqp_spmm_blocks_pay(int64_t n_rows_taken, int64_t n_cols, int64_t ldh)
 {
     return n_rows_taken >= kFewestRows && n_cols > 0 && n_cols <= kMostCols && ldh < kMostPitch && n_cols * ldh <= kMostBytes / 4 ? 1 : 0;
+}
+
+// What the entries cost in tile order against what their blocks cost: a step is a load and a split of coefficients per chunk of feature
+// columns and of the rows of H per line beside its matrix instructions.  Fitted to 38 shapes of 24 000 and 90 000 columns, 130 to 1 792 rows
+// that list 5.5, 12 or 25 % of them, 32 to 602 columns of H, beside 10 000 rows of 100 entries; without and with blocks, one after the
+// other: 384 rows of 12 %, 90 000 columns of H of 64 87 -> 112 us (no), of 96 141 -> 129 (yes), of 602 702 -> 520 (yes); 256 rows of 12 %,
+// 24 000 columns, 128 columns of H 65 -> 67 (no), 256 109 -> 95 (yes); 1 152 rows of 5.5 %, 90 000 columns, 256 columns 381 -> 418 (no).
+extern "C" int32_t adaqp_spmm_blocks_save(int64_t n_entries, int64_t n_steps, int32_t dim)
+{
+    if (n_entries <= 0 || n_steps <= 0 || dim <= 0) return 0;
+    const double lines = (double)(((int64_t)dim + 31) / 32), chunks = (double)(((int64_t)dim + kChunk - 1) / kChunk);
+    const double entries_ns = 5.6e-3 * lines * (double)n_entries;
+    return entries_ns > 15e3 + (2.7 * chunks + 0.75 * lines) * (double)n_steps ? 1 : 0;
 }
 
 extern "C" int64_t adaqp_spmm_blocks_table_floats(int64_t n_steps) { return n_steps < 0 ? -1 : n_steps * kStepCols * kBlockRows; }

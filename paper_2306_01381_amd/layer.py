@@ -144,8 +144,9 @@ class LayerStep:
         # row range (adaqp_spmm_tiled_pays: mean row length).
         self.tile_off_overlap = self.tile_off_dependent = None
         self.tile_chunk_overlap = self.tile_chunk_dependent = 0
+        self._tiles_asked_for = tiled
         # within a tiled range, rows that list a good part of the columns go to the matrix cores: panels=None in dense blocks,
-        # where the library says that pays; True: rows of panel_min_row entries in panels, always
+        # where the library says that pays (tiled=True: where they can be more than a few workgroups); True: rows of panel_min_row entries in panels, always
         self.panels_overlap = self.panels_dependent = B.DevicePanels(None)
         self.blocks_overlap = self.blocks_dependent = B.DeviceBlocks(None)
         # and the others' entries are kept a second time, in the order of the tiles
@@ -211,7 +212,7 @@ class LayerStep:
         elif panels is None:
             with_blocks = B.DeviceBlocks(B.adaqp_plan_spmm_blocks(
                 p.rowptr, p.col, begin, end, n_cols, dim, B.adaqp_spmm_blocks_min_row(int(bounds[-1])), off,
-                only_if_pays_for_ld=self.feat.stride(0)), self.device)
+                only_if_pays_for_ld=self.feat.stride(0), if_slower=bool(self._tiles_asked_for)), self.device)
             if with_blocks:
                 B.adaqp_fill_spmm_blocks(with_blocks, begin, end, self.rowptr, self.col, self.val)
         segments = B.DeviceSegments(None)

@@ -535,6 +535,37 @@ def test_rule_that_decides_whether_a_panel_plan_pays():
     assert not np.array_equal(off, before)
 
 
+@pytest.mark.parametrize("n_cols,share,rows,dim,saves", [
+    (24_000, 0.055, 1792, 64, False), (24_000, 0.055, 1792, 256, False), (24_000, 0.12, 256, 128, False), (24_000, 0.12, 256, 256, True),
+    (24_000, 0.25, 512, 64, True), (24_000, 0.25, 256, 602, True), (90_000, 0.055, 1152, 256, False), (90_000, 0.12, 384, 64, False),
+    (90_000, 0.12, 384, 96, True), (90_000, 0.12, 384, 602, True), (90_000, 0.12, 130, 32, False)])
+def test_rule_that_decides_whether_blocks_save(n_cols, share, rows, dim, saves):
+    """Timed with and without blocks: the faster way, where they differ."""
+    steps = -(-rows // 128) * -(-n_cols // 32)
+    assert bool(B.lib().adaqp_spmm_blocks_save(int(rows * share * n_cols), steps, dim)) == saves
+
+
+def test_plan_spmm_blocks_takes_the_rows_that_pay():
+    """300 rows that list a quarter of the columns beside 8 000 that list a twentieth: all of them would be slower in blocks, the long
+    ones are faster, and with few columns of H none are."""
+    rng = np.random.default_rng(3)
+    n_cols = 4_000
+    degs = np.concatenate([np.full(8_000, 204), np.full(300, 1_000)])
+    rowptr = np.concatenate([[0], np.cumsum(degs)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n_cols, d, replace=False)) for d in degs]).astype(np.int32)
+    n = degs.size
+    _, off = B.adaqp_plan_spmm_tiles(rowptr, col, 0, n, n_cols)
+    before = off.copy()
+    assert B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, 64, 200, off, only_if_pays_for_ld=64) is None
+    assert np.array_equal(off, before)
+    plan = B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, 602, 200, off, only_if_pays_for_ld=608)
+    assert plan["n_rows_taken"] == 300 and np.array_equal(np.sort(plan["rows"][:300]), np.arange(8_000, n))
+    assert np.all(off[8_000:] == -1) and np.array_equal(off[:8_000], before[:8_000])
+    # where the caller has asked for tiles, and where for blocks
+    assert B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, 64, 200, only_if_pays_for_ld=64, if_slower=True)["n_rows_taken"] == n
+    assert B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, 64, 200)["n_rows_taken"] == n
+
+
 def test_layer_desc_mirror_matches_the_library():
     import ctypes
     assert int(B.lib().adaqp_layer_desc_bytes()) == ctypes.sizeof(B.LayerDesc)
