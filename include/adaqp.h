@@ -474,6 +474,10 @@ int32_t adaqp_spmm_blocks_min_row(int64_t n_cols);
 int32_t adaqp_spmm_blocks_pay(int64_t n_rows_taken, int64_t n_cols, int64_t ldh);
 int32_t adaqp_spmm_blocks_save(int64_t n_entries, int64_t n_steps, int32_t dim);
 
+/* Host only: steps whose table stays within four times the bytes of col and val of a range with nnz entries, or 64 MB.  A table takes
+ * 16 KB per step, 80 bytes per entry of rows that list a twentieth of the columns. */
+int64_t adaqp_spmm_blocks_most_steps(int64_t nnz);
+
 /* Floats of table_dev for that many steps. */
 int64_t adaqp_spmm_blocks_table_floats(int64_t n_steps);
 

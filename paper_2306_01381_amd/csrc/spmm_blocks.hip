@@ -547,9 +547,10 @@ extern "C" int32_t adaqp_spmm_blocks_pay(int64_t n_rows_taken, int64_t n_cols, i
 }
 
 // What the entries cost in tile order against what their blocks cost: a step is a load and a split of coefficients per chunk of feature
-// columns and of the rows of H per line beside its matrix instructions.  Fitted to 38 shapes of 24 000 and 90 000 columns, 130 to 1 792 rows
-// that list 5.5, 12 or 25 % of them, 32 to 602 columns of H, beside 10 000 rows of 100 entries; without and with blocks, one after the
-// other: 384 rows of 12 %, 90 000 columns of H of 64 87 -> 112 us (no), of 96 141 -> 129 (yes), of 602 702 -> 520 (yes); 256 rows of 12 %,
+// columns and of the rows of H per line beside its matrix instructions.  Fitted to 228 launches of 24 000 and 90 000 columns, 130 to 1 792
+// rows that list 5.5, 12 or 25 % of them, 32 to 602 columns of H, beside 10 000 rows of 100 entries.  Geometric mean against no blocks 1.16,
+// the largest loss 10 % (blocks for every 256 rows: 1.04, 2.05 times as slow at worst).  Without and with blocks, one launch after the
+// other: 384 rows of 12 %, 90 000 columns, 64 columns of H 87 -> 112 us (no), 96 141 -> 129 (yes), 602 702 -> 520 (yes); 256 rows of 12 %,
 // 24 000 columns, 128 columns of H 65 -> 67 (no), 256 109 -> 95 (yes); 1 152 rows of 5.5 %, 90 000 columns, 256 columns 381 -> 418 (no).
 extern "C" int32_t adaqp_spmm_blocks_save(int64_t n_entries, int64_t n_steps, int32_t dim)
 {
@@ -557,6 +558,14 @@ extern "C" int32_t adaqp_spmm_blocks_save(int64_t n_entries, int64_t n_steps, in
     const double lines = (double)(((int64_t)dim + 31) / 32), chunks = (double)(((int64_t)dim + kChunk - 1) / kChunk);
     const double entries_ns = 5.6e-3 * lines * (double)n_entries;
     return entries_ns > 15e3 + (2.7 * chunks + 0.75 * lines) * (double)n_steps ? 1 : 0;
+}
+
+// A table takes 16 KB per step, however few of its places are filled: ten times what the entries of rows at the threshold take.  Four times
+// the col and val of the range leaves 58 000 rows with 28 M entries what they have (2.0 and 2.4 times); 64 MB are never too many.
+extern "C" int64_t adaqp_spmm_blocks_most_steps(int64_t nnz)
+{
+    constexpr int64_t kStepBytes = (int64_t)kStepCols * kBlockRows * 4;
+    return std::max<int64_t>((nnz < 0 ? 0 : nnz) / (kStepBytes / (4 * 8)), ((int64_t)64 << 20) / kStepBytes);
 }
 
 extern "C" int64_t adaqp_spmm_blocks_table_floats(int64_t n_steps) { return n_steps < 0 ? -1 : n_steps * kStepCols * kBlockRows; }

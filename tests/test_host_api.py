@@ -561,9 +561,26 @@ def test_plan_spmm_blocks_takes_the_rows_that_pay():
     plan = B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, 602, 200, off, only_if_pays_for_ld=608)
     assert plan["n_rows_taken"] == 300 and np.array_equal(np.sort(plan["rows"][:300]), np.arange(8_000, n))
     assert np.all(off[8_000:] == -1) and np.array_equal(off[:8_000], before[:8_000])
-    # where the caller has asked for tiles, and where for blocks
-    assert B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, 64, 200, only_if_pays_for_ld=64, if_slower=True)["n_rows_taken"] == n
+    # where the caller has asked for tiles (the long rows: all of them would take a table of 133 MB), and where for blocks
+    assert B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, 64, 200, only_if_pays_for_ld=64, if_slower=True)["n_rows_taken"] == 300
     assert B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, 64, 200)["n_rows_taken"] == n
+
+
+def test_plan_spmm_blocks_bounds_its_table():
+    """Rows at the threshold take ten times their bytes: no more than four times those of the range, or 64 MB."""
+    assert B.lib().adaqp_spmm_blocks_most_steps(0) == B.lib().adaqp_spmm_blocks_most_steps(-1) == 4096
+    assert B.lib().adaqp_spmm_blocks_most_steps(512 * 5_000) == 5_000
+    n_cols, dim, n, d = 40_000, 602, 1_500, 3_000                      # 12 blocks x 1 250 steps: 246 MB; 4.5 M entries: 36 MB
+    rng = np.random.default_rng(7)
+    col = np.sort((np.arange(d) * 13 + rng.integers(0, n_cols, size=(n, 1))) % n_cols, axis=1).astype(np.int32)
+    col[:300] = np.arange(37_000, n_cols)                              # rows that share their columns: few steps
+    rowptr = np.arange(n + 1, dtype=np.int64) * d
+    plan = B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, dim, 2_000)
+    assert plan["n_steps"] > 4_500_000 // 512 and B.lib().adaqp_spmm_blocks_save(4_500_000, plan["n_steps"], dim)
+    for if_slower in (False, True):
+        assert B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, dim, 2_000, only_if_pays_for_ld=608, if_slower=if_slower) is None
+    small = B.adaqp_plan_spmm_blocks(rowptr, col, 0, 300, n_cols, dim, 2_000, only_if_pays_for_ld=608)
+    assert small["n_rows_taken"] == 300 and small["n_steps"] <= 400
 
 
 def test_layer_desc_mirror_matches_the_library():
