@@ -537,6 +537,8 @@ def adaqp_spmm_segments_workspace_bytes(segments: DeviceSegments, dim: int) -> i
 def adaqp_spmm_csr_segments(segments: DeviceSegments, row_begin: int, H: torch.Tensor, dim: int, out: torch.Tensor,
                             workspace: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
     """out: the whole matrix; row_begin: the first row of the range the plan was made for."""
+    if row_begin < 0 or row_begin + segments.c.n_rows > out.shape[0]:
+        raise ValueError("out does not have the rows of the plan from row_begin on")
     hp, n_cols, ldh = _matrix(H, "H")
     _, _, ldo = _matrix(out, "out")
     op, _, _ = _matrix(out[row_begin:], "out")

@@ -106,6 +106,19 @@ def test_argument_errors_are_caught_before_any_launch():
     assert L.adaqp_spmm_csr_panels(ctypes.byref(bad), 0, 4, one, 8, 32, 8, one, 32, one, 1 << 20, None) == B.EINVAL
 
 
+def test_segments_of_rows_that_the_output_does_not_have():
+    """A first row from which the plan's rows do not fit the matrix is refused before anything is launched."""
+    import torch
+    from types import SimpleNamespace
+    plan = SimpleNamespace(c=B.SpmmSegments(3, 100, 6, 256, 256, 256, 256, 256))
+    out, ws = torch.zeros(8, 32), torch.zeros(256, dtype=torch.uint8)
+    for row_begin in (-1, 3, 8, 9):
+        with pytest.raises(ValueError):
+            B.adaqp_spmm_csr_segments(plan, row_begin, torch.zeros(8, 32), 32, out, ws)
+    with pytest.raises(TypeError):                                     # the rows fit: a host matrix is refused next
+        B.adaqp_spmm_csr_segments(plan, 2, torch.zeros(8, 32), 32, out, ws)
+
+
 def test_workspace_query():
     assert B.adaqp_spmm_workspace_bytes(0, 0, 8) == 0
     small = B.adaqp_spmm_workspace_bytes(2000, 20000, 128)
