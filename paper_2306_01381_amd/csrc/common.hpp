@@ -26,6 +26,12 @@ int spmm_rows(const int64_t *rowptr_dev, const int32_t *col_dev, const float *va
               int64_t packed_bytes, const float *params_dev, const uint8_t *bits_dev, const int64_t *row_offset_dev,
               int64_t n_slots, void *workspace_dev, int64_t workspace_bytes, void *stream, bool skewed_columns);
 
+// What adaqp_spmm_csr_segments and adaqp_spmm_csr_blocks refuse, but for their workspaces: the layer step asks before it queues anything.
+int check_segments_call(const adaqp_spmm_segments *p, const float *H_dev, int64_t n_cols, int64_t ldh, int32_t dim, const float *out_dev,
+                        int64_t ldo);
+int check_blocks_call(const adaqp_spmm_blocks *p, int64_t row_begin, int64_t row_end, const float *H_dev, int64_t n_cols, int64_t ldh,
+                      int32_t dim, const float *out_dev, int64_t ldo);
+
 inline bool valid_bits(int b) { return b == 2 || b == 4 || b == 8; }
 
 inline bool aligned_to(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }

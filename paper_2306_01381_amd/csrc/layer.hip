@@ -171,10 +171,23 @@ int check_desc(const adaqp_layer_desc *d)
         const adaqp_spmm_segments *s = part ? &d->segments_overlap : &d->segments_dependent;
         if (s->n_seg < 0 || s->n_entries < 0 || s->n_rows < 0) return ADAQP_EINVAL;
         if (s->n_seg > 0 && (!tile_off || !s->ptr_dev || !s->of_row_dev || !s->col_dev || !s->val_dev)) return ADAQP_EINVAL;
+        const int64_t rb = part ? d->overlap_begin : d->dependent_begin, re = part ? d->overlap_end : d->dependent_end;
+        const void *ws = part ? d->workspace_overlap_dev : d->workspace_dependent_dev;
+        if (s->n_seg > 0) {
+            if (s->n_rows != re - rb) return ADAQP_EINVAL;
+            const int rc = check_segments_call(s, d->feat_dev, d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo);
+            if (rc != ADAQP_OK) return rc;
+            if (!aligned_to(ws, 256)) return ADAQP_EINVAL;
+        }
         const adaqp_spmm_blocks *b = part ? &d->blocks_overlap : &d->blocks_dependent;
         if (b->n_blocks < 0 || b->n_pieces < 0 || b->n_steps < 0) return ADAQP_EINVAL;
         if (b->n_blocks > 0 && (!tile_off || p->n_panels > 0 || !b->rows_dev || !b->step_ptr_dev || !b->cols_dev || !b->table_dev))
             return ADAQP_EINVAL;
+        if (b->n_blocks > 0) {
+            const int rc = check_blocks_call(b, rb, re, d->feat_dev, d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo);
+            if (rc != ADAQP_OK) return rc;
+            if (!aligned_to(ws, 256)) return ADAQP_EINVAL;
+        }
         if (p->n_panels == 0) continue;
         if (!tile_off) return ADAQP_EINVAL;                 // panels complement a tile table, never the merge path
         if (!p->panel_rows_dev || !p->pcol_dev || !p->palpha_dev || !p->piece_dev || !p->panel_piece_ptr_dev ||
@@ -229,9 +242,7 @@ int aggregate_rows(const adaqp_layer_desc *d, bool overlap_part, hipStream_t st)
     const int32_t *tile_off = overlap_part ? d->tile_off_overlap_dev : d->tile_off_dependent_dev;
     const adaqp_spmm_segments *seg = overlap_part ? &d->segments_overlap : &d->segments_dependent;
     if (tile_off && seg->n_seg > 0)
-        return re - rb == seg->n_rows ? adaqp_spmm_csr_segments(seg, d->feat_dev, d->n_feat_rows, d->ld, d->dim,
-                                                                d->out_dev + rb * d->ldo, d->ldo, ws, wsb, st)
-                                      : ADAQP_EINVAL;
+        return adaqp_spmm_csr_segments(seg, d->feat_dev, d->n_feat_rows, d->ld, d->dim, d->out_dev + rb * d->ldo, d->ldo, ws, wsb, st);
     if (tile_off)
         return adaqp_spmm_csr_tiled(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, d->feat_dev,
                                     d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo, tile_off,

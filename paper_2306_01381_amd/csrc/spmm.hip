@@ -766,8 +766,8 @@ extern "C" int adaqp_spmm_segments_workspace_bytes(int64_t n_seg, int64_t n_entr
     return ADAQP_OK;
 }
 
-extern "C" int adaqp_spmm_csr_segments(const adaqp_spmm_segments *p, const float *H_dev, int64_t n_cols, int64_t ldh, int32_t dim,
-                                       float *out_dev, int64_t ldo, void *workspace_dev, int64_t workspace_bytes, void *stream)
+int adaqp::check_segments_call(const adaqp_spmm_segments *p, const float *H_dev, int64_t n_cols, int64_t ldh, int32_t dim, const float *out_dev,
+                               int64_t ldo)
 {
     if (!p || p->n_seg < 0 || p->n_entries < 0 || p->n_rows < 0 || n_cols < 0 || dim <= 0 || ldh < dim || ldo < dim) return ADAQP_EINVAL;
     if (p->n_seg == 0 || p->n_rows == 0) return ADAQP_OK;
@@ -775,6 +775,14 @@ extern "C" int adaqp_spmm_csr_segments(const adaqp_spmm_segments *p, const float
     if (!aligned_to(p->ptr_dev, 8) || !aligned_to(p->of_row_dev, 4) || !aligned_to(p->col_dev, 4) || !aligned_to(p->val_dev, 4)) return ADAQP_EINVAL;
     if (ldh % 32 != 0 || ldo % 32 != 0 || !aligned_to(H_dev, 128) || !aligned_to(out_dev, 128)) return ADAQP_EINVAL;
     if (p->n_seg > INT32_MAX - 1024 || p->n_rows > INT32_MAX - 1 || !sliced_takes(p->n_seg, p->n_entries, n_cols, ldh, false, 0, dim)) return ADAQP_ESIZE;
+    return ADAQP_OK;
+}
+
+extern "C" int adaqp_spmm_csr_segments(const adaqp_spmm_segments *p, const float *H_dev, int64_t n_cols, int64_t ldh, int32_t dim,
+                                       float *out_dev, int64_t ldo, void *workspace_dev, int64_t workspace_bytes, void *stream)
+{
+    const int rc = check_segments_call(p, H_dev, n_cols, ldh, dim, out_dev, ldo);
+    if (rc != ADAQP_OK || p->n_seg == 0 || p->n_rows == 0) return rc;
     const SegmentGeometry g = segment_geometry(p->n_seg, p->n_entries, dim);
     if (!workspace_dev || !aligned_to(workspace_dev, 256)) return ADAQP_EINVAL;
     if (workspace_bytes < g.bytes) return ADAQP_ESIZE;

@@ -46,6 +46,7 @@ constexpr int kRowGroups = kBlockRows / 32;         // one per wave
 constexpr int kMostSteps = 128;                     // of a piece
 constexpr int kTiles = 4;                           // column tiles of 32 of a workgroup, one per wave to load
 constexpr int kChunk = kTiles * 32;                 // feature columns of a workgroup
+constexpr int kStrip = kWave * 4;                   // feature columns of a workgroup of the sums
 constexpr int kXcds = 8;
 constexpr int kRawBuffer = 0x00020000;              // buffer resource, last word: raw 32-bit data, no swizzle
 constexpr int64_t kMostBytes = 0xFFFF0000;          // of H: offsets are kept in 32 bits
@@ -302,7 +303,7 @@ __global__ __launch_bounds__(kBlock) void spmm_block_sum_kernel(const BlockArgs 
     const int64_t row = a.rows[r];
     if (row < a.row_begin || row >= a.row_end) return;              // the whole workgroup: no barrier is skipped by a part
     const int32_t first = (int32_t)(r / kBlockRows) * a.n_pieces, m = (int32_t)(r % kBlockRows);
-    const int32_t c = strip * (kWave * 4) + lane * 4;
+    const int32_t c = strip * kStrip + lane * 4;
     const bool live = c < a.wdim;
     constexpr int kAhead = 8;
     float4_t sum = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -389,6 +390,16 @@ int64_t blocks_bytes(int64_t n_blocks, int64_t n_pieces, int32_t dim)
     const int64_t wdim = ((int64_t)dim + 31) / 32 * 32;
     return (n_blocks * n_pieces * kBlockRows * wdim * 4 + 255) / 256 * 256;
 }
+
+// Of the two launches; a launch has fewer than 2^31 threads.
+constexpr int64_t kMostWorkgroups = 0x7FFFFFFF / kBlock;
+
+int64_t product_workgroups(const adaqp_spmm_blocks *p, int32_t dim)
+{
+    return ((int64_t)p->n_pieces + kXcds - 1) / kXcds * kXcds * p->n_blocks * (((int64_t)dim + kChunk - 1) / kChunk);
+}
+
+int64_t sum_workgroups(int64_t n_blocks, int64_t dim) { return n_blocks * kBlockRows * ((dim + kStrip - 1) / kStrip); }
 
 // Intervals of the columns.  A round is what the GPU's 512 resident workgroups take at a time; an interval costs each of its
 // workgroups about four steps to start and end, and its sums a tenth of a step's time per block to write and read.
@@ -543,7 +554,8 @@ extern "C" int32_t adaqp_spmm_blocks_min_row(int64_t n_cols)
 
 extern "C" int32_t adaqp_spmm_blocks_pay(int64_t n_rows_taken, int64_t n_cols, int64_t ldh)
 {
-    return n_rows_taken >= kFewestRows && n_cols > 0 && n_cols <= kMostCols && ldh < kMostPitch && n_cols * ldh <= kMostBytes / 4 ? 1 : 0;
+    return n_rows_taken >= kFewestRows && n_cols > 0 && n_cols <= kMostCols && ldh < kMostPitch && n_cols * ldh <= kMostBytes / 4 &&
+           sum_workgroups((n_rows_taken + kBlockRows - 1) / kBlockRows, ldh) <= kMostWorkgroups ? 1 : 0;
 }
 
 // What the entries cost in tile order against what their blocks cost: a step is a load and a split of coefficients per chunk of feature
@@ -600,9 +612,8 @@ extern "C" int adaqp_spmm_blocks_workspace_bytes(int32_t n_blocks, int32_t n_pie
     return ADAQP_OK;
 }
 
-extern "C" int adaqp_spmm_csr_blocks(const adaqp_spmm_blocks *p, int64_t row_begin, int64_t row_end, const float *H_dev,
-                                     int64_t n_cols, int64_t ldh, int32_t dim, float *out_dev, int64_t ldo,
-                                     void *workspace_dev, int64_t workspace_bytes, void *stream)
+int adaqp::check_blocks_call(const adaqp_spmm_blocks *p, int64_t row_begin, int64_t row_end, const float *H_dev, int64_t n_cols, int64_t ldh,
+                             int32_t dim, const float *out_dev, int64_t ldo)
 {
     if (!p) return ADAQP_EINVAL;
     const int rc = check_blocks(p);
@@ -612,6 +623,16 @@ extern "C" int adaqp_spmm_csr_blocks(const adaqp_spmm_blocks *p, int64_t row_beg
     if (!H_dev || !out_dev || n_cols == 0) return ADAQP_EINVAL;
     if (n_cols > kMostCols || ldh >= kMostPitch || n_cols * ldh > kMostBytes / 4) return ADAQP_ESIZE;
     if (ldh % 32 != 0 || ldo % 32 != 0 || !aligned_to(H_dev, 128) || !aligned_to(out_dev, 128)) return ADAQP_EINVAL;
+    if (product_workgroups(p, dim) > kMostWorkgroups || sum_workgroups(p->n_blocks, dim) > kMostWorkgroups) return ADAQP_ESIZE;
+    return ADAQP_OK;
+}
+
+extern "C" int adaqp_spmm_csr_blocks(const adaqp_spmm_blocks *p, int64_t row_begin, int64_t row_end, const float *H_dev,
+                                     int64_t n_cols, int64_t ldh, int32_t dim, float *out_dev, int64_t ldo,
+                                     void *workspace_dev, int64_t workspace_bytes, void *stream)
+{
+    const int rc = check_blocks_call(p, row_begin, row_end, H_dev, n_cols, ldh, dim, out_dev, ldo);
+    if (rc != ADAQP_OK || p->n_blocks == 0 || row_end == row_begin) return rc;
     const int64_t need = blocks_bytes(p->n_blocks, p->n_pieces, dim);
     if (!workspace_dev || !aligned_to(workspace_dev, 256)) return ADAQP_EINVAL;
     if (workspace_bytes < need) return ADAQP_ESIZE;
@@ -625,11 +646,8 @@ extern "C" int adaqp_spmm_csr_blocks(const adaqp_spmm_blocks *p, int64_t row_beg
     a.out = out_dev;
     a.ldo = ldo;
     a.partial = reinterpret_cast<float *>(workspace_dev);
-    const int64_t n_chunks = (a.wdim + kChunk - 1) / kChunk;
-    const int64_t blocks = ((int64_t)p->n_pieces + kXcds - 1) / kXcds * kXcds * p->n_blocks * n_chunks;
-    const int64_t n_strips = (a.wdim + kWave * 4 - 1) / (kWave * 4);
-    const int64_t sums = (int64_t)p->n_blocks * kBlockRows * n_strips;
-    if (blocks > 0x7FFFFFFF / kBlock || sums > 0x7FFFFFFF / kBlock) return ADAQP_ESIZE;
+    const int64_t n_chunks = (a.wdim + kChunk - 1) / kChunk, n_strips = (a.wdim + kStrip - 1) / kStrip;
+    const int64_t blocks = product_workgroups(p, dim), sums = sum_workgroups(p->n_blocks, dim);
     hipStream_t st = (hipStream_t)stream;
     hipLaunchKernelGGL(spmm_block_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, st, a, (int32_t)n_chunks);
     ADAQP_HIP_TRY(hipGetLastError());

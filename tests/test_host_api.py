@@ -106,6 +106,40 @@ def test_argument_errors_are_caught_before_any_launch():
     assert L.adaqp_spmm_csr_panels(ctypes.byref(bad), 0, 4, one, 8, 32, 8, one, 32, one, 1 << 20, None) == B.EINVAL
 
 
+def test_layer_step_refuses_plans_before_it_queues_anything():
+    """Segments or blocks that the aggregation would refuse: the codes of its checks, where a step that has begun could only fail to
+    launch (no GPU here) or leave its messages queued."""
+    L = B.lib()
+
+    def desc(**kw):
+        d = B.LayerDesc(direction=B.FORWARD, schedule=B.SERIAL, rowptr_dev=256, col_dev=256, val_dev=256, nnz=100, overlap_begin=0,
+                        overlap_end=4, dependent_begin=4, dependent_end=4, overlap_nnz=100, feat_dev=256, n_feat_rows=8, ld=32, dim=32,
+                        out_dev=256, ldo=32, tile_off_overlap_dev=256, workspace_overlap_dev=256, workspace_overlap_bytes=1 << 30)
+        for k, v in kw.items():
+            setattr(d, k, v)
+        return L.adaqp_layer_step(ctypes.byref(d))
+
+    def segments(n_rows=4, ptr=256):
+        return B.SpmmSegments(3, 100, n_rows, ptr, 256, 256, 256, 256)
+
+    def blocks(n_blocks=1, cols=256):
+        return B.SpmmBlocks(n_blocks, 8, 8, 0, 1, 256, 256, cols, 256)
+
+    assert desc(segments_overlap=segments(n_rows=5)) == B.EINVAL         # of another range
+    assert desc(segments_overlap=segments(), segments_dependent=segments()) == B.EINVAL
+    for plan in ({"segments_overlap": segments()}, {"blocks_overlap": blocks()}):
+        assert desc(**plan, ld=40) == B.EINVAL                          # rows that do not start on lines
+        assert desc(**plan, ldo=40) == B.EINVAL
+        assert desc(**plan, feat_dev=64) == B.EINVAL
+        assert desc(**plan, out_dev=64) == B.EINVAL
+        assert desc(**plan, workspace_overlap_dev=128) == B.EINVAL
+        assert desc(**plan, n_feat_rows=1 << 26) == B.ESIZE             # H of 2^33 bytes
+    assert desc(segments_overlap=segments(ptr=260)) == B.EINVAL
+    assert desc(blocks_overlap=blocks(cols=264)) == B.EINVAL
+    assert desc(blocks_overlap=blocks(n_blocks=1 << 17)) == B.ESIZE     # more workgroups than a launch has
+    assert not L.adaqp_spmm_blocks_pay(1 << 24, 1000, 32) and L.adaqp_spmm_blocks_pay(1 << 22, 1000, 32)
+
+
 def test_segments_of_rows_that_the_output_does_not_have():
     """A first row from which the plan's rows do not fit the matrix is refused before anything is launched."""
     import torch
