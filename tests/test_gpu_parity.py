@@ -965,6 +965,33 @@ def test_spmm_segments(oracle, dim, ld, n_rows, n_cols):
         assert np.all(got[mine][:, dim:zero_to] == 0.0) and np.all(got[mine][:, zero_to:] == 7.0) and np.all(got[~mine] == 7.0)
 
 
+def test_spmm_segments_of_more_rows_than_a_launch_has_waves():
+    """2^26 rows and more: a wave each would be 2^32 threads."""
+    _say("segments of 2^26 rows")
+    n_rows, dim = (1 << 26) + 100, 32
+    rng = np.random.default_rng(13)
+    ptr, cols = np.array([0, 2, 3, 5, 8], np.int64), np.array([0, 3, 1, 0, 2, 1, 2, 3], np.int32)
+    val, H = rng.standard_normal(8).astype(np.float32), rng.standard_normal((4, dim)).astype(np.float32)
+    of_row = torch.full((n_rows, B.SPMM_SEGMENTS), -1, dtype=torch.int32, device=DEV)
+    first, last = 12345, (1 << 26) + 7                                  # rows with segments, and one that is someone else's
+    of_row[first, 0], of_row[last, 0], of_row[last, 5], of_row[n_rows - 1, 0] = 2, 0, 3, -2
+    on = {k: torch.from_numpy(v).to(DEV) for k, v in (("ptr", ptr), ("col", cols), ("val", val))}
+    segments = B.DeviceSegments(None)
+    segments.c = B.SpmmSegments(4, 8, n_rows, on["ptr"].data_ptr(), on["ptr"].data_ptr(), of_row.data_ptr(), on["col"].data_ptr(),
+                                on["val"].data_ptr())
+    out = torch.full((n_rows, dim), 7.0, device=DEV)
+    B.adaqp_spmm_csr_segments(segments, 0, torch.from_numpy(H).to(DEV), dim, out,
+                              torch.empty(B.adaqp_spmm_segments_workspace_bytes(segments, dim), dtype=torch.uint8, device=DEV))
+    terms = val.astype(np.float64)[:, None] * H[cols]
+    for row, parts in ((first, [2]), (last, [0, 3])):
+        entries = np.concatenate([terms[ptr[s]:ptr[s + 1]] for s in parts])
+        assert np.all(np.abs(out[row].cpu().numpy() - entries.sum(0)) <= SPMM_RTOL * np.abs(entries).sum(0))
+        out[row] = 0.0
+    assert bool((out[-1] == 7.0).all())
+    out[-1] = 0.0
+    assert not bool(out.any())
+
+
 @pytest.mark.parametrize("dim,ld", [(128, 128), (602, 608), (64, 64), (7, 32), (96, 96), (130, 160), (256, 288), (1025, 1056)])
 @pytest.mark.parametrize("n_rows,n_heavy,n_cols", [(300, 140, 900), (40, 3, 33), (150, 128, 5_000)])
 def test_spmm_blocks(oracle, dim, ld, n_rows, n_heavy, n_cols):
