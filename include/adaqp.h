@@ -276,7 +276,7 @@ int32_t adaqp_spmm_tiled_pays(int64_t n_rows, int64_t nnz);
  * belong to tiles before t.  For a row of at least ADAQP_SPMM_TILED_SHORT_ROW entries that is the number of
  * entries with column < bounds[t]; a shorter row is assigned whole to tile (row - row_begin) mod
  * ADAQP_SPMM_TILES (eight segments of one or two entries each would cost more than they save).
- * Errors: EINVAL (unsorted / repeated / out-of-range column, bad rowptr). */
+ * Errors: EINVAL (unsorted / repeated / out-of-range column, bad rowptr), ESIZE (no memory for a count per column). */
 int adaqp_plan_spmm_tiles(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end,
                           int64_t n_cols, int32_t *col_bounds_out, int32_t *tile_off_out);
 
@@ -336,7 +336,7 @@ int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_begin, int6
  * of H, negative where they cost more.  A step that aggregates several ranges adds them up and takes segments in all of them from
  * ADAQP_SPMM_SEGMENTS_MIN_GAIN on (what the further launches cost).  transposed: the range belongs to a backward step.  Rows
  * that do not list ascending, distinct, in-range columns have no segments: -infinity, or EINVAL where adaqp_spmm_tiled_pays asks for
- * them. */
+ * them.  -infinity, too, where there is no memory for a count per column. */
 #define ADAQP_SPMM_SEGMENTS_MIN_GAIN 2e6
 int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end, int64_t n_cols,
                              int32_t dim, int32_t transposed, double *gain_out);
@@ -461,7 +461,7 @@ typedef struct adaqp_spmm_blocks {
  * sizes_inout[6] = { rows taken, n_blocks, n_pieces, n_steps, col_begin, piece_width }, then with those sizes and arrays of
  * n_blocks * 128, n_blocks * n_pieces + 1 and n_steps * 32.  tile_off_inout: NULL or adaqp_plan_spmm_tiles' table of the
  * range, from which the rows taken are struck (entries -1; second call only).  dim only picks the number of intervals.
- * Errors: EINVAL (bad rowptr or columns, sizes of another plan), ESIZE. */
+ * Errors: EINVAL (bad rowptr or columns, sizes of another plan), ESIZE (also: no memory for a byte per column). */
 int adaqp_plan_spmm_blocks(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end,
                            int64_t n_cols, int32_t dim, int32_t min_row_len, int64_t *sizes_inout,
                            int32_t *tile_off_inout, int32_t *rows_out, int32_t *step_ptr_out, int32_t *cols_out);

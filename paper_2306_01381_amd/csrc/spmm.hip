@@ -24,6 +24,7 @@
 #include <cmath>
 #include <functional>
 #include <mutex>
+#include <new>
 #include <numeric>
 #include <vector>
 
@@ -741,7 +742,13 @@ extern "C" int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_
         }
     }
     if (!asked_for && cut * lines + *gain_out <= 0.0) return ADAQP_OK;         // whatever the columns are
-    std::vector<int32_t> uses((size_t)n_cols, 0);
+    std::vector<int32_t> uses;
+    try {
+        uses.resize((size_t)n_cols, 0);
+    } catch (const std::bad_alloc &) {          // nothing may be thrown through a C entry; the plan would have no room either
+        *gain_out = -INFINITY;
+        return ADAQP_OK;
+    }
     const int64_t stride = std::max<int64_t>((last - first) / kSample, 1);
     int64_t seen = 0;
     for (int64_t j = first; j < last; j += stride, ++seen) ++uses[(size_t)col_host[j]];

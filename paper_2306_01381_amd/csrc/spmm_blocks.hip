@@ -31,6 +31,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <new>
 #include <type_traits>
 #include <vector>
 
@@ -455,7 +456,7 @@ using namespace adaqp;
 extern "C" int adaqp_plan_spmm_blocks(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end,
                                       int64_t n_cols, int32_t dim, int32_t min_row_len, int64_t *sizes_inout,
                                       int32_t *tile_off_inout, int32_t *rows_out, int32_t *step_ptr_out, int32_t *cols_out)
-{
+try {
     if (row_begin < 0 || row_end < row_begin || n_cols < 0 || n_cols > INT32_MAX || dim <= 0 || min_row_len < 1) return ADAQP_EINVAL;
     if (!rowptr_host || !sizes_inout) return ADAQP_EINVAL;
     const bool fill = rows_out != nullptr;
@@ -541,6 +542,8 @@ extern "C" int adaqp_plan_spmm_blocks(const int64_t *rowptr_host, const int32_t 
         for (const int64_t r : heavy)
             std::fill_n(tile_off_inout + (r - row_begin) * (ADAQP_SPMM_TILES + 1), ADAQP_SPMM_TILES + 1, -1);
     return ADAQP_OK;
+} catch (const std::bad_alloc &) {           // nothing may be thrown through a C entry
+    return ADAQP_ESIZE;
 }
 
 // A row of a block costs every column of the block: at 1.08 PFLOP/s and 7.5 ps per entry and line in tile order 4.5 % of the columns break

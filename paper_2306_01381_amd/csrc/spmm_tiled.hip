@@ -17,6 +17,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <type_traits>
+#include <new>
 #include <vector>
 
 #include "adaqp.h"
@@ -306,7 +307,7 @@ using namespace adaqp;
 extern "C" int adaqp_plan_spmm_tiles(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin,
                                      int64_t row_end, int64_t n_cols, int32_t *col_bounds_out,
                                      int32_t *tile_off_out)
-{
+try {
     if (row_begin < 0 || row_end < row_begin || n_cols < 0 || n_cols > INT32_MAX) return ADAQP_EINVAL;
     if (!rowptr_host || !col_bounds_out) return ADAQP_EINVAL;
     const int64_t n_rows = row_end - row_begin;
@@ -357,6 +358,8 @@ extern "C" int adaqp_plan_spmm_tiles(const int64_t *rowptr_host, const int32_t *
         }
     }
     return ADAQP_OK;
+} catch (const std::bad_alloc &) {           // nothing may be thrown through a C entry
+    return ADAQP_ESIZE;
 }
 
 extern "C" int32_t adaqp_spmm_tiled_pays(int64_t n_rows, int64_t nnz)

@@ -515,6 +515,26 @@ def test_ranges_of_unsorted_rows_are_not_tiled():
         B.adaqp_spmm_segments_gain(np.array([-5, 2], np.int64), col, 0, 1, n_cols, 256)
 
 
+def test_spmm_planners_without_room():
+    """Scratch per column that cannot be had is an error code or no gain, and no exception leaves the library."""
+    code = """
+import resource, numpy as np
+from paper_2306_01381_amd import binding as B
+rowptr, col, n_cols = np.array([0, 300], np.int64), np.arange(300, dtype=np.int32), 2**31 - 1
+B.adaqp_plan_spmm_blocks(rowptr, col, 0, 1, 300, 64, 1)
+limit = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize() + (256 << 20)
+resource.setrlimit(resource.RLIMIT_AS, (limit, limit))
+assert B.adaqp_spmm_segments_gain(rowptr, col, 0, 1, n_cols, 64) == -np.inf
+for plan in (lambda: B.adaqp_plan_spmm_blocks(rowptr, col, 0, 1, n_cols, 64, 1), lambda: B.adaqp_plan_spmm_tiles(rowptr, col, 0, 1, n_cols)):
+    try:
+        plan()
+    except B.AdaqpError as e:
+        print("refused", e)
+"""
+    done = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert done.returncode == 0 and done.stdout.count("refused") == done.stdout.count("too small") == 2, (done.stdout, done.stderr[-2000:])
+
+
 @pytest.mark.parametrize("n_rows,n_cols,min_len", [(1, 1, 1), (40, 33, 5), (130, 900, 60), (300, 2_000, 40)])
 def test_plan_spmm_blocks(n_rows, n_cols, min_len):
     """A block lists exactly the distinct columns of its rows, each in its interval, ascending, steps filled with the last one."""
