@@ -113,7 +113,8 @@ class LayerStep:
         self.fused_receive = fused_receive and not self.backward
         self.rowptr = torch.from_numpy(p.rowptr).to(dev)
         self.col = torch.from_numpy(p.col).to(dev)
-        self.val = torch.from_numpy(p.val).to(dev)
+        with torch.inference_mode(False):           # a tensor made in inference mode does not count what is written to it
+            self.val = torch.from_numpy(p.val).to(dev)
         self.feat = line_padded(p.feat, dev, pad, spread=True)
         self.out = line_padded(np.zeros((p.n_rows, cfg.dim), dtype=np.float32), dev, pad, spread=True)
         self.plan = SendPlan(cfg.dim, p.send_idx, p.bits, p.peer_of_slot, cfg.n_peers, p.halo_idx, dev,
@@ -238,7 +239,7 @@ class LayerStep:
                             (self.blocks_dependent, self.segments_dependent, self.p.dependent_rows)) if c[0] or c[1]]
 
     def _coefficients(self):
-        """val and how often it was written to (None: a tensor made in inference mode, which does not count that)."""
+        """val and how often it was written to (None: a tensor that a caller made in inference mode, which does not count that)."""
         return self.val, None if self.val.is_inference() else self.val._version
 
     def refresh_coefficients(self) -> None:

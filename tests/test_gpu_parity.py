@@ -1208,6 +1208,25 @@ def test_layer_step_follows_new_coefficients():
             assert torch.equal(L.out, before * factor)
 
 
+def test_step_made_in_inference_mode_copies_coefficients_when_they_change():
+    """Not before every step."""
+    _say("inference mode, copies")
+    p = make_partition(replace(CONFIGS["c0"], mean_degree=1500.0))
+    with torch.inference_mode():
+        L = LayerStep(p, DEV, seed=5, tiled=True)
+        assert L.blocks_overlap and L.segments_overlap
+        copies, refresh = [], L.refresh_coefficients
+        L.refresh_coefficients = lambda: (copies.append(1), refresh())
+        for writes, want in ((0, 0), (1, 1), (0, 1), (2, 2)):
+            for _ in range(writes):
+                L.val.mul_(2.0)
+            torch.cuda.synchronize()
+            L.run()
+            L.desc(B.ISOLATED)
+            L.synchronize()
+            assert len(copies) == want
+
+
 @pytest.mark.parametrize("schedule", [B.CHAIN, B.ISOLATED])
 def test_captured_step_and_new_coefficients(schedule):
     """Copies made inside a capture are made by its replays: an eager step does not count on them."""
