@@ -345,6 +345,10 @@ int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_t *col_host
 int adaqp_fill_spmm_segments(const adaqp_spmm_segments *segments_host, const int32_t *col_dev, const float *val_dev, int64_t nnz,
                              void *stream);
 
+/* After writes to val: segments_host->val_dev again, of the same CSR, where it differs from val_dev.  No more than a read of both where
+ * nothing does. */
+int adaqp_update_spmm_segments(const adaqp_spmm_segments *segments_host, const float *val_dev, int64_t nnz, void *stream);
+
 /* Bytes of workspace adaqp_spmm_csr_segments needs. */
 int adaqp_spmm_segments_workspace_bytes(int64_t n_seg, int64_t n_entries, int32_t dim, int64_t *bytes_out);
 
@@ -484,6 +488,12 @@ int64_t adaqp_spmm_blocks_table_floats(int64_t n_steps);
 /* Writes blocks_host->table_dev from the CSR the plan was made for, once per graph (or whenever val changes). */
 int adaqp_fill_spmm_blocks(const adaqp_spmm_blocks *blocks_host, int64_t row_begin, int64_t row_end, const int64_t *rowptr_dev,
                            const int32_t *col_dev, const float *val_dev, int64_t nnz, void *stream);
+
+/* After writes to val: the table again, where val_dev differs from copied_dev, a copy of the entries of rows [row_begin, row_end) from the
+ * time of the fill (entry j of val at j - rowptr[row_begin]) that this call brings up to date for the blocks' rows.  No more than a
+ * read of both where nothing differs. */
+int adaqp_update_spmm_blocks(const adaqp_spmm_blocks *blocks_host, int64_t row_begin, int64_t row_end, const int64_t *rowptr_dev,
+                             const int32_t *col_dev, const float *val_dev, int64_t nnz, float *copied_dev, void *stream);
 
 /* Bytes of workspace adaqp_spmm_csr_blocks needs. */
 int adaqp_spmm_blocks_workspace_bytes(int32_t n_blocks, int32_t n_pieces, int32_t dim, int64_t *bytes_out);

@@ -121,6 +121,7 @@ _SIGNATURES = {
     "adaqp_spmm_segments_gain": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp]),
     "adaqp_plan_spmm_segments": (ctypes.c_int, [_vp, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp]),
     "adaqp_fill_spmm_segments": (ctypes.c_int, [ctypes.POINTER(SpmmSegments), _vp, _vp, _i64, _vp]),
+    "adaqp_update_spmm_segments": (ctypes.c_int, [ctypes.POINTER(SpmmSegments), _vp, _i64, _vp]),
     "adaqp_spmm_segments_workspace_bytes": (ctypes.c_int, [_i64, _i64, _i32, _vp]),
     "adaqp_spmm_csr_segments": (ctypes.c_int, [ctypes.POINTER(SpmmSegments), _vp, _i64, _i64, _i32, _vp, _i64, _vp, _i64, _vp]),
     "adaqp_plan_spmm_blocks": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp]),
@@ -130,6 +131,7 @@ _SIGNATURES = {
     "adaqp_spmm_blocks_most_steps": (_i64, [_i64]),
     "adaqp_spmm_blocks_table_floats": (_i64, [_i64]),
     "adaqp_fill_spmm_blocks": (ctypes.c_int, [ctypes.POINTER(SpmmBlocks), _i64, _i64, _vp, _vp, _vp, _i64, _vp]),
+    "adaqp_update_spmm_blocks": (ctypes.c_int, [ctypes.POINTER(SpmmBlocks), _i64, _i64, _vp, _vp, _vp, _i64, _vp, _vp]),
     "adaqp_spmm_blocks_workspace_bytes": (ctypes.c_int, [_i32, _i32, _i32, _vp]),
     "adaqp_spmm_csr_blocks": (ctypes.c_int, [ctypes.POINTER(SpmmBlocks), _i64, _i64, _vp, _i64, _i64, _i32, _vp, _i64, _vp, _i64,
                                              _vp]),
@@ -527,6 +529,11 @@ def adaqp_fill_spmm_segments(segments: DeviceSegments, col: torch.Tensor, val: t
            "adaqp_fill_spmm_segments")
 
 
+def adaqp_update_spmm_segments(segments: DeviceSegments, val: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
+    _check(lib().adaqp_update_spmm_segments(ctypes.byref(segments.c), _dev(val, torch.float32, "val"), val.numel(), _stream(stream)),
+           "adaqp_update_spmm_segments")
+
+
 def adaqp_spmm_segments_workspace_bytes(segments: DeviceSegments, dim: int) -> int:
     out = ctypes.c_int64(0)
     _check(lib().adaqp_spmm_segments_workspace_bytes(segments.c.n_seg, segments.c.n_entries, dim, ctypes.byref(out)),
@@ -619,6 +626,14 @@ def adaqp_fill_spmm_blocks(blocks: DeviceBlocks, row_begin: int, row_end: int, r
     _check(lib().adaqp_fill_spmm_blocks(ctypes.byref(blocks.c), row_begin, row_end, _dev(rowptr, torch.int64, "rowptr"),
                                         _dev(col, torch.int32, "col"), _dev(val, torch.float32, "val"), col.numel(),
                                         _stream(stream)), "adaqp_fill_spmm_blocks")
+
+
+def adaqp_update_spmm_blocks(blocks: DeviceBlocks, row_begin: int, row_end: int, rowptr: torch.Tensor, col: torch.Tensor,
+                             val: torch.Tensor, copied: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
+    """copied: what val held for the entries of the rows at the time of the fill, brought up to date."""
+    _check(lib().adaqp_update_spmm_blocks(ctypes.byref(blocks.c), row_begin, row_end, _dev(rowptr, torch.int64, "rowptr"),
+                                          _dev(col, torch.int32, "col"), _dev(val, torch.float32, "val"), col.numel(),
+                                          _dev(copied, torch.float32, "copied"), _stream(stream)), "adaqp_update_spmm_blocks")
 
 
 def adaqp_spmm_blocks_workspace_bytes(blocks: DeviceBlocks, dim: int) -> int:

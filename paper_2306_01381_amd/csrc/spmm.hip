@@ -600,6 +600,24 @@ __global__ __launch_bounds__(kBlock) void segments_fill_kernel(const int64_t *pt
     }
 }
 
+// val_out where it is not what val says: LANES lanes per segment.  Reads of both streams bound it; where nothing was written since,
+// nothing is.
+template <int LANES>
+__global__ __launch_bounds__(kBlock) void segments_update_kernel(const int64_t *ptr, const int64_t *src, int64_t n_seg, int64_t n_entries,
+                                                                 const uint32_t *val, int64_t nnz, uint32_t *val_out)
+{
+    const int lane = threadIdx.x & (LANES - 1);
+    const int64_t groups = (int64_t)gridDim.x * (kBlock / LANES);
+    for (int64_t s = (int64_t)blockIdx.x * (kBlock / LANES) + threadIdx.x / LANES; s < n_seg; s += groups) {
+        const int64_t to = clamp64(ptr[s], 0, n_entries), n = clamp64(ptr[s + 1], to, n_entries) - to;
+        const int64_t from = src[s];
+        for (int64_t i = lane; i < n; i += LANES) {
+            const uint32_t now = from >= 0 && from + i < nnz ? val[from + i] : 0;
+            if (now != val_out[to + i]) val_out[to + i] = now;
+        }
+    }
+}
+
 // A launch has fewer than 2^32 threads: rows past what this many workgroups take at one per wave are taken in turns.
 constexpr int64_t kMostSumBlocks = (int64_t)1 << 22;
 
@@ -765,6 +783,22 @@ extern "C" int adaqp_fill_spmm_segments(const adaqp_spmm_segments *p, const int3
     if (!p->ptr_dev || !p->src_dev || !p->col_dev || !p->val_dev || (nnz > 0 && (!col_dev || !val_dev))) return ADAQP_EINVAL;
     hipLaunchKernelGGL(segments_fill_kernel, dim3((unsigned)std::min<int64_t>((p->n_seg + kWavesPerBlock - 1) / kWavesPerBlock, 65536)), dim3(kBlock),
                        0, (hipStream_t)stream, p->ptr_dev, p->src_dev, p->n_seg, p->n_entries, col_dev, val_dev, nnz, p->col_dev, p->val_dev);
+    ADAQP_HIP_TRY(hipGetLastError());
+    return ADAQP_OK;
+}
+
+extern "C" int adaqp_update_spmm_segments(const adaqp_spmm_segments *p, const float *val_dev, int64_t nnz, void *stream)
+{
+    if (!p || p->n_seg < 0 || p->n_entries < 0 || nnz < 0) return ADAQP_EINVAL;
+    if (p->n_seg == 0 || p->n_entries == 0) return ADAQP_OK;
+    if (!p->ptr_dev || !p->src_dev || !p->val_dev || (nnz > 0 && !val_dev)) return ADAQP_EINVAL;
+    const bool long_segments = p->n_entries >= 48 * p->n_seg;
+    const int64_t per_block = kBlock / (long_segments ? kWave : 8);
+    const dim3 grid((unsigned)std::min<int64_t>((p->n_seg + per_block - 1) / per_block, 65536));
+    const uint32_t *val = reinterpret_cast<const uint32_t *>(val_dev);
+    uint32_t *copy = reinterpret_cast<uint32_t *>(p->val_dev);
+    if (long_segments) hipLaunchKernelGGL(segments_update_kernel<kWave>, grid, dim3(kBlock), 0, (hipStream_t)stream, p->ptr_dev, p->src_dev, p->n_seg, p->n_entries, val, nnz, copy);
+    else hipLaunchKernelGGL(segments_update_kernel<8>, grid, dim3(kBlock), 0, (hipStream_t)stream, p->ptr_dev, p->src_dev, p->n_seg, p->n_entries, val, nnz, copy);
     ADAQP_HIP_TRY(hipGetLastError());
     return ADAQP_OK;
 }

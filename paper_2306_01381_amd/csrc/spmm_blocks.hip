@@ -356,19 +356,22 @@ __global__ __launch_bounds__(kBlock) void block_table_clear_kernel(float4_t *tab
         table[i] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
 }
 
-// A workgroup per row of a block.
+// A workgroup per row of a block.  copied: NULL, or what val held for the range's entries when the table was written last: entries that are
+// still the same are left alone, the others are written to both.
 __global__ __launch_bounds__(kBlock) void block_table_fill_kernel(const BlockArgs a, float *table, int32_t col_begin, int32_t width,
-                                                                  const int64_t *rowptr, const int32_t *col, const float *val, int64_t nnz)
+                                                                  const int64_t *rowptr, const int32_t *col, const float *val, int64_t nnz,
+                                                                  float *copied)
 {
     const int64_t row = a.rows[blockIdx.x];
     if (row < a.row_begin || row >= a.row_end) return;
     const int32_t block = (int32_t)(blockIdx.x / kBlockRows), m = (int32_t)(blockIdx.x % kBlockRows);
-    const int64_t lo = max((int64_t)0, min(rowptr[row], nnz)), hi = max(lo, min(rowptr[row + 1], nnz));
-    for (int64_t j = lo + threadIdx.x; j < hi; j += kBlock) {
+    const int64_t base = max((int64_t)0, min(rowptr[a.row_begin], nnz));
+    const int64_t lo = max(base, min(rowptr[row], nnz)), hi = max(lo, min(min(rowptr[row + 1], rowptr[a.row_end]), nnz));
+    auto place = [&](int64_t j, float coefficient) {
         const int32_t c = col[j];
-        if (c < col_begin) continue;
+        if (c < col_begin) return;
         const int32_t interval = (c - col_begin) / width;
-        if (interval >= a.n_pieces) continue;
+        if (interval >= a.n_pieces) return;
         const int32_t piece = block * a.n_pieces + interval;
         const int32_t s0 = max(0, min(a.step_ptr[piece], a.n_steps)), s1 = max(s0, min(a.step_ptr[piece + 1], a.n_steps));
         // the first of the piece's columns that is not below c (behind the last one it is repeated)
@@ -379,10 +382,28 @@ __global__ __launch_bounds__(kBlock) void block_table_fill_kernel(const BlockArg
             if (a.cols[mid] < c) from = mid + 1;
             else to = mid;
         }
-        if (from >= end || a.cols[from] != c) continue;             // not of this plan
+        if (from >= end || a.cols[from] != c) return;               // not of this plan
         const int64_t s = from / kStepCols;
         const int32_t k = (int32_t)(from % kStepCols), lane = (k / 8 % 2) * 32 + m % 32;
-        table[((((s * kRowGroups + m / 32) * 2 + k / 16) * kWave) + lane) * 8 + k % 8] = val[j] == 0.0f ? -0.0f : val[j];
+        table[((((s * kRowGroups + m / 32) * 2 + k / 16) * kWave) + lane) * 8 + k % 8] = coefficient == 0.0f ? -0.0f : coefficient;
+    };
+    constexpr int kAhead = 4;                                       // loads of a lane in flight together
+    for (int64_t j = lo + threadIdx.x; j < hi; j += kAhead * kBlock) {
+        uint32_t now[kAhead], was[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const int64_t at = min(j + q * kBlock, hi - 1);
+            now[q] = __builtin_bit_cast(uint32_t, val[at]);
+            was[q] = copied ? __builtin_bit_cast(uint32_t, copied[at - base]) : ~now[q];
+        }
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const int64_t at = j + q * kBlock;
+            if (at >= hi || now[q] == was[q]) continue;
+            const float coefficient = __builtin_bit_cast(float, now[q]);
+            if (copied) copied[at - base] = coefficient;
+            place(at, coefficient);
+        }
     }
 }
 
@@ -585,8 +606,11 @@ extern "C" int64_t adaqp_spmm_blocks_most_steps(int64_t nnz)
 
 extern "C" int64_t adaqp_spmm_blocks_table_floats(int64_t n_steps) { return n_steps < 0 ? -1 : n_steps * kStepCols * kBlockRows; }
 
-extern "C" int adaqp_fill_spmm_blocks(const adaqp_spmm_blocks *p, int64_t row_begin, int64_t row_end, const int64_t *rowptr_dev,
-                                      const int32_t *col_dev, const float *val_dev, int64_t nnz, void *stream)
+namespace {
+
+// copied: of adaqp_update_spmm_blocks, NULL to write the whole table.
+int write_table(const adaqp_spmm_blocks *p, int64_t row_begin, int64_t row_end, const int64_t *rowptr_dev, const int32_t *col_dev,
+                const float *val_dev, int64_t nnz, float *copied_dev, hipStream_t st)
 {
     if (!p) return ADAQP_EINVAL;
     const int rc = check_blocks(p);
@@ -596,15 +620,31 @@ extern "C" int adaqp_fill_spmm_blocks(const adaqp_spmm_blocks *p, int64_t row_be
     if (!rowptr_dev || !aligned_to(rowptr_dev, 8) || (nnz > 0 && (!col_dev || !val_dev || !aligned_to(col_dev, 4) || !aligned_to(val_dev, 4))))
         return ADAQP_EINVAL;
     const BlockArgs a = block_args(p, row_begin, row_end);
-    const int64_t vectors = adaqp_spmm_blocks_table_floats(p->n_steps) / 4;
-    hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(block_table_clear_kernel, dim3((unsigned)std::min<int64_t>((vectors + kBlock - 1) / kBlock, 16384)), dim3(kBlock), 0, st,
-                       reinterpret_cast<float4_t *>(p->table_dev), vectors);
-    ADAQP_HIP_TRY(hipGetLastError());
+    if (!copied_dev) {
+        const int64_t vectors = adaqp_spmm_blocks_table_floats(p->n_steps) / 4;
+        hipLaunchKernelGGL(block_table_clear_kernel, dim3((unsigned)std::min<int64_t>((vectors + kBlock - 1) / kBlock, 16384)), dim3(kBlock), 0, st,
+                           reinterpret_cast<float4_t *>(p->table_dev), vectors);
+        ADAQP_HIP_TRY(hipGetLastError());
+    }
     hipLaunchKernelGGL(block_table_fill_kernel, dim3((unsigned)(p->n_blocks * kBlockRows)), dim3(kBlock), 0, st, a, p->table_dev,
-                       p->col_begin, p->piece_width, rowptr_dev, col_dev, val_dev, nnz);
+                       p->col_begin, p->piece_width, rowptr_dev, col_dev, val_dev, nnz, copied_dev);
     ADAQP_HIP_TRY(hipGetLastError());
     return ADAQP_OK;
+}
+
+}  // namespace
+
+extern "C" int adaqp_fill_spmm_blocks(const adaqp_spmm_blocks *p, int64_t row_begin, int64_t row_end, const int64_t *rowptr_dev,
+                                      const int32_t *col_dev, const float *val_dev, int64_t nnz, void *stream)
+{
+    return write_table(p, row_begin, row_end, rowptr_dev, col_dev, val_dev, nnz, nullptr, (hipStream_t)stream);
+}
+
+extern "C" int adaqp_update_spmm_blocks(const adaqp_spmm_blocks *p, int64_t row_begin, int64_t row_end, const int64_t *rowptr_dev,
+                                        const int32_t *col_dev, const float *val_dev, int64_t nnz, float *copied_dev, void *stream)
+{
+    if (!copied_dev || !aligned_to(copied_dev, 4)) return ADAQP_EINVAL;
+    return write_table(p, row_begin, row_end, rowptr_dev, col_dev, val_dev, nnz, copied_dev, (hipStream_t)stream);
 }
 
 extern "C" int adaqp_spmm_blocks_workspace_bytes(int32_t n_blocks, int32_t n_pieces, int32_t dim, int64_t *bytes_out)

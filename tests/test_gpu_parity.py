@@ -1254,6 +1254,73 @@ def test_captured_step_and_new_coefficients(schedule):
         assert torch.equal(L.out, before * factor)
 
 
+@pytest.mark.parametrize("schedule", [B.CHAIN, B.ISOLATED])
+@pytest.mark.parametrize("fused", [False, True])
+def test_replays_follow_coefficients_written_after_the_capture(schedule, fused):
+    """Also where val had not been written to before it; both ranges of a step whose dependent rows read val itself."""
+    _say(f"replays, new coefficients, schedule {schedule}, fused {fused}")
+    p = make_partition(replace(CONFIGS["c0"], mean_degree=1500.0))
+    L = LayerStep(p, DEV, seed=5, tiled=True, fused_receive=fused)
+    assert L.blocks_overlap and L.segments_overlap and (fused or L.segments_dependent)
+    L.run(schedule)
+    L.synchronize()
+    before = L.out.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=L.stream_msg):
+        L.run(schedule)
+    for factor in (2.0, 1.0, 0.0, 4.0):
+        L.val.copy_(torch.from_numpy(p.val).to(DEV) * factor)
+        L.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(L.out, before * factor)
+    captured, L.val = L.val, L.val * 0.5                               # another tensor: eager steps follow it, replays the first
+    for _ in range(2):
+        L.run(schedule)
+        L.synchronize()
+        assert torch.equal(L.out, before * 2.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(L.out, before * 4.0)
+    L.val = captured
+    L.run(schedule)
+    L.synchronize()
+    assert torch.equal(L.out, before * 4.0)
+
+
+def test_updates_of_the_copies_write_what_has_changed():
+    """Blocks and segments brought up to date are those of a fill, wherever an entry changes: first and last of the range, zeros of
+    either sign, NaN."""
+    _say("updates of the copies")
+    rng = np.random.default_rng(14)
+    n_rows, n_cols, dim = 300, 3_000, 64
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, np.where(np.arange(n_rows) < 140, 1_500, rng.integers(0, 90, size=n_rows)))
+    rb, re = 3, n_rows - 2
+    bounds, off = B.adaqp_plan_spmm_tiles(rowptr, col, rb, re, n_cols)
+    plan = B.adaqp_plan_spmm_blocks(rowptr, col, rb, re, n_cols, dim, 1_000, off)
+    entries = B.adaqp_plan_spmm_segments(rowptr, rb, re, bounds, off)
+    rp, cl, vl = (torch.from_numpy(x).to(DEV) for x in (rowptr, col, val))
+
+    def filled():
+        blocks, segments = B.DeviceBlocks(plan, DEV), B.DeviceSegments(entries, DEV)
+        B.adaqp_fill_spmm_blocks(blocks, rb, re, rp, cl, vl)
+        B.adaqp_fill_spmm_segments(segments, cl, vl)
+        return blocks, segments
+
+    blocks, segments = filled()
+    copied = vl[rowptr[rb]:rowptr[re]].clone()
+    some = torch.from_numpy(rng.choice(val.size, 500, replace=False)).to(DEV)
+    ends = torch.tensor([rowptr[rb], rowptr[rb + 1] - 1, rowptr[re] - 1, rowptr[140], 0, val.size - 1], device=DEV)
+    for at, to in ((ends, 3.0), (some, 0.0), (some[:250], -0.0), (some[100:], 2.5), (some[::7], float("nan")), (some, -1.0)):
+        vl[at] = to
+        B.adaqp_update_spmm_blocks(blocks, rb, re, rp, cl, vl, copied)
+        B.adaqp_update_spmm_segments(segments, vl)
+        want_blocks, want_segments = filled()
+        for got, want, key in ((blocks, want_blocks, "table"), (segments, want_segments, "val")):
+            assert torch.equal(got.tensors[key].view(torch.int32), want.tensors[key].view(torch.int32))
+
+
 @pytest.mark.parametrize("name", ["c0", "c0_backward"])
 def test_layer_step_matches_oracle_in_every_schedule(oracle, name):
     _say(f"layer step {name}")
