@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kBlock) void block_table_fill_kernel(const BlockArg
     if (row < a.row_begin || row >= a.row_end) return;
     const int32_t block = (int32_t)(blockIdx.x / kBlockRows), m = (int32_t)(blockIdx.x % kBlockRows);
     const int64_t base = max((int64_t)0, min(rowptr[a.row_begin], nnz));
-    const int64_t lo = max(base, min(rowptr[row], nnz)), hi = max(lo, min(min(rowptr[row + 1], rowptr[a.row_end]), nnz));
+    const int64_t lo = max(base, min(rowptr[row], nnz)), hi = max(lo, min(rowptr[row + 1], nnz));
     auto place = [&](int64_t j, float coefficient) {
         const int32_t c = col[j];
         if (c < col_begin) return;

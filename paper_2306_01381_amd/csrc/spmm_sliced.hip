@@ -378,8 +378,8 @@ __device__ __forceinline__ void walk_share(const SlicedArgs &sa, const int32_t f
     };
 
     // Sums of the open row: acc what the present chunk has given so far, per group; before what earlier chunks of the share
-    // gave, as `sum_groups` leaves it.  No addition chain is longer than a chunk's 48 steps, the chunks of a share, or the
-    // shares of a row (one running sum over a share would be thousands of terms long and rounds accordingly).
+    // gave, as `sum_groups` leaves it.  No addition chain is longer than the 48 steps of half a chunk, the halves of a share's
+    // chunks, or the shares of a row (one running sum over a share would be thousands of terms long and rounds accordingly).
     float4_t acc[VPL];
     float before[VPL];
 #pragma unroll
