@@ -28,6 +28,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0
 GATHER_RATE_GBPS = 25000.0      # 16-byte-per-lane gather out of L2, every XCD on its own 4 MB: measured on MI355X
+MFMA_FP32_PEAK_TFLOPS = 157.3   # dense fp32 on the matrix cores
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16 on the matrix cores
 FMA_RATE_PER_S = 78.65e12       # fp32 vector FMAs per second (157.3 TFLOP/s)
 METRIC = "quantize+pack / unpack+dequant GB/s, halo SpMM edges/s, % HBM peak, 1xMI355X"
@@ -520,19 +521,22 @@ def measure_config(name, args, headline, B, torch, np):
             "neighbour_rows_fetched": fetched, "t_gather_ms": fetched * 4 * dim / GATHER_RATE_GBPS / 1e6,
             "t_mfma_executed_ms": executed / MFMA_BF16_PEAK_TFLOPS / 1e9,
             "note": "floors of the two kernels: the gather at the L2 rate, the matrix-core work at the bf16 MFMA peak"}
+        # `frac` is the method's own fp32 multiply-adds against the fp32 matrix rate, as for the fp32 panels; what the bf16 matrix cores
+        # execute for them stands beside it
         roofline = {
-            "kernel": "spmm_block_kernel", "bound": "mfma", "dtype": "bf16",
-            "achieved": executed / t_p / 1e9, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
-            "frac": executed / t_p / 1e9 / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
+            "kernel": "spmm_block_kernel", "bound": "mfma", "dtype": "f32",
+            "achieved": useful / t_p / 1e9, "peak": MFMA_FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
+            "frac": useful / t_p / 1e9 / MFMA_FP32_PEAK_TFLOPS, "traffic": None,
             "launches_per_step": launches, "avg_launch_ms": t_p / launches,
             "algorithmic_flops_per_launch": useful / launches,
-            "useful": {"TFLOPs": useful / t_p / 1e9,
-                       "block_density": sum(v["block_edges"] for v in block_parts.values())
-                       / (float(B.SPMM_BLOCK_ROWS) * sum(v["block_columns_padded"] for v in block_parts.values())),
-                       "note": "2 * entries * dim"},
-            "binding_limit": "the bf16 matrix cores beside the vector instructions that split fp32 operands in three; "
-                             "`achieved` counts the six bf16 products of every fp32 one, the zeros of the dense blocks and the "
-                             "padding of dim to whole tiles of 32 columns"}
+            "executed": {"dtype": "bf16", "TFLOPs": executed / t_p / 1e9, "peak": MFMA_BF16_PEAK_TFLOPS,
+                         "frac": executed / t_p / 1e9 / MFMA_BF16_PEAK_TFLOPS,
+                         "block_density": sum(v["block_edges"] for v in block_parts.values())
+                         / (float(B.SPMM_BLOCK_ROWS) * sum(v["block_columns_padded"] for v in block_parts.values())),
+                         "note": "six bf16 products of every fp32 one, the zeros of the dense blocks and the padding of dim to whole "
+                                 "tiles of 32 columns"},
+            "binding_limit": "the bf16 matrix cores beside the vector instructions that split fp32 operands in three; `frac` counts "
+                             "the method's own multiply-adds (2 * entries * dim)"}
     else:
         alg = (b_o + b_d) / launches
         avg_ms = t_both / launches
