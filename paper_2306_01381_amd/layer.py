@@ -31,7 +31,18 @@ def _hip_runtime() -> ctypes.CDLL:
         _hip.hipEventCreateWithFlags.restype = ctypes.c_int
         _hip.hipEventDestroy.argtypes = [ctypes.c_void_p]
         _hip.hipEventDestroy.restype = ctypes.c_int
+        _hip.hipStreamIsCapturing.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_int)]
+        _hip.hipStreamIsCapturing.restype = ctypes.c_int
     return _hip
+
+
+def _capturing(stream: torch.cuda.Stream) -> bool:
+    """torch answers this for the current stream only, and making another one current costs every step 10 us and more."""
+    status = ctypes.c_int(0)
+    rc = _hip_runtime().hipStreamIsCapturing(stream.cuda_stream, ctypes.byref(status))
+    if rc != 0:
+        raise RuntimeError(f"hipStreamIsCapturing failed: {rc}")
+    return status.value != 0
 
 
 class HipEvent:
@@ -262,8 +273,7 @@ class LayerStep:
         if not self._copies():
             return
         # in a capture whatever val is now: what the replays copy must not hang on when it was last written to
-        with torch.cuda.stream(self.stream_msg):
-            captured = torch.cuda.is_current_stream_capturing()
+        captured = _capturing(self.stream_msg)
         tensor, version = self._coefficients()
         if captured:
             if not any(kept() is tensor for kept in self._captured):
