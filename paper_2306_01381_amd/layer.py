@@ -261,7 +261,7 @@ class LayerStep:
         starts from.  run() and desc() call it when val was written to or replaced, and in every capture, whose replays
         follow val then.  A caller does after writes that torch does not count (through val.data or from a kernel of its own)
         and with a descriptor kept across writes.  Where nothing has changed it costs a read of val and the copies (28 M
-        entries 0.11 to 0.13 ms, all of them changed 0.15 to 1.2)."""
+        entries 0.11 to 0.12 ms, all of them changed 0.16 to 1.2)."""
         for blocks, segments, (begin, end) in self._copies():
             if blocks:
                 B.adaqp_update_spmm_blocks(blocks, begin, end, self.rowptr, self.col, self.val, blocks.tensors["copied"],
