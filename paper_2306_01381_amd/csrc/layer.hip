@@ -177,7 +177,7 @@ int check_desc(const adaqp_layer_desc *d)
             if (s->n_rows != re - rb) return ADAQP_EINVAL;
             const int rc = check_segments_call(s, d->feat_dev, d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo);
             if (rc != ADAQP_OK) return rc;
-            if (!aligned_to(ws, 256)) return ADAQP_EINVAL;
+            if (re > rb && !aligned_to(ws, 256)) return ADAQP_EINVAL;
         }
         const adaqp_spmm_blocks *b = part ? &d->blocks_overlap : &d->blocks_dependent;
         if (b->n_blocks < 0 || b->n_pieces < 0 || b->n_steps < 0) return ADAQP_EINVAL;
@@ -186,7 +186,7 @@ int check_desc(const adaqp_layer_desc *d)
         if (b->n_blocks > 0) {
             const int rc = check_blocks_call(b, rb, re, d->feat_dev, d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo);
             if (rc != ADAQP_OK) return rc;
-            if (!aligned_to(ws, 256)) return ADAQP_EINVAL;
+            if (re > rb && !aligned_to(ws, 256)) return ADAQP_EINVAL;
         }
         if (p->n_panels == 0) continue;
         if (!tile_off) return ADAQP_EINVAL;                 // panels complement a tile table, never the merge path

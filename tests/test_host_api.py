@@ -135,6 +135,8 @@ def test_layer_step_refuses_plans_before_it_queues_anything():
         assert desc(**plan, workspace_overlap_dev=128) == B.EINVAL
         assert desc(**plan, n_feat_rows=1 << 26) == B.ESIZE             # H of 2^33 bytes
     assert desc(segments_overlap=segments(ptr=260)) == B.EINVAL
+    # a range without rows reads no workspace
+    assert desc(overlap_end=0, dependent_begin=0, dependent_end=0, blocks_overlap=blocks(), workspace_overlap_dev=128) == B.OK
     assert desc(blocks_overlap=blocks(cols=264)) == B.EINVAL
     assert desc(blocks_overlap=blocks(n_blocks=1 << 17)) == B.ESIZE     # more workgroups than a launch has
     assert not L.adaqp_spmm_blocks_pay(1 << 24, 1000, 32) and L.adaqp_spmm_blocks_pay(1 << 22, 1000, 32)
