@@ -473,10 +473,11 @@ int adaqp_plan_spmm_blocks(const int64_t *rowptr_host, const int32_t *col_host, 
 /* Host only: the row length from which a row can be worth a place in a block, where the rows of the range reference columns below
  * n_cols (column bound ADAQP_SPMM_TILES of adaqp_plan_spmm_tiles); whether a plan that takes n_rows_taken rows can be worth
  * launching on a matrix of n_cols rows with a pitch of ldh floats (1) or not, or is not possible (0); and whether blocks of
- * n_entries entries in n_steps steps take less time than the entries in tile order (1) or not (0). */
+ * n_entries entries in n_steps steps take less time than the entries in tile order (1) or not (0).  beside: another range's entries
+ * are walked at the same time, as in a forward step of two streams. */
 int32_t adaqp_spmm_blocks_min_row(int64_t n_cols);
 int32_t adaqp_spmm_blocks_pay(int64_t n_rows_taken, int64_t n_cols, int64_t ldh);
-int32_t adaqp_spmm_blocks_save(int64_t n_entries, int64_t n_steps, int32_t dim);
+int32_t adaqp_spmm_blocks_save(int64_t n_entries, int64_t n_steps, int32_t dim, int32_t beside);
 
 /* Host only: steps whose table stays within four times the bytes of col and val of a range with nnz entries, or 64 MB.  A table takes
  * 16 KB per step, 80 bytes per entry of rows that list a twentieth of the columns. */

@@ -127,7 +127,7 @@ _SIGNATURES = {
     "adaqp_plan_spmm_blocks": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp]),
     "adaqp_spmm_blocks_min_row": (_i32, [_i64]),
     "adaqp_spmm_blocks_pay": (_i32, [_i64, _i64, _i64]),
-    "adaqp_spmm_blocks_save": (_i32, [_i64, _i64, _i32]),
+    "adaqp_spmm_blocks_save": (_i32, [_i64, _i64, _i32, _i32]),
     "adaqp_spmm_blocks_most_steps": (_i64, [_i64]),
     "adaqp_spmm_blocks_table_floats": (_i64, [_i64]),
     "adaqp_fill_spmm_blocks": (ctypes.c_int, [ctypes.POINTER(SpmmBlocks), _i64, _i64, _vp, _vp, _vp, _i64, _vp]),
@@ -560,10 +560,10 @@ SPMM_BLOCK_STEP = 32
 
 def adaqp_plan_spmm_blocks(rowptr_host: np.ndarray, col_host: np.ndarray, row_begin: int, row_end: int, n_cols: int, dim: int,
                            min_row_len: int, tile_off: Optional[np.ndarray] = None,
-                           only_if_pays_for_ld: int = 0, if_slower: bool = False) -> Optional[dict]:
+                           only_if_pays_for_ld: int = 0, if_slower: bool = False, beside: bool = False) -> Optional[dict]:
     """Host-only.  None when no row of the range has min_row_len entries, else a dict of host arrays (rows, step_ptr, cols) and
     sizes.  With only_if_pays_for_ld = the pitch of H: the longest of these rows whose blocks adaqp_spmm_blocks_pay and
-    (unless if_slower) adaqp_spmm_blocks_save speak for and whose table adaqp_spmm_blocks_most_steps allows, None if there are none.
+    (unless if_slower) adaqp_spmm_blocks_save(beside) speak for and whose table adaqp_spmm_blocks_most_steps allows, None if there are none.
     tile_off (the table of adaqp_plan_spmm_tiles for the same range) is changed in place: the rows taken are struck."""
     rowptr = np.ascontiguousarray(rowptr_host, dtype=np.int64)
     col = np.ascontiguousarray(col_host, dtype=np.int32)
@@ -585,7 +585,7 @@ def adaqp_plan_spmm_blocks(rowptr_host: np.ndarray, col_host: np.ndarray, row_be
         if not lib().adaqp_spmm_blocks_pay(plan["n_rows_taken"], n_cols, only_if_pays_for_ld):
             return None
         if plan["n_steps"] <= lib().adaqp_spmm_blocks_most_steps(int(degs.sum())) and \
-                (if_slower or lib().adaqp_spmm_blocks_save(int(degs[degs >= min_row_len].sum()), plan["n_steps"], dim)):
+                (if_slower or lib().adaqp_spmm_blocks_save(int(degs[degs >= min_row_len].sum()), plan["n_steps"], dim, int(beside))):
             break
         min_row_len += min_row_len // 2 + 1                 # the longer ones fill their blocks better
     plan.update(rows=np.empty(plan["n_blocks"] * SPMM_BLOCK_ROWS, dtype=np.int32),

@@ -584,17 +584,22 @@ extern "C" int32_t adaqp_spmm_blocks_pay(int64_t n_rows_taken, int64_t n_cols, i
 }
 
 // What the entries cost in tile order against what their blocks cost: a step is a load and a split of coefficients per chunk of feature
-// columns and of the rows of H per line beside its matrix instructions.  Fitted to 228 launches of 24 000 and 90 000 columns, 130 to 1 792
-// rows that list 5.5, 12 or 25 % of them, 32 to 602 columns of H, beside 10 000 rows of 100 entries.  Geometric mean against no blocks 1.16,
-// the largest loss 10 % (blocks for every 256 rows: 1.04, 2.05 times as slow at worst).  Without and with blocks, one launch after the
-// other: 384 rows of 12 %, 90 000 columns, 64 columns of H 87 -> 112 us (no), 96 141 -> 129 (yes), 602 702 -> 520 (yes); 256 rows of 12 %,
-// 24 000 columns, 128 columns of H 65 -> 67 (no), 256 109 -> 95 (yes); 1 152 rows of 5.5 %, 90 000 columns, 256 columns 381 -> 418 (no).
-extern "C" int32_t adaqp_spmm_blocks_save(int64_t n_entries, int64_t n_steps, int32_t dim)
+// columns and of the rows of H per line beside its matrix instructions, and less of it shows where another range's entries are walked at
+// the same time.
+// One after the other: 228 launches of 24 000 and 90 000 columns, 130 to 1 792 rows that list 5.5, 12 or 25 % of them, 32 to 602 columns of H,
+// beside 10 000 rows of 100 entries.  Geometric mean against no blocks 1.16, the largest loss 10 % (blocks for every 256 rows: 1.04, 2.05 times
+// as slow at worst).  384 rows of 12 %, 90 000 columns, 64 columns of H 87 -> 112 us (no), 96 141 -> 129 (yes), 602 702 -> 520 (yes);
+// 256 rows of 12 %, 24 000 columns, 128 columns of H 65 -> 67 (no), 256 109 -> 95 (yes).
+// Beside: 133 forward steps of 6 000 to 58 000 rows, 130 to 450 entries per row, Zipf and log-normal, 32 to 602 columns of H.  Geometric mean
+// against no blocks 1.258, the largest loss 8 % (the better of both each time 1.264, blocks for every 256 rows 1.213 and 54 %).
+// 20 000 rows, 9 M entries, log-normal, 64 columns 154 -> 171 us (no); 10 000 rows, 4.5 M entries, log-normal, 400 columns 400 -> 324 (yes),
+// 32 70 -> 108 (no).
+extern "C" int32_t adaqp_spmm_blocks_save(int64_t n_entries, int64_t n_steps, int32_t dim, int32_t beside)
 {
     if (n_entries <= 0 || n_steps <= 0 || dim <= 0) return 0;
     const double lines = (double)(((int64_t)dim + 31) / 32), chunks = (double)(((int64_t)dim + kChunk - 1) / kChunk);
-    const double entries_ns = 5.6e-3 * lines * (double)n_entries;
-    return entries_ns > 15e3 + (2.7 * chunks + 0.75 * lines) * (double)n_steps ? 1 : 0;
+    const double entries_ns = 5.6e-3 * lines * (double)n_entries, step_ns = beside ? 2.0 * chunks + 0.35 * lines : 2.7 * chunks + 0.75 * lines;
+    return entries_ns > 15e3 + step_ns * (double)n_steps ? 1 : 0;
 }
 
 // A table takes 16 KB per step, however few of its places are filled: ten times what the entries of rows at the threshold take.  Four times

@@ -226,7 +226,8 @@ class LayerStep:
         elif panels is None:
             with_blocks = B.DeviceBlocks(B.adaqp_plan_spmm_blocks(
                 p.rowptr, p.col, begin, end, n_cols, dim, B.adaqp_spmm_blocks_min_row(int(bounds[-1])), off,
-                only_if_pays_for_ld=self.feat.stride(0), if_slower=bool(self._tiles_asked_for)), self.device)
+                only_if_pays_for_ld=self.feat.stride(0), if_slower=bool(self._tiles_asked_for),
+                beside=not self.backward), self.device)
             if with_blocks:
                 B.adaqp_fill_spmm_blocks(with_blocks, begin, end, self.rowptr, self.col, self.val)
                 with_blocks.tensors["copied"] = self.val[int(p.rowptr[begin]): int(p.rowptr[end])].clone()

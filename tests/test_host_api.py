@@ -611,7 +611,15 @@ def test_rule_that_decides_whether_a_panel_plan_pays():
 def test_rule_that_decides_whether_blocks_save(n_cols, share, rows, dim, saves):
     """Timed with and without blocks: the faster way, where they differ."""
     steps = -(-rows // 128) * -(-n_cols // 32)
-    assert bool(B.lib().adaqp_spmm_blocks_save(int(rows * share * n_cols), steps, dim)) == saves
+    assert bool(B.lib().adaqp_spmm_blocks_save(int(rows * share * n_cols), steps, dim, 0)) == saves
+
+
+@pytest.mark.parametrize("entries,steps,dim,saves", [
+    (294_861, 1_120, 32, False), (774_930, 926, 602, True), (2_315_452, 7_209, 64, False), (1_462_590, 3_833, 32, False),
+    (1_462_590, 3_785, 400, True), (1_057_932, 3_234, 400, True), (2_839_519, 3_468, 64, True)])
+def test_rule_that_decides_whether_blocks_save_beside_another_range(entries, steps, dim, saves):
+    """Forward steps timed with and without blocks."""
+    assert bool(B.lib().adaqp_spmm_blocks_save(entries, steps, dim, 1)) == saves
 
 
 def test_plan_spmm_blocks_takes_the_rows_that_pay():
@@ -645,7 +653,7 @@ def test_plan_spmm_blocks_bounds_its_table():
     col[:300] = np.arange(37_000, n_cols)                              # rows that share their columns: few steps
     rowptr = np.arange(n + 1, dtype=np.int64) * d
     plan = B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, dim, 2_000)
-    assert plan["n_steps"] > 4_500_000 // 512 and B.lib().adaqp_spmm_blocks_save(4_500_000, plan["n_steps"], dim)
+    assert plan["n_steps"] > 4_500_000 // 512 and B.lib().adaqp_spmm_blocks_save(4_500_000, plan["n_steps"], dim, 0)
     for if_slower in (False, True):
         assert B.adaqp_plan_spmm_blocks(rowptr, col, 0, n, n_cols, dim, 2_000, only_if_pays_for_ld=608, if_slower=if_slower) is None
     small = B.adaqp_plan_spmm_blocks(rowptr, col, 0, 300, n_cols, dim, 2_000, only_if_pays_for_ld=608)
