@@ -310,6 +310,30 @@ int adaqp_spmm_csr_tiled(const int64_t *rowptr_dev, const int32_t *col_dev, cons
  * whose lines stay in its L2), and the segments of a row are added up in group order.  The copy costs 8 bytes per entry. */
 #define ADAQP_SPMM_SEGMENTS 8           /* of a row, at most */
 
+/* A piece of the walk over the segments: what one wave adds up.  entry, segment: entries and segments that lie before the piece;
+ * partial: partial row that takes what the piece before leaves of a segment it does not finish, -1 = it finishes all. */
+typedef struct adaqp_spmm_piece {
+    int64_t entry;
+    int32_t segment;
+    int32_t partial;
+} adaqp_spmm_piece;
+#define ADAQP_SPMM_PIECE_ENTRIES 768    /* of a piece, at most */
+#define ADAQP_SPMM_PIECE_SEGMENTS 62    /* that end in a piece, at most */
+
+/* Device side of a plan of pieces (adaqp_plan_spmm_pieces).  Rows of a single segment that no piece cuts are written at once, the others from
+ * their partial rows. */
+typedef struct adaqp_spmm_pieces {
+    int64_t n_pieces;                   /* 0: no pieces, the struct is ignored */
+    int64_t n_partials;                 /* partial rows */
+    int64_t n_sums;                     /* rows that are sums of partial rows, or have no segment */
+    int32_t lines_per_slice;            /* 128-byte lines of a row of H that an XCD takes at a time: 1, 2 or 4 */
+    int32_t reserved;
+    const adaqp_spmm_piece *pieces_dev; /* [n_pieces + 1] */
+    const int32_t *dest_dev;            /* [n_seg] partial row of a segment (of its last part), or -1 - row */
+    const int32_t *sum_row_dev;         /* [n_sums] */
+    const int32_t *sum_ptr_dev;         /* [n_sums + 1] the row's partial rows, in the order in which they are added */
+} adaqp_spmm_pieces;
+
 /* Device side of a segment plan for one row range.  The struct lives in host memory and is read during the call only. */
 typedef struct adaqp_spmm_segments {
     int64_t n_seg;                      /* 0: no segments, the struct is ignored */
@@ -321,6 +345,7 @@ typedef struct adaqp_spmm_segments {
                                            is not of this plan (struck from the tile table): -2 first */
     int32_t *col_dev;                   /* [n_entries] adaqp_fill_spmm_segments writes both */
     float   *val_dev;
+    adaqp_spmm_pieces pieces;           /* optional (n_pieces = 0: the walk is cut on the device) */
 } adaqp_spmm_segments;
 
 /* Host only.  Segments of rows [row_begin, row_end) from adaqp_plan_spmm_tiles' outputs for the range (rows struck from the
@@ -331,6 +356,21 @@ typedef struct adaqp_spmm_segments {
 int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_begin, int64_t row_end, const int32_t *col_bounds_host,
                              const int32_t *tile_off_host, int64_t *sizes_inout, int64_t *ptr_out, int64_t *src_out,
                              int32_t *of_row_out);
+
+/* Host only.  Lines per slice (adaqp_spmm_pieces) for segments of tiles with these bounds. */
+int32_t adaqp_spmm_segments_lines(const int32_t *col_bounds_host);
+
+/* Host only.  Cuts the walk over the segments (ptr_host: [n_seg + 1], of_row_host: [n_rows][ADAQP_SPMM_SEGMENTS], both of
+ * adaqp_plan_spmm_segments) into pieces of about equal length, between segments where these are short, for rows of dim columns.  Two
+ * calls: with the output arrays NULL to learn sizes_inout[3] = { n_pieces, n_partials, n_sums }, then with those and arrays of
+ * n_pieces + 1, n_seg, n_sums and n_sums + 1.  Errors: EINVAL (ptr that descends, segments of no row or of two, sizes of another plan),
+ * ESIZE (more than 2^24 pieces, no memory). */
+int adaqp_plan_spmm_pieces(const int64_t *ptr_host, int64_t n_seg, const int32_t *of_row_host, int64_t n_rows, int32_t dim,
+                           int32_t lines_per_slice, int64_t *sizes_inout, adaqp_spmm_piece *pieces_out, int32_t *dest_out,
+                           int32_t *sum_row_out, int32_t *sum_ptr_out);
+
+/* Bytes of workspace that segments with pieces need: a row of whole lines per partial row. */
+int adaqp_spmm_pieces_workspace_bytes(int64_t n_partials, int32_t dim, int64_t *bytes_out);
 
 /* Host only.  What segments save over adaqp_spmm_csr on whole lines for rows [row_begin, row_end): *gain_out in entries times 128-byte lines
  * of H, negative where they cost more.  A step that aggregates several ranges adds them up and takes segments in all of them from
@@ -349,7 +389,8 @@ int adaqp_fill_spmm_segments(const adaqp_spmm_segments *segments_host, const int
  * nothing does. */
 int adaqp_update_spmm_segments(const adaqp_spmm_segments *segments_host, const float *val_dev, int64_t nnz, void *stream);
 
-/* Bytes of workspace adaqp_spmm_csr_segments needs: a row of whole lines per segment, up to eight per row of the range, and carries. */
+/* Bytes of workspace adaqp_spmm_csr_segments needs without pieces: a row of whole lines per segment, up to eight per row of the range, and
+ * carries. */
 int adaqp_spmm_segments_workspace_bytes(int64_t n_seg, int64_t n_entries, int32_t dim, int64_t *bytes_out);
 
 /* out[r, 0:dim] = sum_j val[j] * H[col[j], 0:dim] for the rows of the plan, out_dev being the row of the range's first row;

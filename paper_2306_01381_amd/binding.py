@@ -51,11 +51,19 @@ class SpmmBlocks(ctypes.Structure):
     ]
 
 
+class SpmmPieces(ctypes.Structure):
+    """Mirror of struct adaqp_spmm_pieces."""
+    _fields_ = [
+        ("n_pieces", _i64), ("n_partials", _i64), ("n_sums", _i64), ("lines_per_slice", _i32), ("reserved", _i32),
+        ("pieces_dev", _vp), ("dest_dev", _vp), ("sum_row_dev", _vp), ("sum_ptr_dev", _vp),
+    ]
+
+
 class SpmmSegments(ctypes.Structure):
     """Mirror of struct adaqp_spmm_segments."""
     _fields_ = [
         ("n_seg", _i64), ("n_entries", _i64), ("n_rows", _i64), ("ptr_dev", _vp), ("src_dev", _vp), ("of_row_dev", _vp),
-        ("col_dev", _vp), ("val_dev", _vp),
+        ("col_dev", _vp), ("val_dev", _vp), ("pieces", SpmmPieces),
     ]
 
 
@@ -120,6 +128,9 @@ _SIGNATURES = {
     "adaqp_spmm_panels_pay": (_i32, [_i64, _i32]),
     "adaqp_spmm_segments_gain": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp]),
     "adaqp_plan_spmm_segments": (ctypes.c_int, [_vp, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp]),
+    "adaqp_spmm_segments_lines": (_i32, [_vp]),
+    "adaqp_plan_spmm_pieces": (ctypes.c_int, [_vp, _i64, _vp, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp]),
+    "adaqp_spmm_pieces_workspace_bytes": (ctypes.c_int, [_i64, _i32, _vp]),
     "adaqp_fill_spmm_segments": (ctypes.c_int, [ctypes.POINTER(SpmmSegments), _vp, _vp, _i64, _vp]),
     "adaqp_update_spmm_segments": (ctypes.c_int, [ctypes.POINTER(SpmmSegments), _vp, _i64, _vp]),
     "adaqp_spmm_segments_workspace_bytes": (ctypes.c_int, [_i64, _i64, _i32, _vp]),
@@ -488,6 +499,40 @@ def adaqp_plan_spmm_segments(rowptr_host: np.ndarray, row_begin: int, row_end: i
     return plan
 
 
+def adaqp_spmm_segments_lines(col_bounds_host: np.ndarray) -> int:
+    bounds = np.ascontiguousarray(col_bounds_host, dtype=np.int32)
+    if bounds.shape[0] != SPMM_TILES + 1:
+        raise ValueError("col_bounds must be an output of adaqp_plan_spmm_tiles")
+    return int(lib().adaqp_spmm_segments_lines(bounds.ctypes.data))
+
+
+SPMM_PIECE = np.dtype([("entry", np.int64), ("segment", np.int32), ("partial", np.int32)])
+
+
+def adaqp_plan_spmm_pieces(ptr_host: np.ndarray, of_row_host: np.ndarray, dim: int, lines_per_slice: int) -> dict:
+    """Host-only.  The pieces of the walk over the segments of adaqp_plan_spmm_segments (its ptr and of_row), for rows of dim columns:
+    a dict of host arrays (pieces, dest, sum_row, sum_ptr) and lines_per_slice."""
+    ptr = np.ascontiguousarray(ptr_host, dtype=np.int64)
+    of_row = np.ascontiguousarray(of_row_host, dtype=np.int32).reshape(-1, SPMM_SEGMENTS)
+    sizes = np.zeros(3, dtype=np.int64)
+    args = (ptr.ctypes.data, ptr.shape[0] - 1, of_row.ctypes.data, of_row.shape[0], dim, lines_per_slice, sizes.ctypes.data)
+    _check(lib().adaqp_plan_spmm_pieces(*args, None, None, None, None), "adaqp_plan_spmm_pieces")
+    plan = {"pieces": np.empty(int(sizes[0]) + 1, dtype=SPMM_PIECE), "dest": np.empty(ptr.shape[0] - 1, dtype=np.int32),
+            "sum_row": np.empty(int(sizes[2]), dtype=np.int32), "sum_ptr": np.empty(int(sizes[2]) + 1, dtype=np.int32)}
+    _check(lib().adaqp_plan_spmm_pieces(*args, *(plan[k].ctypes.data for k in ("pieces", "dest", "sum_row", "sum_ptr"))),
+           "adaqp_plan_spmm_pieces")
+    plan["lines_per_slice"] = lines_per_slice
+    return plan
+
+
+def _device_pieces(plan: dict, device, tensors: dict) -> SpmmPieces:
+    """Uploads a plan of pieces into `tensors`, which keeps them alive, and returns the struct the C calls take."""
+    for k in ("pieces", "dest", "sum_row", "sum_ptr"):
+        tensors[k] = torch.from_numpy(plan[k].view(np.int32)).to(device)
+    return SpmmPieces(plan["pieces"].shape[0] - 1, int(plan["sum_ptr"][-1]), plan["sum_row"].shape[0], plan["lines_per_slice"], 0,
+                      *(tensors[k].data_ptr() for k in ("pieces", "dest", "sum_row", "sum_ptr")))
+
+
 SPMM_SEGMENTS_MIN_GAIN = 2e6
 
 
@@ -517,6 +562,8 @@ class DeviceSegments:
         t = self.tensors
         self.c = SpmmSegments(plan["n_seg"], plan["n_entries"], plan["n_rows"], t["ptr"].data_ptr(), t["src"].data_ptr(),
                               t["of_row"].data_ptr(), t["col"].data_ptr(), t["val"].data_ptr())
+        if "pieces" in plan:
+            self.c.pieces = _device_pieces(plan["pieces"], device, t)
 
     def __bool__(self) -> bool:
         return self.c.n_seg > 0
@@ -536,6 +583,10 @@ def adaqp_update_spmm_segments(segments: DeviceSegments, val: torch.Tensor, stre
 
 def adaqp_spmm_segments_workspace_bytes(segments: DeviceSegments, dim: int) -> int:
     out = ctypes.c_int64(0)
+    if segments.c.pieces.n_pieces > 0:
+        _check(lib().adaqp_spmm_pieces_workspace_bytes(segments.c.pieces.n_partials, dim, ctypes.byref(out)),
+               "adaqp_spmm_pieces_workspace_bytes")
+        return int(out.value)
     _check(lib().adaqp_spmm_segments_workspace_bytes(segments.c.n_seg, segments.c.n_entries, dim, ctypes.byref(out)),
            "adaqp_spmm_segments_workspace_bytes")
     return int(out.value)

@@ -17,6 +17,12 @@ int note_hip_error(hipError_t err, const char *what);
         if (adaqp_err__ != hipSuccess) return ::adaqp::note_hip_error(adaqp_err__, #expr); \
     } while (0)
 
+#define ADAQP_TRY(expr)                                                  \
+    do {                                                                 \
+        const int adaqp_rc__ = (expr);                                   \
+        if (adaqp_rc__ != ADAQP_OK) return adaqp_rc__;                   \
+    } while (0)
+
 // adaqp_spmm_csr_packed (slot_of_row_dev NULL: adaqp_spmm_csr) with what the caller knows about the columns: skewed_columns
 // = a few columns hold most of the entries, as in a transposed graph of power-law degrees, whose columns are used as often as
 // their nodes' degrees say.  It only picks how the work is cut.

@@ -216,8 +216,9 @@ int64_t tiled_part_bytes(const adaqp_layer_desc *d, bool overlap_part)
     const int64_t rows = overlap_part ? d->overlap_end - d->overlap_begin : d->dependent_end - d->dependent_begin;
     const adaqp_spmm_segments *seg = overlap_part ? &d->segments_overlap : &d->segments_dependent;
     int64_t bytes = 0;
-    const int rc = seg->n_seg > 0 ? adaqp_spmm_segments_workspace_bytes(seg->n_seg, seg->n_entries, d->dim, &bytes)
-                                  : adaqp_spmm_tiled_workspace_bytes(rows, d->dim, &bytes);
+    const int rc = seg->n_seg > 0 && seg->pieces.n_pieces > 0 ? adaqp_spmm_pieces_workspace_bytes(seg->pieces.n_partials, d->dim, &bytes)
+                   : seg->n_seg > 0 ? adaqp_spmm_segments_workspace_bytes(seg->n_seg, seg->n_entries, d->dim, &bytes)
+                                    : adaqp_spmm_tiled_workspace_bytes(rows, d->dim, &bytes);
     return rc == ADAQP_OK ? bytes : -1;
 }
 

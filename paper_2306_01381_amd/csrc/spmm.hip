@@ -583,6 +583,20 @@ SegmentGeometry segment_geometry(int64_t n_seg, int64_t n_entries, int32_t dim)
     return g;
 }
 
+constexpr int32_t kGroupCols = 12288;
+
+// First tile of each group, and behind the last one; 0 groups: bounds that descend.
+int segment_groups(const int32_t *col_bounds, int (&first_tile)[ADAQP_SPMM_TILES + 1])
+{
+    int n_groups = 0;
+    for (int t = 0; t < ADAQP_SPMM_TILES; ++t) {
+        if (col_bounds[t + 1] < col_bounds[t]) return 0;
+        if (n_groups == 0 || col_bounds[t + 1] - col_bounds[first_tile[n_groups - 1]] > kGroupCols) first_tile[n_groups++] = t;
+    }
+    first_tile[n_groups] = ADAQP_SPMM_TILES;
+    return n_groups;
+}
+
 // A wave per segment.
 __global__ __launch_bounds__(kBlock) void segments_fill_kernel(const int64_t *ptr, const int64_t *src, int64_t n_seg, int64_t n_entries,
                                                                const int32_t *col, const float *val, int64_t nnz, int32_t *col_out,
@@ -662,16 +676,12 @@ extern "C" int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_
     if (n_rows > 0 && !tile_off_host) return ADAQP_EINVAL;
     const bool fill = ptr_out != nullptr;
     if (fill && (!src_out || (n_rows > 0 && !of_row_out))) return ADAQP_EINVAL;
-    // Groups of tiles: an L2 of 4 MB holds two lines of 16 384 columns.  Sums included, 12.7 M entries in 58 000 columns, 256 columns of
+    // Groups of tiles (segment_groups): an L2 of 4 MB holds two lines of 16 384 columns.  Sums included, 12.7 M entries in 58 000 columns, 256 columns of
     // H: groups of 7 000 columns 0.64 ms, 14 000 0.65, 21 000 0.70, 29 000 0.72; 15 M in 98 000 columns: 13 000 0.75, 24 000 0.77, 32 000
     // 0.81.  Smaller graphs with short segments: 2.5 M entries in 58 000 columns, 602 columns of H 0.41, 0.42, 0.43, 0.47.
-    constexpr int32_t kGroupCols = 12288;
-    int first_tile[T + 1], n_groups = 0;
-    for (int t = 0; t < T; ++t) {
-        if (col_bounds_host[t + 1] < col_bounds_host[t]) return ADAQP_EINVAL;
-        if (n_groups == 0 || col_bounds_host[t + 1] - col_bounds_host[first_tile[n_groups - 1]] > kGroupCols) first_tile[n_groups++] = t;
-    }
-    first_tile[n_groups] = T;
+    int first_tile[T + 1];
+    const int n_groups = segment_groups(col_bounds_host, first_tile);
+    if (n_groups == 0) return ADAQP_EINVAL;
     int64_t n_seg = 0, n_entries = 0;
     for (int g = 0; g < n_groups; ++g)
         for (int64_t r = 0; r < n_rows; ++r) {
@@ -704,6 +714,17 @@ extern "C" int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_
     for (int g = n_groups; g < kSegments; ++g)
         for (int64_t r = 0; r < n_rows; ++r) of_row_out[r * kSegments + g] = -1;
     return ADAQP_OK;
+}
+
+// Two lines where an L2 of 4 MB holds them of a whole group, or one: 12 300 columns per group, 28 M entries, 256 columns of H 1.46 and 1.19 ms
+// with one and two; 57 000 columns per group, 7.7 M entries 0.75 and 0.83.
+extern "C" int32_t adaqp_spmm_segments_lines(const int32_t *col_bounds_host)
+{
+    int first_tile[ADAQP_SPMM_TILES + 1];
+    const int n_groups = col_bounds_host ? segment_groups(col_bounds_host, first_tile) : 0;
+    int32_t widest = 0;
+    for (int g = 0; g < n_groups; ++g) widest = std::max(widest, col_bounds_host[first_tile[g + 1]] - col_bounds_host[first_tile[g]]);
+    return widest > 16384 ? 1 : 2;
 }
 
 // What segments save is what the sliced kernel misses in its L2s: entries of rows that are cut up (shorter ones lie whole in one group and
@@ -812,6 +833,10 @@ int adaqp::check_segments_call(const adaqp_spmm_segments *p, const float *H_dev,
     if (!p->ptr_dev || !p->of_row_dev || !p->col_dev || !p->val_dev || !H_dev || !out_dev || n_cols == 0 || p->n_entries == 0) return ADAQP_EINVAL;
     if (!aligned_to(p->ptr_dev, 8) || !aligned_to(p->of_row_dev, 4) || !aligned_to(p->col_dev, 4) || !aligned_to(p->val_dev, 4)) return ADAQP_EINVAL;
     if (ldh % 32 != 0 || ldo % 32 != 0 || !aligned_to(H_dev, 128) || !aligned_to(out_dev, 128)) return ADAQP_EINVAL;
+    if (p->pieces.n_pieces != 0) {
+        const int rc = check_pieces(&p->pieces, p->n_seg);
+        if (rc != ADAQP_OK) return rc;
+    }
     if (p->n_seg > INT32_MAX - 1024 || p->n_rows > INT32_MAX - 1 || !sliced_takes(p->n_seg, p->n_entries, n_cols, ldh, false, 0, dim)) return ADAQP_ESIZE;
     return ADAQP_OK;
 }
@@ -821,6 +846,27 @@ extern "C" int adaqp_spmm_csr_segments(const adaqp_spmm_segments *p, const float
 {
     const int rc = check_segments_call(p, H_dev, n_cols, ldh, dim, out_dev, ldo);
     if (rc != ADAQP_OK || p->n_seg == 0 || p->n_rows == 0) return rc;
+    if (p->pieces.n_pieces > 0) {
+        int64_t need = 0;
+        ADAQP_TRY(adaqp_spmm_pieces_workspace_bytes(p->pieces.n_partials, dim, &need));
+        if (need > 0 && (!workspace_dev || !aligned_to(workspace_dev, 256))) return ADAQP_EINVAL;
+        if (workspace_bytes < need) return ADAQP_ESIZE;
+        PieceArgs a = {};
+        a.ptr = p->ptr_dev;
+        a.col = p->col_dev;
+        a.val = p->val_dev;
+        a.n_entries = p->n_entries;
+        a.n_seg = (int32_t)p->n_seg;
+        a.H = H_dev;
+        a.n_cols = n_cols;
+        a.ldh = ldh;
+        a.dim = dim;
+        a.out = out_dev;
+        a.ldo = ldo;
+        a.n_rows = (int32_t)p->n_rows;
+        a.partial = reinterpret_cast<float *>(workspace_dev);
+        return launch_pieces(&p->pieces, a, (hipStream_t)stream);
+    }
     const SegmentGeometry g = segment_geometry(p->n_seg, p->n_entries, dim);
     if (!workspace_dev || !aligned_to(workspace_dev, 256)) return ADAQP_EINVAL;
     if (workspace_bytes < g.bytes) return ADAQP_ESIZE;

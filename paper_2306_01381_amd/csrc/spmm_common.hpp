@@ -43,4 +43,28 @@ SlicedCut plan_sliced(const SpmmArgs &a, int64_t nnz_hint, bool whole_lines, boo
 hipError_t launch_sliced(const SpmmArgs &a, const SlicedCut &cut, int64_t nnz_hint, bool whole_lines, hipStream_t st,
                          int32_t *n_carries_out);
 
+// Segments in planned pieces (spmm_pieces.hip): ptr, entries and destinations of n_seg segments, n_rows rows of out.
+struct PieceArgs {
+    const adaqp_spmm_piece *pieces;     // [n_pieces + 1]
+    const int32_t *dest;                // [n_seg]
+    const int64_t *ptr;                 // [n_seg + 1]
+    const int32_t *col;
+    const float *val;
+    int64_t n_entries;                  // capacity of col / val
+    int32_t n_pieces, n_seg;
+    const float *H;
+    int64_t n_cols, ldh;
+    int32_t dim, wdim, lines;           // of a launch: columns, columns in whole lines, lines
+    float *out;
+    int64_t ldo;
+    int32_t n_rows;
+    float *partial;                     // [n_partials, ldp]
+    int64_t ldp;
+    int32_t n_partials;
+    int32_t n_blocks;                   // workgroups per slice
+};
+// What of a plan can be seen from the host, and the launches; the caller has filled in everything from ptr on but what the plan says.
+int check_pieces(const adaqp_spmm_pieces *p, int64_t n_seg);
+int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st);
+
 }  // namespace adaqp

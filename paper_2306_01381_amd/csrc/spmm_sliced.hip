@@ -38,25 +38,20 @@
 #include <algorithm>
 
 #include "spmm_common.hpp"
+#include "spmm_wave.hpp"
 
 namespace adaqp {
 namespace {
 
-// A lambda that is not inlined keeps what it captures in scratch memory.
-#define ADAQP_INLINE __attribute__((always_inline))
-
 constexpr int64_t kMinPath = 1024;                  // of a workgroup's four shares
-constexpr int kStep = 8;                            // entries of a step = groups of a wave
-constexpr int kGroup = kWave / kStep;               // lanes per entry: 8 x 16 bytes = one line
-constexpr int kLine = 32;                           // columns per line
+
 constexpr int kLoads = 3;                           // of four entries per lane: what a chunk takes of col, and of val
 constexpr int kChunk = kLoads * 4 * kWave;          // entries of a chunk
 constexpr int kPart = kChunk / 2;                   // no sum runs longer: a whole number of rings for every VPL
 constexpr int kEnds = kWave - 1;                    // row ends of a chunk at most
 constexpr int32_t kNoEnd = 0x10000;                 // lies after every step of a chunk
 constexpr int kRowSteps = 8;                        // entries a row end counts for where shares are cut
-constexpr int kNonTemporal = 2;                     // cache policy bits of a buffer load: nt
-constexpr int kRawBuffer = 0x00020000;              // buffer resource, last word: raw 32-bit data, no swizzle
+
 
 struct SlicedArgs {
     SpmmArgs s;
@@ -64,23 +59,11 @@ struct SlicedArgs {
     int32_t lines;              // lines of a row
 };
 
-typedef float float4_t __attribute__((ext_vector_type(4)));
-typedef int int4_t __attribute__((ext_vector_type(4)));
-
 // An entry in LDS: byte offset of its row of H and its coefficient.  PACKED: bits 0-1 of the offset name the width of
 // a row that is still packed (1, 2, 3: 2, 4, 8 bits; the offset is then one into the receive buffer) and (Z, S) follow.
 template <bool PACKED> struct Entry;
 template <> struct alignas(8) Entry<false> { uint32_t off; float val; };
 template <> struct alignas(16) Entry<true> { uint32_t off; float val; float z, s; };
-
-template <int U, int N, typename F>
-__device__ __forceinline__ void unroll(F &&f)
-{
-    if constexpr (U < N) {
-        f(std::integral_constant<int, U>());
-        unroll<U + 1, N>(f);
-    }
-}
 
 // Row ends before two diagonals of the merge path: row end p precedes d iff end_p + kRowSteps * (p + 1) <= d.  256-ary
 // search by a whole wave; wave-uniform results.
@@ -125,36 +108,6 @@ __device__ __forceinline__ void split_rows2(const SpmmArgs &a, const int64_t (&d
     }
     at[0] = __builtin_amdgcn_readfirstlane(lo[0]);
     at[1] = __builtin_amdgcn_readfirstlane(lo[1]);
-}
-
-// x and y hold two values per lane for two halves of the wave (HALF = 32) or of each half (16): afterwards a lane of the
-// lower half holds the sum of both halves' x, a lane of the upper half that of both halves' y.
-template <int HALF>
-__device__ __forceinline__ float fold(float x, float y)
-{
-    typedef unsigned pair_t __attribute__((ext_vector_type(2)));
-    const uint32_t ux = __builtin_bit_cast(uint32_t, x), uy = __builtin_bit_cast(uint32_t, y);
-    pair_t r;
-    if constexpr (HALF == 32) r = __builtin_bit_cast(pair_t, __builtin_amdgcn_permlane32_swap(ux, uy, false, false));
-    else                      r = __builtin_bit_cast(pair_t, __builtin_amdgcn_permlane16_swap(ux, uy, false, false));
-    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
-}
-
-__device__ __forceinline__ float ror8(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int32_t, v), 0x128, 0xF, 0xF, false));
-}
-
-// x of all lanes or-ed together.
-__device__ __forceinline__ uint32_t or_lanes(uint32_t x)
-{
-    int32_t v = (int32_t)x;
-    v |= __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, false);     // row_ror:1, 2, 4, 8: the row of 16 lanes
-    v |= __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, false);
-    v |= __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, false);
-    v |= __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);
-    return (uint32_t)(__builtin_amdgcn_readlane(v, 0) | __builtin_amdgcn_readlane(v, 16) | __builtin_amdgcn_readlane(v, 32) |
-                      __builtin_amdgcn_readlane(v, 48));
 }
 
 // One wave's share of the path for one slice of VPL lines.  WHOLE: rows of H and out start on lines and have whole lines

@@ -233,7 +233,10 @@ class LayerStep:
                 with_blocks.tensors["copied"] = self.val[int(p.rowptr[begin]): int(p.rowptr[end])].clone()
         segments = B.DeviceSegments(None)
         if n_cols * self.feat.stride(0) * 4 < B.SPMM_SEGMENTS_MOST_BYTES:
-            segments = B.DeviceSegments(B.adaqp_plan_spmm_segments(p.rowptr, begin, end, bounds, off), self.device)
+            entries = B.adaqp_plan_spmm_segments(p.rowptr, begin, end, bounds, off)
+            if entries is not None:
+                entries["pieces"] = B.adaqp_plan_spmm_pieces(entries["ptr"], entries["of_row"], dim, B.adaqp_spmm_segments_lines(bounds))
+            segments = B.DeviceSegments(entries, self.device)
         if segments:
             B.adaqp_fill_spmm_segments(segments, self.col, self.val)
         need = (B.adaqp_spmm_segments_workspace_bytes(segments, dim) if segments else B.adaqp_spmm_tiled_workspace_bytes(end - begin, dim)) \

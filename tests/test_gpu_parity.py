@@ -965,6 +965,44 @@ def test_spmm_segments(oracle, dim, ld, n_rows, n_cols):
         assert np.all(got[mine][:, dim:zero_to] == 0.0) and np.all(got[mine][:, zero_to:] == 7.0) and np.all(got[~mine] == 7.0)
 
 
+@pytest.mark.parametrize("lines", [1, 2, 4])
+@pytest.mark.parametrize("dim,ld", [(7, 32), (64, 96), (96, 96), (128, 128), (602, 608), (2049, 2080)])
+def test_spmm_pieces(oracle, lines, dim, ld):
+    """Segments in planned pieces: of none, one and many entries, cut by pieces, more ends than a piece takes, in rows of several segments,
+    of one, struck ones; the sums of the same segments cut on the device."""
+    _say(f"pieces spmm lines={lines} dim={dim} ld={ld}")
+    rng = np.random.default_rng(6000 + dim)
+    n_rows, n_cols = 420, 40_000
+    degs = rng.integers(0, 130, size=n_rows)
+    degs[:100], degs[100:110], degs[110], degs[111], degs[112] = 1, [0, 1, 7, 8, 9, 63, 64, 255, 256, 257], 9_000, 767, 769
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, degs)
+    H = np.full((n_cols, ld), np.nan, dtype=np.float32)
+    H[:, :dim] = rng.standard_normal((n_cols, dim), dtype=np.float32)
+    want, mag = oracle.spmm_csr(rowptr, col, val, 0, n_rows, np.ascontiguousarray(H[:, :dim]), dim)
+    cl, vl, Hd = (torch.from_numpy(x).to(DEV) for x in (col, val, H))
+    bounds, off = B.adaqp_plan_spmm_tiles(rowptr, col, 0, n_rows, n_cols)
+    struck = np.arange(n_rows) % 7 == 3
+    off[struck] = -1
+    plan = B.adaqp_plan_spmm_segments(rowptr, 0, n_rows, bounds, off)
+    plan["pieces"] = B.adaqp_plan_spmm_pieces(plan["ptr"], plan["of_row"], dim, lines)
+    assert (plan["pieces"]["dest"] < 0).any() and (plan["pieces"]["pieces"]["partial"] >= 0).any()
+    segments = B.DeviceSegments(plan, DEV)
+    B.adaqp_fill_spmm_segments(segments, cl, vl)
+    ws = torch.empty(max(B.adaqp_spmm_segments_workspace_bytes(segments, dim), 1), dtype=torch.uint8, device=DEV)
+    outs = []
+    for _ in range(2):
+        ws.fill_(0xFF)
+        outs.append(torch.full((n_rows, ld), 7.0, dtype=torch.float32, device=DEV))
+        B.adaqp_spmm_csr_segments(segments, 0, Hd, dim, outs[-1], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))
+    got = outs[0].cpu().numpy()
+    err = np.abs(got[~struck][:, :dim].astype(np.float64) - want[~struck])
+    assert float((err / (SPMM_RTOL * mag[~struck] + 1e-30)).max()) <= 1.0
+    zero_to = _padded_cols(dim, ld)
+    assert np.all(got[~struck][:, dim:zero_to] == 0.0) and np.all(got[~struck][:, zero_to:] == 7.0) and np.all(got[struck] == 7.0)
+
+
 def test_spmm_segments_of_more_rows_than_a_launch_has_waves():
     """2^26 rows and more: a wave each would be 2^32 threads."""
     _say("segments of 2^26 rows")

@@ -464,6 +464,49 @@ def test_plan_spmm_segments(n_rows, n_cols):
         B.adaqp_plan_spmm_segments(rowptr, 0, n_rows, bounds, off)
 
 
+@pytest.mark.parametrize("lengths", [[], [1], [0, 5, 0], [768], [769], [5_000], [1] * 200, [700, 30, 40, 100, 2_000, 3] * 9])
+@pytest.mark.parametrize("dim,lines", [(32, 1), (602, 2), (602, 4)])
+def test_plan_spmm_pieces(lengths, dim, lines):
+    """Pieces are consecutive, within their limits, and end with a segment or inside one; every part of a row goes to a place of its own."""
+    lengths = np.array(lengths, np.int64)
+    n_seg, S = lengths.size, B.SPMM_SEGMENTS
+    ptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    of_row = np.full((n_seg + 3, S), -1, np.int32)                     # rows of one, two and no segments, and one that is not of the plan
+    row, seg = 1, 0
+    while seg < n_seg:
+        of_row[row, 2] = seg
+        if seg % 3 == 1 and seg + 1 < n_seg:
+            of_row[row, 7] = seg + 1
+            seg += 1
+        row, seg = row + 1, seg + 1
+    of_row[-1, 0] = -2
+    plan = B.adaqp_plan_spmm_pieces(ptr, of_row, dim, lines)
+    pieces, dest = plan["pieces"], plan["dest"]
+    assert pieces[0].tolist() == (0, 0, -1) and pieces[-1].tolist() == (ptr[-1], n_seg, -1)
+    parts = [[] for _ in range(n_seg)]                                 # places that the parts of a segment go to
+    for here, there in zip(pieces[:-1], pieces[1:]):
+        assert 0 <= there["entry"] - here["entry"] <= 768 and 0 <= there["segment"] - here["segment"] <= 62
+        assert (there["entry"], there["segment"]) > (here["entry"], here["segment"])
+        for s in range(here["segment"], there["segment"]):
+            parts[s].append(int(dest[s]))
+        if there["partial"] < 0:
+            assert there["entry"] == ptr[there["segment"]]
+        else:
+            assert max(here["entry"], ptr[there["segment"]]) < there["entry"] < ptr[there["segment"] + 1]
+            parts[there["segment"]].append(int(there["partial"]))
+    sums = dict(zip(plan["sum_row"].tolist(), zip(plan["sum_ptr"][:-1].tolist(), plan["sum_ptr"][1:].tolist())))
+    assert plan["sum_ptr"][0] == 0 and np.all(np.diff(plan["sum_row"]) > 0) and of_row.shape[0] - 1 not in sums
+    for r in range(of_row.shape[0] - 1):
+        want = [p for s in of_row[r][of_row[r] >= 0] for p in parts[s]]
+        assert want == ([-1 - r] if r not in sums else list(range(*sums[r])))
+    with pytest.raises(B.AdaqpError):
+        B.adaqp_plan_spmm_pieces(ptr, of_row, dim, 3)
+    if n_seg:
+        of_row[0, 0] = 0                                               # a segment of two rows
+        with pytest.raises(B.AdaqpError):
+            B.adaqp_plan_spmm_pieces(ptr, of_row, dim, lines)
+
+
 @pytest.mark.parametrize("n_rows,n_cols,mean,transposed", [(0, 8, 0, False), (300, 50, 30, False), (3_000, 9_000, 90, False),
                                                            (3_000, 9_000, 90, True), (400, 5_000, 700, False)])
 def test_spmm_segments_gain(n_rows, n_cols, mean, transposed):
