@@ -240,6 +240,14 @@ int adaqp_assign_bits(int64_t n, const float *beta_host, const int32_t *peer_of_
  * other row.  Errors: EINVAL (index out of range, a row listed twice), ESIZE (n > 2^31 - 1). */
 int adaqp_plan_slot_of_row(int64_t n_rows, int64_t n, const int32_t *halo_idx_host, int32_t *slot_of_row_out);
 
+/* Host only: where the kernels that walk planned pieces find a received row: packed_row_out[r] = { byte offset in the receive buffer, its two low
+ * bits 1, 2, 3 for 2, 4, 8 bits, slot } for the row r = halo_idx_host[t], { 0, 0 } for rows that are not received or whose slot's width or
+ * place is not one.  Per-slot arrays as for adaqp_unpack_dequant.  Errors: EINVAL (as adaqp_plan_slot_of_row), ESIZE (2^32 - 2^16 bytes and
+ * more). */
+typedef struct adaqp_packed_row { uint32_t place, slot; } adaqp_packed_row;
+int adaqp_plan_packed_rows(int64_t n_rows, int64_t n, const int32_t *halo_idx_host, const uint8_t *bits_host, const int64_t *row_offset_host,
+                           int32_t dim, int64_t packed_bytes, adaqp_packed_row *packed_row_out);
+
 /* adaqp_spmm_csr with some rows of H still packed: an entry whose column c has slot_of_row[c] = t >= 0 takes
  * the neighbour row from the receive buffer (packed + row_offset[t], bits[t], params[t]) and de-quantises it
  * in registers, (float)code * S + Z with the two roundings of Eq. 5, instead of reading H[c].  The result is
@@ -311,7 +319,8 @@ int adaqp_spmm_csr_tiled(const int64_t *rowptr_dev, const int32_t *col_dev, cons
 #define ADAQP_SPMM_SEGMENTS 8           /* of a row, at most */
 
 /* A piece of the walk over the segments: what one wave adds up.  entry, segment: entries and segments that lie before the piece;
- * partial: partial row that takes what the piece before leaves of a segment it does not finish, -1 = it finishes all. */
+ * partial: partial row that takes what the piece before leaves of a segment it does not finish, -1 = it finishes all, -2 = the wave
+ * that finishes it takes it over, being of the same workgroup. */
 typedef struct adaqp_spmm_piece {
     int64_t entry;
     int32_t segment;
@@ -326,7 +335,10 @@ typedef struct adaqp_spmm_pieces {
     int64_t n_pieces;                   /* 0: no pieces, the struct is ignored */
     int64_t n_partials;                 /* partial rows */
     int64_t n_sums;                     /* rows that are sums of partial rows, or have no segment */
+    int64_t n_seg, row_begin;           /* rows without tiles: the range it was made for; a layer step of another one does without */
     int32_t lines_per_slice;            /* 128-byte lines of a row of H that an XCD takes at a time: 1, 2 or 4 */
+    int32_t waves;                      /* of a workgroup: 4 or 8 */
+    int32_t entries;                    /* of a piece, at most: 256 or 768 */
     int32_t reserved;
     const adaqp_spmm_piece *pieces_dev; /* [n_pieces + 1] */
     const int32_t *dest_dev;            /* [n_seg] partial row of a segment (of its last part), or -1 - row */
@@ -361,13 +373,23 @@ int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_begin, int6
 int32_t adaqp_spmm_segments_lines(const int32_t *col_bounds_host);
 
 /* Host only.  Cuts the walk over the segments (ptr_host: [n_seg + 1], of_row_host: [n_rows][ADAQP_SPMM_SEGMENTS], both of
- * adaqp_plan_spmm_segments) into pieces of about equal length, between segments where these are short, for rows of dim columns.  Two
- * calls: with the output arrays NULL to learn sizes_inout[3] = { n_pieces, n_partials, n_sums }, then with those and arrays of
+ * adaqp_plan_spmm_segments; or of_row_host NULL, n_rows = n_seg: segments are rows, ptr_host the rowptr of a range) into pieces of
+ * about equal length, between segments where these are short, for rows of dim columns.  Two
+ * calls: with the output arrays NULL to learn sizes_inout[5] = { n_pieces, n_partials, n_sums, waves, entries }, then with those and arrays of
  * n_pieces + 1, n_seg, n_sums and n_sums + 1.  Errors: EINVAL (ptr that descends, segments of no row or of two, sizes of another plan),
  * ESIZE (more than 2^24 pieces, no memory). */
 int adaqp_plan_spmm_pieces(const int64_t *ptr_host, int64_t n_seg, const int32_t *of_row_host, int64_t n_rows, int32_t dim,
                            int32_t lines_per_slice, int64_t *sizes_inout, adaqp_spmm_piece *pieces_out, int32_t *dest_out,
                            int32_t *sum_row_out, int32_t *sum_ptr_out);
+
+/* Host only.  For rows [row_begin, row_end) on whole lines: *lines_out = lines per slice in which pieces over the rows take least time (0: they
+ * take more than no pieces), and
+ * *segments_gain_out = what segments of the rows save over that, in entries times 128-byte lines of H, negative where they cost more; a
+ * step that aggregates several ranges adds them up and takes segments in all of them where the sum is positive.  transposed: the
+ * range belongs to a backward step.  Rows that do not list ascending, distinct, in-range columns have no segments: -infinity, or EINVAL
+ * where adaqp_spmm_tiled_pays asks for them.  -infinity and 2 lines where there is no memory for a count per column. */
+int adaqp_spmm_pieces_rule(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end, int64_t n_cols,
+                           int32_t dim, int32_t transposed, int32_t *lines_out, double *segments_gain_out);
 
 /* Bytes of workspace that segments with pieces need: a row of whole lines per partial row. */
 int adaqp_spmm_pieces_workspace_bytes(int64_t n_partials, int32_t dim, int64_t *bytes_out);
@@ -640,6 +662,14 @@ typedef struct adaqp_layer_desc {
     void *stream_agg;           /* ISOLATED, FREE: overlapped aggregation; joined back into stream_msg before returning */
     void *event_fork;           /* ISOLATED, FREE: two hipEvent_t created by the caller (timing may be disabled) */
     void *event_join;
+    /* optional (n_pieces = 0: the walk is cut on the device): adaqp_plan_spmm_pieces of the rows of a range without tile table, and of both
+     * ranges where they touch (CHAIN), from the rowptr that rowptr_dev holds.  Line-padded feat and out only.  The workspace of the range
+     * (the larger one) holds adaqp_spmm_pieces_workspace_bytes.  Where received rows are read packed (slot_of_row_dev) pieces take
+     * packed_row_dev [n_feat_rows], adaqp_plan_packed_rows of the receive buffer, and are not looked at without it. */
+    const adaqp_packed_row *packed_row_dev;
+    adaqp_spmm_pieces pieces_overlap;
+    adaqp_spmm_pieces pieces_dependent;
+    adaqp_spmm_pieces pieces_both;
 } adaqp_layer_desc;
 
 /* Enqueues one layer step.  On return all work has been enqueued and stream_msg has been made to wait for

@@ -54,7 +54,8 @@ class SpmmBlocks(ctypes.Structure):
 class SpmmPieces(ctypes.Structure):
     """Mirror of struct adaqp_spmm_pieces."""
     _fields_ = [
-        ("n_pieces", _i64), ("n_partials", _i64), ("n_sums", _i64), ("lines_per_slice", _i32), ("reserved", _i32),
+        ("n_pieces", _i64), ("n_partials", _i64), ("n_sums", _i64), ("n_seg", _i64), ("row_begin", _i64),
+        ("lines_per_slice", _i32), ("waves", _i32), ("entries", _i32), ("reserved", _i32),
         ("pieces_dev", _vp), ("dest_dev", _vp), ("sum_row_dev", _vp), ("sum_ptr_dev", _vp),
     ]
 
@@ -92,6 +93,8 @@ class LayerDesc(ctypes.Structure):
         ("workspace_overlap_dev", _vp), ("workspace_overlap_bytes", _i64),
         ("workspace_dependent_dev", _vp), ("workspace_dependent_bytes", _i64),
         ("stream_msg", _vp), ("stream_agg", _vp), ("event_fork", _vp), ("event_join", _vp),
+        ("packed_row_dev", _vp),
+        ("pieces_overlap", SpmmPieces), ("pieces_dependent", SpmmPieces), ("pieces_both", SpmmPieces),
     ]
 
 
@@ -128,6 +131,8 @@ _SIGNATURES = {
     "adaqp_spmm_panels_pay": (_i32, [_i64, _i32]),
     "adaqp_spmm_segments_gain": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp]),
     "adaqp_plan_spmm_segments": (ctypes.c_int, [_vp, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _vp]),
+    "adaqp_plan_packed_rows": (ctypes.c_int, [_i64, _i64, _vp, _vp, _vp, _i32, _i64, _vp]),
+    "adaqp_spmm_pieces_rule": (ctypes.c_int, [_vp, _vp, _i64, _i64, _i64, _i32, _i32, _vp, _vp]),
     "adaqp_spmm_segments_lines": (_i32, [_vp]),
     "adaqp_plan_spmm_pieces": (ctypes.c_int, [_vp, _i64, _vp, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp]),
     "adaqp_spmm_pieces_workspace_bytes": (ctypes.c_int, [_i64, _i32, _vp]),
@@ -509,27 +514,46 @@ def adaqp_spmm_segments_lines(col_bounds_host: np.ndarray) -> int:
 SPMM_PIECE = np.dtype([("entry", np.int64), ("segment", np.int32), ("partial", np.int32)])
 
 
-def adaqp_plan_spmm_pieces(ptr_host: np.ndarray, of_row_host: np.ndarray, dim: int, lines_per_slice: int) -> dict:
+def adaqp_plan_spmm_pieces(ptr_host: np.ndarray, of_row_host: Optional[np.ndarray], dim: int, lines_per_slice: int) -> dict:
     """Host-only.  The pieces of the walk over the segments of adaqp_plan_spmm_segments (its ptr and of_row), for rows of dim columns:
-    a dict of host arrays (pieces, dest, sum_row, sum_ptr) and lines_per_slice."""
+    or, without of_row, over rows whose rowptr is ptr: a dict of host arrays (pieces, dest, sum_row, sum_ptr) and lines_per_slice."""
     ptr = np.ascontiguousarray(ptr_host, dtype=np.int64)
-    of_row = np.ascontiguousarray(of_row_host, dtype=np.int32).reshape(-1, SPMM_SEGMENTS)
-    sizes = np.zeros(3, dtype=np.int64)
-    args = (ptr.ctypes.data, ptr.shape[0] - 1, of_row.ctypes.data, of_row.shape[0], dim, lines_per_slice, sizes.ctypes.data)
+    of_row = None if of_row_host is None else np.ascontiguousarray(of_row_host, dtype=np.int32).reshape(-1, SPMM_SEGMENTS)
+    sizes = np.zeros(5, dtype=np.int64)
+    args = (ptr.ctypes.data, ptr.shape[0] - 1, None if of_row is None else of_row.ctypes.data,
+            ptr.shape[0] - 1 if of_row is None else of_row.shape[0], dim, lines_per_slice, sizes.ctypes.data)
     _check(lib().adaqp_plan_spmm_pieces(*args, None, None, None, None), "adaqp_plan_spmm_pieces")
     plan = {"pieces": np.empty(int(sizes[0]) + 1, dtype=SPMM_PIECE), "dest": np.empty(ptr.shape[0] - 1, dtype=np.int32),
             "sum_row": np.empty(int(sizes[2]), dtype=np.int32), "sum_ptr": np.empty(int(sizes[2]) + 1, dtype=np.int32)}
     _check(lib().adaqp_plan_spmm_pieces(*args, *(plan[k].ctypes.data for k in ("pieces", "dest", "sum_row", "sum_ptr"))),
            "adaqp_plan_spmm_pieces")
-    plan["lines_per_slice"] = lines_per_slice
+    plan["lines_per_slice"], plan["waves"], plan["entries"] = lines_per_slice, int(sizes[3]), int(sizes[4])
     return plan
 
 
-def _device_pieces(plan: dict, device, tensors: dict) -> SpmmPieces:
+def adaqp_spmm_pieces_workspace_bytes(n_partials: int, dim: int) -> int:
+    out = ctypes.c_int64(0)
+    _check(lib().adaqp_spmm_pieces_workspace_bytes(n_partials, dim, ctypes.byref(out)), "adaqp_spmm_pieces_workspace_bytes")
+    return int(out.value)
+
+
+class DevicePieces:
+    """Device copies of a plan of pieces over rows and the struct the C calls take.  Keeps the tensors alive."""
+
+    def __init__(self, plan: Optional[dict], device="cuda", row_begin: int = 0):
+        self.tensors = {}
+        self.c = SpmmPieces() if plan is None else _device_pieces(plan, device, self.tensors, row_begin)
+
+    def __bool__(self) -> bool:
+        return self.c.n_pieces > 0
+
+
+def _device_pieces(plan: dict, device, tensors: dict, row_begin: int = 0) -> SpmmPieces:
     """Uploads a plan of pieces into `tensors`, which keeps them alive, and returns the struct the C calls take."""
     for k in ("pieces", "dest", "sum_row", "sum_ptr"):
         tensors[k] = torch.from_numpy(plan[k].view(np.int32)).to(device)
-    return SpmmPieces(plan["pieces"].shape[0] - 1, int(plan["sum_ptr"][-1]), plan["sum_row"].shape[0], plan["lines_per_slice"], 0,
+    return SpmmPieces(plan["pieces"].shape[0] - 1, int(plan["sum_ptr"][-1]), plan["sum_row"].shape[0], plan["dest"].shape[0], row_begin,
+                      plan["lines_per_slice"], plan["waves"], plan["entries"], 0,
                       *(tensors[k].data_ptr() for k in ("pieces", "dest", "sum_row", "sum_ptr")))
 
 
@@ -545,6 +569,18 @@ def adaqp_spmm_segments_gain(rowptr_host: np.ndarray, col_host: np.ndarray, row_
     _check(lib().adaqp_spmm_segments_gain(rowptr.ctypes.data, col.ctypes.data, row_begin, row_end, n_cols, dim, int(transposed),
                                           ctypes.byref(out)), "adaqp_spmm_segments_gain")
     return out.value
+
+
+def adaqp_spmm_pieces_rule(rowptr_host: np.ndarray, col_host: np.ndarray, row_begin: int, row_end: int, n_cols: int, dim: int,
+                           transposed: bool = False):
+    """Host-only.  (lines per slice of pieces over these rows, what segments save over that: the ranges of a step add up to more than 0
+    where they pay)."""
+    rowptr = np.ascontiguousarray(rowptr_host, dtype=np.int64)
+    col = np.ascontiguousarray(col_host, dtype=np.int32)
+    lines, gain = ctypes.c_int32(0), ctypes.c_double(0.0)
+    _check(lib().adaqp_spmm_pieces_rule(rowptr.ctypes.data, col.ctypes.data, row_begin, row_end, n_cols, dim, int(transposed),
+                                        ctypes.byref(lines), ctypes.byref(gain)), "adaqp_spmm_pieces_rule")
+    return lines.value, gain.value
 
 
 class DeviceSegments:
@@ -584,9 +620,7 @@ def adaqp_update_spmm_segments(segments: DeviceSegments, val: torch.Tensor, stre
 def adaqp_spmm_segments_workspace_bytes(segments: DeviceSegments, dim: int) -> int:
     out = ctypes.c_int64(0)
     if segments.c.pieces.n_pieces > 0:
-        _check(lib().adaqp_spmm_pieces_workspace_bytes(segments.c.pieces.n_partials, dim, ctypes.byref(out)),
-               "adaqp_spmm_pieces_workspace_bytes")
-        return int(out.value)
+        return adaqp_spmm_pieces_workspace_bytes(segments.c.pieces.n_partials, dim)
     _check(lib().adaqp_spmm_segments_workspace_bytes(segments.c.n_seg, segments.c.n_entries, dim, ctypes.byref(out)),
            "adaqp_spmm_segments_workspace_bytes")
     return int(out.value)
@@ -740,6 +774,20 @@ def adaqp_plan_slot_of_row(n_rows: int, halo_idx_host: np.ndarray) -> np.ndarray
     out = np.zeros(n_rows, dtype=np.int32)
     _check(lib().adaqp_plan_slot_of_row(n_rows, halo.shape[0], halo.ctypes.data, out.ctypes.data),
            "adaqp_plan_slot_of_row")
+    return out
+
+
+def adaqp_plan_packed_rows(n_rows: int, halo_idx_host: np.ndarray, bits_host: np.ndarray, row_offset_host: np.ndarray, dim: int,
+                           packed_bytes: int) -> np.ndarray:
+    """Host-only.  uint32[n_rows, 2]: place in the receive buffer and slot of each received row, 0 elsewhere."""
+    halo = np.ascontiguousarray(halo_idx_host, dtype=np.int32)
+    bits = np.ascontiguousarray(bits_host, dtype=np.uint8)
+    offset = np.ascontiguousarray(row_offset_host, dtype=np.int64)
+    if not halo.shape == bits.shape == offset.shape:
+        raise ValueError("halo_idx, bits and row_offset must have one value per slot")
+    out = np.zeros((n_rows, 2), dtype=np.uint32)
+    _check(lib().adaqp_plan_packed_rows(n_rows, halo.shape[0], halo.ctypes.data, bits.ctypes.data, offset.ctypes.data, dim, packed_bytes,
+                                        out.ctypes.data), "adaqp_plan_packed_rows")
     return out
 
 

@@ -6,7 +6,7 @@
 
 #include <algorithm>
 
-#include "common.hpp"
+#include "spmm_common.hpp"
 #include "host_sort.hpp"
 
 namespace adaqp {
@@ -117,6 +117,26 @@ extern "C" int adaqp_plan_slot_of_row(int64_t n_rows, int64_t n, const int32_t *
     return ADAQP_OK;
 }
 
+extern "C" int adaqp_plan_packed_rows(int64_t n_rows, int64_t n, const int32_t *halo_idx_host, const uint8_t *bits_host,
+                                      const int64_t *row_offset_host, int32_t dim, int64_t packed_bytes, adaqp_packed_row *packed_row_out)
+{
+    if (n_rows < 0 || n < 0 || dim <= 0 || packed_bytes < 0 || (n_rows > 0 && !packed_row_out)) return ADAQP_EINVAL;
+    if (n > 0 && (!halo_idx_host || !bits_host || !row_offset_host)) return ADAQP_EINVAL;
+    if (n > INT32_MAX || packed_bytes >= (int64_t)kOutside) return ADAQP_ESIZE;
+    std::fill_n(packed_row_out, n_rows, adaqp_packed_row{0, (uint32_t)n});          // a slot that there is not: not yet named
+    for (int64_t t = 0; t < n; ++t) {
+        const int32_t r = halo_idx_host[t];
+        if (r < 0 || r >= n_rows || packed_row_out[r].slot != (uint32_t)n) return ADAQP_EINVAL;
+        const int64_t stride = adaqp_row_stride(dim, bits_host[t]), at = row_offset_host[t];
+        const bool ok = stride > 0 && at >= 0 && at % 4 == 0 && at + stride <= packed_bytes;
+        packed_row_out[r] = ok ? adaqp_packed_row{(uint32_t)at | (bits_host[t] == 2 ? 1u : (bits_host[t] == 4 ? 2u : 3u)), (uint32_t)t}
+                               : adaqp_packed_row{0, 0};
+    }
+    for (int64_t r = 0; r < n_rows; ++r)
+        if (packed_row_out[r].place == 0) packed_row_out[r].slot = 0;
+    return ADAQP_OK;
+}
+
 extern "C" int adaqp_plan_recv_segments(int64_t n, const int32_t *dst_idx_host, int32_t *order_out,
                                         int64_t *seg_ptr_out, int64_t *n_seg_out)
 {
@@ -142,6 +162,12 @@ extern "C" int adaqp_plan_recv_segments(int64_t n, const int32_t *dst_idx_host, 
 namespace {
 
 bool two_streams(const adaqp_layer_desc *d) { return d->schedule == ADAQP_ISOLATED || d->schedule == ADAQP_FREE; }
+
+bool fused_receive(const adaqp_layer_desc *d)
+{
+    return d->direction == ADAQP_FORWARD && d->slot_of_row_dev && !d->tile_off_dependent_dev && d->n_send > 0 &&
+           d->packed_bytes >= 4;
+}
 
 int check_desc(const adaqp_layer_desc *d)
 {
@@ -194,6 +220,18 @@ int check_desc(const adaqp_layer_desc *d)
             !p->panel_piece_dev)
             return ADAQP_EINVAL;
     }
+    for (const adaqp_spmm_pieces *p : {&d->pieces_overlap, &d->pieces_dependent, &d->pieces_both}) {
+        if (p->n_pieces == 0) continue;
+        if (p->n_seg > INT32_MAX - 1024) return ADAQP_ESIZE;
+        ADAQP_TRY(check_pieces(p, p->n_seg));
+        if (d->ld % 32 != 0 || d->ldo % 32 != 0 || !aligned_to(d->feat_dev, 128) || !aligned_to(d->out_dev, 128)) return ADAQP_EINVAL;
+        if (!d->col_dev || !d->val_dev || !aligned_to(d->rowptr_dev, 8) || !aligned_to(d->col_dev, 4) || !aligned_to(d->val_dev, 4)) return ADAQP_EINVAL;
+        const bool packed = p != &d->pieces_overlap && fused_receive(d);
+        if (packed && (!aligned_to(d->slot_of_row_dev, 4) || !aligned_to(d->recv_packed_dev, 4) || !aligned_to(d->recv_params_dev, 8) ||
+                       !aligned_to(d->row_offset_dev, 8) || !aligned_to(d->packed_row_dev, 8)))
+            return ADAQP_EINVAL;
+        if (!sliced_takes(p->n_seg, d->nnz, d->n_feat_rows, d->ld, packed, d->packed_bytes, d->dim)) return ADAQP_ESIZE;
+    }
     if (two_streams(d)) {
         if (!d->event_fork || !d->event_join) return ADAQP_EINVAL;
         if (d->stream_msg == d->stream_agg) return ADAQP_EINVAL;
@@ -201,12 +239,6 @@ int check_desc(const adaqp_layer_desc *d)
         if (d->workspace_overlap_dev && d->workspace_overlap_dev == d->workspace_dependent_dev) return ADAQP_EINVAL;
     }
     return ADAQP_OK;
-}
-
-bool fused_receive(const adaqp_layer_desc *d)
-{
-    return d->direction == ADAQP_FORWARD && d->slot_of_row_dev && !d->tile_off_dependent_dev && d->n_send > 0 &&
-           d->packed_bytes >= 4;
 }
 
 // Workspace of a row range: the partial sums of the tiled kernel or of the segments first, then (if the range has panels or blocks)
@@ -222,10 +254,46 @@ int64_t tiled_part_bytes(const adaqp_layer_desc *d, bool overlap_part)
     return rc == ADAQP_OK ? bytes : -1;
 }
 
-// Rows [rb, re) along the merge path; fused: received rows are read from the receive buffer.
-int aggregate_range(const adaqp_layer_desc *d, int64_t rb, int64_t re, int64_t nz, bool fused, void *ws, int64_t wsb,
-                    hipStream_t st)
+bool planned_for(const adaqp_spmm_pieces *p, int64_t rb, int64_t re)
 {
+    return p->n_pieces > 0 && re > rb && p->n_seg == re - rb && p->row_begin == rb;
+}
+
+// Workspace of rows [rb, re) without tiles, whether planned or not.
+int range_bytes(const adaqp_layer_desc *d, const adaqp_spmm_pieces *pieces, int64_t rb, int64_t re, int64_t nz, int64_t *bytes)
+{
+    ADAQP_TRY(adaqp_spmm_workspace_bytes(re - rb, nz, d->dim, bytes));
+    if (!planned_for(pieces, rb, re)) return ADAQP_OK;
+    int64_t planned = 0;
+    ADAQP_TRY(adaqp_spmm_pieces_workspace_bytes(pieces->n_partials, d->dim, &planned));
+    *bytes = std::max(*bytes, planned);
+    return ADAQP_OK;
+}
+
+// Rows [rb, re) as planned, or along the merge path; fused: received rows are read from the receive buffer.
+int aggregate_range(const adaqp_layer_desc *d, int64_t rb, int64_t re, int64_t nz, bool fused, const adaqp_spmm_pieces *pieces, void *ws,
+                    int64_t wsb, hipStream_t st)
+{
+    if (planned_for(pieces, rb, re) && (!fused || d->packed_row_dev)) {
+        PieceArgs a = {};
+        a.ptr = d->rowptr_dev + rb;
+        a.col = d->col_dev;
+        a.val = d->val_dev;
+        a.n_entries = d->nnz;
+        a.n_seg = a.n_rows = (int32_t)(re - rb);
+        a.of_rows = true;
+        a.H = d->feat_dev;
+        a.n_cols = d->n_feat_rows;
+        a.ldh = d->ld;
+        if (fused)
+            a.p = PackedRows{d->slot_of_row_dev, d->recv_packed_dev, d->packed_bytes, d->recv_params_dev, d->bits_dev, d->row_offset_dev,
+                             d->n_send, 0, d->dim, d->packed_row_dev};
+        a.dim = d->dim;
+        a.out = d->out_dev + rb * d->ldo;
+        a.ldo = d->ldo;
+        a.partial = static_cast<float *>(ws);
+        return launch_pieces(pieces, a, st);
+    }
     return spmm_rows(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, nz, d->feat_dev, d->n_feat_rows, d->ld, d->dim,
                      d->out_dev, d->ldo, fused ? d->slot_of_row_dev : nullptr, d->recv_packed_dev, d->packed_bytes,
                      d->recv_params_dev, d->bits_dev, d->row_offset_dev, d->n_send, ws, wsb, st,
@@ -248,7 +316,8 @@ int aggregate_rows(const adaqp_layer_desc *d, bool overlap_part, hipStream_t st)
         return adaqp_spmm_csr_tiled(d->rowptr_dev, d->col_dev, d->val_dev, d->nnz, rb, re, d->feat_dev,
                                     d->n_feat_rows, d->ld, d->dim, d->out_dev, d->ldo, tile_off,
                                     overlap_part ? d->tile_chunk_overlap : d->tile_chunk_dependent, ws, wsb, st);
-    return aggregate_range(d, rb, re, nz, !overlap_part && fused_receive(d), ws, wsb, st);
+    return aggregate_range(d, rb, re, nz, !overlap_part && fused_receive(d), overlap_part ? &d->pieces_overlap : &d->pieces_dependent, ws,
+                           wsb, st);
 }
 
 bool has_blocks(const adaqp_layer_desc *d, bool overlap_part)
@@ -367,7 +436,7 @@ bool one_launch(const adaqp_layer_desc *d)
         return false;
     const int64_t rows = d->dependent_end - d->overlap_begin;
     int64_t need = 0;
-    if (rows > INT32_MAX - 1 || adaqp_spmm_workspace_bytes(rows, both_nnz(d), d->dim, &need) != ADAQP_OK) return false;
+    if (rows > INT32_MAX - 1 || range_bytes(d, &d->pieces_both, d->overlap_begin, d->dependent_end, both_nnz(d), &need) != ADAQP_OK) return false;
     return larger_is_overlap(d) ? d->workspace_overlap_dev && d->workspace_overlap_bytes >= need
                                 : d->workspace_dependent_dev && d->workspace_dependent_bytes >= need;
 }
@@ -377,7 +446,7 @@ bool one_launch(const adaqp_layer_desc *d)
 int aggregate_both(const adaqp_layer_desc *d, hipStream_t st)
 {
     const bool first = larger_is_overlap(d);
-    return aggregate_range(d, d->overlap_begin, d->dependent_end, both_nnz(d), fused_receive(d),
+    return aggregate_range(d, d->overlap_begin, d->dependent_end, both_nnz(d), fused_receive(d), &d->pieces_both,
                            first ? d->workspace_overlap_dev : d->workspace_dependent_dev,
                            first ? d->workspace_overlap_bytes : d->workspace_dependent_bytes, st);
 }
@@ -422,7 +491,8 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
         int64_t nz = part ? d->overlap_nnz : d->dependent_nnz;
         if (nz < 0 || nz > d->nnz) nz = d->nnz;
         int64_t need = 0;
-        rc = adaqp_spmm_workspace_bytes(rows, nz, d->dim, &need);
+        rc = range_bytes(d, part ? &d->pieces_overlap : &d->pieces_dependent, part ? d->overlap_begin : d->dependent_begin,
+                         part ? d->overlap_end : d->dependent_end, nz, &need);
         if (rc != ADAQP_OK) return rc;
         if (part ? d->tile_off_overlap_dev != nullptr : d->tile_off_dependent_dev != nullptr) {
             need = tiled_part_bytes(d, part != 0);          // that range takes the tiled kernel, or its segments

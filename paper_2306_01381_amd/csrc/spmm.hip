@@ -200,16 +200,16 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
             my_val = __builtin_nontemporal_load(valp + j + lane);
             if (my_col < 0 || my_col >= a.n_cols) { my_col = 0; my_val = 0.0f; }   // out-of-range entry: skipped
             if (PACKED) {
-                const int32_t slot = a.slot_of_row[my_col];
-                if (slot >= 0 && slot < a.n_slots) {
-                    my_b = a.bits[slot];
-                    my_off = a.row_offset[slot];
-                    const float2 zs = *reinterpret_cast<const float2 *>(a.params + 2 * (int64_t)slot);
+                const int32_t slot = a.p.slot_of_row[my_col];
+                if (slot >= 0 && slot < a.p.n_slots) {
+                    my_b = a.p.bits[slot];
+                    my_off = a.p.row_offset[slot];
+                    const float2 zs = *reinterpret_cast<const float2 *>(a.p.params + 2 * (int64_t)slot);
                     my_z = zs.x;
                     my_s = zs.y;
-                    const int64_t stride = 4 * (((int64_t)a.full_dim * my_b + 31) >> 5);
+                    const int64_t stride = 4 * (((int64_t)a.p.full_dim * my_b + 31) >> 5);
                     const bool ok = (my_b == 2 || my_b == 4 || my_b == 8) && my_off >= 0 && (my_off & 3) == 0 &&
-                                    my_off + stride <= a.packed_bytes;
+                                    my_off + stride <= a.p.packed_bytes;
                     if (!ok) my_b = 0;                      // broken slot: fall back to the row in H
                 }
             }
@@ -223,11 +223,11 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
                 const int32_t pb = PACKED ? __builtin_amdgcn_readlane(my_b, eu) : 0;
                 if (PACKED && pb != 0) {                                           // wave-uniform
                     // one 32-bit word holds the VW codes of a lane's vector (VW * b <= 32 and divides 32)
-                    const uint32_t *words = reinterpret_cast<const uint32_t *>(a.packed + readlane_i64(my_off, eu));
-                    const uint32_t last_word = (uint32_t)(((int64_t)a.full_dim * pb - 1) >> 5);
+                    const uint32_t *words = reinterpret_cast<const uint32_t *>(a.p.packed + readlane_i64(my_off, eu));
+                    const uint32_t last_word = (uint32_t)(((int64_t)a.p.full_dim * pb - 1) >> 5);
 #pragma unroll
                     for (int v = 0; v < NV; ++v) {
-                        const uint32_t bit = (uint32_t)(a.col0 + (v * kWave + lane) * VW) * (uint32_t)pb;
+                        const uint32_t bit = (uint32_t)(a.p.col0 + (v * kWave + lane) * VW) * (uint32_t)pb;
                         const uint32_t idx = (bit >> 5) < last_word ? (bit >> 5) : last_word;
 #pragma unroll
                         for (int k = 0; k < VW; ++k) h[u][v][k] = 0.0f;
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
                         const uint32_t mask = (1u << pb) - 1u;
 #pragma unroll
                         for (int v = 0; v < NV; ++v) {
-                            const uint32_t bit = (uint32_t)(a.col0 + (v * kWave + lane) * VW) * (uint32_t)pb;
+                            const uint32_t bit = (uint32_t)(a.p.col0 + (v * kWave + lane) * VW) * (uint32_t)pb;
                             const uint32_t word = __builtin_bit_cast(uint32_t, h[u][v][0]) >> (bit & 31u);
 #pragma unroll
                             for (int k = 0; k < VW; ++k) {
@@ -387,7 +387,7 @@ template <int VW, int NV>
 hipError_t launch_merge(const SpmmArgs &a, dim3 grid, hipStream_t st)
 {
     constexpr int U = NV >= 4 ? 4 : (NV >= 2 ? 8 : 16);
-    if (a.slot_of_row) hipLaunchKernelGGL((spmm_merge_kernel<VW, NV, U, true>), grid, dim3(kBlock), 0, st, a);
+    if (a.p.slot_of_row) hipLaunchKernelGGL((spmm_merge_kernel<VW, NV, U, true>), grid, dim3(kBlock), 0, st, a);
     else hipLaunchKernelGGL((spmm_merge_kernel<VW, NV, U, false>), grid, dim3(kBlock), 0, st, a);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
@@ -527,15 +527,15 @@ int adaqp::spmm_rows(const int64_t *rowptr_dev, const int32_t *col_dev, const fl
         a.carry = reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(workspace_dev) + g.carry_off);
         a.carry_ld = g.carry_ld;
         a.n_items = g.n_items;
-        a.slot_of_row = slot_of_row_dev;
-        a.col0 = c0;
-        a.full_dim = dim;
-        a.packed = packed_dev;
-        a.packed_bytes = packed_bytes;
-        a.params = params_dev;
-        a.bits = bits_dev;
-        a.row_offset = row_offset_dev;
-        a.n_slots = n_slots;
+        a.p.slot_of_row = slot_of_row_dev;
+        a.p.col0 = c0;
+        a.p.full_dim = dim;
+        a.p.packed = packed_dev;
+        a.p.packed_bytes = packed_bytes;
+        a.p.params = params_dev;
+        a.p.bits = bits_dev;
+        a.p.row_offset = row_offset_dev;
+        a.p.n_slots = n_slots;
         const int nv = (a.wdim + kWave * vw - 1) / (kWave * vw);
         const dim3 grid((unsigned)((g.n_items + kWavesPerBlock - 1) / kWavesPerBlock));
         hipError_t err;
@@ -716,15 +716,16 @@ extern "C" int adaqp_plan_spmm_segments(const int64_t *rowptr_host, int64_t row_
     return ADAQP_OK;
 }
 
-// Two lines where an L2 of 4 MB holds them of a whole group, or one: 12 300 columns per group, 28 M entries, 256 columns of H 1.46 and 1.19 ms
-// with one and two; 57 000 columns per group, 7.7 M entries 0.75 and 0.83.
+// Two lines where an L2 of 4 MB holds them of a good part of a group, else one: 12 300 columns per group, 28 M entries, 256 columns of H 1.46
+// and 1.19 ms with one and two; 57 000 columns per group, 7.7 M entries 0.75 and 0.83; 400 steps, one against two: 16 000 to 25 000 columns
+// 1.01, 25 000 to 38 000 0.97, more 0.93.
 extern "C" int32_t adaqp_spmm_segments_lines(const int32_t *col_bounds_host)
 {
     int first_tile[ADAQP_SPMM_TILES + 1];
     const int n_groups = col_bounds_host ? segment_groups(col_bounds_host, first_tile) : 0;
     int32_t widest = 0;
     for (int g = 0; g < n_groups; ++g) widest = std::max(widest, col_bounds_host[first_tile[g + 1]] - col_bounds_host[first_tile[g]]);
-    return widest > 16384 ? 1 : 2;
+    return widest > 20480 ? 1 : 2;
 }
 
 // What segments save is what the sliced kernel misses in its L2s: entries of rows that are cut up (shorter ones lie whole in one group and
@@ -893,7 +894,7 @@ extern "C" int adaqp_spmm_csr_segments(const adaqp_spmm_segments *p, const float
         a.carry = reinterpret_cast<float *>(ws + g.carry_off);
         a.carry_ld = g.wdim;
         a.n_items = (int32_t)g.n_items;
-        a.full_dim = dim;
+        a.p.full_dim = dim;
         // two lines per slice (15 M entries, 98 000 columns: one line 0.80 ms, two 0.75, four 0.81)
         const SlicedCut cut = {a.wdim > 32 ? 2 : 1, 0, segment_blocks(p->n_seg, p->n_entries)};
         ADAQP_HIP_TRY(launch_sliced(a, cut, p->n_entries, true, st, &a.n_items));

@@ -8,6 +8,19 @@
 
 namespace adaqp {
 
+// Rows of H that are still packed (received halo rows, de-quantised on the fly).
+struct PackedRows {
+    const int32_t *slot_of_row; // [n_cols], -1 = read the row from H; NULL: no row is packed
+    const uint8_t *packed;
+    int64_t packed_bytes;
+    const float *params;
+    const uint8_t *bits;
+    const int64_t *row_offset;
+    int64_t n_slots;
+    int32_t col0, full_dim;     // first column of this launch's chunk and the row length of the packed layout
+    const adaqp_packed_row *row;        // [n_cols], planned pieces: in place of slot_of_row, bits and row_offset
+};
+
 struct SpmmArgs {
     const int64_t *rowptr;      // already offset: rowptr[0] is the start of the first row of the range
     const int32_t *col;
@@ -23,15 +36,7 @@ struct SpmmArgs {
     float *carry;               // [n_items, carry_ld]
     int64_t carry_ld;
     int32_t n_items;
-    // optional: rows of H that are still packed (received halo rows, de-quantised on the fly)
-    const int32_t *slot_of_row; // [n_cols], -1 = read the row from H
-    const uint8_t *packed;
-    int64_t packed_bytes;
-    const float *params;
-    const uint8_t *bits;
-    const int64_t *row_offset;
-    int64_t n_slots;
-    int32_t col0, full_dim;     // first column of this launch's chunk and the row length of the packed layout
+    PackedRows p;
 };
 
 __device__ __forceinline__ int64_t clamp64(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
@@ -52,8 +57,10 @@ struct PieceArgs {
     const float *val;
     int64_t n_entries;                  // capacity of col / val
     int32_t n_pieces, n_seg;
+    bool of_rows;                       // segments are the rows of out (always where rows of H may be packed)
     const float *H;
     int64_t n_cols, ldh;
+    PackedRows p;
     int32_t dim, wdim, lines;           // of a launch: columns, columns in whole lines, lines
     float *out;
     int64_t ldo;

@@ -15,6 +15,9 @@
 // than their group; two lines per slice 1.19, one 1.46, four 1.31).  306 000 rows, 7.7 M entries, 456 000 columns, whose groups
 // are three times an L2: shares 1.04 ms, two lines per slice 0.83, one 0.75.
 #include <algorithm>
+#include <cmath>
+#include <functional>
+#include <numeric>
 #include <new>
 #include <vector>
 
@@ -24,31 +27,96 @@
 namespace adaqp {
 namespace {
 
-constexpr int kEntries = ADAQP_SPMM_PIECE_ENTRIES;
+constexpr int kEntries = ADAQP_SPMM_PIECE_ENTRIES, kFewEntries = 256;      // of a piece
+constexpr int kJoinWaves = 8;                               // of a workgroup whose waves join the parts of a segment
 constexpr int kEnds = ADAQP_SPMM_PIECE_SEGMENTS;
-constexpr int kPart = 256, kParts = kEntries / kPart;       // no sum runs longer than a part's 32 steps
-constexpr int kLoads = kEntries / (4 * kWave);              // of four entries per lane: what a piece takes of col, and of val
+constexpr int kPart = 256;                                  // no sum runs longer than a part's 32 steps
+constexpr int32_t kJoined = -2, kNowhere = INT32_MIN;       // a piece's partial; a destination
 constexpr int32_t kNoEnd = 0x10000;                         // lies after every step of a piece
+constexpr int kPackedLines = 4;                             // per slice where rows may be packed: their codes share lines
 constexpr unsigned kIdleLds = 6144;                         // of a workgroup, beside its 26 KB: no more than 16 waves on a CU
 constexpr int64_t kMostPieces = 1 << 24, kMostTasks = 1 << 23;
 static_assert(kEnds < kWave - 1, "a lane per end, and one that has none");
 
-struct alignas(8) Entry { uint32_t off; float val; };       // byte offset of a row of H, coefficient
+// A sum to its place.  Lanes without a column of their own store outside the row's buffer: no branch.
+template <int VPL>
+__device__ __forceinline__ void store_row(const PieceArgs &a, float *row, bool known, int32_t first_line, int lane, const float (&sum)[VPL])
+{
+    const uint32_t at = lane < kLine ? (uint32_t)(first_line * kLine + lane) * 4u : kOutside;
+    const auto to = __builtin_amdgcn_make_buffer_rsrc(row, 0, known ? a.wdim * 4 : 0, kRawBuffer);
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) {
+        const float x = (first_line + v) * kLine + (lane & (kLine - 1)) < a.dim ? sum[v] : 0.0f;        // row padding
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), to, (int)at + v * kLine * 4, 0, kNonTemporal);
+    }
+}
 
-template <int VPL, int AHEAD>
-__device__ __forceinline__ void walk_piece(const PieceArgs &a, const int32_t first_line, const int32_t item, Entry *stage)
+// dest: a partial row, or -1 - row.
+template <int VPL>
+__device__ __forceinline__ void store_row(const PieceArgs &a, int32_t dest, int32_t first_line, int lane, const float (&sum)[VPL])
+{
+    const bool part = dest >= 0, known = part ? dest < a.n_partials : -1 - dest < a.n_rows;
+    store_row<VPL>(a, part ? a.partial + (int64_t)dest * a.ldp : a.out + (int64_t)(-1 - dest) * a.ldo, known, first_line, lane, sum);
+}
+
+// stage_entries where rows may be packed, whose places have been looked up beforehand: a load per entry and one of (Z, S) instead of four, and
+// two that wait for one another instead of three (24 000 rows, 0.42 M entries, 66 columns, whole step: 40.2 -> 37.4 us; shares cut on the
+// device 38.7).
+template <int LOADS>
+__device__ __forceinline__ void stage_packed(int4_t (&st_col)[LOADS], const float4_t (&st_val)[LOADS], int32_t n_ent, uint32_t n_cols,
+                                             uint32_t pitch, const PackedRows &p, int lane, Entry<true> *stage)
+{
+    auto valid = [&](int k, int q) ADAQP_INLINE { return (k * kWave + lane) * 4 + q < n_ent && (uint32_t)st_col[k][q] < n_cols; };
+    uint2 at[LOADS][4];
+#pragma unroll
+    for (int k = 0; k < LOADS; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) at[k][q] = *reinterpret_cast<const uint2 *>(p.row + (valid(k, q) ? st_col[k][q] : 0));
+#pragma unroll
+    for (int k = 0; k < LOADS; ++k) {
+        if (k > 0 && k * 4 * kWave >= n_ent) break;         // a whole number of turns past every entry: never read
+        bool packed[4];
+        float2 zs[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            packed[q] = valid(k, q) && at[k][q].x != 0 && at[k][q].y < (uint64_t)p.n_slots;
+            zs[q] = *reinterpret_cast<const float2 *>(p.params + 2 * (int64_t)(packed[q] ? at[k][q].y : 0));
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t row = valid(k, q) ? (uint32_t)st_col[k][q] * pitch : kOutside;
+            stage[(k * kWave + lane) * 4 + q] = Entry<true>{packed[q] ? at[k][q].x : row, valid(k, q) ? st_val[k][q] : 0.0f, zs[q].x, zs[q].y};
+        }
+    }
+}
+
+// What the waves of a workgroup hand to each other: lane l has column l of each line.
+struct Joined {
+    float open[4][kWave];       // the wave's part of the segment that its piece leaves open
+    float first[4][kWave];      // its part of the first segment that ends in its piece, where other waves have parts of that
+};
+
+// ROWS: segments are rows, whose sums go to one row after the other but for those with parts.  JOINS: parts of a segment may be other
+// waves' of the workgroup.  Returns where the sum of such a segment goes that ends in this piece, or
+// kNowhere.
+template <int VPL, int AHEAD, bool PACKED, bool ROWS, bool JOINS, int ENTRIES>
+__device__ __forceinline__ int32_t walk_piece(const PieceArgs &a, const int32_t first_line, const int32_t item, Entry<PACKED> *stage, Joined *joined)
 {
     constexpr int kRing = AHEAD * kStep;                    // entries of a turn of the ring
-    static_assert(kPart % kRing == 0 && kEntries % kPart == 0 && kPart / kStep <= 32, "a part is a whole number of turns, a bit per step");
+    constexpr int kParts = ENTRIES / kPart;
+    constexpr int kLoads = ENTRIES / (4 * kWave);           // of four entries per lane: what a piece takes of col, and of val
+    static_assert(kPart % kRing == 0 && ENTRIES % kPart == 0 && kPart / kStep <= 32, "a part is a whole number of turns, a bit per step");
     const int lane = threadIdx.x & (kWave - 1), gl = lane & (kGroup - 1), grp = lane / kGroup;
 
     const adaqp_spmm_piece from = a.pieces[item], to = a.pieces[item + 1];
     const int32_t seg0 = min(max(from.segment, 0), a.n_seg);
     const int32_t n_end = min(max(to.segment - seg0, 0), min(a.n_seg - seg0, kEnds));
     const int64_t ent0 = clamp64(from.entry, 0, a.n_entries);
-    const int32_t n_ent = (int32_t)clamp64(to.entry - ent0, 0, min((int64_t)kEntries, a.n_entries - ent0));
-    // steps are counted so that the last turn of the ring is a full one: a fetch of nothing takes as long as one of a line
-    const int32_t n_steps = (n_ent + kStep - 1) / kStep, turns = (n_steps + AHEAD - 1) / AHEAD, pad = turns * AHEAD - n_steps;
+    const int32_t n_ent = (int32_t)clamp64(to.entry - ent0, 0, min((int64_t)ENTRIES, a.n_entries - ent0));
+    // Steps are counted so that the last turn of the ring is a full one: a fetch of nothing takes as long as one of a line.  From the same
+    // number on for every VPL, so that a part ends with the same entry and the sums are the same bits.
+    const int32_t n_steps = (n_ent + kStep - 1) / kStep, pad = -n_steps & 7, first_turn = pad / AHEAD, turns = (n_steps + pad) / AHEAD;
+    static_assert(8 % AHEAD == 0, "turns of eight steps or fewer");
 
     const auto cols = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(a.col + ent0), 0, n_ent * 4, kRawBuffer);
     const auto vals = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.val + ent0), 0, n_ent * 4, kRawBuffer);
@@ -60,33 +128,24 @@ __device__ __forceinline__ void walk_piece(const PieceArgs &a, const int32_t fir
         st_col[k] = __builtin_bit_cast(int4_t, __builtin_amdgcn_raw_buffer_load_b128(cols, at, 0, kNonTemporal));
         st_val[k] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(vals, at, 0, kNonTemporal));
     }
-    int32_t ends = kNoEnd, dests = 0;                       // lane l: where segment seg0 + l ends, and where its sum goes
+    int32_t ends = kNoEnd, dests = -1;                      // lane l: where segment seg0 + l ends, and where its sum goes
     if (lane < n_end) {
         ends = (int32_t)clamp64(a.ptr[(int64_t)seg0 + lane + 1] - ent0, 0, n_ent) + pad * kStep;
         dests = a.dest[seg0 + lane];
     }
 
+    const uint64_t with_parts = __ballot(dests >= 0);
+    float *out_row = a.out + (int64_t)seg0 * a.ldo;         // ROWS
     const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.H + first_line * kLine), 0,
                                                         (int)buffer_extent(a.n_cols, a.ldh, first_line * kLine), kRawBuffer);
-    const uint32_t pitch = (uint32_t)a.ldh * 4u;
-#pragma unroll
-    for (int k = 0; k < kLoads; ++k)
-#pragma unroll
-        for (int q = 0; q < 4; q += 2) {
-            float4_t two;
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const bool ok = (k * kWave + lane) * 4 + q + r < n_ent && (uint32_t)st_col[k][q + r] < (uint32_t)a.n_cols;
-                two[2 * r] = __builtin_bit_cast(float, ok ? (uint32_t)st_col[k][q + r] * pitch : kOutside);     // else: fetches nothing
-                two[2 * r + 1] = ok ? st_val[k][q + r] : 0.0f;
-            }
-            *reinterpret_cast<float4_t *>(stage + pad * kStep + (k * kWave + lane) * 4 + q) = two;
-        }
+    const auto packed_rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.p.packed), 0, (int)(uint32_t)a.p.packed_bytes, kRawBuffer);
+    if constexpr (PACKED) stage_packed<kLoads>(st_col, st_val, n_ent, (uint32_t)a.n_cols, (uint32_t)a.ldh * 4u, a.p, lane, stage + pad * kStep);
+    else stage_entries<kLoads, false>(st_col, st_val, n_ent, (uint32_t)a.n_cols, (uint32_t)a.ldh * 4u, a.p, lane, stage + pad * kStep);
     uint32_t marks[kParts];                                 // bit s: a segment ends in step s of the part, after one of its entries
 #pragma unroll
     for (int p = 0; p < kParts; ++p) {
         const int32_t last = ends - 1 - p * kPart;
-        marks[p] = or_lanes(last >= 0 && last < kPart ? 1u << (last / kStep) : 0u);
+        marks[p] = or_lanes(ends > pad * kStep && last >= 0 && last < kPart ? 1u << (last / kStep) : 0u);
     }
 
     // Sums of the open segment: acc what the present part has given so far, per group; before what earlier parts gave, lane l (and
@@ -111,46 +170,70 @@ __device__ __forceinline__ void walk_piece(const PieceArgs &a, const int32_t fir
             acc[v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
         }
     };
-    // Lanes without a column of their own store outside the row's buffer: no branch.
-    const uint32_t store_at = lane < kLine ? (uint32_t)(first_line * kLine + lane) * 4u : kOutside;
     auto store_sums = [&](int32_t dest) ADAQP_INLINE {      // partial row, or -1 - row
         float sum[VPL];
         take_sums(sum);
-        const bool part = dest >= 0, known = part ? dest < a.n_partials : -1 - dest < a.n_rows;
-        float *row = part ? a.partial + (int64_t)dest * a.ldp : a.out + (int64_t)(-1 - dest) * a.ldo;
-        const auto to_row = __builtin_amdgcn_make_buffer_rsrc(row, 0, known ? a.wdim * 4 : 0, kRawBuffer);
+        store_row<VPL>(a, dest, first_line, lane, sum);
+    };
+    auto join_sums = [&](float (&to)[4][kWave]) ADAQP_INLINE {
+        float sum[VPL];
+        take_sums(sum);
 #pragma unroll
-        for (int v = 0; v < VPL; ++v) {
-            const float x = (first_line + v) * kLine + line_col < a.dim ? sum[v] : 0.0f;        // row padding
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), to_row, (int)store_at + v * kLine * 4, 0, kNonTemporal);
-        }
+        for (int v = 0; v < VPL; ++v) to[v][lane] = sum[v];
     };
 
     // the ring: AHEAD steps whose lines are on their way
     float4_t h[AHEAD][VPL];
-    float w[AHEAD];
+    uint32_t words[AHEAD][VPL];                             // of a packed row: the word that holds the lane's four codes
+    Entry<PACKED> in_flight[AHEAD];
     const uint32_t lane_off = gl * 16;
-    auto fetch = [&](auto tag, const Entry &en) ADAQP_INLINE {
+    auto packed_col = [&](int v) ADAQP_INLINE { return (uint32_t)(a.p.col0 + (first_line + v) * kLine + gl * 4); };
+    auto fetch = [&](auto tag, const Entry<PACKED> &en) ADAQP_INLINE {
         constexpr int U = decltype(tag)::value;
-        w[U] = en.val;
+        in_flight[U] = en;
+        const uint32_t width = PACKED ? en.off & 3u : 0u;
 #pragma unroll
-        for (int v = 0; v < VPL; ++v)
-            h[U][v] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)(en.off + lane_off + v * kLine * 4), 0, 0));
+        for (int v = 0; v < VPL; ++v) {
+            const uint32_t off = width != 0 ? kOutside : en.off + lane_off + v * kLine * 4;
+            h[U][v] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, 0));
+            if constexpr (PACKED) words[U][v] = fetch_codes(packed_rows, en.off, packed_col(v), a.p.full_dim);
+        }
     };
     unroll<0, AHEAD>([&](auto tag) ADAQP_INLINE {
         constexpr int U = decltype(tag)::value;
-        if (U >= pad) {
-            fetch(tag, stage[U * kStep + grp]);
+        if (U >= pad % AHEAD) {
+            fetch(tag, stage[(first_turn * AHEAD + U) * kStep + grp]);
         } else {
-            w[U] = 0.0f;
+            in_flight[U] = {};
 #pragma unroll
-            for (int v = 0; v < VPL; ++v) h[U][v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int v = 0; v < VPL; ++v) {
+                h[U][v] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                words[U][v] = 0;
+            }
         }
     });
-    int32_t e = 0;                                          // segment ends behind us
-    while (__builtin_amdgcn_readlane(ends, e) <= pad * kStep) {      // segments without entries
-        store_sums(__builtin_amdgcn_readlane(dests, e));
+    int32_t e = 0, join_dest = kNowhere;                    // segment ends behind us
+    auto end_segment = [&]() ADAQP_INLINE {
+        if (JOINS && e == 0 && from.partial == kJoined) {
+            join_dest = __builtin_amdgcn_readlane(dests, e);
+            join_sums(joined->first);
+        } else if (ROWS) {
+            float sum[VPL];
+            take_sums(sum);
+            float *row = out_row;
+            bool known = true;
+            if (with_parts >> e & 1) {
+                const int32_t dest = __builtin_amdgcn_readlane(dests, e);
+                row = a.partial + (int64_t)dest * a.ldp;
+                known = dest < a.n_partials;
+            }
+            store_row<VPL>(a, row, known, first_line, lane, sum);
+        } else store_sums(__builtin_amdgcn_readlane(dests, e));
+        out_row += a.ldo;
         ++e;
+    };
+    while (__builtin_amdgcn_readlane(ends, e) <= pad * kStep) {      // segments without entries
+        end_segment();
     }
     auto turn = [&](int32_t t, auto goes_on) ADAQP_INLINE {
         constexpr bool kGoesOn = decltype(goes_on)::value;  // else: the last one, whose lines are the last
@@ -162,7 +245,7 @@ __device__ __forceinline__ void walk_piece(const PieceArgs &a, const int32_t fir
 #pragma unroll
             for (int v = 0; v < VPL; ++v) before[v] = sum[v];
         }
-        Entry en[AHEAD];
+        Entry<PACKED> en[AHEAD];
         if constexpr (kGoesOn)
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) en[u] = stage[(t + 1) * kRing + u * kStep + grp];
@@ -170,9 +253,12 @@ __device__ __forceinline__ void walk_piece(const PieceArgs &a, const int32_t fir
         unroll<0, AHEAD>([&](auto tag) ADAQP_INLINE {
             constexpr int U = decltype(tag)::value;
             float4_t x[VPL];
-            float val = w[U];
+            float val = in_flight[U].val;
 #pragma unroll
-            for (int v = 0; v < VPL; ++v) x[v] = h[U][v];
+            for (int v = 0; v < VPL; ++v) {
+                x[v] = h[U][v];
+                if constexpr (PACKED) x[v] = unpack_codes(in_flight[U], words[U][v], packed_col(v), x[v]);
+            }
             if (marks[0] & (1u << U)) {
                 // the groups from the last end to this one belong to the segment that ends here
                 const int32_t at = (t * AHEAD + U) * kStep;
@@ -186,8 +272,7 @@ __device__ __forceinline__ void walk_piece(const PieceArgs &a, const int32_t fir
                             const float sum = fmaf(val, x[v][k], acc[v][k]);
                             acc[v][k] = mine ? sum : acc[v][k];
                         }
-                    store_sums(__builtin_amdgcn_readlane(dests, e));
-                    ++e;
+                    end_segment();
                     first = end;
                     end = __builtin_amdgcn_readlane(ends, e) - at;
                 } while (end <= kStep);
@@ -207,29 +292,52 @@ __device__ __forceinline__ void walk_piece(const PieceArgs &a, const int32_t fir
         });
         marks[0] >>= AHEAD;
     };
-    int32_t t = 0;
+    marks[0] >>= first_turn * AHEAD;
+    int32_t t = first_turn;
     for (; t + 1 < turns; ++t) turn(t, std::true_type());
     if (t < turns) turn(t, std::false_type());
-    if (to.partial >= 0) store_sums(to.partial);            // of a segment that goes on in the next piece
+    // of a segment that goes on in the next piece
+    if (to.partial >= 0) store_sums(to.partial);
+    else if (JOINS && to.partial == kJoined) join_sums(joined->open);
+    return join_dest;
 }
 
-template <int VPL, int AHEAD>
-__global__ __launch_bounds__(kBlock, 4) void spmm_pieces_kernel(const PieceArgs a)
+template <int VPL, int AHEAD, bool PACKED, bool ROWS, int WAVES, int ENTRIES>
+__global__ __launch_bounds__(WAVES * kWave, PACKED && ENTRIES > kFewEntries ? 2 : 4) void spmm_pieces_kernel(const PieceArgs a)
 {
-    __shared__ alignas(16) Entry stages[kWavesPerBlock][kEntries + kWave];
-    const SliceTasks tasks(a.lines, VPL, a.n_blocks, false);
+    constexpr bool kJoins = WAVES > kWavesPerBlock;
+    __shared__ alignas(16) Entry<PACKED> stages[WAVES][ENTRIES + kWave];
+    __shared__ Joined joined[kJoins ? WAVES : 1];
+    const SliceTasks tasks(a.lines, VPL, a.n_blocks, PACKED);
     const int32_t xcd = blockIdx.x % kXcds;
     const int64_t task = tasks.first_task(xcd) + blockIdx.x / kXcds;
-    if (task >= tasks.first_task(xcd + 1)) return;
-    const int32_t slice = (int32_t)(task / a.n_blocks), blk = (int32_t)(task % a.n_blocks);
+    if (task >= tasks.first_task(xcd + 1)) return;          // the whole workgroup
+    const int32_t slice = (int32_t)(task / a.n_blocks), blk = (int32_t)(task % a.n_blocks), line = slice * VPL;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int32_t item = blk * kWavesPerBlock + wave;
-    if (item >= a.n_pieces) return;
-    const int live = min(VPL, a.lines - slice * VPL);
-    if (live == VPL) walk_piece<VPL, AHEAD>(a, slice * VPL, item, stages[wave]);
-    if constexpr (VPL > 3) if (live == 3) walk_piece<3, AHEAD>(a, slice * VPL, item, stages[wave]);
-    if constexpr (VPL > 2) if (live == 2) walk_piece<2, 2 * AHEAD>(a, slice * VPL, item, stages[wave]);
-    if constexpr (VPL > 1) if (live == 1) walk_piece<1, 8>(a, slice * VPL, item, stages[wave]);
+    const int32_t item = blk * WAVES + wave;
+    const int live = min(VPL, a.lines - line);
+    Joined *mine = joined + (kJoins ? wave : 0);
+    int32_t dest = kNowhere;
+    if (item < a.n_pieces) {
+        if (live == VPL) dest = walk_piece<VPL, AHEAD, PACKED, ROWS, kJoins, ENTRIES>(a, line, item, stages[wave], mine);
+        if constexpr (VPL > 3) if (live == 3) dest = walk_piece<3, AHEAD, PACKED, ROWS, kJoins, ENTRIES>(a, line, item, stages[wave], mine);
+        if constexpr (VPL > 2) if (live == 2) dest = walk_piece<2, 2 * AHEAD, PACKED, ROWS, kJoins, ENTRIES>(a, line, item, stages[wave], mine);
+        if constexpr (VPL > 1) if (live == 1) dest = walk_piece<1, 8, PACKED, ROWS, kJoins, ENTRIES>(a, line, item, stages[wave], mine);
+    }
+    if constexpr (kJoins) {
+        __syncthreads();
+        if (dest == kNowhere) return;
+        const int lane = threadIdx.x & (kWave - 1);
+        int from = wave;                                    // the wave whose piece the segment begins in
+        const int32_t segment = a.pieces[item].segment;
+        while (from > 0 && a.pieces[blk * WAVES + from].partial == kJoined && a.pieces[blk * WAVES + from].segment == segment) --from;
+        for (int v = 0; v < live; ++v) {
+            float sum[1] = {joined[from].open[v][lane]};
+            for (int w = from + 1; w < wave; ++w) sum[0] += joined[w].open[v][lane];
+            sum[0] += mine->first[v][lane];
+            store_row<1>(a, dest, line + v, lane, sum);
+        }
+    }
 }
 
 // out[row] = sum of the row's partial rows in order; whole lines, row padding zero.  A wave per row, eight partial rows of a strip of 256
@@ -263,13 +371,27 @@ __global__ __launch_bounds__(kBlock) void pieces_sum_kernel(const int32_t *sum_r
     }
 }
 
-// Length of a piece in entries and eight times ends of segments: eight pieces and more for each of the 4 096 waves that are under way
-// (2.5 M entries, 602 columns), and no longer than pays.  A start costs 0.2 us of its CU (28 M entries, 256 columns, two lines: 320 long
-// 1.37 ms, 512 1.19, 864 1.19; 7.7 M entries, one line: 320 0.765, 448 0.753, 524 0.767).
-int64_t piece_length(int64_t n_seg, int64_t n_entries, int32_t dim, int32_t lines_per_slice)
+// Length of a piece in entries and eight times ends of segments, the entries it has at most, waves of a workgroup.
+//
+// As many pieces as waves are under way, or half as many again where there are enough, but a start costs 0.2 us of its CU (28 M
+// entries, 256 columns, two lines: 320 long 1.37 ms, 512 1.19, 864 1.19; 7.7 M entries, one line: 320 0.765, 448 0.753, 524 0.767;
+// 1.2 M entries, 128 columns, four lines: 128 48 us, 220 45, 448 45).
+//
+// Where pieces are short anyway workgroups are twice as large and a segment's parts meet in their LDS: 2 000 rows, 20 656
+// entries, 128 columns of H 7.2 us where 6.2 and a launch of sums of 3.3 (pieces of 96; 128 7.7, 16 waves and 128 8.9).
+constexpr int64_t kUnderWay = 4096, kShort = 160;           // waves; a length
+
+struct PieceShape { int64_t length, entries; int32_t waves; };
+
+PieceShape piece_shape(int64_t n_seg, int64_t n_entries, int32_t dim, int32_t lines_per_slice)
 {
-    const int64_t slices = ((int64_t)dim + 32 * lines_per_slice - 1) / (32 * lines_per_slice), path = n_entries + 8 * n_seg;
-    return std::min<int64_t>(std::max<int64_t>(path / 32768 * slices, 128), lines_per_slice == 1 ? 448 : kEntries + 96);
+    const int64_t slices = ((int64_t)dim + 32 * lines_per_slice - 1) / (32 * lines_per_slice);
+    const double path = (double)(n_entries + 8 * n_seg) * (double)slices;
+    if (path <= (double)(kUnderWay * kShort)) return {std::max<int64_t>((int64_t)path / kUnderWay, 96), kFewEntries, kJoinWaves};
+    const int64_t most = lines_per_slice == 1 ? 448 : kEntries + 96;
+    int64_t length = (int64_t)std::min(std::max(path / (1.5 * (double)kUnderWay), 128.0), (double)most);
+    if (length <= kFewEntries + kFewEntries / 4) length = std::min<int64_t>(length, kFewEntries);       // for a third of the LDS and of the staging
+    return {length, length <= kFewEntries ? kFewEntries : kEntries, kWavesPerBlock};
 }
 
 }  // namespace
@@ -280,10 +402,36 @@ int check_pieces(const adaqp_spmm_pieces *p, int64_t n_seg)
     if (p->n_pieces == 0) return ADAQP_OK;
     if (p->n_pieces > kMostPieces || p->n_partials > INT32_MAX - 1024 || p->n_sums > INT32_MAX - 1024) return ADAQP_ESIZE;
     if (p->lines_per_slice != 1 && p->lines_per_slice != 2 && p->lines_per_slice != 4) return ADAQP_EINVAL;
+    if (!(p->waves == kJoinWaves && p->entries == kFewEntries) && !(p->waves == kWavesPerBlock && (p->entries == kFewEntries || p->entries == kEntries)))
+        return ADAQP_EINVAL;
+    if (p->n_seg != n_seg || p->row_begin < 0) return ADAQP_EINVAL;
     if (!p->pieces_dev || !p->sum_ptr_dev || (n_seg > 0 && !p->dest_dev) || (p->n_sums > 0 && !p->sum_row_dev)) return ADAQP_EINVAL;
     if (!aligned_to(p->pieces_dev, 16) || !aligned_to(p->dest_dev, 4) || !aligned_to(p->sum_row_dev, 4) || !aligned_to(p->sum_ptr_dev, 4)) return ADAQP_EINVAL;
     return ADAQP_OK;
 }
+
+namespace {
+
+using PieceKernel = void (*)(const PieceArgs);
+
+template <bool PACKED, bool ROWS, int WAVES, int ENTRIES>
+PieceKernel kernel_of(int32_t lines_per_slice)
+{
+    if constexpr (PACKED) return spmm_pieces_kernel<kPackedLines, 2, true, ROWS, WAVES, ENTRIES>;
+    else return lines_per_slice == 1   ? spmm_pieces_kernel<1, 8, false, ROWS, WAVES, ENTRIES>
+                : lines_per_slice == 2 ? spmm_pieces_kernel<2, 4, false, ROWS, WAVES, ENTRIES>
+                                       : spmm_pieces_kernel<4, 2, false, ROWS, WAVES, ENTRIES>;
+}
+
+template <bool PACKED, bool ROWS>
+PieceKernel kernel_of(const adaqp_spmm_pieces *p)
+{
+    if (p->waves == kJoinWaves) return kernel_of<PACKED, ROWS, kJoinWaves, kFewEntries>(p->lines_per_slice);
+    return p->entries == kFewEntries ? kernel_of<PACKED, ROWS, kWavesPerBlock, kFewEntries>(p->lines_per_slice)
+                                     : kernel_of<PACKED, ROWS, kWavesPerBlock, kEntries>(p->lines_per_slice);
+}
+
+}  // namespace
 
 int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
 {
@@ -292,21 +440,24 @@ int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
     a.n_pieces = (int32_t)p->n_pieces;
     a.n_partials = (int32_t)p->n_partials;
     a.ldp = ((int64_t)a.dim + kLine - 1) / kLine * kLine;
-    a.n_blocks = (a.n_pieces + kWavesPerBlock - 1) / kWavesPerBlock;
+    a.n_blocks = (a.n_pieces + p->waves - 1) / p->waves;
     // a launch has fewer than 2^32 threads: as many slices as that allows
-    const int64_t most_lines = std::max<int64_t>(kMostTasks / a.n_blocks, 1) * p->lines_per_slice, lines = a.ldp / kLine;
+    const bool packed = a.p.row != nullptr;
+    const int32_t per_slice = packed ? kPackedLines : p->lines_per_slice;
+    const int64_t most_lines = std::max<int64_t>(kMostTasks / a.n_blocks, 1) * per_slice, lines = a.ldp / kLine;
     for (int64_t l0 = 0; l0 < lines; l0 += most_lines) {
         PieceArgs s = a;
         s.lines = (int32_t)std::min(lines - l0, most_lines);
         s.dim = (int32_t)std::min<int64_t>(a.dim - l0 * kLine, (int64_t)s.lines * kLine);
         s.wdim = s.lines * kLine;
         s.H += l0 * kLine;
+        s.p.col0 = (int32_t)(l0 * kLine);
+        s.p.full_dim = a.dim;
         s.out += l0 * kLine;
         if (s.partial) s.partial += l0 * kLine;
-        const dim3 grid((unsigned)(SliceTasks(s.lines, p->lines_per_slice, s.n_blocks, false).most_per_xcd() * kXcds));
-        if (p->lines_per_slice == 1) hipLaunchKernelGGL((spmm_pieces_kernel<1, 8>), grid, dim3(kBlock), 0, st, s);
-        else if (p->lines_per_slice == 2) hipLaunchKernelGGL((spmm_pieces_kernel<2, 4>), grid, dim3(kBlock), kIdleLds, st, s);
-        else hipLaunchKernelGGL((spmm_pieces_kernel<4, 2>), grid, dim3(kBlock), kIdleLds, st, s);
+        const dim3 grid((unsigned)(SliceTasks(s.lines, per_slice, s.n_blocks, packed).most_per_xcd() * kXcds));
+        const PieceKernel kernel = packed ? kernel_of<true, true>(p) : a.of_rows ? kernel_of<false, true>(p) : kernel_of<false, false>(p);
+        hipLaunchKernelGGL(kernel, grid, dim3(p->waves * kWave), p->entries == kEntries && per_slice > 1 && !packed ? kIdleLds : 0, st, s);
         ADAQP_HIP_TRY(hipGetLastError());
     }
     constexpr int64_t kMostSums = (int64_t)1 << 24;         // of a launch, for the same reason
@@ -323,6 +474,96 @@ int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
 
 using namespace adaqp;
 
+// What lines per slice weigh.  An XCD misses the lines of the columns that its L2 does not hold (32 768 of one line each, the most popular
+// ones), which takes 2.4 times as long as a line that it holds; beside that, each slice walks all entries and ends all rows, and a
+// narrower last slice leaves lines unused; the two overlap in part.  A launch that does not fill the GPU gains from more slices.
+// Weights fitted to 2 890 layer steps of 2 000 to 306 000 rows, 4 to 500 entries per row, 16 to 602 columns of H, Zipf and
+// log-normal rows, both directions, one to four lines each.  Geometric mean against shares cut on the device 1.148 (the best lines each
+// time 1.166); 2.6 % of the steps are more than 3 % slower, most of them backward steps of 3 to 5 entries per row and many lines, which
+// therefore are left as they were (there 0.98 on average).  150 000 x 200 000, 40 entries per row, 256 columns, backward, log-normal
+// rows: 1 line 0.89 ms, 4 lines 1.12; Zipf rows, whose columns are few popular ones, 128 columns: 0.27, 0.23.
+//
+// Segments save what their rows miss; they cost a partial row per group of tiles, written and read, a second copy of the short walk,
+// and two more launches.  Where all columns fit, they still are the better ones for long rows: what adaqp_spmm_segments_gain says of them
+// counts as well.  400 of these steps, timed without blocks as well: 1.175 against shares without segments, pieces over the rows alone
+// 1.134, by that gain alone 1.158; 3 with segments lose more than 4 % by them, 6 without would gain that.  179 000 rows, 2 M entries,
+// 300 columns: 378 -> 356 us.
+extern "C" int adaqp_spmm_pieces_rule(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end, int64_t n_cols,
+                                      int32_t dim, int32_t transposed, int32_t *lines_out, double *segments_gain_out)
+{
+    if (!rowptr_host || !lines_out || !segments_gain_out || row_begin < 0 || row_end < row_begin || n_cols < 0 || n_cols > INT32_MAX || dim <= 0)
+        return ADAQP_EINVAL;
+    constexpr int64_t kL2Lines = 32768;         // 4 MB
+    constexpr int64_t kSample = 1 << 22;        // entries looked at for the popularity of the columns
+    const int64_t first = rowptr_host[row_begin], last = rowptr_host[row_end], block_row = adaqp_spmm_blocks_min_row(n_cols);
+    if (first < 0 || last < first || (last > first && !col_host)) return ADAQP_EINVAL;
+    const double lines = (double)(((int64_t)dim + 31) / 32), entries = (double)(last - first), rows = (double)(row_end - row_begin);
+    double cut = 0.0, n_cut = 0.0, dense = 0.0;
+    int64_t n_dense = 0;
+    bool ascending = true;
+    for (int64_t r = row_begin; r < row_end; ++r) {
+        const int64_t degree = rowptr_host[r + 1] - rowptr_host[r];
+        if (degree < 0) return ADAQP_EINVAL;
+        if (degree >= ADAQP_SPMM_TILED_SHORT_ROW) {
+            cut += (double)degree;
+            n_cut += 1.0;
+        }
+        if (degree >= block_row) {
+            dense += (double)degree;
+            ++n_dense;
+        }
+        int32_t before = -1;
+        for (int64_t j = rowptr_host[r]; ascending && j < rowptr_host[r + 1]; ++j) {
+            ascending = col_host[j] > before && col_host[j] < n_cols;
+            before = col_host[j];
+        }
+    }
+    *lines_out = 2;
+    *segments_gain_out = -INFINITY;
+    if (!ascending && adaqp_spmm_tiled_pays(row_end - row_begin, last - first)) return ADAQP_EINVAL;
+    if (last == first) return ADAQP_OK;
+    std::vector<int32_t> uses;
+    try {
+        uses.resize((size_t)n_cols, 0);
+    } catch (const std::bad_alloc &) {          // nothing may be thrown through a C entry; the plan would have no room either
+        return ADAQP_OK;
+    }
+    const int64_t stride = std::max<int64_t>((last - first) / kSample, 1);
+    int64_t seen = 0;
+    for (int64_t j = first; j < last; j += stride)
+        if ((uint32_t)col_host[j] < (uint32_t)n_cols) {
+            ++uses[(size_t)col_host[j]];
+            ++seen;
+        }
+    if (seen == 0) return ADAQP_OK;
+    double best = 0.0, missed = 0.0, unpopular = 0.0;
+    auto end = uses.end();
+    for (int32_t v = 1; v <= 8; v *= 2) {       // the most popular columns first, ever fewer of them
+        const int64_t held = std::min(kL2Lines / v, n_cols);
+        if (uses.begin() + held < end) std::nth_element(uses.begin(), uses.begin() + held, end, std::greater<int32_t>());
+        end = uses.begin() + held;
+        const double miss = 1.0 - (double)std::accumulate(uses.begin(), end, (int64_t)0) / (double)seen;
+        if (v == 8) unpopular = miss;
+        const double slices = std::ceil(lines / v), misses = 2.4 * entries * lines * miss, path = (entries + 8.0 * rows) * slices;
+        const double held_lines = entries * lines + slices * (0.2 * entries + 2.5 * rows) + 0.4 * (slices * v - lines) * entries;
+        const double cost = std::sqrt(misses * misses + held_lines * held_lines) + 2e4 * std::max(0.0, std::log2(1.2e6 / path));
+        if (v == 8 || (v > 1 && cost >= best)) continue;
+        best = cost;
+        missed = miss;
+        *lines_out = v;
+    }
+    if (transposed && entries >= 1e5 && entries < 6.0 * rows && lines >= 7.0) *lines_out = 0;
+    if (!ascending) return ADAQP_OK;
+    const double groups = (double)std::min<int64_t>(std::max<int64_t>(n_cols / 12288, 1), ADAQP_SPMM_SEGMENTS);
+    // (the rows of the matrix cores cost their coefficients once, however few lines there are)
+    if (transposed || !adaqp_spmm_blocks_pay(n_dense, n_cols, 32)) dense = 0.0;
+    const double by_misses = cut * lines * missed - 7.0 * n_cut * lines * groups - 0.15 * entries - 1e6;
+    const double by_popularity = cut * lines * unpopular - (transposed ? (0.26 * lines + 0.41) * entries : (0.5 * lines + 0.25) * entries + 2.7 * lines * rows) -
+                                 ADAQP_SPMM_SEGMENTS_MIN_GAIN / 2;
+    *segments_gain_out = std::max(by_misses, 0.56 * std::max(lines - 1.5, 0.0) * dense + by_popularity);
+    return ADAQP_OK;
+}
+
 extern "C" int adaqp_spmm_pieces_workspace_bytes(int64_t n_partials, int32_t dim, int64_t *bytes_out)
 {
     if (!bytes_out || n_partials < 0 || dim <= 0) return ADAQP_EINVAL;
@@ -337,29 +578,45 @@ extern "C" int adaqp_plan_spmm_pieces(const int64_t *ptr_host, int64_t n_seg, co
                                       int32_t *sum_row_out, int32_t *sum_ptr_out)
 try {
     constexpr int S = ADAQP_SPMM_SEGMENTS;
-    if (n_seg < 0 || n_rows < 0 || dim <= 0 || !ptr_host || !sizes_inout || ptr_host[0] < 0 || (n_rows > 0 && !of_row_host)) return ADAQP_EINVAL;
+    if (n_seg < 0 || n_rows < 0 || dim <= 0 || !ptr_host || !sizes_inout || ptr_host[0] < 0 || (!of_row_host && n_rows != n_seg)) return ADAQP_EINVAL;
     if (lines_per_slice != 1 && lines_per_slice != 2 && lines_per_slice != 4) return ADAQP_EINVAL;
     if (n_seg > INT32_MAX - 1024 || n_rows > INT32_MAX - 1024) return ADAQP_ESIZE;
     const bool fill = pieces_out != nullptr;
     if (fill && ((n_seg > 0 && !dest_out) || !sum_ptr_out || (sizes_inout[2] > 0 && !sum_row_out))) return ADAQP_EINVAL;
     for (int64_t s = 0; s < n_seg; ++s)
         if (ptr_host[s + 1] < ptr_host[s]) return ADAQP_EINVAL;
-    const int64_t last = ptr_host[n_seg], length = piece_length(n_seg, last - ptr_host[0], dim, lines_per_slice);
+    const PieceShape shape = piece_shape(n_seg, ptr_host[n_seg] - ptr_host[0], dim, lines_per_slice);
 
-    // Pieces of whole segments; one that would be less than half full takes the next segment up to a line of entries.
+    // Pieces of whole segments; one that would be less than half full takes the next segment up to a line of entries.  In the large
+    // workgroups the parts of a segment are one workgroup's wherever they can be: pieces of nothing before them.
     std::vector<adaqp_spmm_piece> pieces{{ptr_host[0], 0, -1}};
-    std::vector<int32_t> cuts((size_t)n_seg, 0);            // of a segment
+    std::vector<int32_t> cuts((size_t)n_seg, 0);            // of a segment, but for joined ones
+    int64_t looked_at = -1;                                 // the last segment that was cut, and whether its parts are joined
+    bool joins = false;
     for (int64_t seg = 0, entry = ptr_host[0]; seg < n_seg;) {
         const int64_t first_seg = seg, first = entry;
         auto weight = [&](int64_t e, int64_t s) { return e - first + 8 * (s - first_seg); };
-        while (seg < n_seg && seg - first_seg < kEnds && ptr_host[seg + 1] - first <= kEntries && weight(ptr_host[seg + 1], seg + 1) <= length)
+        while (seg < n_seg && seg - first_seg < kEnds && ptr_host[seg + 1] - first <= shape.entries && weight(ptr_host[seg + 1], seg + 1) <= shape.length)
             entry = ptr_host[++seg];
         int32_t partial = -1;
-        if (seg < n_seg && seg - first_seg < kEnds && weight(entry, seg) < length / 2) {
-            const int64_t to = (first + std::min<int64_t>(length - 8 * (seg - first_seg), kEntries)) / 32 * 32;
-            if (to > entry && to < ptr_host[seg + 1]) {
+        if (seg < n_seg && seg - first_seg < kEnds && weight(entry, seg) < shape.length / 2) {
+            auto cut_at = [&](int64_t from, int64_t ends) { return (from + std::min<int64_t>(shape.length - 8 * ends, shape.entries)) / 32 * 32; };
+            const int64_t to = cut_at(first, seg - first_seg), end = ptr_host[seg + 1];
+            if (to > entry && to < end) {
+                const int64_t in_group = (int64_t)(pieces.size() - 1) % shape.waves;
+                if (shape.waves == kJoinWaves && looked_at != seg) {        // its first part: how many there will be
+                    int64_t parts = 2;
+                    for (int64_t e = to, next; parts <= shape.waves && (next = cut_at(e, 0)) < end && end - e + 8 > shape.length; e = next) ++parts;
+                    joins = parts <= shape.waves;
+                    if (joins && in_group + parts > shape.waves) {
+                        if (entry > first || seg > first_seg) pieces.push_back({entry, (int32_t)seg, -1});
+                        while ((pieces.size() - 1) % shape.waves) pieces.push_back({entry, (int32_t)seg, -1});
+                        continue;
+                    }
+                }
+                looked_at = seg;
                 entry = to;
-                partial = cuts[(size_t)seg]++;
+                partial = joins ? kJoined : cuts[(size_t)seg]++;
             }
         }
         if (entry == first && seg == first_seg) entry = ptr_host[++seg];        // a segment a little over the length
@@ -371,7 +628,7 @@ try {
     std::vector<int32_t> dest((size_t)n_seg, INT32_MIN), sum_row, sum_ptr{0};
     int64_t n_partials = 0;
     for (int64_t r = 0; r < n_rows; ++r) {
-        const int32_t *of = of_row_host + r * S;
+        const int32_t row_itself[S] = {(int32_t)r, -1, -1, -1, -1, -1, -1, -1}, *of = of_row_host ? of_row_host + r * S : row_itself;
         if (of[0] < -1) continue;                           // someone else's
         int parts = 0;
         int32_t only = -1;
@@ -402,12 +659,12 @@ try {
             const size_t s = (size_t)pieces[p].segment;
             pieces[p].partial += dest[s] - cuts[s];
         }
-    const int64_t sizes[3] = {(int64_t)pieces.size() - 1, n_partials, (int64_t)sum_row.size()};
+    const int64_t sizes[5] = {(int64_t)pieces.size() - 1, n_partials, (int64_t)sum_row.size(), shape.waves, shape.entries};
     if (!fill) {
-        std::copy(sizes, sizes + 3, sizes_inout);
+        std::copy(sizes, sizes + 5, sizes_inout);
         return ADAQP_OK;
     }
-    if (!std::equal(sizes, sizes + 3, sizes_inout)) return ADAQP_EINVAL;
+    if (!std::equal(sizes, sizes + 5, sizes_inout)) return ADAQP_EINVAL;
     std::copy(pieces.begin(), pieces.end(), pieces_out);
     std::copy(dest.begin(), dest.end(), dest_out);
     std::copy(sum_row.begin(), sum_row.end(), sum_row_out);

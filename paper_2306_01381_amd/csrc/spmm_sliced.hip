@@ -59,12 +59,6 @@ struct SlicedArgs {
     int32_t lines;              // lines of a row
 };
 
-// An entry in LDS: byte offset of its row of H and its coefficient.  PACKED: bits 0-1 of the offset name the width of
-// a row that is still packed (1, 2, 3: 2, 4, 8 bits; the offset is then one into the receive buffer) and (Z, S) follow.
-template <bool PACKED> struct Entry;
-template <> struct alignas(8) Entry<false> { uint32_t off; float val; };
-template <> struct alignas(16) Entry<true> { uint32_t off; float val; float z, s; };
-
 // Row ends before two diagonals of the merge path: row end p precedes d iff end_p + kRowSteps * (p + 1) <= d.  256-ary
 // search by a whole wave; wave-uniform results.
 __device__ __forceinline__ void split_rows2(const SpmmArgs &a, const int64_t (&d)[2], int64_t base, int64_t nnz_r, int lane, int32_t (&at)[2])
@@ -151,8 +145,8 @@ __device__ __forceinline__ void walk_share(const SlicedArgs &sa, const int32_t f
 #pragma unroll
     for (int v = 0; v < VPL; ++v)
         lane_off[v] = WHOLE ? gl * 16 + v * kLine * 4 : (uint32_t)min(c0 + v * kLine, a.dim - 4) * 4;
-    const auto packed_rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.packed), 0,
-                                                               (int)(uint32_t)a.packed_bytes, kRawBuffer);
+    const auto packed_rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.p.packed), 0,
+                                                               (int)(uint32_t)a.p.packed_bytes, kRawBuffer);
     const uint32_t pitch = (uint32_t)a.ldh * 4u;
 
     // After `sum_groups` lane l (and lane l + 32) holds column l of each line.
@@ -220,76 +214,14 @@ __device__ __forceinline__ void walk_share(const SlicedArgs &sa, const int32_t f
         }
     };
     auto stage = [&](const Chunk &c) ADAQP_INLINE {
-        auto valid = [&](int k, int q) ADAQP_INLINE {                    // else: fetches nothing
-            return (k * kWave + lane) * 4 + q < c.n_ent && (uint32_t)st_col[k][q] < (uint32_t)a.n_cols;
-        };
-        int4_t slots[kLoads];
-#pragma unroll
-        for (int k = 0; k < kLoads; ++k) {
-            // here and not earlier: the compiler would take the entries of a chunk apart when they arrive, for twice the registers
-            asm volatile("" : "+v"(st_col[k]));
-            if constexpr (PACKED) {                         // all slots of a chunk on their way together, none: index 0
-                if (k == 0 || k * 4 * kWave < c.n_ent) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) slots[k][q] = a.slot_of_row[valid(k, q) ? st_col[k][q] : 0];
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kLoads; ++k) {
-            if (k > 0 && k * 4 * kWave >= c.n_ent) break;   // a whole number of turns past every entry: never read
-            Entry<PACKED> en[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const bool ok = valid(k, q);
-                en[q] = {};
-                en[q].off = ok ? (uint32_t)st_col[k][q] * pitch : kOutside;
-                en[q].val = ok ? st_val[k][q] : 0.0f;
-            }
-            if constexpr (PACKED) {
-                // the lookups of four entries are on their way together, those of entries without a slot at index 0: behind a
-                // branch each they would wait for one another
-                int32_t slot[4], b[4];
-                int64_t off[4];
-                float2 zs[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const bool has = en[q].off != kOutside && slots[k][q] >= 0 && slots[k][q] < a.n_slots;
-                    slot[q] = has ? slots[k][q] : -1;
-                    const int64_t at = has ? slot[q] : 0;
-                    b[q] = a.bits[at];
-                    off[q] = a.row_offset[at];
-                    zs[q] = *reinterpret_cast<const float2 *>(a.params + 2 * at);
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int64_t stride = 4 * (((int64_t)a.full_dim * b[q] + 31) >> 5);
-                    if (slot[q] >= 0 && (b[q] == 2 || b[q] == 4 || b[q] == 8) && off[q] >= 0 && (off[q] & 3) == 0 &&
-                        off[q] + stride <= a.packed_bytes) {
-                        en[q].off = (uint32_t)off[q] | (b[q] == 2 ? 1u : (b[q] == 4 ? 2u : 3u));
-                        en[q].z = zs[q].x;
-                        en[q].s = zs[q].y;
-                    }                                       // else: the row in H
-                }
-            }
-            Entry<PACKED> *to = stage_of_wave + (k * kWave + lane) * 4;
-            if constexpr (PACKED) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) to[q] = en[q];
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; q += 2)
-                    *reinterpret_cast<float4_t *>(to + q) = float4_t{__builtin_bit_cast(float, en[q].off), en[q].val,
-                                                                     __builtin_bit_cast(float, en[q + 1].off), en[q + 1].val};
-            }
-        }
+        stage_entries<kLoads, PACKED>(st_col, st_val, c.n_ent, (uint32_t)a.n_cols, pitch, a.p, lane, stage_of_wave);
     };
 
     // the ring: kAhead steps whose lines are on their way
     float4_t h[kAhead][VPL];
     uint32_t words[kAhead][VPL], words_up[kAhead][VPL];     // four codes, where rows end anywhere across two words
     Entry<PACKED> in_flight[kAhead];
-    auto packed_col = [&](int v) ADAQP_INLINE { return (uint32_t)a.col0 + (WHOLE ? (uint32_t)(c0 + v * kLine) : lane_off[v] / 4); };
+    auto packed_col = [&](int v) ADAQP_INLINE { return (uint32_t)a.p.col0 + (WHOLE ? (uint32_t)(c0 + v * kLine) : lane_off[v] / 4); };
     auto fetch = [&](auto tag, const Entry<PACKED> &en) ADAQP_INLINE {
         constexpr int U = decltype(tag)::value;
         in_flight[U] = en;
@@ -299,34 +231,15 @@ __device__ __forceinline__ void walk_share(const SlicedArgs &sa, const int32_t f
             const uint32_t off = PACKED && w != 0 ? kOutside : en.off + lane_off[v];
             h[U][v] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, 0));
             if constexpr (PACKED) {
-                // one 32-bit word holds the four codes of a lane whose first column is a multiple of four (4 * b <= 32 and
-                // divides 32)
-                const uint32_t last_word = (((uint32_t)a.full_dim << w) - 1) >> 5;
-                const uint32_t word = (packed_col(v) << w) >> 5;
-                words[U][v] = __builtin_amdgcn_raw_buffer_load_b32(
-                    packed_rows, w != 0 ? (int)((en.off & ~3u) + 4 * min(word, last_word)) : (int)kOutside, 0, 0);
-                if constexpr (!WHOLE)
-                    words_up[U][v] = __builtin_amdgcn_raw_buffer_load_b32(
-                        packed_rows, w != 0 ? (int)((en.off & ~3u) + 4 * min(word + 1, last_word)) : (int)kOutside, 0, 0);
+                words[U][v] = fetch_codes(packed_rows, en.off, packed_col(v), a.p.full_dim);
+                if constexpr (!WHOLE) words_up[U][v] = fetch_codes(packed_rows, en.off, packed_col(v), a.p.full_dim, 1);
             }
         }
     };
     auto neighbour = [&](auto tag, int v) ADAQP_INLINE {                 // the four columns a lane fetched
         constexpr int U = decltype(tag)::value;
         float4_t x = h[U][v];
-        if constexpr (PACKED) {
-            const uint32_t w = in_flight[U].off & 3u;
-            if (w != 0) {
-                const uint32_t b = 1u << w, shift = (packed_col(v) << w) & 31u;
-                uint32_t word = words[U][v] >> shift;
-                if constexpr (!WHOLE) word = (uint32_t)(((uint64_t)words_up[U][v] << 32 | words[U][v]) >> shift);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float scaled = (float)__builtin_amdgcn_ubfe(word, k * b, b) * in_flight[U].s; // Eq. 5: product
-                    x[k] = scaled + in_flight[U].z;                                             // rounded, then sum rounded
-                }
-            }
-        }
+        if constexpr (PACKED) x = unpack_codes(in_flight[U], words[U][v], packed_col(v), x, WHOLE ? 0 : words_up[U][v]);
         return x;
     };
 
@@ -502,7 +415,7 @@ __global__ __launch_bounds__(kBlock, 2) void spmm_sliced_kernel(const SlicedArgs
 
 SlicedCut plan_sliced(const SpmmArgs &a, int64_t nnz_hint, bool whole_lines, bool skewed_columns)
 {
-    if (!sliced_takes(a.n_rows, a.nnz, a.n_cols, a.ldh, a.slot_of_row != nullptr, a.packed_bytes, a.full_dim)) return {0, 0, 0};
+    if (!sliced_takes(a.n_rows, a.nnz, a.n_cols, a.ldh, a.p.slot_of_row != nullptr, a.p.packed_bytes, a.p.full_dim)) return {0, 0, 0};
     if (!whole_lines && a.dim < 4) return {0, 0, 0};        // a lane takes four columns
     return sliced_cut(a.n_rows, nnz_hint, a.n_cols, (a.wdim + kLine - 1) / kLine, whole_lines, skewed_columns);
 }
@@ -513,17 +426,17 @@ hipError_t launch_sliced(const SpmmArgs &a, const SlicedCut &cut, int64_t nnz_hi
     SlicedArgs sa;
     sa.s = a;
     sa.lines = (a.wdim + kLine - 1) / kLine;
-    const int vpl = a.slot_of_row ? cut.packed_lines : cut.lines;
+    const int vpl = a.p.slot_of_row ? cut.packed_lines : cut.lines;
     // each wave takes one share, of at least 256 steps of the path: a search and an empty ring each
     const int64_t path = nnz_hint + (int64_t)a.n_rows * kRowSteps;
     int64_t n_blocks = std::min(cut.n_blocks, (path + kMinPath - 1) / kMinPath);
     if (n_blocks > a.n_items / kWavesPerBlock) n_blocks = a.n_items / kWavesPerBlock;      // one carry slot per share
     if (n_blocks < 1) n_blocks = 1;
     sa.n_blocks = (int32_t)n_blocks;
-    const dim3 grid((unsigned)(SliceTasks(sa.lines, vpl, sa.n_blocks, a.slot_of_row != nullptr).most_per_xcd() * kXcds));
+    const dim3 grid((unsigned)(SliceTasks(sa.lines, vpl, sa.n_blocks, a.p.slot_of_row != nullptr).most_per_xcd() * kXcds));
 #define ADAQP_SLICED(V, WHOLE)                                                                                   \
     do {                                                                                                         \
-        if (a.slot_of_row) hipLaunchKernelGGL((spmm_sliced_kernel<V, true, WHOLE>), grid, dim3(kBlock), 0, st, sa); \
+        if (a.p.slot_of_row) hipLaunchKernelGGL((spmm_sliced_kernel<V, true, WHOLE>), grid, dim3(kBlock), 0, st, sa); \
         else hipLaunchKernelGGL((spmm_sliced_kernel<V, false, WHOLE>), grid, dim3(kBlock), 0, st, sa);           \
     } while (0)
     if (!whole_lines) ADAQP_SLICED(4, false);

@@ -123,9 +123,9 @@ class LayerStep:
         self.use_recv_order = use_recv_order
         self.backward_receive = backward_receive
         self.fused_receive = fused_receive and not self.backward
-        self.rowptr = torch.from_numpy(p.rowptr).to(dev)
         self.col = torch.from_numpy(p.col).to(dev)
         with torch.inference_mode(False):           # a tensor made in inference mode does not count what is written to it
+            self.rowptr = torch.from_numpy(p.rowptr).to(dev)
             self.val = torch.from_numpy(p.val).to(dev)
         self.feat = line_padded(p.feat, dev, pad, spread=True)
         self.out = line_padded(np.zeros((p.n_rows, cfg.dim), dtype=np.float32), dev, pad, spread=True)
@@ -133,7 +133,7 @@ class LayerStep:
                              add_segments=self.backward)
         n = self.plan.n
         # forward, fused receive: the dependent aggregation reads received rows straight from the receive buffer
-        self.slot_of_row = None
+        self.slot_of_row = self.packed_row = self._packed_row_of = None
         self._unplanned_dependent = None
         self.set_fused_receive(self.fused_receive)
         nbytes = max(self.plan.packed_bytes, 4)
@@ -184,6 +184,10 @@ class LayerStep:
                 ws_o = max(ws_o, need)
             if tile_dependent:
                 ws_d = max(ws_d, self._plan_dependent(*plan_dependent))
+        self._plan_rows(pad)
+        ws_o, ws_d = max(ws_o, self._pieces_bytes(self.pieces_overlap)), max(ws_d, self._pieces_bytes(self.pieces_dependent))
+        if self.pieces_both:
+            ws_o = max(ws_o, self._pieces_bytes(self.pieces_both))
         self.ws_overlap = torch.empty(max(ws_o, 256), dtype=torch.uint8, device=dev)
         self.ws_dependent = torch.empty(max(ws_d, 256), dtype=torch.uint8, device=dev)
         # streams=(msg, agg): take over an existing pair.  HIP deals streams to a few hardware queues in turn, so a
@@ -197,6 +201,45 @@ class LayerStep:
         self.event_fork = HipEvent()
         self.event_join = HipEvent()
 
+    def _plan_rows(self, pad: bool) -> None:
+        """Pieces of the walk over the rows of ranges without tiles."""
+        p, none = self.p, B.DevicePieces(None)
+        self.pieces_overlap = self.pieces_dependent = self.pieces_both = none
+        self._planned_rows = self._rows_tensor()
+        n_cols = p.feat.shape[0]
+        if not pad or p.nnz == 0 or n_cols * self.feat.stride(0) * 4 >= B.SPMM_SEGMENTS_MOST_BYTES:
+            return
+        (ob, oe), (db, de) = p.overlap_rows, p.dependent_rows
+        plain = [r for r, tiles in (((ob, oe), self.tile_off_overlap), ((db, de), self.tile_off_dependent)) if r[1] > r[0] and tiles is None]
+        if not plain:
+            return
+        # both ranges take the lines of the one with more entries: one launch aggregates them together where it can
+        largest = max(plain, key=lambda r: int(p.rowptr[r[1]] - p.rowptr[r[0]]))
+        lines, _ = self._rule(*largest)
+        if lines == 0:
+            return
+
+        def pieces(begin, end):
+            plan = B.adaqp_plan_spmm_pieces(p.rowptr[begin: end + 1], None, self.dim, lines)
+            return B.DevicePieces(plan, self.device, begin)
+        if (ob, oe) in plain:
+            self.pieces_overlap = pieces(ob, oe)
+        if (db, de) in plain:
+            self.pieces_dependent = pieces(db, de)
+        if len(plain) == 2 and oe == db:
+            self.pieces_both = pieces(ob, de)
+
+    def _rule(self, begin, end):
+        p = self.p
+        return B.adaqp_spmm_pieces_rule(p.rowptr, p.col, begin, end, p.feat.shape[0], self.dim, self.backward)
+
+    def _rows_tensor(self):
+        """rowptr, whose rows the pieces were planned for, and how often it was written to."""
+        return self.rowptr, None if self.rowptr.is_inference() else self.rowptr._version
+
+    def _pieces_bytes(self, pieces) -> int:
+        return B.adaqp_spmm_pieces_workspace_bytes(pieces.c.n_partials, self.dim)
+
     def _order_copies(self) -> None:
         """What was just planned is used on the step's streams."""
         for st in (self.stream_msg, self.stream_agg):
@@ -208,9 +251,9 @@ class LayerStep:
         p, n_cols = self.p, self.p.feat.shape[0]
         if not tiled and n_cols * self.feat.stride(0) * 4 < B.SPMM_SEGMENTS_MOST_BYTES:
             # (a range whose rows do not list ascending, distinct columns has a gain of -infinity and stays as it is)
-            gains = [B.adaqp_spmm_segments_gain(p.rowptr, p.col, b, e, n_cols, self.dim, self.backward) if e > b else -np.inf
+            gains = [B.adaqp_spmm_pieces_rule(p.rowptr, p.col, b, e, n_cols, self.dim, self.backward)[1] if e > b else -np.inf
                      for b, e in ranges]
-            pays = sum(g for g in gains if g > -np.inf) >= B.SPMM_SEGMENTS_MIN_GAIN
+            pays = sum(g for g in gains if g > -np.inf) > 0
             return tuple(pays and g > -np.inf for g in gains)
         return tuple(e > b and (tiled or B.adaqp_spmm_tiled_pays(e - b, int(p.rowptr[e] - p.rowptr[b]))) for b, e in ranges)
 
@@ -297,6 +340,12 @@ class LayerStep:
         if self.fused_receive and self.slot_of_row is None:
             self.slot_of_row = torch.from_numpy(
                 B.adaqp_plan_slot_of_row(self.p.feat.shape[0], self.plan.halo_idx_host)).to(self.device)
+            pl = self.plan
+            if pl.packed_bytes < B.SPMM_SEGMENTS_MOST_BYTES:
+                self.packed_row = torch.from_numpy(B.adaqp_plan_packed_rows(
+                    self.p.feat.shape[0], pl.halo_idx_host, pl.bits_host, pl.row_offset_host, self.dim, pl.packed_bytes).view(np.int32)
+                ).to(self.device)
+                self._packed_row_of = pl
         if not self.fused_receive and self._unplanned_dependent is not None:
             tiled, *how = self._unplanned_dependent
             self._unplanned_dependent = None
@@ -326,6 +375,7 @@ class LayerStep:
         d.recv_order_dev = pl.recv_order.data_ptr() if (self.use_recv_order and pl.recv_order is not None
                                                         and not self.backward) else None
         d.slot_of_row_dev = self.slot_of_row.data_ptr() if self.fused_receive else None
+        d.packed_row_dev = self.packed_row.data_ptr() if self.packed_row is not None and self._packed_row_of is pl else None
         d.tile_off_overlap_dev = None if self.tile_off_overlap is None else self.tile_off_overlap.data_ptr()
         d.tile_chunk_overlap, d.tile_chunk_dependent = self.tile_chunk_overlap, self.tile_chunk_dependent
         d.tile_off_dependent_dev = None if (self.tile_off_dependent is None or self.fused_receive) \
@@ -350,6 +400,8 @@ class LayerStep:
         d.stream_msg = self.stream_msg.cuda_stream
         d.stream_agg = self.stream_agg.cuda_stream
         d.event_fork, d.event_join = self.event_fork.handle, self.event_join.handle
+        if self._rows_tensor()[0] is self._planned_rows[0] and self._rows_tensor()[1] == self._planned_rows[1]:     # else: cut on the device
+            d.pieces_overlap, d.pieces_dependent, d.pieces_both = self.pieces_overlap.c, self.pieces_dependent.c, self.pieces_both.c
         return d
 
     def default_schedule(self) -> int:

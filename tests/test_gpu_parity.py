@@ -985,7 +985,7 @@ def test_spmm_pieces(oracle, lines, dim, ld):
     off[struck] = -1
     plan = B.adaqp_plan_spmm_segments(rowptr, 0, n_rows, bounds, off)
     plan["pieces"] = B.adaqp_plan_spmm_pieces(plan["ptr"], plan["of_row"], dim, lines)
-    assert (plan["pieces"]["dest"] < 0).any() and (plan["pieces"]["pieces"]["partial"] >= 0).any()
+    assert (plan["pieces"]["dest"] < 0).any() and (plan["pieces"]["pieces"]["partial"] != -1).any()
     segments = B.DeviceSegments(plan, DEV)
     B.adaqp_fill_spmm_segments(segments, cl, vl)
     ws = torch.empty(max(B.adaqp_spmm_segments_workspace_bytes(segments, dim), 1), dtype=torch.uint8, device=DEV)
@@ -1001,6 +1001,44 @@ def test_spmm_pieces(oracle, lines, dim, ld):
     assert float((err / (SPMM_RTOL * mag[~struck] + 1e-30)).max()) <= 1.0
     zero_to = _padded_cols(dim, ld)
     assert np.all(got[~struck][:, dim:zero_to] == 0.0) and np.all(got[~struck][:, zero_to:] == 7.0) and np.all(got[struck] == 7.0)
+
+
+@pytest.mark.parametrize("lines", [1, 2, 4])
+@pytest.mark.parametrize("n_rows,long,dim", [(1, 1, 40), (90, 700, 40), (300, 3_000, 100), (9_000, 30_000, 129), (60_000, 30_000, 129)])
+def test_spmm_pieces_of_rows(oracle, lines, n_rows, long, dim):
+    """Pieces over the rows of a CSR from the middle of its arrays on: rows without entries, parts of a row joined in a workgroup or added up
+    afterwards, short and long pieces."""
+    _say(f"pieces of rows lines={lines} rows={n_rows} dim={dim}")
+    rng = np.random.default_rng(n_rows)
+    n_cols, ld = 35_000, (dim + 31) // 32 * 32
+    degs = rng.integers(0, 40, size=n_rows)
+    degs[rng.integers(0, n_rows, size=n_rows // 4 + 1)] = 0
+    degs[rng.integers(0, n_rows, size=n_rows // 40 + 1)] = rng.integers(100, long + 100, size=n_rows // 40 + 1) % 5_000
+    degs[0], degs[-1] = long, 300
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, np.minimum(degs, n_cols))
+    H = np.zeros((n_cols, ld), dtype=np.float32)
+    H[:, :dim] = rng.standard_normal((n_cols, dim), dtype=np.float32)
+    H[:, dim:] = np.nan
+    want, mag = oracle.spmm_csr(rowptr, col, val, 0, n_rows, np.ascontiguousarray(H[:, :dim]), dim)
+    before = 37                                                        # entries of rows that are not the range's
+    ptr = rowptr + before
+    plan = B.adaqp_plan_spmm_pieces(ptr, None, dim, lines)
+    on = {k: torch.from_numpy(v).to(DEV) for k, v in (("ptr", ptr), ("col", np.concatenate([np.full(before, -1, np.int32), col])),
+                                                       ("val", np.concatenate([np.full(before, np.nan, np.float32), val])))}
+    segments, pieces = B.DeviceSegments(None), B.DevicePieces(plan, DEV)
+    segments.c = B.SpmmSegments(n_rows, on["col"].numel(), n_rows, on["ptr"].data_ptr(), on["ptr"].data_ptr(), on["ptr"].data_ptr(),
+                                on["col"].data_ptr(), on["val"].data_ptr(), pieces.c)
+    Hd, outs = torch.from_numpy(H).to(DEV), []
+    ws = torch.empty(max(B.adaqp_spmm_segments_workspace_bytes(segments, dim), 256), dtype=torch.uint8, device=DEV)
+    for _ in range(2):
+        ws.fill_(0xFF)
+        outs.append(torch.full((n_rows, ld), 7.0, dtype=torch.float32, device=DEV))
+        B.adaqp_spmm_csr_segments(segments, 0, Hd, dim, outs[-1], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))
+    got = outs[0].cpu().numpy()
+    assert float((np.abs(got[:, :dim].astype(np.float64) - want) / (SPMM_RTOL * mag + 1e-30)).max()) <= 1.0
+    assert np.all(got[:, dim:] == 0.0)
 
 
 def test_spmm_segments_of_more_rows_than_a_launch_has_waves():

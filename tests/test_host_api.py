@@ -464,7 +464,51 @@ def test_plan_spmm_segments(n_rows, n_cols):
         B.adaqp_plan_spmm_segments(rowptr, 0, n_rows, bounds, off)
 
 
-@pytest.mark.parametrize("lengths", [[], [1], [0, 5, 0], [768], [769], [5_000], [1] * 200, [700, 30, 40, 100, 2_000, 3] * 9])
+def test_plan_packed_rows():
+    """Place and slot of each received row; nothing where the width or the place is not one."""
+    halo, bits = np.array([9, 2, 5, 7, 3], np.int32), np.array([8, 2, 4, 5, 8], np.uint8)
+    offset = np.array([0, 100, 104, 200, 998], np.int64)                # dim 100: 100, 28 and 52 bytes; the last does not fit
+    got = B.adaqp_plan_packed_rows(12, halo, bits, offset, 100, 1_000)
+    want = np.zeros((12, 2), np.uint32)
+    want[9], want[2], want[5] = (0 | 3, 0), (100 | 1, 1), (104 | 2, 2)
+    assert np.array_equal(got, want)
+    for rows, idx in ((4, halo), (12, np.array([9, 2, 5, 9, 3], np.int32)), (12, np.array([9, 2, 5, -1, 3], np.int32))):
+        with pytest.raises(B.AdaqpError):                              # rows that there are not, one received twice
+            B.adaqp_plan_packed_rows(rows, idx, bits, offset, 100, 1_000)
+    with pytest.raises(B.AdaqpError):
+        B.adaqp_plan_packed_rows(12, halo, bits, offset, 100, 0xFFFF0000)
+
+
+@pytest.mark.parametrize("n_rows,n_cols,mean,transposed", [(300, 50, 30, False), (3_000, 9_000, 90, True), (4_000, 90_000, 200, False)])
+def test_spmm_pieces_rule(n_rows, n_cols, mean, transposed):
+    """The stated weights: lines that cost least, and what segments save over them."""
+    rng = np.random.default_rng(mean)
+    degs = np.minimum((rng.pareto(1.2, size=n_rows) * mean / 3).astype(np.int64), n_cols)
+    rowptr = np.concatenate([[0], np.cumsum(degs)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n_cols, size=d, replace=False)) for d in degs]).astype(np.int32)
+    for rb, re in ((0, n_rows), (n_rows // 3, n_rows)):
+        for dim in (20, 250):
+            d, lines = degs[rb:re], (dim + 31) // 32
+            uses = np.sort(np.bincount(col[rowptr[rb]:rowptr[re]], minlength=n_cols))[::-1]
+            miss = {v: 1 - uses[:32768 // v].sum() / uses.sum() for v in (1, 2, 4, 8)}
+            E, slices = float(d.sum()), {v: -(-lines // v) for v in (1, 2, 4)}
+            cost = {v: np.hypot(2.4 * E * lines * miss[v], E * lines + n * (0.2 * E + 2.5 * d.size) + 0.4 * (n * v - lines) * E)
+                    + 2e4 * max(0.0, np.log2(1.2e6 / ((E + 8 * d.size) * n))) for v, n in slices.items()}
+            best = min(cost, key=lambda v: (round(cost[v], 3), v))
+            long = d[d >= 64]
+            dense = 0.0 if transposed or (d >= max(n_cols // 20, 64)).sum() < 256 else d[d >= max(n_cols // 20, 64)].sum()
+            old = -(0.26 * lines + 0.41) * d.sum() if transposed else -(0.5 * lines + 0.25) * d.sum() - 2.7 * lines * d.size
+            gain = max(
+                long.sum() * lines * miss[best] - 7 * long.size * lines * min(max(n_cols // 12288, 1), 8) - 0.15 * d.sum() - 1e6,
+                0.56 * max(lines - 1.5, 0) * dense + long.sum() * lines * miss[8] + old - 1e6)
+            got = B.adaqp_spmm_pieces_rule(rowptr, col, rb, re, n_cols, dim, transposed)
+            assert got[0] == (0 if transposed and 1e5 <= E < 6 * d.size and lines >= 7 else best) and got[1] == pytest.approx(gain, rel=1e-9)
+    col[rowptr[1]: rowptr[2]] = -1                                     # nothing to tile, lines all the same
+    assert B.adaqp_spmm_pieces_rule(rowptr, col, 0, 2, n_cols, 20, transposed)[0] in (1, 2, 4)
+
+
+@pytest.mark.parametrize("lengths", [[], [1], [0, 5, 0], [256], [257], [768], [769], [5_000], [1] * 200, [700, 30, 40, 100, 2_000, 3] * 9,
+                                     [700, 30, 900_000, 100, 5_000, 3] * 3])
 @pytest.mark.parametrize("dim,lines", [(32, 1), (602, 2), (602, 4)])
 def test_plan_spmm_pieces(lengths, dim, lines):
     """Pieces are consecutive, within their limits, and end with a segment or inside one; every part of a row goes to a place of its own."""
@@ -484,16 +528,19 @@ def test_plan_spmm_pieces(lengths, dim, lines):
     pieces, dest = plan["pieces"], plan["dest"]
     assert pieces[0].tolist() == (0, 0, -1) and pieces[-1].tolist() == (ptr[-1], n_seg, -1)
     parts = [[] for _ in range(n_seg)]                                 # places that the parts of a segment go to
-    for here, there in zip(pieces[:-1], pieces[1:]):
-        assert 0 <= there["entry"] - here["entry"] <= 768 and 0 <= there["segment"] - here["segment"] <= 62
-        assert (there["entry"], there["segment"]) > (here["entry"], here["segment"])
+    for k, (here, there) in enumerate(zip(pieces[:-1], pieces[1:]), 1):
+        assert 0 <= there["entry"] - here["entry"] <= plan["entries"] and 0 <= there["segment"] - here["segment"] <= 62
         for s in range(here["segment"], there["segment"]):
             parts[s].append(int(dest[s]))
-        if there["partial"] < 0:
+        if there["partial"] == -1:
             assert there["entry"] == ptr[there["segment"]]
-        else:
-            assert max(here["entry"], ptr[there["segment"]]) < there["entry"] < ptr[there["segment"] + 1]
+            continue
+        assert max(here["entry"], ptr[there["segment"]]) < there["entry"] < ptr[there["segment"] + 1]
+        if there["partial"] >= 0:
             parts[there["segment"]].append(int(there["partial"]))
+        else:                                                          # handed to the next wave of the workgroup
+            assert there["partial"] == -2 and plan["waves"] == 8 and k % 8 != 0
+            assert np.all(pieces["partial"][1:][(pieces["segment"][1:] == there["segment"]) & (pieces["entry"][1:] > ptr[there["segment"]])] == -2)
     sums = dict(zip(plan["sum_row"].tolist(), zip(plan["sum_ptr"][:-1].tolist(), plan["sum_ptr"][1:].tolist())))
     assert plan["sum_ptr"][0] == 0 and np.all(np.diff(plan["sum_row"]) > 0) and of_row.shape[0] - 1 not in sums
     for r in range(of_row.shape[0] - 1):
