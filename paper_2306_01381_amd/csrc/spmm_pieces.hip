@@ -340,9 +340,10 @@ __global__ __launch_bounds__(WAVES * kWave, PACKED && ENTRIES > kFewEntries ? 2 
     }
 }
 
-// out[row] = sum of the row's partial rows in order; whole lines, row padding zero.  A wave per row, eight partial rows of a strip of 256
-// columns in flight together (28 000 rows of eight, 256 columns: 42 us, 6.1 TB/s).  Rows of one segment need none: of 306 000 rows
-// one in twelve has two (129 -> 20 us).
+// out[row] = sum of the row's partial rows, always in the same order; whole lines, row padding zero.  A wave per row and strip of at most
+// 256 columns (28 000 rows of eight, 256 columns: 42 us, 6.1 TB/s).  Rows of one segment need none: of 306 000 rows one in twelve has
+// two (129 -> 20 us).  Few rows are bound by the latency of their loads: narrow strips leave the wave's other lanes to other parts, and
+// the strips of a wide row are waves of their own.  Sums go by pairs, as a chain of 24 parts is where the error of a long row comes from.
 __global__ __launch_bounds__(kBlock) void pieces_sum_kernel(const int32_t *sum_row, const int32_t *sum_ptr, int64_t n_sums, int32_t n_partials,
                                                             const float *partial, int32_t dim, int64_t wdim, float *out, int64_t ldo, int32_t n_rows)
 {
@@ -352,18 +353,29 @@ __global__ __launch_bounds__(kBlock) void pieces_sum_kernel(const int32_t *sum_r
     if (s >= n_sums) return;
     const int32_t row = sum_row[s], from = max(0, sum_ptr[s]), end = min(sum_ptr[s + 1], n_partials);
     if (row < 0 || row >= n_rows) return;
-    for (int64_t c = lane * 4; c < wdim; c += kWave * 4) {
+    const int of_part = wdim <= 32 ? 8 : wdim <= 64 ? 16 : wdim <= 128 ? 32 : kWave;        // lanes of one part
+    const int apart = kWave / of_part;
+    for (int64_t strip = blockIdx.y; strip * kWave * 4 < wdim; strip += gridDim.y) {
+        const int64_t c = (strip * kWave + lane % of_part) * 4;
         float4_t sum = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int32_t p = from; p < end; p += kAhead) {
+        for (int64_t p = from + lane / of_part; p < end; p += kAhead * apart) {
             float4_t x[kAhead];
 #pragma unroll
             for (int q = 0; q < kAhead; ++q) {
                 x[q] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-                if (p + q < end) x[q] = __builtin_nontemporal_load(reinterpret_cast<const float4_t *>(partial + (int64_t)(p + q) * wdim + c));
+                if (p + q * apart < end && c < wdim)
+                    x[q] = __builtin_nontemporal_load(reinterpret_cast<const float4_t *>(partial + (p + q * apart) * wdim + c));
             }
 #pragma unroll
-            for (int q = 0; q < kAhead; ++q) sum += x[q];
+            for (int half = kAhead / 2; half > 0; half /= 2)
+#pragma unroll
+                for (int q = 0; q < half; ++q) x[q] += x[q + half];
+            sum += x[0];
         }
+        for (int other = of_part; other < kWave; other *= 2)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sum[k] += __shfl_xor(sum[k], other);
+        if (lane >= of_part || c >= wdim) continue;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             if (c + k >= dim) sum[k] = 0.0f;
@@ -463,7 +475,8 @@ int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
     constexpr int64_t kMostSums = (int64_t)1 << 24;         // of a launch, for the same reason
     for (int64_t s0 = 0; s0 < p->n_sums; s0 += kMostSums) {
         const int64_t n = std::min(p->n_sums - s0, kMostSums);
-        hipLaunchKernelGGL(pieces_sum_kernel, dim3((unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock), 0, st, p->sum_row_dev + s0,
+        const dim3 grid((unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock), (unsigned)std::min<int64_t>((a.ldp + kWave * 4 - 1) / (kWave * 4), 64));
+        hipLaunchKernelGGL(pieces_sum_kernel, grid, dim3(kBlock), 0, st, p->sum_row_dev + s0,
                            p->sum_ptr_dev + s0, n, a.n_partials, a.partial, a.dim, a.ldp, a.out, a.ldo, a.n_rows);
         ADAQP_HIP_TRY(hipGetLastError());
     }
