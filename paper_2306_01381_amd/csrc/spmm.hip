@@ -116,7 +116,7 @@ constexpr int32_t kFar = 0x7FFFFFFF;
 // PACKED: entries whose column has a slot in slot_of_row take the neighbour row from the packed receive buffer
 // and de-quantise it in registers, (float)code * S + Z as in Sec. 2.3 Eq. 5 (product rounded, then sum rounded),
 // so the result is bit-identical to de-quantising into H first - without writing and re-reading those rows.
-template <int VW, int NV, int U, bool PACKED>
+template <int VW, int NV, int U, bool PACKED, bool CHAINS>
 __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -142,11 +142,15 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
     // per-lane slice of a row: vectors v*64 + lane, v < NV; only the last one can fall off the row
     const bool last_ok = ((NV - 1) * kWave + lane) * VW < a.wdim;
 
-    float acc[NV][VW];
+    // CHAINS: a row's sum is what it had at the piece's last multiple of kChain entries, and what came since, so that in long pieces no
+    // chain of roundings is longer than in pieces of 32 steps (one sum over 128: up to 1.28 times their error against 64 bits).
+    constexpr int kChain = 32;
+    static_assert(kChain % U == 0 && kWave % kChain == 0, "chains end between groups of loads");
+    float acc[NV][VW], before[NV][VW];                      // (before: CHAINS)
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
-        for (int k = 0; k < VW; ++k) acc[v][k] = 0.0f;
+        for (int k = 0; k < VW; ++k) acc[v][k] = before[v][k] = 0.0f;
 
     // row-end staging: lane q holds the end (relative to j0) of row row_blk + q
     int64_t row = i0, row_blk = i0;
@@ -163,8 +167,20 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
     int32_t cur_end = __builtin_amdgcn_readlane(my_end, 0);
     bool dirty = false;
 
+    auto whole_sum = [&]() {
+        if constexpr (CHAINS) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int k = 0; k < VW; ++k) {
+                    acc[v][k] += before[v][k];
+                    before[v][k] = 0.0f;
+                }
+        }
+    };
     auto flush_row = [&]() {
         float *o = a.out + row * a.ldo;
+        whole_sum();
         if (a.wdim > a.dim) {                                   // row padding: whatever was gathered there is dropped
 #pragma unroll
             for (int k = 0; k < VW; ++k)
@@ -215,6 +231,17 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
             }
         }
         for (int32_t e = 0; e < nb; e += U) {
+            if constexpr (CHAINS) {
+                if (e % kChain == 0) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v)
+#pragma unroll
+                        for (int k = 0; k < VW; ++k) {
+                            before[v][k] += acc[v][k];
+                            acc[v][k] = 0.0f;
+                        }
+                }
+            }
             float h[U][NV][VW];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -288,6 +315,7 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
     // what is left belongs to a row that continues in the next piece
     if (dirty && row < a.n_rows) {
         float *cslot = a.carry + (int64_t)item * a.carry_ld;
+        whole_sum();
 #pragma unroll
         for (int v = 0; v < NV; ++v)
             if (v < NV - 1 || last_ok) store_vec<VW>(cslot + (v * kWave + lane) * VW, acc[v]);
@@ -383,12 +411,31 @@ bool geometry(int64_t n_rows, int64_t nnz, int32_t dim, Geometry *g)
     return true;
 }
 
+// Pieces of the merge-path kernel for rows that share lines: of at least 64 or 128 steps, or n_items.  Nearly every piece leaves a row
+// to the next, so short ones are held up by searches and carries once 6 000 of them fill the chip (send, receive and sums together,
+// pieces of 32 steps / as here: 8 000 rows of 30 entries, 72 columns 45.9 / 36.6 us; 60 000 of 16, 72 columns 107 / 85, 130 columns
+// 126 / 110; 30 000 of 55, 72 columns 165 / 122; 90 000 of 5, 72 columns 70.8 / 71.2).  Wide rows stay as they are: 64 steps gave 1.02
+// at 301 and 470 columns, 128 0.94 to 1.05.  So do whole lines (90 000 rows of 5, 160 columns: 0.945).
+constexpr int32_t kNarrow = 160;            // columns
+
+int32_t longer_pieces(int64_t total, int32_t dim, int32_t n_items)
+{
+    int64_t per = 32;
+    while (per < 128 && total / per > 6000) per *= 2;
+    const int64_t items = (total + per - 1) / per;
+    return dim <= kNarrow && items < n_items ? (int32_t)items : n_items;
+}
+
 template <int VW, int NV>
-hipError_t launch_merge(const SpmmArgs &a, dim3 grid, hipStream_t st)
+hipError_t launch_merge(const SpmmArgs &a, bool chains, hipStream_t st)
 {
     constexpr int U = NV >= 4 ? 4 : (NV >= 2 ? 8 : 16);
-    if (a.p.slot_of_row) hipLaunchKernelGGL((spmm_merge_kernel<VW, NV, U, true>), grid, dim3(kBlock), 0, st, a);
-    else hipLaunchKernelGGL((spmm_merge_kernel<VW, NV, U, false>), grid, dim3(kBlock), 0, st, a);
+    constexpr bool kMay = (NV - 1) * kWave * VW < kNarrow;      // some row with so many vectors is narrow
+    auto kernel = a.p.slot_of_row ? spmm_merge_kernel<VW, NV, U, true, false> : spmm_merge_kernel<VW, NV, U, false, false>;
+    if constexpr (kMay)
+        if (chains) kernel = a.p.slot_of_row ? spmm_merge_kernel<VW, NV, U, true, true> : spmm_merge_kernel<VW, NV, U, false, true>;
+    const dim3 grid((unsigned)((a.n_items + kWavesPerBlock - 1) / kWavesPerBlock));
+    hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, st, a);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((spmm_carry_kernel<VW, NV>), grid, dim3(kBlock), 0, st, a);
@@ -396,17 +443,17 @@ hipError_t launch_merge(const SpmmArgs &a, dim3 grid, hipStream_t st)
 }
 
 template <int VW>
-hipError_t launch_merge_nv(const SpmmArgs &a, int nv, dim3 grid, hipStream_t st)
+hipError_t launch_merge_nv(const SpmmArgs &a, int nv, bool chains, hipStream_t st)
 {
     switch (nv) {
-        case 1: return launch_merge<VW, 1>(a, grid, st);
-        case 2: return launch_merge<VW, 2>(a, grid, st);
-        case 3: return launch_merge<VW, 3>(a, grid, st);
-        case 4: return launch_merge<VW, 4>(a, grid, st);
-        case 5: return launch_merge<VW, 5>(a, grid, st);
-        case 6: return launch_merge<VW, 6>(a, grid, st);
-        case 7: return launch_merge<VW, 7>(a, grid, st);
-        case 8: return launch_merge<VW, 8>(a, grid, st);
+        case 1: return launch_merge<VW, 1>(a, chains, st);
+        case 2: return launch_merge<VW, 2>(a, chains, st);
+        case 3: return launch_merge<VW, 3>(a, chains, st);
+        case 4: return launch_merge<VW, 4>(a, chains, st);
+        case 5: return launch_merge<VW, 5>(a, chains, st);
+        case 6: return launch_merge<VW, 6>(a, chains, st);
+        case 7: return launch_merge<VW, 7>(a, chains, st);
+        case 8: return launch_merge<VW, 8>(a, chains, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -537,7 +584,6 @@ int adaqp::spmm_rows(const int64_t *rowptr_dev, const int32_t *col_dev, const fl
         a.p.row_offset = row_offset_dev;
         a.p.n_slots = n_slots;
         const int nv = (a.wdim + kWave * vw - 1) / (kWave * vw);
-        const dim3 grid((unsigned)((g.n_items + kWavesPerBlock - 1) / kWavesPerBlock));
         hipError_t err;
         const SlicedCut cut = plan_sliced(a, nnz_range, whole_lines, skewed_columns);
         if (cut.lines > 0) {
@@ -545,9 +591,12 @@ int adaqp::spmm_rows(const int64_t *rowptr_dev, const int32_t *col_dev, const fl
             if (err == hipSuccess)
                 err = vw == 4 ? launch_carry_nv<4>(a, nv, st)
                               : (vw == 2 ? launch_carry_nv<2>(a, nv, st) : launch_carry_nv<1>(a, nv, st));
-        } else if (vw == 4) err = launch_merge_nv<4>(a, nv, grid, st);
-        else if (vw == 2) err = launch_merge_nv<2>(a, nv, grid, st);
-        else err = launch_merge_nv<1>(a, nv, grid, st);
+        } else {
+            if (!whole_lines) a.n_items = longer_pieces(n_rows + nnz_range, dim, g.n_items);
+            const bool chains = a.n_items < g.n_items;
+            err = vw == 4 ? launch_merge_nv<4>(a, nv, chains, st)
+                          : (vw == 2 ? launch_merge_nv<2>(a, nv, chains, st) : launch_merge_nv<1>(a, nv, chains, st));
+        }
         ADAQP_HIP_TRY(err);
     }
     return ADAQP_OK;

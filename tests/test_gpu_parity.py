@@ -528,6 +528,26 @@ def _gpu_spmm_packed(rowptr, col, val, rb, re, H, dim, slot_of_row, packed, para
     return out.cpu().numpy()
 
 
+@pytest.mark.parametrize("dim,n_rows", [(65, 9_000), (72, 17_000), (129, 17_000), (130, 9_000), (160, 17_000), (161, 9_000)])
+def test_spmm_longer_pieces(oracle, dim, n_rows):
+    """Rows that share lines, pieces of 64 and 128 steps and (161 columns) of 32: rows of every length around a chain's and a piece's, the
+    same bits from packed rows."""
+    _say(f"spmm longer pieces dim={dim} rows={n_rows}")
+    rng = np.random.default_rng(7000 + dim)
+    n_cols, ld = 3_000, dim if dim != 160 else 164
+    degs = rng.integers(0, 48, size=n_rows)
+    degs[:18] = [2_900, 0, 1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 255, 256, 257]
+    degs[400:700], degs[-1] = 0, 1_500
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, degs)
+    assert n_rows + len(col) > 6_000 * (32 if n_rows == 9_000 else 64) and len(col) > 110_000
+    halo, bits, off, packed, params, H_plain, H_ref = _packed_case(oracle, rng, n_cols, 1_000, dim, ld, seed=5)
+    H = np.full((n_cols, ld), np.nan, dtype=np.float32)
+    H[:, :dim] = H_ref
+    plain = _check_spmm(oracle, rowptr, col, val, 0, n_rows, H, dim, ldo=ld)
+    fused = _gpu_spmm_packed(rowptr, col, val, 0, n_rows, H_plain, dim, B.adaqp_plan_slot_of_row(n_cols, halo), packed, params, bits, off, ld)
+    assert np.array_equal(plain.view(np.uint32), fused.view(np.uint32))
+
+
 @pytest.mark.parametrize("dim,ldh", [(128, 128), (602, 608), (602, 602), (300, 300), (7, 7), (1, 1), (66, 66),
                                      (130, 132), (250, 256), (2049, 2080), (2304, 2304), (4100, 4100), (515, 515)])
 def test_spmm_packed_rows(oracle, dim, ldh):
