@@ -540,9 +540,12 @@ def measure_config(name, args, headline, B, torch, np):
     else:
         alg = (b_o + b_d) / launches
         avg_ms = t_both / launches
+        planned = [x.c for x in (L.pieces_overlap, L.pieces_dependent, L.pieces_both)]
+        planned += [x.c.pieces for x in (L.segments_overlap, L.segments_dependent)]
         frac_hbm = primary_gbps / HBM_PEAK_GBPS
         roofline = {
-            "kernel": "spmm_sliced_kernel" if tiled or p.nnz >= 100_000 else "spmm_merge_kernel",
+            "kernel": ("spmm_pieces_kernel" if any(pieces.n_pieces for pieces in planned) else
+                       "spmm_sliced_kernel" if tiled or p.nnz >= 100_000 else "spmm_merge_kernel"),
             "bound": "hbm" if frac_hbm <= 1.0 else "l2",
             "achieved": primary_gbps, "peak": HBM_PEAK_GBPS if frac_hbm <= 1.0 else GATHER_RATE_GBPS, "unit": "GB/s",
             "frac": frac_hbm if frac_hbm <= 1.0 else primary_gbps / GATHER_RATE_GBPS, "traffic": None,
