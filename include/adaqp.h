@@ -240,7 +240,8 @@ int adaqp_assign_bits(int64_t n, const float *beta_host, const int32_t *peer_of_
  * other row.  Errors: EINVAL (index out of range, a row listed twice), ESIZE (n > 2^31 - 1). */
 int adaqp_plan_slot_of_row(int64_t n_rows, int64_t n, const int32_t *halo_idx_host, int32_t *slot_of_row_out);
 
-/* Host only: where the kernels that walk planned pieces find a received row: packed_row_out[r] = { byte offset in the receive buffer, its two low
+/* Host only: where the kernels that walk planned pieces find a received row, as adaqp_layer_step works it out on the device (packed_row_dev)
+ * from slot_of_row, bits and row_offset; for callers who want to see it.  packed_row_out[r] = { byte offset in the receive buffer, its two low
  * bits 1, 2, 3 for 2, 4, 8 bits, slot } for the row r = halo_idx_host[t], { 0, 0 } for rows that are not received or whose slot's width or
  * place is not one.  Per-slot arrays as for adaqp_unpack_dequant.  Errors: EINVAL (as adaqp_plan_slot_of_row), ESIZE (2^32 - 2^16 bytes and
  * more). */
@@ -665,8 +666,9 @@ typedef struct adaqp_layer_desc {
     /* optional (n_pieces = 0: the walk is cut on the device): adaqp_plan_spmm_pieces of the rows of a range without tile table, and of both
      * ranges where they touch (CHAIN), from the rowptr that rowptr_dev holds.  Line-padded feat and out only.  The workspace of the range
      * (the larger one) holds adaqp_spmm_pieces_workspace_bytes.  Where received rows are read packed (slot_of_row_dev) pieces take
-     * packed_row_dev [n_feat_rows], adaqp_plan_packed_rows of the receive buffer, and are not looked at without it. */
-    const adaqp_packed_row *packed_row_dev;
+     * packed_row_dev [n_feat_rows], scratch that each step fills from slot_of_row_dev, bits_dev and row_offset_dev, and are not
+     * looked at without it. */
+    adaqp_packed_row *packed_row_dev;
     adaqp_spmm_pieces pieces_overlap;
     adaqp_spmm_pieces pieces_dependent;
     adaqp_spmm_pieces pieces_both;

@@ -270,11 +270,17 @@ int range_bytes(const adaqp_layer_desc *d, const adaqp_spmm_pieces *pieces, int6
     return ADAQP_OK;
 }
 
+// Whether rows [rb, re) go as planned; fused: with received rows read from the receive buffer.
+bool takes_pieces(const adaqp_layer_desc *d, const adaqp_spmm_pieces *pieces, int64_t rb, int64_t re, bool fused)
+{
+    return planned_for(pieces, rb, re) && (!fused || d->packed_row_dev);
+}
+
 // Rows [rb, re) as planned, or along the merge path; fused: received rows are read from the receive buffer.
 int aggregate_range(const adaqp_layer_desc *d, int64_t rb, int64_t re, int64_t nz, bool fused, const adaqp_spmm_pieces *pieces, void *ws,
                     int64_t wsb, hipStream_t st)
 {
-    if (planned_for(pieces, rb, re) && (!fused || d->packed_row_dev)) {
+    if (takes_pieces(d, pieces, rb, re, fused)) {
         PieceArgs a = {};
         a.ptr = d->rowptr_dev + rb;
         a.col = d->col_dev;
@@ -377,6 +383,27 @@ CopyArgs copy_args(const void *from, void *to, int64_t bytes)
     return c;
 }
 
+// Where each row of feat is found: the place and slot of those that lie packed in the receive buffer, for the kernels that walk planned
+// pieces.  Widths and offsets are read when they are used, as the quantisation reads them: a step follows what was written to them.
+struct PackedRowArgs {
+    const int32_t *slot_of_row;
+    const uint8_t *bits;
+    const int64_t *row_offset;
+    int64_t n_rows, n_slots, packed_bytes;
+    int32_t dim;
+    adaqp_packed_row *row;
+};
+
+__device__ __forceinline__ adaqp_packed_row packed_row_at(const PackedRowArgs &p, int64_t r)
+{
+    const int32_t slot = p.slot_of_row[r];
+    if (slot < 0 || slot >= p.n_slots) return {0, 0};
+    const int32_t b = p.bits[slot];
+    const int64_t at = p.row_offset[slot], stride = 4 * (((int64_t)p.dim * b + 31) >> 5);
+    if (!(b == 2 || b == 4 || b == 8) || at < 0 || (at & 3) != 0 || at > p.packed_bytes - stride) return {0, 0};
+    return {(uint32_t)at | (b == 2 ? 1u : (b == 4 ? 2u : 3u)), (uint32_t)slot};
+}
+
 // Thread i copies unit i, or one byte of what the whole units leave over.
 __device__ __forceinline__ void copy_one(const CopyArgs &c, int64_t i)
 {
@@ -395,23 +422,36 @@ __device__ __forceinline__ void copy_one(const CopyArgs &c, int64_t i)
 // A launch has fewer than 2^32 threads: what 2^20 workgroups per buffer do not copy at one unit each they copy in turns.
 constexpr int64_t kCopyBlocks = (int64_t)1 << 20;
 
-__global__ __launch_bounds__(kBlock) void loop_back_kernel(const CopyArgs a, const CopyArgs b, uint32_t blocks_a)
+// The table of received rows is filled beside the copies, which do not fill the GPU (34 000 rows, 66 columns, the whole step: 35.1 us, 35.0 with
+// a table that the host made).
+__global__ __launch_bounds__(kBlock) void loop_back_kernel(const CopyArgs a, const CopyArgs b, uint32_t blocks_a, uint32_t blocks_b,
+                                                           const PackedRowArgs p)
 {
+    if (blockIdx.x >= blocks_a + blocks_b) {
+        const int64_t blocks = gridDim.x - blocks_a - blocks_b;
+        for (int64_t r = (int64_t)(blockIdx.x - blocks_a - blocks_b) * kBlock + threadIdx.x; r < p.n_rows; r += blocks * kBlock)
+            p.row[r] = packed_row_at(p, r);
+        return;
+    }
     const bool first = blockIdx.x < blocks_a;
     const CopyArgs &c = first ? a : b;
-    const int64_t block = first ? blockIdx.x : blockIdx.x - blocks_a, blocks = first ? blocks_a : gridDim.x - blocks_a;
+    const int64_t block = first ? blockIdx.x : blockIdx.x - blocks_a, blocks = first ? blocks_a : blocks_b;
     const int64_t n = c.units + (c.bytes - c.units * c.unit);
     for (int64_t i = block * kBlock + threadIdx.x; i < n; i += blocks * kBlock) copy_one(c, i);
 }
 
-int loop_back(const adaqp_layer_desc *d, hipStream_t st)
+int loop_back(const adaqp_layer_desc *d, bool fill_packed_rows, hipStream_t st)
 {
     if (d->n_send == 0) return ADAQP_OK;
+    const PackedRowArgs p = {d->slot_of_row_dev, d->bits_dev, d->row_offset_dev, fill_packed_rows ? d->n_feat_rows : 0, d->n_send,
+                             d->packed_bytes, d->dim, d->packed_row_dev};
     const CopyArgs a = copy_args(d->packed_dev, d->recv_packed_dev, d->packed_bytes);
     const CopyArgs b = copy_args(d->params_dev, d->recv_params_dev, d->n_send * 2 * (int64_t)sizeof(float));
     const int64_t blocks_a = std::min((a.units + a.bytes % a.unit + kBlock - 1) / kBlock, kCopyBlocks);
     const int64_t blocks_b = std::min((b.units + b.bytes % b.unit + kBlock - 1) / kBlock, kCopyBlocks);
-    hipLaunchKernelGGL(loop_back_kernel, dim3((unsigned)(blocks_a + blocks_b)), dim3(kBlock), 0, st, a, b, (uint32_t)blocks_a);
+    const int64_t blocks_p = std::min((p.n_rows + kBlock - 1) / kBlock, kCopyBlocks);
+    hipLaunchKernelGGL(loop_back_kernel, dim3((unsigned)(blocks_a + blocks_b + blocks_p)), dim3(kBlock), 0, st, a, b, (uint32_t)blocks_a,
+                       (uint32_t)blocks_b, p);
     ADAQP_HIP_TRY(hipGetLastError());
     return ADAQP_OK;
 }
@@ -525,6 +565,8 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
     const bool joint = one_launch(d);
     const bool paired = forward && both_tiled && two_streams(d) &&
                         (has_panels(d, true) || has_panels(d, false));
+    const bool fills = fused_receive(d) && takes_pieces(d, joint ? &d->pieces_both : &d->pieces_dependent,
+                                                        joint ? d->overlap_begin : d->dependent_begin, d->dependent_end, true);
     bool forked = false;
     auto fork_now = [&]() -> int {
         if (!two_streams(d)) return ADAQP_OK;
@@ -563,7 +605,7 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
             ADAQP_STEP(fork_now());
             ADAQP_STEP(paired ? aggregate_rows(d, true, agg) : aggregate(d, true, agg));
         }
-        ADAQP_STEP(loop_back(d, msg));
+        ADAQP_STEP(loop_back(d, fills, msg));
         ADAQP_STEP(receive(d, msg));
         if (!two_streams(d) && !joint) ADAQP_STEP(aggregate(d, true, msg));
         if (joint) {
@@ -595,7 +637,7 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
             ADAQP_STEP(fork_now());
             ADAQP_STEP(aggregate(d, true, agg));
         }
-        ADAQP_STEP(loop_back(d, msg));
+        ADAQP_STEP(loop_back(d, fills, msg));
         if (!two_streams(d) && !joint) ADAQP_STEP(aggregate(d, true, msg));
         // the received gradients are added to rows that the local aggregation also writes: join first
         ADAQP_STEP(join_now());

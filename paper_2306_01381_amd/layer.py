@@ -133,7 +133,7 @@ class LayerStep:
                              add_segments=self.backward)
         n = self.plan.n
         # forward, fused receive: the dependent aggregation reads received rows straight from the receive buffer
-        self.slot_of_row = self.packed_row = self._packed_row_of = None
+        self.slot_of_row = self.packed_row = None
         self._unplanned_dependent = None
         self.set_fused_receive(self.fused_receive)
         nbytes = max(self.plan.packed_bytes, 4)
@@ -338,14 +338,10 @@ class LayerStep:
         them from the receive buffer.  Off, in a step that was made with it on: plans the tiles of the dependent rows."""
         self.fused_receive = bool(on) and not self.backward and self.plan.halo_idx_host is not None
         if self.fused_receive and self.slot_of_row is None:
+            # scratch of each step; before the upload, which waits for whatever its memory was used for
+            self.packed_row = torch.empty((self.p.feat.shape[0], 2), dtype=torch.int32, device=self.device)
             self.slot_of_row = torch.from_numpy(
                 B.adaqp_plan_slot_of_row(self.p.feat.shape[0], self.plan.halo_idx_host)).to(self.device)
-            pl = self.plan
-            if pl.packed_bytes < B.SPMM_SEGMENTS_MOST_BYTES:
-                self.packed_row = torch.from_numpy(B.adaqp_plan_packed_rows(
-                    self.p.feat.shape[0], pl.halo_idx_host, pl.bits_host, pl.row_offset_host, self.dim, pl.packed_bytes).view(np.int32)
-                ).to(self.device)
-                self._packed_row_of = pl
         if not self.fused_receive and self._unplanned_dependent is not None:
             tiled, *how = self._unplanned_dependent
             self._unplanned_dependent = None
@@ -375,7 +371,7 @@ class LayerStep:
         d.recv_order_dev = pl.recv_order.data_ptr() if (self.use_recv_order and pl.recv_order is not None
                                                         and not self.backward) else None
         d.slot_of_row_dev = self.slot_of_row.data_ptr() if self.fused_receive else None
-        d.packed_row_dev = self.packed_row.data_ptr() if self.packed_row is not None and self._packed_row_of is pl else None
+        d.packed_row_dev = self.packed_row.data_ptr() if self.fused_receive and pl.packed_bytes < B.SPMM_SEGMENTS_MOST_BYTES else None
         d.tile_off_overlap_dev = None if self.tile_off_overlap is None else self.tile_off_overlap.data_ptr()
         d.tile_chunk_overlap, d.tile_chunk_dependent = self.tile_chunk_overlap, self.tile_chunk_dependent
         d.tile_off_dependent_dev = None if (self.tile_off_dependent is None or self.fused_receive) \

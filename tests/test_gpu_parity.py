@@ -1504,6 +1504,52 @@ def test_layer_step_fused_receive(oracle):
         assert np.array_equal(L.recv_packed.cpu().numpy(), plain.recv_packed.cpu().numpy())
 
 
+@pytest.mark.parametrize("how", ["run", "descriptor", "replay"])
+@pytest.mark.parametrize("schedule", [B.CHAIN, B.ISOLATED])
+def test_fused_receive_follows_what_is_written_to_the_plan(schedule, how):
+    """Widths, offsets and slots written in place after the step was made: the bits of the step that de-quantises first with the same
+    arrays, in a new step, with a descriptor kept from before and in replays."""
+    _say(f"fused receive, arrays written in place, schedule {schedule}, {how}")
+    p = make_partition(CONFIGS["c0"])
+    rng = np.random.default_rng(8)
+    steps = [LayerStep(p, DEV, seed=7, fused_receive=fused) for fused in (True, False)]
+    assert steps[0].pieces_dependent and steps[0].pieces_both
+    go = []
+    for L in steps:
+        if how == "replay":
+            L.run(schedule)
+            L.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=L.stream_msg):
+                L.run(schedule)
+            go.append((graph, graph.replay))
+        else:
+            kept = L.desc(schedule)
+            go.append((kept, (lambda d=kept: B.adaqp_layer_step(d)) if how == "descriptor" else (lambda L=L: L.run(schedule))))
+    halo, first = p.halo_idx[steps[0].plan.perm], None
+    for _ in range(3):
+        bits = rng.permutation(p.bits)
+        stride = np.array([0, 0, 2, 0, 4, 0, 0, 0, 8])[bits] * p.cfg.dim // 8
+        order = rng.permutation(halo)
+        for L in steps:
+            L.plan.bits.copy_(torch.from_numpy(bits))
+            L.plan.row_offset.copy_(torch.from_numpy(np.cumsum(stride) - stride))
+            L.plan.halo_idx.copy_(torch.from_numpy(order))
+            if L.fused_receive:
+                L.slot_of_row.copy_(torch.from_numpy(B.adaqp_plan_slot_of_row(p.feat.shape[0], order)))
+            L.out.fill_(float("nan"))
+            L.recv_packed.zero_()
+        torch.cuda.synchronize()
+        for _, step in go:
+            step()
+        torch.cuda.synchronize()
+        assert torch.equal(steps[0].out.view(torch.int32), steps[1].out.view(torch.int32))
+        first = steps[0].out.clone() if first is None else first
+        want = B.adaqp_plan_packed_rows(p.feat.shape[0], order, bits, np.cumsum(stride) - stride, p.cfg.dim, steps[0].plan.packed_bytes)
+        assert np.array_equal(steps[0].packed_row.cpu().numpy().view(np.uint32), want)
+    assert not torch.equal(first, steps[0].out)
+
+
 def test_layer_step_fused_receive_with_a_tiled_range(oracle):
     """The central rows tiled, the marginal ones read from the receive buffer: two streams, the same bits in every schedule,
     the halo rows of the feature matrix untouched."""
