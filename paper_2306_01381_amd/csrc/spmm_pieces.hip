@@ -32,6 +32,7 @@ constexpr int kJoinWaves = 8;                               // of a workgroup wh
 constexpr int kEnds = ADAQP_SPMM_PIECE_SEGMENTS;
 constexpr int kPart = 256;                                  // no sum runs longer than a part's 32 steps
 constexpr int32_t kJoined = -2, kNowhere = INT32_MIN;       // a piece's partial; a destination
+constexpr int32_t kMoved = INT32_MIN + 1;                   // in place of a destination: rowptr is no longer what the plan was made from
 constexpr int32_t kNoEnd = 0x10000;                         // lies after every step of a piece
 constexpr int kPackedLines = 4;                             // per slice where rows may be packed: their codes share lines
 constexpr unsigned kIdleLds = 6144;                         // of a workgroup, beside its 26 KB: no more than 16 waves on a CU
@@ -96,9 +97,88 @@ struct Joined {
     float first[4][kWave];      // its part of the first segment that ends in its piece, where other waves have parts of that
 };
 
+// A piece of rows whose rowptr was written to after it was planned, for all `live` lines of a slice.  The wave adds up what its piece is due of
+// each of its rows: the entries of the row as they are now, from where the piece begins if it was planned to begin inside the row, up
+// to where it ends if it was planned to end inside.  The pieces of a row so have each of its entries once, wherever it lies.  Returns
+// what walk_piece does.  No limit to how long a row can have become: one line at a time, no staging, few registers.  What bounds it is the
+// piece that has become the longest (lengths of the rows permuted, the whole step as planned, so, and cut on the device: 2 000 rows, 128
+// columns 15, 36, 23 us; 24 000 rows, 66 columns, packed 34, 560, 48; 376 000 rows, 256 columns 0.88, 5.4, 0.86 ms).
+template <bool PACKED, bool JOINS>
+__device__ __forceinline__ int32_t walk_moved(const PieceArgs &a, const int32_t first_line, const int live, const int32_t item, Joined *joined)
+{
+    constexpr int kAhead = 4;                               // steps on their way
+    const int lane = threadIdx.x & (kWave - 1), gl = lane & (kGroup - 1), grp = lane / kGroup;
+    const adaqp_spmm_piece from = a.pieces[item], to = a.pieces[item + 1];
+    const int32_t seg0 = min(max(from.segment, 0), a.n_seg);
+    const int32_t n_end = min(max(to.segment - seg0, 0), min(a.n_seg - seg0, kEnds));
+    const int32_t n_mine = min(n_end + (to.partial != -1 ? 1 : 0), a.n_seg - seg0);
+    int32_t join_dest = kNowhere;
+    for (int32_t q = 0; q < n_mine; ++q) {
+        int64_t first = max(a.ptr[seg0 + q], (int64_t)0), end = min(a.ptr[seg0 + q + 1], a.n_entries);
+        if (q == 0 && from.partial != -1) first = max(first, from.entry);
+        if (q == n_end) end = min(end, to.entry);
+        const int32_t dest = q < n_end ? a.dest[seg0 + q] : to.partial;
+        for (int v = 0; v < live; ++v) {
+            const int32_t at = (first_line + v) * kLine + gl * 4;
+            const uint32_t packed_col = (uint32_t)(a.p.col0 + at);
+            float4_t total = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int64_t part = first; part < end; part += kPart) {
+                const int64_t part_end = min(end, part + kPart);
+                float4_t sum = {0.0f, 0.0f, 0.0f, 0.0f};
+                for (int64_t e0 = part; e0 < part_end; e0 += kAhead * kStep) {
+                    float val[kAhead];
+                    float4_t x[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int64_t e = min(e0 + u * kStep + grp, part_end - 1);
+                        const int32_t c = a.col[e];
+                        const bool ok = e0 + u * kStep + grp < part_end && (uint32_t)c < (uint32_t)a.n_cols;
+                        const int64_t row = ok ? c : 0;
+                        val[u] = ok ? a.val[e] : 0.0f;
+                        x[u] = *reinterpret_cast<const float4_t *>(a.H + row * a.ldh + at);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) x[u][k] = ok ? x[u][k] : 0.0f;
+                        if constexpr (PACKED) {
+                            const adaqp_packed_row place = a.p.row[row];
+                            if (ok && place.place != 0 && place.slot < (uint64_t)a.p.n_slots) {
+                                const uint32_t w = place.place & 3u, last_word = (((uint32_t)a.p.full_dim << w) - 1) >> 5;
+                                const uint32_t word = *reinterpret_cast<const uint32_t *>(
+                                    a.p.packed + (place.place & ~3u) + 4 * (int64_t)min((packed_col << w) >> 5, last_word));
+                                const float2 zs = *reinterpret_cast<const float2 *>(a.p.params + 2 * (int64_t)place.slot);
+                                x[u] = unpack_codes(Entry<true>{place.place, val[u], zs.x, zs.y}, word, packed_col, x[u]);
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) sum[k] = fmaf(val[u], x[u][k], sum[k]);
+                }
+                total += sum;
+            }
+            float sum[1] = {0.0f};                          // lane l: column l of the line, of all groups
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                for (int other = kGroup; other < kWave; other *= 2) total[k] += __shfl_xor(total[k], other);
+                const float of_column = __shfl(total[k], (lane & (kLine - 1)) / 4);
+                if ((lane & 3) == k) sum[0] = of_column;
+            }
+            if (JOINS && q == 0 && q < n_end && from.partial == kJoined) {
+                join_dest = dest;
+                joined->first[v][lane] = sum[0];
+            } else if (JOINS && q == n_end && dest == kJoined) {
+                joined->open[v][lane] = sum[0];
+            } else if (q < n_end || dest >= 0) {
+                store_row<1>(a, dest, first_line + v, lane, sum);
+            }
+        }
+    }
+    return join_dest;
+}
+
 // ROWS: segments are rows, whose sums go to one row after the other but for those with parts.  JOINS: parts of a segment may be other
-// waves' of the workgroup.  Returns where the sum of such a segment goes that ends in this piece, or
-// kNowhere.
+// waves' of the workgroup.  Returns where the sum of such a segment goes that ends in this piece, kNowhere, or
+// kMoved before anything is written (ROWS).
 template <int VPL, int AHEAD, bool PACKED, bool ROWS, bool JOINS, int ENTRIES>
 __device__ __forceinline__ int32_t walk_piece(const PieceArgs &a, const int32_t first_line, const int32_t item, Entry<PACKED> *stage, Joined *joined)
 {
@@ -129,9 +209,19 @@ __device__ __forceinline__ int32_t walk_piece(const PieceArgs &a, const int32_t 
         st_val[k] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(vals, at, 0, kNonTemporal));
     }
     int32_t ends = kNoEnd, dests = -1;                      // lane l: where segment seg0 + l ends, and where its sum goes
+    const bool open = ROWS && to.partial != -1;             // a row goes on in the next piece: lane n_end
+    int64_t end = 0;
+    if (lane < n_end + open) end = a.ptr[(int64_t)min(seg0 + lane + 1, a.n_seg)] - ent0;
     if (lane < n_end) {
-        ends = (int32_t)clamp64(a.ptr[(int64_t)seg0 + lane + 1] - ent0, 0, n_ent) + pad * kStep;
+        ends = (int32_t)clamp64(end, 0, n_ent) + pad * kStep;
         dests = a.dest[seg0 + lane];
+    }
+    if constexpr (ROWS) {                                   // the caller's rowptr, which may have been written to: still the rows of the plan?
+        const int64_t begin = a.ptr[seg0] - ent0;
+        bool moved = lane < n_end ? end < 0 || end > n_ent : open && lane == n_end && end < n_ent;
+        moved |= lane == 0 && n_end + open > 0 && (from.partial == -1 ? begin != 0 : begin > 0);
+        moved |= lane > 0 && ends < __shfl_up(ends, 1);
+        if (__ballot(moved) != 0) return kMoved;
     }
 
     const uint64_t with_parts = __ballot(dests >= 0);
@@ -323,6 +413,7 @@ __global__ __launch_bounds__(WAVES * kWave, PACKED && ENTRIES > kFewEntries ? 2 
         if constexpr (VPL > 3) if (live == 3) dest = walk_piece<3, AHEAD, PACKED, ROWS, kJoins, ENTRIES>(a, line, item, stages[wave], mine);
         if constexpr (VPL > 2) if (live == 2) dest = walk_piece<2, 2 * AHEAD, PACKED, ROWS, kJoins, ENTRIES>(a, line, item, stages[wave], mine);
         if constexpr (VPL > 1) if (live == 1) dest = walk_piece<1, 8, PACKED, ROWS, kJoins, ENTRIES>(a, line, item, stages[wave], mine);
+        if constexpr (ROWS) if (dest == kMoved) dest = walk_moved<PACKED, kJoins>(a, line, live, item, mine);
     }
     if constexpr (kJoins) {
         __syncthreads();

@@ -234,7 +234,8 @@ class LayerStep:
         return B.adaqp_spmm_pieces_rule(p.rowptr, p.col, begin, end, p.feat.shape[0], self.dim, self.backward)
 
     def _rows_tensor(self):
-        """rowptr, whose rows the pieces were planned for, and how often it was written to."""
+        """rowptr, whose rows the pieces were planned for, and how often it was written to.  Writes that torch does not count, and those
+        that replays and descriptors meet that were taken before, are followed as well, by the kernel and slowly."""
         return self.rowptr, None if self.rowptr.is_inference() else self.rowptr._version
 
     def _pieces_bytes(self, pieces) -> int:

@@ -1550,6 +1550,42 @@ def test_fused_receive_follows_what_is_written_to_the_plan(schedule, how):
     assert not torch.equal(first, steps[0].out)
 
 
+@pytest.mark.parametrize("rows,mean,dim,shape", [(2_000, 10, 128, (8, 256)), (2_000, 10, 40, (8, 256)), (24_000, 18, 66, (4, 256)),
+                                                 (24_000, 60, 150, (4, 768)), (24_000, 100, 40, (4, 768))])
+@pytest.mark.parametrize("kind", ["forward", "fused", "backward"])
+def test_layer_step_follows_rowptr(oracle, kind, rows, mean, dim, shape):
+    """Rows that were planned in pieces and whose rowptr is written to afterwards, where nobody counts that: by a descriptor kept from before,
+    a replay, and a step after a write through .data.  Rows of other lengths, moved by some entries, all entries in one row, none."""
+    _say(f"layer step, rowptr written in place, {kind} rows={rows} dim={dim}")
+    p = make_partition(replace(CONFIGS["c0"], n_local=rows, n_halo=rows // 4, n_send=rows // 5, mean_degree=float(mean), dim=dim,
+                               feat="grad" if kind == "backward" else "normal", backward=kind == "backward"))
+    L = LayerStep(p, DEV, seed=3, tiled=False, fused_receive=kind == "fused", backward_receive=False)
+    assert (L.pieces_both.c.waves, L.pieces_both.c.entries) == shape
+    # any row may list received rows now: ranges that are aggregated before these are in place are not for a forward step
+    schedules = {"forward": (B.CHAIN, B.SERIAL), "fused": (B.CHAIN,), "backward": (B.CHAIN, B.ISOLATED, B.FREE)}[kind]
+    L.run(schedules[-1])
+    L.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=L.stream_msg):
+        L.run(schedules[-1])
+    steps = [lambda d=L.desc(s): B.adaqp_layer_step(d) for s in schedules] + [graph.replay, lambda: L.run(B.CHAIN)]
+    n, rng = p.n_rows, np.random.default_rng(6)
+    ptr = np.arange(n + 1)
+    for rowptr in (np.concatenate([[0], np.cumsum(rng.permutation(np.diff(p.rowptr)))]), np.clip(p.rowptr + 1, 0, p.nnz),
+                   np.clip(p.rowptr - 3, 0, p.nnz), np.where(ptr > n // 2, p.nnz, 0), np.where(ptr > n - 2, p.nnz - 5, 5),
+                   np.full(n + 1, p.nnz // 2), p.rowptr):
+        rowptr = np.ascontiguousarray(rowptr, dtype=np.int64)
+        L.rowptr.data.copy_(torch.from_numpy(rowptr))
+        _, _, _, out64, mag = _oracle_layer(oracle, replace(p, rowptr=rowptr), 3)
+        for step in steps:
+            L.out.fill_(float("nan"))
+            torch.cuda.synchronize()
+            step()
+            torch.cuda.synchronize()
+            got = L.out.cpu().numpy().astype(np.float64)
+            assert np.all(np.abs(got - out64) <= SPMM_RTOL * mag + 1e-30)
+
+
 def test_layer_step_fused_receive_with_a_tiled_range(oracle):
     """The central rows tiled, the marginal ones read from the receive buffer: two streams, the same bits in every schedule,
     the halo rows of the feature matrix untouched."""
