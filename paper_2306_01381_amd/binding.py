@@ -572,14 +572,14 @@ def adaqp_spmm_segments_gain(rowptr_host: np.ndarray, col_host: np.ndarray, row_
 
 
 def adaqp_spmm_pieces_rule(rowptr_host: np.ndarray, col_host: np.ndarray, row_begin: int, row_end: int, n_cols: int, dim: int,
-                           transposed: bool = False):
+                           transposed: bool = False, segments: bool = True):
     """Host-only.  (lines per slice of pieces over these rows, what segments save over that: the ranges of a step add up to more than 0
-    where they pay)."""
+    where they pay).  segments=False: only the lines, of rows that list their columns in any order; the gain is -infinity."""
     rowptr = np.ascontiguousarray(rowptr_host, dtype=np.int64)
     col = np.ascontiguousarray(col_host, dtype=np.int32)
-    lines, gain = ctypes.c_int32(0), ctypes.c_double(0.0)
+    lines, gain = ctypes.c_int32(0), ctypes.c_double(-np.inf)
     _check(lib().adaqp_spmm_pieces_rule(rowptr.ctypes.data, col.ctypes.data, row_begin, row_end, n_cols, dim, int(transposed),
-                                        ctypes.byref(lines), ctypes.byref(gain)), "adaqp_spmm_pieces_rule")
+                                        ctypes.byref(lines), ctypes.byref(gain) if segments else None), "adaqp_spmm_pieces_rule")
     return lines.value, gain.value
 
 

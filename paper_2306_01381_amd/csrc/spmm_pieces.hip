@@ -595,7 +595,7 @@ using namespace adaqp;
 extern "C" int adaqp_spmm_pieces_rule(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end, int64_t n_cols,
                                       int32_t dim, int32_t transposed, int32_t *lines_out, double *segments_gain_out)
 {
-    if (!rowptr_host || !lines_out || !segments_gain_out || row_begin < 0 || row_end < row_begin || n_cols < 0 || n_cols > INT32_MAX || dim <= 0)
+    if (!rowptr_host || !lines_out || row_begin < 0 || row_end < row_begin || n_cols < 0 || n_cols > INT32_MAX || dim <= 0)
         return ADAQP_EINVAL;
     constexpr int64_t kL2Lines = 32768;         // 4 MB
     constexpr int64_t kSample = 1 << 22;        // entries looked at for the popularity of the columns
@@ -604,7 +604,7 @@ extern "C" int adaqp_spmm_pieces_rule(const int64_t *rowptr_host, const int32_t 
     const double lines = (double)(((int64_t)dim + 31) / 32), entries = (double)(last - first), rows = (double)(row_end - row_begin);
     double cut = 0.0, n_cut = 0.0, dense = 0.0;
     int64_t n_dense = 0;
-    bool ascending = true;
+    bool ascending = segments_gain_out != nullptr;          // (nobody asks: not looked at)
     for (int64_t r = row_begin; r < row_end; ++r) {
         const int64_t degree = rowptr_host[r + 1] - rowptr_host[r];
         if (degree < 0) return ADAQP_EINVAL;
@@ -623,8 +623,8 @@ extern "C" int adaqp_spmm_pieces_rule(const int64_t *rowptr_host, const int32_t 
         }
     }
     *lines_out = 2;
-    *segments_gain_out = -INFINITY;
-    if (!ascending && adaqp_spmm_tiled_pays(row_end - row_begin, last - first)) return ADAQP_EINVAL;
+    if (segments_gain_out) *segments_gain_out = -INFINITY;
+    if (segments_gain_out && !ascending && adaqp_spmm_tiled_pays(row_end - row_begin, last - first)) return ADAQP_EINVAL;
     if (last == first) return ADAQP_OK;
     std::vector<int32_t> uses;
     try {

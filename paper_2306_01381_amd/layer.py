@@ -108,6 +108,19 @@ def line_padded(a: np.ndarray, device, pad: bool = True, spread: bool = False) -
     return view
 
 
+def _or_none(plan, *args, **options):
+    """What plan(*args) returns, or None where the library refuses the rows, there would be too many pieces, or there is no room to plan
+    them.  Pieces are never needed: the walk is cut on the device then, by kernels that take any rows."""
+    try:
+        return plan(*args, **options)
+    except MemoryError:
+        return None
+    except B.AdaqpError as e:
+        if e.status not in (B.EINVAL, B.ESIZE):
+            raise
+        return None
+
+
 class LayerStep:
     def __init__(self, p: Partition, device="cuda:0", seed: int = 0, pad: bool = True, use_recv_order: bool = False,
                  backward_receive: bool = True, trace: bool = True, fused_receive: bool = False,
@@ -155,6 +168,7 @@ class LayerStep:
         # aggregation tiled over the L2 caches: pays when rows are long (every row of feat re-used many times).
         # tiled=None lets the library decide: by what segments of both ranges save, or where they cannot be used per
         # row range (adaqp_spmm_tiled_pays: mean row length).
+        self._lines = {}                            # per slice of pieces, of ranges that the rule has been asked about
         self.tile_off_overlap = self.tile_off_dependent = None
         self.tile_chunk_overlap = self.tile_chunk_dependent = 0
         self._tiles_asked_for = tiled
@@ -215,23 +229,20 @@ class LayerStep:
             return
         # both ranges take the lines of the one with more entries: one launch aggregates them together where it can
         largest = max(plain, key=lambda r: int(p.rowptr[r[1]] - p.rowptr[r[0]]))
-        lines, _ = self._rule(*largest)
+        lines = self._lines.get(largest)
+        if lines is None:
+            lines, _ = _or_none(B.adaqp_spmm_pieces_rule, p.rowptr, p.col, *largest, n_cols, self.dim, self.backward, segments=False) or (0, 0)
         if lines == 0:
             return
 
         def pieces(begin, end):
-            plan = B.adaqp_plan_spmm_pieces(p.rowptr[begin: end + 1], None, self.dim, lines)
-            return B.DevicePieces(plan, self.device, begin)
+            return B.DevicePieces(_or_none(B.adaqp_plan_spmm_pieces, p.rowptr[begin: end + 1], None, self.dim, lines), self.device, begin)
         if (ob, oe) in plain:
             self.pieces_overlap = pieces(ob, oe)
         if (db, de) in plain:
             self.pieces_dependent = pieces(db, de)
         if len(plain) == 2 and oe == db:
             self.pieces_both = pieces(ob, de)
-
-    def _rule(self, begin, end):
-        p = self.p
-        return B.adaqp_spmm_pieces_rule(p.rowptr, p.col, begin, end, p.feat.shape[0], self.dim, self.backward)
 
     def _rows_tensor(self):
         """rowptr, whose rows the pieces were planned for, and how often it was written to.  Writes that torch does not count, and those
@@ -252,8 +263,10 @@ class LayerStep:
         p, n_cols = self.p, self.p.feat.shape[0]
         if not tiled and n_cols * self.feat.stride(0) * 4 < B.SPMM_SEGMENTS_MOST_BYTES:
             # (a range whose rows do not list ascending, distinct columns has a gain of -infinity and stays as it is)
-            gains = [B.adaqp_spmm_pieces_rule(p.rowptr, p.col, b, e, n_cols, self.dim, self.backward)[1] if e > b else -np.inf
+            rules = [B.adaqp_spmm_pieces_rule(p.rowptr, p.col, b, e, n_cols, self.dim, self.backward) if e > b else (0, -np.inf)
                      for b, e in ranges]
+            self._lines = {r: lines for r, (lines, _) in zip(ranges, rules)}
+            gains = [gain for _, gain in rules]
             pays = sum(g for g in gains if g > -np.inf) > 0
             return tuple(pays and g > -np.inf for g in gains)
         return tuple(e > b and (tiled or B.adaqp_spmm_tiled_pays(e - b, int(p.rowptr[e] - p.rowptr[b]))) for b, e in ranges)
@@ -278,8 +291,9 @@ class LayerStep:
         segments = B.DeviceSegments(None)
         if n_cols * self.feat.stride(0) * 4 < B.SPMM_SEGMENTS_MOST_BYTES:
             entries = B.adaqp_plan_spmm_segments(p.rowptr, begin, end, bounds, off)
-            if entries is not None:
-                entries["pieces"] = B.adaqp_plan_spmm_pieces(entries["ptr"], entries["of_row"], dim, B.adaqp_spmm_segments_lines(bounds))
+            planned = entries and _or_none(B.adaqp_plan_spmm_pieces, entries["ptr"], entries["of_row"], dim, B.adaqp_spmm_segments_lines(bounds))
+            if planned:
+                entries["pieces"] = planned
             segments = B.DeviceSegments(entries, self.device)
         if segments:
             B.adaqp_fill_spmm_segments(segments, self.col, self.val)

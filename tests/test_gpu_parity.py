@@ -1637,6 +1637,52 @@ def test_layer_step_with_a_range_of_unsorted_rows(oracle, fused):
         LayerStep(p, DEV, seed=9, tiled=True)
 
 
+@pytest.mark.parametrize("how", [dict(tiled=False), dict(fused_receive=True), dict(tiled=False, fused_receive=True)])
+@pytest.mark.parametrize("twice", [False, True])
+def test_layer_step_with_long_unsorted_rows(oracle, how, twice):
+    """Long rows that list their columns in no order, or one of them twice: refused where they would have to be tiled, and nowhere else."""
+    _say(f"layer step, long unsorted rows, {how} twice={twice}")
+    p = make_partition(replace(CONFIGS["c0"], mean_degree=4000.0))
+    b, e = p.dependent_rows if "tiled" not in how else (0, p.n_rows)
+    assert p.rowptr[e] - p.rowptr[b] >= 128 * (e - b)
+    col = p.col.copy()
+    for r in range(b, e):
+        row = col[p.rowptr[r]: p.rowptr[r + 1]]
+        row[:] = row[::-1]
+        if twice:
+            row[1] = row[0]
+    p = replace(p, col=col)
+    _, _, _, out64, mag = _oracle_layer(oracle, p, 9)
+    with pytest.raises(B.AdaqpError):
+        LayerStep(p, DEV, seed=9)
+    L = LayerStep(p, DEV, seed=9, **how)
+    assert L.pieces_dependent
+    L.run()
+    L.synchronize()
+    assert np.all(np.abs(L.out.cpu().numpy().astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
+
+
+@pytest.mark.parametrize("status", [B.ESIZE, B.EINVAL])
+@pytest.mark.parametrize("tiled", [False, True])
+def test_layer_step_without_a_plan_of_pieces(oracle, monkeypatch, status, tiled):
+    """A plan that the library refuses is done without: rows and segments are cut on the device."""
+    _say(f"layer step, no plan of pieces, status {status} tiled={tiled}")
+    p = make_partition(CONFIGS["c0"])
+
+    def refuse(*args):
+        raise B.AdaqpError(status, "plan")
+    monkeypatch.setattr(B, "adaqp_plan_spmm_pieces", refuse)
+    L = LayerStep(p, DEV, seed=9, tiled=tiled)
+    assert bool(L.segments_overlap) == tiled and not L.segments_overlap.c.pieces.n_pieces and not L.pieces_overlap and not L.pieces_both
+    _, _, _, out64, mag = _oracle_layer(oracle, p, 9)
+    for schedule in (B.CHAIN, B.ISOLATED):
+        L.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        L.run(schedule)
+        L.synchronize()
+        assert np.all(np.abs(L.out.cpu().numpy().astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
+
+
 def test_layer_step_made_with_fused_receive_plans_tiles_when_it_is_switched_off(oracle):
     """Nothing reads tiles of received rows that stay packed: they are planned when these rows are to be de-quantised first."""
     _say("layer step, tiles after fused receive")

@@ -507,6 +507,18 @@ def test_spmm_pieces_rule(n_rows, n_cols, mean, transposed):
     assert B.adaqp_spmm_pieces_rule(rowptr, col, 0, 2, n_cols, 20, transposed)[0] in (1, 2, 4)
 
 
+@pytest.mark.parametrize("column", [149, 10_000, -1])
+def test_spmm_pieces_rule_of_unsorted_rows(column):
+    """Pieces take columns in any order: lines are told for rows that segments are refused for."""
+    rowptr = np.array([0, 200, 400], np.int64)
+    col = np.tile(np.arange(200, dtype=np.int32), 2)
+    col[350] = column                                                  # twice, outside
+    with pytest.raises(B.AdaqpError):
+        B.adaqp_spmm_pieces_rule(rowptr, col, 0, 2, 10_000, 64)
+    assert B.adaqp_spmm_pieces_rule(rowptr, col, 0, 2, 10_000, 64, segments=False)[0] in (1, 2, 4)
+    assert B.adaqp_spmm_pieces_rule(rowptr[:2], col, 0, 1, 10_000, 64)[0] == B.adaqp_spmm_pieces_rule(rowptr[:2], col, 0, 1, 10_000, 64, segments=False)[0]
+
+
 @pytest.mark.parametrize("lengths", [[], [1], [0, 5, 0], [256], [257], [768], [769], [5_000], [1] * 200, [700, 30, 40, 100, 2_000, 3] * 9,
                                      [700, 30, 900_000, 100, 5_000, 3] * 3])
 @pytest.mark.parametrize("dim,lines", [(32, 1), (602, 2), (602, 4)])
