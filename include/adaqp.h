@@ -664,11 +664,11 @@ typedef struct adaqp_layer_desc {
     void *event_fork;           /* ISOLATED, FREE: two hipEvent_t created by the caller (timing may be disabled) */
     void *event_join;
     /* optional (n_pieces = 0: the walk is cut on the device): adaqp_plan_spmm_pieces of the rows of a range without tile table, and of both
-     * ranges where they touch (CHAIN), from the rowptr that rowptr_dev holds.  What is written to rowptr_dev afterwards is followed, but a step
- * of rows that are no longer those of the plan is a slow one (a walk cut on the device 2 to 12 times as fast).  Line-padded feat and out only.  The workspace of the range
-     * (the larger one) holds adaqp_spmm_pieces_workspace_bytes.  Where received rows are read packed (slot_of_row_dev) pieces take
-     * packed_row_dev [n_feat_rows], scratch that each step fills from slot_of_row_dev, bits_dev and row_offset_dev, and are not
-     * looked at without it. */
+     * ranges where they touch (CHAIN), from the rowptr that rowptr_dev holds.  What is written to rowptr_dev afterwards is followed, but
+     * a step of rows that are no longer those of the plan is a slow one (a walk cut on the device 1.5 to 12 times as fast).  Taken for
+     * line-padded feat and out only; others are aggregated as without a plan.  The workspace of the range (the larger one) holds
+     * adaqp_spmm_pieces_workspace_bytes.  Where received rows are read packed (slot_of_row_dev) pieces take packed_row_dev
+     * [n_feat_rows], scratch that each step fills from slot_of_row_dev, bits_dev and row_offset_dev, and are not looked at without it. */
     adaqp_packed_row *packed_row_dev;
     adaqp_spmm_pieces pieces_overlap;
     adaqp_spmm_pieces pieces_dependent;

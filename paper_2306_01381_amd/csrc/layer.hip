@@ -224,13 +224,8 @@ int check_desc(const adaqp_layer_desc *d)
         if (p->n_pieces == 0) continue;
         if (p->n_seg > INT32_MAX - 1024) return ADAQP_ESIZE;
         ADAQP_TRY(check_pieces(p, p->n_seg));
-        if (d->ld % 32 != 0 || d->ldo % 32 != 0 || !aligned_to(d->feat_dev, 128) || !aligned_to(d->out_dev, 128)) return ADAQP_EINVAL;
-        if (!d->col_dev || !d->val_dev || !aligned_to(d->rowptr_dev, 8) || !aligned_to(d->col_dev, 4) || !aligned_to(d->val_dev, 4)) return ADAQP_EINVAL;
-        const bool packed = p != &d->pieces_overlap && fused_receive(d);
-        if (packed && (!aligned_to(d->slot_of_row_dev, 4) || !aligned_to(d->recv_packed_dev, 4) || !aligned_to(d->recv_params_dev, 8) ||
-                       !aligned_to(d->row_offset_dev, 8) || !aligned_to(d->packed_row_dev, 8)))
-            return ADAQP_EINVAL;
-        if (!sliced_takes(p->n_seg, d->nnz, d->n_feat_rows, d->ld, packed, d->packed_bytes, d->dim)) return ADAQP_ESIZE;
+        if (d->overlap_end > d->overlap_begin && !aligned_to(d->workspace_overlap_dev, 256)) return ADAQP_EINVAL;
+        if (d->dependent_end > d->dependent_begin && !aligned_to(d->workspace_dependent_dev, 256)) return ADAQP_EINVAL;
     }
     if (two_streams(d)) {
         if (!d->event_fork || !d->event_join) return ADAQP_EINVAL;
@@ -259,21 +254,28 @@ bool planned_for(const adaqp_spmm_pieces *p, int64_t rb, int64_t re)
     return p->n_pieces > 0 && re > rb && p->n_seg == re - rb && p->row_begin == rb;
 }
 
+// Whether rows [rb, re) go as planned; fused: with received rows read from the receive buffer.  Matrices of another layout than the one
+// that the kernels of the plan are built for, or too large for it, go along the merge path as without a plan.
+bool takes_pieces(const adaqp_layer_desc *d, const adaqp_spmm_pieces *pieces, int64_t rb, int64_t re, bool fused)
+{
+    if (!planned_for(pieces, rb, re)) return false;
+    if (d->ld % 32 != 0 || d->ldo % 32 != 0 || !aligned_to(d->feat_dev, 128) || !aligned_to(d->out_dev, 128)) return false;
+    if (!d->col_dev || !d->val_dev || !aligned_to(d->rowptr_dev, 8) || !aligned_to(d->col_dev, 4) || !aligned_to(d->val_dev, 4)) return false;
+    if (fused && (!d->packed_row_dev || !aligned_to(d->slot_of_row_dev, 4) || !aligned_to(d->recv_packed_dev, 4) ||
+                  !aligned_to(d->recv_params_dev, 8) || !aligned_to(d->row_offset_dev, 8) || !aligned_to(d->packed_row_dev, 8)))
+        return false;
+    return sliced_takes(re - rb, d->nnz, d->n_feat_rows, d->ld, fused, d->packed_bytes, d->dim);
+}
+
 // Workspace of rows [rb, re) without tiles, whether planned or not.
-int range_bytes(const adaqp_layer_desc *d, const adaqp_spmm_pieces *pieces, int64_t rb, int64_t re, int64_t nz, int64_t *bytes)
+int range_bytes(const adaqp_layer_desc *d, const adaqp_spmm_pieces *pieces, int64_t rb, int64_t re, int64_t nz, bool fused, int64_t *bytes)
 {
     ADAQP_TRY(adaqp_spmm_workspace_bytes(re - rb, nz, d->dim, bytes));
-    if (!planned_for(pieces, rb, re)) return ADAQP_OK;
+    if (!takes_pieces(d, pieces, rb, re, fused)) return ADAQP_OK;
     int64_t planned = 0;
     ADAQP_TRY(adaqp_spmm_pieces_workspace_bytes(pieces->n_partials, d->dim, &planned));
     *bytes = std::max(*bytes, planned);
     return ADAQP_OK;
-}
-
-// Whether rows [rb, re) go as planned; fused: with received rows read from the receive buffer.
-bool takes_pieces(const adaqp_layer_desc *d, const adaqp_spmm_pieces *pieces, int64_t rb, int64_t re, bool fused)
-{
-    return planned_for(pieces, rb, re) && (!fused || d->packed_row_dev);
 }
 
 // Rows [rb, re) as planned, or along the merge path; fused: received rows are read from the receive buffer.
@@ -476,7 +478,7 @@ bool one_launch(const adaqp_layer_desc *d)
         return false;
     const int64_t rows = d->dependent_end - d->overlap_begin;
     int64_t need = 0;
-    if (rows > INT32_MAX - 1 || range_bytes(d, &d->pieces_both, d->overlap_begin, d->dependent_end, both_nnz(d), &need) != ADAQP_OK) return false;
+    if (rows > INT32_MAX - 1 || range_bytes(d, &d->pieces_both, d->overlap_begin, d->dependent_end, both_nnz(d), fused_receive(d), &need) != ADAQP_OK) return false;
     return larger_is_overlap(d) ? d->workspace_overlap_dev && d->workspace_overlap_bytes >= need
                                 : d->workspace_dependent_dev && d->workspace_dependent_bytes >= need;
 }
@@ -532,7 +534,7 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
         if (nz < 0 || nz > d->nnz) nz = d->nnz;
         int64_t need = 0;
         rc = range_bytes(d, part ? &d->pieces_overlap : &d->pieces_dependent, part ? d->overlap_begin : d->dependent_begin,
-                         part ? d->overlap_end : d->dependent_end, nz, &need);
+                         part ? d->overlap_end : d->dependent_end, nz, part == 0 && fused_receive(d), &need);
         if (rc != ADAQP_OK) return rc;
         if (part ? d->tile_off_overlap_dev != nullptr : d->tile_off_dependent_dev != nullptr) {
             need = tiled_part_bytes(d, part != 0);          // that range takes the tiled kernel, or its segments

@@ -1662,6 +1662,29 @@ def test_layer_step_with_long_unsorted_rows(oracle, how, twice):
     assert np.all(np.abs(L.out.cpu().numpy().astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
 
 
+@pytest.mark.parametrize("which", ["feat", "out", "both"])
+@pytest.mark.parametrize("ld,offset", [(128, 4), (129, 0), (160, 33)])
+@pytest.mark.parametrize("fused", [False, True])
+def test_layer_step_with_matrices_put_in_its_place(oracle, which, ld, offset, fused):
+    """A step whose rows were planned in pieces, with matrices of its caller's that do not start on lines or have no whole lines."""
+    _say(f"layer step, other matrices, {which} ld={ld} offset={offset} fused={fused}")
+    p = make_partition(CONFIGS["c0"])
+    _, _, _, out64, mag = _oracle_layer(oracle, p, 9)
+    L = LayerStep(p, DEV, seed=9, fused_receive=fused)
+    assert L.pieces_both and L.pieces_overlap
+    for name in ("feat", "out") if which == "both" else (which,):
+        n, dim = getattr(L, name).shape
+        mine = torch.full((offset + n * ld,), float("nan"), device=DEV)[offset:].view(n, ld)[:, :dim]
+        mine.copy_(getattr(L, name))
+        setattr(L, name, mine)
+    for schedule in (B.CHAIN, B.ISOLATED):
+        L.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        L.run(schedule)
+        L.synchronize()
+        assert np.all(np.abs(L.out.cpu().numpy().astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
+
+
 @pytest.mark.parametrize("status", [B.ESIZE, B.EINVAL])
 @pytest.mark.parametrize("tiled", [False, True])
 def test_layer_step_without_a_plan_of_pieces(oracle, monkeypatch, status, tiled):
