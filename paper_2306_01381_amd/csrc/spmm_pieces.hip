@@ -36,7 +36,6 @@ constexpr int32_t kMoved = INT32_MIN + 1;                   // in place of a des
 constexpr int32_t kNoEnd = 0x10000;                         // lies after every step of a piece
 constexpr int kPackedLines = 4;                             // per slice where rows may be packed: their codes share lines
 constexpr unsigned kIdleLds = 6144;                         // of a workgroup, beside its 26 KB: no more than 16 waves on a CU
-constexpr int64_t kMostPieces = 1 << 24, kMostTasks = 1 << 23;
 static_assert(kEnds < kWave - 1, "a lane per end, and one that has none");
 
 // A sum to its place.  Lanes without a column of their own store outside the row's buffer: no branch.
@@ -544,10 +543,9 @@ int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
     a.n_partials = (int32_t)p->n_partials;
     a.ldp = ((int64_t)a.dim + kLine - 1) / kLine * kLine;
     a.n_blocks = (a.n_pieces + p->waves - 1) / p->waves;
-    // a launch has fewer than 2^32 threads: as many slices as that allows
     const bool packed = a.p.row != nullptr;
     const int32_t per_slice = packed ? kPackedLines : p->lines_per_slice;
-    const int64_t most_lines = std::max<int64_t>(kMostTasks / a.n_blocks, 1) * per_slice, lines = a.ldp / kLine;
+    const int64_t most_lines = pieces_lines(a.n_blocks, p->waves, per_slice), lines = a.ldp / kLine;
     for (int64_t l0 = 0; l0 < lines; l0 += most_lines) {
         PieceArgs s = a;
         s.lines = (int32_t)std::min(lines - l0, most_lines);
@@ -563,7 +561,7 @@ int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
         hipLaunchKernelGGL(kernel, grid, dim3(p->waves * kWave), p->entries == kEntries && per_slice > 1 && !packed ? kIdleLds : 0, st, s);
         ADAQP_HIP_TRY(hipGetLastError());
     }
-    constexpr int64_t kMostSums = (int64_t)1 << 24;         // of a launch, for the same reason
+    constexpr int64_t kMostSums = (int64_t)1 << 24;         // of a launch, which has fewer than 2^32 threads
     for (int64_t s0 = 0; s0 < p->n_sums; s0 += kMostSums) {
         const int64_t n = std::min(p->n_sums - s0, kMostSums);
         const dim3 grid((unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock), (unsigned)std::min<int64_t>((a.ldp + kWave * 4 - 1) / (kWave * 4), 64));

@@ -123,4 +123,16 @@ struct SliceTasks {
     }
 };
 
+// Pieces of a plan, at most.
+constexpr int64_t kMostPieces = 1 << 24;
+
+// Lines that one launch of planned pieces takes at most, for n_blocks workgroups of so many waves per slice.  A launch has fewer than 2^32
+// threads, and the grid has room for up to three times as many tasks as there are (SliceTasks: those of a narrower slice weigh that
+// much less).
+constexpr int64_t pieces_lines(int64_t n_blocks, int32_t waves, int32_t lines_per_slice)
+{
+    const int64_t slices = kMostPieces / waves / n_blocks;
+    return (slices > 1 ? slices : 1) * lines_per_slice;
+}
+
 }  // namespace adaqp

@@ -129,3 +129,18 @@ def test_every_slice_task_is_taken_once(tmp_path):
                 }
             }
     """)
+
+
+def test_launches_of_planned_pieces_have_room(tmp_path):
+    """Fewer than 2^32 threads, however many pieces and lines there are; a whole number of slices, at least one."""
+    _run(tmp_path, """
+    for (int32_t waves : {4, 8}) for (int packed = 0; packed < 2; ++packed) for (int32_t vpl : {1, 2, 4}) {
+        const int64_t most = kMostPieces / waves;
+        for (int64_t n = 1; n <= most; n = n < most && n * 5 / 4 + 1 > most ? most : n * 5 / 4 + 1) {
+            const int64_t lines = pieces_lines(n, waves, vpl);
+            CHECK(lines >= vpl && lines % vpl == 0);
+            for (int64_t l = 1; l <= lines && l < INT32_MAX; l = l < 64 || l >= lines - 64 ? l + 1 : (2 * l < lines - 64 ? 2 * l : lines - 64))
+                CHECK(SliceTasks((int32_t)l, vpl, (int32_t)n, packed != 0).most_per_xcd() * kXcds * waves * 64 < ((int64_t)1 << 32));
+        }
+    }
+    """)
