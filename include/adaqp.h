@@ -59,7 +59,11 @@ typedef enum adaqp_status {
 
 const char *adaqp_strerror(int status);
 const char *adaqp_last_hip_error(void);     /* text of the last HIP error seen by this thread, "" if none */
-int adaqp_version(void);                    /* major * 10000 + minor * 100 + patch */
+
+/* major * 10000 + minor * 100 + patch.  The structs of this header are laid out as the version says: a program is built with the header of
+ * the library that it loads.  200: adaqp_spmm_segments has pieces, adaqp_layer_desc has them and packed_row_dev. */
+#define ADAQP_VERSION 200
+int adaqp_version(void);
 
 /* ---------------------------------------------------------------------------------------------------- */
 /* Buffer layout (host only).  Sec. 5 "Implementation": messages are grouped by assigned bit-width, each   */

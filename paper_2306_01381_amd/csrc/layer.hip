@@ -37,7 +37,7 @@ extern "C" const char *adaqp_strerror(int status)
 
 extern "C" const char *adaqp_last_hip_error(void) { return g_hip_error; }
 
-extern "C" int adaqp_version(void) { return 100; }
+extern "C" int adaqp_version(void) { return ADAQP_VERSION; }
 
 extern "C" int64_t adaqp_row_stride(int32_t dim, int32_t bits)
 {

@@ -762,6 +762,14 @@ def test_plan_spmm_blocks_bounds_its_table():
     assert small["n_rows_taken"] == 300 and small["n_steps"] <= 400
 
 
+def test_version_says_how_the_structs_are_laid_out():
+    """Whoever changes a layout gives it a version of its own."""
+    sizes = {200: (152, 88, 1200)}
+    assert (ctypes.sizeof(B.SpmmSegments), ctypes.sizeof(B.SpmmPieces), int(B.lib().adaqp_layer_desc_bytes())) == sizes[B.adaqp_version()]
+    with open(os.path.join(ROOT, "include", "adaqp.h")) as f:
+        assert f"#define ADAQP_VERSION {B.adaqp_version()}\n" in f.read()
+
+
 def test_layer_desc_mirror_matches_the_library():
     import ctypes
     assert int(B.lib().adaqp_layer_desc_bytes()) == ctypes.sizeof(B.LayerDesc)
