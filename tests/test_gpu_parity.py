@@ -1004,6 +1004,7 @@ def test_spmm_pieces(oracle, lines, dim, ld):
     struck = np.arange(n_rows) % 7 == 3
     off[struck] = -1
     plan = B.adaqp_plan_spmm_segments(rowptr, 0, n_rows, bounds, off)
+    cut = B.DeviceSegments(plan, DEV)
     plan["pieces"] = B.adaqp_plan_spmm_pieces(plan["ptr"], plan["of_row"], dim, lines)
     assert (plan["pieces"]["dest"] < 0).any() and (plan["pieces"]["pieces"]["partial"] != -1).any()
     segments = B.DeviceSegments(plan, DEV)
@@ -1021,6 +1022,13 @@ def test_spmm_pieces(oracle, lines, dim, ld):
     assert float((err / (SPMM_RTOL * mag[~struck] + 1e-30)).max()) <= 1.0
     zero_to = _padded_cols(dim, ld)
     assert np.all(got[~struck][:, dim:zero_to] == 0.0) and np.all(got[~struck][:, zero_to:] == 7.0) and np.all(got[struck] == 7.0)
+    B.adaqp_fill_spmm_segments(cut, cl, vl)
+    ws = torch.empty(max(B.adaqp_spmm_segments_workspace_bytes(cut, dim), 1), dtype=torch.uint8, device=DEV)
+    B.adaqp_spmm_csr_segments(cut, 0, Hd, dim, outs[1].fill_(7.0), ws)
+    torch.cuda.synchronize()
+    shares = outs[1].cpu().numpy()                                     # either is off by no more than the bound
+    assert np.all(np.abs(got[:, :dim].astype(np.float64) - shares[:, :dim])[~struck] <= 2 * SPMM_RTOL * mag[~struck] + 1e-30)
+    assert np.array_equal(got[:, dim:], shares[:, dim:]) and np.array_equal(got[struck], shares[struck])
 
 
 @pytest.mark.parametrize("lines", [1, 2, 4])
@@ -1548,6 +1556,54 @@ def test_fused_receive_follows_what_is_written_to_the_plan(schedule, how):
         want = B.adaqp_plan_packed_rows(p.feat.shape[0], order, bits, np.cumsum(stride) - stride, p.cfg.dim, steps[0].plan.packed_bytes)
         assert np.array_equal(steps[0].packed_row.cpu().numpy().view(np.uint32), want)
     assert not torch.equal(first, steps[0].out)
+
+
+@pytest.mark.parametrize("rows,mean,dim,shape", [(2_000, 10, 20, (8, 256)), (2_000, 10, 40, (8, 256)), (2_000, 10, 150, (8, 256)),
+                                                 (24_000, 12, 66, (4, 256)), (24_000, 8, 200, (4, 768)), (24_000, 30, 20, (4, 256)),
+                                                 (24_000, 90, 33, (4, 768)), (24_000, 40, 130, (4, 768)), (24_000, 40, 224, (4, 768))])
+@pytest.mark.parametrize("lines", [1, 2, 4])
+def test_layer_step_in_planned_pieces(oracle, monkeypatch, rows, mean, dim, shape, lines):
+    """Rows in pieces of every shape, with slices of one to four lines: against the oracle, and the same bits whether received rows are read
+    from the receive buffer or from feat.  A long row whose parts are added up, columns that there are not, and an infinity and a NaN in
+    rows of feat: they reach the rows that list them, and neither their neighbours in the same step nor anybody else."""
+    _say(f"layer step in pieces, rows={rows} mean={mean} dim={dim} lines={lines}")
+    monkeypatch.setattr(B, "adaqp_spmm_pieces_rule", lambda *args, **options: (lines, -np.inf))
+    p = make_partition(replace(CONFIGS["c0"], n_local=rows, n_halo=rows // 4, n_send=rows // 5, mean_degree=float(mean), dim=dim))
+    rng = np.random.default_rng(dim)
+    col, n_cols = p.col.copy(), p.feat.shape[0]
+    first = p.dependent_rows[0]
+    lengths = np.diff(p.rowptr)
+    lengths[-1] += lengths[first: first + rows // 40].sum()            # the last row takes the entries of others
+    lengths[first: first + rows // 40] = 0
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    out_of_range = rng.choice(col.size, col.size // 50, replace=False)
+    sent = np.isin(np.arange(n_cols), np.concatenate([p.send_idx, p.halo_idx]))
+    bad = rng.choice(np.flatnonzero(~sent & (np.bincount(col, minlength=n_cols) > 0)), 6, replace=False)
+    feat = p.feat.copy()
+    feat[bad] = 0.0
+    clean = replace(p, rowptr=rowptr, val=np.where(np.isin(np.arange(col.size), out_of_range), 0.0, p.val).astype(np.float32), feat=feat)
+    _, _, _, out64, mag = _oracle_layer(oracle, clean, 5)
+    col[out_of_range] = np.where(rng.random(out_of_range.size) < 0.5, -1, n_cols + 3)
+    feat = p.feat.copy()
+    feat[bad[:3]], feat[bad[3:]] = np.inf, np.nan
+    touched = np.zeros(rows, bool)
+    touched[np.repeat(np.arange(rows), np.diff(rowptr))[np.isin(col, bad)]] = True
+    assert touched.any() and not touched.all()
+    p, want = replace(p, rowptr=rowptr, col=col, feat=feat), None
+    for fused in (False, True):
+        L = LayerStep(p, DEV, seed=5, tiled=False, fused_receive=fused)
+        assert L.pieces_both.c.lines_per_slice == lines and (lines != 1 or (L.pieces_both.c.waves, L.pieces_both.c.entries) == shape)
+        for schedule in (B.CHAIN, B.ISOLATED):
+            L.out.fill_(7.0)
+            torch.cuda.synchronize()
+            L.run(schedule)
+            L.synchronize()
+            got = L.out.cpu().numpy()
+            assert np.all(np.abs(got[~touched].astype(np.float64) - out64[~touched]) <= SPMM_RTOL * mag[~touched] + 1e-30)
+            assert not np.isfinite(got[touched]).any()
+            want = want or {}
+            kept = want.setdefault(schedule, got)
+            assert np.array_equal(np.isnan(got), np.isnan(kept)) and np.array_equal(got[~touched].view(np.uint32), kept[~touched].view(np.uint32))
 
 
 @pytest.mark.parametrize("rows,mean,dim,shape", [(2_000, 10, 128, (8, 256)), (2_000, 10, 40, (8, 256)), (24_000, 18, 66, (4, 256)),
