@@ -562,7 +562,7 @@ SPMM_SEGMENTS_MIN_GAIN = 2e6
 
 def adaqp_spmm_segments_gain(rowptr_host: np.ndarray, col_host: np.ndarray, row_begin: int, row_end: int, n_cols: int, dim: int,
                              transposed: bool = False) -> float:
-    """Host-only.  What segments save for these rows; the ranges of a step add up to SPMM_SEGMENTS_MIN_GAIN where they pay."""
+    """Host-only.  What segments without pieces save for these rows; the ranges of a step add up to SPMM_SEGMENTS_MIN_GAIN where they pay."""
     rowptr = np.ascontiguousarray(rowptr_host, dtype=np.int64)
     col = np.ascontiguousarray(col_host, dtype=np.int32)
     out = ctypes.c_double(0.0)

@@ -820,12 +820,7 @@ extern "C" int adaqp_spmm_segments_gain(const int64_t *rowptr_host, const int32_
     }
     if (!adaqp_spmm_blocks_pay(n_dense, n_cols, 32)) dense = 0.0;
     const double entries = (double)(last - first), rows = (double)(row_end - row_begin);
-    // forward slices are one line, backward ones four: the misses that are left, and their weight, differ
-    const double cost = transposed ? (0.26 * lines + 0.41) * entries : (0.5 * lines + 0.25) * entries + 2.7 * lines * rows;
-    // (the matrix cores' rows cost their coefficients once, however few lines there are: 50 000 rows, 97 entries per row, 64 columns 121 ->
-    // 151 us with segments and blocks; 60 000 rows, 110, 256 columns 525 -> 402)
-    const double saved = transposed ? 0.0 : 0.56 * std::max(lines - 1.5, 0.0) * dense;
-    *gain_out = saved - cost;
+    *gain_out = (transposed ? 0.0 : blocks_gain(lines, dense)) - segments_cost(transposed != 0, lines, entries, rows);
     if (!asked_for && cut * lines + *gain_out <= 0.0) return ADAQP_OK;         // whatever the columns are
     std::vector<int32_t> uses;
     try {

@@ -586,8 +586,8 @@ using namespace adaqp;
 // rows: 1 line 0.89 ms, 4 lines 1.12; Zipf rows, whose columns are few popular ones, 128 columns: 0.27, 0.23.
 //
 // Segments save what their rows miss; they cost a partial row per group of tiles, written and read, a second copy of the short walk,
-// and two more launches.  Where all columns fit, they still are the better ones for long rows: what adaqp_spmm_segments_gain says of them
-// counts as well.  400 of these steps, timed without blocks as well: 1.175 against shares without segments, pieces over the rows alone
+// and two more launches.  Where all columns fit, they still are the better ones for long rows: what adaqp_spmm_segments_gain weighs
+// counts as well (with the columns that an L2 holds eight lines of as the popular ones).  400 of these steps, timed without blocks as well: 1.175 against shares without segments, pieces over the rows alone
 // 1.134, by that gain alone 1.158; 3 with segments lose more than 4 % by them, 6 without would gain that.  179 000 rows, 2 M entries,
 // 300 columns: 378 -> 356 us.
 extern "C" int adaqp_spmm_pieces_rule(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end, int64_t n_cols,
@@ -657,12 +657,10 @@ extern "C" int adaqp_spmm_pieces_rule(const int64_t *rowptr_host, const int32_t 
     if (transposed && entries >= 1e5 && entries < 6.0 * rows && lines >= 7.0) *lines_out = 0;
     if (!ascending) return ADAQP_OK;
     const double groups = (double)std::min<int64_t>(std::max<int64_t>(n_cols / 12288, 1), ADAQP_SPMM_SEGMENTS);
-    // (the rows of the matrix cores cost their coefficients once, however few lines there are)
     if (transposed || !adaqp_spmm_blocks_pay(n_dense, n_cols, 32)) dense = 0.0;
     const double by_misses = cut * lines * missed - 7.0 * n_cut * lines * groups - 0.15 * entries - 1e6;
-    const double by_popularity = cut * lines * unpopular - (transposed ? (0.26 * lines + 0.41) * entries : (0.5 * lines + 0.25) * entries + 2.7 * lines * rows) -
-                                 ADAQP_SPMM_SEGMENTS_MIN_GAIN / 2;
-    *segments_gain_out = std::max(by_misses, 0.56 * std::max(lines - 1.5, 0.0) * dense + by_popularity);
+    const double by_popularity = cut * lines * unpopular - segments_cost(transposed != 0, lines, entries, rows) - ADAQP_SPMM_SEGMENTS_MIN_GAIN / 2;
+    *segments_gain_out = std::max(by_misses, blocks_gain(lines, dense) + by_popularity);
     return ADAQP_OK;
 }
 

@@ -123,6 +123,18 @@ struct SliceTasks {
     }
 };
 
+// What segments cost beside a walk over the rows, in entries times lines: the walk over all entries and a partial row and its sum per
+// row.  Forward slices are one line, backward ones four: the weights differ.  (Fitted to steps timed with and without segments,
+// adaqp_spmm_segments_gain.)
+constexpr double segments_cost(bool transposed, double lines, double entries, double rows)
+{
+    return transposed ? (0.26 * lines + 0.41) * entries : (0.5 * lines + 0.25) * entries + 2.7 * lines * rows;
+}
+
+// What the matrix cores save of that for the entries of their rows, in forward steps.  They cost their coefficients once, however few lines
+// there are: 50 000 rows, 97 entries per row, 64 columns 121 -> 151 us with segments and blocks; 60 000 rows, 110, 256 columns 525 -> 402.
+constexpr double blocks_gain(double lines, double dense_entries) { return 0.56 * (lines > 1.5 ? lines - 1.5 : 0.0) * dense_entries; }
+
 // Pieces of a plan, at most.
 constexpr int64_t kMostPieces = 1 << 24;
 
