@@ -4,11 +4,12 @@
 //
 // What bounds the gathers of segments is what their group of tiles misses in the L2, and that hangs on how far apart the entries are
 // that an XCD has under way.  Shares cut on the device are a search each (eight loads that wait for one another, 20 us under load)
-// and so have to be long: 128 workgroups with 4 600 entries each span two groups, 13 % of the lines come from behind the L2, and the
-// L1, which answers in order, stands still for each of them (31 % of its time).  A planned piece begins with one load of its bounds and
-// is 700 entries long; workgroups start in order, so that those under way are neighbours: 5.7 % from behind the L2, 24 %.
+// and so have to be long: 128 workgroups with 4 600 entries each span two groups, 6 and 13 % of the lines of the two ranges of the step
+// below come from behind the L2, and the L1, which answers in order, stands still for each of them (25 and 30 % of its time).  A planned
+// piece begins with one load of its bounds and is 700 entries long; workgroups start in order, so that those under way are
+// neighbours: 6 and 8 % from behind the L2, 17 and 23 %.
 // Waves that take piece after piece drift apart and lose that (28 % from behind the L2, 1.29 -> 1.55 ms for the step below).
-// A piece is one LDS fill, so nothing of the next has to wait in registers: 75 of them, and no spilled scalars.
+// A piece is one LDS fill, so nothing of the next has to wait in registers: 76 of them for segments, and no spilled scalars.
 //
 // 58 000 rows, 27.8 M entries, 98 000 columns, 256 columns of H, the whole layer step: shares 1.40 ms, here with as many waves as
 // registers allow 1.29, with 16 per CU 1.19 (25 TB/s of gathers; bare loads out of the L2 31; 24 waves of two lines ask for more
