@@ -479,7 +479,8 @@ def test_plan_packed_rows():
         B.adaqp_plan_packed_rows(12, halo, bits, offset, 100, 0xFFFF0000)
 
 
-@pytest.mark.parametrize("n_rows,n_cols,mean,transposed", [(300, 50, 30, False), (3_000, 9_000, 90, True), (4_000, 90_000, 200, False)])
+@pytest.mark.parametrize("n_rows,n_cols,mean,transposed", [(300, 50, 30, False), (3_000, 9_000, 90, True), (4_000, 90_000, 200, False),
+                                                           (30_000, 20, 12, False)])
 def test_spmm_pieces_rule(n_rows, n_cols, mean, transposed):
     """The stated weights: lines that cost least, and what segments save over them."""
     rng = np.random.default_rng(mean)
