@@ -673,7 +673,8 @@ typedef struct adaqp_layer_desc {
      * a step of rows that are no longer those of the plan is a slow one (a walk cut on the device 1.5 to 12 times as fast).  Taken for
      * line-padded feat and out only; others are aggregated as without a plan.  The workspace of the range (the larger one) holds
      * adaqp_spmm_pieces_workspace_bytes.  Where received rows are read packed (slot_of_row_dev) pieces take packed_row_dev
-     * [n_feat_rows], scratch that each step fills from slot_of_row_dev, bits_dev and row_offset_dev, and are not looked at without it. */
+     * [n_feat_rows], scratch that each step fills from slot_of_row_dev [n_feat_rows], bits_dev and row_offset_dev, and are not looked
+     * at without it. */
     adaqp_packed_row *packed_row_dev;
     adaqp_spmm_pieces pieces_overlap;
     adaqp_spmm_pieces pieces_dependent;

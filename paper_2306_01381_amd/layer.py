@@ -386,7 +386,9 @@ class LayerStep:
         d.recv_order_dev = pl.recv_order.data_ptr() if (self.use_recv_order and pl.recv_order is not None
                                                         and not self.backward) else None
         d.slot_of_row_dev = self.slot_of_row.data_ptr() if self.fused_receive else None
-        d.packed_row_dev = self.packed_row.data_ptr() if self.fused_receive and pl.packed_bytes < B.SPMM_SEGMENTS_MOST_BYTES else None
+        # (filled for every row of feat: not where a caller has put a taller matrix in its place)
+        tables = min(self.packed_row.shape[0], self.slot_of_row.shape[0]) if self.fused_receive else 0
+        d.packed_row_dev = self.packed_row.data_ptr() if tables >= self.feat.shape[0] > 0 else None
         d.tile_off_overlap_dev = None if self.tile_off_overlap is None else self.tile_off_overlap.data_ptr()
         d.tile_chunk_overlap, d.tile_chunk_dependent = self.tile_chunk_overlap, self.tile_chunk_dependent
         d.tile_off_dependent_dev = None if (self.tile_off_dependent is None or self.fused_receive) \

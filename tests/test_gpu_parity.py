@@ -1741,6 +1741,23 @@ def test_layer_step_with_matrices_put_in_its_place(oracle, which, ld, offset, fu
         assert np.all(np.abs(L.out.cpu().numpy().astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
 
 
+@pytest.mark.parametrize("fused", [False, True])
+def test_layer_step_with_a_taller_matrix_in_its_place(oracle, fused):
+    """More rows of feat than the step was made with, none of them listed: tables of the rows there were are not written past their ends."""
+    _say(f"layer step, taller feat, fused={fused}")
+    p = make_partition(CONFIGS["c0"])
+    _, _, _, out64, mag = _oracle_layer(oracle, p, 9)
+    L = LayerStep(p, DEV, seed=9, fused_receive=fused)
+    n, taller = L.feat.shape[0], torch.full((L.feat.shape[0] + 5_000, L.feat.stride(0)), float("nan"), device=DEV)
+    taller[:n, :L.dim] = L.feat
+    L.feat = taller[:, :L.dim]
+    d = L.desc(B.CHAIN)
+    assert d.n_feat_rows == n + 5_000 and not d.packed_row_dev
+    L.run()
+    L.synchronize()
+    assert np.all(np.abs(L.out.cpu().numpy().astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
+
+
 @pytest.mark.parametrize("status", [B.ESIZE, B.EINVAL])
 @pytest.mark.parametrize("tiled", [False, True])
 def test_layer_step_without_a_plan_of_pieces(oracle, monkeypatch, status, tiled):
