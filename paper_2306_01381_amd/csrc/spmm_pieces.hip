@@ -588,16 +588,19 @@ void sums_of_largest(const std::vector<int32_t> &values, const int64_t (&held)[N
 {
     std::vector<int64_t> n_of((size_t)kFew, 0);
     std::vector<int32_t> many;
+    int32_t most = 0;                           // of the few
     for (const int32_t v : values) {
-        if (v < kFew) ++n_of[(size_t)v];
-        else many.push_back(v);
+        if (v < kFew) {
+            ++n_of[(size_t)v];
+            most = std::max(most, v);
+        } else many.push_back(v);
     }
     std::sort(many.begin(), many.end(), std::greater<int32_t>());
     for (int q = 0; q < N; ++q) {
         const int64_t of_many = std::min<int64_t>(held[q], (int64_t)many.size());
         sums[q] = std::accumulate(many.begin(), many.begin() + of_many, (int64_t)0);
         int64_t left = held[q] - of_many;
-        for (int32_t v = kFew - 1; v > 0 && left > 0; --v) {
+        for (int32_t v = most; v > 0 && left > 0; --v) {
             const int64_t n = std::min(left, n_of[(size_t)v]);
             sums[q] += n * v;
             left -= n;
