@@ -388,11 +388,11 @@ int adaqp_plan_spmm_pieces(const int64_t *ptr_host, int64_t n_seg, const int32_t
                            int32_t *sum_row_out, int32_t *sum_ptr_out);
 
 /* Host only.  For rows [row_begin, row_end) on whole lines: *lines_out = lines per slice in which pieces over the rows take least time (0: they
- * take more than no pieces), and *segments_gain_out = what segments of the rows save over that, in entries times 128-byte lines of H, negative where they cost more; a
- * step that aggregates several ranges adds them up and takes segments in all of them where the sum is positive.  transposed: the
- * range belongs to a backward step.  Rows that do not list ascending, distinct, in-range columns have no segments: -infinity, or EINVAL
- * where adaqp_spmm_tiled_pays asks for them.  Pieces take columns in any order: with segments_gain_out NULL such rows are not
- * refused.  -infinity and 2 lines where there is no memory for a count per column. */
+ * take more than no pieces), and *segments_gain_out = what segments of the rows save over that, in entries times 128-byte lines of H,
+ * negative where they cost more; a step that aggregates several ranges adds them up and takes segments in all of them where the sum is
+ * positive.  transposed: the range belongs to a backward step.  Rows that do not list ascending, distinct, in-range columns have no
+ * segments: -infinity, or EINVAL where adaqp_spmm_tiled_pays asks for them.  Pieces take columns in any order: with segments_gain_out
+ * NULL such rows are not refused.  -infinity and 2 lines where there is no memory for a count per column. */
 int adaqp_spmm_pieces_rule(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end, int64_t n_cols,
                            int32_t dim, int32_t transposed, int32_t *lines_out, double *segments_gain_out);
 

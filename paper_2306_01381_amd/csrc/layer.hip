@@ -478,7 +478,8 @@ bool one_launch(const adaqp_layer_desc *d)
         return false;
     const int64_t rows = d->dependent_end - d->overlap_begin;
     int64_t need = 0;
-    if (rows > INT32_MAX - 1 || range_bytes(d, &d->pieces_both, d->overlap_begin, d->dependent_end, both_nnz(d), fused_receive(d), &need) != ADAQP_OK) return false;
+    if (rows > INT32_MAX - 1) return false;
+    if (range_bytes(d, &d->pieces_both, d->overlap_begin, d->dependent_end, both_nnz(d), fused_receive(d), &need) != ADAQP_OK) return false;
     return larger_is_overlap(d) ? d->workspace_overlap_dev && d->workspace_overlap_bytes >= need
                                 : d->workspace_dependent_dev && d->workspace_dependent_bytes >= need;
 }

@@ -621,9 +621,9 @@ void sums_of_largest(const std::vector<int32_t> &values, const int64_t (&held)[N
 //
 // Segments save what their rows miss; they cost a partial row per group of tiles, written and read, a second copy of the short walk,
 // and two more launches.  Where all columns fit, they still are the better ones for long rows: what adaqp_spmm_segments_gain weighs
-// counts as well (with the columns that an L2 holds eight lines of as the popular ones).  400 of these steps, timed without blocks as well: 1.175 against shares without segments, pieces over the rows alone
-// 1.134, by that gain alone 1.158; 3 with segments lose more than 4 % by them, 6 without would gain that.  179 000 rows, 2 M entries,
-// 300 columns: 378 -> 356 us.
+// counts as well (with the columns that an L2 holds eight lines of as the popular ones).  400 of these steps, timed without blocks as
+// well: 1.175 against shares without segments, pieces over the rows alone 1.134, by that gain alone 1.158; 3 with segments lose more
+// than 4 % by them, 6 without would gain that.  179 000 rows, 2 M entries, 300 columns: 378 -> 356 us.
 extern "C" int adaqp_spmm_pieces_rule(const int64_t *rowptr_host, const int32_t *col_host, int64_t row_begin, int64_t row_end, int64_t n_cols,
                                       int32_t dim, int32_t transposed, int32_t *lines_out, double *segments_gain_out)
 {
