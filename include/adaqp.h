@@ -660,6 +660,7 @@ typedef struct adaqp_layer_desc {
     uint8_t *packed_dev;   float *params_dev;           /* send buffers */
     const float *alpha_sq_dev; float *beta_dev;         /* optional trace (adaqp_quantize_pack_trace); both or none */
     uint8_t *recv_packed_dev; float *recv_params_dev;   /* receive buffers; the loop-back copy stands in for the exchange */
+                        /* (ADAQP_CHAIN: copied by the launch that receives, which reads what it copies) */
     int64_t packed_bytes;
     /* scratch and streams */
     void *workspace_overlap_dev;   int64_t workspace_overlap_bytes;

@@ -18,6 +18,7 @@
 // fp32 arithmetic is written operation by operation and the file is compiled with -ffp-contract=off: the
 // integer codes depend on every rounding.
 #include "common.hpp"
+#include "loop_back.hpp"
 #include "adaqp_probe.h"
 
 namespace adaqp {
@@ -58,6 +59,8 @@ constexpr uint32_t kCounterTag = 0x41645150u;
 
 
 struct QuantArgs {
+    uint32_t own_blocks;        // workgroups that quantise; the others of the launch fill the table of received rows.  (Here, with what every
+    int32_t lpr_log2;           // wave reads first: behind the other workgroups' arguments it is another load, 0.8 % of the kernel)
     const float *feat;
     int64_t n_feat_rows, ld;
     int32_t dim, n_granules;
@@ -71,7 +74,6 @@ struct QuantArgs {
     float *params;
     const float *alpha_sq;      // optional trace input / output (both or none)
     float *beta;
-    int32_t lpr_log2;
 };
 
 template <int VW> struct VecOf;
@@ -261,8 +263,9 @@ __device__ __forceinline__ void pin(Rand128 &r)
 // addresses), but no generator, no min / max reduction, no codes: what is stored is derived from the loaded values
 // with two operations per granule.  Its time is the floor of this access pattern.
 template <int GPL, int VW, bool PROBE>
-__global__ __launch_bounds__(kBlock) void quantize_pack_kernel(const QuantArgs a)
+__global__ __launch_bounds__(kBlock) void quantize_pack_kernel(const QuantArgs a, const PackedRowArgs table)
 {
+    if (blockIdx.x >= a.own_blocks) return fill_packed_rows(table, blockIdx.x - a.own_blocks);
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
     const int lpr = 1 << a.lpr_log2;
@@ -380,8 +383,9 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(const QuantArgs a
 // Rows too wide for registers (dim > 8 * 64 * kMaxGpl): one wave per row, two passes over the row (the
 // second one is served by the caches).
 // ---------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void quantize_pack_wide_kernel(const QuantArgs a)
+__global__ __launch_bounds__(kBlock) void quantize_pack_wide_kernel(const QuantArgs a, const PackedRowArgs table)
 {
+    if (blockIdx.x >= a.own_blocks) return fill_packed_rows(table, blockIdx.x - a.own_blocks);
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t s = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);     // wave-uniform
     if (s >= a.n_send) return;
@@ -446,6 +450,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_wide_kernel(const QuantA
 // before the first one is decoded, so a wave pays two memory latencies for R rows.
 // ---------------------------------------------------------------------------------------------------------
 struct DequantArgs {
+    uint32_t own_blocks;        // workgroups that de-quantise; the others of the launch copy
     const uint8_t *packed;
     int64_t packed_bytes;
     const float *params;
@@ -470,8 +475,9 @@ __device__ __forceinline__ int64_t readlane_i64(int64_t v, int lane_id)
 // cache (R <= 2); otherwise lanes 0..R-1 fetch them with one vector load each and broadcast them (R = 4).
 // STREAM: rows are written in whole lines (line-padded layout): non-temporal stores.
 template <int VW, int NV, int R, bool SCALAR, bool STREAM>
-__global__ __launch_bounds__(kBlock) void unpack_dequant_kernel(const DequantArgs a)
+__global__ __launch_bounds__(kBlock) void unpack_dequant_kernel(const DequantArgs a, const LoopBack copies)
 {
+    if (blockIdx.x >= a.own_blocks) return copy_blocks(copies, blockIdx.x - a.own_blocks, kBlock);
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t t0 = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * R;                    // wave-uniform
@@ -585,8 +591,9 @@ __global__ __launch_bounds__(kBlock) void unpack_dequant_kernel(const DequantArg
 
 // Any row length: one wave per slot, looping over the row.
 template <int VW>
-__global__ __launch_bounds__(kBlock) void unpack_dequant_long_kernel(const DequantArgs a)
+__global__ __launch_bounds__(kBlock) void unpack_dequant_long_kernel(const DequantArgs a, const LoopBack copies)
 {
+    if (blockIdx.x >= a.own_blocks) return copy_blocks(copies, blockIdx.x - a.own_blocks, kBlock);
     const int lane = threadIdx.x & (kWave - 1);
     int64_t t = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);           // wave-uniform
     if (t >= a.n_recv) return;
@@ -629,6 +636,7 @@ __global__ __launch_bounds__(kBlock) void unpack_dequant_long_kernel(const Dequa
 // part of the result) and stores the row once.  Rows wider than 64*VW*4 columns are walked in column chunks.
 // ---------------------------------------------------------------------------------------------------------
 struct DequantAddArgs {
+    uint32_t own_blocks;        // workgroups that add; the others of the launch copy
     const uint8_t *packed;
     int64_t packed_bytes;
     const float *params;
@@ -745,8 +753,9 @@ __device__ void add_one_segment(const DequantAddArgs &a, int64_t g, int lane)
 }
 
 template <int VW, int NV, bool STREAM>
-__global__ __launch_bounds__(kBlock) void unpack_dequant_add_kernel(const DequantAddArgs a)
+__global__ __launch_bounds__(kBlock) void unpack_dequant_add_kernel(const DequantAddArgs a, const LoopBack copies)
 {
+    if (blockIdx.x >= a.own_blocks) return copy_blocks(copies, blockIdx.x - a.own_blocks, kBlock);
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t g = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);             // wave-uniform
     if (g >= a.n_seg) return;
@@ -760,8 +769,9 @@ __global__ __launch_bounds__(kBlock) void unpack_dequant_add_kernel(const Dequan
 // PROBE: the no-compute twin - the same loads and stores at the same addresses, but a message's words are xor-ed
 // into its row instead of being decoded and added (the rows end up holding meaningless bits).
 template <int VW, int NV, int S, bool STREAM, bool PROBE>
-__global__ __launch_bounds__(kBlock) void unpack_dequant_add4_kernel(const DequantAddArgs a)
+__global__ __launch_bounds__(kBlock) void unpack_dequant_add4_kernel(const DequantAddArgs a, const LoopBack copies)
 {
+    if (blockIdx.x >= a.own_blocks) return copy_blocks(copies, blockIdx.x - a.own_blocks, kBlock);
     constexpr int G = 4;
     static_assert(NV * S <= 8, "register budget: S rows of NV vectors");
     const int lane = threadIdx.x & (kWave - 1);
@@ -916,10 +926,10 @@ int vector_width(const void *base, int64_t ld, int32_t dim, bool whole_vectors)
 bool line_padded(const void *base, int64_t ld) { return ld % 32 == 0 && aligned_to(base, 128); }
 
 template <int VW, bool PROBE = false>
-hipError_t launch_quantize(const QuantArgs &a, int gpl, dim3 grid, hipStream_t st)
+hipError_t launch_quantize(const QuantArgs &a, const PackedRowArgs &table, int gpl, dim3 grid, hipStream_t st)
 {
     switch (gpl) {
-#define ADAQP_CASE(G) case G: hipLaunchKernelGGL((quantize_pack_kernel<G, VW, PROBE>), grid, dim3(kBlock), 0, st, a); break;
+#define ADAQP_CASE(G) case G: hipLaunchKernelGGL((quantize_pack_kernel<G, VW, PROBE>), grid, dim3(kBlock), 0, st, a, table); break;
         ADAQP_CASE(1) ADAQP_CASE(2) ADAQP_CASE(3) ADAQP_CASE(4)
         ADAQP_CASE(5) ADAQP_CASE(6) ADAQP_CASE(7) ADAQP_CASE(8)
 #undef ADAQP_CASE
@@ -935,13 +945,14 @@ constexpr int kMaxDequantNv = 8;
 inline int dequant_rows_per_wave(int nv) { return nv == 1 ? 4 : (nv == 2 ? 2 : 1); }
 
 template <int VW, bool STREAM>
-hipError_t launch_dequant(const DequantArgs &a, int nv, int64_t n_waves, hipStream_t st)
+hipError_t launch_dequant(DequantArgs a, const LoopBack &copies, int nv, int64_t n_waves, hipStream_t st)
 {
-    const dim3 grid((unsigned)((n_waves + kWavesPerBlock - 1) / kWavesPerBlock));
+    a.own_blocks = (uint32_t)((n_waves + kWavesPerBlock - 1) / kWavesPerBlock);
+    const dim3 grid(a.own_blocks + copies.blocks());
     switch (nv) {
-        case 1: hipLaunchKernelGGL((unpack_dequant_kernel<VW, 1, 4, false, STREAM>), grid, dim3(kBlock), 0, st, a); break;
-        case 2: hipLaunchKernelGGL((unpack_dequant_kernel<VW, 2, 2, true, STREAM>), grid, dim3(kBlock), 0, st, a); break;
-#define ADAQP_CASE(N) case N: hipLaunchKernelGGL((unpack_dequant_kernel<VW, N, 1, true, STREAM>), grid, dim3(kBlock), 0, st, a); break;
+        case 1: hipLaunchKernelGGL((unpack_dequant_kernel<VW, 1, 4, false, STREAM>), grid, dim3(kBlock), 0, st, a, copies); break;
+        case 2: hipLaunchKernelGGL((unpack_dequant_kernel<VW, 2, 2, true, STREAM>), grid, dim3(kBlock), 0, st, a, copies); break;
+#define ADAQP_CASE(N) case N: hipLaunchKernelGGL((unpack_dequant_kernel<VW, N, 1, true, STREAM>), grid, dim3(kBlock), 0, st, a, copies); break;
         ADAQP_CASE(3) ADAQP_CASE(4) ADAQP_CASE(5) ADAQP_CASE(6) ADAQP_CASE(7) ADAQP_CASE(8)
 #undef ADAQP_CASE
         default: return hipErrorInvalidValue;
@@ -969,7 +980,7 @@ namespace {
 int quantize_pack_launch(const float *feat_dev, int64_t n_feat_rows, int64_t ld, int32_t dim,
                          const int32_t *send_idx_dev, const uint8_t *bits_dev, const int64_t *row_offset_dev,
                          int64_t n_send, uint64_t seed, uint8_t *packed_dev, int64_t packed_bytes, float *params_dev,
-                         const float *alpha_sq_dev, float *beta_dev, void *stream, bool probe)
+                         const float *alpha_sq_dev, float *beta_dev, PackedRowArgs table, void *stream, bool probe)
 {
     if ((alpha_sq_dev == nullptr) != (beta_dev == nullptr)) return ADAQP_EINVAL;
     if (!aligned_to(alpha_sq_dev, 4) || !aligned_to(beta_dev, 4)) return ADAQP_EINVAL;
@@ -1039,7 +1050,8 @@ int quantize_pack_launch(const float *feat_dev, int64_t n_feat_rows, int64_t ld,
         if (probe) return ADAQP_EINVAL;                 // rows too wide for registers have no twin
         const int64_t blocks = (n_send + kWavesPerBlock - 1) / kWavesPerBlock;
         if (blocks > INT32_MAX) return ADAQP_ESIZE;
-        hipLaunchKernelGGL(quantize_pack_wide_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, st, a);
+        a.own_blocks = (uint32_t)blocks;
+        hipLaunchKernelGGL(quantize_pack_wide_kernel, dim3((unsigned)blocks + table.blocks), dim3(kBlock), 0, st, a, table);
         ADAQP_HIP_TRY(hipGetLastError());
         return ADAQP_OK;
     }
@@ -1047,15 +1059,16 @@ int quantize_pack_launch(const float *feat_dev, int64_t n_feat_rows, int64_t ld,
     const int64_t rows_per_block = (int64_t)kWavesPerBlock * (kWave >> best_k);
     const int64_t blocks = (n_send + rows_per_block - 1) / rows_per_block;
     if (blocks > INT32_MAX) return ADAQP_ESIZE;
-    const dim3 grid((unsigned)blocks);
+    a.own_blocks = (uint32_t)blocks;
+    const dim3 grid((unsigned)blocks + table.blocks);
     const int vw = vector_width(feat_dev, ld, dim, false);
     hipError_t err;
     if (probe) {
         if (vw != 4) return ADAQP_EINVAL;               // the twin exists for 16-byte-aligned rows only
-        err = launch_quantize<4, true>(a, best_gpl, grid, st);
-    } else if (vw == 4) err = launch_quantize<4>(a, best_gpl, grid, st);
-    else if (vw == 2) err = launch_quantize<2>(a, best_gpl, grid, st);
-    else err = launch_quantize<1>(a, best_gpl, grid, st);
+        err = launch_quantize<4, true>(a, table, best_gpl, grid, st);
+    } else if (vw == 4) err = launch_quantize<4>(a, table, best_gpl, grid, st);
+    else if (vw == 2) err = launch_quantize<2>(a, table, best_gpl, grid, st);
+    else err = launch_quantize<1>(a, table, best_gpl, grid, st);
     ADAQP_HIP_TRY(err);
     return ADAQP_OK;
 }
@@ -1069,7 +1082,16 @@ extern "C" int adaqp_quantize_pack_trace(const float *feat_dev, int64_t n_feat_r
                                          const float *alpha_sq_dev, float *beta_dev, void *stream)
 {
     return quantize_pack_launch(feat_dev, n_feat_rows, ld, dim, send_idx_dev, bits_dev, row_offset_dev, n_send, seed,
-                                packed_dev, packed_bytes, params_dev, alpha_sq_dev, beta_dev, stream, false);
+                                packed_dev, packed_bytes, params_dev, alpha_sq_dev, beta_dev, kNoPackedRows, stream, false);
+}
+
+int adaqp::quantize_pack_beside(const float *feat_dev, int64_t n_feat_rows, int64_t ld, int32_t dim, const int32_t *send_idx_dev,
+                                const uint8_t *bits_dev, const int64_t *row_offset_dev, int64_t n_send, uint64_t seed, uint8_t *packed_dev,
+                                int64_t packed_bytes, float *params_dev, const float *alpha_sq_dev, float *beta_dev, PackedRowArgs table,
+                                void *stream)
+{
+    return quantize_pack_launch(feat_dev, n_feat_rows, ld, dim, send_idx_dev, bits_dev, row_offset_dev, n_send, seed, packed_dev, packed_bytes,
+                                params_dev, alpha_sq_dev, beta_dev, table, stream, false);
 }
 
 extern "C" int adaqp_probe_quantize_pack(const float *feat_dev, int64_t n_feat_rows, int64_t ld, int32_t dim,
@@ -1078,13 +1100,12 @@ extern "C" int adaqp_probe_quantize_pack(const float *feat_dev, int64_t n_feat_r
                                          uint8_t *packed_dev, int64_t packed_bytes, float *params_dev, void *stream)
 {
     return quantize_pack_launch(feat_dev, n_feat_rows, ld, dim, send_idx_dev, bits_dev, row_offset_dev, n_send, 0,
-                                packed_dev, packed_bytes, params_dev, nullptr, nullptr, stream, true);
+                                packed_dev, packed_bytes, params_dev, nullptr, nullptr, kNoPackedRows, stream, true);
 }
 
-extern "C" int adaqp_unpack_dequant(const uint8_t *packed_dev, int64_t packed_bytes, const float *params_dev,
-                                    const uint8_t *bits_dev, const int64_t *row_offset_dev,
-                                    const int32_t *halo_idx_dev, const int32_t *order_dev, int64_t n_recv,
-                                    int32_t dim, float *feat_dev, int64_t n_feat_rows, int64_t ld, void *stream)
+int adaqp::unpack_dequant_beside(const uint8_t *packed_dev, int64_t packed_bytes, const float *params_dev, const uint8_t *bits_dev,
+                                 const int64_t *row_offset_dev, const int32_t *halo_idx_dev, const int32_t *order_dev, int64_t n_recv,
+                                 int32_t dim, float *feat_dev, int64_t n_feat_rows, int64_t ld, LoopBack copies, void *stream)
 {
     if (n_recv < 0 || dim <= 0 || ld < dim || n_feat_rows < 0 || packed_bytes < 0) return ADAQP_EINVAL;
     if (n_recv == 0) return ADAQP_OK;
@@ -1128,29 +1149,39 @@ extern "C" int adaqp_unpack_dequant(const uint8_t *packed_dev, int64_t packed_by
         // whole-line writes go out as non-temporal stores; rows that share lines with their neighbours stay with
         // ordinary stores, which the L2 merges
         if (whole_lines) {
-            err = launch_dequant<4, true>(a, nv, waves, st);            // line-padded rows take 16-byte vectors
+            err = launch_dequant<4, true>(a, copies, nv, waves, st);            // line-padded rows take 16-byte vectors
         } else {
-            if (vw == 4) err = launch_dequant<4, false>(a, nv, waves, st);
-            else if (vw == 2) err = launch_dequant<2, false>(a, nv, waves, st);
-            else err = launch_dequant<1, false>(a, nv, waves, st);
+            if (vw == 4) err = launch_dequant<4, false>(a, copies, nv, waves, st);
+            else if (vw == 2) err = launch_dequant<2, false>(a, copies, nv, waves, st);
+            else err = launch_dequant<1, false>(a, copies, nv, waves, st);
         }
         ADAQP_HIP_TRY(err);
         return ADAQP_OK;
     }
-    const dim3 grid((unsigned)blocks);
+    a.own_blocks = (uint32_t)blocks;
+    const dim3 grid((unsigned)blocks + copies.blocks());
     a.write_dim = write_dim;
     const int vw_long = vector_width(feat_dev, ld, dim, true);
-    if (vw_long == 4) hipLaunchKernelGGL(unpack_dequant_long_kernel<4>, grid, dim3(kBlock), 0, st, a);
-    else if (vw_long == 2) hipLaunchKernelGGL(unpack_dequant_long_kernel<2>, grid, dim3(kBlock), 0, st, a);
-    else hipLaunchKernelGGL(unpack_dequant_long_kernel<1>, grid, dim3(kBlock), 0, st, a);
+    if (vw_long == 4) hipLaunchKernelGGL(unpack_dequant_long_kernel<4>, grid, dim3(kBlock), 0, st, a, copies);
+    else if (vw_long == 2) hipLaunchKernelGGL(unpack_dequant_long_kernel<2>, grid, dim3(kBlock), 0, st, a, copies);
+    else hipLaunchKernelGGL(unpack_dequant_long_kernel<1>, grid, dim3(kBlock), 0, st, a, copies);
     ADAQP_HIP_TRY(hipGetLastError());
     return ADAQP_OK;
+}
+
+extern "C" int adaqp_unpack_dequant(const uint8_t *packed_dev, int64_t packed_bytes, const float *params_dev,
+                                    const uint8_t *bits_dev, const int64_t *row_offset_dev,
+                                    const int32_t *halo_idx_dev, const int32_t *order_dev, int64_t n_recv,
+                                    int32_t dim, float *feat_dev, int64_t n_feat_rows, int64_t ld, void *stream)
+{
+    return unpack_dequant_beside(packed_dev, packed_bytes, params_dev, bits_dev, row_offset_dev, halo_idx_dev, order_dev, n_recv, dim, feat_dev,
+                                 n_feat_rows, ld, kNoLoopBack, stream);
 }
 
 static int dequant_add_launch(const uint8_t *packed_dev, int64_t packed_bytes, const float *params_dev,
                               const uint8_t *bits_dev, const int64_t *row_offset_dev, const int32_t *dst_idx_dev,
                               int64_t n_recv, const int32_t *seg_order_dev, const int64_t *seg_ptr_dev, int64_t n_seg,
-                              int32_t dim, float *grad_dev, int64_t n_grad_rows, int64_t ld, void *stream, bool probe)
+                              int32_t dim, float *grad_dev, int64_t n_grad_rows, int64_t ld, LoopBack copies, void *stream, bool probe)
 {
     if (n_recv < 0 || n_seg < 0 || dim <= 0 || ld < dim || n_grad_rows < 0 || packed_bytes < 0) return ADAQP_EINVAL;
     if (n_recv == 0 || n_seg == 0) return ADAQP_OK;
@@ -1183,25 +1214,25 @@ static int dequant_add_launch(const uint8_t *packed_dev, int64_t packed_bytes, c
     a.n_grad_rows = n_grad_rows;
     a.ld = ld;
     hipStream_t st = (hipStream_t)stream;
-    const dim3 grid((unsigned)blocks);
     const int vw = vector_width(grad_dev, ld, dim, true);
     const int nv = (dim + kWave * vw - 1) / (kWave * vw);          // rows wider than 4 vectors per lane: chunks of 4
     const int seg_per_wave = 4;     // measured on 150 000 messages: two per wave the same, one + 20 %, eight + 9 %
-    const dim3 grid4((unsigned)((n_seg + seg_per_wave * kWavesPerBlock - 1) / (seg_per_wave * kWavesPerBlock)));
+    a.own_blocks = (uint32_t)(nv <= 2 ? (n_seg + seg_per_wave * kWavesPerBlock - 1) / (seg_per_wave * kWavesPerBlock) : blocks);
+    const dim3 grid(a.own_blocks + copies.blocks());
 #define ADAQP_ADD(VW_, ST_)                                                                                        \
     do {                                                                                                           \
-        if (nv == 1) hipLaunchKernelGGL((unpack_dequant_add4_kernel<VW_, 1, 4, ST_, false>), grid4, dim3(kBlock), 0, st, a);   \
-        else if (nv == 2) hipLaunchKernelGGL((unpack_dequant_add4_kernel<VW_, 2, 4, ST_, false>), grid4, dim3(kBlock), 0, st, a); \
-        else if (nv == 3) hipLaunchKernelGGL((unpack_dequant_add_kernel<VW_, 3, ST_>), grid, dim3(kBlock), 0, st, a);   \
-        else hipLaunchKernelGGL((unpack_dequant_add_kernel<VW_, 4, ST_>), grid, dim3(kBlock), 0, st, a);                \
+        if (nv == 1) hipLaunchKernelGGL((unpack_dequant_add4_kernel<VW_, 1, 4, ST_, false>), grid, dim3(kBlock), 0, st, a, copies);   \
+        else if (nv == 2) hipLaunchKernelGGL((unpack_dequant_add4_kernel<VW_, 2, 4, ST_, false>), grid, dim3(kBlock), 0, st, a, copies); \
+        else if (nv == 3) hipLaunchKernelGGL((unpack_dequant_add_kernel<VW_, 3, ST_>), grid, dim3(kBlock), 0, st, a, copies);   \
+        else hipLaunchKernelGGL((unpack_dequant_add_kernel<VW_, 4, ST_>), grid, dim3(kBlock), 0, st, a, copies);                \
     } while (0)
     // rows that are whole 128-byte lines (line-padded layout, dim a multiple of 32) are written back non-temporally
     const bool whole_lines = line_padded(grad_dev, ld) && dim % 32 == 0;
     if (probe) {
         // the twin exists for the shape the full-size workloads take: whole-line rows of at most 512 columns
         if (vw != 4 || !whole_lines || nv > 2) return ADAQP_EINVAL;
-        if (nv == 1) hipLaunchKernelGGL((unpack_dequant_add4_kernel<4, 1, 4, true, true>), grid4, dim3(kBlock), 0, st, a);
-        else hipLaunchKernelGGL((unpack_dequant_add4_kernel<4, 2, 4, true, true>), grid4, dim3(kBlock), 0, st, a);
+        if (nv == 1) hipLaunchKernelGGL((unpack_dequant_add4_kernel<4, 1, 4, true, true>), grid, dim3(kBlock), 0, st, a, copies);
+        else hipLaunchKernelGGL((unpack_dequant_add4_kernel<4, 2, 4, true, true>), grid, dim3(kBlock), 0, st, a, copies);
         ADAQP_HIP_TRY(hipGetLastError());
         return ADAQP_OK;
     }
@@ -1221,7 +1252,16 @@ extern "C" int adaqp_unpack_dequant_add(const uint8_t *packed_dev, int64_t packe
                                         int64_t n_grad_rows, int64_t ld, void *stream)
 {
     return dequant_add_launch(packed_dev, packed_bytes, params_dev, bits_dev, row_offset_dev, dst_idx_dev, n_recv,
-                              seg_order_dev, seg_ptr_dev, n_seg, dim, grad_dev, n_grad_rows, ld, stream, false);
+                              seg_order_dev, seg_ptr_dev, n_seg, dim, grad_dev, n_grad_rows, ld, kNoLoopBack, stream, false);
+}
+
+int adaqp::unpack_dequant_add_beside(const uint8_t *packed_dev, int64_t packed_bytes, const float *params_dev, const uint8_t *bits_dev,
+                                     const int64_t *row_offset_dev, const int32_t *dst_idx_dev, int64_t n_recv, const int32_t *seg_order_dev,
+                                     const int64_t *seg_ptr_dev, int64_t n_seg, int32_t dim, float *grad_dev, int64_t n_grad_rows, int64_t ld,
+                                     LoopBack copies, void *stream)
+{
+    return dequant_add_launch(packed_dev, packed_bytes, params_dev, bits_dev, row_offset_dev, dst_idx_dev, n_recv, seg_order_dev, seg_ptr_dev,
+                              n_seg, dim, grad_dev, n_grad_rows, ld, copies, stream, false);
 }
 
 extern "C" int adaqp_probe_unpack_dequant_add(const uint8_t *packed_dev, int64_t packed_bytes, const float *params_dev,
@@ -1232,5 +1272,5 @@ extern "C" int adaqp_probe_unpack_dequant_add(const uint8_t *packed_dev, int64_t
                                               void *stream)
 {
     return dequant_add_launch(packed_dev, packed_bytes, params_dev, bits_dev, row_offset_dev, dst_idx_dev, n_recv,
-                              seg_order_dev, seg_ptr_dev, n_seg, dim, grad_dev, n_grad_rows, ld, stream, true);
+                              seg_order_dev, seg_ptr_dev, n_seg, dim, grad_dev, n_grad_rows, ld, kNoLoopBack, stream, true);
 }

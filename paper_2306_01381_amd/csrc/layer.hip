@@ -6,6 +6,7 @@
 
 #include <algorithm>
 
+#include "loop_back.hpp"
 #include "spmm_common.hpp"
 #include "host_sort.hpp"
 
@@ -278,6 +279,17 @@ int range_bytes(const adaqp_layer_desc *d, const adaqp_spmm_pieces *pieces, int6
     return ADAQP_OK;
 }
 
+// CHAIN has nothing to overlap the transfer with, and the copy that stands in for it is a launch of 2.5 to 5 us that leaves the GPU part
+// empty.  There the launch that receives takes the bytes from where the copy takes them, and copies them beside; the table of received
+// rows is then filled in the quantisation's launch.  Whole steps: 2 000 rows, 128 columns 19.4 -> 15.4 us (the host's time for its
+// launches), 24 000 rows, 66 columns, packed 32.7 -> 30.3, 179 000 rows, 300 columns 361 -> 355, 30 000 nodes backward 106 -> 104.
+// Buffers that the receiving calls refuse go the other way, and are refused there.
+bool receives_beside(const adaqp_layer_desc *d)
+{
+    return d->schedule == ADAQP_CHAIN && d->n_send > 0 && d->n_send < kBesideMessages && d->packed_bytes >= 4 && aligned_to(d->packed_dev, 4) &&
+           aligned_to(d->params_dev, 8) && aligned_to(d->recv_packed_dev, 4) && aligned_to(d->recv_params_dev, 8);
+}
+
 // Rows [rb, re) as planned, or along the merge path; fused: received rows are read from the receive buffer.
 int aggregate_range(const adaqp_layer_desc *d, int64_t rb, int64_t re, int64_t nz, bool fused, const adaqp_spmm_pieces *pieces, void *ws,
                     int64_t wsb, hipStream_t st)
@@ -293,9 +305,12 @@ int aggregate_range(const adaqp_layer_desc *d, int64_t rb, int64_t re, int64_t n
         a.H = d->feat_dev;
         a.n_cols = d->n_feat_rows;
         a.ldh = d->ld;
-        if (fused)
-            a.p = PackedRows{d->slot_of_row_dev, d->recv_packed_dev, d->packed_bytes, d->recv_params_dev, d->bits_dev, d->row_offset_dev,
-                             d->n_send, 0, d->dim, d->packed_row_dev};
+        if (fused) {
+            const bool beside = receives_beside(d);
+            a.p = PackedRows{d->slot_of_row_dev, beside ? d->packed_dev : d->recv_packed_dev, d->packed_bytes,
+                             beside ? d->params_dev : d->recv_params_dev, d->bits_dev, d->row_offset_dev, d->n_send, 0, d->dim, d->packed_row_dev};
+            a.copies = beside ? loop_back_of(d) : kNoLoopBack;
+        }
         a.dim = d->dim;
         a.out = d->out_dev + rb * d->ldo;
         a.ldo = d->ldo;
@@ -365,95 +380,21 @@ int aggregate(const adaqp_layer_desc *d, bool overlap_part, hipStream_t st)
     return rc != ADAQP_OK ? rc : aggregate_panels(d, overlap_part, st);
 }
 
-// The loop-back copy, both buffers in one launch (the runtime's copies cost the host more than a launch each, and the
-// second one waits for the first).
-struct CopyArgs {
-    const uint8_t *from;
-    uint8_t *to;
-    int64_t bytes, units;       // whole units of 16, 4 or 1 bytes, as the addresses allow
-    int32_t unit;
-};
-
-CopyArgs copy_args(const void *from, void *to, int64_t bytes)
-{
-    CopyArgs c;
-    c.from = static_cast<const uint8_t *>(from);
-    c.to = static_cast<uint8_t *>(to);
-    c.bytes = bytes;
-    c.unit = aligned_to(from, 16) && aligned_to(to, 16) ? 16 : (aligned_to(from, 4) && aligned_to(to, 4) ? 4 : 1);
-    c.units = bytes / c.unit;
-    return c;
-}
-
-// Where each row of feat is found: the place and slot of those that lie packed in the receive buffer, for the kernels that walk planned
-// pieces.  Widths and offsets are read when they are used, as the quantisation reads them: a step follows what was written to them.
-struct PackedRowArgs {
-    const int32_t *slot_of_row;
-    const uint8_t *bits;
-    const int64_t *row_offset;
-    int64_t n_rows, n_slots, packed_bytes;
-    int32_t dim;
-    adaqp_packed_row *row;
-};
-
-__device__ __forceinline__ adaqp_packed_row packed_row_at(const PackedRowArgs &p, int64_t r)
-{
-    const int32_t slot = p.slot_of_row[r];
-    if (slot < 0 || slot >= p.n_slots) return {0, 0};
-    const int32_t b = p.bits[slot];
-    const int64_t at = p.row_offset[slot], stride = 4 * (((int64_t)p.dim * b + 31) >> 5);
-    if (!(b == 2 || b == 4 || b == 8) || at < 0 || (at & 3) != 0 || at > p.packed_bytes - stride) return {0, 0};
-    return {(uint32_t)at | (b == 2 ? 1u : (b == 4 ? 2u : 3u)), (uint32_t)slot};
-}
-
-// Thread i copies unit i, or one byte of what the whole units leave over.
-__device__ __forceinline__ void copy_one(const CopyArgs &c, int64_t i)
-{
-    if (i >= c.units) {
-        const int64_t at = c.units * c.unit + (i - c.units);
-        if (at < c.bytes) c.to[at] = c.from[at];
-    } else if (c.unit == 16) {
-        reinterpret_cast<uint4 *>(c.to)[i] = reinterpret_cast<const uint4 *>(c.from)[i];
-    } else if (c.unit == 4) {
-        reinterpret_cast<uint32_t *>(c.to)[i] = reinterpret_cast<const uint32_t *>(c.from)[i];
-    } else {
-        c.to[i] = c.from[i];
-    }
-}
-
-// A launch has fewer than 2^32 threads: what 2^20 workgroups per buffer do not copy at one unit each they copy in turns.
-constexpr int64_t kCopyBlocks = (int64_t)1 << 20;
-
 // The table of received rows is filled beside the copies, which do not fill the GPU (34 000 rows, 66 columns, the whole step: 35.1 us, 35.0 with
 // a table that the host made).
-__global__ __launch_bounds__(kBlock) void loop_back_kernel(const CopyArgs a, const CopyArgs b, uint32_t blocks_a, uint32_t blocks_b,
-                                                           const PackedRowArgs p)
+__global__ __launch_bounds__(kBlock) void loop_back_kernel(const LoopBack c, const PackedRowArgs p)
 {
-    if (blockIdx.x >= blocks_a + blocks_b) {
-        const int64_t blocks = gridDim.x - blocks_a - blocks_b;
-        for (int64_t r = (int64_t)(blockIdx.x - blocks_a - blocks_b) * kBlock + threadIdx.x; r < p.n_rows; r += blocks * kBlock)
-            p.row[r] = packed_row_at(p, r);
-        return;
-    }
-    const bool first = blockIdx.x < blocks_a;
-    const CopyArgs &c = first ? a : b;
-    const int64_t block = first ? blockIdx.x : blockIdx.x - blocks_a, blocks = first ? blocks_a : blocks_b;
-    const int64_t n = c.units + (c.bytes - c.units * c.unit);
-    for (int64_t i = block * kBlock + threadIdx.x; i < n; i += blocks * kBlock) copy_one(c, i);
+    const uint32_t copying = c.blocks_packed + c.blocks_params;
+    if (blockIdx.x >= copying) fill_packed_rows(p, blockIdx.x - copying);
+    else copy_blocks(c, blockIdx.x, kBlock);
 }
 
-int loop_back(const adaqp_layer_desc *d, bool fill_packed_rows, hipStream_t st)
+int loop_back(const adaqp_layer_desc *d, bool fill_table, hipStream_t st)
 {
     if (d->n_send == 0) return ADAQP_OK;
-    const PackedRowArgs p = {d->slot_of_row_dev, d->bits_dev, d->row_offset_dev, fill_packed_rows ? d->n_feat_rows : 0, d->n_send,
-                             d->packed_bytes, d->dim, d->packed_row_dev};
-    const CopyArgs a = copy_args(d->packed_dev, d->recv_packed_dev, d->packed_bytes);
-    const CopyArgs b = copy_args(d->params_dev, d->recv_params_dev, d->n_send * 2 * (int64_t)sizeof(float));
-    const int64_t blocks_a = std::min((a.units + a.bytes % a.unit + kBlock - 1) / kBlock, kCopyBlocks);
-    const int64_t blocks_b = std::min((b.units + b.bytes % b.unit + kBlock - 1) / kBlock, kCopyBlocks);
-    const int64_t blocks_p = std::min((p.n_rows + kBlock - 1) / kBlock, kCopyBlocks);
-    hipLaunchKernelGGL(loop_back_kernel, dim3((unsigned)(blocks_a + blocks_b + blocks_p)), dim3(kBlock), 0, st, a, b, (uint32_t)blocks_a,
-                       (uint32_t)blocks_b, p);
+    const LoopBack c = loop_back_of(d);
+    const PackedRowArgs p = fill_table ? packed_rows_of(d) : kNoPackedRows;
+    hipLaunchKernelGGL(loop_back_kernel, dim3(c.blocks() + p.blocks), dim3(kBlock), 0, st, c, p);
     ADAQP_HIP_TRY(hipGetLastError());
     return ADAQP_OK;
 }
@@ -494,30 +435,37 @@ int aggregate_both(const adaqp_layer_desc *d, hipStream_t st)
                            first ? d->workspace_overlap_bytes : d->workspace_dependent_bytes, st);
 }
 
-int quantise(const adaqp_layer_desc *d, hipStream_t st)
+int quantise(const adaqp_layer_desc *d, bool fill_table, hipStream_t st)
 {
     const bool forward = d->direction == ADAQP_FORWARD;
-    return adaqp_quantize_pack_trace(forward ? d->feat_dev : d->out_dev,
-                                     forward ? d->n_feat_rows : std::max(d->dependent_end, d->overlap_end),
-                                     forward ? d->ld : d->ldo, d->dim, d->send_idx_dev, d->bits_dev, d->row_offset_dev,
-                                     d->n_send, d->seed, d->packed_dev, d->packed_bytes, d->params_dev, d->alpha_sq_dev,
-                                     d->beta_dev, st);
+    return quantize_pack_beside(forward ? d->feat_dev : d->out_dev, forward ? d->n_feat_rows : std::max(d->dependent_end, d->overlap_end),
+                                forward ? d->ld : d->ldo, d->dim, d->send_idx_dev, d->bits_dev, d->row_offset_dev, d->n_send, d->seed,
+                                d->packed_dev, d->packed_bytes, d->params_dev, d->alpha_sq_dev, d->beta_dev,
+                                fill_table ? packed_rows_of(d) : kNoPackedRows, st);
+}
+
+// Whether received messages become additions to rows of out.
+bool adds_received(const adaqp_layer_desc *d)
+{
+    return d->direction == ADAQP_BACKWARD && d->n_recv_seg > 0 && d->recv_seg_order_dev && d->recv_seg_ptr_dev && d->halo_idx_dev;
 }
 
 // What the received messages become: halo rows of feat (forward, unless the aggregation reads them packed), or additions
-// to rows of out (backward, if segments are given).
-int receive(const adaqp_layer_desc *d, hipStream_t st)
+// to rows of out (backward, if segments are given).  beside: the loop-back copy is part of the launch.
+int receive(const adaqp_layer_desc *d, bool beside, hipStream_t st)
 {
+    const uint8_t *packed = beside ? d->packed_dev : d->recv_packed_dev;
+    const float *params = beside ? d->params_dev : d->recv_params_dev;
+    const LoopBack copies = beside ? loop_back_of(d) : kNoLoopBack;
     if (d->direction == ADAQP_FORWARD) {
         if (fused_receive(d)) return ADAQP_OK;
-        return adaqp_unpack_dequant(d->recv_packed_dev, d->packed_bytes, d->recv_params_dev, d->bits_dev, d->row_offset_dev,
-                                    d->halo_idx_dev, d->recv_order_dev, d->n_send, d->dim, d->feat_dev, d->n_feat_rows,
-                                    d->ld, st);
+        return unpack_dequant_beside(packed, d->packed_bytes, params, d->bits_dev, d->row_offset_dev, d->halo_idx_dev, d->recv_order_dev,
+                                     d->n_send, d->dim, d->feat_dev, d->n_feat_rows, d->ld, copies, st);
     }
-    if (!(d->n_recv_seg > 0 && d->recv_seg_order_dev && d->recv_seg_ptr_dev && d->halo_idx_dev)) return ADAQP_OK;
-    return adaqp_unpack_dequant_add(d->recv_packed_dev, d->packed_bytes, d->recv_params_dev, d->bits_dev, d->row_offset_dev,
-                                    d->halo_idx_dev, d->n_send, d->recv_seg_order_dev, d->recv_seg_ptr_dev, d->n_recv_seg,
-                                    d->dim, d->out_dev, std::max(d->dependent_end, d->overlap_end), d->ldo, st);
+    if (!adds_received(d)) return ADAQP_OK;
+    return unpack_dequant_add_beside(packed, d->packed_bytes, params, d->bits_dev, d->row_offset_dev, d->halo_idx_dev, d->n_send,
+                                     d->recv_seg_order_dev, d->recv_seg_ptr_dev, d->n_recv_seg, d->dim, d->out_dev,
+                                     std::max(d->dependent_end, d->overlap_end), d->ldo, copies, st);
 }
 
 }  // namespace
@@ -570,6 +518,8 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
                         (has_panels(d, true) || has_panels(d, false));
     const bool fills = fused_receive(d) && takes_pieces(d, joint ? &d->pieces_both : &d->pieces_dependent,
                                                         joint ? d->overlap_begin : d->dependent_begin, d->dependent_end, true);
+    // whether there is a launch that takes the loop-back copy with it
+    const bool beside = receives_beside(d) && (forward ? !fused_receive(d) || fills : adds_received(d) && d->n_recv_seg <= d->n_send);
     bool forked = false;
     auto fork_now = [&]() -> int {
         if (!two_streams(d)) return ADAQP_OK;
@@ -603,13 +553,13 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
             ADAQP_STEP(fork_now());
             ADAQP_STEP(paired ? aggregate_rows(d, true, agg) : aggregate(d, true, agg));
         }
-        ADAQP_STEP(quantise(d, msg));
+        ADAQP_STEP(quantise(d, fills && beside, msg));
         if (d->schedule == ADAQP_ISOLATED) {
             ADAQP_STEP(fork_now());
             ADAQP_STEP(paired ? aggregate_rows(d, true, agg) : aggregate(d, true, agg));
         }
-        ADAQP_STEP(loop_back(d, fills, msg));
-        ADAQP_STEP(receive(d, msg));
+        if (!beside) ADAQP_STEP(loop_back(d, fills, msg));
+        ADAQP_STEP(receive(d, beside, msg));
         if (!two_streams(d) && !joint) ADAQP_STEP(aggregate(d, true, msg));
         if (joint) {
             ADAQP_STEP(aggregate_both(d, msg));
@@ -635,16 +585,16 @@ extern "C" int adaqp_layer_step(const adaqp_layer_desc *d)
             if (both_tiled) ADAQP_STEP(join_now());         // as in the forward step: one tiled launch at a time
         }
         ADAQP_STEP(joint ? aggregate_both(d, msg) : aggregate(d, false, msg));
-        ADAQP_STEP(quantise(d, msg));
+        ADAQP_STEP(quantise(d, fills && beside, msg));
         if (d->schedule == ADAQP_ISOLATED) {
             ADAQP_STEP(fork_now());
             ADAQP_STEP(aggregate(d, true, agg));
         }
-        ADAQP_STEP(loop_back(d, fills, msg));
+        if (!beside) ADAQP_STEP(loop_back(d, fills, msg));
         if (!two_streams(d) && !joint) ADAQP_STEP(aggregate(d, true, msg));
         // the received gradients are added to rows that the local aggregation also writes: join first
         ADAQP_STEP(join_now());
-        ADAQP_STEP(receive(d, msg));
+        ADAQP_STEP(receive(d, beside, msg));
     }
     ADAQP_STEP(join_now());
 #undef ADAQP_STEP

@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "loop_back.hpp"
 #include "spmm_rules.hpp"
 
 namespace adaqp {
@@ -69,6 +70,8 @@ struct PieceArgs {
     int64_t ldp;
     int32_t n_partials;
     int32_t n_blocks;                   // workgroups per slice
+    uint32_t own_blocks;                // workgroups of the launch that walk; the others copy, where rows may be packed
+    LoopBack copies;
 };
 // What of a plan can be seen from the host, and the launches; the caller has filled in everything from ptr on but what the plan says.
 int check_pieces(const adaqp_spmm_pieces *p, int64_t n_seg);

@@ -1917,6 +1917,41 @@ def test_layer_step_copies_the_whole_buffer(extra, offset):
     assert torch.equal(L.recv_params, L.params)
 
 
+@pytest.mark.parametrize("kind,dim,extra,offset", [("forward", 128, 0, 0), ("forward", 97, 5, 4), ("forward", 2100, 3, 16), ("fused", 66, 0, 0),
+                                                   ("fused", 130, 4099, 8), ("backward", 128, 0, 0), ("backward", 97, 5, 4), ("backward", 2100, 3, 16)])
+def test_layer_step_chain_copies_beside_the_receive(kind, dim, extra, offset):
+    """CHAIN receives from where the loop-back copy takes the bytes, and copies in the same launch: what the other schedules leave, in every
+    buffer, also bytes that no message covers and messages that are skipped."""
+    _say(f"chain, {kind} dim={dim} extra={extra} offset={offset}")
+    backward = kind == "backward"
+    p = make_partition(replace(CONFIGS["c0"], dim=dim) if not backward else
+                       replace(CONFIGS["c4"], n_local=2000, n_halo=1800, n_send=1500, mean_degree=9.0, dim=dim))
+    left = []
+    for schedule in (B.SERIAL, B.CHAIN):
+        L = LayerStep(p, DEV, seed=5, fused_receive=kind == "fused")
+        n = L.plan.packed_bytes + extra
+        sent = torch.full((n + 16,), 3, dtype=torch.uint8, device=DEV)
+        received = torch.full((n + 48,), 7, dtype=torch.uint8, device=DEV)
+        L.params.fill_(0.5)
+        L.plan.bits[3], L.plan.send_idx[7] = 5, -1                          # skipped: their bytes and (Z, S) stay what they are
+        L.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        d = L.desc(schedule)
+        d.packed_dev, d.packed_bytes, d.recv_packed_dev = sent.data_ptr(), n, received.data_ptr() + offset
+        if backward:
+            d.overlap_end -= 1                                              # what is sent are sums: two launches in either schedule, the same bits
+        B.adaqp_layer_step(d)
+        L.synchronize()
+        assert torch.equal(received[offset:offset + n], sent[:n]) and torch.equal(L.recv_params, L.params)
+        assert bool((received[:offset] == 7).all()) and bool((received[offset + n:] == 7).all())
+        left.append([t.contiguous().view(torch.int32).clone() for t in (L.out, L.feat, L.params, L.beta)] + [sent])
+    for a, b in zip(left[0][not backward:], left[1][not backward:]):
+        assert torch.equal(a, b)
+    if not backward:                                                        # rows in one launch may be cut in other places
+        a, b = (x[0].view(torch.float32).double() for x in left)
+        assert not bool(torch.isnan(b).any()) and float((a - b).norm()) <= 1e-6 * float(a.norm())
+
+
 def test_mean_aggregator_layer_step(oracle):
     """GraphSAGE-style mean coefficients (1 / row degree) through the same step."""
     p = make_partition(replace(CONFIGS["c0"], aggregator="mean"))
