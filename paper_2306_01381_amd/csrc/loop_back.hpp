@@ -69,6 +69,7 @@ __device__ __forceinline__ void copy_one(const CopyArgs &c, int64_t i)
 __device__ __forceinline__ void copy_blocks(const LoopBack &c, uint32_t block, int32_t threads)
 {
     const bool first = block < c.blocks_packed;
+    if (block >= c.blocks_packed + c.blocks_params) return;
     const CopyArgs &of = first ? c.packed : c.params;
     const int64_t mine = first ? block : block - c.blocks_packed, blocks = first ? c.blocks_packed : c.blocks_params;
     const int64_t n = of.units + (of.bytes - of.units * of.unit);

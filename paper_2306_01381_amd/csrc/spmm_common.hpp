@@ -70,7 +70,7 @@ struct PieceArgs {
     int64_t ldp;
     int32_t n_partials;
     int32_t n_blocks;                   // workgroups per slice
-    uint32_t own_blocks;                // workgroups of the launch that walk; the others copy, where rows may be packed
+    uint32_t copy_blocks;               // first workgroups of the launch, whole rounds over the XCDs, that copy, where rows may be packed
     LoopBack copies;
 };
 // What of a plan can be seen from the host, and the launches; the caller has filled in everything from ptr on but what the plan says.

@@ -397,10 +397,11 @@ __global__ __launch_bounds__(WAVES * kWave, PACKED && ENTRIES > kFewEntries ? 2 
     constexpr bool kJoins = WAVES > kWavesPerBlock;
     __shared__ alignas(16) Entry<PACKED> stages[WAVES][ENTRIES + kWave];
     __shared__ Joined joined[kJoins ? WAVES : 1];
-    if constexpr (PACKED) if (blockIdx.x >= a.own_blocks) return copy_blocks(a.copies, blockIdx.x - a.own_blocks, WAVES * kWave);
+    if constexpr (PACKED) if (blockIdx.x < a.copy_blocks) return copy_blocks(a.copies, blockIdx.x, WAVES * kWave);
+    const uint32_t block = PACKED ? blockIdx.x - a.copy_blocks : blockIdx.x;
     const SliceTasks tasks(a.lines, VPL, a.n_blocks, PACKED);
-    const int32_t xcd = blockIdx.x % kXcds;
-    const int64_t task = tasks.first_task(xcd) + blockIdx.x / kXcds;
+    const int32_t xcd = block % kXcds;
+    const int64_t task = tasks.first_task(xcd) + block / kXcds;
     if (task >= tasks.first_task(xcd + 1)) return;          // the whole workgroup
     const int32_t slice = (int32_t)(task / a.n_blocks), blk = (int32_t)(task % a.n_blocks), line = slice * VPL;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -557,8 +558,8 @@ int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
         s.p.full_dim = a.dim;
         s.out += l0 * kLine;
         if (s.partial) s.partial += l0 * kLine;
-        s.own_blocks = (uint32_t)(SliceTasks(s.lines, per_slice, s.n_blocks, packed).most_per_xcd() * kXcds);
-        const dim3 grid(s.own_blocks + (packed && l0 == 0 ? s.copies.blocks() : 0));
+        s.copy_blocks = packed && l0 == 0 ? (s.copies.blocks() + kXcds - 1) / kXcds * kXcds : 0;
+        const dim3 grid((unsigned)(SliceTasks(s.lines, per_slice, s.n_blocks, packed).most_per_xcd() * kXcds) + s.copy_blocks);
         const PieceKernel kernel = packed ? kernel_of<true, true>(p) : a.of_rows ? kernel_of<false, true>(p) : kernel_of<false, false>(p);
         hipLaunchKernelGGL(kernel, grid, dim3(p->waves * kWave), p->entries == kEntries && per_slice > 1 && !packed ? kIdleLds : 0, st, s);
         ADAQP_HIP_TRY(hipGetLastError());
