@@ -300,6 +300,7 @@ int aggregate_range(const adaqp_layer_desc *d, int64_t rb, int64_t re, int64_t n
         a.col = d->col_dev;
         a.val = d->val_dev;
         a.n_entries = d->nnz;
+        a.n_walked = nz;
         a.n_seg = a.n_rows = (int32_t)(re - rb);
         a.of_rows = true;
         a.H = d->feat_dev;

@@ -57,6 +57,7 @@ struct PieceArgs {
     const int32_t *col;
     const float *val;
     int64_t n_entries;                  // capacity of col / val
+    int64_t n_walked;                   // of rows: entries that the caller says they have
     int32_t n_pieces, n_seg;
     bool of_rows;                       // segments are the rows of out (always where rows of H may be packed)
     const float *H;

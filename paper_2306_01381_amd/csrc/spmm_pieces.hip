@@ -36,7 +36,7 @@ constexpr int32_t kJoined = -2, kNowhere = INT32_MIN;       // a piece's partial
 constexpr int32_t kMoved = INT32_MIN + 1;                   // in place of a destination: rowptr is no longer what the plan was made from
 constexpr int32_t kNoEnd = 0x10000;                         // lies after every step of a piece
 constexpr int kPackedLines = 4;                             // per slice where rows may be packed: their codes share lines
-constexpr unsigned kIdleLds = 6144;                         // of a workgroup, beside its 26 KB: no more than 16 waves on a CU
+constexpr unsigned kIdleLds[2] = {6144, 24576};             // of a workgroup, beside its 26 KB: no more than 16 or 12 waves on a CU
 static_assert(kEnds < kWave - 1, "a lane per end, and one that has none");
 
 // A sum to its place.  Lanes without a column of their own store outside the row's buffer: no branch.
@@ -535,6 +535,20 @@ PieceKernel kernel_of(const adaqp_spmm_pieces *p)
                                      : kernel_of<PACKED, ROWS, kWavesPerBlock, kEntries>(p->lines_per_slice);
 }
 
+// LDS that keeps waves away.  Lines that are asked for wait in the order of the asking in the L1, which has room for 256; where some of them miss
+// the L2 more waves only wait longer and ask for more than the L2 holds.  Segments: 16 waves (see above).  Rows of about 40 entries and
+// more: 12 (16.3 M entries, 376 000 rows, 256 columns, the step 875 -> 858 us; 4 M, 50 000 rows, 128 columns 110.7 -> 107.6; 15.3 M, 223 000
+// rows, 320 columns 935 -> 899), but all that fit where rows are shorter (with 12, 17 entries 0.94, 3 entries 0.93), where there are
+// pieces for a turn or two only (6 144, two lines 0.94-0.97; four lines 0.97 with 330 entries each, 1.02 with 600) and for one line per
+// slice (0.83).
+unsigned idle_lds(const adaqp_spmm_pieces *p, const PieceArgs &a, int32_t per_slice, bool packed)
+{
+    if (p->entries != kEntries || per_slice == 1 || packed) return 0;
+    const int64_t waves = (int64_t)a.n_pieces * ((a.lines + per_slice - 1) / per_slice);
+    const bool turns = waves >= 9000 || (per_slice == 4 && a.n_walked >= 550 * (int64_t)a.n_pieces);
+    return kIdleLds[a.of_rows && turns && a.n_walked >= 40 * (int64_t)a.n_seg];
+}
+
 }  // namespace
 
 int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
@@ -561,7 +575,7 @@ int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
         s.copy_blocks = packed && l0 == 0 ? (s.copies.blocks() + kXcds - 1) / kXcds * kXcds : 0;
         const dim3 grid((unsigned)(SliceTasks(s.lines, per_slice, s.n_blocks, packed).most_per_xcd() * kXcds) + s.copy_blocks);
         const PieceKernel kernel = packed ? kernel_of<true, true>(p) : a.of_rows ? kernel_of<false, true>(p) : kernel_of<false, false>(p);
-        hipLaunchKernelGGL(kernel, grid, dim3(p->waves * kWave), p->entries == kEntries && per_slice > 1 && !packed ? kIdleLds : 0, st, s);
+        hipLaunchKernelGGL(kernel, grid, dim3(p->waves * kWave), idle_lds(p, s, per_slice, packed), st, s);
         ADAQP_HIP_TRY(hipGetLastError());
     }
     constexpr int64_t kMostSums = (int64_t)1 << 24;         // of a launch, which has fewer than 2^32 threads
