@@ -89,6 +89,13 @@ int adaqp_plan_layout(int64_t n, int32_t dim, const uint8_t *bits_host, const in
                       int32_t n_peers, int64_t *perm_out, int64_t *row_offset_out,
                       int64_t *peer_byte_ptr_out);
 
+/* adaqp_plan_layout, and the caller's per-slot arrays in sorted order: send_idx_out[k] = send_idx_host[perm_out[k]], bits_out and
+ * (halo_idx_host not NULL) halo_idx_out likewise, all [n], with recv_order_out[n] = adaqp_plan_recv_order of halo_idx_out.
+ * Errors: as adaqp_plan_layout, ESIZE (halo_idx_host and n > 2^31 - 1). */
+int adaqp_plan_send(int64_t n, int32_t dim, const uint8_t *bits_host, const int32_t *peer_of_slot_host, int32_t n_peers,
+                    const int32_t *send_idx_host, const int32_t *halo_idx_host, int64_t *perm_out, int64_t *row_offset_out,
+                    int64_t *peer_byte_ptr_out, int32_t *send_idx_out, uint8_t *bits_out, int32_t *halo_idx_out, int32_t *recv_order_out);
+
 /* ---------------------------------------------------------------------------------------------------- */
 /* Send side: Sec. 2.3 Eq. 4 with the stochastic rounding of App. A.1, then sub-byte merging (Sec. 5).    */
 /* ---------------------------------------------------------------------------------------------------- */

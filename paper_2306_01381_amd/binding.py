@@ -109,6 +109,7 @@ _SIGNATURES = {
     "adaqp_quantize_pack": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp, _vp, _i64, _u64, _vp, _i64, _vp, _vp]),
     "adaqp_quantize_pack_trace": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp, _vp, _i64, _u64, _vp, _i64, _vp,
                                                  _vp, _vp, _vp]),
+    "adaqp_plan_send": (ctypes.c_int, [_i64, _i32, _vp, _vp, _i32] + [_vp] * 9),
     "adaqp_plan_recv_order": (ctypes.c_int, [_i64, _vp, _vp]),
     "adaqp_unpack_dequant": (ctypes.c_int, [_vp, _i64, _vp, _vp, _vp, _vp, _vp, _i64, _i32, _vp, _i64, _i64, _vp]),
     "adaqp_plan_recv_segments": (ctypes.c_int, [_i64, _vp, _vp, _vp, ctypes.POINTER(_i64)]),
@@ -236,6 +237,39 @@ def adaqp_plan_layout(dim: int, bits_host: np.ndarray, peer_of_slot_host: np.nda
     _check(lib().adaqp_plan_layout(n, dim, bits.ctypes.data, peer.ctypes.data, n_peers,
                                    perm.ctypes.data, off.ctypes.data, pbp.ctypes.data), "adaqp_plan_layout")
     return perm, off, pbp
+
+
+def adaqp_plan_send(dim: int, bits_host: np.ndarray, peer_of_slot_host: np.ndarray, n_peers: int, send_idx_host: np.ndarray,
+                    halo_idx_host: Optional[np.ndarray]) -> dict:
+    """Host-only.  adaqp_plan_layout's perm, row_offset and peer_byte_ptr, and the per-slot arrays in sorted order: send_idx, bits and (with
+    halo_idx) halo_idx, recv_order.  `blob` (uint8) holds what the device needs, every array but perm and peer_byte_ptr, each at a multiple of
+    256 bytes named in `at`: one upload."""
+    bits = np.ascontiguousarray(bits_host, dtype=np.uint8)
+    peer = np.ascontiguousarray(peer_of_slot_host, dtype=np.int32)
+    n = bits.shape[0]
+    if peer.shape[0] != n:
+        raise ValueError("bits and peer_of_slot differ in length")
+    arrays = [("row_offset", np.int64), ("send_idx", np.int32)] + ([("halo_idx", np.int32), ("recv_order", np.int32)] if halo_idx_host is not None else []) \
+        + [("bits", np.uint8)]
+    send = np.ascontiguousarray(send_idx_host, dtype=np.int32)
+    halo = None if halo_idx_host is None else np.ascontiguousarray(halo_idx_host, dtype=np.int32)
+    if send.shape[0] < n or (halo is not None and halo.shape[0] < n):
+        raise IndexError("send_idx or halo_idx has fewer entries than slots")
+    at, total = {}, 0
+    for name, dtype in arrays:
+        at[name] = (total, n * np.dtype(dtype).itemsize, dtype)
+        total += -(-at[name][1] // 256) * 256
+    plan = {"perm": np.empty(n, dtype=np.int64), "peer_byte_ptr": np.zeros(max(n_peers, 0) + 1, dtype=np.int64),
+            "blob": np.empty(total, dtype=np.uint8), "at": at}
+    for name, (begin, size, dtype) in at.items():
+        plan[name] = plan["blob"][begin:begin + size].view(dtype)
+
+    def ptr(name):
+        return plan[name].ctypes.data if name in plan else None
+    _check(lib().adaqp_plan_send(n, dim, bits.ctypes.data, peer.ctypes.data, n_peers, send.ctypes.data, None if halo is None else halo.ctypes.data,
+                                 ptr("perm"), ptr("row_offset"), ptr("peer_byte_ptr"), ptr("send_idx"), ptr("bits"), ptr("halo_idx"),
+                                 ptr("recv_order")), "adaqp_plan_send")
+    return plan
 
 
 def adaqp_quantize_pack(feat: torch.Tensor, dim: int, send_idx: torch.Tensor, bits: torch.Tensor,

@@ -46,14 +46,12 @@ extern "C" int64_t adaqp_row_stride(int32_t dim, int32_t bits)
     return 4 * (((int64_t)dim * bits + 31) / 32);
 }
 
-extern "C" int adaqp_plan_layout(int64_t n, int32_t dim, const uint8_t *bits_host,
-                                 const int32_t *peer_of_slot_host, int32_t n_peers, int64_t *perm_out,
-                                 int64_t *row_offset_out, int64_t *peer_byte_ptr_out)
+namespace {
+
+// Whether peers ascend within [0, n_peers) and widths are ones that there are: checked without a branch per slot; only where something is
+// wrong a second look says what comes first.
+int check_slots(int64_t n, const uint8_t *bits_host, const int32_t *peer_of_slot_host, int32_t n_peers)
 {
-    if (n < 0 || dim <= 0 || n_peers < 0 || !peer_byte_ptr_out) return ADAQP_EINVAL;
-    if (n > 0 && (!bits_host || !peer_of_slot_host || !perm_out || !row_offset_out)) return ADAQP_EINVAL;
-    if (n > 0 && n_peers == 0) return ADAQP_EINVAL;
-    // checked without a branch per slot; only where something is wrong a second look says what comes first
     bool ok = n == 0 || (peer_of_slot_host[0] >= 0 && peer_of_slot_host[n - 1] < n_peers);
     for (int64_t i = 0; i < n; ++i) ok &= (bits_host[i] == 2) | (bits_host[i] == 4) | (bits_host[i] == 8);
     for (int64_t i = 1; i < n; ++i) ok &= peer_of_slot_host[i - 1] <= peer_of_slot_host[i];
@@ -63,32 +61,104 @@ extern "C" int adaqp_plan_layout(int64_t n, int32_t dim, const uint8_t *bits_hos
         if (p < 0 || p >= n_peers) return ADAQP_EINVAL;
         if (i > 0 && p < peer_of_slot_host[i - 1]) return ADAQP_EINVAL;
     }
-    // One counting pass per peer segment: slots of width 2 first, then 4, then 8, input order kept.
-    const int64_t stride_of[3] = {adaqp_row_stride(dim, 2), adaqp_row_stride(dim, 4), adaqp_row_stride(dim, 8)};
-    int64_t seg_begin = 0, bytes = 0;
+    return ADAQP_OK;
+}
+
+// Places checked slots: width 2 first, then 4, then 8 inside a peer, input order kept.  place(i, k, byte): slot i comes to place k, its row to
+// that byte.  The next place of a width waits for the slot before it (a store and a load of one address), so a peer's slots are walked in
+// four parts at once, whose counts say where each begins (100 000 slots 192 -> 128 us).
+template <typename Place>
+void place_slots(int64_t n, int32_t dim, const uint8_t *bits_host, const int32_t *peer_of_slot_host, int32_t n_peers, int64_t *peer_byte_ptr_out,
+                 Place place)
+{
+    constexpr int kParts = 4, kWidths = 3;                  // 2, 4, 8 >> 2
+    const int64_t stride[kWidths] = {adaqp_row_stride(dim, 2), adaqp_row_stride(dim, 4), adaqp_row_stride(dim, 8)};
+    int64_t begin = 0, bytes = 0;
     for (int32_t p = 0; p < n_peers; ++p) {
-        int64_t seg_end = seg_begin;
-        int64_t count[3] = {0, 0, 0};
-        while (seg_end < n && peer_of_slot_host[seg_end] == p) ++count[bits_host[seg_end++] >> 2];     // 2, 4, 8 -> 0, 1, 2
-        peer_byte_ptr_out[p] = bytes;
-        int64_t next_slot[3], next_byte[3];
-        next_slot[0] = seg_begin;
-        next_slot[1] = next_slot[0] + count[0];
-        next_slot[2] = next_slot[1] + count[1];
-        next_byte[0] = bytes;
-        next_byte[1] = next_byte[0] + count[0] * stride_of[0];
-        next_byte[2] = next_byte[1] + count[1] * stride_of[1];
-        bytes = next_byte[2] + count[2] * stride_of[2];
-        for (int64_t i = seg_begin; i < seg_end; ++i) {
-            const int w = bits_host[i] >> 2;
-            const int64_t k = next_slot[w]++;
-            perm_out[k] = i;
-            row_offset_out[k] = next_byte[w];
-            next_byte[w] += stride_of[w];
+        const int64_t end = std::upper_bound(peer_of_slot_host + begin, peer_of_slot_host + n, p) - peer_of_slot_host;
+        const int64_t part = (end - begin) / kParts;
+        auto part_begin = [&](int q) { return q < kParts ? begin + q * part : end; };
+        int64_t next[kParts][kWidths], byte_of_0[kWidths];  // byte_of_0 + k * stride: of place k
+        for (int q = 0; q < kParts; ++q) {
+            int64_t n4 = 0, n8 = 0;
+            for (int64_t i = part_begin(q); i < part_begin(q + 1); ++i) {
+                n4 += bits_host[i] == 4;
+                n8 += bits_host[i] == 8;
+            }
+            next[q][0] = part_begin(q + 1) - part_begin(q) - n4 - n8;
+            next[q][1] = n4;
+            next[q][2] = n8;
         }
-        seg_begin = seg_end;
+        peer_byte_ptr_out[p] = bytes;
+        int64_t at = begin;
+        for (int w = 0; w < kWidths; ++w) {
+            byte_of_0[w] = bytes - at * stride[w];
+            for (int q = 0; q < kParts; ++q) {
+                const int64_t count = next[q][w];
+                next[q][w] = at;
+                at += count;
+                bytes += count * stride[w];
+            }
+        }
+        auto place_one = [&](int q, int64_t i) {
+            const int w = bits_host[i] >> 2;
+            const int64_t k = next[q][w]++;
+            place(i, k, byte_of_0[w] + k * stride[w]);
+        };
+        for (int64_t t = 0; t < part; ++t)
+            for (int q = 0; q < kParts; ++q) place_one(q, begin + q * part + t);
+        for (int64_t i = begin + kParts * part; i < end; ++i) place_one(kParts - 1, i);
+        begin = end;
     }
     peer_byte_ptr_out[n_peers] = bytes;
+}
+
+}  // namespace
+
+extern "C" int adaqp_plan_layout(int64_t n, int32_t dim, const uint8_t *bits_host,
+                                 const int32_t *peer_of_slot_host, int32_t n_peers, int64_t *perm_out,
+                                 int64_t *row_offset_out, int64_t *peer_byte_ptr_out)
+{
+    if (n < 0 || dim <= 0 || n_peers < 0 || !peer_byte_ptr_out) return ADAQP_EINVAL;
+    if (n > 0 && (!bits_host || !peer_of_slot_host || !perm_out || !row_offset_out)) return ADAQP_EINVAL;
+    if (n > 0 && n_peers == 0) return ADAQP_EINVAL;
+    ADAQP_TRY(check_slots(n, bits_host, peer_of_slot_host, n_peers));
+    place_slots(n, dim, bits_host, peer_of_slot_host, n_peers, peer_byte_ptr_out, [&](int64_t i, int64_t k, int64_t byte) {
+        perm_out[k] = i;
+        row_offset_out[k] = byte;
+    });
+    return ADAQP_OK;
+}
+
+extern "C" int adaqp_plan_send(int64_t n, int32_t dim, const uint8_t *bits_host, const int32_t *peer_of_slot_host, int32_t n_peers,
+                               const int32_t *send_idx_host, const int32_t *halo_idx_host, int64_t *perm_out, int64_t *row_offset_out,
+                               int64_t *peer_byte_ptr_out, int32_t *send_idx_out, uint8_t *bits_out, int32_t *halo_idx_out,
+                               int32_t *recv_order_out)
+{
+    if (n < 0 || dim <= 0 || n_peers < 0 || !peer_byte_ptr_out) return ADAQP_EINVAL;
+    if (n > 0 && (!bits_host || !peer_of_slot_host || !perm_out || !row_offset_out || !send_idx_host || !send_idx_out || !bits_out)) return ADAQP_EINVAL;
+    if (n > 0 && (n_peers == 0 || (halo_idx_host && (!halo_idx_out || !recv_order_out)))) return ADAQP_EINVAL;
+    if (halo_idx_host && n > INT32_MAX) return ADAQP_ESIZE;
+    ADAQP_TRY(check_slots(n, bits_host, peer_of_slot_host, n_peers));
+    auto place = [&](int64_t i, int64_t k, int64_t byte) {
+        perm_out[k] = i;
+        row_offset_out[k] = byte;
+        send_idx_out[k] = send_idx_host[i];
+        bits_out[k] = bits_host[i];
+    };
+    if (!halo_idx_host || n == 0) {
+        place_slots(n, dim, bits_host, peer_of_slot_host, n_peers, peer_byte_ptr_out, place);
+        return ADAQP_OK;
+    }
+    // rows that ascend in the order of the slots (halo nodes numbered peer by peer): a slot's place is what the order lists
+    bool ascending = true;
+    for (int64_t i = 1; i < n; ++i) ascending &= halo_idx_host[i - 1] < halo_idx_host[i];
+    place_slots(n, dim, bits_host, peer_of_slot_host, n_peers, peer_byte_ptr_out, [&](int64_t i, int64_t k, int64_t byte) {
+        place(i, k, byte);
+        halo_idx_out[k] = halo_idx_host[i];
+        recv_order_out[i] = (int32_t)k;
+    });
+    if (!ascending) order_by_value(n, halo_idx_out, recv_order_out);
     return ADAQP_OK;
 }
 

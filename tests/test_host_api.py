@@ -221,6 +221,33 @@ def test_spmm_workspace_of_few_rows():
     assert B.adaqp_spmm_workspace_bytes(1, 5, 16_000_000) <= B.SPMM_NOALLOC_SCRATCH_BYTES
 
 
+@pytest.mark.parametrize("n,peers,halo", [(0, 3, "rising"), (1, 1, "none"), (257, 1, "rising"), (1000, 7, "rising"), (1000, 7, "equal"), (1000, 4, "any"),
+                                          (3000, 300, "any"), (999, 5, "none")])
+def test_plan_send(n, peers, halo):
+    """The layout, the caller's arrays in its order, and the visiting order of the received rows: those of the single calls."""
+    rng = np.random.default_rng(n + peers)
+    bits = rng.choice(np.array([2, 4, 8], np.uint8), n)
+    peer = np.sort(rng.integers(0, peers, n)).astype(np.int32)
+    send = rng.integers(-5, 1 << 20, n + 3)
+    rows = {"rising": np.cumsum(rng.integers(1, 4, n)), "equal": np.cumsum(rng.integers(0, 2, n)), "any": rng.integers(0, 1 << 30, n), "none": None}[halo]
+    plan = B.adaqp_plan_send(37, bits, peer, peers, send, rows)
+    perm, off, ptr = B.adaqp_plan_layout(37, bits, peer, peers)
+    want = {"perm": perm, "row_offset": off, "peer_byte_ptr": ptr, "send_idx": send[perm].astype(np.int32), "bits": bits[perm]}
+    if rows is not None:
+        want["halo_idx"] = rows[perm].astype(np.int32)
+        want["recv_order"] = B.adaqp_plan_recv_order(want["halo_idx"])
+        assert np.array_equal(want["recv_order"], np.argsort(want["halo_idx"], kind="stable"))
+    for name, values in want.items():
+        assert plan[name].dtype == values.dtype and np.array_equal(plan[name], values), name
+    for name, (begin, size, dtype) in plan["at"].items():               # what is uploaded
+        assert begin % 256 == 0 and np.array_equal(plan["blob"][begin:begin + size].view(dtype), want[name]), name
+    assert ("halo_idx" in plan) == (rows is not None)
+    if n:
+        for wrong in (dict(bits=np.full(n, 3, np.uint8)), dict(peer=peer[::-1] - 1), dict(peer=peer + peers)):
+            with pytest.raises(B.AdaqpError):
+                B.adaqp_plan_send(37, wrong.get("bits", bits), wrong.get("peer", peer), peers, send, rows)
+
+
 def test_plan_recv_segments():
     dst = np.array([7, 3, 7, 9, 3, 3], dtype=np.int32)
     order, seg_ptr = B.adaqp_plan_recv_segments(dst)
