@@ -10,8 +10,9 @@
 //   * row ends are staged the same way, 64 rows at a time;
 //   * U entries are in flight at once (U * NV vector loads per lane) before the first is consumed;
 //   * a row that ends inside the piece is stored directly; what a piece has accumulated for a row that
-//     continues into the next piece goes to a carry slot in the workspace.
-// A second, tiny kernel adds the carries of each split row in piece order.  The summation order therefore
+//     continues into the next piece meets the rest of the row in LDS, where that is a piece of the same workgroup; what a workgroup has of
+//     a row that continues in the next one goes to a carry slot in the workspace.
+// A second, tiny kernel adds the carries of each split row in order.  The summation order therefore
 // depends only on the launch geometry: results are bit-identical from run to run and across schedules.
 //
 // Where sliced_cut (spmm_rules.hpp) says so the kernel of spmm_sliced.hip takes the call instead (same path, feature columns
@@ -116,12 +117,23 @@ constexpr int32_t kFar = 0x7FFFFFFF;
 // PACKED: entries whose column has a slot in slot_of_row take the neighbour row from the packed receive buffer
 // and de-quantise it in registers, (float)code * S + Z as in Sec. 2.3 Eq. 5 (product rounded, then sum rounded),
 // so the result is bit-identical to de-quantising into H first - without writing and re-reading those rows.
+//
+// JOINS: nearly every piece leaves a part of a row to the next one.  As long as a row's parts and ends lie in one workgroup they are added up
+// in its LDS, and there is a carry slot per workgroup instead of one per piece (send, receive and sums of 60 000 rows, 1 M entries, 301
+// columns 213 -> 201 us, of it the carries 17 -> 7; 150 000 rows, 1.2 M, 472 columns 440 -> 404; error against 64 bits 0.98 times, never more,
+// over 14 graphs).  The LDS of wider rows would keep other workgroups away: a carry slot per piece.
+constexpr int kJoinFloats = 8;              // of a lane, per row: 16 KB for a workgroup's parts and first rows
+
 template <int VW, int NV, int U, bool PACKED, bool CHAINS>
 __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
 {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int32_t item = uniform_i32((int32_t)(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)));
-    if (item >= a.n_items) return;
+    constexpr bool JOINS = VW * NV <= kJoinFloats;
+    __shared__ float open[JOINS ? kWavesPerBlock : 1][JOINS ? VW * NV : 1][kWave];      // what a piece has of the row that it leaves open
+    __shared__ float first[JOINS ? kWavesPerBlock : 1][JOINS ? VW * NV : 1][kWave];     // and of the first row that ends in it
+    __shared__ int32_t open_row[kWavesPerBlock];
+    const int lane = threadIdx.x & (kWave - 1), wave = uniform_i32((int32_t)(threadIdx.x >> 6));
+    const int32_t item = uniform_i32((int32_t)(blockIdx.x * kWavesPerBlock) + wave);
+    if (!JOINS && item >= a.n_items) return;
 
     // extent of the range on the device: the host only sized the launch
     const int64_t base = uniform_i64(clamp64(a.rowptr[0], 0, a.nnz));
@@ -129,8 +141,8 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
     const int64_t total = (int64_t)a.n_rows + nnz_r;
     const int64_t per = (total + a.n_items - 1) / a.n_items;
     const int64_t d0 = (int64_t)item * per < total ? (int64_t)item * per : total;
-    const int64_t d1 = d0 + per < total ? d0 + per : total;
-    if (d0 >= d1) {
+    const int64_t d1 = item < a.n_items && d0 + per < total ? d0 + per : (item < a.n_items ? total : d0);
+    if (!JOINS && d0 >= d1) {
         if (lane == 0) a.carry_row[item] = kNoRow;
         return;
     }
@@ -178,20 +190,33 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
                 }
         }
     };
-    auto flush_row = [&]() {
-        float *o = a.out + row * a.ldo;
-        whole_sum();
+    auto store_row = [&](int64_t r, float (&sum)[NV][VW]) {
+        float *o = a.out + r * a.ldo;
         if (a.wdim > a.dim) {                                   // row padding: whatever was gathered there is dropped
 #pragma unroll
             for (int k = 0; k < VW; ++k)
-                if (((NV - 1) * kWave + lane) * VW + k >= a.dim) acc[NV - 1][k] = 0.0f;
+                if (((NV - 1) * kWave + lane) * VW + k >= a.dim) sum[NV - 1][k] = 0.0f;
         }
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            if (v < NV - 1 || last_ok) store_vec_streaming<VW>(o + (v * kWave + lane) * VW, acc[v]);
+        for (int v = 0; v < NV; ++v)
+            if (v < NV - 1 || last_ok) store_vec_streaming<VW>(o + (v * kWave + lane) * VW, sum[v]);
+    };
+    auto to_lds = [&](float (&to)[JOINS ? VW * NV : 1][kWave]) {
+        if constexpr (JOINS)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int k = 0; k < VW; ++k) to[v * VW + k][lane] = acc[v][k];
+    };
+    auto flush_row = [&]() {
+        whole_sum();
+        // other waves may have parts of the first one
+        if (JOINS && wave > 0 && row == i0) to_lds(first[wave]);
+        else store_row(row, acc);
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
 #pragma unroll
             for (int k = 0; k < VW; ++k) acc[v][k] = 0.0f;
-        }
         dirty = false;
         ++row;
         if (row - row_blk == kWave) {
@@ -313,20 +338,53 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
     while (row < i1) flush_row();                           // rows that end at the piece's last entry, empty rows
 
     // what is left belongs to a row that continues in the next piece
-    if (dirty && row < a.n_rows) {
-        float *cslot = a.carry + (int64_t)item * a.carry_ld;
-        whole_sum();
+    const int32_t left = dirty && row < a.n_rows ? (int32_t)row : kNoRow;
+    if (left != kNoRow) whole_sum();
+    auto store_carry = [&](int32_t slot) {
+        float *cslot = a.carry + (int64_t)slot * a.carry_ld;
 #pragma unroll
         for (int v = 0; v < NV; ++v)
             if (v < NV - 1 || last_ok) store_vec<VW>(cslot + (v * kWave + lane) * VW, acc[v]);
-        if (lane == 0) a.carry_row[item] = (int32_t)row;
+    };
+    if constexpr (!JOINS) {
+        if (left != kNoRow) store_carry(item);
+        if (lane == 0) a.carry_row[item] = left;
     } else {
-        if (lane == 0) a.carry_row[item] = kNoRow;
+        if (left != kNoRow) to_lds(open[wave]);
+        if (lane == 0) open_row[wave] = left;
+        __syncthreads();
+        // acc = the parts of row r that the waves before `end` leave open, in order
+        auto add_open = [&](int32_t r, int end) {
+            int begin = end;
+            while (begin > 0 && uniform_i32(open_row[begin - 1]) == r) --begin;
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int k = 0; k < VW; ++k) {
+                    acc[v][k] = 0.0f;
+                    for (int w = begin; w < end; ++w) acc[v][k] += open[w][v * VW + k][lane];
+                }
+        };
+        if (wave > 0 && i1 > i0) {
+            add_open((int32_t)i0, wave);
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int k = 0; k < VW; ++k) acc[v][k] += first[wave][v * VW + k][lane];
+            store_row(i0, acc);
+        }
+        if (wave == kWavesPerBlock - 1) {                   // the path goes on in the next workgroup
+            if (left != kNoRow) {
+                add_open(left, kWavesPerBlock);
+                store_carry((int32_t)blockIdx.x);
+            }
+            if (lane == 0) a.carry_row[blockIdx.x] = left;
+        }
     }
 }
 
-// Adds the carries of every split row to the part stored by the piece that finished the row, in piece order.
-// One wave per piece; only the wave of a row's first carry does the work.  Lanes own the same column slices
+// Adds the carries of every split row to the part stored by the piece that finished the row, in order.
+// One wave per carry; only the wave of a row's first carry does the work.  Lanes own the same column slices
 // as in the main kernel, and several carries are in flight at once.
 template <int VW, int NV>
 __global__ __launch_bounds__(kBlock) void spmm_carry_kernel(const SpmmArgs a)
@@ -438,7 +496,9 @@ hipError_t launch_merge(const SpmmArgs &a, bool chains, hipStream_t st)
     hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, st, a);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL((spmm_carry_kernel<VW, NV>), grid, dim3(kBlock), 0, st, a);
+    SpmmArgs carries = a;
+    if (VW * NV <= kJoinFloats) carries.n_items = (int32_t)grid.x;      // one of a workgroup
+    hipLaunchKernelGGL((spmm_carry_kernel<VW, NV>), dim3((carries.n_items + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock), 0, st, carries);
     return hipGetLastError();
 }
 

@@ -548,6 +548,23 @@ def test_spmm_longer_pieces(oracle, dim, n_rows):
     assert np.array_equal(plain.view(np.uint32), fused.view(np.uint32))
 
 
+@pytest.mark.parametrize("dim,ld", [(5, 5), (301, 301), (512, 513), (513, 513), (512, 514), (514, 514), (512, 512), (516, 516), (608, 608)])
+def test_spmm_joined_pieces(oracle, dim, ld):
+    """Pieces of 32 steps, four to a workgroup: rows that end with a piece and with a workgroup, that begin and end in any two of its waves, that
+    fill several workgroups, empty ones between them; widths whose parts meet in LDS and (514, 516, 608 columns) leave a carry each."""
+    _say(f"spmm joined pieces dim={dim} ld={ld}")
+    rng = np.random.default_rng(9100 + dim + ld)
+    n_cols = 1_500
+    degs = np.concatenate([[31, 31, 63, 127, 126, 0, 0, 128, 1_400, 5, 30, 33, 700, 0, 1], rng.integers(0, 90, 200), [0] * 140, rng.integers(0, 6, 300),
+                           [95, 32, 64, 1_023, 0, 0, 3, 129]])
+    rowptr, col, val = _random_graph(rng, degs.size, n_cols, degs)
+    H = np.full((n_cols, ld), np.nan, dtype=np.float32)
+    H[:, :dim] = rng.standard_normal((n_cols, dim))
+    for rb, re in ((0, degs.size), (8, 9), (3, degs.size - 2)):
+        once = _check_spmm(oracle, rowptr, col, val, rb, re, H, dim, ldo=ld)
+        assert np.array_equal(once.view(np.uint32), _gpu_spmm(rowptr, col, val, rb, re, H, dim, ldo=ld).view(np.uint32))
+
+
 @pytest.mark.parametrize("dim,ldh", [(128, 128), (602, 608), (602, 602), (300, 300), (7, 7), (1, 1), (66, 66),
                                      (130, 132), (250, 256), (2049, 2080), (2304, 2304), (4100, 4100), (515, 515)])
 def test_spmm_packed_rows(oracle, dim, ldh):
