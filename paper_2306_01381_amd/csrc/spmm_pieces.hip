@@ -35,7 +35,6 @@ constexpr int kPart = 256;                                  // no sum runs longe
 constexpr int32_t kJoined = -2, kNowhere = INT32_MIN;       // a piece's partial; a destination
 constexpr int32_t kMoved = INT32_MIN + 1;                   // in place of a destination: rowptr is no longer what the plan was made from
 constexpr int32_t kNoEnd = 0x10000;                         // lies after every step of a piece
-constexpr int kPackedLines = 4;                             // per slice where rows may be packed: their codes share lines
 constexpr unsigned kIdleLds[2] = {6144, 24576};             // of a workgroup, beside its 26 KB: no more than 16 or 12 waves on a CU
 static_assert(kEnds < kWave - 1, "a lane per end, and one that has none");
 
@@ -521,18 +520,31 @@ using PieceKernel = void (*)(const PieceArgs);
 template <bool PACKED, bool ROWS, int WAVES, int ENTRIES>
 PieceKernel kernel_of(int32_t lines_per_slice)
 {
-    if constexpr (PACKED) return spmm_pieces_kernel<kPackedLines, 2, true, ROWS, WAVES, ENTRIES>;
+    if constexpr (PACKED && ENTRIES == kEntries)
+        if (lines_per_slice == 2) return spmm_pieces_kernel<2, 4, true, ROWS, WAVES, ENTRIES>;
+    if constexpr (PACKED) return spmm_pieces_kernel<4, 2, true, ROWS, WAVES, ENTRIES>;
     else return lines_per_slice == 1   ? spmm_pieces_kernel<1, 8, false, ROWS, WAVES, ENTRIES>
                 : lines_per_slice == 2 ? spmm_pieces_kernel<2, 4, false, ROWS, WAVES, ENTRIES>
                                        : spmm_pieces_kernel<4, 2, false, ROWS, WAVES, ENTRIES>;
 }
 
 template <bool PACKED, bool ROWS>
-PieceKernel kernel_of(const adaqp_spmm_pieces *p)
+PieceKernel kernel_of(const adaqp_spmm_pieces *p, int32_t lines_per_slice)
 {
-    if (p->waves == kJoinWaves) return kernel_of<PACKED, ROWS, kJoinWaves, kFewEntries>(p->lines_per_slice);
-    return p->entries == kFewEntries ? kernel_of<PACKED, ROWS, kWavesPerBlock, kFewEntries>(p->lines_per_slice)
-                                     : kernel_of<PACKED, ROWS, kWavesPerBlock, kEntries>(p->lines_per_slice);
+    if (p->waves == kJoinWaves) return kernel_of<PACKED, ROWS, kJoinWaves, kFewEntries>(lines_per_slice);
+    return p->entries == kFewEntries ? kernel_of<PACKED, ROWS, kWavesPerBlock, kFewEntries>(lines_per_slice)
+                                     : kernel_of<PACKED, ROWS, kWavesPerBlock, kEntries>(lines_per_slice);
+}
+
+// Lines per slice where rows may be packed.  Their codes share lines, and each slice looks up the places again: four, but two where the plan
+// says two and rows are shorter than 100 entries (four, two: 27 000 rows of 6 entries, 528 columns 94.7, 73.5 us; 12 000 of 70, 264 columns 117,
+// 102; 42 000 of 11, 372 columns 129, 107; but 115 entries, 200 columns 146, 155; 280 entries, 512 columns 281, 298; in small pieces 0.94
+// to 1.03; where the plan says one 0.89 to 1.12, four 0.89 to 1.04) and whole slices of four are not waves enough (157 000 rows, 240
+// columns, 4 600 waves: 175, 186).  The same bits either way.
+int32_t packed_lines(const adaqp_spmm_pieces *p, const PieceArgs &a, int64_t lines)
+{
+    const bool fills = lines % 4 == 0 && a.n_pieces * (lines / 4) >= kUnderWay;
+    return p->lines_per_slice == 2 && p->entries == kEntries && lines > 4 && !fills && a.n_walked < 100 * (int64_t)a.n_seg ? 2 : 4;
 }
 
 // LDS that keeps waves away.  Lines that are asked for wait in the order of the asking in the L1, which has room for 256; where some of them miss
@@ -560,8 +572,9 @@ int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
     a.ldp = ((int64_t)a.dim + kLine - 1) / kLine * kLine;
     a.n_blocks = (a.n_pieces + p->waves - 1) / p->waves;
     const bool packed = a.p.row != nullptr;
-    const int32_t per_slice = packed ? kPackedLines : p->lines_per_slice;
-    const int64_t most_lines = pieces_lines(a.n_blocks, p->waves, per_slice), lines = a.ldp / kLine;
+    const int64_t lines = a.ldp / kLine;
+    const int32_t per_slice = packed ? packed_lines(p, a, lines) : p->lines_per_slice;
+    const int64_t most_lines = pieces_lines(a.n_blocks, p->waves, per_slice);
     for (int64_t l0 = 0; l0 < lines; l0 += most_lines) {
         PieceArgs s = a;
         s.lines = (int32_t)std::min(lines - l0, most_lines);
@@ -574,7 +587,7 @@ int launch_pieces(const adaqp_spmm_pieces *p, PieceArgs a, hipStream_t st)
         if (s.partial) s.partial += l0 * kLine;
         s.copy_blocks = packed && l0 == 0 ? (s.copies.blocks() + kXcds - 1) / kXcds * kXcds : 0;
         const dim3 grid((unsigned)(SliceTasks(s.lines, per_slice, s.n_blocks, packed).most_per_xcd() * kXcds) + s.copy_blocks);
-        const PieceKernel kernel = packed ? kernel_of<true, true>(p) : a.of_rows ? kernel_of<false, true>(p) : kernel_of<false, false>(p);
+        const PieceKernel kernel = packed ? kernel_of<true, true>(p, per_slice) : a.of_rows ? kernel_of<false, true>(p, per_slice) : kernel_of<false, false>(p, per_slice);
         hipLaunchKernelGGL(kernel, grid, dim3(p->waves * kWave), idle_lds(p, s, per_slice, packed), st, s);
         ADAQP_HIP_TRY(hipGetLastError());
     }
