@@ -36,6 +36,7 @@ constexpr int32_t kJoined = -2, kNowhere = INT32_MIN;       // a piece's partial
 constexpr int32_t kMoved = INT32_MIN + 1;                   // in place of a destination: rowptr is no longer what the plan was made from
 constexpr int32_t kNoEnd = 0x10000;                         // lies after every step of a piece
 constexpr unsigned kIdleLds[2] = {6144, 24576};             // of a workgroup, beside its 26 KB: no more than 16 or 12 waves on a CU
+constexpr unsigned kIdleLdsPacked = 12288;                  // beside 52 KB: 8 instead of 12
 static_assert(kEnds < kWave - 1, "a lane per end, and one that has none");
 
 // A sum to its place.  Lanes without a column of their own store outside the row's buffer: no branch.
@@ -57,6 +58,29 @@ __device__ __forceinline__ void store_row(const PieceArgs &a, int32_t dest, int3
 {
     const bool part = dest >= 0, known = part ? dest < a.n_partials : -1 - dest < a.n_rows;
     store_row<VPL>(a, part ? a.partial + (int64_t)dest * a.ldp : a.out + (int64_t)(-1 - dest) * a.ldo, known, first_line, lane, sum);
+}
+
+// off of an entry that may be packed: rotated by two, so that the width of a packed row is at the top and the row's 32-bit word in the others.
+__device__ __forceinline__ uint32_t packed_width(uint32_t off) { return off >> 30; }
+
+// unpack_codes of a lane's columns in VPL lines: a line's codes fill whole words at each width, so they begin at the same bit in all of
+// them, and v_bfe_u32 takes that modulo 32 by itself.  Where most rows come out of the L2 the instructions count: with these places, one shift
+// per entry and the words asked for before the rows, 24 000 rows of 17 entries, 66 columns, packed, the step 30.1 -> 28.4 us; 7 700 of 156, 316
+// columns 131 -> 109; 17 500 of 75, 96 columns 66 -> 54; 150 such steps 1.055 times as fast.
+template <int VPL>
+__device__ __forceinline__ void unpack_lines(const Entry<true> &en, const uint32_t (&words)[VPL], uint32_t col, float4_t (&x)[VPL])
+{
+    const uint32_t w = packed_width(en.off);
+    const uint32_t b = 1u << w, at = col << w;
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) {
+        if (w == 0) continue;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float scaled = (float)__builtin_amdgcn_ubfe(words[v], at + k * b, b) * en.s;
+            x[v][k] = scaled + en.z;
+        }
+    }
 }
 
 // stage_entries where rows may be packed, whose places have been looked up beforehand: a load per entry and one of (Z, S) instead of four, and
@@ -85,7 +109,8 @@ __device__ __forceinline__ void stage_packed(int4_t (&st_col)[LOADS], const floa
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const uint32_t row = valid(k, q) ? (uint32_t)st_col[k][q] * pitch : kOutside;
-            stage[(k * kWave + lane) * 4 + q] = Entry<true>{packed[q] ? at[k][q].x : row, valid(k, q) ? st_val[k][q] : 0.0f, zs[q].x, zs[q].y};
+            stage[(k * kWave + lane) * 4 + q] = Entry<true>{__builtin_rotateright32(packed[q] ? at[k][q].x : row, 2),
+                                                            valid(k, q) ? st_val[k][q] : 0.0f, zs[q].x, zs[q].y};
         }
     }
 }
@@ -269,17 +294,26 @@ __device__ __forceinline__ int32_t walk_piece(const PieceArgs &a, const int32_t 
     uint32_t words[AHEAD][VPL];                             // of a packed row: the word that holds the lane's four codes
     Entry<PACKED> in_flight[AHEAD];
     const uint32_t lane_off = gl * 16;
-    auto packed_col = [&](int v) ADAQP_INLINE { return (uint32_t)(a.p.col0 + (first_line + v) * kLine + gl * 4); };
+    const uint32_t packed_col = (uint32_t)(a.p.col0 + first_line * kLine + gl * 4);     // of the lane's codes in the first line
+    const uint32_t last_col = min(packed_col + (VPL - 1) * kLine, (uint32_t)a.p.full_dim - 1);
     auto fetch = [&](auto tag, const Entry<PACKED> &en) ADAQP_INLINE {
         constexpr int U = decltype(tag)::value;
         in_flight[U] = en;
-        const uint32_t width = PACKED ? en.off & 3u : 0u;
+        const uint32_t width = PACKED ? packed_width(en.off) : 0u;
+        const uint32_t off = width != 0 ? kOutside : (PACKED ? en.off << 2 : en.off) + lane_off;
+        if constexpr (PACKED) {
+            // The word of the lane's four codes, and as far behind it the one of each line.
+            const uint32_t first = width != 0 ? (en.off + (packed_col << width >> 5)) << 2 : kOutside;
+            const uint32_t last = width != 0 ? (en.off + (last_col << width >> 5)) << 2 : kOutside;
 #pragma unroll
-        for (int v = 0; v < VPL; ++v) {
-            const uint32_t off = width != 0 ? kOutside : en.off + lane_off + v * kLine * 4;
-            h[U][v] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, 0));
-            if constexpr (PACKED) words[U][v] = fetch_codes(packed_rows, en.off, packed_col(v), a.p.full_dim);
+            for (int v = 0; v < VPL; ++v) {
+                const uint32_t at = v + 1 < VPL ? first + ((uint32_t)v * (kLine / 8) << width) : last;
+                words[U][v] = __builtin_amdgcn_raw_buffer_load_b32(packed_rows, (int)at, 0, 0);
+            }
         }
+#pragma unroll
+        for (int v = 0; v < VPL; ++v)
+            h[U][v] = __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)(off + v * kLine * 4), 0, 0));
     };
     unroll<0, AHEAD>([&](auto tag) ADAQP_INLINE {
         constexpr int U = decltype(tag)::value;
@@ -339,10 +373,8 @@ __device__ __forceinline__ int32_t walk_piece(const PieceArgs &a, const int32_t 
             float4_t x[VPL];
             float val = in_flight[U].val;
 #pragma unroll
-            for (int v = 0; v < VPL; ++v) {
-                x[v] = h[U][v];
-                if constexpr (PACKED) x[v] = unpack_codes(in_flight[U], words[U][v], packed_col(v), x[v]);
-            }
+            for (int v = 0; v < VPL; ++v) x[v] = h[U][v];
+            if constexpr (PACKED) unpack_lines<VPL>(in_flight[U], words[U], packed_col, x);
             if (marks[0] & (1u << U)) {
                 // the groups from the last end to this one belong to the segment that ends here
                 const int32_t at = (t * AHEAD + U) * kStep;
@@ -552,11 +584,14 @@ int32_t packed_lines(const adaqp_spmm_pieces *p, const PieceArgs &a, int64_t lin
 // more: 12 (16.3 M entries, 376 000 rows, 256 columns, the step 875 -> 858 us; 4 M, 50 000 rows, 128 columns 110.7 -> 107.6; 15.3 M, 223 000
 // rows, 320 columns 935 -> 899), but all that fit where rows are shorter (with 12, 17 entries 0.94, 3 entries 0.93), where there are
 // pieces for a turn or two only (6 144, two lines 0.94-0.97; four lines 0.97 with 330 entries each, 1.02 with 600) and for one line per
-// slice (0.83).
+// slice (0.83).  Packed rows, whose workgroups have 52 KB: 8 instead of 12 where slices have three lines or more and there are
+// 9 000 waves (28 000 rows, 7.5 M entries, 387 columns 635 -> 565 us; 70 000, 7.7 M, 96 columns 280 -> 250; 130 000, 17.9 M, 314 columns 1 735 ->
+// 1 617; with fewer waves 0.81 to 1.02, with one or two lines 0.84 to 0.99).
 unsigned idle_lds(const adaqp_spmm_pieces *p, const PieceArgs &a, int32_t per_slice, bool packed)
 {
-    if (p->entries != kEntries || per_slice == 1 || packed) return 0;
+    if (p->entries != kEntries || per_slice == 1) return 0;
     const int64_t waves = (int64_t)a.n_pieces * ((a.lines + per_slice - 1) / per_slice);
+    if (packed) return per_slice == 4 && a.lines >= 3 && waves >= 9000 ? kIdleLdsPacked : 0;
     const bool turns = waves >= 9000 || (per_slice == 4 && a.n_walked >= 550 * (int64_t)a.n_pieces);
     return kIdleLds[a.of_rows && turns && a.n_walked >= 40 * (int64_t)a.n_seg];
 }

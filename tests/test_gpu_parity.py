@@ -1623,6 +1623,22 @@ def test_layer_step_in_planned_pieces(oracle, monkeypatch, rows, mean, dim, shap
             assert np.array_equal(np.isnan(got), np.isnan(kept)) and np.array_equal(got[~touched].view(np.uint32), kept[~touched].view(np.uint32))
 
 
+@pytest.mark.parametrize("dim", [641, 768])
+def test_layer_step_in_planned_pieces_of_many_waves(monkeypatch, dim):
+    """Enough waves for the launch of packed rows that keeps a third of them away: the bits of the step that reads what was received from feat."""
+    _say(f"layer step in many pieces, dim={dim}")
+    monkeypatch.setattr(B, "adaqp_spmm_pieces_rule", lambda *args, **options: (1, -np.inf))
+    p, want = make_partition(replace(CONFIGS["c0"], n_local=15_000, n_halo=3_000, n_send=3_000, mean_degree=130.0, dim=dim)), None
+    for fused in (False, True):
+        L = LayerStep(p, DEV, seed=5, tiled=False, fused_receive=fused)
+        c = L.pieces_both.c
+        assert c.entries == 768 and c.n_pieces * ((dim + 127) // 128) >= 9_000 and c.lines_per_slice == 1
+        L.run(B.CHAIN)
+        L.synchronize()
+        want = L.out.clone() if want is None else want
+        assert torch.equal(L.out.view(torch.int32), want.view(torch.int32))
+
+
 @pytest.mark.parametrize("rows,mean,dim,shape", [(2_000, 10, 128, (8, 256)), (2_000, 10, 40, (8, 256)), (24_000, 18, 66, (4, 256)),
                                                  (24_000, 60, 150, (4, 768)), (24_000, 100, 40, (4, 768))])
 @pytest.mark.parametrize("kind", ["forward", "fused", "backward"])
