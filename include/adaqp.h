@@ -220,8 +220,8 @@ int adaqp_spmm_csr(const int64_t *rowptr_dev, const int32_t *col_dev, const floa
  *          ADAQP_SPMM_NOALLOC_SCRATCH_BYTES, else ESIZE and nothing is launched.
  *   Every call on a GPU uses that GPU's one buffer: two calls that may run at the same time on one GPU (two
  *   streams, two threads) race on it - order them, or give one of them adaqp_spmm_csr with its own workspace.
- *   The buffer keeps the last call's contents; nothing in it needs to start at zero (every piece writes its
- *   carry slot's row number before the fix-up kernel reads it).
+ *   The buffer keeps the last call's contents; nothing in it needs to start at zero (the row number of
+ *   each carry slot that the fix-up kernel reads is written before).
  * Errors: as adaqp_spmm_csr. */
 #define ADAQP_SPMM_NOALLOC_SCRATCH_BYTES (64 << 20)
 int adaqp_spmm_csr_noalloc(const int64_t *rowptr_dev, const int32_t *col_dev, const float *val_dev, int64_t nnz,
