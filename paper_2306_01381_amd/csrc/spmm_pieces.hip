@@ -569,10 +569,10 @@ PieceKernel kernel_of(const adaqp_spmm_pieces *p, int32_t lines_per_slice)
 }
 
 // Lines per slice where rows may be packed.  Their codes share lines, and each slice looks up the places again: four, but two where the plan
-// says two and rows are shorter than 100 entries (four, two: 27 000 rows of 6 entries, 528 columns 94.7, 73.5 us; 12 000 of 70, 264 columns 117,
-// 102; 42 000 of 11, 372 columns 129, 107; but 115 entries, 200 columns 146, 155; 280 entries, 512 columns 281, 298; in small pieces 0.94
-// to 1.03; where the plan says one 0.89 to 1.12, four 0.89 to 1.04) and whole slices of four are not waves enough (157 000 rows, 240
-// columns, 4 600 waves: 175, 186).  The same bits either way.
+// says two and rows are shorter than 100 entries (four, two: 10 000 rows of 56 entries, 414 columns 88.7, 80.7 us; 15 000 of 47, 160 columns 56.6,
+// 53.3; 27 000 of 19, 336 columns 90.7, 85.6; 11 000 of 67, 336 columns 97.9, 100.2; but 394 entries, 441 columns 121, 130; 298 entries, 208 columns
+// 191, 197) and whole slices of four are not waves enough (157 000 rows, 240 columns, 4 600 waves: 175, 186).  In small pieces 0.94 to 1.03 with two;
+// where the plan says one 0.89 to 1.12, four 0.89 to 1.04.  The same bits either way.
 int32_t packed_lines(const adaqp_spmm_pieces *p, const PieceArgs &a, int64_t lines)
 {
     const bool fills = lines % 4 == 0 && a.n_pieces * (lines / 4) >= kUnderWay;
