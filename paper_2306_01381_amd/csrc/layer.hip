@@ -349,15 +349,31 @@ int range_bytes(const adaqp_layer_desc *d, const adaqp_spmm_pieces *pieces, int6
     return ADAQP_OK;
 }
 
+// Whether the memory that is sent is no part of b.
+bool send_buffers_apart(const adaqp_layer_desc *d, const void *b, int64_t b_bytes)
+{
+    auto apart = [&](const void *a, int64_t a_bytes) {
+        const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+        return !a || !b || x + (uint64_t)a_bytes <= y || y + (uint64_t)b_bytes <= x;
+    };
+    return apart(d->packed_dev, d->packed_bytes) && apart(d->params_dev, d->n_send * 2 * (int64_t)sizeof(float));
+}
+
 // CHAIN has nothing to overlap the transfer with, and the copy that stands in for it is a launch of 2.5 to 5 us that leaves the GPU part
 // empty.  There the launch that receives takes the bytes from where the copy takes them, and copies them beside; the table of received
 // rows is then filled in the quantisation's launch.  Whole steps: 2 000 rows, 128 columns 19.4 -> 15.4 us (the host's time for its
 // launches), 24 000 rows, 66 columns, packed 32.7 -> 30.3, 179 000 rows, 300 columns 361 -> 355, 30 000 nodes backward 106 -> 104.
-// Buffers that the receiving calls refuse go the other way, and are refused there.
+// Buffers that the receiving calls refuse go the other way, and are refused there.  So do send buffers in memory that the launch writes, which
+// a caller may use again once the messages are on their way: rows of feat that are received, out, a workspace.
 bool receives_beside(const adaqp_layer_desc *d)
 {
-    return d->schedule == ADAQP_CHAIN && d->n_send > 0 && d->n_send < kBesideMessages && d->packed_bytes >= 4 && aligned_to(d->packed_dev, 4) &&
-           aligned_to(d->params_dev, 8) && aligned_to(d->recv_packed_dev, 4) && aligned_to(d->recv_params_dev, 8);
+    if (!(d->schedule == ADAQP_CHAIN && d->n_send > 0 && d->n_send < kBesideMessages && d->packed_bytes >= 4 && aligned_to(d->packed_dev, 4) &&
+          aligned_to(d->params_dev, 8) && aligned_to(d->recv_packed_dev, 4) && aligned_to(d->recv_params_dev, 8)))
+        return false;
+    return send_buffers_apart(d, d->feat_dev, d->n_feat_rows * d->ld * (int64_t)sizeof(float)) &&
+           send_buffers_apart(d, d->out_dev, std::max(d->overlap_end, d->dependent_end) * d->ldo * (int64_t)sizeof(float)) &&
+           send_buffers_apart(d, d->workspace_overlap_dev, d->workspace_overlap_bytes) &&
+           send_buffers_apart(d, d->workspace_dependent_dev, d->workspace_dependent_bytes);
 }
 
 // Rows [rb, re) as planned, or along the merge path; fused: received rows are read from the receive buffer.

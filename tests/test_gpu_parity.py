@@ -1985,6 +1985,36 @@ def test_layer_step_chain_copies_beside_the_receive(kind, dim, extra, offset):
         assert not bool(torch.isnan(b).any()) and float((a - b).norm()) <= 1e-6 * float(a.norm())
 
 
+@pytest.mark.parametrize("kind,where", [("forward", "feat"), ("forward", "out"), ("fused", "out"), ("fused", "workspace"), ("backward", "workspace")])
+def test_layer_step_chain_with_send_buffers_in_memory_that_is_used_again(kind, where):
+    """Nothing reads the send buffers once the messages are copied: they may lie in rows of feat that are received, in out or in a workspace."""
+    _say(f"chain, {kind}, send buffers in {where}")
+    p = make_partition(replace(CONFIGS["c0"], n_local=6_000, n_halo=900, n_send=900, mean_degree=60.0, dim=70) if kind != "backward" else
+                       replace(CONFIGS["c4"], n_local=2000, n_halo=1800, n_send=1500, mean_degree=9.0, dim=128))
+    left = []
+    for shared in (False, True):
+        L = LayerStep(p, DEV, seed=5, fused_receive=kind == "fused")
+        d = L.desc(B.CHAIN)
+        assert d.pieces_both.n_pieces > 0
+        if shared:
+            received = np.sort(p.halo_idx)
+            assert kind == "backward" or np.array_equal(received, np.arange(p.n_rows, p.n_rows + received.size))
+            memory = {"feat": L.feat[p.n_rows if kind != "backward" else 0:], "out": L.out, "workspace": L.ws_overlap}[where]
+            assert d.workspace_overlap_bytes >= d.workspace_dependent_bytes
+            room = memory.numel() * memory.element_size()
+            params_at = -(-d.packed_bytes // 256) * 256
+            assert params_at + 8 * d.n_send <= room
+            d.packed_dev = memory.data_ptr()
+            d.params_dev = memory.data_ptr() + params_at
+        L.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        B.adaqp_layer_step(d)
+        L.synchronize()
+        left.append([t.contiguous().view(torch.int32).clone() for t in (L.out, L.feat, L.recv_params, L.beta)] + [L.recv_packed.clone()])
+    for a, b in zip(*left):
+        assert torch.equal(a, b)
+
+
 def test_mean_aggregator_layer_step(oracle):
     """GraphSAGE-style mean coefficients (1 / row degree) through the same step."""
     p = make_partition(replace(CONFIGS["c0"], aggregator="mean"))
