@@ -13,8 +13,37 @@ namespace adaqp {
 
 template <typename Index> struct KeyedIndex { uint32_t key; Index index; };
 
+// The passes of sort_by_key.  A loop over a number of digits that is not known to the compiler takes up to 1.5 times as long.
+template <int DIGITS, typename Index, typename Count>
+void sort_by_digits(KeyedIndex<Index> *items, KeyedIndex<Index> *other, size_t n, uint32_t lo, int bits, Count *counts)
+{
+    const uint32_t mask = (1u << bits) - 1;
+    for (size_t i = 0; i < n; ++i) {
+        const uint32_t key = items[i].key - lo;
+#pragma unroll
+        for (int d = 0; d < DIGITS; ++d) ++counts[((size_t)d << bits) + ((key >> (d * bits)) & mask)];
+    }
+    KeyedIndex<Index> *from = items, *to = other;
+#pragma unroll
+    for (int d = 0; d < DIGITS; ++d) {
+        Count *at = counts + ((size_t)d << bits);
+        const int shift = d * bits;
+        if (at[((items[0].key - lo) >> shift) & mask] == n) continue;
+        Count sum = 0;
+        for (uint32_t b = 0; b <= mask; ++b) {
+            const Count c = at[b];
+            at[b] = sum;
+            sum += c;
+        }
+        for (size_t i = 0; i < n; ++i) to[at[((from[i].key - lo) >> shift) & mask]++] = from[i];
+        std::swap(from, to);
+    }
+    if (from != items) memcpy(items, from, n * sizeof(*items));
+}
+
 // Sorts by ascending key, equal keys in their present order: least significant digit first, in as few digits of up to eleven bits as the keys'
-// range needs, all of about the same width.  A comparison sort through an index spends its time on mispredicted branches and
+// range needs, all of about the same width, and digits in which all keys agree left out (100 000 floats that came from 16 bits: 1.05 -> 0.83
+// ms).  A comparison sort through an index spends its time on mispredicted branches and
 // scattered reads; digits no wider than needed leave a cache line per value of a digit in the first-level cache (100 000 floats of 27 bits,
 // three digits of nine bits instead of eleven: 0.95 of the time).  `other`: scratch of n items.
 template <typename Index>
@@ -36,30 +65,14 @@ void sort_by_key(KeyedIndex<Index> *items, KeyedIndex<Index> *other, size_t n)
     const int digits = (range_bits + kMostBits - 1) / kMostBits;
     if (digits == 0) return;
     const int bits = (range_bits + digits - 1) / digits;
-    const uint32_t mask = (1u << bits) - 1;
-    auto passes = [&](auto *counts) {
-        for (size_t i = 0; i < n; ++i) {
-            const uint32_t key = items[i].key - lo;
-            for (int d = 0; d < digits; ++d) ++counts[((size_t)d << bits) + ((key >> (d * bits)) & mask)];
-        }
-        KeyedIndex<Index> *from = items, *to = other;
-        for (int d = 0; d < digits; ++d) {
-            auto *at = counts + ((size_t)d << bits);
-            size_t sum = 0;
-            for (uint32_t b = 0; b <= mask; ++b) {
-                const size_t c = at[b];
-                at[b] = sum;
-                sum += c;
-            }
-            for (size_t i = 0; i < n; ++i) to[at[((from[i].key - lo) >> (d * bits)) & mask]++] = from[i];
-            std::swap(from, to);
-        }
-        if (from != items) memcpy(items, from, n * sizeof(*items));
+    auto passes = [&](auto count) {
+        std::vector<decltype(count)> counts((size_t)digits << bits);
+        if (digits == 1) sort_by_digits<1>(items, other, n, lo, bits, counts.data());
+        else if (digits == 2) sort_by_digits<2>(items, other, n, lo, bits, counts.data());
+        else sort_by_digits<3>(items, other, n, lo, bits, counts.data());
     };
-    std::vector<uint32_t> count(n <= UINT32_MAX ? (size_t)digits << bits : 0);
-    std::vector<uint64_t> count64(n <= UINT32_MAX ? 0 : (size_t)digits << bits);
-    if (n <= UINT32_MAX) passes(count.data());
-    else passes(count64.data());
+    if (n <= UINT32_MAX) passes(uint32_t());
+    else passes(uint64_t());
 }
 
 // order_out[k] = position of the k-th smallest value, ties by position (n up to 2^31 - 1).
