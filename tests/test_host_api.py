@@ -248,6 +248,21 @@ def test_plan_send(n, peers, halo):
                 B.adaqp_plan_send(37, wrong.get("bits", bits), wrong.get("peer", peer), peers, send, rows)
 
 
+@pytest.mark.parametrize("sizes", [[63, 64, 65, 0, 66, 67, 1, 0, 0, 255, 256, 257], [0, 0, 64], [1] * 300, [128, 0]])
+def test_plan_layout_of_small_and_large_peers(sizes):
+    """Peers whose slots are placed in one part and in four, peers without any, and ends that are looked for near the beginning."""
+    n_peers = len(sizes)
+    peer = np.repeat(np.arange(n_peers, dtype=np.int32), sizes)
+    rng = np.random.default_rng(peer.size)
+    bits = rng.choice(np.array([2, 4, 8], np.uint8), peer.size)
+    perm, off, ptr = B.adaqp_plan_layout(19, bits, peer, n_peers)
+    want = np.lexsort((np.arange(peer.size), bits, peer))
+    stride = np.array([B.lib().adaqp_row_stride(19, int(b)) for b in bits[want]], dtype=np.int64)
+    assert np.array_equal(perm, want) and np.array_equal(off, np.cumsum(stride) - stride)
+    ends = np.concatenate([[0], np.cumsum(stride)])
+    assert np.array_equal(ptr, ends[np.concatenate([[0], np.cumsum(sizes)])])
+
+
 def test_plan_recv_segments():
     dst = np.array([7, 3, 7, 9, 3, 3], dtype=np.int32)
     order, seg_ptr = B.adaqp_plan_recv_segments(dst)
