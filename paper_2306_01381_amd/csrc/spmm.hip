@@ -10,8 +10,8 @@
 //   * row ends are staged the same way, 64 rows at a time;
 //   * U entries are in flight at once (U * NV vector loads per lane) before the first is consumed;
 //   * a row that ends inside the piece is stored directly; what a piece has accumulated for a row that
-//     continues into the next piece meets the rest of the row in LDS, where that is a piece of the same workgroup; what a workgroup has of
-//     a row that continues in the next one goes to a carry slot in the workspace.
+//     continues into the next piece goes to a carry slot in the workspace, or (merge_joins, spmm_rules.hpp) meets the rest of the row in LDS,
+//     where that is a piece of the same workgroup, and a workgroup has a carry slot for the row that continues in the next one.
 // A second, tiny kernel adds the carries of each split row in order.  The summation order therefore
 // depends only on the launch geometry: results are bit-identical from run to run and across schedules.
 //
@@ -121,16 +121,19 @@ constexpr int32_t kFar = 0x7FFFFFFF;
 // JOINS: nearly every piece leaves a part of a row to the next one.  As long as a row's parts and ends lie in one workgroup they are added up
 // in its LDS, and there is a carry slot per workgroup instead of one per piece (send, receive and sums of 60 000 rows, 1 M entries, 301
 // columns 213 -> 201 us, of it the carries 17 -> 7; 150 000 rows, 1.2 M, 472 columns 440 -> 404; error against 64 bits 0.98 times, never more,
-// over 14 graphs).  The LDS of wider rows would keep other workgroups away: a carry slot per piece.
+// over 14 graphs).  Parts are read whole and all open rows at once: column by column, with a wait for each, small calls took 1.04 times as long
+// (462 calls 1.02).  Rows of more floats per lane leave a carry per piece.  Joining up to 16 would keep no workgroup away (registers allow
+// fewer of them than 33 KB of LDS each) and was faster where it was timed, 602 columns 368 -> 346 us, 1 000 columns 387 -> 367.
 constexpr int kJoinFloats = 8;              // of a lane, per row: 16 KB for a workgroup's parts and first rows
 
-template <int VW, int NV, int U, bool PACKED, bool CHAINS>
+template <int VW, int NV, int U, bool PACKED, bool CHAINS, bool JOINS>
 __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
 {
-    constexpr bool JOINS = VW * NV <= kJoinFloats;
-    __shared__ float open[JOINS ? kWavesPerBlock : 1][JOINS ? VW * NV : 1][kWave];      // what a piece has of the row that it leaves open
-    __shared__ float first[JOINS ? kWavesPerBlock : 1][JOINS ? VW * NV : 1][kWave];     // and of the first row that ends in it
-    __shared__ int32_t open_row[kWavesPerBlock];
+    static_assert(!JOINS || VW * NV <= kJoinFloats);
+    constexpr int kPartFloats = JOINS ? NV * kWave * VW : 1;
+    __shared__ alignas(16) float open[JOINS ? kWavesPerBlock : 1][kPartFloats];         // what a piece has of the row that it leaves open
+    __shared__ alignas(16) float first[JOINS ? kWavesPerBlock : 1][kPartFloats];        // and of the first row that ends in it
+    __shared__ alignas(16) int32_t open_row[kWavesPerBlock];
     const int lane = threadIdx.x & (kWave - 1), wave = uniform_i32((int32_t)(threadIdx.x >> 6));
     const int32_t item = uniform_i32((int32_t)(blockIdx.x * kWavesPerBlock) + wave);
     if (!JOINS && item >= a.n_items) return;
@@ -201,12 +204,10 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
         for (int v = 0; v < NV; ++v)
             if (v < NV - 1 || last_ok) store_vec_streaming<VW>(o + (v * kWave + lane) * VW, sum[v]);
     };
-    auto to_lds = [&](float (&to)[JOINS ? VW * NV : 1][kWave]) {
+    auto to_lds = [&](float *to) {
         if constexpr (JOINS)
 #pragma unroll
-            for (int v = 0; v < NV; ++v)
-#pragma unroll
-                for (int k = 0; k < VW; ++k) to[v * VW + k][lane] = acc[v][k];
+            for (int v = 0; v < NV; ++v) store_vec<VW>(to + (v * kWave + lane) * VW, acc[v]);
     };
     auto flush_row = [&]() {
         whole_sum();
@@ -353,24 +354,33 @@ __global__ __launch_bounds__(kBlock) void spmm_merge_kernel(const SpmmArgs a)
         if (left != kNoRow) to_lds(open[wave]);
         if (lane == 0) open_row[wave] = left;
         __syncthreads();
+        const int4 rows = *reinterpret_cast<const int4 *>(open_row);
+        const int32_t left_open[kWavesPerBlock] = {uniform_i32(rows.x), uniform_i32(rows.y), uniform_i32(rows.z), uniform_i32(rows.w)};
+        static_assert(kWavesPerBlock == 4, "open_row is read at once");
+        auto add = [&](const float *part) {
+            float x[NV][VW];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) load_vec<VW>(part + (v * kWave + lane) * VW, x[v]);
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int k = 0; k < VW; ++k) acc[v][k] += x[v][k];
+        };
         // acc = the parts of row r that the waves before `end` leave open, in order
         auto add_open = [&](int32_t r, int end) {
             int begin = end;
-            while (begin > 0 && uniform_i32(open_row[begin - 1]) == r) --begin;
+#pragma unroll
+            for (int w = kWavesPerBlock - 1; w >= 0; --w)
+                if (begin == w + 1 && left_open[w] == r) begin = w;
 #pragma unroll
             for (int v = 0; v < NV; ++v)
 #pragma unroll
-                for (int k = 0; k < VW; ++k) {
-                    acc[v][k] = 0.0f;
-                    for (int w = begin; w < end; ++w) acc[v][k] += open[w][v * VW + k][lane];
-                }
+                for (int k = 0; k < VW; ++k) acc[v][k] = 0.0f;
+            for (int w = begin; w < end; ++w) add(open[w]);
         };
         if (wave > 0 && i1 > i0) {
             add_open((int32_t)i0, wave);
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-#pragma unroll
-                for (int k = 0; k < VW; ++k) acc[v][k] += first[wave][v * VW + k][lane];
+            add(first[wave]);
             store_row(i0, acc);
         }
         if (wave == kWavesPerBlock - 1) {                   // the path goes on in the next workgroup
@@ -485,35 +495,45 @@ int32_t longer_pieces(int64_t total, int32_t dim, int32_t n_items)
 }
 
 template <int VW, int NV>
-hipError_t launch_merge(const SpmmArgs &a, bool chains, hipStream_t st)
+hipError_t launch_merge(const SpmmArgs &a, bool chains, bool joins, hipStream_t st)
 {
     constexpr int U = NV >= 4 ? 4 : (NV >= 2 ? 8 : 16);
     constexpr bool kMay = (NV - 1) * kWave * VW < kNarrow;      // some row with so many vectors is narrow
-    auto kernel = a.p.slot_of_row ? spmm_merge_kernel<VW, NV, U, true, false> : spmm_merge_kernel<VW, NV, U, false, false>;
+    auto kernel_of = [&](auto with_chains, auto with_joins) {
+        constexpr bool kChains = decltype(with_chains)::value, kJoins = decltype(with_joins)::value;
+        return a.p.slot_of_row ? spmm_merge_kernel<VW, NV, U, true, kChains, kJoins> : spmm_merge_kernel<VW, NV, U, false, kChains, kJoins>;
+    };
+    joins = joins && VW * NV <= kJoinFloats;
+    auto kernel = kernel_of(std::false_type(), std::false_type());
     if constexpr (kMay)
-        if (chains) kernel = a.p.slot_of_row ? spmm_merge_kernel<VW, NV, U, true, true> : spmm_merge_kernel<VW, NV, U, false, true>;
+        if (chains) kernel = kernel_of(std::true_type(), std::false_type());
+    if constexpr (VW * NV <= kJoinFloats) {
+        if (joins) kernel = kernel_of(std::false_type(), std::true_type());
+        if constexpr (kMay)
+            if (joins && chains) kernel = kernel_of(std::true_type(), std::true_type());
+    }
     const dim3 grid((unsigned)((a.n_items + kWavesPerBlock - 1) / kWavesPerBlock));
     hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, st, a);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     SpmmArgs carries = a;
-    if (VW * NV <= kJoinFloats) carries.n_items = (int32_t)grid.x;      // one of a workgroup
+    if (joins) carries.n_items = (int32_t)grid.x;               // one of a workgroup
     hipLaunchKernelGGL((spmm_carry_kernel<VW, NV>), dim3((carries.n_items + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock), 0, st, carries);
     return hipGetLastError();
 }
 
 template <int VW>
-hipError_t launch_merge_nv(const SpmmArgs &a, int nv, bool chains, hipStream_t st)
+hipError_t launch_merge_nv(const SpmmArgs &a, int nv, bool chains, bool joins, hipStream_t st)
 {
     switch (nv) {
-        case 1: return launch_merge<VW, 1>(a, chains, st);
-        case 2: return launch_merge<VW, 2>(a, chains, st);
-        case 3: return launch_merge<VW, 3>(a, chains, st);
-        case 4: return launch_merge<VW, 4>(a, chains, st);
-        case 5: return launch_merge<VW, 5>(a, chains, st);
-        case 6: return launch_merge<VW, 6>(a, chains, st);
-        case 7: return launch_merge<VW, 7>(a, chains, st);
-        case 8: return launch_merge<VW, 8>(a, chains, st);
+        case 1: return launch_merge<VW, 1>(a, chains, joins, st);
+        case 2: return launch_merge<VW, 2>(a, chains, joins, st);
+        case 3: return launch_merge<VW, 3>(a, chains, joins, st);
+        case 4: return launch_merge<VW, 4>(a, chains, joins, st);
+        case 5: return launch_merge<VW, 5>(a, chains, joins, st);
+        case 6: return launch_merge<VW, 6>(a, chains, joins, st);
+        case 7: return launch_merge<VW, 7>(a, chains, joins, st);
+        case 8: return launch_merge<VW, 8>(a, chains, joins, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -653,9 +673,9 @@ int adaqp::spmm_rows(const int64_t *rowptr_dev, const int32_t *col_dev, const fl
                               : (vw == 2 ? launch_carry_nv<2>(a, nv, st) : launch_carry_nv<1>(a, nv, st));
         } else {
             if (!whole_lines) a.n_items = longer_pieces(n_rows + nnz_range, dim, g.n_items);
-            const bool chains = a.n_items < g.n_items;
-            err = vw == 4 ? launch_merge_nv<4>(a, nv, chains, st)
-                          : (vw == 2 ? launch_merge_nv<2>(a, nv, chains, st) : launch_merge_nv<1>(a, nv, chains, st));
+            const bool chains = a.n_items < g.n_items, joins = merge_joins(n_rows, nnz_range, a.n_items, dim);
+            err = vw == 4 ? launch_merge_nv<4>(a, nv, chains, joins, st)
+                          : (vw == 2 ? launch_merge_nv<2>(a, nv, chains, joins, st) : launch_merge_nv<1>(a, nv, chains, joins, st));
         }
         ADAQP_HIP_TRY(err);
     }

@@ -89,6 +89,15 @@ constexpr SlicedCut sliced_cut(int64_t n_rows, int64_t nnz, int64_t n_cols, int3
     return {1, 4, (halves ? 2 : 1) * kBlocks / fours};
 }
 
+// Whether workgroups of the merge path add up the parts that their pieces have of a row.  That saves three of four carries and shortens the chain of
+// a long row's, but the rows that begin a piece are stored a barrier and three LDS reads later, which launches of little else show.  A carry
+// per piece / joined, 924 calls of two degree laws: rows of 10 and more entries 1.0-1.35 (mostly 1.02-1.25); of 1 to 4 entries, up to 5 000 rows
+// 0.88-0.98, 150 000 rows of 301 columns 1.02-1.09, of 33 columns 1.0; of 6 entries 0.96 (log-normal degrees) and 1.08 (Zipf).
+constexpr bool merge_joins(int64_t n_rows, int64_t nnz, int64_t n_items, int32_t dim)
+{
+    return nnz >= 6 * n_rows || n_items * dim >= 300000;
+}
+
 // Which workgroup takes which slice and share.  Tasks in slice-major order, n_blocks of each slice; consecutive workgroups land
 // on consecutive XCDs, and an XCD takes a run of tasks of an eighth of the whole weight.  The last slice may be narrower than
 // the others; walking the entries costs it as much as them, so a task weighs its lines and that walk.

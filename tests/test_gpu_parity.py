@@ -565,6 +565,28 @@ def test_spmm_joined_pieces(oracle, dim, ld):
         assert np.array_equal(once.view(np.uint32), _gpu_spmm(rowptr, col, val, rb, re, H, dim, ldo=ld).view(np.uint32))
 
 
+@pytest.mark.parametrize("dim,ld,n_rows,joined", [(33, 33, 2_000, False), (301, 301, 2_000, False), (300, 320, 2_000, False), (65, 65, 36_900, False),
+                                                  (301, 301, 10_000, True), (512, 512, 6_000, True)])
+def test_spmm_merge_path_of_short_rows(oracle, dim, ld, n_rows, joined):
+    """Rows of two or three entries along the merge path: a carry per piece in small calls, joined pieces in larger ones; a row over several
+    workgroups among them, the same bits from packed rows and in a second call."""
+    _say(f"spmm short rows dim={dim} ld={ld} rows={n_rows}")
+    rng = np.random.default_rng(8100 + dim + n_rows)
+    n_cols = 3_000
+    degs = rng.integers(0, 6, size=n_rows)
+    degs[5:9] = [0, 700, 33, 64]
+    rowptr, col, val = _random_graph(rng, n_rows, n_cols, degs)
+    items = (n_rows + len(col) + 31) // 32
+    assert len(col) < 6 * n_rows and (items * dim >= 300_000) == joined and len(col) < 100_000
+    halo, bits, off, packed, params, H_plain, H_ref = _packed_case(oracle, rng, n_cols, 1_000, dim, ld, seed=6)
+    H = np.full((n_cols, ld), np.nan, dtype=np.float32)
+    H[:, :dim] = H_ref
+    once = _check_spmm(oracle, rowptr, col, val, 0, n_rows, H, dim, ldo=ld)
+    assert np.array_equal(once.view(np.uint32), _gpu_spmm(rowptr, col, val, 0, n_rows, H, dim, ldo=ld).view(np.uint32))
+    fused = _gpu_spmm_packed(rowptr, col, val, 0, n_rows, H_plain, dim, B.adaqp_plan_slot_of_row(n_cols, halo), packed, params, bits, off, ld)
+    assert np.array_equal(once.view(np.uint32), fused.view(np.uint32))
+
+
 @pytest.mark.parametrize("dim,ldh", [(128, 128), (602, 608), (602, 602), (300, 300), (7, 7), (1, 1), (66, 66),
                                      (130, 132), (250, 256), (2049, 2080), (2304, 2304), (4100, 4100), (515, 515)])
 def test_spmm_packed_rows(oracle, dim, ldh):
