@@ -582,16 +582,22 @@ int32_t packed_lines(const adaqp_spmm_pieces *p, const PieceArgs &a, int64_t lin
 // LDS that keeps waves away.  Lines that are asked for wait in the order of the asking in the L1, which has room for 256; where some of them miss
 // the L2 more waves only wait longer and ask for more than the L2 holds.  Segments: 16 waves (see above).  Rows of about 40 entries and
 // more: 12 (16.3 M entries, 376 000 rows, 256 columns, the step 875 -> 858 us; 4 M, 50 000 rows, 128 columns 110.7 -> 107.6; 15.3 M, 223 000
-// rows, 320 columns 935 -> 899), but all that fit where rows are shorter (with 12, 17 entries 0.94, 3 entries 0.93), where there are
-// pieces for a turn or two only (6 144, two lines 0.94-0.97; four lines 0.97 with 330 entries each, 1.02 with 600) and for one line per
-// slice (0.83).  Packed rows, whose workgroups have 52 KB: 8 instead of 12 where slices have three lines or more and there are
-// 9 000 waves (28 000 rows, 7.5 M entries, 387 columns 635 -> 565 us; 70 000, 7.7 M, 96 columns 280 -> 250; 130 000, 17.9 M, 314 columns 1 735 ->
-// 1 617; with fewer waves 0.81 to 1.02, with one or two lines 0.84 to 0.99).
+// rows, 320 columns 935 -> 899), but all that fit where rows are shorter, where there are pieces for a turn or two only and for one line per
+// slice (0.83).  81 steps of 6 to 130 entries per row, 64 to 600 columns, slices of two and four lines, with 16 and with 12 waves: where the rule
+// takes 12 they are 0.999 to 1.037 times as fast, elsewhere 0.91 to 1.04 (above 1.015 in four).
+//
+// Packed rows, whose workgroups have 52 KB: 8 instead of 12 in slices of four lines with 9 000 waves and 2.2 M entries, or with three
+// lines and 18 000 waves (28 000 rows, 7.5 M entries, 387 columns 635 -> 565 us; 130 000, 17.9 M, 314 columns 1 735 -> 1 617).  169 steps of
+// 8 to 150 entries per row, 64 to 600 columns: where the rule takes 8 waves 0.98 to 1.045, 1.016 on average; with four lines and fewer entries
+// 0.94 to 1.03 (0.987), fewer waves 0.89 to 1.04 (0.976), with three lines and fewer waves 0.80 to 1.06 (0.957), with two lines 0.87 to 0.98.
 unsigned idle_lds(const adaqp_spmm_pieces *p, const PieceArgs &a, int32_t per_slice, bool packed)
 {
     if (p->entries != kEntries || per_slice == 1) return 0;
     const int64_t waves = (int64_t)a.n_pieces * ((a.lines + per_slice - 1) / per_slice);
-    if (packed) return per_slice == 4 && a.lines >= 3 && waves >= 9000 ? kIdleLdsPacked : 0;
+    if (packed) {
+        const bool many = a.lines == 3 ? waves >= 18000 : a.lines > 3 && waves >= 9000 && a.n_walked >= 2200000;
+        return per_slice == 4 && many ? kIdleLdsPacked : 0;
+    }
     const bool turns = waves >= 9000 || (per_slice == 4 && a.n_walked >= 550 * (int64_t)a.n_pieces);
     return kIdleLds[a.of_rows && turns && a.n_walked >= 40 * (int64_t)a.n_seg];
 }

@@ -1661,6 +1661,23 @@ def test_layer_step_in_planned_pieces_of_many_waves(monkeypatch, dim):
         assert torch.equal(L.out.view(torch.int32), want.view(torch.int32))
 
 
+def test_layer_step_in_planned_pieces_of_many_waves_and_entries(monkeypatch):
+    """Enough waves and entries for the launch of packed rows that keeps a third of the waves away, in slices of four lines: the bits of the step
+    that reads what was received from feat."""
+    _say("layer step in many pieces of many entries")
+    monkeypatch.setattr(B, "adaqp_spmm_pieces_rule", lambda *args, **options: (1, -np.inf))
+    p, want = make_partition(replace(CONFIGS["c0"], n_local=20_000, n_halo=3_000, n_send=3_000, mean_degree=200.0, dim=650)), None
+    assert p.nnz >= 2_200_000
+    for fused in (False, True):
+        L = LayerStep(p, DEV, seed=5, tiled=False, fused_receive=fused)
+        c = L.pieces_both.c
+        assert c.entries == 768 and c.n_pieces * 6 >= 9_000 and c.lines_per_slice == 1
+        L.run(B.CHAIN)
+        L.synchronize()
+        want = L.out.clone() if want is None else want
+        assert torch.equal(L.out.view(torch.int32), want.view(torch.int32))
+
+
 @pytest.mark.parametrize("rows,mean,dim,shape", [(2_000, 10, 128, (8, 256)), (2_000, 10, 40, (8, 256)), (24_000, 18, 66, (4, 256)),
                                                  (24_000, 60, 150, (4, 768)), (24_000, 100, 40, (4, 768))])
 @pytest.mark.parametrize("kind", ["forward", "fused", "backward"])
