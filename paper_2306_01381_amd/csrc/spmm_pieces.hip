@@ -60,17 +60,27 @@ __device__ __forceinline__ void store_row(const PieceArgs &a, int32_t dest, int3
     store_row<VPL>(a, part ? a.partial + (int64_t)dest * a.ldp : a.out + (int64_t)(-1 - dest) * a.ldo, known, first_line, lane, sum);
 }
 
-// off of an entry that may be packed: rotated by two, so that the width of a packed row is at the top and the row's 32-bit word in the others.
-__device__ __forceinline__ uint32_t packed_width(uint32_t off) { return off >> 30; }
+// An entry in LDS.  Where rows may be packed: its place rotated by two, so that the width of a packed row is at the top and the row's 32-bit word in
+// the others; not what Entry<true> holds, which keeps the width in the lowest bits.
+struct alignas(16) RotatedEntry { uint32_t place; float val; float z, s; };
+static_assert(!std::is_convertible_v<Entry<true>, RotatedEntry> && !std::is_convertible_v<RotatedEntry, Entry<true>>,
+              "unpack_lines and unpack_codes read places of their own kind only");
+template <bool PACKED> using PieceEntry = std::conditional_t<PACKED, RotatedEntry, Entry<false>>;
+
+__device__ __forceinline__ uint32_t packed_width(const RotatedEntry &en) { return en.place >> 30; }
+
+// Byte offset of the row in H.
+__device__ __forceinline__ uint32_t row_offset(const RotatedEntry &en) { return en.place << 2; }
+__device__ __forceinline__ uint32_t row_offset(const Entry<false> &en) { return en.off; }
 
 // unpack_codes of a lane's columns in VPL lines: a line's codes fill whole words at each width, so they begin at the same bit in all of
 // them, and v_bfe_u32 takes that modulo 32 by itself.  Where most rows come out of the L2 the instructions count: with these places, one shift
 // per entry and the words asked for before the rows, 24 000 rows of 17 entries, 66 columns, packed, the step 30.1 -> 28.4 us; 7 700 of 156, 316
 // columns 131 -> 109; 17 500 of 75, 96 columns 66 -> 54; 150 such steps 1.055 times as fast.
 template <int VPL>
-__device__ __forceinline__ void unpack_lines(const Entry<true> &en, const uint32_t (&words)[VPL], uint32_t col, float4_t (&x)[VPL])
+__device__ __forceinline__ void unpack_lines(const RotatedEntry &en, const uint32_t (&words)[VPL], uint32_t col, float4_t (&x)[VPL])
 {
-    const uint32_t w = packed_width(en.off);
+    const uint32_t w = packed_width(en);
     const uint32_t b = 1u << w, at = col << w;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
@@ -88,7 +98,7 @@ __device__ __forceinline__ void unpack_lines(const Entry<true> &en, const uint32
 // device 38.7).
 template <int LOADS>
 __device__ __forceinline__ void stage_packed(int4_t (&st_col)[LOADS], const float4_t (&st_val)[LOADS], int32_t n_ent, uint32_t n_cols,
-                                             uint32_t pitch, const PackedRows &p, int lane, Entry<true> *stage)
+                                             uint32_t pitch, const PackedRows &p, int lane, RotatedEntry *stage)
 {
     auto valid = [&](int k, int q) ADAQP_INLINE { return (k * kWave + lane) * 4 + q < n_ent && (uint32_t)st_col[k][q] < n_cols; };
     uint2 at[LOADS][4];
@@ -109,8 +119,8 @@ __device__ __forceinline__ void stage_packed(int4_t (&st_col)[LOADS], const floa
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const uint32_t row = valid(k, q) ? (uint32_t)st_col[k][q] * pitch : kOutside;
-            stage[(k * kWave + lane) * 4 + q] = Entry<true>{__builtin_rotateright32(packed[q] ? at[k][q].x : row, 2),
-                                                            valid(k, q) ? st_val[k][q] : 0.0f, zs[q].x, zs[q].y};
+            stage[(k * kWave + lane) * 4 + q] = RotatedEntry{__builtin_rotateright32(packed[q] ? at[k][q].x : row, 2),
+                                                             valid(k, q) ? st_val[k][q] : 0.0f, zs[q].x, zs[q].y};
         }
     }
 }
@@ -204,7 +214,7 @@ __device__ __forceinline__ int32_t walk_moved(const PieceArgs &a, const int32_t 
 // waves' of the workgroup.  Returns where the sum of such a segment goes that ends in this piece, kNowhere, or
 // kMoved before anything is written (ROWS).
 template <int VPL, int AHEAD, bool PACKED, bool ROWS, bool JOINS, int ENTRIES>
-__device__ __forceinline__ int32_t walk_piece(const PieceArgs &a, const int32_t first_line, const int32_t item, Entry<PACKED> *stage, Joined *joined)
+__device__ __forceinline__ int32_t walk_piece(const PieceArgs &a, const int32_t first_line, const int32_t item, PieceEntry<PACKED> *stage, Joined *joined)
 {
     constexpr int kRing = AHEAD * kStep;                    // entries of a turn of the ring
     constexpr int kParts = ENTRIES / kPart;
@@ -292,19 +302,20 @@ __device__ __forceinline__ int32_t walk_piece(const PieceArgs &a, const int32_t 
     // the ring: AHEAD steps whose lines are on their way
     float4_t h[AHEAD][VPL];
     uint32_t words[AHEAD][VPL];                             // of a packed row: the word that holds the lane's four codes
-    Entry<PACKED> in_flight[AHEAD];
+    PieceEntry<PACKED> in_flight[AHEAD];
     const uint32_t lane_off = gl * 16;
     const uint32_t packed_col = (uint32_t)(a.p.col0 + first_line * kLine + gl * 4);     // of the lane's codes in the first line
     const uint32_t last_col = min(packed_col + (VPL - 1) * kLine, (uint32_t)a.p.full_dim - 1);
-    auto fetch = [&](auto tag, const Entry<PACKED> &en) ADAQP_INLINE {
+    auto fetch = [&](auto tag, const PieceEntry<PACKED> &en) ADAQP_INLINE {
         constexpr int U = decltype(tag)::value;
         in_flight[U] = en;
-        const uint32_t width = PACKED ? packed_width(en.off) : 0u;
-        const uint32_t off = width != 0 ? kOutside : (PACKED ? en.off << 2 : en.off) + lane_off;
+        uint32_t off = row_offset(en) + lane_off;
         if constexpr (PACKED) {
+            const uint32_t width = packed_width(en);
+            off = width != 0 ? kOutside : off;
             // The word of the lane's four codes, and as far behind it the one of each line.
-            const uint32_t first = width != 0 ? (en.off + (packed_col << width >> 5)) << 2 : kOutside;
-            const uint32_t last = width != 0 ? (en.off + (last_col << width >> 5)) << 2 : kOutside;
+            const uint32_t first = width != 0 ? (en.place + (packed_col << width >> 5)) << 2 : kOutside;
+            const uint32_t last = width != 0 ? (en.place + (last_col << width >> 5)) << 2 : kOutside;
 #pragma unroll
             for (int v = 0; v < VPL; ++v) {
                 const uint32_t at = v + 1 < VPL ? first + ((uint32_t)v * (kLine / 8) << width) : last;
@@ -363,7 +374,7 @@ __device__ __forceinline__ int32_t walk_piece(const PieceArgs &a, const int32_t 
 #pragma unroll
             for (int v = 0; v < VPL; ++v) before[v] = sum[v];
         }
-        Entry<PACKED> en[AHEAD];
+        PieceEntry<PACKED> en[AHEAD];
         if constexpr (kGoesOn)
 #pragma unroll
             for (int u = 0; u < AHEAD; ++u) en[u] = stage[(t + 1) * kRing + u * kStep + grp];
@@ -426,7 +437,7 @@ template <int VPL, int AHEAD, bool PACKED, bool ROWS, int WAVES, int ENTRIES>
 __global__ __launch_bounds__(WAVES * kWave, PACKED && ENTRIES > kFewEntries ? 2 : 4) void spmm_pieces_kernel(const PieceArgs a)
 {
     constexpr bool kJoins = WAVES > kWavesPerBlock;
-    __shared__ alignas(16) Entry<PACKED> stages[WAVES][ENTRIES + kWave];
+    __shared__ alignas(16) PieceEntry<PACKED> stages[WAVES][ENTRIES + kWave];
     __shared__ Joined joined[kJoins ? WAVES : 1];
     if constexpr (PACKED) if (blockIdx.x < a.copy_blocks) return copy_blocks(a.copies, blockIdx.x, WAVES * kWave);
     const uint32_t block = PACKED ? blockIdx.x - a.copy_blocks : blockIdx.x;
