@@ -3,6 +3,7 @@
 Bars: packed bytes, (Z, S) and de-quantised fp32 values bit-exact; aggregation within
 1e-5 * sum|terms| per output element (the fp64 oracle also returns that sum).
 """
+import ctypes
 import sys
 from dataclasses import replace
 
@@ -2052,6 +2053,56 @@ def test_layer_step_chain_with_send_buffers_in_memory_that_is_used_again(kind, w
         left.append([t.contiguous().view(torch.int32).clone() for t in (L.out, L.feat, L.recv_params, L.beta)] + [L.recv_packed.clone()])
     for a, b in zip(*left):
         assert torch.equal(a, b)
+
+
+def _launches(L, d):
+    """Kernels of one step, counted in a capture that is not replayed."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    graph, nodes = ctypes.c_void_p(), ctypes.c_size_t(0)
+    stream = ctypes.c_void_p(L.stream_msg.cuda_stream)
+    assert hip.hipStreamBeginCapture(stream, ctypes.c_int(2)) == 0
+    B.adaqp_layer_step(d)
+    assert hip.hipStreamEndCapture(stream, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(nodes)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return nodes.value
+
+
+@pytest.mark.parametrize("kind", ["forward", "fused", "backward"])
+def test_layer_step_chain_has_no_launch_for_the_copy(kind):
+    """One launch fewer than where the send buffers lie in memory that the receive writes, whose copy is a launch of its own."""
+    _say(f"launches of a chain, {kind}")
+    p = make_partition(replace(CONFIGS["c0"], n_local=6_000, n_halo=900, n_send=900, mean_degree=60.0, dim=66) if kind != "backward" else
+                       replace(CONFIGS["c4"], n_local=2000, n_halo=1800, n_send=1500, mean_degree=9.0, dim=128))
+    L = LayerStep(p, DEV, seed=5, fused_receive=kind == "fused")
+    d = L.desc(B.CHAIN)
+    assert d.pieces_both.n_pieces > 0 and bool(d.slot_of_row_dev) == (kind == "fused")
+    L.run(B.CHAIN)
+    L.synchronize()
+    beside = _launches(L, d)
+    d.packed_dev = L.out.data_ptr()
+    assert _launches(L, d) == beside + 1
+    sums = int(d.pieces_both.n_sums > 0)
+    assert beside == (2 if kind == "fused" else 3) + sums
+
+
+def test_layer_step_packed_rows_in_slices_of_two_lines(oracle, monkeypatch):
+    """Seven lines, a plan of two per slice, long pieces of rows shorter than 100 entries: packed rows are walked two lines at a time, the last
+    slice one.  Against the oracle, and the bits of the step that reads what was received from feat."""
+    _say("layer step, packed rows in slices of two lines")
+    monkeypatch.setattr(B, "adaqp_spmm_pieces_rule", lambda *args, **options: (2, -np.inf))
+    p, want = make_partition(replace(CONFIGS["c0"], n_local=24_000, n_halo=6_000, n_send=4_800, mean_degree=40.0, dim=220)), None
+    _, _, _, out64, mag = _oracle_layer(oracle, p, 5)
+    for fused in (True, False):
+        L = LayerStep(p, DEV, seed=5, tiled=False, fused_receive=fused)
+        c = L.pieces_both.c
+        assert (c.entries, c.lines_per_slice) == (768, 2) and p.nnz < 100 * c.n_seg
+        L.run(B.CHAIN)
+        L.synchronize()
+        got = L.out.cpu().numpy()
+        assert np.all(np.abs(got.astype(np.float64) - out64) <= SPMM_RTOL * mag + 1e-30)
+        want = got if want is None else want
+        assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
 def test_mean_aggregator_layer_step(oracle):
