@@ -595,6 +595,11 @@ typedef enum adaqp_schedule {
                            table, the overlap range ends where the dependent one begins and one of the two
                            workspaces holds adaqp_spmm_workspace_bytes of both ranges together, they are
                            aggregated in one launch.  Its sums may be cut differently (other rounding).
+                           The loop-back copy is part of the launch that receives, which reads the send buffers:
+                           possible because the stand-in exchange is a copy on one GPU, and the one thing in
+                           a step that an exchange would have to give back (2 to 2.5 us of small steps).  It is
+                           a launch of its own, which the receive follows, where the send buffers lie in
+                           feat, out or a workspace.
                            SERIAL and CHAIN use neither stream_agg nor the events */
 } adaqp_schedule;
 
@@ -633,7 +638,8 @@ typedef struct adaqp_layer_desc {
     const int32_t *recv_order_dev;  /* forward only, optional: adaqp_plan_recv_order of halo_idx */
     const int32_t *slot_of_row_dev; /* forward only, optional: adaqp_plan_slot_of_row of halo_idx.  If given, the
                                        received rows are NOT de-quantised into feat; the dependent aggregation
-                                       reads them from the receive buffer (adaqp_spmm_csr_packed) */
+                                       reads them from the receive buffer (adaqp_spmm_csr_packed; ADAQP_CHAIN: from
+                                       what is copied there) */
     const int32_t *tile_off_overlap_dev;    /* optional: adaqp_plan_spmm_tiles of the overlap / dependent row range. */
     const int32_t *tile_off_dependent_dev;  /* If given, that range is aggregated by adaqp_spmm_csr_tiled (line-padded
                                                layout required; the range's workspace must then hold
@@ -667,7 +673,7 @@ typedef struct adaqp_layer_desc {
     uint8_t *packed_dev;   float *params_dev;           /* send buffers */
     const float *alpha_sq_dev; float *beta_dev;         /* optional trace (adaqp_quantize_pack_trace); both or none */
     uint8_t *recv_packed_dev; float *recv_params_dev;   /* receive buffers; the loop-back copy stands in for the exchange */
-                        /* (ADAQP_CHAIN: copied by the launch that receives, which reads what it copies) */
+                        /* (ADAQP_CHAIN: written by the launch that receives, read by nothing in the step) */
     int64_t packed_bytes;
     /* scratch and streams */
     void *workspace_overlap_dev;   int64_t workspace_overlap_bytes;

@@ -374,8 +374,9 @@ bool send_buffers_apart(const adaqp_layer_desc *d, const void *b, int64_t b_byte
 
 // CHAIN has nothing to overlap the transfer with, and the copy that stands in for it is a launch of 2.5 to 5 us that leaves the GPU part
 // empty.  There the launch that receives takes the bytes from where the copy takes them, and copies them beside; the table of received
-// rows is then filled in the quantisation's launch.  Whole steps: 2 000 rows, 128 columns 19.4 -> 15.4 us (the host's time for its
-// launches), 24 000 rows, 66 columns, packed 32.7 -> 30.3, 179 000 rows, 300 columns 361 -> 355, 30 000 nodes backward 106 -> 104.
+// rows is then filled in the quantisation's launch.  An exchange with another GPU would have to end before its receive begins: what this saves
+// it saves in the loop-back only.  Whole steps, launch by launch in turn: 2 000 rows, 128 columns 15.1 -> 13.0 us, 24 000 rows, 66 columns, packed
+// 30.1 -> 27.6, 306 000 rows, 256 columns 754.6 -> 751.6, 179 000 rows, 300 columns 345.6 -> 341.0, 30 000 nodes backward 104.6 -> 102.2.
 // Buffers that the receiving calls refuse go the other way, and are refused there.  So do send buffers in memory that the launch writes, which
 // a caller may use again once the messages are on their way: rows of feat that are received, out, a workspace.
 bool receives_beside(const adaqp_layer_desc *d)

@@ -136,7 +136,7 @@ struct Joined {
 // to where it ends if it was planned to end inside.  The pieces of a row so have each of its entries once, wherever it lies.  Returns
 // what walk_piece does.  No limit to how long a row can have become: one line at a time, no staging, few registers.  What bounds it is the
 // piece that has become the longest (lengths of the rows permuted, the whole step as planned, so, and cut on the device: 2 000 rows, 128
-// columns 15, 36, 23 us; 24 000 rows, 66 columns, packed 34, 560, 48; 376 000 rows, 256 columns 0.88, 5.4, 0.86 ms).
+// columns 13, 35, 19 us; 24 000 rows, 66 columns, packed 28, 720, 46; 376 000 rows, 256 columns 0.84, 5.0, 0.86 ms, with 16 waves per CU 4.1).
 template <bool PACKED, bool JOINS>
 __device__ __forceinline__ int32_t walk_moved(const PieceArgs &a, const int32_t first_line, const int live, const int32_t item, Joined *joined)
 {
@@ -582,25 +582,27 @@ PieceKernel kernel_of(const adaqp_spmm_pieces *p, int32_t lines_per_slice)
 // Lines per slice where rows may be packed.  Their codes share lines, and each slice looks up the places again: four, but two where the plan
 // says two and rows are shorter than 100 entries (four, two: 10 000 rows of 56 entries, 414 columns 88.7, 80.7 us; 15 000 of 47, 160 columns 56.6,
 // 53.3; 27 000 of 19, 336 columns 90.7, 85.6; 11 000 of 67, 336 columns 97.9, 100.2; but 394 entries, 441 columns 121, 130; 298 entries, 208 columns
-// 191, 197) and whole slices of four are not waves enough (157 000 rows, 240 columns, 4 600 waves: 175, 186).  In small pieces 0.94 to 1.03 with two;
-// where the plan says one 0.89 to 1.12, four 0.89 to 1.04.  The same bits either way.
+// 191, 197) and whole slices of four are not waves enough (157 000 rows, 240 columns, 4 600 waves: 175, 186).  80 steps of 9 to 150 entries per row,
+// 160 to 600 columns, whose plan says two: where the rule takes two 0.94 to 1.28 times as fast, 1.07 on average, elsewhere 0.90 to 1.22.  In small
+// pieces 0.94 to 1.03 with two; where the plan says one 0.89 to 1.12, four 0.89 to 1.04.  The same bits either way.
 int32_t packed_lines(const adaqp_spmm_pieces *p, const PieceArgs &a, int64_t lines)
 {
     const bool fills = lines % 4 == 0 && a.n_pieces * (lines / 4) >= kUnderWay;
     return p->lines_per_slice == 2 && p->entries == kEntries && lines > 4 && !fills && a.n_walked < 100 * (int64_t)a.n_seg ? 2 : 4;
 }
 
-// LDS that keeps waves away.  Lines that are asked for wait in the order of the asking in the L1, which has room for 256; where some of them miss
-// the L2 more waves only wait longer and ask for more than the L2 holds.  Segments: 16 waves (see above).  Rows of about 40 entries and
-// more: 12 (16.3 M entries, 376 000 rows, 256 columns, the step 875 -> 858 us; 4 M, 50 000 rows, 128 columns 110.7 -> 107.6; 15.3 M, 223 000
-// rows, 320 columns 935 -> 899), but all that fit where rows are shorter, where there are pieces for a turn or two only and for one line per
-// slice (0.83).  81 steps of 6 to 130 entries per row, 64 to 600 columns, slices of two and four lines, with 16 and with 12 waves: where the rule
-// takes 12 they are 0.999 to 1.037 times as fast, elsewhere 0.91 to 1.04 (above 1.015 in four).
+// LDS that keeps waves away.  Where the L1 returns data all the time already (94 % of it, 16.3 M entries, 376 000 rows, 256 columns, a fifth of the
+// lines from behind the L2) more waves only wait longer: with 12 instead of 16 they wait 0.42 of their time instead of 0.60, the misses stay the
+// same, and the L1 stands still for 0.314 of the time instead of 0.323 (800 -> 787 us).  Segments: 16 waves (see above).  Rows of about 40
+// entries and more: 12 (besides, 4 M, 50 000 rows, 128 columns 92.9 -> 92.3; 15.3 M, 223 000 rows, 320 columns, the step 935 -> 899), but all that
+// fit where rows are shorter, where there are pieces for a turn or two only and for one line per slice (0.83).  81 steps of 6 to 130 entries per
+// row, 64 to 600 columns, slices of two and four lines, with 16 and with 12 waves: where the rule takes 12 they are 0.999 to 1.037 times as fast,
+// elsewhere 0.91 to 1.04 (above 1.015 in four).
 //
-// Packed rows, whose workgroups have 52 KB: 8 instead of 12 in slices of four lines with 9 000 waves and 2.2 M entries, or with three
-// lines and 18 000 waves (28 000 rows, 7.5 M entries, 387 columns 635 -> 565 us; 130 000, 17.9 M, 314 columns 1 735 -> 1 617).  169 steps of
-// 8 to 150 entries per row, 64 to 600 columns: where the rule takes 8 waves 0.98 to 1.045, 1.016 on average; with four lines and fewer entries
-// 0.94 to 1.03 (0.987), fewer waves 0.89 to 1.04 (0.976), with three lines and fewer waves 0.80 to 1.06 (0.957), with two lines 0.87 to 0.98.
+// Packed rows, whose workgroups have 52 KB: 8 instead of 12 in slices of four lines with 9 000 waves and 2.2 M entries, or with three lines and
+// 18 000 waves.  169 steps of 8 to 150 entries per row, 64 to 600 columns: where the rule takes 8 waves 0.98 to 1.045 times as fast, 1.016 on
+// average; with four lines and fewer entries 0.94 to 1.03 (0.987), fewer waves 0.89 to 1.04 (0.976), with three lines and fewer waves 0.80 to
+// 1.06 (0.957), with two lines 0.87 to 0.98.
 unsigned idle_lds(const adaqp_spmm_pieces *p, const PieceArgs &a, int32_t per_slice, bool packed)
 {
     if (p->entries != kEntries || per_slice == 1) return 0;
